@@ -30,6 +30,42 @@ __device__ __forceinline__ void lds_dma(const void *g_uniform, uint32_t voff, co
                      : "=&s"(saved) : "s"(lds_addr), "v"(voff), "s"(g_uniform) : "memory");
 }
 
+// N loads of 16 bytes per lane like lds_dma<16>, all from one wavefront-uniform base, load i to lds_uniform + i * STEP
+// bytes: one assembly block, so that M0 is saved and restored once and merely stepped from load to load.
+template <int N, int STEP>
+__device__ __forceinline__ void lds_dma_n(const void *g_uniform, const uint32_t (&off)[N], const void *lds_uniform)
+{
+    static_assert(N == 1 || N == 2 || N == 4 || N == 8, "");
+    {   // (uniform by contract; said again so that it is kept in scalar registers)
+        const uint64_t p = (uint64_t)g_uniform;
+        g_uniform = reinterpret_cast<const void *>((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p) |
+                                                   (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) << 32);
+    }
+    const uint32_t lds_addr = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)lds_uniform;
+    uint32_t saved;
+#define LSS_FIRST "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %2\n\t"
+#define LSS_NEXT(v) "s_add_u32 m0, m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %" #v ", %2\n\t"
+#define LSS_LAST "s_mov_b32 m0, %0"
+    if constexpr (N == 1)
+        asm volatile(LSS_FIRST LSS_LAST : "=&s"(saved) : "s"(lds_addr), "s"(g_uniform), "i"(STEP), "v"(off[0]) : "memory", "scc");
+    else if constexpr (N == 2)
+        asm volatile(LSS_FIRST LSS_NEXT(5) LSS_LAST
+                     : "=&s"(saved) : "s"(lds_addr), "s"(g_uniform), "i"(STEP), "v"(off[0]), "v"(off[1]) : "memory", "scc");
+    else if constexpr (N == 4)
+        asm volatile(LSS_FIRST LSS_NEXT(5) LSS_NEXT(6) LSS_NEXT(7) LSS_LAST
+                     : "=&s"(saved) : "s"(lds_addr), "s"(g_uniform), "i"(STEP), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3])
+                     : "memory", "scc");
+    else
+        asm volatile(LSS_FIRST LSS_NEXT(5) LSS_NEXT(6) LSS_NEXT(7) LSS_NEXT(8) LSS_NEXT(9) LSS_NEXT(10) LSS_NEXT(11) LSS_LAST
+                     : "=&s"(saved)
+                     : "s"(lds_addr), "s"(g_uniform), "i"(STEP), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "v"(off[4]),
+                       "v"(off[5]), "v"(off[6]), "v"(off[7])
+                     : "memory", "scc");
+#undef LSS_FIRST
+#undef LSS_NEXT
+#undef LSS_LAST
+}
+
 // Chunk permutation of a row-major LDS tile with D bf16 columns (D / 8 chunks of 16 bytes per row): chunk c
 // of row r sits at chunk position c ^ tile_swizzle<D>(r).  The LDS has 64 banks of 4 bytes, i.e. 16
 // chunk-wide bank groups.  D = 64 (rows of 128 bytes, two rows per pass over the banks): r & 7 -- the 16
@@ -175,6 +211,13 @@ __device__ __forceinline__ const T *tile_ptr(const T *base, int tile, uint32_t t
 // Wait until every outstanding vector-memory load of this wave has returned, the direct
 // global -> LDS ones included (their data is then in LDS; a barrier publishes it to the other
 // wavefronts).
+// Wait until at most N of this wave's vector-memory operations are outstanding (they complete in order).
+template <int N>
+__device__ __forceinline__ void wait_vmem()
+{
+    static_assert(N >= 0 && N < 64, "");
+    asm volatile("s_waitcnt vmcnt(%0)" :: "i"(N) : "memory");       // (also keeps the compiler from moving stores past it)
+}
 __device__ __forceinline__ void wait_vmem_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0), others untouched
 
 // 4 floats -> 4 bf16 (round to nearest even), as one 8-byte value

@@ -5,15 +5,16 @@
 // dx_partial is what the segment sum (the reduce-scatter's arithmetic) then adds over segments.
 //
 // One kernel template computes C[m, n] = sum_k A[m, k] W'[k, n] for a short list of jobs.  A
-// workgroup of eight wavefronts owns a 256 (m) x 256 (n) tile of C, held transposed in the
-// accumulators (lane = row m of A, as the attention kernels hold one query per lane):
-// C^T += W'^T A^T, so the weights are the A operand of the matrix instruction and the activations
-// its B operand.  Each wavefront owns 128 (m) x 64 (n): 4 x 2 accumulator tiles, 8 matrix
-// instructions per 6 operand fragments; two wavefronts share a SIMD, so one's LDS reads and barrier
-// waits hide behind the other's matrix instructions.  The contraction runs in tiles of 64 through
-// two LDS slots (64 KB each), the next tile loaded global -> LDS directly while the current one is
-// multiplied; one barrier per tile.  The finished tile goes through LDS once more so that it is
-// written to memory as whole rows.
+// workgroup owns a TM x TN tile of C, held transposed in the accumulators (lane = row m of A, as the
+// attention kernels hold one query per lane): C^T += W'^T A^T, so the weights are the A operand of the
+// matrix instruction and the activations its B operand.  Each wavefront owns a WM x WN part.  The
+// contraction runs in tiles of 64 through a ring of STAGES LDS slots that are filled global -> LDS
+// directly, one barrier per tile.  The finished tile goes through LDS once more so that it is written to
+// memory as whole rows.  The tile is chosen per launch (launch_proj): 2048 x 512 -> 2048 took 17.0 us with
+// the 256 x 256 tile alone and takes 9.1, 2048 x 2048 -> 512 46.2 and now 9.4; at 16384 x 2048 -> 8192 the barrier ahead
+// of a tile's last step and the order of the tiles took the 256 x 256 tile from 526 to 466 us (1180 TFLOP/s; the
+// vendor's library 432).  What bounds it there is LDS traffic next to the matrix cores: 196 KB of operand
+// reads and 64 KB of tile writes per contraction tile are as many cycles as its matrix instructions.
 //   W_TR   weights stored [k][n] (forward: W as given).  Their fragments come from the LDS tile
 //          by transposing reads; otherwise the weights are stored [n][k] (backward: W as given
 //          IS W'^T) and are read plainly.
@@ -33,10 +34,23 @@ namespace lss {
 
 namespace {
 
-constexpr int PM = 256, PN = 256, PK = 64;      // workgroup tile, contraction tile
-constexpr int P_WAVES = 8, P_NT = 64 * P_WAVES;
-constexpr int P_ABYTES = PM * PK * 2, P_WBYTES = PN * PK * 2, P_SLOT = P_ABYTES + P_WBYTES;
-constexpr int P_LDS = 2 * P_SLOT;               // 128 KB: one workgroup per compute unit
+constexpr int PK = 64;                          // contraction tile
+constexpr int kLdsPerCu = 160 * 1024;
+
+// A workgroup's tile of C, its wavefronts' parts and its ring.  KG > 1: KG groups of wavefronts, each with a
+// ring of its own, take every KG-th contraction tile and add their results up (in group order) at the end.
+template <int TM_, int TN_, int WM_, int WN_, int STAGES_, int KG_ = 1>
+struct GemmShape {
+    static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, STAGES = STAGES_, KG = KG_;
+    static constexpr int MW = TM / WM, NW = TN / WN, GW = MW * NW;      // wavefronts of a group
+    static constexpr int WAVES = KG * GW, NT = 64 * WAVES, GT = 64 * GW;
+    static constexpr int MB = WM / 32, NB = WN / 32;            // accumulator blocks of a wavefront
+    static constexpr int ABYTES = TM * PK * 2, WBYTES = TN * PK * 2, SLOT = ABYTES + WBYTES, RING = STAGES * SLOT;
+    static constexpr int LDS = KG * RING;
+    static constexpr int PER_CU = kLdsPerCu / LDS;              // workgroups a compute unit holds at once
+    static constexpr int WAVES_PER_SIMD = PER_CU * WAVES / 4;   // what the register count has to allow
+    static_assert(STAGES >= 2 && LDS <= kLdsPerCu && (KG - 1) * GW * MB * NB * 4096 <= LDS, "");
+};
 
 struct ProjJob {
     const void *a0, *a1;        // A: [batches][rows][lda]; a1 serves contraction indices >= k_split (or is unused)
@@ -59,44 +73,46 @@ struct ProjArgs {
     int n_jobs, lda, ldc, skip_tail;
 };
 
-using ATile = DirectTile<PK, PM, P_WAVES>;      // activations [256 m][64 k]
-using WTile = DirectTile<PK, PN, P_WAVES>;      // weights [256 n][64 k]
-
-// Weights [64 k][256 n], read transposed.  Loaded directly like a DirectTile, but its 512-byte rows
-// all start at the same LDS bank, so the 16-byte chunk c of row r sits at chunk position
-// c ^ 4 (r % 4): the eight rows that one transposing read touches (64 bytes of each) then spread
-// evenly over the banks.
-struct WTileTr {
-    static constexpr int NI = PK * (PN / 8) / 64 / P_WAVES;     // load instructions per wavefront (2 rows each)
-    // chunks >= chunks_ok (columns past the matrix) re-read chunk chunks_ok - 1; chunks_ok is a multiple of 8;
-    // rows >= rows_ok re-read row rows_ok - 1
+// Operand tile [64 k][COLS], to be read transposed.  Loaded directly like a DirectTile.  Its rows start
+// at the same LDS bank (COLS >= 128) or alternate between two (COLS = 64), so the 16-byte chunk c of row
+// r sits at chunk position c ^ swizzle(r): the four consecutive rows of which one transposing read
+// takes 64 bytes each then spread evenly over the 64 banks.
+template <int COLS, int WAVES>
+struct TrTile {
+    static constexpr int CPR = COLS / 8;                        // 16-byte chunks per row
+    static constexpr int NI = PK * CPR / 64 / WAVES;            // load instructions per wavefront
+    static_assert(PK * CPR % (64 * WAVES) == 0 && NI >= 1, "");
+    static __device__ __forceinline__ int swizzle(int r) { return COLS >= 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1); }
+    static __device__ __forceinline__ int row_of(int i, int wave, int lane) { return ((i * WAVES + wave) * 64 + lane) / CPR; }
+    // chunks >= chunks_ok (columns past the matrix) re-read chunk chunks_ok - 1; rows >= rows_ok re-read row
+    // rows_ok - 1
     static __device__ __forceinline__ void offsets(uint32_t (&off)[NI], int ldw, int wave, int lane, int chunks_ok,
                                                    int rows_ok = PK)
     {
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-            const int row = (i * P_WAVES + wave) * 2 + lane / 32, pos = lane % 32;
-            const int chunk = min(pos ^ (4 * (row & 3)), chunks_ok - 1);
+            const int row = row_of(i, wave, lane), pos = lane % CPR;
+            const int chunk = min(pos ^ swizzle(row), chunks_ok - 1);
             off[i] = ((uint32_t)min(row, rows_ok - 1) * (uint32_t)ldw + (uint32_t)chunk * 8u) * 2u;
         }
     }
+    static __device__ __forceinline__ int chunk_offset(int r, int c) { return r * (COLS * 2) + ((c ^ swizzle(r)) * 16); }
     // Transposing reads (see load_frag_tr_sw for the instruction's lane mapping): within its group
     // of 16 lanes, lane s addresses row 8 hh + s / 4 and the 8-byte piece s % 4 of the 32-byte
     // column group nh of column block db (hh, nh: bits 1 and 0 of the group index).
     static __device__ __forceinline__ int lane_offset(int lane, int db)
     {
         const int grp = lane >> 4, hh = grp >> 1, nh = grp & 1, s = lane & 15;
-        const int row = 8 * hh + (s >> 2), chunk = 4 * db + 2 * nh + ((s & 3) >> 1);
-        return row * (PN * 2) + ((chunk ^ (4 * (row & 3))) * 16) + (s & 1) * 8;
+        return chunk_offset(8 * hh + (s >> 2), 4 * db + 2 * nh + ((s & 3) >> 1)) + (s & 1) * 8;
     }
     // A-operand fragment of the transposed tile for contraction step ks: operand row = column
     // (lane % 32) of block db, slot e = contraction index 16 ks + 8 hh + e -- the order in which a
-    // plain 16-byte read delivers the other operand.
+    // plain 16-byte read delivers the other operand.  (Rows 16 and 4 further down keep the permutation.)
     static __device__ __forceinline__ Frag<bf16_t> load_frag(const char *tile, int ks, int lane_off)
     {
-        const char *p = tile + ks * 16 * (PN * 2) + lane_off;
+        const char *p = tile + ks * 16 * (COLS * 2) + lane_off;
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * (PN * 2)));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * (COLS * 2)));
         const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
         Frag<bf16_t> f;
         f.v = __builtin_bit_cast(bf16x8, both);
@@ -104,83 +120,217 @@ struct WTileTr {
     }
 };
 
-template <bool A_ANY, bool W_TR, bool OUT_F32, int EPI>
-__global__ __launch_bounds__(P_NT, 1) void proj_gemm_kernel(ProjArgs args)
+// Operand fragments of one contraction step, for a wavefront's MB x NB accumulator blocks
+template <typename S>
+struct GemmFrags { Frag<bf16_t> fb[S::MB], fw[S::NB]; };
+
+// The contraction.  Tile i of this wavefront's group (contraction tile g + KG i) is multiplied from slot
+// i % STAGES, in four steps of 16 indices.  Operand fragments are read from LDS one step ahead of their
+// matrix instructions, across tiles too: the barrier that publishes the next tile stands before the last step
+// of the current one, so that the reads of the next tile's first fragments -- every wavefront's at once,
+// right after the barrier -- run under that step's matrix instructions.  (With the barrier at the end of the
+// tile the matrix cores idled through them: a quarter of a 256 x 256 workgroup's time.)  Behind that
+// barrier no wavefront reads the current tile any more: its slot takes the tile STAGES further on.
+//   issue(t, slot)       starts the direct loads of contraction tile t: LOADS instructions
+//   load(slot, ks, f)    reads the fragments of step ks
+//   publish(t, slot)     what is left to do for tile t before the barrier that publishes it, its loads having landed
+//   fetch(t)             REGS: starts the loads of the part of tile t that travels through registers to publish(t)
+template <typename S, int LOADS, typename Issue, typename Load, typename Publish, typename Fetch>
+__device__ __forceinline__ void gemm_loop(f32x16 (&acc)[S::MB][S::NB], int T, int group, bool regs, Issue &&issue, Load &&load,
+                                          Publish &&publish, Fetch &&fetch)
+{
+    const int iters = (T + S::KG - 1) / S::KG, mine = (T - group + S::KG - 1) / S::KG;      // tiles of the longest and of this group
+    auto tile = [&](int i) { return group + S::KG * i; };
+    // all but the loads of the `ahead` tiles issued last have landed (REGS: all)
+    auto landed = [&](int ahead_have, auto ahead) {
+        if (!regs && ahead_have >= decltype(ahead)::value) wait_vmem<decltype(ahead)::value * LOADS>();
+        else wait_vmem_all();
+    };
+    using std::integral_constant;
+#pragma unroll
+    for (int i = 0; i < S::STAGES; ++i)
+        if (i < mine) issue(tile(i), i);
+    if (regs && mine > 0) fetch(tile(0));
+    landed(mine - 1, integral_constant<int, S::STAGES - 1>{});
+    if (mine > 0) publish(tile(0), 0);
+    __syncthreads();
+    if (regs && mine > 1) fetch(tile(1));
+    GemmFrags<S> f[2];
+    auto multiply = [&](const GemmFrags<S> &g) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int mb = 0; mb < S::MB; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < S::NB; ++nb) acc[mb][nb] = mma(g.fw[nb], g.fb[mb], acc[mb][nb]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr int KS = PK / 16;
+    if (S::KG == 1 || mine > 0) load(0, 0, f[0]);
+    int slot = 0;
+    for (int i = 0; i < iters; ++i) {
+        const int nxt = slot + 1 == S::STAGES ? 0 : slot + 1;
+        const bool busy = S::KG == 1 || i < mine;
+        if (busy) {
+#pragma unroll
+            for (int ks = 0; ks + 1 < KS; ++ks) {
+                load(slot, ks + 1, f[(ks + 1) & 1]);
+                multiply(f[ks & 1]);
+            }
+        }
+        if (i + 1 < iters) {
+            landed(mine - 2 - i, integral_constant<int, S::STAGES - 2>{});
+            const bool more = S::KG == 1 || i + 1 < mine;
+            if (more) publish(tile(i + 1), nxt);
+            __syncthreads();
+            if (i + S::STAGES < mine) issue(tile(i + S::STAGES), slot);
+            if (regs && i + 2 < mine) fetch(tile(i + 2));
+            if (more) load(nxt, 0, f[0]);
+        }
+        if (busy) multiply(f[(KS - 1) & 1]);
+        slot = nxt;
+    }
+}
+// Adds the groups' accumulators up into group 0's, in group order, through the (now free) LDS.
+template <typename S>
+__device__ __forceinline__ void gemm_add_groups(char *smem, f32x16 (&acc)[S::MB][S::NB], int group, int gwave, int lane)
+{
+    if constexpr (S::KG > 1) {
+        constexpr int BLOCKS = S::MB * S::NB;
+        auto at = [&](int g, int blk, int e4) {
+            return reinterpret_cast<f32x4 *>(smem + ((((g - 1) * S::GW + gwave) * BLOCKS + blk) * 4 + e4) * 1024 + lane * 16);
+        };
+        __syncthreads();
+#pragma unroll
+        for (int blk = 0; blk < BLOCKS; ++blk)
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) {
+                const f32x16 &a = acc[blk / S::NB][blk % S::NB];
+                if (group > 0) *at(group, blk, e4) = f32x4{a[4 * e4], a[4 * e4 + 1], a[4 * e4 + 2], a[4 * e4 + 3]};
+            }
+        __syncthreads();
+        if (group == 0) {
+#pragma unroll
+            for (int g = 1; g < S::KG; ++g)
+#pragma unroll
+                for (int blk = 0; blk < BLOCKS; ++blk)
+#pragma unroll
+                    for (int e4 = 0; e4 < 4; ++e4) {
+                        const f32x4 v = *at(g, blk, e4);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[blk / S::NB][blk % S::NB][4 * e4 + e] += v[e];
+                    }
+        }
+    }
+}
+template <typename S>
+__device__ __forceinline__ void gemm_clear(f32x16 (&acc)[S::MB][S::NB])
+{
+#pragma unroll
+    for (int mb = 0; mb < S::MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < S::NB; ++nb)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[mb][nb][e] = 0.f;
+}
+
+// The finished tile -> LDS, a pass of CPP columns at a time, from where every wavefront reads whole row
+// pieces: the 16-byte chunk c of row m sits at chunk position c ^ (m % chunks per row).
+// Accumulator block (mb, nb), element v of a lane: row m = WM wm + 32 mb + lq, column n = WN wn +
+// 32 nb + 8 (v / 4) + 4 hh + v % 4.  Rows >= rows_data are written as zeros.
+template <typename S, bool OUT_F32>
+struct GemmStore {
+    static constexpr int EB = OUT_F32 ? 4 : 2, CW = 16 / EB;            // bytes per element, columns per chunk
+    static constexpr int PASSES = S::TM * S::TN * EB > S::LDS ? 2 : 1;
+    static constexpr int CPP = S::TN / PASSES, CPR = CPP / CW;          // columns and chunks per row of a pass
+    static_assert(CPP % S::WN == 0 && S::TM * CPP * EB <= S::LDS && S::NT % CPR == 0, "");
+    static constexpr int ROWS_PER_IT = S::NT / CPR, ITS = (S::TM + ROWS_PER_IT - 1) / ROWS_PER_IT;
+    static __device__ __forceinline__ int offset(int m, int c) { return m * (CPP * EB) + ((c ^ (m & (CPR - 1))) * 16); }
+    static __device__ __forceinline__ void to_lds(char *smem, const f32x16 (&acc)[S::MB][S::NB], int pass, int wm, int wn, int lq,
+                                                  int hh, int rows_data)
+    {
+        if (PASSES > 1 && wn * S::WN / CPP != pass) return;
+        const int c_first = wn * S::WN % CPP / CW;
+#pragma unroll
+        for (int mb = 0; mb < S::MB; ++mb) {
+            const int m = S::WM * wm + 32 * mb + lq;
+            const bool data = m < rows_data;
+#pragma unroll
+            for (int nb = 0; nb < S::NB; ++nb)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    f32x4 val = {0.f, 0.f, 0.f, 0.f};
+                    if (data) val = f32x4{acc[mb][nb][4 * g], acc[mb][nb][4 * g + 1], acc[mb][nb][4 * g + 2], acc[mb][nb][4 * g + 3]};
+                    if constexpr (OUT_F32)
+                        *reinterpret_cast<f32x4 *>(smem + offset(m, c_first + 8 * nb + 2 * g + hh)) = val;
+                    else
+                        *reinterpret_cast<bf16x4 *>(smem + offset(m, c_first + 4 * nb + g) + hh * 8) = pack4(val[0], val[1], val[2], val[3]);
+                }
+        }
+    }
+};
+
+// Position of workgroup `id` of a grid of m_tiles x n_tiles tiles: consecutive ids go to consecutive XCDs
+// (each with its own L2), and every XCD gets a contiguous run of tiles, so that few row tiles still fill all
+// XCDs.  Tiles are numbered in blocks of four row tiles, column by column: the 32 workgroups an XCD runs at a
+// time then read few different operand strips (4 + 8 instead of 2 + 16 where a row has 16 column tiles).
+struct TileId { int m, n; bool ok; };
+__device__ __forceinline__ TileId xcd_tile(int id, int m_tiles, int n_tiles)
+{
+    const int tiles = m_tiles * n_tiles, per_xcd = (tiles + kXcds - 1) / kXcds;
+    const int t = id % kXcds * per_xcd + id / kXcds;
+    const int block = t / (4 * n_tiles), in = t % (4 * n_tiles), rows = min(4, m_tiles - 4 * block);
+    return {4 * block + in % rows, in / rows, id / kXcds < per_xcd && t < tiles};
+}
+int xcd_tile_grid(int m_tiles, int n_tiles) { return kXcds * ((m_tiles * n_tiles + kXcds - 1) / kXcds); }
+
+template <typename S, bool A_ANY, bool W_TR, bool OUT_F32, int EPI>
+__global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(ProjArgs args)
 {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     using OutT = typename std::conditional<OUT_F32, float, bf16_t>::type;
+    using Store = GemmStore<S, OUT_F32>;
+    using ATile = DirectTile<PK, S::TM, S::GW>;         // activations [TM m][64 k]
+    using WPlain = DirectTile<PK, S::TN, S::GW>;        // weights [TN n][64 k]
+    using WTr = TrTile<S::TN, S::GW>;                   // weights [64 k][TN n]
+    constexpr int W_NI = W_TR ? WTr::NI : WPlain::NI, LOADS = ATile::NI + W_NI;     // load instructions per wavefront and tile
     static_assert(EPI == EPI_NONE || !OUT_F32, "the GeLU epilogues work on bf16 results");
 
     const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave & 1, wn = wave >> 1;
+    const int all_waves = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = all_waves / S::GW, wave = all_waves % S::GW, gtid = tid % S::GT;     // wave, gtid: within the group
+    const int wm = wave % S::MW, wn = wave / S::MW;
+    char *const ring = smem + group * S::RING;
 
-    // ---- which tile: jobs back to back; inside a job consecutive ids go to consecutive XCDs, and an
-    // XCD walks the column tiles of one row tile before the next, so the A rows it streams from HBM
-    // are re-read from its own L2
     int ji = 0;
     if (args.n_jobs > 1 && (int)blockIdx.x >= args.job[1].wg_begin) ji = 1;
     const ProjJob &J = args.job[ji];
-    const int id = blockIdx.x - J.wg_begin;
-    const int slot_id = id / kXcds;
-    const int n_tile = slot_id % J.n_tiles;
-    const int bm = id % kXcds + kXcds * (slot_id / J.n_tiles);
-    if (bm >= J.batches * J.m_tiles) return;
-    const int batch = bm / J.m_tiles, m0 = (bm % J.m_tiles) * PM, n0 = n_tile * PN;
+    const TileId tile = xcd_tile(blockIdx.x - J.wg_begin, J.batches * J.m_tiles, J.n_tiles);
+    if (!tile.ok) return;
+    const int batch = tile.m / J.m_tiles, m0 = (tile.m % J.m_tiles) * S::TM, n0 = tile.n * S::TN;
 
-    const int rows_here = min(J.rows - m0, PM);                     // rows of C this tile owns
-    const int rows_data = min(min(J.rows, J.rows_ok) - m0, PM);     // of which this many have data in A
-    const int cols_here = min(J.N - n0, PN);                        // a multiple of 64
+    const int rows_here = min(J.rows - m0, S::TM);                      // rows of C this tile owns
+    const int rows_data = min(min(J.rows, J.rows_ok) - m0, S::TM);      // of which this many have data in A
+    const int cols_here = min(J.N - n0, S::TN);                         // a multiple of 64
 
-    // ---- the finished tile -> memory, through LDS so that whole rows are written: a pass covers
-    // 16-byte chunks [0, 32) of every row (bf16: all 256 columns, one pass; float: 128 columns, two
-    // passes); chunk c of row m sits at chunk position c ^ (m % 32) of the row's 512 bytes.
-    // Accumulator tile (mb, nb), element v of this lane: row m = 128 wm + 32 mb + lq, columns
-    // n = 64 wn + 32 nb + 8 (v / 4) + 4 hh + (v % 4).
-    constexpr int CW = OUT_F32 ? 4 : 8;         // columns per 16-byte chunk
-    constexpr int PASSES = OUT_F32 ? 2 : 1;
-    auto store_tiles = [&](const f32x16 (&acc)[4][2], bool from_acc) {
+    auto store_tiles = [&](const f32x16 (&acc)[S::MB][S::NB], bool from_acc) {
         OutT *c0 = static_cast<OutT *>(J.c0) + (int64_t)batch * J.c_batch_stride + (int64_t)m0 * args.ldc;
         OutT *c1 = static_cast<OutT *>(J.c1) + (int64_t)batch * J.c_batch_stride + (int64_t)m0 * args.ldc;
 #pragma unroll
-        for (int pass = 0; pass < PASSES; ++pass) {
+        for (int pass = 0; pass < Store::PASSES; ++pass) {
             if (from_acc) {
                 __syncthreads();        // every wavefront is done with what the LDS held
-                if (!OUT_F32 || (wn >> 1) == pass) {
-#pragma unroll
-                    for (int mb = 0; mb < 4; ++mb) {
-                        const int m = 128 * wm + 32 * mb + lq;
-                        const bool data = m < rows_data;
-                        char *row = smem + m * 512;
-#pragma unroll
-                        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                            for (int g = 0; g < 4; ++g) {
-                                f32x4 val = {0.f, 0.f, 0.f, 0.f};
-                                if (data) val = f32x4{acc[mb][nb][4 * g], acc[mb][nb][4 * g + 1], acc[mb][nb][4 * g + 2], acc[mb][nb][4 * g + 3]};
-                                if constexpr (OUT_F32) {
-                                    const int c = 16 * (wn & 1) + 8 * nb + 2 * g + hh;
-                                    *reinterpret_cast<f32x4 *>(row + ((c ^ (m & 31)) * 16)) = val;
-                                } else {
-                                    const int c = 8 * wn + 4 * nb + g;
-                                    *reinterpret_cast<bf16x4 *>(row + ((c ^ (m & 31)) * 16) + hh * 8) = pack4(val[0], val[1], val[2], val[3]);
-                                }
-                            }
-                    }
-                }
+                if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, lq, hh, rows_data);
                 __syncthreads();
             }
-            // thread tid: chunk tid % 32 of rows tid / 32, + 16, ...
-            const int c = tid & 31;
-            const int n = n0 + pass * 128 + c * CW;         // column of C; a chunk never straddles n_split
-            const bool col_ok = pass * 128 + c * CW < cols_here;
+            const int c = tid % Store::CPR, col = pass * Store::CPP + c * Store::CW;
+            const int n = n0 + col;         // column of C; a chunk never straddles n_split
             OutT *dst = n < J.n_split ? c0 + n : c1 + (n - J.n_split);
 #pragma unroll
-            for (int i = 0; i < PM / 16; ++i) {
-                const int m = i * 16 + (tid >> 5);
+            for (int i = 0; i < Store::ITS; ++i) {
+                const int m = i * Store::ROWS_PER_IT + tid / Store::CPR;
                 f32x4 raw = {0.f, 0.f, 0.f, 0.f};
-                if (from_acc) raw = *reinterpret_cast<const f32x4 *>(smem + m * 512 + ((c ^ (m & 31)) * 16));
-                if (col_ok && m < rows_here) {
+                if (from_acc && m < S::TM) raw = *reinterpret_cast<const f32x4 *>(smem + Store::offset(m, c));
+                if (col < cols_here && m < rows_here) {
                     if constexpr (EPI == EPI_GELU_BWD) {
                         const bf16_t *u = static_cast<const bf16_t *>(J.a1) + (int64_t)batch * J.c_batch_stride + (int64_t)(m0 + m) * args.ldc + n;
                         const bf16x8 uu = *reinterpret_cast<const bf16x8 *>(u);
@@ -201,15 +351,11 @@ __global__ __launch_bounds__(P_NT, 1) void proj_gemm_kernel(ProjArgs args)
         }
     };
 
-    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    f32x16 acc[4][2];
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = zero16;
-
+    f32x16 acc[S::MB][S::NB];
+    gemm_clear<S>(acc);
     if (rows_data <= 0) {       // no row of this tile has data: its rows of C are zero
-        if (!args.skip_tail) store_tiles(acc, false);
+        // (skip_tail leaves the rows unwritten from the next multiple of 256 on, whatever the tile)
+        if (!args.skip_tail || m0 < (J.rows_ok + 255) / 256 * 256) store_tiles(acc, false);
         return;
     }
 
@@ -217,11 +363,11 @@ __global__ __launch_bounds__(P_NT, 1) void proj_gemm_kernel(ProjArgs args)
     const int t_split = J.k_split / PK;
 
     // ---- tile loads
-    uint32_t offA[ATile::NI], offW[W_TR ? WTileTr::NI : WTile::NI];
+    uint32_t offA[ATile::NI], offW[W_NI];
     const bool a_f32 = A_ANY && J.a_f32 != 0;   // workgroup-uniform
     ATile::offsets(offA, args.lda, rows_data, wave, lane);
-    if constexpr (W_TR) WTileTr::offsets(offW, J.ldw, wave, lane, cols_here / 8);
-    else WTile::offsets(offW, J.ldw, cols_here, wave, lane);
+    if constexpr (W_TR) WTr::offsets(offW, J.ldw, wave, lane, cols_here / 8);
+    else WPlain::offsets(offW, J.ldw, cols_here, wave, lane);
 
     const char *a0 = static_cast<const char *>(J.a0), *a1 = static_cast<const char *>(J.a1);
     const int AE = a_f32 ? 4 : 2;               // bytes per element of A
@@ -230,27 +376,22 @@ __global__ __launch_bounds__(P_NT, 1) void proj_gemm_kernel(ProjArgs args)
         return (t < t_split ? a0 + (int64_t)t * PK * AE : a1 + (int64_t)(t - t_split) * PK * AE) + a_tile0;
     };
     auto issue_w = [&](int t, int slot) {
-        char *dst = smem + slot * P_SLOT + P_ABYTES;
         const bf16_t *src = W_TR ? J.w + (int64_t)t * PK * J.ldw + n0 : J.w + (int64_t)n0 * J.ldw + (int64_t)t * PK;
-#pragma unroll
-        for (int i = 0; i < (W_TR ? WTileTr::NI : WTile::NI); ++i) lds_dma<16>(src, offW[i], dst + (i * P_WAVES + wave) * 1024);
+        lds_dma_n<W_NI, S::GW * 1024>(src, offW, ring + slot * S::SLOT + S::ABYTES + wave * 1024);
     };
     auto issue_a = [&](int t, int slot) {       // bf16 A: direct
-        char *dst = smem + slot * P_SLOT;
-        const char *src = a_src(t);
-#pragma unroll
-        for (int i = 0; i < ATile::NI; ++i) lds_dma<16>(src, offA[i], dst + (i * P_WAVES + wave) * 1024);
+        lds_dma_n<ATile::NI, S::GW * 1024>(a_src(t), offA, ring + slot * S::SLOT + wave * 1024);
     };
-    // float A: thread `tid` converts the 8-element chunks tid, tid + 512, ... of the tile
+    // float A: thread `gtid` converts the 8-element chunks gtid, gtid + GT, ... of the tile
     // (chunk c is columns 8 (c % 8) .. + 7 of row c / 8) and writes them where the direct load would
-    constexpr int FCH = PM * 8 / P_NT;          // chunks per thread
+    constexpr int FCH = S::TM * 8 / S::GT;      // chunks per thread
     f32x4 stage[A_ANY ? 2 * FCH : 1];
     auto fetch_a = [&](int t) {
         if constexpr (A_ANY) {
             const char *src = a_src(t);
 #pragma unroll
             for (int i = 0; i < FCH; ++i) {
-                const int c = i * P_NT + tid, row = min(c >> 3, rows_data - 1);
+                const int c = i * S::GT + gtid, row = min(c >> 3, rows_data - 1);
                 const f32x4 *p = reinterpret_cast<const f32x4 *>(src + ((int64_t)row * args.lda + (c & 7) * 8) * 4);
                 stage[2 * i] = p[0];       // (re-read from L2 by the workgroups of the other column tiles)
                 stage[2 * i + 1] = p[1];
@@ -259,10 +400,10 @@ __global__ __launch_bounds__(P_NT, 1) void proj_gemm_kernel(ProjArgs args)
     };
     auto stash_a = [&](int slot) {
         if constexpr (A_ANY) {
-            char *dst = smem + slot * P_SLOT;
+            char *dst = ring + slot * S::SLOT;
 #pragma unroll
             for (int i = 0; i < FCH; ++i) {
-                const int c = i * P_NT + tid;
+                const int c = i * S::GT + gtid;
                 bf16x8 v;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) { v[e] = (bf16_t)stage[2 * i][e]; v[4 + e] = (bf16_t)stage[2 * i + 1][e]; }
@@ -272,93 +413,41 @@ __global__ __launch_bounds__(P_NT, 1) void proj_gemm_kernel(ProjArgs args)
     };
 
     // ---- per-lane LDS offsets of the operand fragments of contraction step ks (16 indices): slot e
-    // of a fragment carries index 16 ks + 8 hh + e
-    int b_off[4][4];
+    // of a fragment carries index 16 ks + 8 hh + e.  (A row 32 further down keeps the permutation.)
+    int b_off[PK / 16], w_off[PK / 16], wt_off[S::NB];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const int m = 128 * wm + 32 * mb + lq;
-            b_off[mb][ks] = ATile::chunk_offset(m, 2 * ks + hh);
-        }
-    int w_off[2][4];            // plain weights: row n = 64 wn + 32 nb + lq, chunk 2 ks + hh
-    int wt_off[2];              // transposed reads: column block 2 wn + nb
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-        wt_off[nb] = WTileTr::lane_offset(lane, 2 * wn + nb);
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) w_off[nb][ks] = WTile::chunk_offset(64 * wn + 32 * nb + lq, 2 * ks + hh);
+    for (int ks = 0; ks < PK / 16; ++ks) {
+        b_off[ks] = ATile::chunk_offset(S::WM * wm + lq, 2 * ks + hh);
+        w_off[ks] = WPlain::chunk_offset(S::WN * wn + lq, 2 * ks + hh);
     }
-    // One contraction tile: four steps of 16 indices.  The six operand fragments of step ks + 1 are
-    // requested from LDS before the eight matrix instructions of step ks are issued (two sets of
-    // fragment registers), so a wavefront's matrix instructions wait for reads that are a whole step
-    // old instead of for the ones just issued.
-    struct Frags { Frag<bf16_t> fb[4], fw[2]; };
-    auto load_frags = [&](const char *at, const char *wt, int ks, Frags &f) __attribute__((always_inline)) {
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-            if constexpr (W_TR) f.fw[nb] = WTileTr::load_frag(wt, ks, wt_off[nb]);
-            else f.fw[nb] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(wt + w_off[nb][ks]));
+    for (int nb = 0; nb < S::NB; ++nb) wt_off[nb] = WTr::lane_offset(lane, S::NB * wn + nb);
+    auto load = [&](int slot, int ks, GemmFrags<S> &f) __attribute__((always_inline)) {
+        const char *at = ring + slot * S::SLOT, *wt = at + S::ABYTES;
+#pragma unroll
+        for (int nb = 0; nb < S::NB; ++nb) {
+            if constexpr (W_TR) f.fw[nb] = WTr::load_frag(wt, ks, wt_off[nb]);
+            else f.fw[nb] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(wt + w_off[ks] + nb * 32 * PK * 2));
         }
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) f.fb[mb] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(at + b_off[mb][ks]));
+        for (int mb = 0; mb < S::MB; ++mb)
+            f.fb[mb] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(at + b_off[ks] + mb * 32 * PK * 2));
     };
-    auto compute = [&](int slot) {
-        const char *at = smem + slot * P_SLOT, *wt = at + P_ABYTES;
-        Frags f[2];
-        load_frags(at, wt, 0, f[0]);
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            if (ks + 1 < 4) load_frags(at, wt, ks + 1, f[(ks + 1) & 1]);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = mma(f[ks & 1].fw[nb], f[ks & 1].fb[mb], acc[mb][nb]);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+    auto issue = [&](int t, int slot) {
+        if (!a_f32) issue_a(t, slot);
+        issue_w(t, slot);
     };
-
-    // ---- main loop: tile t is multiplied from slot t % 2 while tile t + 1 travels into the other slot
-    // (last read during tile t - 1, which every wavefront left at the barrier)
-    if (a_f32) {
-        fetch_a(0);
-        issue_w(0, 0);
-        stash_a(0);
-        if (T > 1) fetch_a(1);
-        wait_vmem_all();
-        __syncthreads();
-        for (int t = 0; t < T; ++t) {
-            const int slot = t & 1;
-            if (t + 1 < T) issue_w(t + 1, slot ^ 1);
-            compute(slot);
-            if (t + 1 < T) stash_a(slot ^ 1);
-            wait_vmem_all();
-            if (t + 2 < T) fetch_a(t + 2);      // in flight across the barrier, stashed after tile t + 1
-            __syncthreads();
-        }
-    } else {
-        issue_a(0, 0); issue_w(0, 0);
-        wait_vmem_all();
-        __syncthreads();
-        for (int t = 0; t < T; ++t) {
-            const int slot = t & 1;
-            if (t + 1 < T) { issue_a(t + 1, slot ^ 1); issue_w(t + 1, slot ^ 1); }
-            compute(slot);
-            wait_vmem_all();
-            __syncthreads();
-        }
-    }
+    gemm_loop<S, LOADS>(acc, T, group, a_f32, issue, load, [&](int, int slot) { if (a_f32) stash_a(slot); }, fetch_a);
+    gemm_add_groups<S>(smem, acc, group, wave, lane);
     store_tiles(acc, true);
 }
 
-
 // Weight gradient of a linear map: dW[k, n] = sum_r A[r, k] dC[r, n], the contraction running over
-// the rows of both operands.  Both are therefore loaded as [64 rows][256 columns] tiles and read
-// through transposing LDS reads (WTileTr); a workgroup owns a 256 (k) x 256 (n) tile of dW for one
+// the rows of both operands.  Both are therefore loaded as [64 rows][columns] tiles and read
+// through transposing LDS reads (TrTile); a workgroup owns a TM (k) x TN (n) tile of dW for one
 // chunk of rows of one batch entry and writes it in fp32, to dW itself when there is a single chunk,
 // else to that chunk's partial result, which a fixed-order sum adds up afterwards.  Same wavefront
-// layout, two-slot ring and LDS-staged stores as proj_gemm_kernel.
+// layout, ring and LDS-staged stores as proj_gemm_kernel.
 //   DC_F32  dC is float and may come from two tensors side by side (the dK and dV partials): it is
 //           rounded to bf16 on its way into LDS, through registers, as proj_gemm_kernel does for a
 //           float A.
@@ -373,74 +462,79 @@ struct WgradArgs {
     int splits_per_batch, m_tiles, n_tiles;
 };
 
-template <bool DC_F32>
-__global__ __launch_bounds__(P_NT, 1) void wgrad_gemm_kernel(WgradArgs g)
+template <typename S, bool DC_F32>
+__global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(WgradArgs g)
 {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
+    using Store = GemmStore<S, true>;
+    using ATile = TrTile<S::TM, S::GW>;
+    using WTile = TrTile<S::TN, S::GW>;
+    constexpr int LOADS = ATile::NI + (DC_F32 ? 0 : WTile::NI);
     const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave & 1, wn = wave >> 1;
+    const int all_waves = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = all_waves / S::GW, wave = all_waves % S::GW, gtid = tid % S::GT;     // wave, gtid: within the group
+    const int wm = wave % S::MW, wn = wave / S::MW;
+    char *const ring = smem + group * S::RING;
 
-    // consecutive ids go to consecutive XCDs; an XCD walks the output tiles of one chunk of rows, so
-    // that chunk's rows of A and dC are read from HBM once per XCD
-    const int tiles = g.m_tiles * g.n_tiles, splits = g.batches * g.splits_per_batch;
-    const int x = blockIdx.x % kXcds, rest = blockIdx.x / kXcds;
-    const int tile = rest % tiles, split = x + kXcds * (rest / tiles);
-    if (split >= splits) return;
+    // an XCD walks the output tiles of one chunk of rows, so that chunk's rows of A and dC are read from
+    // HBM once per XCD
+    const int splits = g.batches * g.splits_per_batch;
+    const int tiles = g.m_tiles * g.n_tiles, per_xcd = (splits * tiles + kXcds - 1) / kXcds;
+    const int item = blockIdx.x % kXcds * per_xcd + blockIdx.x / kXcds;
+    if ((int)blockIdx.x / kXcds >= per_xcd || item >= splits * tiles) return;
+    const int split = item / tiles, tile = item % tiles;
     const int batch = split / g.splits_per_batch;
-    const int m0 = (tile / g.n_tiles) * PM, n0 = (tile % g.n_tiles) * PN;
+    const int m0 = (tile / g.n_tiles) * S::TM, n0 = (tile % g.n_tiles) * S::TN;
     const int r0 = (split % g.splits_per_batch) * g.chunk_rows, r1 = min(r0 + g.chunk_rows, g.rows);
     const int T = (r1 - r0 + PK - 1) / PK;          // >= 1: the host sizes the splits so
     const int tail = (r1 - r0) - (T - 1) * PK;      // rows of the last tile, 1 .. 64
-    const int cols_m = min(g.K - m0, PM), cols_n = min(g.N - n0, PN);
+    const int cols_m = min(g.K - m0, S::TM), cols_n = min(g.N - n0, S::TN);
 
-    uint32_t offA[WTileTr::NI], offA_last[WTileTr::NI], offW[DC_F32 ? 1 : WTileTr::NI], offW_last[DC_F32 ? 1 : WTileTr::NI];
-    WTileTr::offsets(offA, g.lda, wave, lane, cols_m / 8);
-    WTileTr::offsets(offA_last, g.lda, wave, lane, cols_m / 8, tail);
+    uint32_t offA[ATile::NI], offA_last[ATile::NI], offW[DC_F32 ? 1 : WTile::NI], offW_last[DC_F32 ? 1 : WTile::NI];
+    ATile::offsets(offA, g.lda, wave, lane, cols_m / 8);
+    ATile::offsets(offA_last, g.lda, wave, lane, cols_m / 8, tail);
     if constexpr (!DC_F32) {
-        WTileTr::offsets(offW, g.ldc, wave, lane, cols_n / 8);
-        WTileTr::offsets(offW_last, g.ldc, wave, lane, cols_n / 8, tail);
+        WTile::offsets(offW, g.ldc, wave, lane, cols_n / 8);
+        WTile::offsets(offW_last, g.ldc, wave, lane, cols_n / 8, tail);
     }
     const bf16_t *a_base = g.a + (int64_t)batch * g.a_batch_stride + (int64_t)r0 * g.lda + m0;
     auto issue = [&](int t, int slot) {
-        char *dst = smem + slot * P_SLOT;
+        char *dst = ring + slot * S::SLOT + wave * 1024;
         const bf16_t *pa = a_base + (int64_t)t * PK * g.lda;
-        const bool last = t == T - 1;
-#pragma unroll
-        for (int i = 0; i < WTileTr::NI; ++i) lds_dma<16>(pa, last ? offA_last[i] : offA[i], dst + (i * P_WAVES + wave) * 1024);
+        if (t == T - 1) lds_dma_n<ATile::NI, S::GW * 1024>(pa, offA_last, dst);
+        else lds_dma_n<ATile::NI, S::GW * 1024>(pa, offA, dst);
         if constexpr (!DC_F32) {
             const bf16_t *pw = static_cast<const bf16_t *>(g.dc0) + (int64_t)batch * g.dc_batch_stride + (int64_t)(r0 + t * PK) * g.ldc + n0;
-#pragma unroll
-            for (int i = 0; i < WTileTr::NI; ++i)
-                lds_dma<16>(pw, last ? offW_last[i] : offW[i], dst + P_ABYTES + (i * P_WAVES + wave) * 1024);
+            if (t == T - 1) lds_dma_n<WTile::NI, S::GW * 1024>(pw, offW_last, dst + S::ABYTES);
+            else lds_dma_n<WTile::NI, S::GW * 1024>(pw, offW, dst + S::ABYTES);
         }
     };
     // Rows past the end of the chunk re-read its last row; their copies in the tiles are replaced
     // by zeros, each lane clearing exactly the 16 bytes its own loads wrote (after waiting for them).
     auto clear_tail = [&](int slot) {
         if (tail == PK) return;
-        char *dst = smem + slot * P_SLOT;
+        char *dst = ring + slot * S::SLOT;
 #pragma unroll
-        for (int i = 0; i < WTileTr::NI; ++i) {
-            const int row = (i * P_WAVES + wave) * 2 + lane / 32;
-            if (row >= tail) {
-                *reinterpret_cast<f32x4 *>(dst + (i * P_WAVES + wave) * 1024 + lane * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
-                if constexpr (!DC_F32)
-                    *reinterpret_cast<f32x4 *>(dst + P_ABYTES + (i * P_WAVES + wave) * 1024 + lane * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
+        for (int i = 0; i < ATile::NI; ++i)
+            if (ATile::row_of(i, wave, lane) >= tail)
+                *reinterpret_cast<f32x4 *>(dst + (i * S::GW + wave) * 1024 + lane * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (!DC_F32) {
+#pragma unroll
+            for (int i = 0; i < WTile::NI; ++i)
+                if (WTile::row_of(i, wave, lane) >= tail)
+                    *reinterpret_cast<f32x4 *>(dst + S::ABYTES + (i * S::GW + wave) * 1024 + lane * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
         }
     };
-    // float dC: thread `tid` converts the 8-column chunks tid, tid + 512, ... of the [64][256] tile
-    // (chunk c is columns 8 (c % 32) .. + 7 of row c / 32) and writes them where the direct load would;
-    // rows past the end of the chunk are written as zeros
-    constexpr int FCH = PK * (PN / 8) / P_NT;       // chunks per thread
+    // float dC: thread `gtid` converts the 8-column chunks gtid, gtid + GT, ... of the [64][TN] tile and
+    // writes them where the direct load would; rows past the end of the chunk are written as zeros
+    constexpr int FCH = PK * (S::TN / 8) / S::GT;   // chunks per thread
     f32x4 stage[DC_F32 ? 2 * FCH : 1];
     auto fetch_w = [&](int t) {
         if constexpr (DC_F32) {
             const int rows_here = t == T - 1 ? tail : PK;
 #pragma unroll
             for (int i = 0; i < FCH; ++i) {
-                const int c = i * P_NT + tid, row = min(c >> 5, rows_here - 1), col = min(c & 31, cols_n / 8 - 1);
+                const int c = i * S::GT + gtid, row = min(c / WTile::CPR, rows_here - 1), col = min(c % WTile::CPR, cols_n / 8 - 1);
                 const int n = n0 + col * 8;
                 const float *src = n < g.n_split ? static_cast<const float *>(g.dc0) + n : static_cast<const float *>(g.dc1) + (n - g.n_split);
                 const f32x4 *p = reinterpret_cast<const f32x4 *>(src + (int64_t)batch * g.dc_batch_stride + (int64_t)(r0 + t * PK + row) * g.ldc);
@@ -452,135 +546,154 @@ __global__ __launch_bounds__(P_NT, 1) void wgrad_gemm_kernel(WgradArgs g)
     auto stash_w = [&](int t, int slot) {
         if constexpr (DC_F32) {
             const int rows_here = t == T - 1 ? tail : PK;
-            char *dst = smem + slot * P_SLOT + P_ABYTES;
+            char *dst = ring + slot * S::SLOT + S::ABYTES;
 #pragma unroll
             for (int i = 0; i < FCH; ++i) {
-                const int c = i * P_NT + tid, row = c >> 5, col = c & 31;
+                const int c = i * S::GT + gtid, row = c / WTile::CPR, col = c % WTile::CPR;
                 bf16x8 v;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     v[e] = row < rows_here ? (bf16_t)stage[2 * i][e] : (bf16_t)0.f;
                     v[4 + e] = row < rows_here ? (bf16_t)stage[2 * i + 1][e] : (bf16_t)0.f;
                 }
-                *reinterpret_cast<bf16x8 *>(dst + row * (PN * 2) + ((col ^ (4 * (row & 3))) * 16)) = v;
+                *reinterpret_cast<bf16x8 *>(dst + WTile::chunk_offset(row, col)) = v;
             }
         }
     };
 
-    int at_off[4], wt_off[2];
+    int at_off[S::MB], wt_off[S::NB];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) at_off[mb] = WTileTr::lane_offset(lane, 4 * wm + mb);
+    for (int mb = 0; mb < S::MB; ++mb) at_off[mb] = ATile::lane_offset(lane, S::MB * wm + mb);
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) wt_off[nb] = WTileTr::lane_offset(lane, 2 * wn + nb);
-
-    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    f32x16 acc[4][2];
+    for (int nb = 0; nb < S::NB; ++nb) wt_off[nb] = WTile::lane_offset(lane, S::NB * wn + nb);
+    f32x16 acc[S::MB][S::NB];
+    gemm_clear<S>(acc);
+    auto load = [&](int slot, int ks, GemmFrags<S> &f) __attribute__((always_inline)) {
+        const char *at = ring + slot * S::SLOT, *wt = at + S::ABYTES;
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+        for (int nb = 0; nb < S::NB; ++nb) f.fw[nb] = WTile::load_frag(wt, ks, wt_off[nb]);
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = zero16;
-
-    struct Frags { Frag<bf16_t> fb[4], fw[2]; };
-    auto load_frags = [&](const char *at, const char *wt, int ks, Frags &f) __attribute__((always_inline)) {
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) f.fw[nb] = WTileTr::load_frag(wt, ks, wt_off[nb]);
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb) f.fb[mb] = WTileTr::load_frag(at, ks, at_off[mb]);
+        for (int mb = 0; mb < S::MB; ++mb) f.fb[mb] = ATile::load_frag(at, ks, at_off[mb]);
     };
-    auto compute = [&](int slot) {
-        const char *at = smem + slot * P_SLOT, *wt = at + P_ABYTES;
-        Frags f[2];
-        load_frags(at, wt, 0, f[0]);
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            if (ks + 1 < 4) load_frags(at, wt, ks + 1, f[(ks + 1) & 1]);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = mma(f[ks & 1].fw[nb], f[ks & 1].fb[mb], acc[mb][nb]);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+    auto publish = [&](int t, int slot) {
+        stash_w(t, slot);
+        if (t == T - 1) clear_tail(slot);
     };
+    gemm_loop<S, LOADS>(acc, T, group, DC_F32, issue, load, publish, fetch_w);
+    gemm_add_groups<S>(smem, acc, group, wave, lane);
 
-    // tile t is multiplied from slot t % 2 while tile t + 1 travels into the other slot; a float
-    // dC tile is fetched into registers two tiles ahead and written to LDS one tile ahead
-    fetch_w(0);
-    issue(0, 0);
-    stash_w(0, 0);
-    if (T > 1) fetch_w(1);
-    wait_vmem_all();
-    if (T == 1) clear_tail(0);
-    __syncthreads();
-    for (int t = 0; t < T; ++t) {
-        const int slot = t & 1;
-        if (t + 1 < T) issue(t + 1, slot ^ 1);
-        compute(slot);
-        if (t + 1 < T) stash_w(t + 1, slot ^ 1);
-        wait_vmem_all();
-        if (t + 1 == T - 1) clear_tail(slot ^ 1);
-        if (t + 2 < T) fetch_w(t + 2);
-        __syncthreads();
-    }
-
-    // ---- the finished tile -> memory through LDS (whole rows written), 128 columns per pass; see
-    // proj_gemm_kernel for the layout: element v of accumulator (mb, nb) is row 128 wm + 32 mb + lq,
-    // column 64 wn + 32 nb + 8 (v / 4) + 4 hh + v % 4
     float *out = g.out + (int64_t)split * g.K * g.N + (int64_t)m0 * g.N + n0;
 #pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        if (pass) __syncthreads();
-        if ((wn >> 1) == pass) {
-#pragma unroll
-            for (int mb = 0; mb < 4; ++mb) {
-                const int m = 128 * wm + 32 * mb + lq;
-                char *row = smem + m * 512;
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int c = 16 * (wn & 1) + 8 * nb + 2 * q + hh;
-                        *reinterpret_cast<f32x4 *>(row + ((c ^ (m & 31)) * 16)) =
-                            f32x4{acc[mb][nb][4 * q], acc[mb][nb][4 * q + 1], acc[mb][nb][4 * q + 2], acc[mb][nb][4 * q + 3]};
-                    }
-            }
-        }
+    for (int pass = 0; pass < Store::PASSES; ++pass) {
         __syncthreads();
-        const int c = tid & 31;
-        if (pass * 128 + c * 4 < cols_n) {
+        if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, lq, hh, S::TM);
+        __syncthreads();
+        const int c = tid % Store::CPR, col = pass * Store::CPP + c * Store::CW;
+        if (col < cols_n) {
 #pragma unroll
-            for (int i = 0; i < PM / 16; ++i) {
-                const int m = i * 16 + (tid >> 5);
+            for (int i = 0; i < Store::ITS; ++i) {
+                const int m = i * Store::ROWS_PER_IT + tid / Store::CPR;
                 if (m < cols_m)
-                    *reinterpret_cast<f32x4 *>(out + (int64_t)m * g.N + pass * 128 + c * 4) =
-                        *reinterpret_cast<const f32x4 *>(smem + m * 512 + ((c ^ (m & 31)) * 16));
+                    *reinterpret_cast<f32x4 *>(out + (int64_t)m * g.N + col) = *reinterpret_cast<const f32x4 *>(smem + Store::offset(m, c));
             }
         }
     }
 }
 
-template <bool A_ANY, bool W_TR, bool OUT_F32, int EPI = EPI_NONE>
-hipError_t launch_proj(ProjArgs &args, int kernel_id, hipStream_t st)
+// ---- the tiles a launch may take
+using ShapeL = GemmShape<256, 256, 128, 64, 2>;         // eight wavefronts, one workgroup per compute unit
+using ShapeM = GemmShape<128, 128, 64, 64, 2>;          // four wavefronts, two workgroups per compute unit
+using ShapeM2 = GemmShape<128, 128, 64, 64, 2, 2>;      // ... two such groups share the contraction
+using ShapeS = GemmShape<64, 64, 32, 32, 4>;
+using ShapeS4 = GemmShape<64, 64, 32, 32, 2, 4>;
+
+template <typename K>
+hipError_t allow_lds(K kernel, int bytes, std::once_flag &once, hipError_t &attr)
+{
+    std::call_once(once, [&] { attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
+    return attr;
+}
+
+template <typename S, bool A_ANY, bool W_TR, bool OUT_F32, int EPI>
+hipError_t launch_proj_shape(ProjArgs &args, int kernel_id, hipStream_t st)
 {
     int wgs = 0;
     for (int j = 0; j < args.n_jobs; ++j) {
         ProjJob &J = args.job[j];
-        J.m_tiles = (J.rows + PM - 1) / PM;
-        J.n_tiles = (J.N + PN - 1) / PN;
+        J.m_tiles = (J.rows + S::TM - 1) / S::TM;
+        J.n_tiles = (J.N + S::TN - 1) / S::TN;
         J.wg_begin = wgs;
-        wgs += xcd_grid(J.batches * J.m_tiles, J.n_tiles);
+        wgs += xcd_tile_grid(J.batches * J.m_tiles, J.n_tiles);
     }
     if (wgs == 0) return hipSuccess;
     static std::once_flag once;
     static hipError_t attr = hipSuccess;
-    std::call_once(once, [] {
-        attr = hipFuncSetAttribute(reinterpret_cast<const void *>(proj_gemm_kernel<A_ANY, W_TR, OUT_F32, EPI>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-    });
-    if (attr != hipSuccess) return attr;
+    const auto kernel = proj_gemm_kernel<S, A_ANY, W_TR, OUT_F32, EPI>;
+    if (allow_lds(kernel, S::LDS, once, attr) != hipSuccess) return attr;
     TimedLaunch tl(kernel_id, st);
-    hipLaunchKernelGGL((proj_gemm_kernel<A_ANY, W_TR, OUT_F32, EPI>), dim3(wgs), dim3(P_NT), P_LDS, st, args);
+    hipLaunchKernelGGL(kernel, dim3(wgs), dim3(S::NT), S::LDS, st, args);
     return hipGetLastError();
+}
+
+// Which tile a launch takes: the one with the smallest estimated time.  A round of workgroups costs
+//     fixed + contraction tiles x per_tile   microseconds;
+// where compute units hold one workgroup each (PER_CU = 1: where half of them have one) a contraction tile takes
+// per_tile[0], where they are full per_tile[1].  The figures are fitted to linear_fwd and linear_bwd_input at 230 .. 98304 rows and
+// 512 .. 8192 columns either way (20 launches in a graph each).  Large tiles move the fewest bytes per flop
+// but a launch of few of them leaves compute units idle (2048 x 2048 -> 512: 16 workgroups of 256 x 256, 46 us;
+// 256 of 64 x 64, 12 us), and where even 64 x 64 tiles leave one wavefront per SIMD the chain of contraction
+// tiles is what takes the time: four groups of wavefronts that share it take 9 us.
+struct GemmCost { double fixed, per_tile[2]; };
+template <typename S> constexpr GemmCost gemm_cost();
+template <> constexpr GemmCost gemm_cost<ShapeL>() { return {6.5, {1.40, 1.70}}; }
+template <> constexpr GemmCost gemm_cost<ShapeM>() { return {2.8, {0.62, 1.00}}; }
+template <> constexpr GemmCost gemm_cost<ShapeM2>() { return {3.0, {0.50, 0.58}}; }
+template <> constexpr GemmCost gemm_cost<ShapeS>() { return {2.5, {0.30, 0.40}}; }
+template <> constexpr GemmCost gemm_cost<ShapeS4>() { return {3.3, {0.165, 0.22}}; }
+
+// `tiles`: contraction tiles of a workgroup
+template <typename S>
+double gemm_estimate(double wgs, double tiles)
+{
+    constexpr GemmCost c = gemm_cost<S>();
+    constexpr double room = 256.0 * S::PER_CU;
+    const double full = (double)(int64_t)(wgs / room), rest = wgs - full * room;
+    return full * (c.fixed + tiles * c.per_tile[1]) + (rest > 0 ? c.fixed + tiles * c.per_tile[rest > (S::PER_CU == 1 ? 128 : 256)] : 0.0);
+}
+
+template <bool A_ANY, bool W_TR, bool OUT_F32, int EPI = EPI_NONE>
+hipError_t launch_proj(ProjArgs &args, int kernel_id, hipStream_t st)
+{
+    auto estimate = [&](auto shape) {
+        using S = decltype(shape);
+        double wgs = 0, work = 0;
+        for (int j = 0; j < args.n_jobs; ++j) {
+            const ProjJob &J = args.job[j];
+            const double n = (double)J.batches * ((J.rows + S::TM - 1) / S::TM) * ((J.N + S::TN - 1) / S::TN);
+            // A float A costs more the smaller the tile, whose workgroups re-read it more often, and the less of it
+            // fits the last-level cache (project_bwd, 1024 columns: 256 x 256 against 128 x 128 tiles take 79 and
+            // 62 us at 8192 rows, 109 and 111 at 16384, 208 and 278 at 32768)
+            double slow = 1.0;
+            if (J.a_f32) {
+                const double a_bytes = (double)J.batches * J.rows_ok * J.K * 4.0, far = a_bytes < 256e6 ? a_bytes / 256e6 : 1.0;
+                slow = S::TM == 256 ? 1.27 : S::TM == 128 ? 1.15 + 0.45 * far : 1.6 + 0.5 * far;
+            }
+            wgs += n;
+            work += n * (J.K / PK) * slow;
+        }
+        return gemm_estimate<S>(wgs, wgs > 0 ? work / wgs : 0.0);
+    };
+    const double t[5] = {estimate(ShapeL{}), estimate(ShapeM{}), estimate(ShapeM2{}), estimate(ShapeS{}), estimate(ShapeS4{})};
+    int best = 0;
+    for (int i = 1; i < 5; ++i)
+        if (t[i] < t[best]) best = i;
+    switch (best) {
+    case 0: return launch_proj_shape<ShapeL, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    case 1: return launch_proj_shape<ShapeM, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    case 2: return launch_proj_shape<ShapeM2, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    case 3: return launch_proj_shape<ShapeS, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    default: return launch_proj_shape<ShapeS4, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    }
 }
 
 } // namespace
@@ -669,56 +782,75 @@ hipError_t launch_linear_bwd_input(const bf16_t *dc, const bf16_t *w, const bf16
     return launch_proj<false, false, false>(args, K_LINEAR_BWD, st);
 }
 
-// How the rows are split for the weight gradient: about two workgroups per compute unit, at least
-// eight 64-row tiles per workgroup; a chunk never crosses batch entries.  Shape-only, deterministic.
-static int wgrad_want(int batches, int K, int N)       // chunks per batch entry aimed at; never exceeded
+// Tile and split of the rows for a weight gradient: the pair with the smallest estimated time, the sum of the
+// chunks' partial results (3.5 us and their bytes at 4 TB/s) included; a chunk never crosses batch
+// entries.  Shape-only, deterministic.  There are never more chunks than 512 workgroups of 256 x 256 would
+// take, which bounds the scratch for any number of rows.
+static int wgrad_max_chunks(int batches, int K, int N)      // per batch entry
 {
-    const int tiles = ((K + PM - 1) / PM) * ((N + PN - 1) / PN);
-    const int want = ((512 + tiles - 1) / tiles + batches - 1) / batches;
-    return want < 1 ? 1 : want;
+    const int tiles = ((K + 255) / 256) * ((N + 255) / 256);
+    return ((512 + tiles - 1) / tiles + batches - 1) / batches;
 }
-static void wgrad_plan(int rows, int batches, int K, int N, int &splits_per_batch, int &chunk_rows)
+struct WgradPlan { int shape, splits_per_batch, chunk_rows; };
+static WgradPlan wgrad_plan(int rows, int batches, int K, int N)
 {
-    const int R = (rows + PK - 1) / PK;
-    const int want = wgrad_want(batches, K, N);
-    int chunk_tiles = (R + want - 1) / want;
-    if (chunk_tiles < 8) chunk_tiles = R < 8 ? R : 8;
-    if (chunk_tiles < 1) chunk_tiles = 1;
-    splits_per_batch = (R + chunk_tiles - 1) / chunk_tiles;
-    if (splits_per_batch < 1) splits_per_batch = 1;
-    chunk_rows = chunk_tiles * PK;
+    const int R = (rows + PK - 1) / PK, most = wgrad_max_chunks(batches, K, N);
+    WgradPlan best{0, 1, PK};
+    double best_t = 0.0;
+    for (int want = 1; want <= most && want <= R; want = want < 4 ? want + 1 : want + want / 3) {
+        const int chunk_tiles = (R + want - 1) / want, splits = (R + chunk_tiles - 1) / chunk_tiles;
+        const double parts = (double)batches * splits;
+        const double sum = parts > 1 ? 3.5 + (parts + 1) * K * N * 4e-6 / 4.0 : 0.0;
+        auto estimate = [&](auto shape) {
+            using S = decltype(shape);
+            // (both operands through transposing reads: a fifth slower per tile, but for the largest)
+            return sum + gemm_estimate<S>(parts * ((K + S::TM - 1) / S::TM) * ((N + S::TN - 1) / S::TN), chunk_tiles * (S::TM == 256 ? 1.0 : 1.2));
+        };
+        const double t[5] = {estimate(ShapeL{}), estimate(ShapeM{}), estimate(ShapeM2{}), estimate(ShapeS{}), estimate(ShapeS4{})};
+        for (int i = 0; i < 5; ++i)
+            if (best_t == 0.0 || t[i] < best_t) { best_t = t[i]; best = {i, splits, chunk_tiles * PK}; }
+    }
+    return best;
 }
 
 static size_t wgrad_scratch_bytes(int rows, int batches, int K, int N)
 {
-    int spb, chunk_rows;
-    wgrad_plan(rows, batches, K, N, spb, chunk_rows);
+    const int spb = wgrad_plan(rows, batches, K, N).splits_per_batch;
     return batches * spb > 1 ? (size_t)batches * spb * K * N * sizeof(float) : 0;
+}
+
+template <typename S, bool DC_F32>
+static hipError_t launch_wgrad_shape(WgradArgs &g, hipStream_t st)
+{
+    g.m_tiles = (g.K + S::TM - 1) / S::TM;
+    g.n_tiles = (g.N + S::TN - 1) / S::TN;
+    static std::once_flag once;
+    static hipError_t attr = hipSuccess;
+    const auto kernel = wgrad_gemm_kernel<S, DC_F32>;
+    if (allow_lds(kernel, S::LDS, once, attr) != hipSuccess) return attr;
+    TimedLaunch tl(K_LINEAR_WGRAD, st);
+    hipLaunchKernelGGL(kernel, dim3(xcd_tile_grid(g.batches * g.splits_per_batch, g.m_tiles * g.n_tiles)), dim3(S::NT), S::LDS, st, g);
+    return hipGetLastError();
 }
 
 // g: operands, rows, batches, K, N, strides filled in; dw [K][N]; rows >= 1, batches >= 1
 template <bool DC_F32>
 static hipError_t launch_wgrad(WgradArgs &g, float *dw, float *scratch, hipStream_t st)
 {
-    wgrad_plan(g.rows, g.batches, g.K, g.N, g.splits_per_batch, g.chunk_rows);
+    const WgradPlan p = wgrad_plan(g.rows, g.batches, g.K, g.N);
+    g.splits_per_batch = p.splits_per_batch;
+    g.chunk_rows = p.chunk_rows;
     const int splits = g.batches * g.splits_per_batch;
     g.out = splits > 1 ? scratch : dw;
-    g.m_tiles = (g.K + PM - 1) / PM;
-    g.n_tiles = (g.N + PN - 1) / PN;
-    static std::once_flag once;
-    static hipError_t attr = hipSuccess;
-    std::call_once(once, [] {
-        attr = hipFuncSetAttribute(reinterpret_cast<const void *>(wgrad_gemm_kernel<DC_F32>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-    });
-    if (attr != hipSuccess) return attr;
-    {
-        TimedLaunch tl(K_LINEAR_WGRAD, st);
-        hipLaunchKernelGGL(wgrad_gemm_kernel<DC_F32>, dim3(xcd_grid(splits, g.m_tiles * g.n_tiles)), dim3(P_NT), P_LDS, st, g);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    hipError_t e;
+    switch (p.shape) {
+    case 0: e = launch_wgrad_shape<ShapeL, DC_F32>(g, st); break;
+    case 1: e = launch_wgrad_shape<ShapeM, DC_F32>(g, st); break;
+    case 2: e = launch_wgrad_shape<ShapeM2, DC_F32>(g, st); break;
+    case 3: e = launch_wgrad_shape<ShapeS, DC_F32>(g, st); break;
+    default: e = launch_wgrad_shape<ShapeS4, DC_F32>(g, st); break;
     }
-    if (splits == 1) return hipSuccess;
+    if (e != hipSuccess || splits == 1) return e;
     std::vector<const float *> parts(splits);
     for (int i = 0; i < splits; ++i) parts[i] = scratch + (size_t)i * g.K * g.N;
     return launch_reduce(parts.data(), splits, nullptr, g.K, 1, 1, g.N, dw, st);   // chunk 0 + chunk 1 + ..., in that order
@@ -736,12 +868,12 @@ hipError_t launch_linear_bwd_weight(const bf16_t *a, const bf16_t *dc, int rows,
     return launch_wgrad<false>(g, dw, scratch, st);
 }
 
-// enough for any rows_valid <= l_x: a plan never has more chunks per batch entry than wgrad_want()
+// enough for any rows_valid <= l_x: a plan never has more chunks per batch entry than wgrad_max_chunks()
 size_t project_bwd_weight_scratch_bytes(int l_s, int l_x, int B, int E)
 {
     (void)l_x;
     const size_t q = l_s > 0 ? wgrad_scratch_bytes(l_s, B, E, E) : 0;
-    const size_t kv = (size_t)B * wgrad_want(B, E, 2 * E) * E * 2 * E * sizeof(float);
+    const size_t kv = (size_t)B * wgrad_max_chunks(B, E, 2 * E) * E * 2 * E * sizeof(float);
     return q > kv ? q : kv;
 }
 size_t project_bwd_weight_scratch_needed(int l_s, int rows_valid, int B, int E)
