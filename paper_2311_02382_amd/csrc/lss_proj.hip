@@ -782,23 +782,32 @@ hipError_t launch_linear_bwd_input(const bf16_t *dc, const bf16_t *w, const bf16
     return launch_proj<false, false, false>(args, K_LINEAR_BWD, st);
 }
 
-// Tile and split of the rows for a weight gradient: the pair with the smallest estimated time, the sum of the
-// chunks' partial results (3.5 us and their bytes at 4 TB/s) included; a chunk never crosses batch
-// entries.  Shape-only, deterministic.  There are never more chunks than 512 workgroups of 256 x 256 would
-// take, which bounds the scratch for any number of rows.
-static int wgrad_max_chunks(int batches, int K, int N)      // per batch entry
+// The most chunks of rows a weight gradient is split into, per batch entry: what two 256 x 256 workgroups per
+// compute unit would take (wgrad_max_chunks: for any number of rows), of at least eight 64-row tiles each.
+// The scratch sizes the header promises follow from it.
+static int wgrad_max_chunks(int batches, int K, int N)
 {
     const int tiles = ((K + 255) / 256) * ((N + 255) / 256);
     return ((512 + tiles - 1) / tiles + batches - 1) / batches;
 }
+static int wgrad_most_chunks(int rows, int batches, int K, int N)
+{
+    const int R = (rows + PK - 1) / PK, want = wgrad_max_chunks(batches, K, N);
+    int chunk_tiles = (R + want - 1) / want;
+    if (chunk_tiles < 8) chunk_tiles = R < 8 ? R : 8;
+    return chunk_tiles < 1 ? 1 : (R + chunk_tiles - 1) / chunk_tiles;
+}
+// Tile and split of the rows: the pair with the smallest estimated time, the sum of the chunks' partial results
+// (3.5 us and their bytes at 4 TB/s) included; a chunk never crosses batch entries.  Shape-only,
+// deterministic.
 struct WgradPlan { int shape, splits_per_batch, chunk_rows; };
 static WgradPlan wgrad_plan(int rows, int batches, int K, int N)
 {
-    const int R = (rows + PK - 1) / PK, most = wgrad_max_chunks(batches, K, N);
+    const int R = (rows + PK - 1) / PK, most = wgrad_most_chunks(rows, batches, K, N);
     WgradPlan best{0, 1, PK};
     double best_t = 0.0;
-    for (int want = 1; want <= most && want <= R; want = want < 4 ? want + 1 : want + want / 3) {
-        const int chunk_tiles = (R + want - 1) / want, splits = (R + chunk_tiles - 1) / chunk_tiles;
+    for (int want = 1; want <= most; want = want < 4 ? want + 1 : want + want / 3) {
+        const int chunk_tiles = (R + want - 1) / want, splits = (R + chunk_tiles - 1) / chunk_tiles;      // splits <= want
         const double parts = (double)batches * splits;
         const double sum = parts > 1 ? 3.5 + (parts + 1) * K * N * 4e-6 / 4.0 : 0.0;
         auto estimate = [&](auto shape) {
@@ -815,7 +824,7 @@ static WgradPlan wgrad_plan(int rows, int batches, int K, int N)
 
 static size_t wgrad_scratch_bytes(int rows, int batches, int K, int N)
 {
-    const int spb = wgrad_plan(rows, batches, K, N).splits_per_batch;
+    const int spb = wgrad_most_chunks(rows, batches, K, N);
     return batches * spb > 1 ? (size_t)batches * spb * K * N * sizeof(float) : 0;
 }
 
