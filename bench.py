@@ -54,13 +54,11 @@ PEAK_HBM_GBS = 8000.0          # MI355X HBM3E peak (published)
 # Matrix products each kernel contributes to the strict count (per pair: 2*d flops each).
 # fwd: S and PV.  The backward's main kernel holds two kinds of workgroup: dQ (dP and dQ; it also
 # recomputes S) and dK/dV (dV and dK; it also recomputes S and dP).  Together the six products of
-# the 12*d count.  (bwd_dq_kernel / bwd_dkv_kernel: the fp32 path, which launches them separately.)
-# Names are those of the __global__ functions, as a profiler prints them (bf16: the tuned kernels; fwd_kernel,
-# bwd_dq_kernel, bwd_dkv_kernel: the general kernels that serve --dtype f32, launched separately).
-ALGO_PRODUCTS = {"fwd_bf16_kernel": 2, "bwd_main_bf16_kernel": 4, "fwd_kernel": 2, "bwd_dq_kernel": 2, "bwd_dkv_kernel": 2}
-EXEC_PRODUCTS = {"fwd_bf16_kernel": 2, "bwd_main_bf16_kernel": 7, "fwd_kernel": 2, "bwd_dq_kernel": 3, "bwd_dkv_kernel": 4}
-FWD_KERNELS = ("fwd_bf16_kernel", "fwd_kernel", "fwd_merge_kernel")
-BWD_KERNELS = ("bwd_prep_bf16_kernel", "bwd_rowdot_kernel", "bwd_main_bf16_kernel", "bwd_dq_kernel", "bwd_dkv_kernel",
+# the 12*d count.  Names are those of the __global__ functions, as a profiler prints them (*_f32_kernel: --dtype f32).
+ALGO_PRODUCTS = {"fwd_bf16_kernel": 2, "bwd_main_bf16_kernel": 4, "fwd_f32_kernel": 2, "bwd_main_f32_kernel": 4}
+EXEC_PRODUCTS = {"fwd_bf16_kernel": 2, "bwd_main_bf16_kernel": 7, "fwd_f32_kernel": 2, "bwd_main_f32_kernel": 7}
+FWD_KERNELS = ("fwd_bf16_kernel", "fwd_f32_kernel", "fwd_merge_kernel")
+BWD_KERNELS = ("bwd_prep_bf16_kernel", "bwd_rowdot_kernel", "bwd_main_bf16_kernel", "bwd_main_f32_kernel",
                "bwd_dq_merge_kernel")
 
 
@@ -480,10 +478,10 @@ def attention(args, w, steps, warmup, with_cpu_baseline, min_warm_ms=0.0, min_ti
         # memory, and the roofline is reported against the HBM peak instead.
         eb, bh = (4 if f32 else 2), w.B * w.H
         def alg_bytes(kv):
-            if dom in ("fwd_kernel", "fwd_bf16_kernel"):
+            if dom in ("fwd_f32_kernel", "fwd_bf16_kernel"):
                 return bh * (eb * w.d * (2 * l_s + 2 * kv) + 4 * l_s)
             return bh * (eb * w.d * (4 * l_s + 2 * kv) + 8 * l_s + 8 * w.d * kv)    # backward: also the fp32 partials
-        if dom in ("fwd_kernel", "fwd_bf16_kernel", "bwd_main_bf16_kernel"):
+        if dom in ("fwd_f32_kernel", "fwd_bf16_kernel", "bwd_main_bf16_kernel", "bwd_main_f32_kernel"):
             byts = sum(alg_bytes(rv) for rv in rows_valid) / len(rows_valid)
             roofline["algorithmic_bytes_per_launch"] = byts
             roofline["flop_per_byte"] = round(per_launch / byts, 1)

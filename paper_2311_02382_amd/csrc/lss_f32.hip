@@ -1,0 +1,624 @@
+// Single-precision forward and backward of Eq. 2 (Section 3, Principle 3) for one segment.  The matrix products run
+// on the bf16 matrix cores, every float split into three bf16 parts.
+//
+// A float x is the exact sum of three bf16 numbers: x0 = bf16(x), x1 = bf16(x - x0), x2 = x - x0 - x1 (rounded to
+// nearest, each part takes 8 of the 24 significand bits; both differences are exact).  A product of two
+// floats is then nine products of parts, |x_i y_j| <= 2^-8(i+j) |x y|, each exact in the matrix core's fp32
+// accumulation.  The six with i + j <= 2 are added, smallest first; the three left out are together below 2^-23
+// of |x y|, the size of the rounding an fp32 multiply-add makes at every step, while a matrix instruction here
+// adds 16 products per rounding instead of two.  Relative errors against fp64 (2000 keys, N(0, 1) inputs; in
+// brackets those of V_MFMA_F32_32X32X2_F32, which these kernels used before): out 4.3e-7 (5.9e-7), dq 6.5e-7
+// (6.3e-7), dk 5.5e-7 (7.0e-7), dv 5.3e-7 (6.7e-7); at three times the standard deviation out 1.0e-6 (1.5e-6).
+// What it buys: six V_MFMA_F32_32X32X16_BF16 (192 cycles) do what eight 32x32x2 fp32 ones (512 cycles) did.
+// lx8k in single precision, eight segments: forward 1605 -> 910 us, backward 5460 -> 2750 us.  Each further
+// segment of lx8k costs 64 us backward (1.4 PFLOP/s of executed bf16 products, what the chip sustains on
+// random data); what is left is the chain of a workgroup's tiles in launches that fill the chip once or twice, and
+// in the forward the vector work (splitting costs 5.5 instructions for every float of a tile and every weight).
+//
+// Operand roles, layouts and the online softmax are those of the bf16 kernels: scores transposed with one query
+// per lane in the forward and dQ workgroups, one key per lane in the dK/dV workgroups; K/V (or Q/dO) tiles go
+// global -> registers -> three bf16 planes in LDS (row-major, swizzled), from where the products over tile rows
+// read them transposed.  Two workgroups share a compute unit: one splits and stores a tile while the other
+// multiplies.
+#include "lss_bf16.h"
+#include "lss_kernels.h"
+
+#include <type_traits>
+
+namespace lss {
+
+namespace {
+
+struct Frag3 { Frag<bf16_t> p[3]; };            // the three parts of one operand fragment
+
+// Pairs at a time, through the bits: one packed conversion per pair and part, 5.5 vector instructions per element
+// (converted one by one, the parts that are needed as floats again take a conversion each: 7.5).
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t round_pair(float a, float b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+__device__ __forceinline__ float low_of(uint32_t pair) { return __builtin_bit_cast(float, pair << 16); }
+__device__ __forceinline__ float high_of(uint32_t pair) { return __builtin_bit_cast(float, pair & 0xffff0000u); }
+__device__ __forceinline__ Frag3 split8(const float (&x)[8])
+{
+    u32x4 part[3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t b0 = round_pair(x[2 * i], x[2 * i + 1]);
+        const float r0 = x[2 * i] - low_of(b0), r1 = x[2 * i + 1] - high_of(b0);
+        const uint32_t b1 = round_pair(r0, r1);
+        part[0][i] = b0;
+        part[1][i] = b1;
+        part[2][i] = round_pair(r0 - low_of(b1), r1 - high_of(b1));
+    }
+    Frag3 f;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) f.p[p].v = __builtin_bit_cast(bf16x8, part[p]);
+    return f;
+}
+__device__ __forceinline__ Frag3 split_global(const float *p)      // 8 consecutive floats
+{
+    const f32x4 lo = *reinterpret_cast<const f32x4 *>(p), hi = *reinterpret_cast<const f32x4 *>(p + 4);
+    const float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return split8(x);
+}
+__device__ __forceinline__ Frag3 split_acc(const f32x16 &c, int half)      // slots 8 half .. of a C tile
+{
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = c[8 * half + e];
+    return split8(x);
+}
+__device__ __forceinline__ f32x16 mma_small(const Frag3 &a, const Frag3 &b, f32x16 c)       // the five products below x0 y0
+{
+    c = mma(a.p[2], b.p[0], c);
+    c = mma(a.p[0], b.p[2], c);
+    c = mma(a.p[1], b.p[1], c);
+    c = mma(a.p[1], b.p[0], c);
+    return mma(a.p[0], b.p[1], c);
+}
+__device__ __forceinline__ f32x16 mma6(const Frag3 &a, const Frag3 &b, f32x16 c)
+{
+    return mma(a.p[0], b.p[0], mma_small(a, b, c));
+}
+
+// A [ROWS][D] float tile as three bf16 planes in LDS, each laid out like a DirectTile<D, ROWS>.
+template <int D>
+struct PlaneTile {
+    static constexpr int ROWS = D == 64 ? 64 : 32;      // two tensors' planes: 48 KB
+    static constexpr int CPR = D / 8, NT = 256, CHUNKS = ROWS * CPR / NT;       // 8-element chunks per row; per thread
+    static constexpr int PLANE = ROWS * D * 2, BYTES = 3 * PLANE;
+    static_assert(ROWS * CPR % NT == 0, "");
+    static __device__ __forceinline__ int chunk_offset(int r, int c) { return r * (D * 2) + ((c ^ tile_swizzle<D>(r)) * 16); }
+    struct Regs { f32x4 v[2 * CHUNKS]; };
+    // rows >= rows_ok re-read row rows_ok - 1 (the kernels mask or discard what they produce)
+    static __device__ __forceinline__ void fetch(Regs &g, const float *base, int64_t ld, int rows_ok, int tid)
+    {
+#pragma unroll
+        for (int i = 0; i < CHUNKS; ++i) {
+            const int c = i * NT + tid;
+            const f32x4 *p = reinterpret_cast<const f32x4 *>(base + (int64_t)min(c / CPR, rows_ok - 1) * ld + (c % CPR) * 8);
+            g.v[2 * i] = p[0];
+            g.v[2 * i + 1] = p[1];
+        }
+    }
+    static __device__ __forceinline__ void store(char *tile, const Regs &g, int tid)
+    {
+#pragma unroll
+        for (int i = 0; i < CHUNKS; ++i) {
+            const int c = i * NT + tid;
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { x[e] = g.v[2 * i][e]; x[4 + e] = g.v[2 * i + 1][e]; }
+            const Frag3 f = split8(x);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x8 *>(tile + p * PLANE + chunk_offset(c / CPR, c % CPR)) = f.p[p].v;
+        }
+    }
+    // A-operand fragment of rows [row0, row0 + 32), operand step kb
+    static __device__ __forceinline__ Frag3 rows_frag(const char *tile, int row0, int off)
+    {
+        Frag3 f;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) f.p[p] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(tile + p * PLANE + row0 * (D * 2) + off));
+        return f;
+    }
+    static __device__ __forceinline__ Frag<bf16_t> rows_frag_high(const char *tile, int row0, int off)
+    {
+        return load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(tile + row0 * (D * 2) + off));
+    }
+    // C tile of 32 tile rows against the operand `b` over the whole width: every step's small products first, the
+    // large ones at the end, so that the sum is rounded at its full size D / 16 times and not six times as often
+    // (scores and dP enter differences of large terms).  The large products read the first plane again.
+    static __device__ __forceinline__ f32x16 product(const char *tile, int row0, const int (&off)[D / 16], const Frag3 (&b)[D / 16])
+    {
+        f32x16 c = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kb = 0; kb < D / 16; ++kb) c = mma_small(rows_frag(tile, row0, off[kb]), b[kb], c);
+#pragma unroll
+        for (int kb = 0; kb < D / 16; ++kb) c = mma(rows_frag_high(tile, row0, off[kb]), b[kb].p[0], c);
+        return c;
+    }
+    // ... of the transposed tile: rows [row0, row0 + 16) are the contraction slots (load_frag_tr_sw)
+    static __device__ __forceinline__ Frag3 cols_frag(const char *tile, int row0, int off)
+    {
+        Frag3 f;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) f.p[p] = load_frag_tr_sw<D>(tile + p * PLANE, row0, off);
+        return f;
+    }
+};
+
+constexpr int kRowsPerWg = 128;             // query rows of a workgroup: four wavefronts of 32
+// Keys of a dK/dV workgroup: 128, a block of 32 per wavefront; or (HALVES = 2, d = 64) two blocks of 32, each held by
+// two wavefronts that take one of the two 32-row halves of every Q/dO tile and add their results up at the end --
+// twice as many workgroups, with chains half as long, for launches that do not fill the chip.
+template <int HALVES> constexpr int kKeysPerWg = 128 / HALVES;
+
+__device__ __forceinline__ void clear(f32x16 &a)
+{
+#pragma unroll
+    for (int e = 0; e < 16; ++e) a[e] = 0.f;
+}
+
+// ------------------------------------------------------------------------------------------ forward
+template <int D, bool DROP>
+__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_f32_kernel(SegShape s, DropArgs dr, const float *__restrict__ q,
+                                                         const float *__restrict__ k, const float *__restrict__ v,
+                                                         float *__restrict__ out, float *__restrict__ lse,
+                                                         float *__restrict__ o_part, float *__restrict__ lse_part, int n_splits,
+                                                         int n_q_tiles)
+{
+    using Tile = PlaneTile<D>;
+    constexpr int NU = D / 16, BC = Tile::ROWS;
+    __shared__ __attribute__((aligned(1024))) char smem[2 * Tile::BYTES];
+    char *const sk = smem, *const sv = smem + Tile::BYTES;
+
+    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bhs = s.B * s.H;
+    int bh, inner;
+    if (!xcd_item(blockIdx.x, bhs, n_q_tiles * n_splits, bh, inner)) return;
+    const int b = bh / s.H, h = bh % s.H, split = inner / n_q_tiles;
+    const int r0 = (n_q_tiles - 1 - inner % n_q_tiles) * kRowsPerWg, rw0 = r0 + wave * 32;
+    const int64_t ld = (int64_t)s.H * D;
+
+    // the keys any row of this tile sees, and this split's share of their tiles
+    const int r_last = min(r0 + kRowsPerWg, s.l_s) - 1;
+    const int kv_end = s.causal ? (int)min<int64_t>(s.l_x, s.s0 + r_last + 1) : s.l_x;
+    const int n_tiles = (kv_end + BC - 1) / BC, per = (n_tiles + n_splits - 1) / n_splits;
+    const int t_begin = split * per, t_end = min(n_tiles, t_begin + per);
+
+    // this lane's query row; rows past the segment re-read its last row and are never stored
+    const int r = rw0 + lq;
+    const bool row_ok = r < s.l_s;
+    Frag3 qf[NU];
+    {
+        const float *qp = q + ((int64_t)b * s.l_s + min(r, s.l_s - 1)) * ld + (int64_t)h * D + hh * 8;
+#pragma unroll
+        for (int kb = 0; kb < NU; ++kb) qf[kb] = split_global(qp + kb * 16);
+    }
+    f32x16 o[D / 32];
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) clear(o[db]);
+    float m = -INFINITY, l = 0.f;               // running maximum (log2 domain); this lane's half of the row sum
+    const float c = kLog2e / sqrtf((float)D);
+    uint32_t drop_rk = 0u, drop_cs = 0u;
+    if (DROP) { drop_rk = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + r)); drop_cs = drop_col_seed(dr.seed_hi); }
+
+    const float *kbase = k + (int64_t)b * s.l_x * ld + (int64_t)h * D, *vbase = v + (int64_t)b * s.l_x * ld + (int64_t)h * D;
+    int a_off[NU], t_off[D / 32];
+#pragma unroll
+    for (int kb = 0; kb < NU; ++kb) a_off[kb] = Tile::chunk_offset(lq, 2 * kb + hh);
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) t_off[db] = tr_lane_offset_sw<D>(lane, db);
+
+    for (int t = t_begin; t < t_end; ++t) {
+        {
+            typename Tile::Regs gk, gv;
+            Tile::fetch(gk, kbase + (int64_t)t * BC * ld, ld, s.l_x - t * BC, tid);
+            Tile::fetch(gv, vbase + (int64_t)t * BC * ld, ld, s.l_x - t * BC, tid);
+            __syncthreads();                    // the tile before has been read
+            Tile::store(sk, gk, tid);
+            Tile::store(sv, gv, tid);
+        }
+        __syncthreads();
+        if (rw0 >= s.l_s) continue;             // none of this wavefront's rows exists
+#pragma unroll
+        for (int kb2 = 0; kb2 < BC / 32; ++kb2) {
+            const int jb = t * BC + kb2 * 32;
+            // a block no row of this wavefront sees
+            if (jb >= s.l_x || (s.causal && jb > (int)s.s0 + rw0 + 31)) continue;
+            f32x16 sc = Tile::product(sk, kb2 * 32, a_off, qf);
+            // element e of this lane is key jb + 8 (e / 4) + 4 hh + e % 4
+            if ((s.causal && jb + 31 > (int)s.s0 + rw0) || jb + 32 > s.l_x) {
+                const int last = s.causal ? min((int)s.s0 + r, s.l_x - 1) : s.l_x - 1, rel = last - jb - 4 * hh;
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (8 * (e >> 2) + (e & 3) > rel) sc[e] = -INFINITY;
+            }
+            float mx = sc[0];
+#pragma unroll
+            for (int e = 1; e < 16; ++e) mx = fmaxf(mx, sc[e]);
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float m_new = fmaxf(m, mx * c);
+            if (__any(m_new > m)) {             // some row's maximum rises: rescale what was accumulated
+                const float alpha = m == -INFINITY ? 0.f : fast_exp2(m - m_new);
+                l *= alpha;
+#pragma unroll
+                for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
+                m = m_new;
+            }
+            const float m_use = m == -INFINITY ? 0.f : m;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float p = fast_exp2(sc[e] * c - m_use);
+                l += p;             // the row sum (hence lse and the normalisation) is that of the softmax
+                if (DROP) {
+                    const int key = jb + 8 * (e >> 2) + 4 * hh + (e & 3);
+                    sc[e] = drop_keep(drop_rk, drop_col_key(drop_cs, (uint32_t)key), dr.thr) ? p * dr.scale : 0.f;
+                } else {
+                    sc[e] = p;
+                }
+            }
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const Frag3 pf = split_acc(sc, half);
+#pragma unroll
+                for (int db = 0; db < D / 32; ++db) o[db] = mma6(Tile::cols_frag(sv, kb2 * 32 + half * 16, t_off[db]), pf, o[db]);
+            }
+        }
+    }
+
+    const float l_tot = l + __shfl_xor(l, 32);
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    const float lse_nat = l_tot > 0.f ? (m + log2f(l_tot)) * kLn2 : -INFINITY;
+    if (!row_ok) return;
+    const int64_t row = ((int64_t)split * bhs + bh) * s.l_s + r;
+    float *op = n_splits == 1 ? out + ((int64_t)b * s.l_s + r) * ld + (int64_t)h * D : o_part + row * D;
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4)
+            *reinterpret_cast<f32x4 *>(op + db * 32 + 8 * e4 + 4 * hh) =
+                f32x4{o[db][4 * e4] * inv, o[db][4 * e4 + 1] * inv, o[db][4 * e4 + 2] * inv, o[db][4 * e4 + 3] * inv};
+    if (hh == 0) {
+        if (n_splits == 1) lse[(int64_t)bh * s.l_s + r] = lse_nat;
+        else lse_part[row] = lse_nat;
+    }
+}
+
+// ------------------------------------------------------------------------------------------ dQ
+// S^T = K Q^T, dP^T = V dO^T, dS = P (dP - D) (dropout: P (M dP - D)), dQ^T += K^T dS^T.
+template <int D, bool DROP>
+__device__ __forceinline__ void bwd_dq_f32_body(char *smem, const SegShape &s, const DropArgs &dr, const float *__restrict__ q,
+                                                const float *__restrict__ k, const float *__restrict__ v,
+                                                const float *__restrict__ dO, const float *__restrict__ lse,
+                                                const float *__restrict__ Dv, float *__restrict__ dq, float *__restrict__ dq_part,
+                                                int n_splits, int q_tile, int n_q_tiles, int bh, int split)
+{
+    using Tile = PlaneTile<D>;
+    constexpr int NU = D / 16, BC = Tile::ROWS;
+    char *const sk = smem, *const sv = smem + Tile::BYTES;
+    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = bh / s.H, h = bh % s.H;
+    const int r0 = (n_q_tiles - 1 - q_tile) * kRowsPerWg, rw0 = r0 + wave * 32;
+    const int64_t ld = (int64_t)s.H * D;
+    const int r_last = min(r0 + kRowsPerWg, s.l_s) - 1;
+    const int kv_end = s.causal ? (int)min<int64_t>(s.l_x, s.s0 + r_last + 1) : s.l_x;
+    const int n_tiles = (kv_end + BC - 1) / BC, per = (n_tiles + n_splits - 1) / n_splits;
+    const int t_begin = split * per, t_end = min(n_tiles, t_begin + per);
+
+    // rows past the segment re-read its last row, get lse = +inf (P = dS = 0) and are never stored
+    const int r = rw0 + lq, rc = min(r, s.l_s - 1);
+    const bool row_ok = r < s.l_s;
+    Frag3 qf[NU], gf[NU];
+    {
+        const int64_t off = ((int64_t)b * s.l_s + rc) * ld + (int64_t)h * D + hh * 8;
+#pragma unroll
+        for (int kb = 0; kb < NU; ++kb) { qf[kb] = split_global(q + off + kb * 16); gf[kb] = split_global(dO + off + kb * 16); }
+    }
+    if constexpr (D == 128) {       // (operands live in the accumulation half of the register file: see the bf16 dK/dV workgroups)
+#pragma unroll
+        for (int kb = 0; kb < NU; ++kb)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) { asm volatile("" : "+a"(qf[kb].p[p].v)); asm volatile("" : "+a"(gf[kb].p[p].v)); }
+    }
+    const float L2 = row_ok ? lse[(int64_t)bh * s.l_s + rc] * kLog2e : INFINITY;
+    const float Dr = Dv[(int64_t)bh * s.l_s + rc];
+    const float c = kLog2e / sqrtf((float)D);
+    uint32_t drop_rk = 0u, drop_cs = 0u;
+    if (DROP) { drop_rk = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + r)); drop_cs = drop_col_seed(dr.seed_hi); }
+
+    f32x16 acc[D / 32];
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) clear(acc[db]);
+    const float *kbase = k + (int64_t)b * s.l_x * ld + (int64_t)h * D, *vbase = v + (int64_t)b * s.l_x * ld + (int64_t)h * D;
+    int a_off[NU], t_off[D / 32];
+#pragma unroll
+    for (int kb = 0; kb < NU; ++kb) a_off[kb] = Tile::chunk_offset(lq, 2 * kb + hh);
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) t_off[db] = tr_lane_offset_sw<D>(lane, db);
+
+    for (int t = t_begin; t < t_end; ++t) {
+        const int j0 = t * BC;
+        typename Tile::Regs gk, gv;
+        Tile::fetch(gk, kbase + (int64_t)j0 * ld, ld, s.l_x - j0, tid);
+        Tile::fetch(gv, vbase + (int64_t)j0 * ld, ld, s.l_x - j0, tid);
+        __syncthreads();
+        Tile::store(sk, gk, tid);
+        Tile::store(sv, gv, tid);
+        __syncthreads();
+        if (rw0 >= s.l_s) continue;
+#pragma unroll
+        for (int kb2 = 0; kb2 < BC / 32; ++kb2) {
+            const int jb = j0 + kb2 * 32;
+            if (jb >= s.l_x || (s.causal && jb > (int)s.s0 + rw0 + 31)) continue;
+            f32x16 sc = Tile::product(sk, kb2 * 32, a_off, qf), dp = Tile::product(sv, kb2 * 32, a_off, gf);
+            if ((s.causal && jb + 31 > (int)s.s0 + rw0) || jb + 32 > s.l_x) {
+                const int last = s.causal ? min((int)s.s0 + r, s.l_x - 1) : s.l_x - 1, rel = last - jb - 4 * hh;
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (8 * (e >> 2) + (e & 3) > rel) sc[e] = -INFINITY;
+            }
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float p = fast_exp2(sc[e] * c - L2);
+                float dpe = dp[e];
+                if (DROP) {
+                    const int key = jb + 8 * (e >> 2) + 4 * hh + (e & 3);
+                    dpe = drop_keep(drop_rk, drop_col_key(drop_cs, (uint32_t)key), dr.thr) ? dpe * dr.scale : 0.f;
+                }
+                dp[e] = p * (dpe - Dr);
+            }
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const Frag3 df = split_acc(dp, half);
+#pragma unroll
+                for (int db = 0; db < D / 32; ++db) acc[db] = mma6(Tile::cols_frag(sk, kb2 * 32 + half * 16, t_off[db]), df, acc[db]);
+            }
+        }
+    }
+    if (!row_ok) return;
+    const float scale = 1.f / sqrtf((float)D);
+    float *dst = (n_splits == 1 ? dq : dq_part + (int64_t)split * s.B * s.l_s * ld) + ((int64_t)b * s.l_s + r) * ld + (int64_t)h * D;
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4)
+            *reinterpret_cast<f32x4 *>(dst + db * 32 + 8 * e4 + 4 * hh) =
+                f32x4{acc[db][4 * e4] * scale, acc[db][4 * e4 + 1] * scale, acc[db][4 * e4 + 2] * scale, acc[db][4 * e4 + 3] * scale};
+}
+
+// ------------------------------------------------------------------------------------------ dK, dV
+// Key-owned: S = Q K^T, dP = dO V^T over the query tiles that see the keys, then dV^T += dO^T P, dK^T += Q^T dS.
+template <int D, bool DROP, int HALVES>
+__device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, const DropArgs &dr, const float *__restrict__ q,
+                                                 const float *__restrict__ k, const float *__restrict__ v,
+                                                 const float *__restrict__ dO, const float *__restrict__ lse,
+                                                 const float *__restrict__ Dv, float *__restrict__ dk_part,
+                                                 float *__restrict__ dv_part, int bh, int key_tile)
+{
+    using Tile = PlaneTile<D>;
+    constexpr int NU = D / 16, BQ = Tile::ROWS;
+    char *const sq = smem, *const sg = smem + Tile::BYTES;
+    float *const sl = reinterpret_cast<float *>(smem + 2 * Tile::BYTES), *const sd = sl + 64;
+    uint32_t *const sr = reinterpret_cast<uint32_t *>(sd + 64);
+    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = bh / s.H, h = bh % s.H;
+    constexpr int KEYS = kKeysPerWg<HALVES>;
+    static_assert(HALVES == 1 || BQ == 64, "");
+    const int key_block = wave / HALVES, my_half = wave % HALVES;
+    const int j0 = key_tile * KEYS, jw0 = j0 + key_block * 32, j = jw0 + lq;
+    const int64_t ld = (int64_t)s.H * D, kv_base = (int64_t)b * s.l_x * ld + (int64_t)h * D;
+
+    if (s.causal && j0 >= s.s0 + s.l_s) {       // no query of the segment sees this tile: zeros, or (whole 128-key tiles) left unwritten
+        if (s.skip_tail && j0 / 128 * 128 >= s.s0 + s.l_s) return;
+        constexpr int F4 = D / 4;
+        for (int i = tid; i < KEYS * F4; i += 256) {
+            const int row = j0 + i / F4, c4 = (i % F4) * 4;
+            if (row < s.l_x) {
+                *reinterpret_cast<f32x4 *>(dk_part + kv_base + (int64_t)row * ld + c4) = f32x4{0.f, 0.f, 0.f, 0.f};
+                *reinterpret_cast<f32x4 *>(dv_part + kv_base + (int64_t)row * ld + c4) = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+        return;
+    }
+    // first query row that sees any key of this tile
+    int rq_begin = 0;
+    if (s.causal) rq_begin = (int)min<int64_t>(max<int64_t>((int64_t)j0 - s.s0, 0), s.l_s) / BQ * BQ;
+
+    // this lane's key; keys past the sequence re-read its last row and are never stored
+    Frag3 kf[NU], vf[NU];
+    {
+        const int64_t off = kv_base + (int64_t)min(j, s.l_x - 1) * ld + hh * 8;
+#pragma unroll
+        for (int kb = 0; kb < NU; ++kb) { kf[kb] = split_global(k + off + kb * 16); vf[kb] = split_global(v + off + kb * 16); }
+    }
+    if constexpr (D == 128) {
+#pragma unroll
+        for (int kb = 0; kb < NU; ++kb)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) { asm volatile("" : "+a"(kf[kb].p[p].v)); asm volatile("" : "+a"(vf[kb].p[p].v)); }
+    }
+    f32x16 dk[D / 32], dv[D / 32];
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) { clear(dk[db]); clear(dv[db]); }
+    const float c = kLog2e / sqrtf((float)D);
+    const float *qbase = q + (int64_t)b * s.l_s * ld + (int64_t)h * D, *gbase = dO + (int64_t)b * s.l_s * ld + (int64_t)h * D;
+    const uint32_t drop_ck = DROP ? drop_col_key(drop_col_seed(dr.seed_hi), (uint32_t)j) : 0u;
+    int a_off[NU], t_off[D / 32];
+#pragma unroll
+    for (int kb = 0; kb < NU; ++kb) a_off[kb] = Tile::chunk_offset(lq, 2 * kb + hh);
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) t_off[db] = tr_lane_offset_sw<D>(lane, db);
+
+    for (int rq0 = rq_begin; rq0 < s.l_s; rq0 += BQ) {
+        typename Tile::Regs gq, gg;
+        Tile::fetch(gq, qbase + (int64_t)rq0 * ld, ld, s.l_s - rq0, tid);
+        Tile::fetch(gg, gbase + (int64_t)rq0 * ld, ld, s.l_s - rq0, tid);
+        __syncthreads();
+        Tile::store(sq, gq, tid);
+        Tile::store(sg, gg, tid);
+        if (tid < BQ) {     // rows past the segment: lse = +inf makes P (hence dS) exactly 0
+            const int rr = rq0 + tid;
+            sl[tid] = rr < s.l_s ? lse[(int64_t)bh * s.l_s + rr] * kLog2e : INFINITY;
+            sd[tid] = rr < s.l_s ? Dv[(int64_t)bh * s.l_s + rr] : 0.f;
+            if (DROP) sr[tid] = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + rr));
+        }
+        __syncthreads();
+#pragma unroll
+        for (int qi = 0; qi < BQ / 32 / HALVES; ++qi) {
+            const int qb = HALVES == 1 ? qi : my_half;
+            const int rb = rq0 + 32 * qb;
+            // a block none of whose rows sees a key of this wavefront, or past the segment
+            if (rb >= s.l_s || (s.causal && (int)s.s0 + rb + 31 < jw0)) continue;
+            f32x16 sc = Tile::product(sq, qb * 32, a_off, kf), dp = Tile::product(sg, qb * 32, a_off, vf);
+            const bool diag = s.causal && jw0 + 31 > (int)s.s0 + rb;
+            // element e of this lane is row rb + 8 (e / 4) + 4 hh + e % 4
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) {
+                const int rl = qb * 32 + 8 * e4 + 4 * hh;
+                const f32x4 l4 = *reinterpret_cast<const f32x4 *>(sl + rl), d4 = *reinterpret_cast<const f32x4 *>(sd + rl);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int e = 4 * e4 + i;
+                    float p = fast_exp2(sc[e] * c - l4[i]);
+                    if (diag && j > (int)s.s0 + rq0 + rl + i) p = 0.f;
+                    float pv = p, dpe = dp[e];
+                    if (DROP) {
+                        const float mk = drop_keep(sr[rl + i], drop_ck, dr.thr) ? dr.scale : 0.f;
+                        pv = p * mk;
+                        dpe *= mk;
+                    }
+                    sc[e] = pv;
+                    dp[e] = p * (dpe - d4[i]);
+                }
+            }
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const Frag3 pf = split_acc(sc, half), df = split_acc(dp, half);
+#pragma unroll
+                for (int db = 0; db < D / 32; ++db) {
+                    dv[db] = mma6(Tile::cols_frag(sg, qb * 32 + half * 16, t_off[db]), pf, dv[db]);
+                    dk[db] = mma6(Tile::cols_frag(sq, qb * 32 + half * 16, t_off[db]), df, dk[db]);
+                }
+            }
+        }
+    }
+    if constexpr (HALVES == 2) {        // second half's results -> first half's wavefront, through the planes' LDS
+        static_assert(2 * 2 * (D / 32) * 4096 <= 2 * Tile::BYTES, "");
+        __syncthreads();
+        auto at = [&](int blk, int e4) { return reinterpret_cast<f32x4 *>(smem + ((key_block * 2 * (D / 32) + blk) * 4 + e4) * 1024 + lane * 16); };
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4)
+                if (my_half == 1) {
+                    *at(2 * db, e4) = f32x4{dk[db][4 * e4], dk[db][4 * e4 + 1], dk[db][4 * e4 + 2], dk[db][4 * e4 + 3]};
+                    *at(2 * db + 1, e4) = f32x4{dv[db][4 * e4], dv[db][4 * e4 + 1], dv[db][4 * e4 + 2], dv[db][4 * e4 + 3]};
+                }
+        __syncthreads();
+        if (my_half == 1) return;
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) {
+                const f32x4 a = *at(2 * db, e4), g = *at(2 * db + 1, e4);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { dk[db][4 * e4 + i] += a[i]; dv[db][4 * e4 + i] += g[i]; }
+            }
+    }
+    if (j >= s.l_x) return;
+    const float scale = 1.f / sqrtf((float)D);
+    const int64_t off = kv_base + (int64_t)j * ld;
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {
+            const int col = db * 32 + 8 * e4 + 4 * hh;
+            *reinterpret_cast<f32x4 *>(dk_part + off + col) =
+                f32x4{dk[db][4 * e4] * scale, dk[db][4 * e4 + 1] * scale, dk[db][4 * e4 + 2] * scale, dk[db][4 * e4 + 3] * scale};
+            *reinterpret_cast<f32x4 *>(dv_part + off + col) = f32x4{dv[db][4 * e4], dv[db][4 * e4 + 1], dv[db][4 * e4 + 2], dv[db][4 * e4 + 3]};
+        }
+}
+
+// Both kinds of workgroup in one launch, dQ first, in XCD order: see bwd_main_bf16_kernel.
+template <int D, bool DROP, int HALVES>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_main_f32_kernel(
+    SegShape s, DropArgs dr, const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
+    const float *__restrict__ dO, const float *__restrict__ lse, const float *__restrict__ Dv, float *__restrict__ dq,
+    float *__restrict__ dq_part, float *__restrict__ dk_part, float *__restrict__ dv_part, int n_splits, int n_dq, int n_q_tiles,
+    int n_key_tiles)
+{
+    __shared__ __attribute__((aligned(1024))) char smem[2 * PlaneTile<D>::BYTES + 3 * 64 * 4];
+    const int bhs = s.B * s.H, id = blockIdx.x;
+    int bh, inner;
+    if (id >= n_dq) {
+        if (!xcd_item(id - n_dq, bhs, n_key_tiles, bh, inner)) return;
+        bwd_dkv_f32_body<D, DROP, HALVES>(smem, s, dr, q, k, v, dO, lse, Dv, dk_part, dv_part, bh, inner);
+    } else {
+        if (!xcd_item(id, bhs, n_q_tiles * n_splits, bh, inner)) return;
+        bwd_dq_f32_body<D, DROP>(smem, s, dr, q, k, v, dO, lse, Dv, dq, dq_part, n_splits, inner % n_q_tiles, n_q_tiles, bh,
+                                 inner / n_q_tiles);
+    }
+}
+
+template <int D>
+hipError_t launch_fwd_d(const SegShape &s, const DropArgs &dr, const float *q, const float *k, const float *v, float *out,
+                        float *lse, const Workspace &ws, int n_splits, hipStream_t st)
+{
+    const int n_q_tiles = (s.l_s + kRowsPerWg - 1) / kRowsPerWg;
+    const auto kernel = dr.thr != 0 ? fwd_f32_kernel<D, true> : fwd_f32_kernel<D, false>;
+    TimedLaunch tl(K_FWD_F32, st);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)xcd_grid(s.B * s.H, n_q_tiles * n_splits)), dim3(256), 0, st, s, dr, q, k, v, out, lse,
+                       ws.o_part, ws.lse_part, n_splits, n_q_tiles);
+    return hipGetLastError();
+}
+template <int D>
+hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const float *q, const float *k, const float *v, const float *lse,
+                        const float *dO, float *dq, float *dk_part, float *dv_part, const Workspace &ws, int n_splits, hipStream_t st)
+{
+    // two wavefronts per key block while the key tiles that do work fit the chip about once (two workgroups per
+    // compute unit): lx8k's first segment takes 90 us instead of 150, its fifth as long either way, later ones
+    // would lose 2 %
+    const int64_t seen = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
+    const bool halves = D == 64 && (seen + 127) / 128 * s.B * s.H <= 640;
+    const int keys = halves ? 64 : 128, n_q_tiles = (s.l_s + kRowsPerWg - 1) / kRowsPerWg, n_key_tiles = (s.l_x + keys - 1) / keys;
+    const int n_dq = xcd_grid(s.B * s.H, n_q_tiles * n_splits), n_dkv = xcd_grid(s.B * s.H, n_key_tiles);
+    constexpr int H2 = D == 64 ? 2 : 1;
+    const auto kernel = dr.thr != 0 ? (halves ? bwd_main_f32_kernel<D, true, H2> : bwd_main_f32_kernel<D, true, 1>)
+                                    : (halves ? bwd_main_f32_kernel<D, false, H2> : bwd_main_f32_kernel<D, false, 1>);
+    TimedLaunch tl(K_BWD_MAIN_F32, st);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_dq + n_dkv)), dim3(256), 0, st, s, dr, q, k, v, dO, lse, ws.D, dq, ws.dq_part, dk_part,
+                       dv_part, n_splits, n_dq, n_q_tiles, n_key_tiles);
+    return hipGetLastError();
+}
+
+} // namespace
+
+int f32_rows_per_workgroup() { return kRowsPerWg; }
+
+hipError_t launch_fwd_f32_main(const SegShape &s, const DropArgs &drop, const float *q, const float *k, const float *v, float *out,
+                               float *lse, const Workspace &ws, int n_splits, hipStream_t st)
+{
+    if (s.d == 64) return launch_fwd_d<64>(s, drop, q, k, v, out, lse, ws, n_splits, st);
+    return launch_fwd_d<128>(s, drop, q, k, v, out, lse, ws, n_splits, st);
+}
+
+// dQ and the dK/dV partials in one launch; the caller has run the row-dot kernel and runs the dQ split merge
+hipError_t launch_bwd_f32_main(const SegShape &s, const DropArgs &drop, const float *q, const float *k, const float *v,
+                               const float *lse, const float *dO, float *dq, float *dk_part, float *dv_part, const Workspace &ws,
+                               int n_splits, hipStream_t st)
+{
+    if (s.d == 64) return launch_bwd_d<64>(s, drop, q, k, v, lse, dO, dq, dk_part, dv_part, ws, n_splits, st);
+    return launch_bwd_d<128>(s, drop, q, k, v, lse, dO, dq, dk_part, dv_part, ws, n_splits, st);
+}
+
+} // namespace lss

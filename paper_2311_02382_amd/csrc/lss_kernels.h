@@ -33,8 +33,7 @@ int choose_splits(int l_s, int l_x, int B, int H, int rows_per_wg);
 // Forward: the largest split count the workspace is sized for (shape-only), and the count a launch
 // uses for the `kv_tiles` 64-key tiles its query tiles actually see (never above the former).
 int max_fwd_splits(int l_s, int l_x, int B, int H, int rows_per_wg);
-int pick_fwd_splits(int l_s, int B, int H, int rows_per_wg, int64_t kv_tiles, int max_splits, int resident);
-int fwd_wgs_per_cu(int elem_bytes, int d);      // forward workgroups a compute unit holds at once ("resident")
+int pick_fwd_splits(int l_s, int B, int H, int rows_per_wg, int64_t kv_tiles, int max_splits, int elem_bytes, int d);
 int fwd_rows_per_wg(int elem_bytes, int d);     // query rows per workgroup of the forward kernel
 int dq_rows_per_wg(int elem_bytes, int d);      // ... and of the dQ kernel
 
@@ -66,6 +65,14 @@ int fwd_bf16_rows_per_workgroup(int d);
 hipError_t launch_fwd_bf16_main(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                 const bf16_t *v, bf16_t *out, float *lse, const Workspace &ws, int n_splits, hipStream_t st);
 
+// single-precision kernels (lss_f32.hip); ws.D holds rowsum(dO * out)
+int f32_rows_per_workgroup();
+hipError_t launch_fwd_f32_main(const SegShape &s, const DropArgs &drop, const float *q, const float *k, const float *v, float *out,
+                               float *lse, const Workspace &ws, int n_splits, hipStream_t st);
+hipError_t launch_bwd_f32_main(const SegShape &s, const DropArgs &drop, const float *q, const float *k, const float *v,
+                               const float *lse, const float *dO, float *dq, float *dk_part, float *dv_part, const Workspace &ws,
+                               int n_splits, hipStream_t st);
+
 // tuned bf16 kernels (lss_bwd_bf16.hip): dQ kernel (also writes D = rowsum(dO * out)) then dK/dV kernel
 int dq_bf16_rows_per_workgroup(int d);
 hipError_t launch_bwd_bf16_main(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
@@ -75,7 +82,7 @@ hipError_t launch_bwd_bf16_main(const SegShape &s, const DropArgs &drop, const b
 // Optional per-kernel timing for benchmarks (lss_timing.h): when enabled, every launch site
 // brackets its kernel with a pair of HIP events on the launch stream.  One id per __global__
 // function (per role where several entry points share one).
-enum KernelId { K_FWD = 0, K_FWD_MERGE, K_ROWDOT, K_DQ, K_DQ_MERGE, K_DKV, K_REDUCE, K_BWD_MAIN_BF16, K_PROJ_FWD, K_PROJ_BWD,
+enum KernelId { K_FWD_F32 = 0, K_FWD_MERGE, K_ROWDOT, K_BWD_MAIN_F32, K_DQ_MERGE, K_REDUCE, K_BWD_MAIN_BF16, K_PROJ_FWD, K_PROJ_BWD,
                 K_PE_FWD, K_PE_BWD, K_LN_FWD, K_LN_BWD, K_LN_PARAMS, K_GELU_FWD, K_GELU_BWD, K_LINEAR_FWD, K_LINEAR_BWD, K_RESIDUAL, K_LINEAR_WGRAD,
                 K_FWD_BF16, K_BWD_PREP_BF16, K_COUNT };
 void timing_begin(int id, hipStream_t st);

@@ -22,8 +22,8 @@ double g_total_ms[K_COUNT] = {0};
 int64_t g_count[K_COUNT] = {0};
 
 // the __global__ function each id stands for; ":role" where entry points share one function
-const char *const kNames[K_COUNT] = {"fwd_kernel", "fwd_merge_kernel", "bwd_rowdot_kernel", "bwd_dq_kernel",
-                                     "bwd_dq_merge_kernel", "bwd_dkv_kernel", "reduce_partials_kernel",
+const char *const kNames[K_COUNT] = {"fwd_f32_kernel", "fwd_merge_kernel", "bwd_rowdot_kernel", "bwd_main_f32_kernel",
+                                     "bwd_dq_merge_kernel", "reduce_partials_kernel",
                                      "bwd_main_bf16_kernel", "proj_gemm_kernel:project_qkv", "proj_gemm_kernel:project_bwd",
                                      "embed_pe_fwd_kernel", "embed_pe_bwd_kernel", "layernorm_fwd_kernel",
                                      "layernorm_bwd_kernel", "layernorm_bwd_params_kernel", "gelu_fwd_kernel",

@@ -1,0 +1,43 @@
+"""Attention launches on either side of the choices the launchers make by size (two wavefronts per key block or one,
+how many key splits), at ragged row and key counts, against the oracle."""
+import pytest
+import torch
+
+import oracle
+from paper_2311_02382_amd import lss
+from _util import rel_err, stage_all, to_np
+from test_gpu_parity import run_segment
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # B, l_x, H, d, s0, l_s, causal
+    (1, 129, 1, 64, 64, 65, True),          # one key past a tile of 128, one row past a tile of 64
+    (2, 700, 3, 64, 333, 97, True), (2, 700, 3, 128, 333, 97, True),
+    (1, 1100, 2, 64, 33, 1029, True), (1, 1100, 2, 64, 0, 1029, False),
+    (2, 900, 50, 64, 700, 130, True),       # 800 key tiles: one wavefront per key block
+    (1, 2500, 2, 128, 1000, 70, False),
+]
+
+
+@pytest.mark.parametrize("kind", ["bf16", "f32"])
+@pytest.mark.parametrize("B,l_x,H,d,s0,l_s,causal", SHAPES)
+def test_matches_oracle(B, l_x, H, d, s0, l_s, causal, kind):
+    Q, K, V, DO = stage_all(B, l_x, H, d, 8800 + l_x + H, kind)
+    run_segment(Q, K, V, DO, s0, l_s, causal, kind, tag=f"{(B, l_x, H, d, s0, l_s, causal, kind)}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_float_results_are_those_of_single_precision(d):
+    # three bf16 parts per float: errors of a few units in the last place, not of a bf16 product
+    B, l_x, H, s0, l_s = 1, 800, 2, 250, 300
+    Q, K, V, DO = stage_all(B, l_x, H, d, 8900 + d, "f32", std=2.0)
+    sl = slice(s0, s0 + l_s)
+    q, do = Q.dev[:, sl].contiguous(), DO.dev[:, sl].contiguous()
+    out, lse = lss.lss_segment_attn_fwd(q, K.dev, V.dev, s0, True)
+    dq, dk, dv = lss.lss_segment_attn_bwd(q, K.dev, V.dev, s0, out, lse, do, True)
+    ro, rl = oracle.segment_fwd(Q.f64[:, sl], K.f64, V.f64, s0, True)
+    ref = (ro, rl, *oracle.segment_bwd(Q.f64[:, sl], K.f64, V.f64, DO.f64[:, sl], s0, True))
+    for name, got, want in zip(("out", "lse", "dq", "dk", "dv"), (out, lse, dq, dk, dv), ref):
+        assert rel_err(to_np(got), want) <= 1e-5, name
+    again = lss.lss_segment_attn_bwd(q, K.dev, V.dev, s0, out, lse, do, True)
+    assert all(torch.equal(a, b) for a, b in zip((dq, dk, dv), again))
