@@ -1,6 +1,6 @@
 """Builds liblss_attn.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree.
 
-    python -m paper_2311_02382_amd.build                # the library
+    python -m paper_2311_02382_amd.build                # the library and the binding's native half
     python -m paper_2311_02382_amd.build --microbench   # also lss_microbench (issue-rate microbenchmarks, a stand-alone program)
 
 hipcc cross-compiles without a GPU.  The library lands next to this file so that it
@@ -47,17 +47,53 @@ def _compile(src: str) -> Path:
     return obj
 
 
+BINDING = PKG / "_lss_torch.so"
+
+
+def _compile_binding() -> Path:
+    """csrc/lss_torch.cpp (host code only, against the installed torch's headers)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    obj = OBJ_DIR / "lss_torch.o"
+    include = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], "/opt/rocm/include", str(INCLUDE)]
+    # the torch and HIP headers are written for either vendor: these two macros name this one
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *(x for d in include for x in ("-isystem", d)), "-c", str(CSRC / "lss_torch.cpp"), "-o", str(obj)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on lss_torch.cpp:\n{r.stderr}")
+    return obj
+
+
+def _link_binding(obj: Path) -> None:
+    import torch
+    tmp = BINDING.with_suffix(f".so.tmp{os.getpid()}")
+    libs = Path(torch.__file__).parent / "lib"
+    cmd = ["g++", "-shared", "-o", str(tmp), str(obj), f"-L{PKG}", "-l:liblss_attn.so", f"-L{libs}", "-lc10", "-lc10_hip", "-ltorch_cpu",
+           "-ltorch_python", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"link of the binding failed:\n{r.stderr}")
+    os.replace(tmp, BINDING)
+
+
 def build_library(verbose: bool = True) -> Path:
-    """Compile every HIP source and link liblss_attn.so.  Always recompiles."""
+    """Compile every HIP source and link liblss_attn.so, then the binding's native half.  Always recompiles."""
     OBJ_DIR.mkdir(exist_ok=True)
-    with ThreadPoolExecutor(max_workers=4) as pool:
+    with ThreadPoolExecutor(max_workers=6) as pool:
+        binding = pool.submit(_compile_binding)
         objs = list(pool.map(_compile, SOURCES))
+        binding_obj = binding.result()
     tmp = LIB.with_suffix(f".so.tmp{os.getpid()}")
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", str(tmp), *map(str, objs)]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stderr}")
     os.replace(tmp, LIB)
+    _link_binding(binding_obj)
     if verbose:
         print(f"built {LIB} ({LIB.stat().st_size} bytes)")
     return LIB
