@@ -44,24 +44,25 @@ int max_fwd_splits(int l_s, int l_x, int B, int H, int rows_per_wg)
 int pick_fwd_splits(int l_s, int B, int H, int rows_per_wg, int64_t kv_tiles, int max_splits, int elem_bytes, int d)
 {
     // Measured on the forward kernels (8..2048 query tiles, 1..16 splits), in units of the time a lone workgroup
-    // takes per 64-key tile (0.77 us for bf16 at d = 64, 3.9 for float): a launch takes about
+    // takes per 64-key tile: a launch takes about
     //   (key tiles per workgroup + start) x g(n) + merge if split,   n = workgroups per compute unit, rounded up,
-    // `start` for a workgroup's start and results, `merge` for the merge launch, g(1) = 1 and, where several
-    // workgroups share a compute unit, g(n) = 0.17 + 0.65 n (bf16: a second co-resident workgroup adds about a
-    // third of a workgroup's throughput) or 0.8 n (float), g(n) = n where only one fits (bf16, d = 128).
-    // What matters most is that the workgroup count lands just below a multiple of the 256 compute
-    // units.  The smallest count within 3 % of the best estimate is taken.
-    struct Cost { double start, merge, g0, g1; int least; };
-    const Cost c = elem_bytes == 4 ? Cost{2.0, 1.5, 0.0, 0.8, 4} : d == 64 ? Cost{8.0, 6.0, 0.17, 0.65, 8} : Cost{8.0, 6.0, 0.0, 1.0, 8};
+    // `start` for a workgroup's start and results, `merge` for the merge launch (2 us) and for writing and reading the
+    // partial results (5 bytes per ps), g(1) = 1 and, where several workgroups share a compute unit, g(n) = 0.17 + 0.65 n
+    // (bf16: a second co-resident workgroup adds about a third of a workgroup's throughput) or 0.8 n (float),
+    // g(n) = n where only one fits (bf16, d = 128).  What matters most is that the workgroup count lands just below a
+    // multiple of the 256 compute units.  The smallest count within 3 % of the best estimate is taken.
+    struct Cost { double tile_us, start, g0, g1; };
+    const Cost c = elem_bytes == 4 ? Cost{d == 64 ? 3.9 : 5.8, 2.0, 0.0, 0.8} : d == 64 ? Cost{0.77, 8.0, 0.17, 0.65} : Cost{1.6, 6.0, 0.0, 1.0};
+    const double row_bytes = (double)B * H * l_s * d * elem_bytes;
     const int64_t wgs = (int64_t)((l_s + rows_per_wg - 1) / rows_per_wg) * B * H;
     if (wgs <= 0 || max_splits <= 1) return 1;
     double best = 0.0;
     int best_s = 1;
     for (int sp = 1; sp <= max_splits; ++sp) {
-        if (sp > 1 && kv_tiles / sp < c.least) break;      // shorter splits cost more than they gain
+        if (sp > 1 && kv_tiles / sp < 4) break;      // shorter splits cost more than they gain
         const int64_t per_cu = (wgs * sp + 255) / 256;
         const double g = per_cu <= 1 ? 1.0 : c.g0 + c.g1 * (double)per_cu;
-        const double t = ((double)((kv_tiles + sp - 1) / sp) + c.start) * g + (sp > 1 ? c.merge : 0.0);
+        const double t = ((double)((kv_tiles + sp - 1) / sp) + c.start) * g + (sp > 1 ? (2.0 + row_bytes * (2 * sp + 1) / 5e6) / c.tile_us : 0.0);
         if (sp == 1 || t < 0.97 * best) { best = t; best_s = sp; }
     }
     return best_s;

@@ -54,20 +54,53 @@ __global__ __launch_bounds__(256) void bwd_dq_merge_kernel(const float *__restri
     for (int e = 0; e < 4; ++e) dq[i * 4 + e] = (T)acc[e];
 }
 
+// The dQ workgroups share their launch with the dK/dV ones and need not fill the chip alone: keys are split so far that
+// a dQ workgroup does not outlast the rest of the launch, never further than the workspace was sized for.  In 64-key
+// tiles of dQ, of which a lone workgroup takes one per 1.0 us (d = 64) or 1.4 us (d = 128):
+//   * A launch that leaves compute units idle splits until it fills them (l_x = 1024 in segments of 256, last one:
+//     21.0 us with one range, 15.3 with three), in ranges of at least four tiles that take no less than a dK/dV
+//     workgroup's walk over the queries, 1.35 per 64 of them.  Workgroups that only zero-fill count a quarter.
+//   * Otherwise a range may be half as long again as the launch would take at full balance (the dK/dV and dQ tiles a
+//     compute unit works off per us, and the zero-filled rows), but 24 to 64 tiles: 130 rows against 13,000 keys
+//     take 54 us in ranges of 51 tiles and 38 in ranges of 26; in longer launches shorter ranges gain nothing.
+//     Where one workgroup fills a compute unit (d = 128), a launch that fits the chip keeps fitting it.
+//   * float: 16 tiles (each takes four times as long).
+static int pick_dq_splits(const SegShape &s, int elem_bytes)
+{
+    const int rows_per_wg = dq_rows_per_wg(elem_bytes, s.d);
+    const int most = choose_splits(s.l_s, s.l_x, s.B, s.H, rows_per_wg);
+    if (most <= 1) return 1;
+    const int64_t bhs = (int64_t)s.B * s.H, seen = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
+    const int64_t tiles = (seen + 63) / 64;                                     // key tiles of a query tile
+    const int64_t dq_wgs = bhs * ((s.l_s + rows_per_wg - 1) / rows_per_wg), dkv_wgs = bhs * ((seen + 127) / 128);
+    int64_t want = 1;
+    if (elem_bytes == 4) {
+        want = (tiles + 15) / 16;
+    } else {
+        struct Rate { double tile_us, dkv, dq; };
+        const Rate rate = s.d == 64 ? Rate{1.0, 0.74, 1.25} : Rate{1.4, 0.5, 0.7};
+        const double q_tiles = (double)((s.l_s + 63) / 64), walk = s.l_s <= 64 ? 8.0 : 1.35 * q_tiles;
+        const double us = ((double)dkv_wgs * q_tiles / rate.dkv + (double)dq_wgs * tiles / rate.dq) / 256.0 +
+                          (double)(s.l_x - seen) * bhs * s.d * 8.0 / 5.5e6;
+        double longest = 1.5 * us / rate.tile_us;
+        if (longest < 24.0) longest = 24.0;
+        if (longest < walk) longest = walk;
+        if (longest > 64.0) longest = 64.0;
+        want = (int64_t)ceil((double)tiles / longest);
+        const int64_t idle = (256 - dkv_wgs - (s.l_x - seen) * bhs / 512) / dq_wgs, fill = (int64_t)((double)tiles / (walk > 4.0 ? walk : 4.0));
+        if (idle >= want) want = fill <= want ? want : idle < fill ? idle : fill;
+        else if (s.d == 128 && idle >= 1) want = idle;
+    }
+    return (int)(want < 1 ? 1 : want > most ? most : want);
+}
+
 template <typename T, int D>
 static hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const T *q, const T *k, const T *v, const T *out,
                                const float *lse, const T *dO, T *dq, float *dk_part, float *dv_part,
                                const Workspace &ws, hipStream_t st)
 {
     hipError_t e;
-    // The dQ workgroups share their launch with the dK/dV ones and need not fill the chip alone:
-    // keys are split only so far that a dQ workgroup (64 key tiles at most, 16 of the slower float ones) does
-    // not outlast the rest of the launch.  Never more splits than the workspace was sized for.
-    int n_splits = choose_splits(s.l_s, s.l_x, s.B, s.H, dq_rows_per_wg((int)sizeof(T), D));
-    const int64_t kv_extent = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
-    constexpr int kMostKeys = 64 * (sizeof(T) == 2 ? 64 : 16);
-    const int want = (int)((kv_extent + kMostKeys - 1) / kMostKeys);
-    if (want < n_splits) n_splits = want < 1 ? 1 : want;
+    const int n_splits = pick_dq_splits(s, (int)sizeof(T));
     if constexpr (sizeof(T) == 2) {
         if ((e = launch_bwd_bf16_main(s, dr, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, st)) != hipSuccess)
             return e;

@@ -947,11 +947,11 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_main_bf16_kernel(
     const int id = blockIdx.x;
     int bh, inner;
     if (id >= n_dq) {
-        if (!xcd_item(id - n_dq, bhs, n_key_tiles, bh, inner)) return;
+        if (!xcd_item(id - n_dq, bhs, n_key_tiles, s.causal, bh, inner)) return;
         if constexpr (SKINNY) bwd_dkv_skinny_body<D>(smem, s, q, k, v, dO, Ls, Dn, dk_part, dv_part, bh, inner);
         else bwd_dkv_body<D, DROP>(smem, s, dr, q, k, v, dO, Ls, Dn, row_key, dk_part, dv_part, bh, inner);
     } else {
-        if (!xcd_item(id, bhs, n_q_tiles * n_splits, bh, inner)) return;
+        if (!xcd_item(id, bhs, n_q_tiles * n_splits, s.causal && s.s0 < s.l_s, bh, inner)) return;
         bwd_dq_body<D, DROP>(smem, s, dr, q, k, v, dO, lse, Dn, dq, dq_part, n_splits, inner % n_q_tiles, n_q_tiles, bh,
                              inner / n_q_tiles);
     }

@@ -180,7 +180,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_f32_kernel(SegShape 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int bhs = s.B * s.H;
     int bh, inner;
-    if (!xcd_item(blockIdx.x, bhs, n_q_tiles * n_splits, bh, inner)) return;
+    if (!xcd_item(blockIdx.x, bhs, n_q_tiles * n_splits, s.causal && s.s0 < s.l_s, bh, inner)) return;
     const int b = bh / s.H, h = bh % s.H, split = inner / n_q_tiles;
     const int r0 = (n_q_tiles - 1 - inner % n_q_tiles) * kRowsPerWg, rw0 = r0 + wave * 32;
     const int64_t ld = (int64_t)s.H * D;
@@ -561,10 +561,10 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_main_f32_kernel(
     const int bhs = s.B * s.H, id = blockIdx.x;
     int bh, inner;
     if (id >= n_dq) {
-        if (!xcd_item(id - n_dq, bhs, n_key_tiles, bh, inner)) return;
+        if (!xcd_item(id - n_dq, bhs, n_key_tiles, s.causal, bh, inner)) return;
         bwd_dkv_f32_body<D, DROP, HALVES>(smem, s, dr, q, k, v, dO, lse, Dv, dk_part, dv_part, bh, inner);
     } else {
-        if (!xcd_item(id, bhs, n_q_tiles * n_splits, bh, inner)) return;
+        if (!xcd_item(id, bhs, n_q_tiles * n_splits, s.causal && s.s0 < s.l_s, bh, inner)) return;
         bwd_dq_f32_body<D, DROP>(smem, s, dr, q, k, v, dO, lse, Dv, dq, dq_part, n_splits, inner % n_q_tiles, n_q_tiles, bh,
                                  inner / n_q_tiles);
     }

@@ -62,7 +62,7 @@ __global__ __launch_bounds__(FwdBf16Cfg<D>::NT, D == 64 ? 2 : 1) void fwd_bf16_k
     // launch -- then key splits.
     const int bhs = s.B * s.H;
     int bh, inner;
-    if (!xcd_item(blockIdx.x, bhs, n_q_tiles * n_splits, bh, inner)) return;
+    if (!xcd_item(blockIdx.x, bhs, n_q_tiles * n_splits, s.causal && s.s0 < s.l_s, bh, inner)) return;
     const int b = bh / s.H, h = bh % s.H;
     const int q_tile = inner % n_q_tiles, split = inner / n_q_tiles;
     const int r0 = (n_q_tiles - 1 - q_tile) * C::BR;

@@ -1,5 +1,5 @@
 """Attention launches on either side of the choices the launchers make by size (two wavefronts per key block or one,
-how many key splits), at ragged row and key counts, against the oracle."""
+how many key splits, which XCD gets which head), at ragged row and key counts, against the oracle."""
 import pytest
 import torch
 
@@ -16,6 +16,8 @@ SHAPES = [  # B, l_x, H, d, s0, l_s, causal
     (1, 1100, 2, 64, 33, 1029, True), (1, 1100, 2, 64, 0, 1029, False),
     (2, 900, 50, 64, 700, 130, True),       # 800 key tiles: one wavefront per key block
     (1, 2500, 2, 128, 1000, 70, False),
+    (3, 260, 11, 64, 0, 260, True), (1, 2000, 13, 64, 1700, 300, True),     # heads that the eight XCDs share
+    (2, 1500, 27, 64, 1200, 65, True), (1, 700, 9, 128, 5, 300, False),
 ]
 
 
