@@ -36,13 +36,13 @@ struct DqBf16Cfg {
 // As in the dK/dV kernel below the stages are software-pipelined, step g issuing the matrix
 // instructions of A(g+1) and C(g-1) with the vector work of B(g) spread between them, over a ring
 // of three K/V tiles that are loaded global -> LDS directly, a full loop iteration ahead.
-// -D = -rowsum(dO * out) of the wavefront's rows comes from the preprocess kernel (`Dn`).
+// -D = -rowsum(dO * out) of the wavefront's rows comes from the preprocess kernel (`Dn`), or is computed here (OWN).
 // DROP: dropout on the weights (mask M = keep / (1 - p), decided by drop_keep() of (seed,
 // batch*head, global row, key)): dS = P * (M dP - D).
-template <int D, bool DROP>
+template <int D, bool DROP, bool OWN>
 __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const DropArgs &dr, const bf16_t *__restrict__ q,
                                             const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
-                                            const bf16_t *__restrict__ dO, const float *__restrict__ lse,
+                                            const bf16_t *__restrict__ out, const bf16_t *__restrict__ dO, const float *__restrict__ lse,
                                             const float *__restrict__ Dn, bf16_t *__restrict__ dq,
                                             float *__restrict__ dq_part, int n_splits, int q_tile, int n_q_tiles, int bh,
                                             int split)
@@ -81,7 +81,18 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
             qf[kb] = load_frag<bf16_t>(q + off + kb * 16);
             gf[kb] = load_frag<bf16_t>(dO + off + kb * 16);
         }
-        Dr = -Dn[(int64_t)bh * s.l_s + rc];
+        if constexpr (OWN) {        // the lane's half of the row, then the other half's sum
+            Dr = 0.f;
+#pragma unroll
+            for (int kb = 0; kb < NU; ++kb) {
+                const Frag<bf16_t> of = load_frag<bf16_t>(out + off + kb * 16);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) Dr += (float)gf[kb].v[e] * (float)of.v[e];
+            }
+            Dr += __shfl_xor(Dr, 32);
+        } else {
+            Dr = -Dn[(int64_t)bh * s.l_s + rc];
+        }
         const float lv = lse[(int64_t)bh * s.l_s + rc];
         L2 = row_ok ? lv * kLog2e : INFINITY;
     }
@@ -385,7 +396,47 @@ struct DkvBf16Cfg {
     // (with dropout also the 64 rows' generator keys)
     static constexpr int OFF_G = Tile::BYTES, OFF_L = 2 * Tile::BYTES, OFF_D = OFF_L + BQ * 4, OFF_R = OFF_D + BQ * 4;
     static constexpr int SLOT = OFF_R + (DROP ? BQ * 4 : 0);
+    // OWN workgroups: the start values (and keys) of all rows behind the ring, up to OWN_MAX rows and one more tile
+    static constexpr int OWN_MAX = 512, OWN_ROWS = OWN_MAX + BQ, OFF_OWN = RING * SLOT, OWN_BYTES = OWN_ROWS * 4 * (DROP ? 3 : 2);
 };
+
+// -D = -rowsum(dO * out) of a row from its parts: D/8 consecutive lanes hold one 16-byte chunk each.
+template <int D>
+__device__ __forceinline__ float neg_row_dot(const Frag<bf16_t> &g, const Frag<bf16_t> &o)
+{
+    float dsum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) dsum += (float)g.v[e] * (float)o.v[e];
+#pragma unroll
+    for (int sh = 1; sh < D / 8; sh <<= 1) dsum += __shfl_xor(dsum, sh);
+    return -dsum;
+}
+// The same for `n` rows that lie `ld` elements apart, by a workgroup of 256: put(row, -D, lse) on one lane per row.  The
+// loads of 128 (d = 64) or 64 rows are in flight at once.
+template <int D, typename Put>
+__device__ __forceinline__ void neg_row_dots(const bf16_t *__restrict__ out, const bf16_t *__restrict__ dO,
+                                             const float *__restrict__ lse, int64_t ld, int n, int tid, Put &&put)
+{
+    constexpr int CPR = D / 8, STEP = 256 / CPR, U = 4;
+    const int cpos = tid % CPR;
+    for (int i0 = tid / CPR; i0 - tid / CPR < n; i0 += U * STEP) {
+        Frag<bf16_t> g[U], o[U];
+        float l[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = min(i0 + u * STEP, n - 1);
+            const int64_t off = i * ld + cpos * 8;
+            l[u] = lse[i];
+            g[u] = load_frag<bf16_t>(dO + off);
+            o[u] = load_frag<bf16_t>(out + off);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float nd = neg_row_dot<D>(g[u], o[u]);
+            if (cpos == 0 && i0 + u * STEP < n) put(i0 + u * STEP, nd, l[u]);
+        }
+    }
+}
 
 // The query rows are walked in blocks of 32 (two per 64-row Q/dO tile).  Per block g three stages:
 //     A(g): S and dP products (matrix),  B(g): weights P, dS (vector: exp, multiplies, bf16 packing),
@@ -401,10 +452,14 @@ struct DkvBf16Cfg {
 // this is dS = A * acc + (P - A) * (-D).  The keep decision of an element needs its row's key
 // (precomputed per query row, travelling with the tile like the start values) and this lane's
 // column key; -D of the element's row is read from the tile's start values a second time.
-template <int D, bool DROP>
+//
+// OWN: the workgroup computes the start values (and keys) of its rows itself, into LDS, while its first
+// tiles are on their way, instead of finding them in memory (bwd_own_values).
+template <int D, bool DROP, bool OWN>
 __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, const DropArgs &dr, const bf16_t *__restrict__ q,
                                              const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
-                                             const bf16_t *__restrict__ dO, const float *__restrict__ Ls,
+                                             const bf16_t *__restrict__ out, const bf16_t *__restrict__ dO,
+                                             const float *__restrict__ lse, const float *__restrict__ Ls,
                                              const float *__restrict__ Dn, const uint32_t *__restrict__ row_key,
                                              float *__restrict__ dk_part, float *__restrict__ dv_part, int bh, int key_tile)
 {
@@ -507,9 +562,11 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         static_assert(C::OFF_G == Tile::BYTES, "dO tile follows Q tile");
         char *dst = smem + slot * C::SLOT;
         Tile::issue_pair(tile_ptr(qbase, tq, tile_bytes), tile_ptr(gbase, tq, tile_bytes), off, dst, wave);
-        const uint32_t ro = (uint32_t)min(lane, s.l_s - rq0 - 1) * 4u;
-        lds_dma<4>(sv_base + rq0, ro, dst + sv_off);
-        if (DROP && wave == 2) lds_dma<4>(rbase + rq0, ro, dst + C::OFF_R);
+        if constexpr (!OWN) {
+            const uint32_t ro = (uint32_t)min(lane, s.l_s - rq0 - 1) * 4u;
+            lds_dma<4>(sv_base + rq0, ro, dst + sv_off);
+            if (DROP && wave == 2) lds_dma<4>(rbase + rq0, ro, dst + C::OFF_R);
+        }
     };
 
     // ---- per-lane LDS offsets (bytes, within a tile)
@@ -533,12 +590,18 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     };
     // Accumulators of A start at -lse*sqrt(d) and -D of their rows: C-tile element e of this lane is
     // query row 8*(e/4) + 4*hh + e%4 of the block.  init_load reads the values of element groups
-    // [g0, g1) (4 elements each).
-    auto init_load = [&](const char *tile, int qb, int g0, int g1, f32x16 &sc, f32x16 &dp) __attribute__((always_inline)) {
+    // [g0, g1) (4 elements each).  `start_values`: those of a block, in its tile's slot, or with OWN by its
+    // first row counted from rq_begin; the -D and the row keys follow SV_D and SV_R bytes on.
+    constexpr int SV_D = OWN ? C::OWN_ROWS * 4 : C::OFF_D - C::OFF_L, SV_R = 2 * SV_D;
+    static_assert(OWN || SV_R == C::OFF_R - C::OFF_L, "start values lie in one row of arrays");
+    auto start_values = [&](const char *tile, int qb, int row) __attribute__((always_inline)) {
+        return (OWN ? smem + C::OFF_OWN + row * 4 : tile + C::OFF_L + qb * 32 * 4) + 4 * hh * 4;
+    };
+    auto init_load = [&](const char *sv, int g0, int g1, f32x16 &sc, f32x16 &dp) __attribute__((always_inline)) {
 #pragma unroll
         for (int e4 = g0; e4 < g1; ++e4) {
-            const f32x4 l4 = *reinterpret_cast<const f32x4 *>(tile + C::OFF_L + (qb * 32 + 8 * e4 + 4 * hh) * 4);
-            const f32x4 d4 = *reinterpret_cast<const f32x4 *>(tile + C::OFF_D + (qb * 32 + 8 * e4 + 4 * hh) * 4);
+            const f32x4 l4 = *reinterpret_cast<const f32x4 *>(sv + 8 * e4 * 4);
+            const f32x4 d4 = *reinterpret_cast<const f32x4 *>(sv + SV_D + 8 * e4 * 4);
 #pragma unroll
             for (int i = 0; i < 4; ++i) { sc[4 * e4 + i] = l4[i]; dp[4 * e4 + i] = d4[i]; }
         }
@@ -560,19 +623,19 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     };
     // B for elements [e0, e1): P = 2^(c * (S - lse*sqrt(d))), dS = P * (dP - D); finished pairs are
     // rounded to bf16 into the operand fragments of C
-    // (dropout: `tile_b`, `qb_b` name B's block; the row keys and -D of four elements are read when
+    // (dropout: `sv_b` are B's start values; the row keys and -D of four elements are read when
     // the first of them is due)
     // (An element's exponential and the multiplies that consume it are issued one element apart, as in the dQ
     // workgroups: a transcendental's result may not be read by the very next instruction.)
     u32x4 rk4;
     f32x4 nd4;
-    auto b_elems = [&](const char *tile_b, int qb_b, f32x16 &sc, f32x16 &dp, int e0, int e1, Frag<bf16_t> (&pf)[2],
+    auto b_elems = [&](const char *sv_b, f32x16 &sc, f32x16 &dp, int e0, int e1, Frag<bf16_t> (&pf)[2],
                        Frag<bf16_t> (&df)[2]) __attribute__((always_inline)) {
         auto finish = [&](int i) __attribute__((always_inline)) {           // sc[i] holds P by now
             if constexpr (DROP) {
                 if ((i & 3) == 0) {
-                    rk4 = *reinterpret_cast<const u32x4 *>(tile_b + C::OFF_R + (qb_b * 32 + 8 * (i >> 2) + 4 * hh) * 4);
-                    nd4 = *reinterpret_cast<const f32x4 *>(tile_b + C::OFF_D + (qb_b * 32 + 8 * (i >> 2) + 4 * hh) * 4);
+                    rk4 = *reinterpret_cast<const u32x4 *>(sv_b + SV_R + 8 * (i >> 2) * 4);
+                    nd4 = *reinterpret_cast<const f32x4 *>(sv_b + SV_D + 8 * (i >> 2) * 4);
                 }
                 const float p = sc[i];
                 const float a = drop_keep(rk4[i & 3], drop_ck, dr.thr) ? p * dr.scale : 0.f;
@@ -598,7 +661,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     // instructions alternate C, C, A, A (A, A, C, C in the last unit); after each one come the B
     // elements that fall to its slot.
     // Everything read from LDS is requested well before its use: operand fragments one unit ahead;
-    // for the next step (A on block (tile_an, qb_an), C on (tile_cn, qb_cn)) this step's last
+    // for the next step (A on block (tile_an, qb_an), rows from rq_begin + row_an on, C on (tile_cn, qb_cn)) this step's last
     // unit requests the fragments of C's first unit (cq[0], cg[0]) and, into the three quarters of
     // B's registers that B is done with by then, the start values of A's accumulators (PRE says
     // the step before did that for this one).  `mid` runs before those last requests: the even
@@ -606,9 +669,9 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     // the barrier publishes.
     Frag<bf16_t> cq[2], cg[2];
     auto step = [&](auto has_a, auto has_b, auto has_c, auto pre, const char *tile_a, int qb_a, int r0_a, f32x16 &sc_a,
-                    f32x16 &dp_a, const char *tile_b, int qb_b, f32x16 &sc_b, f32x16 &dp_b, Frag<bf16_t> (&pf_b)[2],
+                    f32x16 &dp_a, const char *sv_b, f32x16 &sc_b, f32x16 &dp_b, Frag<bf16_t> (&pf_b)[2],
                     Frag<bf16_t> (&df_b)[2], const char *tile_c, int qb_c, Frag<bf16_t> (&pf_c)[2], Frag<bf16_t> (&df_c)[2],
-                    const char *tile_an, int qb_an, const char *tile_cn, int qb_cn, auto &&mid) __attribute__((always_inline)) {
+                    const char *tile_an, int qb_an, int row_an, const char *tile_cn, int qb_cn, auto &&mid) __attribute__((always_inline)) {
         constexpr bool HA = decltype(has_a)::value, HB = decltype(has_b)::value, HC = decltype(has_c)::value;
         constexpr bool PRE = decltype(pre)::value;
         constexpr int NS = 4 * NU;                      // slots; 16 elements of B spread over them
@@ -617,13 +680,13 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
             if (HB) {
                 const int e0 = slot * 16 / NS, e1 = (slot + 1) * 16 / NS;
                 __builtin_amdgcn_sched_barrier(0);
-                b_elems(tile_b, qb_b, sc_b, dp_b, e0, e1, pf_b, df_b);
+                b_elems(sv_b, sc_b, dp_b, e0, e1, pf_b, df_b);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
         Frag<bf16_t> aq[2], ag[2];
         if (HA) {
-            init_load(tile_a, qb_a, PRE ? 3 : 0, 4, sc_a, dp_a);
+            init_load(start_values(tile_a, qb_a, r0_a - rq_begin), PRE ? 3 : 0, 4, sc_a, dp_a);
             load_a(tile_a, qb_a, 0, aq[0], ag[0]);
             init_mask(r0_a, sc_a);
         }
@@ -654,7 +717,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
                 b_slot(4 * u + 1);
                 mid();
                 load_c(tile_cn, qb_cn, 0, cq[0], cg[0]);
-                init_load(tile_an, qb_an, 0, 3, sc_b, dp_b);    // elements 0..11 of B are packed by now
+                init_load(start_values(tile_an, qb_an, row_an), 0, 3, sc_b, dp_b);    // elements 0..11 of B are packed by now
                 __builtin_amdgcn_sched_barrier(0);
                 if (HC) dv[db] = mma(cg[u & 1], pf_c[half], dv[db]);
                 b_slot(4 * u + 2);
@@ -674,6 +737,21 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     auto issue_ahead = [&](int t, int slot) { issue_tile(tq_begin + min(t + 2, T - 1), slot); };
     issue_tile(tq_begin, 0);
     if (T > 1) issue_tile(tq_begin + 1, 1);
+    if constexpr (OWN) {
+        float *const own = reinterpret_cast<float *>(smem + C::OFF_OWN);
+        const int n = s.l_s - rq_begin;
+        for (int i = n + tid; i < (T + 1) * C::BQ; i += C::NT) {    // rows past the segment, whose weights are 0: any finite values
+            own[i] = own[C::OWN_ROWS + i] = 0.f;
+            if constexpr (DROP) own[2 * C::OWN_ROWS + i] = 0.f;
+        }
+        const int64_t first = ((int64_t)b * s.l_s + rq_begin) * ld + (int64_t)h * D;
+        neg_row_dots<D>(out + first, dO + first, lse + (int64_t)bh * s.l_s + rq_begin, ld, n, tid, [&](int i, float nd, float l) {
+            own[i] = -l * sqrt_d;
+            own[C::OWN_ROWS + i] = nd;
+            if constexpr (DROP)
+                reinterpret_cast<uint32_t *>(own)[2 * C::OWN_ROWS + i] = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + rq_begin + i));
+        });
+    }
     wait_vmem_all();
     __syncthreads();
 
@@ -682,8 +760,8 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     // step -1: A(0) alone (leaves the first loop step's C operands in cq[0], cg[0]).  That step has
     // no C(-1): it multiplies zeros with tile 0 instead.
     auto nothing = [] {};
-    step(true_type{}, false_type{}, false_type{}, false_type{}, smem, 0, rq_begin, sc0, dp0, smem, 0, sc1, dp1, pf0, df0, smem, 0,
-         pf1, df1, smem, 1, smem, 1, nothing);
+    step(true_type{}, false_type{}, false_type{}, false_type{}, smem, 0, rq_begin, sc0, dp0, smem, sc1, dp1, pf0, df0, smem, 0,
+         pf1, df1, smem, 1, 32, smem, 1, nothing);
 #pragma unroll
     for (int half = 0; half < 2; ++half)
 #pragma unroll
@@ -700,23 +778,25 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         // Before its last requests (which may touch tile t+1): tile t+1's loads, issued one iteration
         // ago, have landed for this wavefront; after the barrier for all, and every wavefront has
         // requested its last operands from tile t-1, whose slot takes tile t+2.
-        step(true_type{}, true_type{}, true_type{}, true_type{}, t_cur, 1, r0 + 32, sc1, dp1, t_cur, 0, sc0, dp0, pf0, df0,
-             t > 0 ? t_prv : t_cur, 1, pf1, df1, t_a2, 0, t_cur, 0, [&] {
+        step(true_type{}, true_type{}, true_type{}, true_type{}, t_cur, 1, r0 + 32, sc1, dp1,
+             start_values(t_cur, 0, t * C::BQ), sc0, dp0, pf0, df0, t > 0 ? t_prv : t_cur, 1, pf1, df1, t_a2, 0, (t + 1) * C::BQ,
+             t_cur, 0, [&] {
                  wait_vmem_all();
                  __syncthreads();
                  issue_ahead(t, prv);
              });
         // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end result unused], B(2t+1),
         // C(2t) [tile t, first half]
-        step(true_type{}, true_type{}, true_type{}, true_type{}, t_a2, 0, r0 + C::BQ, sc0, dp0, t_cur, 1, sc1, dp1, pf1, df1, t_cur,
-             0, pf0, df0, t_a2, 1, t_cur, 1, nothing);
+        step(true_type{}, true_type{}, true_type{}, true_type{}, t_a2, 0, r0 + C::BQ, sc0, dp0,
+             start_values(t_cur, 1, t * C::BQ + 32), sc1, dp1, pf1, df1, t_cur, 0, pf0, df0, t_a2, 1, (t + 1) * C::BQ + 32, t_cur, 1,
+             nothing);
         cur = nxt;
     }
     // step 2T: C(2T-1) [tile T-1, second half] alone
     {
         const char *t_last = smem + (cur == 0 ? C::RING - 1 : cur - 1) * C::SLOT;
-        step(false_type{}, false_type{}, true_type{}, false_type{}, smem, 0, 0, sc0, dp0, smem, 0, sc0, dp0, pf0, df0, t_last, 1, pf1,
-             df1, smem, 0, t_last, 1, nothing);
+        step(false_type{}, false_type{}, true_type{}, false_type{}, smem, 0, 0, sc0, dp0, smem, sc0, dp0, pf0, df0, t_last, 1, pf1,
+             df1, smem, 0, 0, t_last, 1, nothing);
     }
 
     // the ring is free once every wavefront has made its last reads and the last, redundant prefetches have landed
@@ -741,8 +821,8 @@ constexpr int kSkinnyRows = 64, kSkinnyTilesPerWg = 4;
 template <int D>
 __device__ __forceinline__ void bwd_dkv_skinny_body(char *smem, const SegShape &s, const bf16_t *__restrict__ q,
                                                     const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
-                                                    const bf16_t *__restrict__ dO, const float *__restrict__ Ls,
-                                                    const float *__restrict__ Dn, float *__restrict__ dk_part,
+                                                    const bf16_t *__restrict__ out, const bf16_t *__restrict__ dO,
+                                                    const float *__restrict__ lse, float *__restrict__ dk_part,
                                                     float *__restrict__ dv_part, int bh, int tile_group)
 {
     using C = DkvBf16Cfg<D>;
@@ -767,10 +847,6 @@ __device__ __forceinline__ void bwd_dkv_skinny_body(char *smem, const SegShape &
         const bf16_t *qbase = q + (int64_t)b * s.l_s * ld + (int64_t)h * D;
         const bf16_t *gbase = dO + (int64_t)b * s.l_s * ld + (int64_t)h * D;
         Tile::issue_pair(qbase, gbase, off, smem, wave);
-        if (wave < 2) {
-            const float *src = (wave == 0 ? Ls : Dn) + (int64_t)bh * s.l_s;
-            lds_dma<4>(src, (uint32_t)min(lane, s.l_s - 1) * 4u, smem + (wave == 0 ? C::OFF_L : C::OFF_D));
-        }
     }
     auto load_kv = [&](int kt, Frag<bf16_t> (&kf)[NU], Frag<bf16_t> (&vf)[NU]) __attribute__((always_inline)) {
         const int jj = kt * C::BKV + wave * C::KW + lq;
@@ -782,7 +858,16 @@ __device__ __forceinline__ void bwd_dkv_skinny_body(char *smem, const SegShape &
         }
     };
     Frag<bf16_t> kf[NU], vf[NU], kf_n[NU], vf_n[NU];
-    if (kt0 < kt_vis) load_kv(kt0, kf, vf);
+    if (kt0 < kt_vis) {
+        load_kv(kt0, kf, vf);
+        const int64_t first = (int64_t)b * s.l_s * ld + (int64_t)h * D;
+        for (int i = s.l_s + tid; i < C::BQ; i += C::NT)            // rows past the segment, whose weights are 0
+            reinterpret_cast<float *>(smem + C::OFF_L)[i] = reinterpret_cast<float *>(smem + C::OFF_D)[i] = 0.f;
+        neg_row_dots<D>(out + first, dO + first, lse + (int64_t)bh * s.l_s, ld, s.l_s, tid, [&](int i, float nd, float l) {
+            reinterpret_cast<float *>(smem + C::OFF_L)[i] = -l * sqrtf((float)D);
+            reinterpret_cast<float *>(smem + C::OFF_D)[i] = nd;
+        });
+    }
     wait_vmem_all();
     __syncthreads();
 
@@ -904,17 +989,11 @@ __global__ __launch_bounds__(256) void bwd_prep_bf16_kernel(SegShape s, DropArgs
     const int64_t rows = (int64_t)s.B * s.l_s * s.H;
     const int64_t row = min(idx / CPR, rows - 1);       // memory order [b][r][h]; whole lane groups stay in range
     const int cpos = (int)(idx % CPR);
-    const Frag<bf16_t> g = load_frag<bf16_t>(dO + row * D + cpos * 8);
-    const Frag<bf16_t> o = load_frag<bf16_t>(out + row * D + cpos * 8);
-    float dsum = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) dsum += (float)g.v[e] * (float)o.v[e];
-#pragma unroll
-    for (int sh = 1; sh < CPR; sh <<= 1) dsum += __shfl_xor(dsum, sh);
+    const float nd = neg_row_dot<D>(load_frag<bf16_t>(dO + row * D + cpos * 8), load_frag<bf16_t>(out + row * D + cpos * 8));
     if (cpos == 0 && idx / CPR < rows) {
         const int h = (int)(row % s.H), r = (int)((row / s.H) % s.l_s), b = (int)(row / ((int64_t)s.H * s.l_s));
         const int64_t o_idx = ((int64_t)b * s.H + h) * s.l_s + r;
-        Dn[o_idx] = -dsum;
+        Dn[o_idx] = nd;
         Ls[o_idx] = -lse[o_idx] * sqrtf((float)D);
         if constexpr (DROP) row_key[o_idx] = drop_row_key(dr.seed_lo, (uint32_t)(b * s.H + h), (uint32_t)(s.s0 + r));
     }
@@ -930,10 +1009,11 @@ __global__ __launch_bounds__(256) void bwd_prep_bf16_kernel(SegShape s, DropArgs
 // tiles; first key tiles, the zero-fill ones last).
 // SKINNY: segments of at most 64 rows, whose dK/dV workgroups take kSkinnyTilesPerWg key tiles each
 // (n_key_tiles then counts those groups).
-template <int D, bool DROP, bool SKINNY = false>
+// OWN: no preprocess kernel ran, every workgroup computes what it needs of D itself (bwd_own_values).
+template <int D, bool DROP, bool OWN, bool SKINNY = false>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_main_bf16_kernel(
     SegShape s, DropArgs dr, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
-    const bf16_t *__restrict__ dO, const float *__restrict__ lse,
+    const bf16_t *__restrict__ out, const bf16_t *__restrict__ dO, const float *__restrict__ lse,
     const float *__restrict__ Ls, const float *__restrict__ Dn, const uint32_t *__restrict__ row_key, bf16_t *__restrict__ dq,
     float *__restrict__ dq_part, float *__restrict__ dk_part, float *__restrict__ dv_part, int n_splits, int n_dq, int n_q_tiles,
     int n_key_tiles)
@@ -941,20 +1021,42 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_main_bf16_kernel(
     using DkvC = DkvBf16Cfg<D, DROP>;
     // (dropout: the dQ workgroups keep a ring of column keys, 4 x 64, behind their tiles)
     constexpr int SMEM_DQ = DqBf16Cfg<D>::RING * DqBf16Cfg<D>::SLOT + (DROP ? 4 * DqBf16Cfg<D>::BC * 4 : 0);
-    constexpr int SMEM = SMEM_DQ > DkvC::RING * DkvC::SLOT ? SMEM_DQ : DkvC::RING * DkvC::SLOT;
+    constexpr int SMEM_DKV = DkvC::RING * DkvC::SLOT + (OWN && !SKINNY ? DkvC::OWN_BYTES : 0);
+    constexpr int SMEM = SMEM_DQ > SMEM_DKV ? SMEM_DQ : SMEM_DKV;
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
     const int bhs = s.B * s.H;
     const int id = blockIdx.x;
     int bh, inner;
     if (id >= n_dq) {
         if (!xcd_item(id - n_dq, bhs, n_key_tiles, s.causal, bh, inner)) return;
-        if constexpr (SKINNY) bwd_dkv_skinny_body<D>(smem, s, q, k, v, dO, Ls, Dn, dk_part, dv_part, bh, inner);
-        else bwd_dkv_body<D, DROP>(smem, s, dr, q, k, v, dO, Ls, Dn, row_key, dk_part, dv_part, bh, inner);
+        if constexpr (SKINNY) bwd_dkv_skinny_body<D>(smem, s, q, k, v, out, dO, lse, dk_part, dv_part, bh, inner);
+        else bwd_dkv_body<D, DROP, OWN>(smem, s, dr, q, k, v, out, dO, lse, Ls, Dn, row_key, dk_part, dv_part, bh, inner);
     } else {
         if (!xcd_item(id, bhs, n_q_tiles * n_splits, s.causal && s.s0 < s.l_s, bh, inner)) return;
-        bwd_dq_body<D, DROP>(smem, s, dr, q, k, v, dO, lse, Dn, dq, dq_part, n_splits, inner % n_q_tiles, n_q_tiles, bh,
-                             inner / n_q_tiles);
+        bwd_dq_body<D, DROP, OWN>(smem, s, dr, q, k, v, out, dO, lse, Dn, dq, dq_part, n_splits, inner % n_q_tiles, n_q_tiles, bh,
+                                  inner / n_q_tiles);
     }
+}
+
+// Whether the workgroups compute D and the start values themselves: a launch less (2.3 us), for each dK/dV workgroup
+// 0.75 us per 128 rows of 64 elements or 1.5 us per 64 of 128 ahead of its loop.  That is spread over the rounds of
+// workgroups the chip takes (512 or 256 at once); a launch of one round or less pays it in full only if a dK/dV
+// workgroup's walk over the queries, and not a dQ workgroup's over its keys, is what the launch waits for.
+// 4 heads of 256 queries against 512 keys: backward 14.4 us with the preprocess kernel, 12.3 without; 10 x 4 heads of 67
+// against 47,600: 450 and 469.
+template <int D>
+static bool bwd_own_values(const SegShape &s, int n_splits)
+{
+    if (s.l_s <= kSkinnyRows) return true;      // one tile: loaded once per workgroup in any case
+    if (s.l_s > DkvBf16Cfg<D>::OWN_MAX) return false;
+    constexpr double kChunkUs = D == 64 ? 0.75 : 1.5, kRowTileUs = D == 64 ? 1.35 : 1.9, kKeyTileUs = D == 64 ? 1.0 : 1.4;
+    constexpr int kChunkRows = D == 64 ? 128 : 64, kAtOnce = D == 64 ? 512 : 256;
+    const int64_t seen = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
+    const double own_us = kChunkUs * ((s.l_s + kChunkRows - 1) / kChunkRows);
+    const double walk_us = kRowTileUs * ((s.l_s + 63) / 64), dq_us = kKeyTileUs * (double)((seen + 63) / 64) / n_splits;
+    double rounds = (double)((seen + 127) / 128 * s.B * s.H) / kAtOnce;
+    if (rounds < 1.0 && dq_us < walk_us + own_us) rounds = 1.0;
+    return own_us * rounds <= 2.0;
 }
 
 template <int D>
@@ -965,35 +1067,26 @@ static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, con
 {
     hipError_t e;
     const bool with_drop = drop.thr != 0;
-    {
+    const bool skinny = !with_drop && s.l_s <= kSkinnyRows, own = bwd_own_values<D>(s, n_splits);
+    if (!own) {
         const int64_t items = (int64_t)s.B * s.l_s * s.H * (D / 8);
         const dim3 grid((unsigned)((items + 255) / 256));
         TimedLaunch tl(K_BWD_PREP_BF16, st);
-        if (with_drop)
-            hipLaunchKernelGGL((bwd_prep_bf16_kernel<D, true>), grid, dim3(256), 0, st, s, drop, out, dO, lse, ws.D, ws.Ls, ws.row_key);
-        else
-            hipLaunchKernelGGL((bwd_prep_bf16_kernel<D, false>), grid, dim3(256), 0, st, s, drop, out, dO, lse, ws.D, ws.Ls, ws.row_key);
+        const auto kernel = with_drop ? bwd_prep_bf16_kernel<D, true> : bwd_prep_bf16_kernel<D, false>;
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, s, drop, out, dO, lse, ws.D, ws.Ls, ws.row_key);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    {
-        const int n_q_tiles = (s.l_s + DqBf16Cfg<D>::BR - 1) / DqBf16Cfg<D>::BR;
-        const bool skinny = !with_drop && s.l_s <= kSkinnyRows;
-        int n_key_tiles = (s.l_x + DkvBf16Cfg<D>::BKV - 1) / DkvBf16Cfg<D>::BKV;
-        if (skinny) n_key_tiles = (n_key_tiles + kSkinnyTilesPerWg - 1) / kSkinnyTilesPerWg;      // groups of key tiles
-        const int n_dq = xcd_grid(s.B * s.H, n_q_tiles * n_splits), n_dkv = xcd_grid(s.B * s.H, n_key_tiles);
-        const dim3 grid((unsigned)(n_dkv + n_dq));
-        TimedLaunch tl(K_BWD_MAIN_BF16, st);
-        if (skinny)
-            hipLaunchKernelGGL((bwd_main_bf16_kernel<D, false, true>), grid, dim3(256), 0, st, s, drop, q, k, v, dO, lse, ws.Ls,
-                               ws.D, ws.row_key, dq, ws.dq_part, dk_part, dv_part, n_splits, n_dq, n_q_tiles, n_key_tiles);
-        else if (with_drop)
-            hipLaunchKernelGGL((bwd_main_bf16_kernel<D, true>), grid, dim3(256), 0, st, s, drop, q, k, v, dO, lse, ws.Ls, ws.D,
-                               ws.row_key, dq, ws.dq_part, dk_part, dv_part, n_splits, n_dq, n_q_tiles, n_key_tiles);
-        else
-            hipLaunchKernelGGL((bwd_main_bf16_kernel<D, false>), grid, dim3(256), 0, st, s, drop, q, k, v, dO, lse, ws.Ls, ws.D,
-                               ws.row_key, dq, ws.dq_part, dk_part, dv_part, n_splits, n_dq, n_q_tiles, n_key_tiles);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+    const int n_q_tiles = (s.l_s + DqBf16Cfg<D>::BR - 1) / DqBf16Cfg<D>::BR;
+    int n_key_tiles = (s.l_x + DkvBf16Cfg<D>::BKV - 1) / DkvBf16Cfg<D>::BKV;
+    if (skinny) n_key_tiles = (n_key_tiles + kSkinnyTilesPerWg - 1) / kSkinnyTilesPerWg;      // groups of key tiles
+    const int n_dq = xcd_grid(s.B * s.H, n_q_tiles * n_splits), n_dkv = xcd_grid(s.B * s.H, n_key_tiles);
+    const auto kernel = skinny      ? bwd_main_bf16_kernel<D, false, true, true>
+                        : with_drop ? (own ? bwd_main_bf16_kernel<D, true, true> : bwd_main_bf16_kernel<D, true, false>)
+                                    : (own ? bwd_main_bf16_kernel<D, false, true> : bwd_main_bf16_kernel<D, false, false>);
+    TimedLaunch tl(K_BWD_MAIN_BF16, st);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_dkv + n_dq)), dim3(256), 0, st, s, drop, q, k, v, out, dO, lse, ws.Ls, ws.D, ws.row_key,
+                       dq, ws.dq_part, dk_part, dv_part, n_splits, n_dq, n_q_tiles, n_key_tiles);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     return hipSuccess;
 }
 

@@ -18,6 +18,7 @@ SHAPES = [  # B, l_x, H, d, s0, l_s, causal
     (1, 2500, 2, 128, 1000, 70, False),
     (3, 260, 11, 64, 0, 260, True), (1, 2000, 13, 64, 1700, 300, True),     # heads that the eight XCDs share
     (2, 1500, 27, 64, 1200, 65, True), (1, 700, 9, 128, 5, 300, False),
+    (1, 2752, 2, 64, 2240, 512, True), (1, 2752, 2, 64, 2239, 513, True),   # the backward's row sums: within its workgroups or ahead
 ]
 
 
