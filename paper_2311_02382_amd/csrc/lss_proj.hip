@@ -27,6 +27,7 @@
 #include "lss_kernels.h"
 
 #include <mutex>
+#include <algorithm>
 #include <type_traits>
 #include <vector>
 
@@ -60,7 +61,7 @@ struct ProjJob {
     int rows, rows_ok;          // rows per batch; leading rows of A that hold data (the rest count as 0)
     int batches, N, K, k_split, n_split, ldw;
     int a_f32;                  // A is float (only in kernels compiled with A_ANY)
-    int wg_begin, m_tiles, n_tiles;             // first workgroup id of the job, tiles per batch, column tiles
+    int wg_begin, m_tiles, m_data, n_tiles;     // first workgroup id of the job; row tiles per batch, those with data; column tiles
 };
 // What happens to a finished bf16 tile on its way to memory (the feed-forward unit, whose GeLU
 // would otherwise be a pass over memory of its own):
@@ -71,6 +72,7 @@ enum { EPI_NONE = 0, EPI_GELU = 1, EPI_GELU_BWD = 2 };
 struct ProjArgs {
     ProjJob job[2];
     int n_jobs, lda, ldc, skip_tail;
+    int zero_begin;             // first workgroup id of the tiles without data (of job 0; the others have none)
 };
 
 // Operand tile [64 k][COLS], to be read transposed.  Loaded directly like a DirectTile.  Its rows start
@@ -134,10 +136,12 @@ struct GemmFrags { Frag<bf16_t> fb[S::MB], fw[S::NB]; };
 //   issue(t, slot)       starts the direct loads of contraction tile t: LOADS instructions
 //   load(slot, ks, f)    reads the fragments of step ks
 //   publish(t, slot)     what is left to do for tile t before the barrier that publishes it, its loads having landed
-//   fetch(t)             REGS: starts the loads of the part of tile t that travels through registers to publish(t)
-template <typename S, int LOADS, typename Issue, typename Load, typename Publish, typename Fetch>
+//   fetch(t)             REGS: starts the loads of the part of tile t that travels through registers, before those of issue(t)
+//   stash(t, slot)       REGS: writes it to LDS, before issue(t)'s loads are waited for (with both the other way round
+//                        a launch of 8192 x 2048 floats takes 63 us instead of 57)
+template <typename S, int LOADS, typename Issue, typename Load, typename Publish, typename Fetch, typename Stash>
 __device__ __forceinline__ void gemm_loop(f32x16 (&acc)[S::MB][S::NB], int T, int group, bool regs, Issue &&issue, Load &&load,
-                                          Publish &&publish, Fetch &&fetch)
+                                          Publish &&publish, Fetch &&fetch, Stash &&stash)
 {
     const int iters = (T + S::KG - 1) / S::KG, mine = (T - group + S::KG - 1) / S::KG;      // tiles of the longest and of this group
     auto tile = [&](int i) { return group + S::KG * i; };
@@ -150,7 +154,7 @@ __device__ __forceinline__ void gemm_loop(f32x16 (&acc)[S::MB][S::NB], int T, in
 #pragma unroll
     for (int i = 0; i < S::STAGES; ++i)
         if (i < mine) issue(tile(i), i);
-    if (regs && mine > 0) fetch(tile(0));
+    if (regs && mine > 0) { fetch(tile(0)); stash(tile(0), 0); }
     landed(mine - 1, integral_constant<int, S::STAGES - 1>{});
     if (mine > 0) publish(tile(0), 0);
     __syncthreads();
@@ -178,12 +182,13 @@ __device__ __forceinline__ void gemm_loop(f32x16 (&acc)[S::MB][S::NB], int T, in
             }
         }
         if (i + 1 < iters) {
-            landed(mine - 2 - i, integral_constant<int, S::STAGES - 2>{});
             const bool more = S::KG == 1 || i + 1 < mine;
+            if (regs && more) stash(tile(i + 1), nxt);
+            landed(mine - 2 - i, integral_constant<int, S::STAGES - 2>{});
             if (more) publish(tile(i + 1), nxt);
+            if (regs && i + 2 < mine) fetch(tile(i + 2));
             __syncthreads();
             if (i + S::STAGES < mine) issue(tile(i + S::STAGES), slot);
-            if (regs && i + 2 < mine) fetch(tile(i + 2));
             if (more) load(nxt, 0, f[0]);
         }
         if (busy) multiply(f[(KS - 1) & 1]);
@@ -281,7 +286,7 @@ __device__ __forceinline__ TileId xcd_tile(int id, int m_tiles, int n_tiles)
     const int block = t / (4 * n_tiles), in = t % (4 * n_tiles), rows = min(4, m_tiles - 4 * block);
     return {4 * block + in % rows, in / rows, id / kXcds < per_xcd && t < tiles};
 }
-int xcd_tile_grid(int m_tiles, int n_tiles) { return kXcds * ((m_tiles * n_tiles + kXcds - 1) / kXcds); }
+__host__ __device__ __forceinline__ int xcd_tile_grid(int m_tiles, int n_tiles) { return kXcds * ((m_tiles * n_tiles + kXcds - 1) / kXcds); }
 
 template <typename S, bool A_ANY, bool W_TR, bool OUT_F32, int EPI>
 __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(ProjArgs args)
@@ -302,11 +307,16 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(Pro
     char *const ring = smem + group * S::RING;
 
     int ji = 0;
-    if (args.n_jobs > 1 && (int)blockIdx.x >= args.job[1].wg_begin) ji = 1;
+    if (args.n_jobs > 1 && (int)blockIdx.x >= args.job[1].wg_begin && (int)blockIdx.x < args.zero_begin) ji = 1;
     const ProjJob &J = args.job[ji];
-    const TileId tile = xcd_tile(blockIdx.x - J.wg_begin, J.batches * J.m_tiles, J.n_tiles);
+    // Row tiles with data first, of all batches and jobs, then those without, each kind spread over all XCDs: with 28 % of two
+    // batches' rows valid (59,486 x 1024 floats) a plain numbering left all products to three or four of the
+    // eight XCDs, 375 us.
+    const bool data = (int)blockIdx.x < args.zero_begin;
+    const int per_batch = data ? J.m_data : J.m_tiles - J.m_data;
+    const TileId tile = xcd_tile(blockIdx.x - (data ? J.wg_begin : args.zero_begin), J.batches * per_batch, J.n_tiles);
     if (!tile.ok) return;
-    const int batch = tile.m / J.m_tiles, m0 = (tile.m % J.m_tiles) * S::TM, n0 = tile.n * S::TN;
+    const int batch = tile.m / per_batch, m0 = (tile.m % per_batch + (data ? 0 : J.m_data)) * S::TM, n0 = tile.n * S::TN;
 
     const int rows_here = min(J.rows - m0, S::TM);                      // rows of C this tile owns
     const int rows_data = min(min(J.rows, J.rows_ok) - m0, S::TM);      // of which this many have data in A
@@ -437,7 +447,7 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(Pro
         if (!a_f32) issue_a(t, slot);
         issue_w(t, slot);
     };
-    gemm_loop<S, LOADS>(acc, T, group, a_f32, issue, load, [&](int, int slot) { if (a_f32) stash_a(slot); }, fetch_a);
+    gemm_loop<S, LOADS>(acc, T, group, a_f32, issue, load, [](int, int) {}, fetch_a, [&](int, int slot) { stash_a(slot); });
     gemm_add_groups<S>(smem, acc, group, wave, lane);
     store_tiles(acc, true);
 }
@@ -576,10 +586,9 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
         for (int mb = 0; mb < S::MB; ++mb) f.fb[mb] = ATile::load_frag(at, ks, at_off[mb]);
     };
     auto publish = [&](int t, int slot) {
-        stash_w(t, slot);
         if (t == T - 1) clear_tail(slot);
     };
-    gemm_loop<S, LOADS>(acc, T, group, DC_F32, issue, load, publish, fetch_w);
+    gemm_loop<S, LOADS>(acc, T, group, DC_F32, issue, load, publish, fetch_w, stash_w);
     gemm_add_groups<S>(smem, acc, group, wave, lane);
 
     float *out = g.out + (int64_t)split * g.K * g.N + (int64_t)m0 * g.N + n0;
@@ -622,9 +631,12 @@ hipError_t launch_proj_shape(ProjArgs &args, int kernel_id, hipStream_t st)
         ProjJob &J = args.job[j];
         J.m_tiles = (J.rows + S::TM - 1) / S::TM;
         J.n_tiles = (J.N + S::TN - 1) / S::TN;
+        J.m_data = (std::min(J.rows, J.rows_ok) + S::TM - 1) / S::TM;
         J.wg_begin = wgs;
-        wgs += xcd_tile_grid(J.batches * J.m_tiles, J.n_tiles);
+        wgs += xcd_tile_grid(J.batches * J.m_data, J.n_tiles);
     }
+    args.zero_begin = wgs;
+    wgs += xcd_tile_grid(args.job[0].batches * (args.job[0].m_tiles - args.job[0].m_data), args.job[0].n_tiles);
     if (wgs == 0) return hipSuccess;
     static std::once_flag once;
     static hipError_t attr = hipSuccess;
@@ -651,14 +663,14 @@ template <> constexpr GemmCost gemm_cost<ShapeM2>() { return {3.0, {0.50, 0.58}}
 template <> constexpr GemmCost gemm_cost<ShapeS>() { return {2.5, {0.30, 0.40}}; }
 template <> constexpr GemmCost gemm_cost<ShapeS4>() { return {3.3, {0.165, 0.22}}; }
 
-// `tiles`: contraction tiles of a workgroup
+// `tiles`: contraction tiles of a workgroup on average, `rest_tiles`: of those in the last, part-filled round
 template <typename S>
-double gemm_estimate(double wgs, double tiles)
+double gemm_estimate(double wgs, double tiles, double rest_tiles)
 {
     constexpr GemmCost c = gemm_cost<S>();
     constexpr double room = 256.0 * S::PER_CU;
     const double full = (double)(int64_t)(wgs / room), rest = wgs - full * room;
-    return full * (c.fixed + tiles * c.per_tile[1]) + (rest > 0 ? c.fixed + tiles * c.per_tile[rest > (S::PER_CU == 1 ? 128 : 256)] : 0.0);
+    return full * (c.fixed + tiles * c.per_tile[1]) + (rest > 0 ? c.fixed + rest_tiles * c.per_tile[rest > (S::PER_CU == 1 ? 128 : 256)] : 0.0);
 }
 
 template <bool A_ANY, bool W_TR, bool OUT_F32, int EPI = EPI_NONE>
@@ -666,22 +678,29 @@ hipError_t launch_proj(ProjArgs &args, int kernel_id, hipStream_t st)
 {
     auto estimate = [&](auto shape) {
         using S = decltype(shape);
-        double wgs = 0, work = 0;
+        double wgs = 0, work = 0, last_n = 0, last_tiles = 0;
         for (int j = 0; j < args.n_jobs; ++j) {
             const ProjJob &J = args.job[j];
-            const double n = (double)J.batches * ((J.rows + S::TM - 1) / S::TM) * ((J.N + S::TN - 1) / S::TN);
+            const double n = (double)J.batches * ((std::min(J.rows, J.rows_ok) + S::TM - 1) / S::TM) * ((J.N + S::TN - 1) / S::TN);
             // A float A costs more the smaller the tile, whose workgroups re-read it more often, and the less of it
-            // fits the last-level cache (project_bwd, 1024 columns: 256 x 256 against 128 x 128 tiles take 79 and
-            // 62 us at 8192 rows, 109 and 111 at 16384, 208 and 278 at 32768)
-            double slow = 1.0;
+            // fits the last-level cache (project_bwd, 1024 columns: 256 x 256 against 128 x 128 tiles take 64 and
+            // 57 us at 8192 rows, 102 and 97 at 16384, 156 and 165 at 24000)
+            double slow = 1.0, more = 0.0;
             if (J.a_f32) {
-                const double a_bytes = (double)J.batches * J.rows_ok * J.K * 4.0, far = a_bytes < 256e6 ? a_bytes / 256e6 : 1.0;
-                slow = S::TM == 256 ? 1.27 : S::TM == 128 ? 1.15 + 0.45 * far : 1.6 + 0.5 * far;
+                const int zero_rows = args.skip_tail ? 0 : J.rows - std::min(J.rows, J.rows_ok);       // their stores pass through it too
+                const double bytes = (double)J.batches * ((double)J.rows_ok * J.K + (double)zero_rows * J.N) * 4.0;
+                const double far = bytes < 256e6 ? bytes / 256e6 : 1.0;
+                slow = S::TM == 256 ? 1.05 + 0.35 * far : S::TM == 128 ? 1.15 + 0.35 * far : 1.6 + 0.5 * far;
+                more = S::TM == 256 ? 1.5 : S::TM == 128 ? 6.0 + 2.0 * far : 0.0;
             }
             wgs += n;
-            work += n * (J.K / PK) * slow;
+            last_n = n;
+            last_tiles = J.K / PK * slow + more;
+            work += n * last_tiles;
         }
-        return gemm_estimate<S>(wgs, wgs > 0 ? work / wgs : 0.0);
+        if (wgs <= 0) return 0.0;
+        const double room = 256.0 * S::PER_CU, rest = wgs - room * (double)(int64_t)(wgs / room), tiles = work / wgs;
+        return gemm_estimate<S>(wgs, tiles, rest <= last_n ? last_tiles : tiles);     // (the last job's workgroups start last)
     };
     const double t[5] = {estimate(ShapeL{}), estimate(ShapeM{}), estimate(ShapeM2{}), estimate(ShapeS{}), estimate(ShapeS4{})};
     int best = 0;
@@ -813,7 +832,8 @@ static WgradPlan wgrad_plan(int rows, int batches, int K, int N)
         auto estimate = [&](auto shape) {
             using S = decltype(shape);
             // (both operands through transposing reads: a fifth slower per tile, but for the largest)
-            return sum + gemm_estimate<S>(parts * ((K + S::TM - 1) / S::TM) * ((N + S::TN - 1) / S::TN), chunk_tiles * (S::TM == 256 ? 1.0 : 1.2));
+            const double tiles = chunk_tiles * (S::TM == 256 ? 1.0 : 1.2);
+            return sum + gemm_estimate<S>(parts * ((K + S::TM - 1) / S::TM) * ((N + S::TN - 1) / S::TN), tiles, tiles);
         };
         const double t[5] = {estimate(ShapeL{}), estimate(ShapeM{}), estimate(ShapeM2{}), estimate(ShapeS{}), estimate(ShapeS4{})};
         for (int i = 0; i < 5; ++i)
