@@ -65,10 +65,9 @@ __global__ __launch_bounds__(256) void bwd_dq_merge_kernel(const float *__restri
 //     take 54 us in ranges of 51 tiles and 38 in ranges of 26; in longer launches shorter ranges gain nothing.
 //     Where one workgroup fills a compute unit (d = 128), a launch that fits the chip keeps fitting it.
 //   * float: 16 tiles (each takes four times as long).
-static int pick_dq_splits(const SegShape &s, int elem_bytes)
+static int pick_dq_splits(const SegShape &s, int most, int elem_bytes)
 {
     const int rows_per_wg = dq_rows_per_wg(elem_bytes, s.d);
-    const int most = choose_splits(s.l_s, s.l_x, s.B, s.H, rows_per_wg);
     if (most <= 1) return 1;
     const int64_t bhs = (int64_t)s.B * s.H, seen = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
     const int64_t tiles = (seen + 63) / 64;                                     // key tiles of a query tile
@@ -100,9 +99,12 @@ static hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const T *q
                                const Workspace &ws, hipStream_t st)
 {
     hipError_t e;
-    const int n_splits = pick_dq_splits(s, (int)sizeof(T));
+    const int most = choose_splits(s.l_s, s.l_x, s.B, s.H, dq_rows_per_wg((int)sizeof(T), D));
+    const int one_pass = skinny_splits(s, dr.thr != 0, (int)sizeof(T), most);
+    const int n_splits = one_pass > 0 ? one_pass : pick_dq_splits(s, most, (int)sizeof(T));
     if constexpr (sizeof(T) == 2) {
-        if ((e = launch_bwd_bf16_main(s, dr, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, st)) != hipSuccess)
+        if ((e = launch_bwd_bf16_main(s, dr, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, one_pass > 0, st)) !=
+            hipSuccess)
             return e;
     } else {
         {

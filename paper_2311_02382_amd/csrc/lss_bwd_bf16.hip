@@ -13,6 +13,8 @@
 #include "lss_bf16.h"
 #include <type_traits>
 #include "lss_kernels.h"
+#include <algorithm>
+#include <mutex>
 
 namespace lss {
 
@@ -972,6 +974,334 @@ __device__ __forceinline__ void bwd_dkv_skinny_body(char *smem, const SegShape &
     }
 }
 
+// ------------------------------------------------------------------------------- dQ, dK and dV in one pass
+// Segments of at most 128 rows with many heads and keys: all three gradients from ONE read of K and V.  The traffic is
+// all that such a backward is (25,000 visible keys, 32 heads: 205 MB read, 410 MB of partials written, 122 us), and with
+// workgroups of their own for dQ and for dK/dV the reads come twice and the dQ workgroups, half of whose wavefronts have no
+// rows, take as long as the others (171 us; here 104).  A workgroup owns one (batch*head, split) and walks the split's
+// 128-key tiles; each wavefront takes a 32-key block of its own at a time and meets the others only at the start and
+// at the end:
+//   * Its K block travels global -> LDS (4 KB, double-buffered, private to the wavefront: plain reads for S, transposing
+//     ones for dQ), its V block through a slot of its own into registers; both a block ahead.
+//   * S and dP (lane = key) give the operands of dV^T and dK^T as in bwd_dkv_body; the same operands
+//     exchanged give S^T and dP^T (lane = query), whose weights are the second operand of dQ^T += K^T dS^T as in
+//     bwd_dq_body.  Computing the weights twice is cheaper here than turning them round through LDS.
+//   * dK and dV are made 32 columns at a time and leave at once through the K slot just used up.
+//   * dQ stays in accumulators; the four wavefronts' are added up at the end, in wavefront order.
+// QB = 32-row blocks of the segment.  With two the program order is fixed, so that 256 registers and with them two
+// workgroups per compute unit suffice; with three or four a wavefront has 512 and the compiler overlaps the blocks
+// (100 rows: 163 -> 157 us).
+template <int D, int QB_>
+struct SkinnyCfg {
+    static constexpr int QB = QB_, ROWS = 32 * QB, NT = 256, BKV = 128, NU = D / 16;
+    using QTile = DirectTile<D, ROWS>;
+    using KTile = DirectTile<D, 32, 1>;
+    // Q tile, dO tile, start values as in a ring slot of DkvBf16Cfg; then two K slots and a V slot per wavefront
+    static constexpr int OFF_G = QTile::BYTES, OFF_L = 2 * QTile::BYTES, OFF_D = OFF_L + ROWS * 4, OFF_K = (OFF_D + ROWS * 4 + 1023) / 1024 * 1024;
+    // (the four wavefronts' slots also hold two wavefronts' dQ at the end)
+    static constexpr int SLOTS = 12 * KTile::BYTES, HAND = 2 * QB * (D / 32) * 4096;
+    static constexpr int SMEM = OFF_K + (SLOTS > HAND ? SLOTS : HAND);
+};
+
+// One accumulator block, 32 keys x 32 columns, through `buf` (4 KB) to rows of `dst`: 128 bytes of 8 keys per instruction
+template <int D>
+__device__ __forceinline__ void store_key_columns(char *buf, const f32x16 &g, float scale, float *__restrict__ dst, int64_t ld, int rows_ok,
+                                                  int lane)
+{
+    const int lq = lane & 31, hh = lane >> 5;
+#pragma unroll
+    for (int e4 = 0; e4 < 4; ++e4)
+        *reinterpret_cast<f32x4 *>(buf + lq * 128 + (((2 * e4 + hh) ^ (lq & 7)) * 16)) =
+            f32x4{g[4 * e4] * scale, g[4 * e4 + 1] * scale, g[4 * e4 + 2] * scale, g[4 * e4 + 3] * scale};
+    const int c = lane & 7, row = lane >> 3;
+    const uint32_t at = ((uint32_t)row * (uint32_t)ld + (uint32_t)c * 4u) * 4u;        // (8 rows of at most 2^23 floats)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const f32x4 val = *reinterpret_cast<const f32x4 *>(buf + (i * 8 + row) * 128 + ((c ^ row) * 16));
+        if (i * 8 + row < rows_ok) __builtin_nontemporal_store(val, reinterpret_cast<f32x4 *>(reinterpret_cast<char *>(dst + (int64_t)(i * 8) * ld) + at));
+    }
+}
+
+template <int D, int QB>
+__global__ __launch_bounds__(256, QB == 2 ? 2 : 1) void bwd_skinny_bf16_kernel(
+    SegShape s, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
+    const bf16_t *__restrict__ out, const bf16_t *__restrict__ dO, const float *__restrict__ lse, bf16_t *__restrict__ dq,
+    float *__restrict__ dq_part, float *__restrict__ dk_part, float *__restrict__ dv_part, int n_splits)
+{
+    using C = SkinnyCfg<D, QB>;
+    using QTile = typename C::QTile;
+    using KTile = typename C::KTile;
+    constexpr int NU = C::NU, DB = D / 32;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+
+    int bh, split;
+    if (!xcd_item(blockIdx.x, s.B * s.H, n_splits, false, bh, split)) return;
+    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = bh / s.H, h = bh % s.H;
+    const int64_t ld = (int64_t)s.H * D;
+    const int64_t kv_base = (int64_t)b * s.l_x * ld + (int64_t)h * D, q_base = (int64_t)b * s.l_s * ld + (int64_t)h * D;
+    const int n_key_tiles = (s.l_x + C::BKV - 1) / C::BKV;
+    // key tiles from kt_vis on are seen by no query of the segment
+    const int kt_vis = s.causal ? (int)min<int64_t>((s.s0 + s.l_s + C::BKV - 1) / C::BKV, n_key_tiles) : n_key_tiles;
+    const int kt0 = (int)((int64_t)kt_vis * split / n_splits), kt1 = (int)((int64_t)kt_vis * (split + 1) / n_splits);
+
+    char *const k_slots = smem + C::OFF_K + wave * 3 * KTile::BYTES, *const v_slot = k_slots + 2 * KTile::BYTES;
+    // (a load instruction's rows start at a multiple of 8 whose permutation is the same: one offset serves them all)
+    static_assert(D == 64, "");
+    const uint32_t offK = ((uint32_t)(lane / 8) * (uint32_t)ld + (uint32_t)((lane % 8) ^ (lane / 8)) * 8u) * 2u;
+    // the wavefront's block of key tile kt: rows past the sequence re-read its last row, are masked and never stored
+    auto load_kv = [&](int kt, int slot) __attribute__((always_inline)) {
+        const int jw0 = kt * C::BKV + wave * 32, j_first = min(jw0, s.l_x - 1);
+        const int64_t at = kv_base + (int64_t)j_first * ld;
+        char *const dst = k_slots + slot * KTile::BYTES;
+        if (jw0 + 32 <= s.l_x) {
+#pragma unroll
+            for (int i = 0; i < KTile::NI; ++i) {
+                lds_dma<16>(k + at + (int64_t)(8 * i) * ld, offK, dst + i * 1024);
+                lds_dma<16>(v + at + (int64_t)(8 * i) * ld, offK, v_slot + i * 1024);
+            }
+        } else {
+            uint32_t off[KTile::NI];
+            KTile::offsets(off, ld, s.l_x - j_first, 0, lane);
+            lds_dma_n<KTile::NI, 1024>(k + at, off, dst);
+            lds_dma_n<KTile::NI, 1024>(v + at, off, v_slot);
+        }
+    };
+
+    // ---- the segment's rows: Q and dO tile, start values; this lane's row of either block for the transposed products
+    {
+        uint32_t off[QTile::NI];
+        QTile::offsets(off, ld, s.l_s, wave, lane);
+#pragma unroll
+        for (int i = 0; i < QTile::NI; ++i) {
+            lds_dma<16>(q + q_base, off[i], smem + wave * 1024 + i * 4096);
+            lds_dma<16>(dO + q_base, off[i], smem + C::OFF_G + wave * 1024 + i * 4096);
+        }
+    }
+    if (kt0 < kt1) load_kv(kt0, 0);
+    {
+        float *const L = reinterpret_cast<float *>(smem + C::OFF_L), *const Dn = reinterpret_cast<float *>(smem + C::OFF_D);
+        for (int i = s.l_s + tid; i < C::ROWS; i += C::NT) { L[i] = -INFINITY; Dn[i] = 0.f; }   // rows past the segment: weights exactly 0
+        neg_row_dots<D>(out + q_base, dO + q_base, lse + (int64_t)bh * s.l_s, ld, s.l_s, tid, [&](int i, float nd, float l) {
+            L[i] = -l * sqrtf((float)D);
+            Dn[i] = nd;
+        });
+    }
+    wait_vmem_all();
+    __syncthreads();
+
+    const float sqrt_d = sqrtf((float)D), c = kLog2e / sqrt_d, scale = 1.f / sqrt_d;
+    float L2[C::QB], nd[C::QB];
+#pragma unroll
+    for (int qb = 0; qb < C::QB; ++qb) {
+        const int r = 32 * qb + lq;
+        L2[qb] = -reinterpret_cast<const float *>(smem + C::OFF_L)[r] * c;
+        nd[qb] = reinterpret_cast<const float *>(smem + C::OFF_D)[r];
+    }
+    int a_off[NU], t_off[DB];
+#pragma unroll
+    for (int kb = 0; kb < NU; ++kb) a_off[kb] = QTile::chunk_offset(lq, 2 * kb + hh);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) t_off[db] = tr_lane_offset_sw<D>(lane, db);
+
+    f32x16 acc[C::QB][DB];
+#pragma unroll
+    for (int qb = 0; qb < C::QB; ++qb)
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[qb][db][e] = 0.f;
+
+    for (int kt = kt0; kt < kt1; ++kt) {
+        const int slot = (kt - kt0) & 1;
+        char *const kblk = k_slots + slot * KTile::BYTES;
+        // The block's loads have landed: of what was issued after them, 16 stores at most are still on their way (every
+        // block but a sequence's last stores all its rows).
+        if (kt > kt0) wait_vmem<16>();
+        const int jw0 = kt * C::BKV + wave * 32, j = jw0 + lq;
+        Frag<bf16_t> kf[NU], vf[NU];
+#pragma unroll
+        for (int kb = 0; kb < NU; ++kb) {
+            kf[kb] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(kblk + a_off[kb]));
+            vf[kb] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(v_slot + a_off[kb]));
+        }
+        if (kt + 1 < kt1) {
+            asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");       // V is in registers: its slot takes the next block's
+            load_kv(kt + 1, slot ^ 1);
+        }
+        Frag<bf16_t> pf[C::QB][2], df[C::QB][2];
+#pragma unroll
+        for (int qb = 0; qb < C::QB; ++qb) {
+            const int r0 = 32 * qb;
+            const char *const qt = smem + r0 * (D * 2);
+            const bool diag = s.causal && jw0 + 31 > (int)s.s0 + r0;
+            if constexpr (QB == 2) __builtin_amdgcn_sched_barrier(0);
+            // ---- lane = key: the operands P and dS of dV^T and dK^T
+            {
+                f32x16 sc, dp;
+#pragma unroll
+                for (int e4 = 0; e4 < 4; ++e4) {
+                    const f32x4 l4 = *reinterpret_cast<const f32x4 *>(smem + C::OFF_L + (r0 + 8 * e4 + 4 * hh) * 4);
+                    const f32x4 d4 = *reinterpret_cast<const f32x4 *>(smem + C::OFF_D + (r0 + 8 * e4 + 4 * hh) * 4);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) { sc[4 * e4 + i] = l4[i]; dp[4 * e4 + i] = d4[i]; }
+                }
+                if (diag) {
+                    const int first = max(min(j - (int)s.s0 - r0 - 4 * hh, 64), 0);
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        if (8 * (e >> 2) + (e & 3) < first) sc[e] = -INFINITY;
+                }
+#pragma unroll
+                for (int kb = 0; kb < NU; ++kb) {
+                    sc = mma(load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(qt + a_off[kb])), kf[kb], sc);
+                    dp = mma(load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(qt + C::OFF_G + a_off[kb])), vf[kb], dp);
+                }
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const float pw = fast_exp2(sc[e] * c);
+                    pf[qb][e >> 3].v[e & 7] = (bf16_t)pw;
+                    df[qb][e >> 3].v[e & 7] = (bf16_t)(pw * dp[e]);
+                }
+            }
+            if constexpr (QB == 2) asm volatile("" : : : "memory");     // (the row operands are read again, not kept)
+            // ---- lane = query: dQ^T += K^T dS^T
+            {
+                f32x16 sc, dp;
+                float nd_here = nd[qb];
+                if constexpr (QB == 2) asm volatile("" : "+v"(nd_here));       // (so that the start values are made here, not kept in 16 registers)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) { sc[e] = 0.f; dp[e] = nd_here; }
+#pragma unroll
+                for (int kb = 0; kb < NU; ++kb) {
+                    sc = mma(kf[kb], load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(qt + a_off[kb])), sc);
+                    dp = mma(vf[kb], load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(qt + C::OFF_G + a_off[kb])), dp);
+                }
+                if (diag || jw0 + 32 > s.l_x) {
+                    const int last = s.causal ? min((int)s.s0 + r0 + lq, s.l_x - 1) : s.l_x - 1;
+                    const int rel = max(min(last - jw0 - 4 * hh, 64), -1);
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        if (8 * (e >> 2) + (e & 3) > rel) sc[e] = -INFINITY;
+                }
+                Frag<bf16_t> dt[2];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) dt[e >> 3].v[e & 7] = (bf16_t)(fast_exp2(sc[e] * c - L2[qb]) * dp[e]);
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    const int half = u / DB, db = u % DB;
+                    acc[qb][db] = mma(load_frag_tr_sw<D>(kblk, half * 16, t_off[db]), dt[half], acc[qb][db]);
+                }
+            }
+        }
+        if constexpr (QB == 2) __builtin_amdgcn_sched_barrier(0);
+        // ---- dV^T += dO^T P, dK^T += Q^T dS, a column block at a time, each written at once
+        const int64_t off = kv_base + (int64_t)jw0 * ld;
+        auto finish = [&](const char *tile, const Frag<bf16_t> (&w)[C::QB][2], int db, float f, float *dst) __attribute__((always_inline)) {
+            f32x16 g;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) g[e] = 0.f;
+#pragma unroll
+            for (int qb = 0; qb < C::QB; ++qb)
+#pragma unroll
+                    for (int half = 0; half < 2; ++half) g = mma(load_frag_tr_sw<D>(tile, (qb * 2 + half) * 16, t_off[db]), w[qb][half], g);
+            store_key_columns<D>(kblk, g, f, dst + off + db * 32, ld, s.l_x - jw0, lane);
+            if constexpr (QB == 2) __builtin_amdgcn_sched_barrier(0);
+        };
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            finish(smem, df, db, scale, dk_part);
+            finish(smem + C::OFF_G, pf, db, 1.f, dv_part);
+        }
+    }
+
+    // ---- key tiles that no query sees, dealt out among the splits: zeros, or nothing if the caller asked for that
+    if (!s.skip_tail) {
+        constexpr int F4 = D / 4;
+        const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+        for (int kt = kt_vis + split; kt < n_key_tiles; kt += n_splits)
+            for (int i = tid; i < C::BKV * F4; i += C::NT) {
+                const int row = kt * C::BKV + i / F4, c4 = (i % F4) * 4;
+                if (row < s.l_x) {
+                    __builtin_nontemporal_store(z, reinterpret_cast<f32x4 *>(dk_part + kv_base + (int64_t)row * ld + c4));
+                    __builtin_nontemporal_store(z, reinterpret_cast<f32x4 *>(dv_part + kv_base + (int64_t)row * ld + c4));
+                }
+            }
+    }
+
+    // ---- dQ: waves 2 and 3 hand theirs to 0 and 1, then 1 to 0 (the K slots are free once everybody is here)
+    constexpr int BLOCKS = C::QB * DB;
+    auto hand = [&](int region, int blk, int e4) __attribute__((always_inline)) {
+        return reinterpret_cast<f32x4 *>(smem + C::OFF_K + ((region * BLOCKS + blk) * 4 + e4) * 1024 + lane * 16);
+    };
+#pragma unroll
+    for (int step = 2; step >= 1; step >>= 1) {
+        __syncthreads();
+        if (wave >= step && wave < 2 * step) {
+#pragma unroll
+            for (int blk = 0; blk < BLOCKS; ++blk)
+#pragma unroll
+                for (int e4 = 0; e4 < 4; ++e4) {
+                    const f32x16 &a = acc[blk / DB][blk % DB];
+                    *hand(wave - step, blk, e4) = f32x4{a[4 * e4], a[4 * e4 + 1], a[4 * e4 + 2], a[4 * e4 + 3]};
+                }
+        }
+        __syncthreads();
+        if (wave < step) {
+#pragma unroll
+            for (int blk = 0; blk < BLOCKS; ++blk)
+#pragma unroll
+                for (int e4 = 0; e4 < 4; ++e4) {
+                    const f32x4 other = *hand(wave, blk, e4);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[blk / DB][blk % DB][4 * e4 + i] += other[i];
+                }
+        }
+    }
+    if (wave > 0) return;
+#pragma unroll
+    for (int qb = 0; qb < C::QB; ++qb) {
+        const int r = 32 * qb + lq;
+        if (r >= s.l_s) continue;
+        const int64_t off = ((int64_t)b * s.l_s + r) * ld + (int64_t)h * D;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) {
+                f32x4 val;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) val[i] = acc[qb][db][4 * e4 + i] * scale;
+                const int col = db * 32 + 8 * e4 + 4 * hh;
+                if (n_splits == 1) *reinterpret_cast<bf16x4 *>(dq + off + col) = pack4(val[0], val[1], val[2], val[3]);
+                else *reinterpret_cast<f32x4 *>(dq_part + (int64_t)split * s.B * s.l_s * ld + off + col) = val;
+            }
+    }
+}
+
+// Splits of the one-pass kernel, 0 where dQ and dK/dV workgroups of their own are the better ones.  Segments of 33..64
+// rows run two workgroups per compute unit, longer ones (96 or 128 rows' accumulators) one, and a count that fills the
+// chip once is taken, with two tiles per workgroup at least -- three where they share compute units.  Times in us, from
+// launches of 65..15000 (batch*head, tile) pairs: a lone workgroup takes 3.3, 4.6 or 5.6 per 128-key tile (64, 96, 128 rows) and
+// 9 to 16 besides; the two kinds together take what follows from the tiles of all heads, or from the zeros they fill
+// beside them (here that comes last).  32 heads of 58 rows against 25,056 keys: 171 -> 104 us, of 100: 209 -> 157.
+int skinny_splits(const SegShape &s, bool with_drop, int elem_bytes, int most)
+{
+    if (elem_bytes != 2 || with_drop || s.d != 64 || s.l_s > 128) return 0;
+    const int64_t bhs = (int64_t)s.B * s.H, seen = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
+    const int64_t tiles = (seen + 127) / 128;
+    const bool two = s.l_s <= 64;
+    int64_t n = std::min<int64_t>(256 / bhs, (tiles + 1) / 2);
+    if (two) n = std::max(n, std::min<int64_t>(512 / bhs, tiles / 3));
+    n = std::min<int64_t>(n, most);
+    if (n < 1) return 0;
+    const double walk = (double)((tiles + n - 1) / n), all = (double)(tiles * bhs);
+    const double zeros = s.skip_tail ? 0.0 : (double)(s.l_x - seen) * bhs * s.d * 8.0 / 5.0e6;
+    const double here = two ? 9.0 + 3.3 * walk : (s.l_s <= 96 ? 10.0 + 4.6 * walk : 16.0 + 5.6 * walk) + zeros;
+    const double there = two ? 14.0 + 0.02 * all : 9.0 + std::max(0.03 * all, zeros);
+    return here < there ? (int)n : 0;
+}
+
 int dq_bf16_rows_per_workgroup(int d) { return d == 64 ? DqBf16Cfg<64>::BR : DqBf16Cfg<128>::BR; }
 
 // ------------------------------------------------------------------------------------------ launch
@@ -1059,15 +1389,40 @@ static bool bwd_own_values(const SegShape &s, int n_splits)
     return own_us * rounds <= 2.0;
 }
 
+template <int QB>
+static hipError_t launch_skinny(const SegShape &s, const bf16_t *q, const bf16_t *k, const bf16_t *v, const bf16_t *out, const float *lse,
+                                const bf16_t *dO, bf16_t *dq, float *dk_part, float *dv_part, const Workspace &ws, int n_splits,
+                                hipStream_t st)
+{
+    using C = SkinnyCfg<64, QB>;
+    const auto kernel = bwd_skinny_bf16_kernel<64, QB>;
+    static std::once_flag once;
+    static hipError_t attr = hipSuccess;
+    std::call_once(once, [&] {
+        attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, C::SMEM);
+    });
+    if (attr != hipSuccess) return attr;
+    TimedLaunch tl(K_BWD_MAIN_BF16, st);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)xcd_grid(s.B * s.H, n_splits)), dim3(256), C::SMEM, st, s, q, k, v, out, dO, lse, dq, ws.dq_part,
+                       dk_part, dv_part, n_splits);
+    return hipGetLastError();
+}
+
 template <int D>
 static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                     const bf16_t *v, const bf16_t *out, const float *lse, const bf16_t *dO, bf16_t *dq,
                                     float *dk_part, float *dv_part, const Workspace &ws, int n_splits,
-                                    hipStream_t st)
+                                    bool one_pass, hipStream_t st)
 {
     hipError_t e;
     const bool with_drop = drop.thr != 0;
     const bool skinny = !with_drop && s.l_s <= kSkinnyRows, own = bwd_own_values<D>(s, n_splits);
+    if constexpr (D == 64) {
+        if (one_pass)
+            return s.l_s <= 64 ? launch_skinny<2>(s, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, st)
+                 : s.l_s <= 96 ? launch_skinny<3>(s, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, st)
+                               : launch_skinny<4>(s, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, st);
+    }
     if (!own) {
         const int64_t items = (int64_t)s.B * s.l_s * s.H * (D / 8);
         const dim3 grid((unsigned)((items + 255) / 256));
@@ -1094,10 +1449,10 @@ static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, con
 // launch; the caller runs the dQ split merge
 hipError_t launch_bwd_bf16_main(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                 const bf16_t *v, const bf16_t *out, const float *lse, const bf16_t *dO, bf16_t *dq,
-                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, hipStream_t st)
+                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, bool one_pass, hipStream_t st)
 {
-    if (s.d == 64) return launch_bwd_bf16_d<64>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, st);
-    return launch_bwd_bf16_d<128>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, st);
+    if (s.d == 64) return launch_bwd_bf16_d<64>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, one_pass, st);
+    return launch_bwd_bf16_d<128>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, one_pass, st);
 }
 
 } // namespace lss

@@ -37,6 +37,9 @@ int pick_fwd_splits(int l_s, int B, int H, int rows_per_wg, int64_t kv_tiles, in
 int fwd_rows_per_wg(int elem_bytes, int d);     // query rows per workgroup of the forward kernel
 int dq_rows_per_wg(int elem_bytes, int d);      // ... and of the dQ kernel
 
+// Key splits of the backward kernel that makes all three gradients in one pass, 0 where another one is taken; at most `most`.
+int skinny_splits(const SegShape &s, bool with_drop, int elem_bytes, int most);
+
 struct Workspace {
     // forward
     float *o_part;    // [splits, B*H, l_s, d] in the storage type (bf16 kernels write bf16 here)
@@ -77,7 +80,7 @@ hipError_t launch_bwd_f32_main(const SegShape &s, const DropArgs &drop, const fl
 int dq_bf16_rows_per_workgroup(int d);
 hipError_t launch_bwd_bf16_main(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                 const bf16_t *v, const bf16_t *out, const float *lse, const bf16_t *dO, bf16_t *dq,
-                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, hipStream_t st);
+                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, bool one_pass, hipStream_t st);
 
 // Optional per-kernel timing for benchmarks (lss_timing.h): when enabled, every launch site
 // brackets its kernel with a pair of HIP events on the launch stream.  One id per __global__

@@ -19,6 +19,9 @@ SHAPES = [  # B, l_x, H, d, s0, l_s, causal
     (3, 260, 11, 64, 0, 260, True), (1, 2000, 13, 64, 1700, 300, True),     # heads that the eight XCDs share
     (2, 1500, 27, 64, 1200, 65, True), (1, 700, 9, 128, 5, 300, False),
     (1, 2752, 2, 64, 2240, 512, True), (1, 2752, 2, 64, 2239, 513, True),   # the backward's row sums: within its workgroups or ahead
+    # few rows, many keys: all gradients in one pass, with two, three and four blocks of 32 rows
+    (1, 1403, 20, 64, 1203, 58, True), (1, 1403, 20, 64, 900, 33, False), (3, 1500, 11, 64, 1436, 64, True), (1, 1440, 24, 64, 7, 1, False),
+    (2, 1480, 20, 64, 1350, 65, True), (2, 1480, 20, 64, 100, 96, False), (2, 2001, 32, 64, 1830, 128, True), (2, 1990, 32, 64, 1500, 97, False),
 ]
 
 
