@@ -9,7 +9,7 @@
 #include "lss_common.h"
 #include "lss_kernels.h"
 
-#include <mutex>
+#include <algorithm>
 
 namespace lss {
 
@@ -140,30 +140,29 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const bf16_t *__rest
     if (lane == 0) { mean[row] = mu; rstd[row] = rs; }
 }
 
-// Backward of the above.  A workgroup owns LN_ROWS consecutive rows, one wavefront walks every
-// fourth of them: dx of a row needs two row sums; the contributions to dgamma and dbeta stay in the
-// lane that owns the columns and are added up over the wavefront's rows in row order, then over the
-// four wavefronts in wavefront order (through LDS) into part[workgroup] -- a second kernel adds
-// the workgroups' parts in a fixed order.
-constexpr int LN_ROWS = 32;
+// Backward of the above, two kinds of workgroup in one launch, for every LN_ROWS rows ("part") LN_ROWS / 4 of the first and
+// one of the second per 128 columns.  By rows: a wavefront takes one row, whose dx needs two row sums.  By columns: a
+// thread adds up one chunk's contributions to dgamma and dbeta over every 16th row, the 16 sums are added in order
+// (through LDS) into part[], and a second kernel adds the parts in a fixed order.  x and dy are read twice, the second
+// time mostly from the cache; in return no row waits for another one: with a workgroup per part that does both, each
+// wavefront 8 rows in turn, short segments run on a handful of compute units.  Bound by the latency of one load and the two
+// row sums, then by memory.  61 rows of 1152: 20.0 -> 4.8 us, 1826 of 1664: 30 -> 7.5, 16384 of 1024 (100 MB): 29 -> 26.5.
+constexpr int LN_ROWS = 32, LN_COLS = 128, LN_ROW_WGS = LN_ROWS / 4;
+// workgroups [first, first + gridDim.x) of those of a part; all of them by default, or one kind after the other if dx
+// stands in x's or dy's place
 template <int NCH>
-__global__ __launch_bounds__(256) void layernorm_bwd_kernel(const bf16_t *__restrict__ x, const float *__restrict__ gamma,
+__global__ __launch_bounds__(256) void layernorm_bwd_kernel(const bf16_t *x, const float *__restrict__ gamma,
                                                             const float *__restrict__ mean, const float *__restrict__ rstd,
-                                                            const bf16_t *__restrict__ dy, int64_t rows, int E,
-                                                            bf16_t *__restrict__ dx, float *__restrict__ part)
+                                                            const bf16_t *dy, int64_t rows, int E, bf16_t *dx,
+                                                            float *__restrict__ part, int first)
 {
-    extern __shared__ float red[];              // [4][2][E]
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int cpr = E / 8;
-    float dg[NCH][8], db[NCH][8];
-#pragma unroll
-    for (int k = 0; k < NCH; ++k)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { dg[k][e] = 0.f; db[k][e] = 0.f; }
-    const int64_t row0 = (int64_t)blockIdx.x * LN_ROWS;
-    for (int i = wave; i < LN_ROWS; i += 4) {
-        const int64_t row = row0 + i;
-        if (row >= rows) break;
+    const int tid = threadIdx.x, cpr = E / 8, kind = (int)blockIdx.x + first;
+    const int64_t in_part = (int64_t)blockIdx.z * gridDim.y + blockIdx.y, row0 = in_part * LN_ROWS;
+    if (row0 >= rows) return;
+    if (kind < LN_ROW_WGS) {
+        const int lane = tid & 63;
+        const int64_t row = row0 + kind * 4 + (tid >> 6);
+        if (row >= rows) return;
         const float mu = mean[row], rs = rstd[row];
         float xh[NCH][8], g[NCH][8];
         float s1 = 0.f, s2 = 0.f;
@@ -180,8 +179,6 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const bf16_t *__rest
                     g[k][e] = dv[e] * gamma[c * 8 + e];
                     s1 += g[k][e];
                     s2 += g[k][e] * xh[k][e];
-                    dg[k][e] += dv[e] * xh[k][e];
-                    db[k][e] += dv[e];
                 }
             }
         }
@@ -196,43 +193,62 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const bf16_t *__rest
                 *reinterpret_cast<bf16x8 *>(dx + (row * cpr + c) * 8) = pack8(o);
             }
         }
+        return;
     }
+    __shared__ f32x4 red[16][4][16];            // [rows i, i + 16][dgamma, dgamma, dbeta, dbeta][chunk]
+    const int cc = tid & 15, grp = tid >> 4, c = (kind - LN_ROW_WGS) * 16 + cc;
+    f32x4 acc[4] = {};
+    if (c < cpr)
 #pragma unroll
-    for (int k = 0; k < NCH; ++k) {
-        const int c = lane + 64 * k;
-        if (c < cpr) {
+        for (int j = 0; j < LN_ROWS / 16; ++j) {
+            const int64_t row = row0 + grp + 16 * j;
+            if (row >= rows) break;
+            const float mu = mean[row], rs = rstd[row];
+            float xv[8], dv[8];
+            unpack8(*reinterpret_cast<const bf16x8 *>(x + (row * cpr + c) * 8), xv);
+            unpack8(*reinterpret_cast<const bf16x8 *>(dy + (row * cpr + c) * 8), dv);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                red[(wave * 2 + 0) * E + c * 8 + e] = dg[k][e];
-                red[(wave * 2 + 1) * E + c * 8 + e] = db[k][e];
+                acc[e / 4][e % 4] += dv[e] * ((xv[e] - mu) * rs);
+                acc[2 + e / 4][e % 4] += dv[e];
             }
         }
-    }
-    __syncthreads();
-    for (int col = threadIdx.x; col < 2 * E; col += 256) {
-        const int which = col / E, cc = col % E;
-        float acc = red[(0 * 2 + which) * E + cc];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) acc += red[(w * 2 + which) * E + cc];
-        part[((int64_t)blockIdx.x * 2 + which) * E + cc] = acc;
+    for (int k = 0; k < 4; ++k) red[grp][k][cc] = acc[k];
+    __syncthreads();
+    if (tid < 64 && c < cpr) {                  // four columns of dgamma or dbeta each
+        f32x4 sum = red[0][grp][cc];
+#pragma unroll
+        for (int g = 1; g < 16; ++g) sum += red[g][grp][cc];
+        *reinterpret_cast<f32x4 *>(part + (in_part * 2 + grp / 2) * E + c * 8 + (grp % 2) * 4) = sum;
     }
 }
-// 64 columns x 16 groups of parts per workgroup: thread (group pg, chunk cc) adds parts pg, pg + 16, ...
-// of its four columns in increasing order, then the 16 group sums are added in group order.
+// 16 columns x 64 groups of parts per workgroup: thread (group pg, chunk cc) adds parts pg, pg + 64, ...
+// of its four columns in increasing order, then the 64 group sums are added in two steps of eight, in group order.
+// (16,384 rows of 1024 have 512 parts: with 64 columns x 16 groups 32 workgroups took 12.6 us, these 4.8.)
 __global__ __launch_bounds__(256) void layernorm_bwd_params_kernel(const float *__restrict__ part, int n_parts, int E,
                                                                    float *__restrict__ dgamma, float *__restrict__ dbeta)
 {
-    __shared__ f32x4 red[16][16];
-    const int cc = threadIdx.x & 15, pg = threadIdx.x >> 4;
-    const int col = (blockIdx.x * 16 + cc) * 4;         // [0, 2E): dgamma's columns, then dbeta's
+    __shared__ f32x4 red[64][4];
+    const int cc = threadIdx.x & 3, pg = threadIdx.x >> 2;
+    const int col = (blockIdx.x * 4 + cc) * 4;          // [0, 2E): dgamma's columns, then dbeta's
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     if (col < 2 * E)
-        for (int p = pg; p < n_parts; p += 16) acc += *reinterpret_cast<const f32x4 *>(part + (int64_t)p * 2 * E + col);
+#pragma unroll 4
+        for (int p = pg; p < n_parts; p += 64) acc += *reinterpret_cast<const f32x4 *>(part + (int64_t)p * 2 * E + col);
     red[pg][cc] = acc;
+    __syncthreads();
+    if (pg < 8) {
+        acc = red[pg * 8][cc];
+#pragma unroll
+        for (int j = 1; j < 8; ++j) acc += red[pg * 8 + j][cc];
+    }
+    __syncthreads();
+    if (pg < 8) red[pg][cc] = acc;
     __syncthreads();
     if (pg == 0 && col < 2 * E) {
 #pragma unroll
-        for (int j = 1; j < 16; ++j) acc += red[j][cc];
+        for (int j = 1; j < 8; ++j) acc += red[j][cc];
         *reinterpret_cast<f32x4 *>(col < E ? dgamma + col : dbeta + (col - E)) = acc;
     }
 }
@@ -315,28 +331,24 @@ hipError_t launch_layernorm_bwd(const bf16_t *x, const float *gamma, const float
 {
     const int n_parts = (int)((rows + LN_ROWS - 1) / LN_ROWS);
     if (rows > 0) {
-        // the widest variant's LDS (4 wavefronts x 2 x E floats) exceeds the default limit
-        static std::once_flag once;
-        static hipError_t attr = hipSuccess;
-        std::call_once(once, [] {
-            attr = hipFuncSetAttribute(reinterpret_cast<const void *>(layernorm_bwd_kernel<8>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 64 * LN_MAXC * 8 * (int)sizeof(float));
-        });
-        if (attr != hipSuccess) return attr;
         TimedLaunch tl(K_LN_BWD, st);
-        const dim3 grid((unsigned)n_parts);
-        const size_t lds = (size_t)8 * E * sizeof(float);
-#define LSS_LN_BWD(NCH) hipLaunchKernelGGL(layernorm_bwd_kernel<NCH>, grid, dim3(256), lds, st, x, gamma, mean, rstd, dy, rows, E, dx, scratch)
-        if (E <= 512) LSS_LN_BWD(1);
-        else if (E <= 1024) LSS_LN_BWD(2);
-        else if (E <= 2048) LSS_LN_BWD(4);
-        else LSS_LN_BWD(8);
+        const int all = LN_ROW_WGS + (E + LN_COLS - 1) / LN_COLS;
+        const auto overlaps = [&](const bf16_t *p) { return dx < p + rows * E && p < dx + rows * E; };
+        const int apart = overlaps(x) || overlaps(dy) ? LN_ROW_WGS : 0;     // the column kind alone first
+        for (int first = apart, end = all; end > 0; end = first, first = 0) {
+            const dim3 grid((unsigned)(end - first), (unsigned)std::min(n_parts, 32768), (unsigned)((n_parts + 32767) / 32768));
+#define LSS_LN_BWD(NCH) hipLaunchKernelGGL(layernorm_bwd_kernel<NCH>, grid, dim3(256), 0, st, x, gamma, mean, rstd, dy, rows, E, dx, scratch, first)
+            if (E <= 512) LSS_LN_BWD(1);
+            else if (E <= 1024) LSS_LN_BWD(2);
+            else if (E <= 2048) LSS_LN_BWD(4);
+            else LSS_LN_BWD(8);
 #undef LSS_LN_BWD
+        }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     TimedLaunch tl(K_LN_PARAMS, st);
-    hipLaunchKernelGGL(layernorm_bwd_params_kernel, dim3((unsigned)((2 * E + 63) / 64)), dim3(256), 0, st, scratch, n_parts, E,
+    hipLaunchKernelGGL(layernorm_bwd_params_kernel, dim3((unsigned)((2 * E + 15) / 16)), dim3(256), 0, st, scratch, n_parts, E,
                        dgamma, dbeta);
     return hipGetLastError();
 }

@@ -126,6 +126,19 @@ def test_layernorm_is_reproducible_and_checks_scratch():
     assert dx.numel() == 0 and not dg.any() and not db.any()
 
 
+@pytest.mark.parametrize("rows,E", [(1, 8), (33, 136), (64, 1928), (95, 4096)])
+def test_layernorm_backward_in_place(rows, E):
+    X, DY = staged(7220, (rows, E)), staged(7221, (rows, E))
+    G, Bt = staged(7222, (E,), "f32", shift=1.0), staged(7223, (E,), "f32")
+    _, mean, rstd = lss.lss_layernorm_fwd(X.dev, G.dev, Bt.dev)
+    want = lss.lss_layernorm_bwd(X.dev, G.dev, mean, rstd, DY.dev)
+    x, dy = X.dev.clone(), DY.dev.clone()
+    for got in (lss.lss_layernorm_bwd(X.dev, G.dev, mean, rstd, dy, dx=dy), lss.lss_layernorm_bwd(x, G.dev, mean, rstd, DY.dev, dx=x)):
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+    rdx, rdg, rdb = oracle.layernorm_bwd(X.f64, G.f64, DY.f64)
+    assert rel_err(to_np(want[0]), rdx) <= TOL["bf16"]["t"] and rel_err(to_np(want[1]), rdg) <= 1e-4 and rel_err(to_np(want[2]), rdb) <= 1e-4
+
+
 @pytest.mark.parametrize("n", [8, 1000 * 8, 257 * 1024])
 def test_gelu_matches_oracle(n):
     U, DG = staged(7300 + n % 97, (n,), std=2.0), staged(7301 + n % 97, (n,))
