@@ -108,6 +108,9 @@ int lss_segment_attn_fwd(const void *q_seg, const void *k, const void *v,
  *   dq [B, l_s, H, d] bf16 (written)
  *   dk_partial, dv_partial [B, l_x, H, d] float (every row written; with
  *   causal != 0 the rows >= seg_offset + l_s are exactly 0)
+ * A gradient may be written over `out` (dq == out, for instance): every value of `out`
+ * is then read before the first gradient is written.  Otherwise outputs overlap neither
+ * inputs nor each other.
  */
 int lss_segment_attn_bwd(const void *q_seg, const void *k, const void *v,
                          int64_t seg_offset, int64_t l_s, int64_t l_x,

@@ -100,11 +100,16 @@ static hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const T *q
 {
     hipError_t e;
     const int most = choose_splits(s.l_s, s.l_x, s.B, s.H, dq_rows_per_wg((int)sizeof(T), D));
-    const int one_pass = skinny_splits(s, dr.thr != 0, (int)sizeof(T), most);
+    // Gradients may be written over `out`, which nothing reads afterwards.  Workgroups that compute D themselves read all
+    // rows of `out` while others write gradients: then a launch of its own reads it first.
+    const size_t rows_bytes = (size_t)s.B * s.l_s * s.H * D * sizeof(T), part_bytes = (size_t)s.B * s.l_x * s.H * D * sizeof(float);
+    const bool out_first = overlaps(dq, rows_bytes, out, rows_bytes) || overlaps(dk_part, part_bytes, out, rows_bytes) ||
+                           overlaps(dv_part, part_bytes, out, rows_bytes);
+    const int one_pass = out_first ? 0 : skinny_splits(s, dr.thr != 0, (int)sizeof(T), most);
     const int n_splits = one_pass > 0 ? one_pass : pick_dq_splits(s, most, (int)sizeof(T));
     if constexpr (sizeof(T) == 2) {
-        if ((e = launch_bwd_bf16_main(s, dr, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, one_pass > 0, st)) !=
-            hipSuccess)
+        if ((e = launch_bwd_bf16_main(s, dr, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, one_pass > 0, out_first,
+                                      st)) != hipSuccess)
             return e;
     } else {
         {

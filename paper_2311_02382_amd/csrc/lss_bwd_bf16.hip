@@ -1368,7 +1368,8 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_main_bf16_kernel(
     }
 }
 
-// Whether the workgroups compute D and the start values themselves: a launch less (2.3 us), for each dK/dV workgroup
+// Whether the workgroups compute D and the start values themselves (never where a gradient overlaps `out`, see
+// launch_bwd_d): a launch less (2.3 us), for each dK/dV workgroup
 // 0.75 us per 128 rows of 64 elements or 1.5 us per 64 of 128 ahead of its loop.  That is spread over the rounds of
 // workgroups the chip takes (512 or 256 at once); a launch of one round or less pays it in full only if a dK/dV
 // workgroup's walk over the queries, and not a dQ workgroup's over its keys, is what the launch waits for.
@@ -1412,11 +1413,11 @@ template <int D>
 static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                     const bf16_t *v, const bf16_t *out, const float *lse, const bf16_t *dO, bf16_t *dq,
                                     float *dk_part, float *dv_part, const Workspace &ws, int n_splits,
-                                    bool one_pass, hipStream_t st)
+                                    bool one_pass, bool out_first, hipStream_t st)
 {
     hipError_t e;
     const bool with_drop = drop.thr != 0;
-    const bool skinny = !with_drop && s.l_s <= kSkinnyRows, own = bwd_own_values<D>(s, n_splits);
+    const bool own = !out_first && bwd_own_values<D>(s, n_splits), skinny = own && !with_drop && s.l_s <= kSkinnyRows;
     if constexpr (D == 64) {
         if (one_pass)
             return s.l_s <= 64 ? launch_skinny<2>(s, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, st)
@@ -1449,10 +1450,11 @@ static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, con
 // launch; the caller runs the dQ split merge
 hipError_t launch_bwd_bf16_main(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                 const bf16_t *v, const bf16_t *out, const float *lse, const bf16_t *dO, bf16_t *dq,
-                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, bool one_pass, hipStream_t st)
+                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, bool one_pass, bool out_first,
+                                hipStream_t st)
 {
-    if (s.d == 64) return launch_bwd_bf16_d<64>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, one_pass, st);
-    return launch_bwd_bf16_d<128>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, one_pass, st);
+    if (s.d == 64) return launch_bwd_bf16_d<64>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, one_pass, out_first, st);
+    return launch_bwd_bf16_d<128>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, one_pass, out_first, st);
 }
 
 } // namespace lss

@@ -76,11 +76,20 @@ hipError_t launch_bwd_f32_main(const SegShape &s, const DropArgs &drop, const fl
                                const float *lse, const float *dO, float *dq, float *dk_part, float *dv_part, const Workspace &ws,
                                int n_splits, hipStream_t st);
 
-// tuned bf16 kernels (lss_bwd_bf16.hip): dQ kernel (also writes D = rowsum(dO * out)) then dK/dV kernel
+// tuned bf16 kernels (lss_bwd_bf16.hip): all gradients in one launch, after one for D = rowsum(dO * out) where that
+// is not part of it; `out_first`: `out` must have been read before any gradient is written
 int dq_bf16_rows_per_workgroup(int d);
 hipError_t launch_bwd_bf16_main(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                 const bf16_t *v, const bf16_t *out, const float *lse, const bf16_t *dO, bf16_t *dq,
-                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, bool one_pass, hipStream_t st);
+                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, bool one_pass, bool out_first,
+                                hipStream_t st);
+
+// Whether [a, a + a_bytes) and [b, b + b_bytes) have a byte in common
+inline bool overlaps(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+    return p < q + b_bytes && q < p + a_bytes;
+}
 
 // Optional per-kernel timing for benchmarks (lss_timing.h): when enabled, every launch site
 // brackets its kernel with a pair of HIP events on the launch stream.  One id per __global__

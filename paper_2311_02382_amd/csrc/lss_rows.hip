@@ -333,8 +333,8 @@ hipError_t launch_layernorm_bwd(const bf16_t *x, const float *gamma, const float
     if (rows > 0) {
         TimedLaunch tl(K_LN_BWD, st);
         const int all = LN_ROW_WGS + (E + LN_COLS - 1) / LN_COLS;
-        const auto overlaps = [&](const bf16_t *p) { return dx < p + rows * E && p < dx + rows * E; };
-        const int apart = overlaps(x) || overlaps(dy) ? LN_ROW_WGS : 0;     // the column kind alone first
+        const size_t bytes = (size_t)rows * E * sizeof(bf16_t);
+        const int apart = overlaps(dx, bytes, x, bytes) || overlaps(dx, bytes, dy, bytes) ? LN_ROW_WGS : 0;     // the column kind alone first
         for (int first = apart, end = all; end > 0; end = first, first = 0) {
             const dim3 grid((unsigned)(end - first), (unsigned)std::min(n_parts, 32768), (unsigned)((n_parts + 32767) / 32768));
 #define LSS_LN_BWD(NCH) hipLaunchKernelGGL(layernorm_bwd_kernel<NCH>, grid, dim3(256), 0, st, x, gamma, mean, rstd, dy, rows, E, dx, scratch, first)
