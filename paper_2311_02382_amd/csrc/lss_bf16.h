@@ -2,6 +2,7 @@
 // swizzled tiles, LDS transpose reads, packed conversions.
 #pragma once
 #include "lss_common.h"
+#include "lss_grid.h"
 
 namespace lss {
 
@@ -184,35 +185,6 @@ __device__ __forceinline__ int tr_lane_offset_sw(int lane, int db)
     return DirectTile<D, 64>::chunk_offset(row, chunk) + (s & 1) * 8;
 }
 
-// Workgroup order for grids of (batch*head, inner) work items.  Consecutive workgroup ids go to
-// consecutive XCDs (8 of them, each with its own L2 and an eighth of the compute units).
-//   * Whole rounds of eight heads: item `id` is head id % 8 + 8 * (id / 8 / n_inner), inner index
-//     (id / 8) % n_inner, so an XCD sees ONE head at a time (all inner items of head x, then of head
-//     x + 8, ...) and what the workgroups of a head share (K and V, or Q and dO) stays in its L2.
-//   * The r = bhs % 8 heads that are left are dealt out item by item, item i being head i % r, inner index
-//     i / r: all XCDs get their share, an XCD sees r / gcd(r, 8) heads at once.  One head per XCD
-//     here too would leave 8 - r of the eight with nothing to do: three heads of 1721 queries against
-//     12,712 keys in float took 250 us on three XCDs, whatever the split of the keys, and take 105 on eight.
-//   * All heads are dealt out when the work of the items differs (`uneven`: under the causal mask key tiles do, and
-//     query tiles where the segment is a good part of the keys) and they all fit the chip at once (512): the longest items of every head then start before the shortest of any, and each
-//     compute unit gets one of each (4 x 13 heads of 948 tokens: backward 50 us, dealt out 42).
-// Grid size xcd_grid(bhs, n_inner), a multiple of 8; ids past the last item: xcd_item returns false.
-constexpr int kXcds = 8;
-inline int xcd_grid(int bhs, int n_inner) { return kXcds * (int)(((int64_t)bhs * n_inner + kXcds - 1) / kXcds); }
-__device__ __forceinline__ bool xcd_item(int id, int bhs, int n_inner, bool uneven, int &bh, int &inner)
-{
-    const int left = uneven && bhs * n_inner <= 512 ? bhs : bhs % kXcds, whole = bhs - left, i = id - whole * n_inner;
-    if (i < 0) {
-        const int rest = id / kXcds;
-        inner = rest % n_inner;
-        bh = id % kXcds + kXcds * (rest / n_inner);
-        return true;
-    }
-    if (i >= left * n_inner) return false;
-    inner = i / left;
-    bh = whole + i % left;
-    return true;
-}
 // Address of tile `tile` of a tensor whose tiles lie `tile_bytes` apart (below 2^32: 64 rows of at most 2^23
 // elements): one 32 x 32 -> 64-bit scalar multiply and a 64-bit add, wavefront-uniform.
 template <typename T>

@@ -274,20 +274,6 @@ struct GemmStore {
     }
 };
 
-// Position of workgroup `id` of a grid of m_tiles x n_tiles tiles: consecutive ids go to consecutive XCDs
-// (each with its own L2), and every XCD gets a contiguous run of tiles, so that few row tiles still fill all
-// XCDs.  Tiles are numbered in blocks of four row tiles, column by column: the 32 workgroups an XCD runs at a
-// time then read few different operand strips (4 + 8 instead of 2 + 16 where a row has 16 column tiles).
-struct TileId { int m, n; bool ok; };
-__device__ __forceinline__ TileId xcd_tile(int id, int m_tiles, int n_tiles)
-{
-    const int tiles = m_tiles * n_tiles, per_xcd = (tiles + kXcds - 1) / kXcds;
-    const int t = id % kXcds * per_xcd + id / kXcds;
-    const int block = t / (4 * n_tiles), in = t % (4 * n_tiles), rows = min(4, m_tiles - 4 * block);
-    return {4 * block + in % rows, in / rows, id / kXcds < per_xcd && t < tiles};
-}
-__host__ __device__ __forceinline__ int xcd_tile_grid(int m_tiles, int n_tiles) { return kXcds * ((m_tiles * n_tiles + kXcds - 1) / kXcds); }
-
 template <typename S, bool A_ANY, bool W_TR, bool OUT_F32, int EPI>
 __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(ProjArgs args)
 {

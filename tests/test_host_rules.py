@@ -1,0 +1,18 @@
+"""Rules that host and device code share, driven by small host programs under the undefined-behaviour sanitizer (CPU)."""
+import subprocess
+from pathlib import Path
+
+ROOT = Path(__file__).resolve().parent.parent
+
+
+def _run(tmp_path, name, *flags):
+    exe = tmp_path / name
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-Wall", "-Wextra", "-Werror", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                    "-static-libasan", "-static-libubsan", *flags, f"-I{ROOT}/paper_2311_02382_amd/csrc", "-o", str(exe),
+                    str(ROOT / "tests" / "host" / f"{name}.cpp")], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "clean" in r.stdout, r.stdout[-2000:] + r.stderr[-2000:]
+
+
+def test_every_work_item_belongs_to_one_workgroup(tmp_path):
+    _run(tmp_path, "grid_check")
