@@ -14,7 +14,6 @@
 #include <type_traits>
 #include "lss_kernels.h"
 #include <algorithm>
-#include <mutex>
 
 namespace lss {
 
@@ -1397,12 +1396,8 @@ static hipError_t launch_skinny(const SegShape &s, const bf16_t *q, const bf16_t
 {
     using C = SkinnyCfg<64, QB>;
     const auto kernel = bwd_skinny_bf16_kernel<64, QB>;
-    static std::once_flag once;
-    static hipError_t attr = hipSuccess;
-    std::call_once(once, [&] {
-        attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, C::SMEM);
-    });
-    if (attr != hipSuccess) return attr;
+    static DeviceOnce once;
+    if (const hipError_t e = allow_lds(kernel, C::SMEM, once); e != hipSuccess) return e;
     TimedLaunch tl(K_BWD_MAIN_BF16, st);
     hipLaunchKernelGGL(kernel, dim3((unsigned)xcd_grid(s.B * s.H, n_splits)), dim3(256), C::SMEM, st, s, q, k, v, out, dO, lse, dq, ws.dq_part,
                        dk_part, dv_part, n_splits);

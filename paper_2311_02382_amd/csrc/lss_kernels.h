@@ -1,6 +1,7 @@
 // Host-side launchers of the segment-attention kernels; called by the C ABI only.
 #pragma once
 #include <hip/hip_runtime.h>
+#include "lss_device_once.h"
 #include <stddef.h>
 #include <stdint.h>
 
@@ -89,6 +90,16 @@ inline bool overlaps(const void *a, size_t a_bytes, const void *b, size_t b_byte
 {
     const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
     return p < q + b_bytes && q < p + a_bytes;
+}
+
+// Lets launches of `kernel` on the current GPU use `bytes` of dynamic LDS; one `once` per kernel
+template <typename K>
+hipError_t allow_lds(K kernel, int bytes, DeviceOnce &once)
+{
+    int dev = -1;
+    const hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    return once.run(dev, [&] { return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
 }
 
 // Optional per-kernel timing for benchmarks (lss_timing.h): when enabled, every launch site

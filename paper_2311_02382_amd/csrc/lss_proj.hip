@@ -26,7 +26,6 @@
 #include "lss_bf16.h"
 #include "lss_kernels.h"
 
-#include <mutex>
 #include <algorithm>
 #include <type_traits>
 #include <vector>
@@ -602,13 +601,6 @@ using ShapeM2 = GemmShape<128, 128, 64, 64, 2, 2>;      // ... two such groups s
 using ShapeS = GemmShape<64, 64, 32, 32, 4>;
 using ShapeS4 = GemmShape<64, 64, 32, 32, 2, 4>;
 
-template <typename K>
-hipError_t allow_lds(K kernel, int bytes, std::once_flag &once, hipError_t &attr)
-{
-    std::call_once(once, [&] { attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
-    return attr;
-}
-
 template <typename S, bool A_ANY, bool W_TR, bool OUT_F32, int EPI>
 hipError_t launch_proj_shape(ProjArgs &args, int kernel_id, hipStream_t st)
 {
@@ -624,10 +616,9 @@ hipError_t launch_proj_shape(ProjArgs &args, int kernel_id, hipStream_t st)
     args.zero_begin = wgs;
     wgs += xcd_tile_grid(args.job[0].batches * (args.job[0].m_tiles - args.job[0].m_data), args.job[0].n_tiles);
     if (wgs == 0) return hipSuccess;
-    static std::once_flag once;
-    static hipError_t attr = hipSuccess;
+    static DeviceOnce once;
     const auto kernel = proj_gemm_kernel<S, A_ANY, W_TR, OUT_F32, EPI>;
-    if (allow_lds(kernel, S::LDS, once, attr) != hipSuccess) return attr;
+    if (const hipError_t e = allow_lds(kernel, S::LDS, once); e != hipSuccess) return e;
     TimedLaunch tl(kernel_id, st);
     hipLaunchKernelGGL(kernel, dim3(wgs), dim3(S::NT), S::LDS, st, args);
     return hipGetLastError();
@@ -839,10 +830,9 @@ static hipError_t launch_wgrad_shape(WgradArgs &g, hipStream_t st)
 {
     g.m_tiles = (g.K + S::TM - 1) / S::TM;
     g.n_tiles = (g.N + S::TN - 1) / S::TN;
-    static std::once_flag once;
-    static hipError_t attr = hipSuccess;
+    static DeviceOnce once;
     const auto kernel = wgrad_gemm_kernel<S, DC_F32>;
-    if (allow_lds(kernel, S::LDS, once, attr) != hipSuccess) return attr;
+    if (const hipError_t e = allow_lds(kernel, S::LDS, once); e != hipSuccess) return e;
     TimedLaunch tl(K_LINEAR_WGRAD, st);
     hipLaunchKernelGGL(kernel, dim3(xcd_tile_grid(g.batches * g.splits_per_batch, g.m_tiles * g.n_tiles)), dim3(S::NT), S::LDS, st, g);
     return hipGetLastError();

@@ -16,3 +16,14 @@ def _run(tmp_path, name, *flags):
 
 def test_every_work_item_belongs_to_one_workgroup(tmp_path):
     _run(tmp_path, "grid_check")
+
+
+def test_kernel_limits_are_set_on_every_gpu_of_the_process(tmp_path):
+    _run(tmp_path, "device_once_check", "-pthread")
+
+
+def test_no_launcher_keeps_a_limit_per_process():
+    # HIP keeps a kernel's limits per GPU: they are raised through DeviceOnce only
+    csrc = ROOT / "paper_2311_02382_amd" / "csrc"
+    sets = [p.name for p in csrc.iterdir() if "hipFuncSetAttribute" in p.read_text()]
+    assert sets == ["lss_kernels.h"]
