@@ -47,13 +47,14 @@ int pick_fwd_splits(int l_s, int B, int H, int rows_per_wg, int64_t kv_tiles, in
     // takes per 64-key tile: a launch takes about
     //   (key tiles per workgroup + start) x g(n) + merge if split,   n = workgroups per compute unit, rounded up,
     // `start` for a workgroup's start and results, `merge` for the merge launch (2 us) and for writing and reading the
-    // partial results (5 bytes per ps), g(1) = 1 and, where several workgroups share a compute unit, g(n) = 0.17 + 0.65 n
+    // partial results (fp32; 5 MB per us in the float kernels, 10 in the bf16 ones, whose partials mostly stay in the caches:
+    // lx8k with dropout takes 1481 us if they are charged at 5, and 1467), g(1) = 1 and, where several workgroups share a compute unit, g(n) = 0.17 + 0.65 n
     // (bf16: a second co-resident workgroup adds about a third of a workgroup's throughput) or 0.8 n (float),
     // g(n) = n where only one fits (bf16, d = 128).  What matters most is that the workgroup count lands just below a
     // multiple of the 256 compute units.  The smallest count within 3 % of the best estimate is taken.
-    struct Cost { double tile_us, start, g0, g1; };
-    const Cost c = elem_bytes == 4 ? Cost{d == 64 ? 3.9 : 5.8, 2.0, 0.0, 0.8} : d == 64 ? Cost{0.77, 8.0, 0.17, 0.65} : Cost{1.6, 6.0, 0.0, 1.0};
-    const double row_bytes = (double)B * H * l_s * d * elem_bytes;
+    struct Cost { double tile_us, start, g0, g1, mb_per_us; };
+    const Cost c = elem_bytes == 4 ? Cost{d == 64 ? 3.9 : 5.8, 2.0, 0.0, 0.8, 5.0} : d == 64 ? Cost{0.77, 8.0, 0.17, 0.65, 10.0} : Cost{1.6, 6.0, 0.0, 1.0, 10.0};
+    const double out_mb = (double)B * H * l_s * d * 1e-6;     // elements
     const int64_t wgs = (int64_t)((l_s + rows_per_wg - 1) / rows_per_wg) * B * H;
     if (wgs <= 0 || max_splits <= 1) return 1;
     double best = 0.0;
@@ -62,7 +63,7 @@ int pick_fwd_splits(int l_s, int B, int H, int rows_per_wg, int64_t kv_tiles, in
         if (sp > 1 && kv_tiles / sp < 4) break;      // shorter splits cost more than they gain
         const int64_t per_cu = (wgs * sp + 255) / 256;
         const double g = per_cu <= 1 ? 1.0 : c.g0 + c.g1 * (double)per_cu;
-        const double t = ((double)((kv_tiles + sp - 1) / sp) + c.start) * g + (sp > 1 ? (2.0 + row_bytes * (2 * sp + 1) / 5e6) / c.tile_us : 0.0);
+        const double t = ((double)((kv_tiles + sp - 1) / sp) + c.start) * g + (sp > 1 ? (2.0 + out_mb * (8 * sp + elem_bytes) / c.mb_per_us) / c.tile_us : 0.0);
         if (sp == 1 || t < 0.97 * best) { best = t; best_s = sp; }
     }
     return best_s;
@@ -85,7 +86,7 @@ static WsLayout ws_layout(int l_s, int l_x, int B, int H, int d, int elem_bytes)
     w.dq_part = off;  off += align256(sp_q > 1 ? sp_q * rows * d * sizeof(float) : 0);
     w.row_key = off;  off += align256(rows * sizeof(uint32_t));
     w.bwd_total = off;
-    w.o_part = off;   off += align256(sp_f > 1 ? sp_f * rows * d * (size_t)elem_bytes : 0);     // in the storage type
+    w.o_part = off;   off += align256(sp_f > 1 ? sp_f * rows * d * sizeof(float) : 0);
     w.lse_part = off; off += align256(sp_f > 1 ? sp_f * rows * sizeof(float) : 0);
     w.total = off;
     return w;

@@ -43,7 +43,7 @@ int skinny_splits(const SegShape &s, bool with_drop, int elem_bytes, int most);
 
 struct Workspace {
     // forward
-    float *o_part;    // [splits, B*H, l_s, d] in the storage type (bf16 kernels write bf16 here)
+    float *o_part;    // [splits, B*H, l_s, d]
     float *lse_part;  // [splits, B*H, l_s]
     // backward
     float *D;         // [B*H, l_s]      rowsum(dO * out)   (bf16 kernels: its negative)

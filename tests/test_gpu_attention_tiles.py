@@ -1,10 +1,11 @@
 """Attention launches on either side of the choices the launchers make by size (two wavefronts per key block or one,
 how many key splits, which XCD gets which head), at ragged row and key counts, against the oracle."""
+import numpy as np
 import pytest
 import torch
 
 import oracle
-from paper_2311_02382_amd import lss
+from paper_2311_02382_amd import lss, timing
 from _util import rel_err, stage_all, to_np
 from test_gpu_parity import run_segment
 
@@ -47,3 +48,23 @@ def test_float_results_are_those_of_single_precision(d):
         assert rel_err(to_np(got), want) <= 1e-5, name
     again = lss.lss_segment_attn_bwd(q, K.dev, V.dev, s0, out, lse, do, True)
     assert all(torch.equal(a, b) for a, b in zip((dq, dk, dv), again))
+
+
+@pytest.mark.parametrize("B,l_x,H,d,s0,l_s,causal", [(1, 1024, 4, 64, 256, 256, True), (1, 1024, 4, 64, 768, 256, True), (1, 2000, 4, 64, 1900, 58, True),
+                                                     (1, 1500, 8, 128, 100, 130, False)])
+def test_split_forward_rounds_its_output_once(B, l_x, H, d, s0, l_s, causal):
+    # Launches of few query tiles split the keys and merge.  Rounding a Gaussian value to bf16 costs 1.65e-3 of its size
+    # (root mean square).  A row's weights are rounded as matrix operands, its result at the end: 1.65e-3 * sqrt(2) = 2.33e-3.
+    # Partial results that were rounded to bf16 on their way to the merge would make it sqrt(3), 2.86e-3; the line lies at sqrt(2.4).
+    Q, K, V, _ = stage_all(B, l_x, H, d, 8950 + l_s, "bf16")
+    sl = slice(s0, s0 + l_s)
+    merge = {n: i for i, n in timing.kernel_names().items()}["fwd_merge_kernel"]
+    timing.reset()
+    timing.enable(True)
+    try:
+        out, _ = lss.lss_segment_attn_fwd(Q.dev[:, sl].contiguous(), K.dev, V.dev, s0, causal)
+        assert timing.read(merge)[1] == 1
+    finally:
+        timing.enable(False)
+    ref, _ = oracle.segment_fwd(Q.f64[:, sl], K.f64, V.f64, s0, causal)
+    assert np.linalg.norm(to_np(out) - ref) <= 2.55e-3 * np.linalg.norm(ref)
