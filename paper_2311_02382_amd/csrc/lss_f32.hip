@@ -6,9 +6,10 @@
 // floats is then nine products of parts, |x_i y_j| <= 2^-8(i+j) |x y|, each exact in the matrix core's fp32
 // accumulation.  The six with i + j <= 2 are added, smallest first; the three left out are together below 2^-23
 // of |x y|, the size of the rounding an fp32 multiply-add makes at every step, while a matrix instruction here
-// adds 16 products per rounding instead of two.  Relative errors against fp64 (2000 keys, N(0, 1) inputs; in
-// brackets those of V_MFMA_F32_32X32X2_F32, which these kernels used before): out 4.3e-7 (5.9e-7), dq 6.5e-7
-// (6.3e-7), dk 5.5e-7 (7.0e-7), dv 5.3e-7 (6.7e-7); at three times the standard deviation out 1.0e-6 (1.5e-6).
+// adds 16 products per rounding instead of two (with eight of the nine the errors below stay as they are).
+// Relative errors against fp64 (512 rows, 2000 keys, N(0, 1) inputs; in brackets those of V_MFMA_F32_32X32X2_F32,
+// which these kernels used before): out 4.4e-7 (5.8e-7), dq 4.9e-7 (6.4e-7), dk 5.4e-7 (7.0e-7), dv 5.4e-7 (6.8e-7);
+// at three times the standard deviation out 1.0e-6 (1.5e-6), dq 2.9e-6 (3.5e-6).
 // What it buys: six V_MFMA_F32_32X32X16_BF16 (192 cycles) do what eight 32x32x2 fp32 ones (512 cycles) did.
 // lx8k in single precision, eight segments: forward 1605 -> 910 us, backward 5460 -> 2750 us.  Each further
 // segment of lx8k costs 64 us backward (1.4 PFLOP/s of executed bf16 products, what the chip sustains on
@@ -376,11 +377,18 @@ __device__ __forceinline__ void bwd_dq_f32_body(char *smem, const SegShape &s, c
                 }
                 dp[e] = p * (dpe - Dr);
             }
+            // The block's 32 keys are added up before they meet the accumulator, which is rounded at its full size once
+            // per block and not twelve times: dq's error 6.6e-7 -> 4.9e-7, the launch's time the same.
+            const Frag3 df0 = split_acc(dp, 0), df1 = split_acc(dp, 1);
 #pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const Frag3 df = split_acc(dp, half);
+            for (int db = 0; db < D / 32; ++db) {
+                const Frag3 k0 = Tile::cols_frag(sk, kb2 * 32, t_off[db]), k1 = Tile::cols_frag(sk, kb2 * 32 + 16, t_off[db]);
+                f32x16 sum;
+                clear(sum);
+                sum = mma_small(k1, df1, mma_small(k0, df0, sum));
+                sum = mma(k1.p[0], df1.p[0], mma(k0.p[0], df0.p[0], sum));
 #pragma unroll
-                for (int db = 0; db < D / 32; ++db) acc[db] = mma6(Tile::cols_frag(sk, kb2 * 32 + half * 16, t_off[db]), df, acc[db]);
+                for (int e = 0; e < 16; ++e) acc[db][e] += sum[e];
             }
         }
     }

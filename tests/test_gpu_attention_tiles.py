@@ -68,3 +68,21 @@ def test_split_forward_rounds_its_output_once(B, l_x, H, d, s0, l_s, causal):
         timing.enable(False)
     ref, _ = oracle.segment_fwd(Q.f64[:, sl], K.f64, V.f64, s0, causal)
     assert np.linalg.norm(to_np(out) - ref) <= 2.55e-3 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("d,causal", [(64, True), (64, False), (128, True)])
+def test_float_errors_are_no_larger_than_stated(d, causal):
+    # Figures of lss_f32.hip (2-norm of the difference over 2-norm of the result) and a fifth more, for other inputs and orders
+    # of the sums.  What they tell apart: products of two parts per float are off by 2^-17 and more, 4e-6; gradients of
+    # the queries added up product by product 6.6e-7.
+    B, l_x, H, s0, l_s = 1, 2000, 2, 1488 if causal else 700, 512
+    Q, K, V, DO = stage_all(B, l_x, H, d, 8970 + d, "f32")
+    sl = slice(s0, s0 + l_s)
+    q, do = Q.dev[:, sl].contiguous(), DO.dev[:, sl].contiguous()
+    out, lse = lss.lss_segment_attn_fwd(q, K.dev, V.dev, s0, causal)
+    grads = lss.lss_segment_attn_bwd(q, K.dev, V.dev, s0, out, lse, do, causal)
+    ro, _ = oracle.segment_fwd(Q.f64[:, sl], K.f64, V.f64, s0, causal)
+    ref = oracle.segment_bwd(Q.f64[:, sl], K.f64, V.f64, DO.f64[:, sl], s0, causal)
+    for name, got, want, most in zip(("out", "dq", "dk", "dv"), (out, *grads), (ro, *ref), (5.7e-7, 6.2e-7, 7.3e-7, 7.4e-7)):
+        err = np.linalg.norm(to_np(got) - want) / np.linalg.norm(want)
+        assert err <= most, (name, err)
