@@ -144,7 +144,12 @@ int lss_segment_attn_bwd_noalloc(const void *q_seg, const void *k, const void *v
 
 /*
  * Single-precision twins (the paper's runs are single precision, Section 5.2):
- * q_seg, k, v, out, dO, dq are float; products run on fp32 matrix cores.
+ * q_seg, k, v, out, dO, dq are float, and so is the arithmetic: results are at least as
+ * accurate as those of fp32 multiply-adds (relative errors against fp64 of 2e-7 to 7e-7
+ * on N(0, 1) inputs).  Products of normal size run on the bf16 matrix cores, six for each
+ * of three-part operands; where a value is infinite, NaN, above 3.39e38 or below 2^-103
+ * and not 0, the rows or keys it meets are done on the fp32 matrix cores, three to four
+ * times slower.
  */
 int lss_segment_attn_fwd_f32(const void *q_seg, const void *k, const void *v,
                              int64_t seg_offset, int64_t l_s, int64_t l_x,
@@ -171,8 +176,7 @@ int lss_segment_attn_bwd_f32(const void *q_seg, const void *k, const void *v,
  *   seed        any 64-bit value
  *   elem_bytes  2: q_seg, k, v, out, dO, dq are bf16;  4: float
  * All other arguments as in lss_segment_attn_fwd / lss_segment_attn_bwd.
- * With p_drop > 0 the bf16 calls run dropout variants of the tuned kernels; the
- * float case uses the library's general kernels.
+ * With p_drop > 0 the calls run dropout variants of the same kernels.
  */
 int lss_segment_attn_fwd_dropout(const void *q_seg, const void *k, const void *v,
                                  int64_t seg_offset, int64_t l_s, int64_t l_x,

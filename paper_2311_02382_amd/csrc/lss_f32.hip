@@ -2,7 +2,10 @@
 // on the bf16 matrix cores, every float split into three bf16 parts.
 //
 // A float x is the exact sum of three bf16 numbers: x0 = bf16(x), x1 = bf16(x - x0), x2 = x - x0 - x1 (rounded to
-// nearest, each part takes 8 of the 24 significand bits; both differences are exact).  A product of two
+// nearest, each part takes 8 of the 24 significand bits; both differences are exact; the method of Henry, Tang
+// and Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", ARITH 2019).
+// That holds for 0 and for 2^-103 <= |x| < 3.39e38; what lies outside is found and done on the fp32 matrix cores
+// (product_f32).  Weights and score gradients below 2^-103 are carried to 2^-134.  A product of two
 // floats is then nine products of parts, |x_i y_j| <= 2^-8(i+j) |x y|, each exact in the matrix core's fp32
 // accumulation.  The six with i + j <= 2 are added, smallest first; the three left out are together below 2^-23
 // of |x y|, the size of the rounding an fp32 multiply-add makes at every step, while a matrix instruction here
@@ -59,11 +62,53 @@ __device__ __forceinline__ Frag3 split8(const float (&x)[8])
     for (int p = 0; p < 3; ++p) f.p[p].v = __builtin_bit_cast(bf16x8, part[p]);
     return f;
 }
-__device__ __forceinline__ Frag3 split_global(const float *p)      // 8 consecutive floats
+// Below 2^-103 the third part is subnormal and loses bits (bf16 has the exponents of float).  Inputs that small, other than
+// 0, are looked for in two steps: the least magnitude costs half an instruction per float, and only where it is
+// small (zeros make it so as well) is every value looked at.
+constexpr float kTiny = 0x1p-103f;
+template <int N>
+__device__ __forceinline__ float least_magnitude(const f32x4 (&x)[N], float least)
 {
-    const f32x4 lo = *reinterpret_cast<const f32x4 *>(p), hi = *reinterpret_cast<const f32x4 *>(p + 4);
-    const float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    return split8(x);
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; e += 2) asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(least) : "v"(x[i][e]), "v"(x[i][e + 1]));
+    return least;
+}
+// The bits of a float without the sign, doubled: ordered like |x|.  Less one, zeros come last.
+__device__ __forceinline__ uint32_t twice_magnitude(float x) { return __builtin_bit_cast(uint32_t, x) << 1; }
+template <int N>
+__device__ __forceinline__ bool some_below(const f32x4 (&x)[N], float limit)
+{
+    uint32_t least_nonzero = ~0u;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) least_nonzero = min(least_nonzero, twice_magnitude(x[i][e]) - 1u);
+    return least_nonzero < twice_magnitude(limit) - 1u;
+}
+// This lane's fragments of a row: D / 16 times 8 floats, 16 apart.  Returns whether some lane's row holds tiny values.
+template <int D>
+__device__ __forceinline__ bool split_row(const float *p, Frag3 (&f)[D / 16])
+{
+    float least = INFINITY;
+#pragma unroll
+    for (int kb = 0; kb < D / 16; ++kb) {
+        const f32x4 v[2] = {*reinterpret_cast<const f32x4 *>(p + kb * 16), *reinterpret_cast<const f32x4 *>(p + kb * 16 + 4)};
+        least = least_magnitude(v, least);
+        const float x[8] = {v[0][0], v[0][1], v[0][2], v[0][3], v[1][0], v[1][1], v[1][2], v[1][3]};
+        f[kb] = split8(x);
+    }
+    bool tiny = false;
+    if (__any(least < kTiny)) {
+#pragma unroll 1
+        for (int kb = 0; kb < D / 16; ++kb) {
+            const f32x4 v[2] = {*reinterpret_cast<const f32x4 *>(p + kb * 16), *reinterpret_cast<const f32x4 *>(p + kb * 16 + 4)};
+            tiny = tiny || some_below(v, kTiny);
+        }
+        tiny = __any(tiny);
+    }
+    return tiny;
 }
 __device__ __forceinline__ Frag3 split_acc(const f32x16 &c, int half)      // slots 8 half .. of a C tile
 {
@@ -94,6 +139,12 @@ struct PlaneTile {
     static_assert(ROWS * CPR % NT == 0, "");
     static __device__ __forceinline__ int chunk_offset(int r, int c) { return r * (D * 2) + ((c ^ tile_swizzle<D>(r)) * 16); }
     struct Regs { f32x4 v[2 * CHUNKS]; };
+    // `word` (in LDS) becomes 1 where a thread's part of two tiles holds tiny values; everybody may read it after the tiles' barrier
+    static __device__ __forceinline__ void note_tiny(const Regs &a, const Regs &b, uint32_t *word)
+    {
+        if (__any(least_magnitude(b.v, least_magnitude(a.v, INFINITY)) < kTiny))
+            if (some_below(a.v, kTiny) || some_below(b.v, kTiny)) *word = 1u;
+    }
     // rows >= rows_ok re-read row rows_ok - 1 (the kernels mask or discard what they produce)
     static __device__ __forceinline__ void fetch(Regs &g, const float *base, int64_t ld, int rows_ok, int tid)
     {
@@ -164,6 +215,66 @@ __device__ __forceinline__ void clear(f32x16 &a)
     for (int e = 0; e < 16; ++e) a[e] = 0.f;
 }
 
+// ---- The products on the fp32 matrix cores, operands straight from memory, for what three bf16 parts miss: `tiny` inputs,
+// and infinities, NaNs and values whose first part overflows (3.39e38), which all leave NaN in the results (an infinite x has
+// x - x0 = NaN).  A wavefront with such results, or with results so small that parts of the weights
+// were subnormal, does its rows or keys over again this way, without LDS or barriers (1024 rows against 8192 keys, 16 heads:
+// forward 231 us, over again 735; backward 595 and 2226).  Finding out costs 1.5 % of lx8k and 3 us of a launch of few tiles.
+
+// C tile of 32 rows of a matrix (this lane's: a) against 32 others (b) over the whole width
+template <int D>
+__device__ __forceinline__ f32x16 product_f32(const float *a, const float *b)
+{
+    f32x16 c;
+    clear(c);
+#pragma unroll 1
+    for (int kb = 0; kb < D / 16; ++kb)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[kb * 16 + e], b[kb * 16 + e], c, 0, 0, 0);
+    return c;
+}
+// acc += transpose of 32 rows (from `rows` on, rows_ok of which exist) x the C tile w of weights
+template <int D>
+__device__ __forceinline__ void add_product_f32(const float *rows, int64_t ld, int rows_ok, const f32x16 &w, f32x16 (&acc)[D / 32], int lq,
+                                                int hh)
+{
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const int row = 8 * (e >> 2) + 4 * hh + (e & 3);
+        const float *const p = rows + (int64_t)min(row, rows_ok - 1) * ld + lq;
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db) {
+            const uint32_t x = __builtin_bit_cast(uint32_t, p[db * 32]) & (row < rows_ok ? ~0u : 0u);       // 0 past the end
+            acc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, x), w[e], acc[db], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);      // (a row at a time: its registers must not add to the main loop's)
+    }
+}
+// Whether some result is not finite, or below 2^-100 and not 0 (again looked at closely only where the least magnitude is small)
+template <int N>
+__device__ __forceinline__ bool missed(const f32x16 (&acc)[N])
+{
+    float least = INFINITY, zero = 0.f;
+    bool small = false;
+#pragma unroll
+    for (int db = 0; db < N; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+            asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(least) : "v"(acc[db][e]), "v"(acc[db][e + 1]));
+            zero = __builtin_fmaf(acc[db][e], 0.f, zero);               // NaN from infinities and NaNs on
+            zero = __builtin_fmaf(acc[db][e + 1], 0.f, zero);
+        }
+    if (__any(least < 0x1p-100f)) {
+        uint32_t least_nonzero = ~0u;
+#pragma unroll
+        for (int db = 0; db < N; ++db)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) least_nonzero = min(least_nonzero, twice_magnitude(acc[db][e]) - 1u);
+        small = least_nonzero < twice_magnitude(0x1p-100f) - 1u;
+    }
+    return small || zero != zero;
+}
+
 // ------------------------------------------------------------------------------------------ forward
 template <int D, bool DROP>
 __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_f32_kernel(SegShape s, DropArgs dr, const float *__restrict__ q,
@@ -174,8 +285,9 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_f32_kernel(SegShape 
 {
     using Tile = PlaneTile<D>;
     constexpr int NU = D / 16, BC = Tile::ROWS;
-    __shared__ __attribute__((aligned(1024))) char smem[2 * Tile::BYTES];
+    __shared__ __attribute__((aligned(1024))) char smem[2 * Tile::BYTES + 16];
     char *const sk = smem, *const sv = smem + Tile::BYTES;
+    uint32_t *const tiny_word = reinterpret_cast<uint32_t *>(smem + 2 * Tile::BYTES);
 
     const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -196,11 +308,9 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_f32_kernel(SegShape 
     const int r = rw0 + lq;
     const bool row_ok = r < s.l_s;
     Frag3 qf[NU];
-    {
-        const float *qp = q + ((int64_t)b * s.l_s + min(r, s.l_s - 1)) * ld + (int64_t)h * D + hh * 8;
-#pragma unroll
-        for (int kb = 0; kb < NU; ++kb) qf[kb] = split_global(qp + kb * 16);
-    }
+    const float *const qp = q + ((int64_t)b * s.l_s + min(r, s.l_s - 1)) * ld + (int64_t)h * D + hh * 8;
+    const bool tiny = split_row<D>(qp, qf);
+    if (tid == 0) *tiny_word = 0u;
     f32x16 o[D / 32];
 #pragma unroll
     for (int db = 0; db < D / 32; ++db) clear(o[db]);
@@ -216,6 +326,58 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_f32_kernel(SegShape 
 #pragma unroll
     for (int db = 0; db < D / 32; ++db) t_off[db] = tr_lane_offset_sw<D>(lane, db);
 
+    // keys [jb, jb + 32): in half kb2 of the tile in LDS, or (EXACT) in memory
+    auto block = [&](auto exact, int jb, int kb2) __attribute__((always_inline)) {
+        constexpr bool EXACT = decltype(exact)::value;
+        // a block no row of this wavefront sees
+        if (jb >= s.l_x || (s.causal && jb > (int)s.s0 + rw0 + 31)) return;
+        f32x16 sc;
+        if constexpr (EXACT) sc = product_f32<D>(kbase + (int64_t)min(jb + lq, s.l_x - 1) * ld + hh * 8, qp);
+        else sc = Tile::product(sk, kb2 * 32, a_off, qf);
+        // element e of this lane is key jb + 8 (e / 4) + 4 hh + e % 4
+        if ((s.causal && jb + 31 > (int)s.s0 + rw0) || jb + 32 > s.l_x) {
+            const int last = s.causal ? min((int)s.s0 + r, s.l_x - 1) : s.l_x - 1, rel = last - jb - 4 * hh;
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if (8 * (e >> 2) + (e & 3) > rel) sc[e] = -INFINITY;
+        }
+        float mx = sc[0];
+#pragma unroll
+        for (int e = 1; e < 16; ++e) mx = fmaxf(mx, sc[e]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m, mx * c);
+        if (__any(m_new > m)) {             // some row's maximum rises: rescale what was accumulated
+            const float alpha = m == -INFINITY ? 0.f : fast_exp2(m - m_new);
+            l *= alpha;
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
+            m = m_new;
+        }
+        const float m_use = m == -INFINITY ? 0.f : m;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const float p = fast_exp2(sc[e] * c - m_use);
+            l += p;             // the row sum (hence lse and the normalisation) is that of the softmax
+            if (DROP) {
+                const int key = jb + 8 * (e >> 2) + 4 * hh + (e & 3);
+                sc[e] = drop_keep(drop_rk, drop_col_key(drop_cs, (uint32_t)key), dr.thr) ? p * dr.scale : 0.f;
+            } else {
+                sc[e] = p;
+            }
+        }
+        if constexpr (EXACT) {
+            add_product_f32<D>(vbase + (int64_t)jb * ld, ld, s.l_x - jb, sc, o, lq, hh);
+        } else {
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const Frag3 pf = split_acc(sc, half);
+#pragma unroll
+                for (int db = 0; db < D / 32; ++db) o[db] = mma6(Tile::cols_frag(sv, kb2 * 32 + half * 16, t_off[db]), pf, o[db]);
+            }
+        }
+    };
     for (int t = t_begin; t < t_end; ++t) {
         {
             typename Tile::Regs gk, gv;
@@ -224,55 +386,19 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_f32_kernel(SegShape 
             __syncthreads();                    // the tile before has been read
             Tile::store(sk, gk, tid);
             Tile::store(sv, gv, tid);
+            Tile::note_tiny(gk, gv, tiny_word);
         }
         __syncthreads();
         if (rw0 >= s.l_s) continue;             // none of this wavefront's rows exists
 #pragma unroll
-        for (int kb2 = 0; kb2 < BC / 32; ++kb2) {
-            const int jb = t * BC + kb2 * 32;
-            // a block no row of this wavefront sees
-            if (jb >= s.l_x || (s.causal && jb > (int)s.s0 + rw0 + 31)) continue;
-            f32x16 sc = Tile::product(sk, kb2 * 32, a_off, qf);
-            // element e of this lane is key jb + 8 (e / 4) + 4 hh + e % 4
-            if ((s.causal && jb + 31 > (int)s.s0 + rw0) || jb + 32 > s.l_x) {
-                const int last = s.causal ? min((int)s.s0 + r, s.l_x - 1) : s.l_x - 1, rel = last - jb - 4 * hh;
+        for (int kb2 = 0; kb2 < BC / 32; ++kb2) block(std::false_type{}, t * BC + kb2 * 32, kb2);
+    }
+    if (rw0 < s.l_s && t_begin < t_end && (tiny || __builtin_amdgcn_readfirstlane((int)*tiny_word) != 0 || __any(missed(o)))) {
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    if (8 * (e >> 2) + (e & 3) > rel) sc[e] = -INFINITY;
-            }
-            float mx = sc[0];
-#pragma unroll
-            for (int e = 1; e < 16; ++e) mx = fmaxf(mx, sc[e]);
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float m_new = fmaxf(m, mx * c);
-            if (__any(m_new > m)) {             // some row's maximum rises: rescale what was accumulated
-                const float alpha = m == -INFINITY ? 0.f : fast_exp2(m - m_new);
-                l *= alpha;
-#pragma unroll
-                for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
-                m = m_new;
-            }
-            const float m_use = m == -INFINITY ? 0.f : m;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const float p = fast_exp2(sc[e] * c - m_use);
-                l += p;             // the row sum (hence lse and the normalisation) is that of the softmax
-                if (DROP) {
-                    const int key = jb + 8 * (e >> 2) + 4 * hh + (e & 3);
-                    sc[e] = drop_keep(drop_rk, drop_col_key(drop_cs, (uint32_t)key), dr.thr) ? p * dr.scale : 0.f;
-                } else {
-                    sc[e] = p;
-                }
-            }
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const Frag3 pf = split_acc(sc, half);
-#pragma unroll
-                for (int db = 0; db < D / 32; ++db) o[db] = mma6(Tile::cols_frag(sv, kb2 * 32 + half * 16, t_off[db]), pf, o[db]);
-            }
-        }
+        for (int db = 0; db < D / 32; ++db) clear(o[db]);
+        m = -INFINITY;
+        l = 0.f;
+        for (int jb = t_begin * BC; jb < t_end * BC; jb += 32) block(std::true_type{}, jb, 0);
     }
 
     const float l_tot = l + __shfl_xor(l, 32);
@@ -305,6 +431,7 @@ __device__ __forceinline__ void bwd_dq_f32_body(char *smem, const SegShape &s, c
     using Tile = PlaneTile<D>;
     constexpr int NU = D / 16, BC = Tile::ROWS;
     char *const sk = smem, *const sv = smem + Tile::BYTES;
+    uint32_t *const tiny_word = reinterpret_cast<uint32_t *>(smem + 2 * Tile::BYTES);
     const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = bh / s.H, h = bh % s.H;
@@ -319,11 +446,13 @@ __device__ __forceinline__ void bwd_dq_f32_body(char *smem, const SegShape &s, c
     const int r = rw0 + lq, rc = min(r, s.l_s - 1);
     const bool row_ok = r < s.l_s;
     Frag3 qf[NU], gf[NU];
+    bool tiny;
     {
         const int64_t off = ((int64_t)b * s.l_s + rc) * ld + (int64_t)h * D + hh * 8;
-#pragma unroll
-        for (int kb = 0; kb < NU; ++kb) { qf[kb] = split_global(q + off + kb * 16); gf[kb] = split_global(dO + off + kb * 16); }
+        tiny = split_row<D>(q + off, qf);
+        tiny = split_row<D>(dO + off, gf) || tiny;
     }
+    if (tid == 0) *tiny_word = 0u;
     if constexpr (D == 128) {       // (operands live in the accumulation half of the register file: see the bf16 dK/dV workgroups)
 #pragma unroll
         for (int kb = 0; kb < NU; ++kb)
@@ -346,37 +475,41 @@ __device__ __forceinline__ void bwd_dq_f32_body(char *smem, const SegShape &s, c
 #pragma unroll
     for (int db = 0; db < D / 32; ++db) t_off[db] = tr_lane_offset_sw<D>(lane, db);
 
-    for (int t = t_begin; t < t_end; ++t) {
-        const int j0 = t * BC;
-        typename Tile::Regs gk, gv;
-        Tile::fetch(gk, kbase + (int64_t)j0 * ld, ld, s.l_x - j0, tid);
-        Tile::fetch(gv, vbase + (int64_t)j0 * ld, ld, s.l_x - j0, tid);
-        __syncthreads();
-        Tile::store(sk, gk, tid);
-        Tile::store(sv, gv, tid);
-        __syncthreads();
-        if (rw0 >= s.l_s) continue;
+    // keys [jb, jb + 32): in half kb2 of the tile in LDS, or (EXACT) in memory
+    auto block = [&](auto exact, int jb, int kb2) __attribute__((always_inline)) {
+        constexpr bool EXACT = decltype(exact)::value;
+        if (jb >= s.l_x || (s.causal && jb > (int)s.s0 + rw0 + 31)) return;
+        f32x16 sc, dp;
+        if constexpr (EXACT) {
+            int row = r;
+            asm volatile("" : "+v"(row));      // (so that its address is made here, not kept through the main loop)
+            const int64_t key_at = (int64_t)min(jb + lq, s.l_x - 1) * ld + hh * 8;
+            const int64_t row_at = ((int64_t)b * s.l_s + min(row, s.l_s - 1)) * ld + (int64_t)h * D + hh * 8;
+            sc = product_f32<D>(kbase + key_at, q + row_at);
+            dp = product_f32<D>(vbase + key_at, dO + row_at);
+        } else {
+            sc = Tile::product(sk, kb2 * 32, a_off, qf);
+            dp = Tile::product(sv, kb2 * 32, a_off, gf);
+        }
+        if ((s.causal && jb + 31 > (int)s.s0 + rw0) || jb + 32 > s.l_x) {
+            const int last = s.causal ? min((int)s.s0 + r, s.l_x - 1) : s.l_x - 1, rel = last - jb - 4 * hh;
 #pragma unroll
-        for (int kb2 = 0; kb2 < BC / 32; ++kb2) {
-            const int jb = j0 + kb2 * 32;
-            if (jb >= s.l_x || (s.causal && jb > (int)s.s0 + rw0 + 31)) continue;
-            f32x16 sc = Tile::product(sk, kb2 * 32, a_off, qf), dp = Tile::product(sv, kb2 * 32, a_off, gf);
-            if ((s.causal && jb + 31 > (int)s.s0 + rw0) || jb + 32 > s.l_x) {
-                const int last = s.causal ? min((int)s.s0 + r, s.l_x - 1) : s.l_x - 1, rel = last - jb - 4 * hh;
+            for (int e = 0; e < 16; ++e)
+                if (8 * (e >> 2) + (e & 3) > rel) sc[e] = -INFINITY;
+        }
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    if (8 * (e >> 2) + (e & 3) > rel) sc[e] = -INFINITY;
+        for (int e = 0; e < 16; ++e) {
+            const float p = fast_exp2(sc[e] * c - L2);
+            float dpe = dp[e];
+            if (DROP) {
+                const int key = jb + 8 * (e >> 2) + 4 * hh + (e & 3);
+                dpe = drop_keep(drop_rk, drop_col_key(drop_cs, (uint32_t)key), dr.thr) ? dpe * dr.scale : 0.f;
             }
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const float p = fast_exp2(sc[e] * c - L2);
-                float dpe = dp[e];
-                if (DROP) {
-                    const int key = jb + 8 * (e >> 2) + 4 * hh + (e & 3);
-                    dpe = drop_keep(drop_rk, drop_col_key(drop_cs, (uint32_t)key), dr.thr) ? dpe * dr.scale : 0.f;
-                }
-                dp[e] = p * (dpe - Dr);
-            }
+            dp[e] = p * (dpe - Dr);
+        }
+        if constexpr (EXACT) {
+            add_product_f32<D>(kbase + (int64_t)jb * ld, ld, s.l_x - jb, dp, acc, lq, hh);
+        } else {
             // The block's 32 keys are added up before they meet the accumulator, which is rounded at its full size once
             // per block and not twelve times: dq's error 6.6e-7 -> 4.9e-7, the launch's time the same.
             const Frag3 df0 = split_acc(dp, 0), df1 = split_acc(dp, 1);
@@ -391,6 +524,25 @@ __device__ __forceinline__ void bwd_dq_f32_body(char *smem, const SegShape &s, c
                 for (int e = 0; e < 16; ++e) acc[db][e] += sum[e];
             }
         }
+    };
+    for (int t = t_begin; t < t_end; ++t) {
+        const int j0 = t * BC;
+        typename Tile::Regs gk, gv;
+        Tile::fetch(gk, kbase + (int64_t)j0 * ld, ld, s.l_x - j0, tid);
+        Tile::fetch(gv, vbase + (int64_t)j0 * ld, ld, s.l_x - j0, tid);
+        __syncthreads();
+        Tile::store(sk, gk, tid);
+        Tile::store(sv, gv, tid);
+        Tile::note_tiny(gk, gv, tiny_word);
+        __syncthreads();
+        if (rw0 >= s.l_s) continue;
+#pragma unroll
+        for (int kb2 = 0; kb2 < BC / 32; ++kb2) block(std::false_type{}, j0 + kb2 * 32, kb2);
+    }
+    if (rw0 < s.l_s && t_begin < t_end && (tiny || __builtin_amdgcn_readfirstlane((int)*tiny_word) != 0 || __any(missed(acc)))) {
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db) clear(acc[db]);
+        for (int jb = t_begin * BC; jb < t_end * BC; jb += 32) block(std::true_type{}, jb, 0);
     }
     if (!row_ok) return;
     const float scale = 1.f / sqrtf((float)D);
@@ -416,7 +568,7 @@ __device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, 
     constexpr int NU = D / 16, BQ = Tile::ROWS;
     char *const sq = smem, *const sg = smem + Tile::BYTES;
     float *const sl = reinterpret_cast<float *>(smem + 2 * Tile::BYTES), *const sd = sl + 64;
-    uint32_t *const sr = reinterpret_cast<uint32_t *>(sd + 64);
+    uint32_t *const sr = reinterpret_cast<uint32_t *>(sd + 64), *const tiny_word = sr + 64;
     const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = bh / s.H, h = bh % s.H;
@@ -444,11 +596,13 @@ __device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, 
 
     // this lane's key; keys past the sequence re-read its last row and are never stored
     Frag3 kf[NU], vf[NU];
+    bool tiny;
     {
         const int64_t off = kv_base + (int64_t)min(j, s.l_x - 1) * ld + hh * 8;
-#pragma unroll
-        for (int kb = 0; kb < NU; ++kb) { kf[kb] = split_global(k + off + kb * 16); vf[kb] = split_global(v + off + kb * 16); }
+        tiny = split_row<D>(k + off, kf);
+        tiny = split_row<D>(v + off, vf) || tiny;
     }
+    if (tid == 0) *tiny_word = 0u;
     if constexpr (D == 128) {
 #pragma unroll
         for (int kb = 0; kb < NU; ++kb)
@@ -467,48 +621,60 @@ __device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, 
 #pragma unroll
     for (int db = 0; db < D / 32; ++db) t_off[db] = tr_lane_offset_sw<D>(lane, db);
 
-    for (int rq0 = rq_begin; rq0 < s.l_s; rq0 += BQ) {
-        typename Tile::Regs gq, gg;
-        Tile::fetch(gq, qbase + (int64_t)rq0 * ld, ld, s.l_s - rq0, tid);
-        Tile::fetch(gg, gbase + (int64_t)rq0 * ld, ld, s.l_s - rq0, tid);
-        __syncthreads();
-        Tile::store(sq, gq, tid);
-        Tile::store(sg, gg, tid);
-        if (tid < BQ) {     // rows past the segment: lse = +inf makes P (hence dS) exactly 0
-            const int rr = rq0 + tid;
-            sl[tid] = rr < s.l_s ? lse[(int64_t)bh * s.l_s + rr] * kLog2e : INFINITY;
-            sd[tid] = rr < s.l_s ? Dv[(int64_t)bh * s.l_s + rr] : 0.f;
-            if (DROP) sr[tid] = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + rr));
+    // rows [rb, rb + 32) of the segment: block qb of the tile in LDS, or (EXACT) in memory
+    auto block = [&](auto exact, int rb, int qb) __attribute__((always_inline)) {
+        constexpr bool EXACT = decltype(exact)::value;
+        // a block none of whose rows sees a key of this wavefront, or past the segment
+        if (rb >= s.l_s || (s.causal && (int)s.s0 + rb + 31 < jw0)) return;
+        f32x16 sc, dp;
+        if constexpr (EXACT) {
+            int key = j;
+            asm volatile("" : "+v"(key));      // (so that its address is made here, not kept through the main loop)
+            const int64_t row_at = (int64_t)min(rb + lq, s.l_s - 1) * ld + hh * 8, key_at = kv_base + (int64_t)min(key, s.l_x - 1) * ld + hh * 8;
+            sc = product_f32<D>(qbase + row_at, k + key_at);
+            dp = product_f32<D>(gbase + row_at, v + key_at);
+        } else {
+            sc = Tile::product(sq, qb * 32, a_off, kf);
+            dp = Tile::product(sg, qb * 32, a_off, vf);
         }
-        __syncthreads();
+        const bool diag = s.causal && jw0 + 31 > (int)s.s0 + rb;
+        // element e of this lane is row rb + 8 (e / 4) + 4 hh + e % 4
 #pragma unroll
-        for (int qi = 0; qi < BQ / 32 / HALVES; ++qi) {
-            const int qb = HALVES == 1 ? qi : my_half;
-            const int rb = rq0 + 32 * qb;
-            // a block none of whose rows sees a key of this wavefront, or past the segment
-            if (rb >= s.l_s || (s.causal && (int)s.s0 + rb + 31 < jw0)) continue;
-            f32x16 sc = Tile::product(sq, qb * 32, a_off, kf), dp = Tile::product(sg, qb * 32, a_off, vf);
-            const bool diag = s.causal && jw0 + 31 > (int)s.s0 + rb;
-            // element e of this lane is row rb + 8 (e / 4) + 4 hh + e % 4
-#pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) {
-                const int rl = qb * 32 + 8 * e4 + 4 * hh;
-                const f32x4 l4 = *reinterpret_cast<const f32x4 *>(sl + rl), d4 = *reinterpret_cast<const f32x4 *>(sd + rl);
+        for (int e4 = 0; e4 < 4; ++e4) {
+            const int rl = qb * 32 + 8 * e4 + 4 * hh, r4 = rb + 8 * e4 + 4 * hh;        // in the tile; in the segment
+            f32x4 l4, d4;
+            if constexpr (EXACT) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int e = 4 * e4 + i;
-                    float p = fast_exp2(sc[e] * c - l4[i]);
-                    if (diag && j > (int)s.s0 + rq0 + rl + i) p = 0.f;
-                    float pv = p, dpe = dp[e];
-                    if (DROP) {
-                        const float mk = drop_keep(sr[rl + i], drop_ck, dr.thr) ? dr.scale : 0.f;
-                        pv = p * mk;
-                        dpe *= mk;
-                    }
-                    sc[e] = pv;
-                    dp[e] = p * (dpe - d4[i]);
+                    const int64_t at = (int64_t)bh * s.l_s + min(r4 + i, s.l_s - 1);
+                    l4[i] = r4 + i < s.l_s ? lse[at] * kLog2e : INFINITY;
+                    d4[i] = Dv[at];
                 }
+            } else {
+                l4 = *reinterpret_cast<const f32x4 *>(sl + rl);
+                d4 = *reinterpret_cast<const f32x4 *>(sd + rl);
             }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int e = 4 * e4 + i;
+                float p = fast_exp2(sc[e] * c - l4[i]);
+                if (diag && j > (int)s.s0 + r4 + i) p = 0.f;
+                float pv = p, dpe = dp[e];
+                if (DROP) {
+                    const uint32_t rk = EXACT ? drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + r4 + i)) : sr[rl + i];
+                    const float mk = drop_keep(rk, drop_ck, dr.thr) ? dr.scale : 0.f;
+                    pv = p * mk;
+                    dpe *= mk;
+                }
+                sc[e] = pv;
+                dp[e] = p * (dpe - d4[i]);
+            }
+            if constexpr (EXACT) __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (EXACT) {
+            add_product_f32<D>(gbase + (int64_t)rb * ld, ld, s.l_s - rb, sc, dv, lq, hh);
+            add_product_f32<D>(qbase + (int64_t)rb * ld, ld, s.l_s - rb, dp, dk, lq, hh);
+        } else {
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 const Frag3 pf = split_acc(sc, half), df = split_acc(dp, half);
@@ -519,7 +685,29 @@ __device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, 
                 }
             }
         }
+    };
+    for (int rq0 = rq_begin; rq0 < s.l_s; rq0 += BQ) {
+        typename Tile::Regs gq, gg;
+        Tile::fetch(gq, qbase + (int64_t)rq0 * ld, ld, s.l_s - rq0, tid);
+        Tile::fetch(gg, gbase + (int64_t)rq0 * ld, ld, s.l_s - rq0, tid);
+        __syncthreads();
+        Tile::store(sq, gq, tid);
+        Tile::store(sg, gg, tid);
+        Tile::note_tiny(gq, gg, tiny_word);
+        if (tid < BQ) {     // rows past the segment: lse = +inf makes P (hence dS) exactly 0
+            const int rr = rq0 + tid;
+            sl[tid] = rr < s.l_s ? lse[(int64_t)bh * s.l_s + rr] * kLog2e : INFINITY;
+            sd[tid] = rr < s.l_s ? Dv[(int64_t)bh * s.l_s + rr] : 0.f;
+            if (DROP) sr[tid] = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + rr));
+        }
+        __syncthreads();
+#pragma unroll
+        for (int qi = 0; qi < BQ / 32 / HALVES; ++qi) {
+            const int qb = HALVES == 1 ? qi : my_half;
+            block(std::false_type{}, rq0 + 32 * qb, qb);
+        }
     }
+    tiny = tiny || (rq_begin < s.l_s && __builtin_amdgcn_readfirstlane((int)*tiny_word) != 0);
     if constexpr (HALVES == 2) {        // second half's results -> first half's wavefront, through the planes' LDS
         static_assert(2 * 2 * (D / 32) * 4096 <= 2 * Tile::BYTES, "");
         __syncthreads();
@@ -543,6 +731,11 @@ __device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, 
                 for (int i = 0; i < 4; ++i) { dk[db][4 * e4 + i] += a[i]; dv[db][4 * e4 + i] += g[i]; }
             }
     }
+    if (jw0 < s.l_x && (tiny || __any(missed(dk) || missed(dv)))) {
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db) { clear(dk[db]); clear(dv[db]); }
+        for (int rb = rq_begin; rb < s.l_s; rb += 32) block(std::true_type{}, rb, 0);
+    }
     if (j >= s.l_x) return;
     const float scale = 1.f / sqrtf((float)D);
     const int64_t off = kv_base + (int64_t)j * ld;
@@ -565,7 +758,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_main_f32_kernel(
     float *__restrict__ dq_part, float *__restrict__ dk_part, float *__restrict__ dv_part, int n_splits, int n_dq, int n_q_tiles,
     int n_key_tiles)
 {
-    __shared__ __attribute__((aligned(1024))) char smem[2 * PlaneTile<D>::BYTES + 3 * 64 * 4];
+    __shared__ __attribute__((aligned(1024))) char smem[2 * PlaneTile<D>::BYTES + 3 * 64 * 4 + 16];
     const int bhs = s.B * s.H, id = blockIdx.x;
     int bh, inner;
     if (id >= n_dq) {
