@@ -160,8 +160,8 @@ PyObject *pack(std::initializer_list<PyObject *> items)
     return r;
 }
 
-// ---- scratch of the attention calls: one buffer per GPU, passed with every call (and registered with the
-// library, for its own callers, when it is new).  Outgrown buffers are kept alive, because kernels in flight may still use them and nothing here
+// ---- scratch of the attention calls: one buffer per GPU, passed with every call and registered with the
+// library by every call (direct calls of the C entry points without a buffer of their own find it there).  Outgrown buffers are kept alive, because kernels in flight may still use them and nothing here
 // synchronises; a buffer at least doubles when it grows, so together they stay below the current one.
 // (All of this runs under the interpreter lock.)
 std::map<int, at::Tensor> g_ws;
@@ -174,8 +174,8 @@ void *shared_workspace(size_t need, const at::Tensor &like, size_t &bytes)
         int64_t grown = 1 << 20;
         if (cur.defined()) { grown = 2 * cur.numel(); g_ws_retired.push_back(cur); }
         cur = fresh({(int64_t)need > grown ? (int64_t)need : grown}, at::kByte, like);
-        check(lss_set_workspace(ptr(cur), (size_t)cur.numel()));
     }
+    check(lss_set_workspace(ptr(cur), (size_t)cur.numel()));
     bytes = (size_t)cur.numel();
     return ptr(cur);
 }
