@@ -47,7 +47,10 @@ def _compile(src: str) -> Path:
     return obj
 
 
-BINDING = PKG / "_lss_torch.so"
+def binding_path() -> Path:
+    """The native half of the binding; the name carries the Python ABI, so another Python does not load it."""
+    import sysconfig
+    return PKG / f"_lss_torch{sysconfig.get_config_var('EXT_SUFFIX')}"
 
 
 def _compile_binding() -> Path:
@@ -60,7 +63,7 @@ def _compile_binding() -> Path:
     include = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], "/opt/rocm/include", str(INCLUDE)]
     # the torch and HIP headers are written for either vendor: these two macros name this one
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DLSS_TORCH_VERSION="{torch.__version__}"',
            *(x for d in include for x in ("-isystem", d)), "-c", str(CSRC / "lss_torch.cpp"), "-o", str(obj)]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
@@ -70,14 +73,16 @@ def _compile_binding() -> Path:
 
 def _link_binding(obj: Path) -> None:
     import torch
-    tmp = BINDING.with_suffix(f".so.tmp{os.getpid()}")
+    out = binding_path()
+    tmp = out.with_suffix(f".so.tmp{os.getpid()}")
     libs = Path(torch.__file__).parent / "lib"
     cmd = ["g++", "-shared", "-o", str(tmp), str(obj), f"-L{PKG}", "-l:liblss_attn.so", f"-L{libs}", "-lc10", "-lc10_hip", "-ltorch_cpu",
            "-ltorch_python", "-Wl,-rpath,$ORIGIN"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link of the binding failed:\n{r.stderr}")
-    os.replace(tmp, BINDING)
+    os.replace(tmp, out)
+    (PKG / "_lss_torch.so").unlink(missing_ok=True)       # a former name
 
 
 def build_library(verbose: bool = True) -> Path:

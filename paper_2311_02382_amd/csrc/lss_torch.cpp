@@ -522,4 +522,13 @@ PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_lss_torch", nullptr, -1, g_meth
 
 } // namespace
 
-PyMODINIT_FUNC PyInit__lss_torch() { return PyModule_Create(&g_module); }
+PyMODINIT_FUNC PyInit__lss_torch()
+{
+    PyObject *m = PyModule_Create(&g_module);
+    // tensors cross this interface as C++ objects: lss.py refuses any torch but the one whose headers were used
+    if (m && PyModule_AddStringConstant(m, "torch_version", LSS_TORCH_VERSION) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -4,7 +4,7 @@ Argument marshalling only -- every step of the path runs in the HIP kernels.  to
 supplies device memory and the stream; nothing here computes.  The functions below
 declare the public signatures; checking the tensors, allocating outputs that were not
 passed and calling the library is done in native code (csrc/lss_torch.cpp, built into
-_lss_torch.so): in Python that took 13 us per call, more than the kernels of a short
+_lss_torch): in Python that took 13 us per call, more than the kernels of a short
 segment.  If the library has not been built, the first call raises (there is no
 fallback path).
 """
@@ -120,7 +120,14 @@ def _bind():
     global _native
     if _native is None:
         load()
-        from . import _lss_torch
+        try:
+            from . import _lss_torch
+        except ImportError as e:
+            raise RuntimeError(f"the native half of the binding cannot be loaded ({e}): build it with `python -m "
+                               "paper_2311_02382_amd.build` (there is no fallback implementation)") from e
+        if _lss_torch.torch_version != str(torch.__version__):
+            raise RuntimeError(f"the native half of the binding was built for torch {_lss_torch.torch_version} and this is torch "
+                               f"{torch.__version__}: build it again with `python -m paper_2311_02382_amd.build`")
         _lss_torch.set_error_type(LssError)
         _native = _lss_torch
     return _native

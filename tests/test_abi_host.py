@@ -260,6 +260,23 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
         lss.lss_version()
 
 
+def test_binding_refuses_another_torch_and_another_python(lib, monkeypatch):
+    # its native half takes tensors as C++ objects: only the torch it was built for, and a file name for this Python alone
+    import importlib.machinery
+    from paper_2311_02382_amd import _lss_torch
+    assert _lss_torch.__file__.endswith(importlib.machinery.EXTENSION_SUFFIXES[0]) and "cpython" in importlib.machinery.EXTENSION_SUFFIXES[0]
+    monkeypatch.setattr(lss, "_native", None)
+    assert lss._bind() is _lss_torch
+    monkeypatch.setattr(lss, "_native", None)
+    monkeypatch.setattr(lss.torch, "__version__", "1.0.0")
+    with pytest.raises(RuntimeError, match="built for torch .* and this is torch 1.0.0"):
+        lss.lss_gelu_fwd(None)
+    monkeypatch.setitem(__import__("sys").modules, "paper_2311_02382_amd._lss_torch", None)
+    monkeypatch.delattr("paper_2311_02382_amd._lss_torch")
+    with pytest.raises(RuntimeError, match="no fallback"):
+        lss.lss_gelu_fwd(None)
+
+
 def test_product_package_does_not_touch_the_oracle():
     # the oracle is test infrastructure: nothing under the package imports it
     pkg = ROOT / "paper_2311_02382_amd"
