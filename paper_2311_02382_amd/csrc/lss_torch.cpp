@@ -93,12 +93,18 @@ at::Tensor fresh(at::IntArrayRef shape, at::ScalarType dt, const at::Tensor &lik
 {
     return at::empty(shape, at::TensorOptions().dtype(dt).device(like.device()));
 }
+std::string written(at::IntArrayRef shape)      // as Python writes a tuple
+{
+    std::string s = "(";
+    for (size_t i = 0; i < shape.size(); ++i) s += (i ? ", " : "") + std::to_string(shape[i]);
+    return s + (shape.size() == 1 ? ",)" : ")");
+}
 // the caller's output if given (checked), else a new tensor
 at::Tensor output(PyObject *o, at::IntArrayRef shape, at::ScalarType dt, const at::Tensor &like)
 {
     if (none(o)) return fresh(shape, dt, like);
     const at::Tensor &t = tensor(o);
-    require(t.sizes() == shape, "output has another shape than expected");
+    if (t.sizes() != shape) throw ValueError("output has shape " + written(t.sizes()) + ", expected " + written(shape));
     dev(t, dt, "output");
     return t;
 }
