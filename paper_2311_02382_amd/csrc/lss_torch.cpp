@@ -7,7 +7,7 @@
 // object per pointer), more than the kernels it launched; here it is below 1 us beside the launches.
 //
 // Errors: a tensor that does not fit raises ValueError; a status code of the library raises the exception type
-// handed in through set_error_type() as type(code, message).
+// handed in through set_error_type() as type(code, message); torch's own errors keep their types (OutOfMemoryError).
 #include "lss_attn.h"
 
 #include <Python.h>
@@ -16,6 +16,7 @@
 #include <ATen/ops/empty_like.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Dtype.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <initializer_list>
@@ -507,15 +508,16 @@ PyObject *call(PyObject *, PyObject *const *args, Py_ssize_t n)
         PyErr_Format(PyExc_TypeError, "expected %d arguments, got %zd", N, n);
         return nullptr;
     }
+    HANDLE_TH_ERRORS
     try {
         return F(args);
     } catch (const PythonError &) {
+        return nullptr;
     } catch (const ValueError &e) {
         PyErr_SetString(PyExc_ValueError, e.what());
-    } catch (const std::exception &e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+        return nullptr;
     }
-    return nullptr;
+    END_HANDLE_TH_ERRORS
 }
 #define LSS_FN(name, n) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(&call<name, n>)), METH_FASTCALL, nullptr}
 PyMethodDef g_methods[] = {

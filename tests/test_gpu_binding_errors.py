@@ -18,6 +18,13 @@ def test_a_wrong_output_names_both_shapes(given, message):
         lss.lss_gelu_fwd(_t(2, 8, 64), g=_t(*given))
 
 
+def test_out_of_memory_keeps_its_type():
+    # the outputs of 10^11 rows (25 TB) are asked for before the library sees the call
+    with pytest.raises(torch.OutOfMemoryError):
+        lss.lss_project_qkv(_t(1, 8, 128), _t(128, 128), _t(128, 256), 0, 10 ** 11, 2)
+    torch.cuda.synchronize()
+
+
 def test_other_errors():
     with pytest.raises(ValueError, match="u must be a contiguous torch.bfloat16 device tensor"):
         lss.lss_gelu_fwd(_t(2, 64, dtype=torch.float32))
