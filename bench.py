@@ -48,17 +48,18 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 matrix peak (published)
-PEAK_F32_TFLOPS = 157.3        # ... and the fp32 matrix peak, for --dtype f32
+PEAK_F32_TFLOPS = 157.3        # ... and the fp32 matrix peak, for --dtype f32 (whose kernels run six bf16 products per float product)
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E peak (published)
 
 # Matrix products each kernel contributes to the strict count (per pair: 2*d flops each).
 # fwd: S and PV.  The backward's main kernel holds two kinds of workgroup: dQ (dP and dQ; it also
 # recomputes S) and dK/dV (dV and dK; it also recomputes S and dP).  Together the six products of
-# the 12*d count.  Names are those of the __global__ functions, as a profiler prints them (*_f32_kernel: --dtype f32).
-ALGO_PRODUCTS = {"fwd_bf16_kernel": 2, "bwd_main_bf16_kernel": 4, "fwd_f32_kernel": 2, "bwd_main_f32_kernel": 4}
-EXEC_PRODUCTS = {"fwd_bf16_kernel": 2, "bwd_main_bf16_kernel": 7, "fwd_f32_kernel": 2, "bwd_main_f32_kernel": 7}
+# the 12*d count.  For short segments one kind of workgroup makes all three gradients (bwd_skinny_bf16_kernel), with S and
+# dP computed twice.  Names are those of the __global__ functions, as a profiler prints them (*_f32_kernel: --dtype f32).
+ALGO_PRODUCTS = {"fwd_bf16_kernel": 2, "bwd_main_bf16_kernel": 4, "bwd_skinny_bf16_kernel": 4, "fwd_f32_kernel": 2, "bwd_main_f32_kernel": 4}
+EXEC_PRODUCTS = {"fwd_bf16_kernel": 2, "bwd_main_bf16_kernel": 7, "bwd_skinny_bf16_kernel": 7, "fwd_f32_kernel": 2, "bwd_main_f32_kernel": 7}
 FWD_KERNELS = ("fwd_bf16_kernel", "fwd_f32_kernel", "fwd_merge_kernel")
-BWD_KERNELS = ("bwd_prep_bf16_kernel", "bwd_rowdot_kernel", "bwd_main_bf16_kernel", "bwd_main_f32_kernel",
+BWD_KERNELS = ("bwd_prep_bf16_kernel", "bwd_rowdot_kernel", "bwd_main_bf16_kernel", "bwd_skinny_bf16_kernel", "bwd_main_f32_kernel",
                "bwd_dq_merge_kernel")
 
 
@@ -481,7 +482,7 @@ def attention(args, w, steps, warmup, with_cpu_baseline, min_warm_ms=0.0, min_ti
             if dom in ("fwd_f32_kernel", "fwd_bf16_kernel"):
                 return bh * (eb * w.d * (2 * l_s + 2 * kv) + 4 * l_s)
             return bh * (eb * w.d * (4 * l_s + 2 * kv) + 8 * l_s + 8 * w.d * kv)    # backward: also the fp32 partials
-        if dom in ("fwd_f32_kernel", "fwd_bf16_kernel", "bwd_main_bf16_kernel", "bwd_main_f32_kernel"):
+        if dom in ALGO_PRODUCTS:
             byts = sum(alg_bytes(rv) for rv in rows_valid) / len(rows_valid)
             roofline["algorithmic_bytes_per_launch"] = byts
             roofline["flop_per_byte"] = round(per_launch / byts, 1)

@@ -1398,7 +1398,7 @@ static hipError_t launch_skinny(const SegShape &s, const bf16_t *q, const bf16_t
     const auto kernel = bwd_skinny_bf16_kernel<64, QB>;
     static DeviceOnce once;
     if (const hipError_t e = allow_lds(kernel, C::SMEM, once); e != hipSuccess) return e;
-    TimedLaunch tl(K_BWD_MAIN_BF16, st);
+    TimedLaunch tl(K_BWD_SKINNY_BF16, st);
     hipLaunchKernelGGL(kernel, dim3((unsigned)xcd_grid(s.B * s.H, n_splits)), dim3(256), C::SMEM, st, s, q, k, v, out, dO, lse, dq, ws.dq_part,
                        dk_part, dv_part, n_splits);
     return hipGetLastError();

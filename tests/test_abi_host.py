@@ -250,6 +250,22 @@ def test_dropout_argument_checks(lib):
                0x8000, 0x9000, None) == -6
 
 
+def test_every_kernel_is_timed_under_its_own_name(lib):
+    # names as a profiler prints them: each __global__ function of the library has an id, each id names such a function, and
+    # the benchmark knows every attention kernel
+    import sys
+    sys.path.insert(0, str(ROOT))
+    import bench
+    from paper_2311_02382_amd import timing
+    source = "".join(p.read_text() for p in (ROOT / "paper_2311_02382_amd" / "csrc").glob("*.hip") if "microbench" not in p.name)
+    kernels = set(re.findall(r"__global__[^;{]*?\bvoid (\w+)\(", source)) | set(re.findall(r"\) void (\w+_kernel)\(", source))
+    named = {n.split(":")[0] for n in timing.kernel_names().values()}
+    assert kernels and named == kernels, named ^ kernels
+    attention = {k for k in kernels if k.startswith(("fwd_", "bwd_"))}
+    assert attention == set(bench.FWD_KERNELS) | set(bench.BWD_KERNELS)
+    assert set(bench.ALGO_PRODUCTS) == set(bench.EXEC_PRODUCTS) == attention - {"fwd_merge_kernel", "bwd_dq_merge_kernel", "bwd_prep_bf16_kernel", "bwd_rowdot_kernel"}
+
+
 def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     # no library, no result: the binding has no other path to fall back on
     monkeypatch.setattr(lss, "_lib", None)
