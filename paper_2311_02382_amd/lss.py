@@ -160,9 +160,9 @@ def lss_set_workspace(buf) -> None:
 
 def lss_segment_attn_fwd(q_seg, k, v, seg_offset, causal=True, out=None, lse=None, stream=None,
                          p_drop=None, seed=0, workspace=None):
-    """Forward of one segment; dispatches on dtype (bf16 -> lss_segment_attn_fwd, f32 -> _f32), calls
-    lss_segment_attn_fwd_dropout when p_drop is given, and lss_segment_attn_fwd_ex when `workspace` (a
-    device tensor of lss_workspace_bytes() bytes used by this call alone) is given.
+    """Forward of one segment, bf16 or float32 by the tensors' dtype, through lss_segment_attn_fwd_ex: with dropout when
+    p_drop is given, and with scratch of its own when `workspace` (a device tensor of lss_workspace_bytes() bytes
+    used by this call alone) is given; otherwise with the binding's buffer of that GPU.
 
     Returns (out [B,l_s,H,d] in the input dtype, lse [B,H,l_s] float32).
     """
@@ -174,7 +174,8 @@ def lss_segment_attn_bwd(q_seg, k, v, seg_offset, out, lse, d_out, causal=True,
                          skip_masked_tail=False, workspace=None):
     """Backward of one segment.  Returns (dq, dk_partial, dv_partial); partials are float32 [B,l_x,H,d].
 
-    skip_masked_tail (LSS_FLAG_SKIP_MASKED_TAIL) or `workspace` select lss_segment_attn_bwd_ex."""
+    Through lss_segment_attn_bwd_ex; skip_masked_tail is LSS_FLAG_SKIP_MASKED_TAIL, p_drop, seed and `workspace` as in
+    lss_segment_attn_fwd."""
     return (_native or _bind()).attn_bwd(q_seg, k, v, seg_offset, out, lse, d_out, causal, dq, dk_partial, dv_partial, stream, p_drop, seed,
                                skip_masked_tail, workspace)
 
@@ -205,7 +206,7 @@ def lss_project_bwd(dq, dk_partial, dv_partial, w_q, w_kv, rows_valid=None, dx_q
                     skip_masked_tail=False):
     """dx_q = dQ_i W_q^T [B,l_s,E] and dx_partial = dK_part W_k^T + dV_part W_v^T [B,l_x,E], both float32.
 
-    skip_masked_tail selects lss_project_bwd_ex with LSS_FLAG_SKIP_MASKED_TAIL."""
+    Through lss_project_bwd_ex; skip_masked_tail is LSS_FLAG_SKIP_MASKED_TAIL."""
     return (_native or _bind()).project_bwd(dq, dk_partial, dv_partial, w_q, w_kv, rows_valid, dx_q, dx_partial, stream, skip_masked_tail)
 
 
