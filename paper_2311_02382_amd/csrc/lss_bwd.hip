@@ -105,8 +105,11 @@ static hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const T *q
     const size_t rows_bytes = (size_t)s.B * s.l_s * s.H * D * sizeof(T), part_bytes = (size_t)s.B * s.l_x * s.H * D * sizeof(float);
     const bool out_first = overlaps(dq, rows_bytes, out, rows_bytes) || overlaps(dk_part, part_bytes, out, rows_bytes) ||
                            overlaps(dv_part, part_bytes, out, rows_bytes);
-    const int one_pass = out_first ? 0 : skinny_splits(s, dr.thr != 0, (int)sizeof(T), most);
-    const int n_splits = one_pass > 0 ? one_pass : pick_dq_splits(s, most, (int)sizeof(T));
+    const int dq_splits = pick_dq_splits(s, most, (int)sizeof(T));
+    const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x;
+    const int dq_tiles = (int)(((seen + 63) / 64 + dq_splits - 1) / dq_splits);
+    const int one_pass = out_first ? 0 : skinny_splits(s, dr.thr != 0, (int)sizeof(T), most, dq_tiles);
+    const int n_splits = one_pass > 0 ? one_pass : dq_splits;
     if constexpr (sizeof(T) == 2) {
         if ((e = launch_bwd_bf16_main(s, dr, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, one_pass > 0, out_first,
                                       st)) != hipSuccess)

@@ -14,6 +14,7 @@
 #include <type_traits>
 #include "lss_kernels.h"
 #include <algorithm>
+#include <cmath>
 
 namespace lss {
 
@@ -1278,13 +1279,18 @@ __global__ __launch_bounds__(256, QB == 2 ? 2 : 1) void bwd_skinny_bf16_kernel(
     }
 }
 
-// Splits of the one-pass kernel, 0 where dQ and dK/dV workgroups of their own are the better ones.  Segments of 33..64
+// Splits of the one-pass kernel, 0 where dQ and dK/dV workgroups of their own are the better ones.  Segments of up to 64
 // rows run two workgroups per compute unit, longer ones (96 or 128 rows' accumulators) one, and a count that fills the
-// chip once is taken, with two tiles per workgroup at least -- three where they share compute units.  Times in us, from
-// launches of 65..15000 (batch*head, tile) pairs: a lone workgroup takes 3.3, 4.6 or 5.6 per 128-key tile (64, 96, 128 rows) and
-// 9 to 16 besides; the two kinds together take what follows from the tiles of all heads, or from the zeros they fill
-// beside them (here that comes last).  32 heads of 58 rows against 25,056 keys: 171 -> 104 us, of 100: 209 -> 157.
-int skinny_splits(const SegShape &s, bool with_drop, int elem_bytes, int most)
+// chip once is taken, with two tiles per workgroup at least -- three where they share compute units.  Times in us:
+//   here   a workgroup takes 3.3, 5.0 or 5.6 per 128-key tile (64, 96, 128 rows) and 9 to 12 besides, and the rows that no
+//          query sees are zero-filled at the end (6.2 MB per us);
+//   there  9, and the longer of a dQ workgroup's walk (`dq_tiles` of 64 keys) and the dK/dV tiles of all heads, with which
+//          the zeros (5 MB per us) overlap in part.
+// On 1080 launches (20..128 rows, 1000..50,000 keys, 4..128 heads, an eighth to all of the keys seen, zeros written or not) the
+// choice costs 0.9 % over the better one of the two on average; always one pass 17 %, never 11 %.  32 heads of 58 rows against 25,056 keys: 171 -> 104 us, of 100: 209 -> 157.
+// Without dropout and for d = 64 only: at d = 128 the slots alone take 96 KB and dQ's accumulators twice the registers, so that
+// one workgroup per compute unit is left even at 64 rows; that kernel has not been written.
+int skinny_splits(const SegShape &s, bool with_drop, int elem_bytes, int most, int dq_tiles)
 {
     if (elem_bytes != 2 || with_drop || s.d != 64 || s.l_s > 128) return 0;
     const int64_t bhs = (int64_t)s.B * s.H, seen = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
@@ -1296,8 +1302,8 @@ int skinny_splits(const SegShape &s, bool with_drop, int elem_bytes, int most)
     if (n < 1) return 0;
     const double walk = (double)((tiles + n - 1) / n), all = (double)(tiles * bhs);
     const double zeros = s.skip_tail ? 0.0 : (double)(s.l_x - seen) * bhs * s.d * 8.0 / 5.0e6;
-    const double here = two ? 9.0 + 3.3 * walk : (s.l_s <= 96 ? 10.0 + 4.6 * walk : 16.0 + 5.6 * walk) + zeros;
-    const double there = two ? 14.0 + 0.02 * all : 9.0 + std::max(0.03 * all, zeros);
+    const double here = (two ? 9.0 + 3.3 * walk : s.l_s <= 96 ? 10.0 + 5.0 * walk : 12.0 + 5.6 * walk) + 0.8 * zeros;
+    const double there = 9.0 + std::max(std::hypot((two ? 0.025 : 0.035) * all, zeros), 0.8 * dq_tiles);
     return here < there ? (int)n : 0;
 }
 

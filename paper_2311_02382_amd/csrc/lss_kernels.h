@@ -39,7 +39,8 @@ int fwd_rows_per_wg(int elem_bytes, int d);     // query rows per workgroup of t
 int dq_rows_per_wg(int elem_bytes, int d);      // ... and of the dQ kernel
 
 // Key splits of the backward kernel that makes all three gradients in one pass, 0 where another one is taken; at most `most`.
-int skinny_splits(const SegShape &s, bool with_drop, int elem_bytes, int most);
+// `dq_tiles`: key tiles of 64 that a dQ workgroup of that other one walks.
+int skinny_splits(const SegShape &s, bool with_drop, int elem_bytes, int most, int dq_tiles);
 
 struct Workspace {
     // forward
