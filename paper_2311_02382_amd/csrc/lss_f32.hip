@@ -786,11 +786,14 @@ template <int D>
 hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const float *q, const float *k, const float *v, const float *lse,
                         const float *dO, float *dq, float *dk_part, float *dv_part, const Workspace &ws, int n_splits, hipStream_t st)
 {
-    // two wavefronts per key block while the key tiles that do work fit the chip about once (two workgroups per
-    // compute unit): lx8k's first segment takes 90 us instead of 150, its fifth as long either way, later ones
-    // would lose 2 %
+    // Two wavefronts per key block where a dK/dV workgroup's walk over the queries is what the launch waits for: the key
+    // tiles fit the chip about once (two workgroups per compute unit) and a dQ workgroup does not walk much longer.  2048 rows,
+    // 8 heads, 2048 keys: 214 -> 148 us; but 600 rows, 4 heads, 8192 keys 109 -> 119 (dQ walks 16 tiles, the queries are 10), 64
+    // rows against 1664 key tiles 103 -> 121.  On 156 launches (64..2048 rows, 2..96 heads, 100..1700 key tiles) the
+    // rule costs 0.9 % over the better choice on average; never 2.3 %, always 3.4 %.
     const int64_t seen = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
-    const bool halves = D == 64 && (seen + 127) / 128 * s.B * s.H <= 640;
+    const int64_t dq_tiles = ((seen + 63) / 64 + n_splits - 1) / n_splits;
+    const bool halves = D == 64 && (seen + 127) / 128 * s.B * s.H <= 640 && 4 * ((s.l_s + 63) / 64) >= 3 * dq_tiles;
     const int keys = halves ? 64 : 128, n_q_tiles = (s.l_s + kRowsPerWg - 1) / kRowsPerWg, n_key_tiles = (s.l_x + keys - 1) / keys;
     const int n_dq = xcd_grid(s.B * s.H, n_q_tiles * n_splits), n_dkv = xcd_grid(s.B * s.H, n_key_tiles);
     constexpr int H2 = D == 64 ? 2 : 1;
