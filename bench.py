@@ -483,7 +483,7 @@ def attention(args, w, steps, warmup, with_cpu_baseline, min_warm_ms=0.0, min_ti
                 return bh * (eb * w.d * (2 * l_s + 2 * kv) + 4 * l_s)
             return bh * (eb * w.d * (4 * l_s + 2 * kv) + 8 * l_s + 8 * w.d * kv)    # backward: also the fp32 partials
         if dom in ALGO_PRODUCTS:
-            byts = sum(alg_bytes(rv) for rv in rows_valid) / len(rows_valid)
+            byts = sum(alg_bytes(rv) for rv in rows_valid) / timed[dom]["launches_per_step"]      # (a short segment at the start may take another kernel)
             roofline["algorithmic_bytes_per_launch"] = byts
             roofline["flop_per_byte"] = round(per_launch / byts, 1)
             if per_launch / byts < peak * 1e12 / (PEAK_HBM_GBS * 1e9):
