@@ -1,6 +1,6 @@
-// Tuned bf16 backward of Eq. 2 (Section 3, Principle 3) for gfx950: the two matrix kernels of
-// lss_bwd.hip (same mathematics, same operand roles) rebuilt as two kinds of workgroup that share
-// one launch (bwd_main_bf16_kernel):
+// Tuned bf16 backward of Eq. 2 (Section 3, Principle 3) for gfx950 (mathematics: lss_bwd.hip): dQ and dK/dV as two kinds of
+// workgroup that share one launch (bwd_main_bf16_kernel); short segments take one pass for all three gradients
+// (bwd_skinny_bf16_kernel).  In the former:
 //   * 32 x 32 blocks, three stages per block (score-side products, vector work, output-side
 //     products), software-pipelined so that the vector work of one block sits between the matrix
 //     instructions of its neighbours;
@@ -9,7 +9,7 @@
 //   * row-major LDS tiles read transposed with DS_READ_B64_TR_B16 where the contraction runs over
 //     tile rows (K^T for dQ, Q^T and dO^T for dK and dV) -- no transposing stores;
 //   * lse, D = rowsum(dO * out) and the masks folded into accumulator start values where the
-//     layout allows (a small kernel prepares -D and -lse * sqrt(d) per row).
+//     layout allows (-D and -lse * sqrt(d) per row come from a small kernel, or from the workgroup itself: bwd_own_values).
 #include "lss_bf16.h"
 #include <type_traits>
 #include "lss_kernels.h"
@@ -1342,7 +1342,7 @@ __global__ __launch_bounds__(256) void bwd_prep_bf16_kernel(SegShape s, DropArgs
 // out in XCD order (xcd_item): an XCD works on one head at a time, whose workgroups share that
 // head's K, V, Q and dO in its L2; within a head the longest workgroups come first (last query
 // tiles; first key tiles, the zero-fill ones last).
-// SKINNY: segments of at most 64 rows, whose dK/dV workgroups take kSkinnyTilesPerWg key tiles each
+// SKINNY: segments of at most 64 rows that do not take the one-pass kernel, whose dK/dV workgroups take kSkinnyTilesPerWg key tiles each
 // (n_key_tiles then counts those groups).
 // OWN: no preprocess kernel ran, every workgroup computes what it needs of D itself (bwd_own_values).
 template <int D, bool DROP, bool OWN, bool SKINNY = false>

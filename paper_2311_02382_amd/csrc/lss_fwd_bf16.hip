@@ -1,7 +1,6 @@
 // Tuned bf16 forward of Eq. 2 (Section 3, Principle 3) for gfx950.
 //
-// Same mathematics and operand roles as the generic kernel in lss_fwd.hip (S^T = K Q^T with one
-// query per lane, then O^T += V^T P^T with P^T fed straight from the S^T registers).  The keys are
+// S^T = K Q^T with one query per lane, then O^T += V^T P^T with P^T fed straight from the S^T registers.  The keys are
 // walked in blocks of 32 (two per 64-key K/V tile).  Per block g three stages:
 //     A(g): S^T product (matrix),  B(g): weights P^T (vector: exp, row sum, bf16 packing),
 //     C(g): O^T product (matrix).
