@@ -76,7 +76,9 @@ const char *lss_last_error(void);
 /*
  * Bytes of device scratch that one forward or backward call of this shape may use
  * (split-KV partial outputs, the row terms D = rowsum(dO * out), partial dQ).
- * Depends on the shape only, not on seg_offset or causal.  Returns 0 for an
+ * Depends on the shape only, not on seg_offset or causal.  A bf16 call also takes a
+ * buffer with room for half the bytes of split-KV partial outputs (two per element
+ * instead of four), and then splits the keys less far.  Returns 0 for an
  * empty or invalid shape.  `elem_bytes` is 2 (bf16 entry points) or 4 (f32).
  */
 size_t lss_workspace_bytes(int64_t l_s, int64_t l_x, int64_t B, int64_t H, int64_t d, int elem_bytes);

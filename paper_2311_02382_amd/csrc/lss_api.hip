@@ -73,10 +73,10 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // The backward's regions come first: a backward call needs only the first `bwd_total` bytes.
 struct WsLayout { size_t D, Ls, dq_part, row_key, bwd_total, o_part, lse_part, total; };
-static WsLayout ws_layout(int l_s, int l_x, int B, int H, int d, int elem_bytes)
+// `sp_f`: key splits of the forward whose partial results, `part_bytes` per element, there is room for
+static WsLayout ws_layout(int l_s, int l_x, int B, int H, int d, int elem_bytes, size_t sp_f, size_t part_bytes = sizeof(float))
 {
     // forward and dQ kernels may use different tile heights, hence different split counts
-    const size_t sp_f = (size_t)max_fwd_splits(l_s, l_x, B, H, fwd_rows_per_wg(elem_bytes, d));
     const size_t sp_q = (size_t)choose_splits(l_s, l_x, B, H, dq_rows_per_wg(elem_bytes, d));
     const size_t rows = (size_t)B * H * l_s;
     WsLayout w;
@@ -86,24 +86,31 @@ static WsLayout ws_layout(int l_s, int l_x, int B, int H, int d, int elem_bytes)
     w.dq_part = off;  off += align256(sp_q > 1 ? sp_q * rows * d * sizeof(float) : 0);
     w.row_key = off;  off += align256(rows * sizeof(uint32_t));
     w.bwd_total = off;
-    w.o_part = off;   off += align256(sp_f > 1 ? sp_f * rows * d * sizeof(float) : 0);
+    w.o_part = off;   off += align256(sp_f > 1 ? sp_f * rows * d * part_bytes : 0);
     w.lse_part = off; off += align256(sp_f > 1 ? sp_f * rows * sizeof(float) : 0);
     w.total = off;
     return w;
 }
 size_t workspace_bytes(int l_s, int l_x, int B, int H, int d, int elem_bytes)
 {
-    return ws_layout(l_s, l_x, B, H, d, elem_bytes).total;
+    return ws_layout(l_s, l_x, B, H, d, elem_bytes, (size_t)max_fwd_splits(l_s, l_x, B, H, fwd_rows_per_wg(elem_bytes, d))).total;
+}
+size_t least_workspace_bytes(int l_s, int l_x, int B, int H, int d, int elem_bytes)
+{
+    return ws_layout(l_s, l_x, B, H, d, elem_bytes, (size_t)max_fwd_splits(l_s, l_x, B, H, fwd_rows_per_wg(elem_bytes, d)), (size_t)elem_bytes).total;
 }
 size_t bwd_workspace_bytes(int l_s, int l_x, int B, int H, int d, int elem_bytes)
 {
-    return ws_layout(l_s, l_x, B, H, d, elem_bytes).bwd_total;
+    return ws_layout(l_s, l_x, B, H, d, elem_bytes, 1).bwd_total;
 }
-Workspace carve_workspace(void *base, int l_s, int l_x, int B, int H, int d, int elem_bytes)
+Workspace carve_workspace(void *base, size_t bytes, int l_s, int l_x, int B, int H, int d, int elem_bytes)
 {
-    const WsLayout w = ws_layout(l_s, l_x, B, H, d, elem_bytes);
+    size_t sp_f = (size_t)max_fwd_splits(l_s, l_x, B, H, fwd_rows_per_wg(elem_bytes, d));
+    while (sp_f > 1 && ws_layout(l_s, l_x, B, H, d, elem_bytes, sp_f).total > bytes) --sp_f;
+    const WsLayout w = ws_layout(l_s, l_x, B, H, d, elem_bytes, sp_f);
     char *p = static_cast<char *>(base);
     Workspace ws;
+    ws.fwd_splits = (int)sp_f;
     ws.o_part = reinterpret_cast<float *>(p + w.o_part);
     ws.lse_part = reinterpret_cast<float *>(p + w.lse_part);
     ws.D = reinterpret_cast<float *>(p + w.D);
@@ -190,10 +197,11 @@ int get_workspace(int l_s, int l_x, int B, int H, int d, int elem_bytes, void *o
         base = g_ws_ptr[dev];
         have = g_ws_bytes[dev];
     }
-    if (need > 0 && (base == nullptr || have < need))
+    const size_t least = bwd_only ? need : lss::least_workspace_bytes(l_s, l_x, B, H, d, elem_bytes);
+    if (need > 0 && (base == nullptr || have < least))
         return fail(LSS_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu %s", need, base ? have : (size_t)0,
                     own ? "passed" : "registered for this GPU (lss_set_workspace)");
-    *ws = lss::carve_workspace(base, l_s, l_x, B, H, d, elem_bytes);
+    *ws = lss::carve_workspace(base, have, l_s, l_x, B, H, d, elem_bytes);
     if (bwd_only) ws->o_part = ws->lse_part = nullptr;
     return LSS_OK;
 }

@@ -55,11 +55,10 @@ static hipError_t launch_fwd_d(const SegShape &s, const DropArgs &drop, const T 
                                float *lse, const Workspace &ws, hipStream_t st)
 {
     // Under the causal mask a segment near the start of the sequence sees few keys: the split count
-    // follows the keys this segment's query tiles see, within what the workspace was sized for.
+    // follows the keys this segment's query tiles see, within what the workspace has room for.
     const int rows_per_wg = fwd_rows_per_wg((int)sizeof(T), D);
     const int64_t kv_extent = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
-    const int n_splits = pick_fwd_splits(s.l_s, s.B, s.H, rows_per_wg, (kv_extent + 63) / 64,
-                                         max_fwd_splits(s.l_s, s.l_x, s.B, s.H, rows_per_wg), (int)sizeof(T), D);
+    const int n_splits = pick_fwd_splits(s.l_s, s.B, s.H, rows_per_wg, (kv_extent + 63) / 64, ws.fwd_splits, (int)sizeof(T), D);
     hipError_t e;
     if constexpr (sizeof(T) == 2) e = launch_fwd_bf16_main(s, drop, q, k, v, out, lse, ws, n_splits, st);
     else e = launch_fwd_f32_main(s, drop, q, k, v, out, lse, ws, n_splits, st);

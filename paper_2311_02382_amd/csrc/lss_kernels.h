@@ -44,6 +44,7 @@ int skinny_splits(const SegShape &s, bool with_drop, int elem_bytes, int most, i
 
 struct Workspace {
     // forward
+    int fwd_splits;   // key splits there is room for
     float *o_part;    // [splits, B*H, l_s, d]
     float *lse_part;  // [splits, B*H, l_s]
     // backward
@@ -53,8 +54,11 @@ struct Workspace {
     uint32_t *row_key; // [B*H, l_s]      dropout in the bf16 dK/dV workgroups: the generator's key of every query row
 };
 size_t workspace_bytes(int l_s, int l_x, int B, int H, int d, int elem_bytes);
+// The least a call accepts: for bf16 what workspace_bytes() was while partial results were kept in bf16, for callers that
+// sized their buffer then.  The forward splits no further than its partial results fit (about half as far).
+size_t least_workspace_bytes(int l_s, int l_x, int B, int H, int d, int elem_bytes);
 size_t bwd_workspace_bytes(int l_s, int l_x, int B, int H, int d, int elem_bytes);    // the leading part a backward call uses
-Workspace carve_workspace(void *base, int l_s, int l_x, int B, int H, int d, int elem_bytes);
+Workspace carve_workspace(void *base, size_t bytes, int l_s, int l_x, int B, int H, int d, int elem_bytes);
 
 template <typename T>
 hipError_t launch_fwd(const SegShape &s, const DropArgs &drop, const T *q, const T *k, const T *v, T *out, float *lse,

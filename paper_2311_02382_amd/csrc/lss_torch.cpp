@@ -24,6 +24,10 @@
 #include <stdexcept>
 #include <vector>
 
+namespace lss {
+size_t least_workspace_bytes(int l_s, int l_x, int B, int H, int d, int elem_bytes);       // lss_kernels.h, which is HIP code's
+}
+
 namespace {
 
 PyObject *g_error_type = nullptr;
@@ -207,7 +211,9 @@ void *scratch_for(PyObject *workspace, const Dims &m, const at::Tensor &like, si
     const at::Tensor &w = tensor(workspace);
     require(on_gpu(w), "workspace must be a contiguous device tensor");
     bytes = (size_t)w.numel() * w.element_size();
-    if (bytes < need) throw ValueError("workspace of " + std::to_string(bytes) + " bytes, need " + std::to_string(need));
+    // (no less than the library itself accepts)
+    if (need > 0 && bytes < lss::least_workspace_bytes((int)m.l_s, (int)m.l_x, (int)m.B, (int)m.H, (int)m.d, m.eb))
+        throw ValueError("workspace of " + std::to_string(bytes) + " bytes, need " + std::to_string(need));
     return ptr(w);
 }
 void like_q(const at::Tensor &t, const at::Tensor &q, const char *msg)

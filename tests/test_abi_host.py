@@ -64,6 +64,11 @@ def test_workspace_is_required_and_sized(lib):
     assert lib.lss_set_workspace(0x10008, need) == -4
     assert lib.lss_set_workspace(None, 64) == -1
     assert lib.lss_set_workspace(None, 0) == 0
+    # room for half the bytes of 16 splits' partial outputs is enough, a byte less is not
+    need = lib.lss_workspace_bytes(128, 8192, 1, 1, 64, 2)
+    assert lib.lss_set_workspace(0x10000, need - 16 * 128 * 64 * 2 - 1) == 0
+    assert _fwd(lib, l_x=8192) == -6
+    assert lib.lss_set_workspace(None, 0) == 0
     # a skinny segment needs room for its split partial results
     assert lib.lss_workspace_bytes(128, 8192, 1, 1, 64, 2) > 4 * 128 * 64 * 4
 

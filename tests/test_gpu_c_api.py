@@ -2,8 +2,9 @@
 import pytest
 import torch
 
+import oracle
 from paper_2311_02382_amd import lss
-from _util import stage_all
+from _util import TOL, rel_err, stage_all, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -104,3 +105,23 @@ def test_plain_projection_backward_equals_the_bindings():
     assert lss.load().lss_project_bwd(_p(dq), _p(dk), _p(dv), _p(wq), _p(wkv), L_S, L_X, rows, B, h, d, _p(dx_q), _p(dx_p),
                                       torch.cuda.current_stream().cuda_stream) == 0
     assert torch.equal(dx_q, want[0]) and torch.equal(dx_p, want[1])
+
+
+@pytest.mark.parametrize("l_s", [58, 128])
+def test_a_workspace_sized_for_bf16_partial_results_still_serves(l_s):
+    # one head, up to 16 key splits: their partial outputs took two bytes per element, and callers have buffers of that size
+    l_x, d, s0, splits = 8192, 64, 8000, 16
+    Q, K, V, DO = stage_all(1, l_x, 1, d, 9400 + l_s, "bf16")
+    sl = slice(s0, s0 + l_s)
+    q, do = Q.dev[:, sl].contiguous(), DO.dev[:, sl].contiguous()
+    former = lss.lss_workspace_bytes(l_s, l_x, 1, 1, d) - splits * l_s * d * 2      # (a multiple of 256: no rounding between the regions)
+    ro, rl = oracle.segment_fwd(Q.f64[:, sl], K.f64, V.f64, s0, True)
+    ref = oracle.segment_bwd(Q.f64[:, sl], K.f64, V.f64, DO.f64[:, sl], s0, True)
+    ws = torch.full((former + 256,), 7, dtype=torch.uint8, device="cuda")
+    out, lse = lss.lss_segment_attn_fwd(q, K.dev, V.dev, s0, workspace=ws[:former])
+    grads = lss.lss_segment_attn_bwd(q, K.dev, V.dev, s0, out, lse, do, workspace=ws[:former])
+    for a, b in zip((out, *grads), (ro, *ref)):
+        assert rel_err(to_np(a), b) <= TOL["bf16"]["t"]
+    assert torch.all(ws[former:] == 7)
+    with pytest.raises(ValueError, match="need"):
+        lss.lss_segment_attn_fwd(q, K.dev, V.dev, s0, workspace=ws[:former - 1])
