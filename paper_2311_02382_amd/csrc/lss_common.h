@@ -36,6 +36,13 @@ __device__ __forceinline__ f32x16 mma(const Frag<bf16_t> &a, const Frag<bf16_t> 
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, b.v, c, 0, 0, 0);
 }
 
+// C += A * B, one 16x16x32 step: lane l holds, for A, row (l % 16), for B, column (l % 16), both the 8 contraction
+// slots of quarter (l / 16); C is 4 floats per lane, rows 4*(l/16) + v, column l % 16.
+__device__ __forceinline__ f32x4 mma16(const Frag<bf16_t> &a, const Frag<bf16_t> &b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
+}
+
 // 8 consecutive elements, 16-byte aligned
 template <typename T> __device__ __forceinline__ Frag<T> load_frag(const T *p);
 template <> __device__ __forceinline__ Frag<bf16_t> load_frag<bf16_t>(const bf16_t *p)

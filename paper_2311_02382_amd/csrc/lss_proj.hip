@@ -11,10 +11,11 @@
 // contraction runs in tiles of 64 through a ring of STAGES LDS slots that are filled global -> LDS
 // directly, one barrier per tile.  The finished tile goes through LDS once more so that it is written to
 // memory as whole rows.  The tile is chosen per launch (launch_proj): 2048 x 512 -> 2048 took 17.0 us with
-// the 256 x 256 tile alone and takes 9.1, 2048 x 2048 -> 512 46.2 and now 9.4; at 16384 x 2048 -> 8192 the barrier ahead
-// of a tile's last step and the order of the tiles took the 256 x 256 tile from 526 to 466 us (1180 TFLOP/s; the
-// vendor's library 432).  What bounds it there is LDS traffic next to the matrix cores: 196 KB of operand
-// reads and 64 KB of tile writes per contraction tile are as many cycles as its matrix instructions.
+// the 256 x 256 tile alone and takes 9.1, 2048 x 2048 -> 512 46.2 and now 9.4.
+// Matrix instructions of 16 x 16 x 32, not 32 x 32 x 16: on Gaussian operands it is the chip's power that bounds a
+// loop of them, and registers alone reach 2050 TFLOP/s with the former and 1820 with the latter; the operand bytes per
+// flop from LDS are the same.  16384 x 4096 -> 1024: 119 -> 109 us (1260 TFLOP/s), 16384 x 1024 -> 4096: 149 -> 140,
+// the contraction of 16384 x 2048 floats 568 -> 518; launches of a few microseconds are unchanged.
 //   W_TR   weights stored [k][n] (forward: W as given).  Their fragments come from the LDS tile
 //          by transposing reads; otherwise the weights are stored [n][k] (backward: W as given
 //          IS W'^T) and are read plainly.
@@ -44,12 +45,14 @@ struct GemmShape {
     static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, STAGES = STAGES_, KG = KG_;
     static constexpr int MW = TM / WM, NW = TN / WN, GW = MW * NW;      // wavefronts of a group
     static constexpr int WAVES = KG * GW, NT = 64 * WAVES, GT = 64 * GW;
-    static constexpr int MB = WM / 32, NB = WN / 32;            // accumulator blocks of a wavefront
+    static constexpr int MB = WM / 16, NB = WN / 16;            // accumulator blocks of a wavefront
+    static constexpr int HB = MB < 4 ? MB : 4;                  // row blocks of a step: at most 4 x 4 fragments are held twice
+    static constexpr int MH = MB / HB, STEPS = PK / 32 * MH;    // steps per contraction tile
     static constexpr int ABYTES = TM * PK * 2, WBYTES = TN * PK * 2, SLOT = ABYTES + WBYTES, RING = STAGES * SLOT;
     static constexpr int LDS = KG * RING;
     static constexpr int PER_CU = kLdsPerCu / LDS;              // workgroups a compute unit holds at once
     static constexpr int WAVES_PER_SIMD = PER_CU * WAVES / 4;   // what the register count has to allow
-    static_assert(STAGES >= 2 && LDS <= kLdsPerCu && (KG - 1) * GW * MB * NB * 4096 <= LDS, "");
+    static_assert(STAGES >= 2 && LDS <= kLdsPerCu && (KG - 1) * GW * MB * NB * 1024 <= LDS && STEPS % 2 == 0, "");
 };
 
 struct ProjJob {
@@ -76,14 +79,14 @@ struct ProjArgs {
 
 // Operand tile [64 k][COLS], to be read transposed.  Loaded directly like a DirectTile.  Its rows start
 // at the same LDS bank (COLS >= 128) or alternate between two (COLS = 64), so the 16-byte chunk c of row
-// r sits at chunk position c ^ swizzle(r): the four consecutive rows of which one transposing read
-// takes 64 bytes each then spread evenly over the 64 banks.
+// r sits at chunk position c ^ swizzle(r): the rows of which one transposing read takes 32 bytes each (four
+// consecutive ones per 16 lanes, eight further down the next four) then spread evenly over the 64 banks.
 template <int COLS, int WAVES>
 struct TrTile {
     static constexpr int CPR = COLS / 8;                        // 16-byte chunks per row
     static constexpr int NI = PK * CPR / 64 / WAVES;            // load instructions per wavefront
     static_assert(PK * CPR % (64 * WAVES) == 0 && NI >= 1, "");
-    static __device__ __forceinline__ int swizzle(int r) { return COLS >= 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1); }
+    static __device__ __forceinline__ int swizzle(int r) { return (COLS >= 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1)) ^ (2 * ((r >> 3) & 1)); }
     static __device__ __forceinline__ int row_of(int i, int wave, int lane) { return ((i * WAVES + wave) * 64 + lane) / CPR; }
     // chunks >= chunks_ok (columns past the matrix) re-read chunk chunks_ok - 1; rows >= rows_ok re-read row
     // rows_ok - 1
@@ -98,20 +101,19 @@ struct TrTile {
         }
     }
     static __device__ __forceinline__ int chunk_offset(int r, int c) { return r * (COLS * 2) + ((c ^ swizzle(r)) * 16); }
-    // Transposing reads (see load_frag_tr_sw for the instruction's lane mapping): within its group
-    // of 16 lanes, lane s addresses row 8 hh + s / 4 and the 8-byte piece s % 4 of the 32-byte
-    // column group nh of column block db (hh, nh: bits 1 and 0 of the group index).
-    static __device__ __forceinline__ int lane_offset(int lane, int db)
+    // Transposing reads (see load_frag_tr_sw for the instruction's lane mapping): lane s of group g of 16 lanes
+    // addresses row 8 g + s / 4 and the 8-byte piece s % 4 of the 32 bytes of column block nb (16 columns).
+    static __device__ __forceinline__ int lane_offset(int lane, int nb)
     {
-        const int grp = lane >> 4, hh = grp >> 1, nh = grp & 1, s = lane & 15;
-        return chunk_offset(8 * hh + (s >> 2), 4 * db + 2 * nh + ((s & 3) >> 1)) + (s & 1) * 8;
+        const int g = lane >> 4, s = lane & 15;
+        return chunk_offset(8 * g + (s >> 2), 2 * nb + ((s & 3) >> 1)) + (s & 1) * 8;
     }
-    // A-operand fragment of the transposed tile for contraction step ks: operand row = column
-    // (lane % 32) of block db, slot e = contraction index 16 ks + 8 hh + e -- the order in which a
-    // plain 16-byte read delivers the other operand.  (Rows 16 and 4 further down keep the permutation.)
+    // Operand fragment of the transposed tile for contraction step ks: operand row = column
+    // (lane % 16) of block nb, slot e = contraction index 32 ks + 8 (lane / 16) + e -- the order in which a
+    // plain 16-byte read delivers the other operand.  (Rows 32 and 4 further down keep the permutation.)
     static __device__ __forceinline__ Frag<bf16_t> load_frag(const char *tile, int ks, int lane_off)
     {
-        const char *p = tile + ks * 16 * (COLS * 2) + lane_off;
+        const char *p = tile + ks * 32 * (COLS * 2) + lane_off;
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
         const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * (COLS * 2)));
         const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -121,25 +123,26 @@ struct TrTile {
     }
 };
 
-// Operand fragments of one contraction step, for a wavefront's MB x NB accumulator blocks
+// Operand fragments, two sets: step j (contraction index 32 (j / MH), row blocks HB (j % MH) ..) uses fb[j % 2] and
+// fw[(j / MH) % 2]
 template <typename S>
-struct GemmFrags { Frag<bf16_t> fb[S::MB], fw[S::NB]; };
+struct GemmFrags { Frag<bf16_t> fb[2][S::HB], fw[2][S::NB]; };
 
 // The contraction.  Tile i of this wavefront's group (contraction tile g + KG i) is multiplied from slot
-// i % STAGES, in four steps of 16 indices.  Operand fragments are read from LDS one step ahead of their
+// i % STAGES, in steps of 32 indices and at most four row blocks.  Operand fragments are read from LDS one step ahead of their
 // matrix instructions, across tiles too: the barrier that publishes the next tile stands before the last step
 // of the current one, so that the reads of the next tile's first fragments -- every wavefront's at once,
 // right after the barrier -- run under that step's matrix instructions.  (With the barrier at the end of the
 // tile the matrix cores idled through them: a quarter of a 256 x 256 workgroup's time.)  Behind that
 // barrier no wavefront reads the current tile any more: its slot takes the tile STAGES further on.
 //   issue(t, slot)       starts the direct loads of contraction tile t: LOADS instructions
-//   load(slot, ks, f)    reads the fragments of step ks
+//   load(slot, j, f)     reads the fragments that step j needs and step j - 1 did not
 //   publish(t, slot)     what is left to do for tile t before the barrier that publishes it, its loads having landed
 //   fetch(t)             REGS: starts the loads of the part of tile t that travels through registers, before those of issue(t)
 //   stash(t, slot)       REGS: writes it to LDS, before issue(t)'s loads are waited for (with both the other way round
 //                        a launch of 8192 x 2048 floats takes 63 us instead of 57)
 template <typename S, int LOADS, typename Issue, typename Load, typename Publish, typename Fetch, typename Stash>
-__device__ __forceinline__ void gemm_loop(f32x16 (&acc)[S::MB][S::NB], int T, int group, bool regs, Issue &&issue, Load &&load,
+__device__ __forceinline__ void gemm_loop(f32x4 (&acc)[S::MB][S::NB], int T, int group, bool regs, Issue &&issue, Load &&load,
                                           Publish &&publish, Fetch &&fetch, Stash &&stash)
 {
     const int iters = (T + S::KG - 1) / S::KG, mine = (T - group + S::KG - 1) / S::KG;      // tiles of the longest and of this group
@@ -158,26 +161,32 @@ __device__ __forceinline__ void gemm_loop(f32x16 (&acc)[S::MB][S::NB], int T, in
     if (mine > 0) publish(tile(0), 0);
     __syncthreads();
     if (regs && mine > 1) fetch(tile(1));
-    GemmFrags<S> f[2];
-    auto multiply = [&](const GemmFrags<S> &g) {
-        __builtin_amdgcn_sched_barrier(0);
+    GemmFrags<S> f;
+    auto multiply = [&](int j) __attribute__((always_inline)) {
 #pragma unroll
-        for (int mb = 0; mb < S::MB; ++mb)
+        for (int mb = 0; mb < S::HB; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < S::NB; ++nb) acc[mb][nb] = mma(g.fw[nb], g.fb[mb], acc[mb][nb]);
+            for (int nb = 0; nb < S::NB; ++nb) {
+                f32x4 &c = acc[j % S::MH * S::HB + mb][nb];
+                c = mma16(f.fw[j / S::MH & 1][nb], f.fb[j & 1][mb], c);
+            }
+#pragma unroll
+        for (int i = 0; i < S::HB * S::NB; ++i) {       // a matrix instruction, a read of the next step's, ...
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
-    constexpr int KS = PK / 16;
-    if (S::KG == 1 || mine > 0) load(0, 0, f[0]);
+    if (S::KG == 1 || mine > 0) load(0, 0, f);
     int slot = 0;
     for (int i = 0; i < iters; ++i) {
         const int nxt = slot + 1 == S::STAGES ? 0 : slot + 1;
         const bool busy = S::KG == 1 || i < mine;
         if (busy) {
 #pragma unroll
-            for (int ks = 0; ks + 1 < KS; ++ks) {
-                load(slot, ks + 1, f[(ks + 1) & 1]);
-                multiply(f[ks & 1]);
+            for (int j = 0; j + 1 < S::STEPS; ++j) {
+                load(slot, j + 1, f);
+                multiply(j);
             }
         }
         if (i + 1 < iters) {
@@ -188,59 +197,53 @@ __device__ __forceinline__ void gemm_loop(f32x16 (&acc)[S::MB][S::NB], int T, in
             if (regs && i + 2 < mine) fetch(tile(i + 2));
             __syncthreads();
             if (i + S::STAGES < mine) issue(tile(i + S::STAGES), slot);
-            if (more) load(nxt, 0, f[0]);
+            if (more) load(nxt, 0, f);
         }
-        if (busy) multiply(f[(KS - 1) & 1]);
+        if (busy) multiply(S::STEPS - 1);
         slot = nxt;
     }
 }
 // Adds the groups' accumulators up into group 0's, in group order, through the (now free) LDS.
 template <typename S>
-__device__ __forceinline__ void gemm_add_groups(char *smem, f32x16 (&acc)[S::MB][S::NB], int group, int gwave, int lane)
+__device__ __forceinline__ void gemm_add_groups(char *smem, f32x4 (&acc)[S::MB][S::NB], int group, int gwave, int lane)
 {
     if constexpr (S::KG > 1) {
         constexpr int BLOCKS = S::MB * S::NB;
-        auto at = [&](int g, int blk, int e4) {
-            return reinterpret_cast<f32x4 *>(smem + ((((g - 1) * S::GW + gwave) * BLOCKS + blk) * 4 + e4) * 1024 + lane * 16);
+        auto at = [&](int g, int blk) {
+            return reinterpret_cast<f32x4 *>(smem + (((g - 1) * S::GW + gwave) * BLOCKS + blk) * 1024 + lane * 16);
         };
         __syncthreads();
 #pragma unroll
         for (int blk = 0; blk < BLOCKS; ++blk)
-#pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) {
-                const f32x16 &a = acc[blk / S::NB][blk % S::NB];
-                if (group > 0) *at(group, blk, e4) = f32x4{a[4 * e4], a[4 * e4 + 1], a[4 * e4 + 2], a[4 * e4 + 3]};
-            }
+            if (group > 0) *at(group, blk) = acc[blk / S::NB][blk % S::NB];
         __syncthreads();
         if (group == 0) {
 #pragma unroll
             for (int g = 1; g < S::KG; ++g)
 #pragma unroll
-                for (int blk = 0; blk < BLOCKS; ++blk)
+                for (int blk = 0; blk < BLOCKS; ++blk) {
+                    const f32x4 v = *at(g, blk);
 #pragma unroll
-                    for (int e4 = 0; e4 < 4; ++e4) {
-                        const f32x4 v = *at(g, blk, e4);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[blk / S::NB][blk % S::NB][4 * e4 + e] += v[e];
-                    }
+                    for (int e = 0; e < 4; ++e) acc[blk / S::NB][blk % S::NB][e] += v[e];
+                }
         }
     }
 }
 template <typename S>
-__device__ __forceinline__ void gemm_clear(f32x16 (&acc)[S::MB][S::NB])
+__device__ __forceinline__ void gemm_clear(f32x4 (&acc)[S::MB][S::NB])
 {
 #pragma unroll
     for (int mb = 0; mb < S::MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < S::NB; ++nb)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[mb][nb][e] = 0.f;
+            for (int e = 0; e < 4; ++e) acc[mb][nb][e] = 0.f;
 }
 
 // The finished tile -> LDS, a pass of CPP columns at a time, from where every wavefront reads whole row
 // pieces: the 16-byte chunk c of row m sits at chunk position c ^ (m % chunks per row).
-// Accumulator block (mb, nb), element v of a lane: row m = WM wm + 32 mb + lq, column n = WN wn +
-// 32 nb + 8 (v / 4) + 4 hh + v % 4.  Rows >= rows_data are written as zeros.
+// Accumulator block (mb, nb), element v of a lane: row m = WM wm + 16 mb + lane % 16, column n = WN wn +
+// 16 nb + 4 (lane / 16) + v.  Rows >= rows_data are written as zeros.
 template <typename S, bool OUT_F32>
 struct GemmStore {
     static constexpr int EB = OUT_F32 ? 4 : 2, CW = 16 / EB;            // bytes per element, columns per chunk
@@ -249,26 +252,24 @@ struct GemmStore {
     static_assert(CPP % S::WN == 0 && S::TM * CPP * EB <= S::LDS && S::NT % CPR == 0, "");
     static constexpr int ROWS_PER_IT = S::NT / CPR, ITS = (S::TM + ROWS_PER_IT - 1) / ROWS_PER_IT;
     static __device__ __forceinline__ int offset(int m, int c) { return m * (CPP * EB) + ((c ^ (m & (CPR - 1))) * 16); }
-    static __device__ __forceinline__ void to_lds(char *smem, const f32x16 (&acc)[S::MB][S::NB], int pass, int wm, int wn, int lq,
-                                                  int hh, int rows_data)
+    static __device__ __forceinline__ void to_lds(char *smem, const f32x4 (&acc)[S::MB][S::NB], int pass, int wm, int wn, int lane,
+                                                  int rows_data)
     {
         if (PASSES > 1 && wn * S::WN / CPP != pass) return;
         const int c_first = wn * S::WN % CPP / CW;
 #pragma unroll
         for (int mb = 0; mb < S::MB; ++mb) {
-            const int m = S::WM * wm + 32 * mb + lq;
+            const int m = S::WM * wm + 16 * mb + (lane & 15), g = lane >> 4;
             const bool data = m < rows_data;
 #pragma unroll
-            for (int nb = 0; nb < S::NB; ++nb)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    f32x4 val = {0.f, 0.f, 0.f, 0.f};
-                    if (data) val = f32x4{acc[mb][nb][4 * g], acc[mb][nb][4 * g + 1], acc[mb][nb][4 * g + 2], acc[mb][nb][4 * g + 3]};
-                    if constexpr (OUT_F32)
-                        *reinterpret_cast<f32x4 *>(smem + offset(m, c_first + 8 * nb + 2 * g + hh)) = val;
-                    else
-                        *reinterpret_cast<bf16x4 *>(smem + offset(m, c_first + 4 * nb + g) + hh * 8) = pack4(val[0], val[1], val[2], val[3]);
-                }
+            for (int nb = 0; nb < S::NB; ++nb) {
+                f32x4 val = {0.f, 0.f, 0.f, 0.f};
+                if (data) val = acc[mb][nb];
+                if constexpr (OUT_F32)
+                    *reinterpret_cast<f32x4 *>(smem + offset(m, c_first + 4 * nb + g)) = val;
+                else
+                    *reinterpret_cast<bf16x4 *>(smem + offset(m, c_first + 2 * nb + (g >> 1)) + (g & 1) * 8) = pack4(val[0], val[1], val[2], val[3]);
+            }
         }
     }
 };
@@ -285,7 +286,7 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(Pro
     constexpr int W_NI = W_TR ? WTr::NI : WPlain::NI, LOADS = ATile::NI + W_NI;     // load instructions per wavefront and tile
     static_assert(EPI == EPI_NONE || !OUT_F32, "the GeLU epilogues work on bf16 results");
 
-    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int all_waves = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int group = all_waves / S::GW, wave = all_waves % S::GW, gtid = tid % S::GT;     // wave, gtid: within the group
     const int wm = wave % S::MW, wn = wave / S::MW;
@@ -307,14 +308,14 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(Pro
     const int rows_data = min(min(J.rows, J.rows_ok) - m0, S::TM);      // of which this many have data in A
     const int cols_here = min(J.N - n0, S::TN);                         // a multiple of 64
 
-    auto store_tiles = [&](const f32x16 (&acc)[S::MB][S::NB], bool from_acc) {
+    auto store_tiles = [&](const f32x4 (&acc)[S::MB][S::NB], bool from_acc) {
         OutT *c0 = static_cast<OutT *>(J.c0) + (int64_t)batch * J.c_batch_stride + (int64_t)m0 * args.ldc;
         OutT *c1 = static_cast<OutT *>(J.c1) + (int64_t)batch * J.c_batch_stride + (int64_t)m0 * args.ldc;
 #pragma unroll
         for (int pass = 0; pass < Store::PASSES; ++pass) {
             if (from_acc) {
                 __syncthreads();        // every wavefront is done with what the LDS held
-                if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, lq, hh, rows_data);
+                if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, lane, rows_data);
                 __syncthreads();
             }
             const int c = tid % Store::CPR, col = pass * Store::CPP + c * Store::CW;
@@ -346,7 +347,7 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(Pro
         }
     };
 
-    f32x16 acc[S::MB][S::NB];
+    f32x4 acc[S::MB][S::NB];
     gemm_clear<S>(acc);
     if (rows_data <= 0) {       // no row of this tile has data: its rows of C are zero
         // (skip_tail leaves the rows unwritten from the next multiple of 256 on, whatever the tile)
@@ -364,14 +365,18 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(Pro
     if constexpr (W_TR) WTr::offsets(offW, J.ldw, wave, lane, cols_here / 8);
     else WPlain::offsets(offW, J.ldw, cols_here, wave, lane);
 
+    // (copies: the loads' assembly counts as a write to memory, after which what is read through `J` is fetched again, by a
+    // scalar load in every contraction tile whose result waits for all LDS reads on their way)
     const char *a0 = static_cast<const char *>(J.a0), *a1 = static_cast<const char *>(J.a1);
+    const bf16_t *const w0 = J.w + (W_TR ? (int64_t)n0 : (int64_t)n0 * J.ldw);
+    const int lda = args.lda, ldw = J.ldw;
     const int AE = a_f32 ? 4 : 2;               // bytes per element of A
     const int64_t a_tile0 = ((int64_t)batch * J.a_batch_stride + (int64_t)m0 * args.lda) * AE;
     auto a_src = [&](int t) -> const char * {   // first element of contraction tile t of this row tile
         return (t < t_split ? a0 + (int64_t)t * PK * AE : a1 + (int64_t)(t - t_split) * PK * AE) + a_tile0;
     };
     auto issue_w = [&](int t, int slot) {
-        const bf16_t *src = W_TR ? J.w + (int64_t)t * PK * J.ldw + n0 : J.w + (int64_t)n0 * J.ldw + (int64_t)t * PK;
+        const bf16_t *src = w0 + (W_TR ? (int64_t)t * PK * ldw : (int64_t)t * PK);
         lds_dma_n<W_NI, S::GW * 1024>(src, offW, ring + slot * S::SLOT + S::ABYTES + wave * 1024);
     };
     auto issue_a = [&](int t, int slot) {       // bf16 A: direct
@@ -387,7 +392,7 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(Pro
 #pragma unroll
             for (int i = 0; i < FCH; ++i) {
                 const int c = i * S::GT + gtid, row = min(c >> 3, rows_data - 1);
-                const f32x4 *p = reinterpret_cast<const f32x4 *>(src + ((int64_t)row * args.lda + (c & 7) * 8) * 4);
+                const f32x4 *p = reinterpret_cast<const f32x4 *>(src + ((int64_t)row * lda + (c & 7) * 8) * 4);
                 stage[2 * i] = p[0];       // (re-read from L2 by the workgroups of the other column tiles)
                 stage[2 * i + 1] = p[1];
             }
@@ -407,26 +412,29 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(Pro
         }
     };
 
-    // ---- per-lane LDS offsets of the operand fragments of contraction step ks (16 indices): slot e
-    // of a fragment carries index 16 ks + 8 hh + e.  (A row 32 further down keeps the permutation.)
-    int b_off[PK / 16], w_off[PK / 16], wt_off[S::NB];
+    // ---- per-lane LDS offsets of the operand fragments of contraction step ks (32 indices): slot e
+    // of a fragment carries index 32 ks + 8 (lane / 16) + e.  (A row 16 further down keeps the permutation.)
+    int b_off[PK / 32], w_off[PK / 32], wt_off[S::NB];
 #pragma unroll
-    for (int ks = 0; ks < PK / 16; ++ks) {
-        b_off[ks] = ATile::chunk_offset(S::WM * wm + lq, 2 * ks + hh);
-        w_off[ks] = WPlain::chunk_offset(S::WN * wn + lq, 2 * ks + hh);
+    for (int ks = 0; ks < PK / 32; ++ks) {
+        b_off[ks] = ATile::chunk_offset(S::WM * wm + (lane & 15), 4 * ks + (lane >> 4));
+        w_off[ks] = WPlain::chunk_offset(S::WN * wn + (lane & 15), 4 * ks + (lane >> 4));
     }
 #pragma unroll
     for (int nb = 0; nb < S::NB; ++nb) wt_off[nb] = WTr::lane_offset(lane, S::NB * wn + nb);
-    auto load = [&](int slot, int ks, GemmFrags<S> &f) __attribute__((always_inline)) {
+    auto load = [&](int slot, int j, GemmFrags<S> &f) __attribute__((always_inline)) {
         const char *at = ring + slot * S::SLOT, *wt = at + S::ABYTES;
+        const int ks = j / S::MH, first = j % S::MH * S::HB;
+        if (first == 0) {
 #pragma unroll
-        for (int nb = 0; nb < S::NB; ++nb) {
-            if constexpr (W_TR) f.fw[nb] = WTr::load_frag(wt, ks, wt_off[nb]);
-            else f.fw[nb] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(wt + w_off[ks] + nb * 32 * PK * 2));
+            for (int nb = 0; nb < S::NB; ++nb) {
+                if constexpr (W_TR) f.fw[ks & 1][nb] = WTr::load_frag(wt, ks, wt_off[nb]);
+                else f.fw[ks & 1][nb] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(wt + w_off[ks] + nb * 16 * PK * 2));
+            }
         }
 #pragma unroll
-        for (int mb = 0; mb < S::MB; ++mb)
-            f.fb[mb] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(at + b_off[ks] + mb * 32 * PK * 2));
+        for (int mb = 0; mb < S::HB; ++mb)
+            f.fb[j & 1][mb] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(at + b_off[ks] + (first + mb) * 16 * PK * 2));
     };
     auto issue = [&](int t, int slot) {
         if (!a_f32) issue_a(t, slot);
@@ -465,7 +473,7 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
     using ATile = TrTile<S::TM, S::GW>;
     using WTile = TrTile<S::TN, S::GW>;
     constexpr int LOADS = ATile::NI + (DC_F32 ? 0 : WTile::NI);
-    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int all_waves = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int group = all_waves / S::GW, wave = all_waves % S::GW, gtid = tid % S::GT;     // wave, gtid: within the group
     const int wm = wave % S::MW, wn = wave / S::MW;
@@ -556,19 +564,23 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
         }
     };
 
-    int at_off[S::MB], wt_off[S::NB];
-#pragma unroll
-    for (int mb = 0; mb < S::MB; ++mb) at_off[mb] = ATile::lane_offset(lane, S::MB * wm + mb);
+    // (column block mb of A: the first one's chunk position with bits flipped; eight offsets kept apart would not fit
+    // the registers next to a float dC's)
+    const int at_off = ATile::lane_offset(lane, S::MB * wm);
+    int wt_off[S::NB];
 #pragma unroll
     for (int nb = 0; nb < S::NB; ++nb) wt_off[nb] = WTile::lane_offset(lane, S::NB * wn + nb);
-    f32x16 acc[S::MB][S::NB];
+    f32x4 acc[S::MB][S::NB];
     gemm_clear<S>(acc);
-    auto load = [&](int slot, int ks, GemmFrags<S> &f) __attribute__((always_inline)) {
+    auto load = [&](int slot, int j, GemmFrags<S> &f) __attribute__((always_inline)) {
         const char *at = ring + slot * S::SLOT, *wt = at + S::ABYTES;
+        const int ks = j / S::MH, first = j % S::MH * S::HB;
+        if (first == 0) {
 #pragma unroll
-        for (int nb = 0; nb < S::NB; ++nb) f.fw[nb] = WTile::load_frag(wt, ks, wt_off[nb]);
+            for (int nb = 0; nb < S::NB; ++nb) f.fw[ks & 1][nb] = WTile::load_frag(wt, ks, wt_off[nb]);
+        }
 #pragma unroll
-        for (int mb = 0; mb < S::MB; ++mb) f.fb[mb] = ATile::load_frag(at, ks, at_off[mb]);
+        for (int mb = 0; mb < S::HB; ++mb) f.fb[j & 1][mb] = ATile::load_frag(at, ks, at_off ^ ((first + mb) * 32));
     };
     auto publish = [&](int t, int slot) {
         if (t == T - 1) clear_tail(slot);
@@ -580,7 +592,7 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
 #pragma unroll
     for (int pass = 0; pass < Store::PASSES; ++pass) {
         __syncthreads();
-        if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, lq, hh, S::TM);
+        if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, lane, S::TM);
         __syncthreads();
         const int c = tid % Store::CPR, col = pass * Store::CPP + c * Store::CW;
         if (col < cols_n) {
