@@ -74,6 +74,7 @@ enum { EPI_NONE = 0, EPI_GELU = 1, EPI_GELU_BWD = 2 };
 struct ProjArgs {
     ProjJob job[2];
     int n_jobs, lda, ldc, skip_tail;
+    int stream;                 // C is written past the caches (streams_results)
     int zero_begin;             // first workgroup id of the tiles without data (of job 0; the others have none)
 };
 
@@ -308,6 +309,10 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(Pro
     const int rows_data = min(min(J.rows, J.rows_ok) - m0, S::TM);      // of which this many have data in A
     const int cols_here = min(J.N - n0, S::TN);                         // a multiple of 64
 
+    auto put16 = [&](void *to, f32x4 v) __attribute__((always_inline)) {
+        if (args.stream) __builtin_nontemporal_store(v, static_cast<f32x4 *>(to));
+        else *static_cast<f32x4 *>(to) = v;
+    };
     auto store_tiles = [&](const f32x4 (&acc)[S::MB][S::NB], bool from_acc) {
         OutT *c0 = static_cast<OutT *>(J.c0) + (int64_t)batch * J.c_batch_stride + (int64_t)m0 * args.ldc;
         OutT *c1 = static_cast<OutT *>(J.c1) + (int64_t)batch * J.c_batch_stride + (int64_t)m0 * args.ldc;
@@ -335,12 +340,12 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(Pro
                         for (int e = 0; e < 8; ++e) cv[e] = (bf16_t)((float)cv[e] * gelu_slope((float)uu[e]));
                         raw = __builtin_bit_cast(f32x4, cv);
                     }
-                    *reinterpret_cast<f32x4 *>(dst + (int64_t)m * args.ldc) = raw;
+                    put16(dst + (int64_t)m * args.ldc, raw);
                     if constexpr (EPI == EPI_GELU) {
                         bf16x8 cv = __builtin_bit_cast(bf16x8, raw);
 #pragma unroll
                         for (int e = 0; e < 8; ++e) cv[e] = (bf16_t)gelu_value((float)cv[e]);
-                        *reinterpret_cast<bf16x8 *>(c1 + n + (int64_t)m * args.ldc) = cv;
+                        put16(c1 + n + (int64_t)m * args.ldc, __builtin_bit_cast(f32x4, cv));
                     }
                 }
             }
@@ -636,6 +641,21 @@ hipError_t launch_proj_shape(ProjArgs &args, int kernel_id, hipStream_t st)
     return hipGetLastError();
 }
 
+// Whether C is written with non-temporal stores: where A and C together are more than half the last-level cache
+// (256 MB), results kept there and in the L2s only push out the operand tiles that other workgroups are about
+// to read again.  98304 x 1024 -> 2048 columns and -> 1024 more (projections of 4 x 24576 rows): 442 -> 393 us; 65536 x 512 -> 2048:
+// 175 -> 143, with a pass over the results right after it 273 -> 264; gradient of 4 x 12000 rows of 512 columns 97 -> 80.  Below
+// that it gains nothing and a reader of the results pays (16384 x 1024 -> 2048 and GeLU after it: 98.5 -> 100.8).
+bool streams_results(const ProjArgs &args, bool out_f32)
+{
+    double bytes = 0.0;
+    for (int j = 0; j < args.n_jobs; ++j) {
+        const ProjJob &J = args.job[j];
+        bytes += (double)J.batches * ((double)std::min(J.rows, J.rows_ok) * J.K * (J.a_f32 ? 4 : 2) + (double)J.rows * J.N * (out_f32 ? 4 : 2));
+    }
+    return bytes > 128e6;
+}
+
 // Which tile a launch takes: the one with the smallest estimated time.  A round of workgroups costs
 //     fixed + contraction tiles x per_tile   microseconds;
 // where compute units hold one workgroup each (PER_CU = 1: where half of them have one) a contraction tile takes
@@ -691,6 +711,7 @@ hipError_t launch_proj(ProjArgs &args, int kernel_id, hipStream_t st)
         const double room = 256.0 * S::PER_CU, rest = wgs - room * (double)(int64_t)(wgs / room), tiles = work / wgs;
         return gemm_estimate<S>(wgs, tiles, rest <= last_n ? last_tiles : tiles);     // (the last job's workgroups start last)
     };
+    args.stream = streams_results(args, OUT_F32);
     const double t[5] = {estimate(ShapeL{}), estimate(ShapeM{}), estimate(ShapeM2{}), estimate(ShapeS{}), estimate(ShapeS4{})};
     int best = 0;
     for (int i = 1; i < 5; ++i)
