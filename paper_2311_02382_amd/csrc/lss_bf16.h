@@ -110,12 +110,12 @@ struct DirectTile {
             off[i] = ((uint32_t)min(row, rows_ok - 1) * (uint32_t)row_stride + (uint32_t)chunk * 8u) * 2u;
         }
     }
-    // Issue the loads of two tensors' tiles with one set of offsets, the second tile following the
-    // first in LDS (lds_tile + BYTES).  Base pointers, `lds_tile` and `wave` must be wavefront-uniform.
+    // Issue the loads of two tensors' tiles, the second tile following the first in LDS (lds_tile + BYTES); off0 and off1
+    // may be the same.  Base pointers, `lds_tile` and `wave` must be wavefront-uniform.
     // One assembly block (see lds_dma for why assembly), so that M0 is saved and restored once and
     // merely stepped by WAVES KB (one KB per wavefront) from load to load.
-    static __device__ __forceinline__ void issue_pair(const bf16_t *g0_uniform, const bf16_t *g1_uniform,
-                                                      const uint32_t (&off)[NI], char *lds_tile, int wave)
+    static __device__ __forceinline__ void issue_pair(const bf16_t *g0_uniform, const bf16_t *g1_uniform, const uint32_t (&off0)[NI],
+                                                      const uint32_t (&off1)[NI], char *lds_tile, int wave)
     {
         static_assert(NI == 2 || NI == 4, "");
         constexpr int STEP = WAVES * 1024;              // between two load instructions of one wavefront
@@ -123,26 +123,26 @@ struct DirectTile {
         uint32_t saved;
         if constexpr (NI == 2) {
             asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %2, %4\n\ts_add_u32 m0, m0, %6\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %3, %4\n\ts_add_u32 m0, m0, %6\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %2, %5\n\ts_add_u32 m0, m0, %6\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %3, %5\n\ts_mov_b32 m0, %0"
-                         : "=&s"(saved)
-                         : "s"(lds_addr), "v"(off[0]), "v"(off[1]), "s"(g0_uniform), "s"(g1_uniform), "i"(STEP)
-                         : "memory", "scc");
-        } else {
-            asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
                          "global_load_lds_dwordx4 %2, %6\n\ts_add_u32 m0, m0, %8\n\ts_nop 0\n\t"
                          "global_load_lds_dwordx4 %3, %6\n\ts_add_u32 m0, m0, %8\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %4, %6\n\ts_add_u32 m0, m0, %8\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %5, %6\n\ts_add_u32 m0, m0, %8\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %2, %7\n\ts_add_u32 m0, m0, %8\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %3, %7\n\ts_add_u32 m0, m0, %8\n\ts_nop 0\n\t"
                          "global_load_lds_dwordx4 %4, %7\n\ts_add_u32 m0, m0, %8\n\ts_nop 0\n\t"
                          "global_load_lds_dwordx4 %5, %7\n\ts_mov_b32 m0, %0"
                          : "=&s"(saved)
-                         : "s"(lds_addr), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(g0_uniform), "s"(g1_uniform),
-                           "i"(STEP)
+                         : "s"(lds_addr), "v"(off0[0]), "v"(off0[1]), "v"(off1[0]), "v"(off1[1]), "s"(g0_uniform), "s"(g1_uniform), "i"(STEP)
+                         : "memory", "scc");
+        } else {
+            asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+                         "global_load_lds_dwordx4 %2, %10\n\ts_add_u32 m0, m0, %12\n\ts_nop 0\n\t"
+                         "global_load_lds_dwordx4 %3, %10\n\ts_add_u32 m0, m0, %12\n\ts_nop 0\n\t"
+                         "global_load_lds_dwordx4 %4, %10\n\ts_add_u32 m0, m0, %12\n\ts_nop 0\n\t"
+                         "global_load_lds_dwordx4 %5, %10\n\ts_add_u32 m0, m0, %12\n\ts_nop 0\n\t"
+                         "global_load_lds_dwordx4 %6, %11\n\ts_add_u32 m0, m0, %12\n\ts_nop 0\n\t"
+                         "global_load_lds_dwordx4 %7, %11\n\ts_add_u32 m0, m0, %12\n\ts_nop 0\n\t"
+                         "global_load_lds_dwordx4 %8, %11\n\ts_add_u32 m0, m0, %12\n\ts_nop 0\n\t"
+                         "global_load_lds_dwordx4 %9, %11\n\ts_mov_b32 m0, %0"
+                         : "=&s"(saved)
+                         : "s"(lds_addr), "v"(off0[0]), "v"(off0[1]), "v"(off0[2]), "v"(off0[3]), "v"(off1[0]), "v"(off1[1]), "v"(off1[2]),
+                           "v"(off1[3]), "s"(g0_uniform), "s"(g1_uniform), "i"(STEP)
                          : "memory", "scc");
         }
     }

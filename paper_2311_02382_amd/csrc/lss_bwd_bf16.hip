@@ -140,7 +140,7 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
 #pragma unroll
             for (int i = 0; i < Tile::NI; ++i) off[i] = offF[i] + (offD[i] & part);
             static_assert(C::OFF_V == Tile::BYTES, "V tile follows K tile");
-            Tile::issue_pair(tile_ptr(kbase, t, tile_bytes), tile_ptr(vbase, t, tile_bytes), off, smem + slot * C::SLOT, wave);
+            Tile::issue_pair(tile_ptr(kbase, t, tile_bytes), tile_ptr(vbase, t, tile_bytes), off, off, smem + slot * C::SLOT, wave);
             if (DROP && wave == 0)
                 reinterpret_cast<uint32_t *>(ck_ring)[(t & 3) * C::BC + lane] = drop_col_key(drop_cs, (uint32_t)(j0 + lane));
         };
@@ -563,7 +563,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         for (int i = 0; i < Tile::NI; ++i) off[i] = offF[i] + (offD[i] & part);
         static_assert(C::OFF_G == Tile::BYTES, "dO tile follows Q tile");
         char *dst = smem + slot * C::SLOT;
-        Tile::issue_pair(tile_ptr(qbase, tq, tile_bytes), tile_ptr(gbase, tq, tile_bytes), off, dst, wave);
+        Tile::issue_pair(tile_ptr(qbase, tq, tile_bytes), tile_ptr(gbase, tq, tile_bytes), off, off, dst, wave);
         if constexpr (!OWN) {
             const uint32_t ro = (uint32_t)min(lane, s.l_s - rq0 - 1) * 4u;
             lds_dma<4>(sv_base + rq0, ro, dst + sv_off);
@@ -848,7 +848,7 @@ __device__ __forceinline__ void bwd_dkv_skinny_body(char *smem, const SegShape &
         Tile::offsets(off, ld, s.l_s, wave, lane);
         const bf16_t *qbase = q + (int64_t)b * s.l_s * ld + (int64_t)h * D;
         const bf16_t *gbase = dO + (int64_t)b * s.l_s * ld + (int64_t)h * D;
-        Tile::issue_pair(qbase, gbase, off, smem, wave);
+        Tile::issue_pair(qbase, gbase, off, off, smem, wave);
     }
     auto load_kv = [&](int kt, Frag<bf16_t> (&kf)[NU], Frag<bf16_t> (&vf)[NU]) __attribute__((always_inline)) {
         const int jj = kt * C::BKV + wave * C::KW + lq;

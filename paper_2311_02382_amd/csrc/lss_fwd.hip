@@ -56,12 +56,17 @@ static hipError_t launch_fwd_d(const SegShape &s, const DropArgs &drop, const T 
 {
     // Under the causal mask a segment near the start of the sequence sees few keys: the split count
     // follows the keys this segment's query tiles see, within what the workspace has room for.
-    const int rows_per_wg = fwd_rows_per_wg((int)sizeof(T), D);
-    const int64_t kv_extent = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
-    const int n_splits = pick_fwd_splits(s.l_s, s.B, s.H, rows_per_wg, (kv_extent + 63) / 64, ws.fwd_splits, (int)sizeof(T), D);
     hipError_t e;
-    if constexpr (sizeof(T) == 2) e = launch_fwd_bf16_main(s, drop, q, k, v, out, lse, ws, n_splits, st);
-    else e = launch_fwd_f32_main(s, drop, q, k, v, out, lse, ws, n_splits, st);
+    int n_splits;
+    if constexpr (sizeof(T) == 2) {
+        const FwdPlan plan = pick_fwd_plan(s, ws.fwd_splits);
+        n_splits = plan.splits;
+        e = launch_fwd_bf16_main(s, drop, q, k, v, out, lse, ws, plan, st);
+    } else {
+        const int64_t kv_extent = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
+        n_splits = pick_fwd_splits(s.l_s, s.B, s.H, fwd_rows_per_wg(4, D), (kv_extent + 63) / 64, ws.fwd_splits, D);
+        e = launch_fwd_f32_main(s, drop, q, k, v, out, lse, ws, n_splits, st);
+    }
     if (e != hipSuccess || n_splits == 1) return e;
     const int64_t items = (int64_t)s.B * s.H * s.l_s * (D / 4);
     {

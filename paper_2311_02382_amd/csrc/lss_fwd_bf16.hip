@@ -7,8 +7,16 @@
 // A wavefront issues in order, and vector work costs it several times the issue time of a matrix
 // instruction, so the stages are software-pipelined: step g issues the matrix instructions of
 // A(g+1) and C(g-1) with the vector work of B(g) spread between them.  K/V tiles travel
-// global -> LDS directly (no registers in between), a full loop iteration ahead, into a ring of
-// three unpadded, swizzled tiles; V is read transposed by DS_READ_B64_TR_B16.
+// global -> LDS directly (no registers in between), a full loop iteration ahead, into two unpadded, swizzled
+// slots each; V is read transposed by DS_READ_B64_TR_B16.
+//
+// A workgroup is RB wavefronts of 32 query rows, or KG such groups that have a part of the keys each and tiles of their own
+// in LDS, and meet there at the end: what fills the chip in launches of few rows without partial results in memory and
+// a launch to merge them, and shortens the walk that each wavefront is alone with.  Between backward passes, 8 x 2 heads of 1024
+// rows behind 0, 2048 and 4096 others: 128-row workgroups with the best split and its merge 21.1, 29.6 and 38.2 us, 64 rows in two
+// groups 14.9, 27.4 and 38.2, 128 rows in two groups 18.4, 28.5 and 35.9; 4 heads of 256 rows behind 512: 11.3, 9.7 and 12.4.  Large
+// launches keep one group (64 heads of 4096 rows: 1692 us, in two groups
+// 1829): three workgroups per compute unit hide each other's waits.  The form is chosen per launch (pick_fwd_plan).
 //
 // Softmax: B subtracts the running maximum m as it stands (no pass over the block first).  Only
 // when the block's weights of some row add up to more than 2^8 -- so no weight can be larger
@@ -22,39 +30,43 @@
 
 namespace lss {
 
-template <int D>
+template <int D, int RB_, int KG_>
 struct FwdBf16Cfg {
-    // d = 64: four wavefronts, up to three workgroups per compute unit.  d = 128: the K/V ring alone
-    // takes 96 KB of LDS, so only one workgroup fits; it has eight wavefronts (two per SIMD, 256 query
-    // rows sharing the tiles) so that one wavefront's vector work hides behind another's matrix work.
-    static constexpr int WAVES = D == 64 ? 4 : 8, RW = 32;      // wavefronts; query rows per wavefront
-    static constexpr int BR = WAVES * RW, BC = 64, NT = 64 * WAVES;
-    static constexpr int RING = 3;                      // K/V tiles resident in LDS
+    // KG groups of RB wavefronts share the query rows (32 per wavefront of a group) and have a part of the keys each.
+    static constexpr int RB = RB_, KG = KG_, WAVES = RB * KG, RW = 32, BR = RB * RW, BC = 64, NT = 64 * WAVES;
     static constexpr int NU = D / 16;                   // operand steps of the S^T product; same for O^T
-    using Tile = DirectTile<D, BC, WAVES>;
-    static constexpr int OFF_V = Tile::BYTES, SLOT = 2 * Tile::BYTES;   // one ring slot: K tile, V tile
+    using Tile = DirectTile<D, BC, RB>;
+    // A group's LDS: two pair slots, slot p a K tile (number p mod 2) and after it a V tile (number p + 1 mod 2): K is
+    // loaded one tile further ahead than V and done with one tile earlier, so that two tiles of each are enough.
+    static constexpr int OFF_V = Tile::BYTES, PAIR = 2 * Tile::BYTES, RING = 2 * PAIR;
+    // (dropout: behind them, the column keys of the last four tiles issued, 64 each)
+    static constexpr int group_lds(bool drop) { return RING + (drop ? 4 * BC * 4 : 0); }
+    // what the groups hand each other at the end: accumulators in chunks of 16 bytes per lane; maximum and row sum
+    static constexpr int UNITS = D / 8, HAND_ML = WAVES * UNITS * 1024, HAND = KG > 1 ? HAND_ML + WAVES * 512 : 0;
+    static constexpr int lds(bool drop) { return KG * group_lds(drop) > HAND ? KG * group_lds(drop) : HAND; }
     static constexpr float kMaxBlockSum = 256.0f;       // 2^8: largest sum of a lane's weights of one block without a fix-up
 };
 
 // DROP: dropout on the weights (Section 2.2): the weight that multiplies V is dropped or scaled by
 // 1 / (1 - p) according to drop_keep() of (seed, batch*head, global row, key); row sum and lse are
 // those of the softmax.
-template <int D, bool DROP>
-__global__ __launch_bounds__(FwdBf16Cfg<D>::NT, D == 64 ? 2 : 1) void fwd_bf16_kernel(SegShape s, DropArgs dr, const bf16_t *__restrict__ q,
+template <int D, bool DROP, int RB, int KG>
+__global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel(SegShape s, DropArgs dr, const bf16_t *__restrict__ q,
                                                                        const bf16_t *__restrict__ k,
                                                                        const bf16_t *__restrict__ v,
                                                                        bf16_t *__restrict__ out, float *__restrict__ lse,
                                                                        float *__restrict__ o_part,
                                                                        float *__restrict__ lse_part, int n_splits, int n_q_tiles)
 {
-    using C = FwdBf16Cfg<D>;
+    using C = FwdBf16Cfg<D, RB, KG>;
     using Tile = typename C::Tile;
     constexpr int NU = C::NU;
-    // (dropout: behind the ring, the column keys of the last four tiles issued, 64 each)
-    __shared__ __attribute__((aligned(1024))) char smem[C::RING * C::SLOT + (DROP ? 4 * C::BC * 4 : 0)];
+    __shared__ __attribute__((aligned(1024))) char smem[C::lds(DROP)];
 
     const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int all_waves = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = KG > 1 ? all_waves / RB : 0, wave = KG > 1 ? all_waves % RB : all_waves;      // wave: within the group
+    char *const ring = smem + group * C::group_lds(DROP);
     // 1-D grid in XCD order (xcd_item): one head at a time per XCD, whose workgroups share its K and
     // V in that XCD's L2.  Within a head: query tiles, last first -- under the causal mask the last
     // tiles see the most keys, and starting the longest workgroups first shortens the tail of the
@@ -72,8 +84,10 @@ __global__ __launch_bounds__(FwdBf16Cfg<D>::NT, D == 64 ? 2 : 1) void fwd_bf16_k
     const int kv_end = s.causal ? (int)min<int64_t>(s.l_x, s.s0 + r_last + 1) : s.l_x;
     const int n_tiles = (kv_end + C::BC - 1) / C::BC;
     const int per = (n_tiles + n_splits - 1) / n_splits;
-    const int t_begin = split * per, t_end = min(n_tiles, t_begin + per);
-    const int T = max(t_end - t_begin, 0);
+    const int s_begin = split * per, s_tiles = max(min(n_tiles, s_begin + per) - s_begin, 0);
+    // this group's tiles; the first group has `iters` of them, the last ones fewer or none
+    const int iters = KG > 1 ? (s_tiles + KG - 1) / KG : s_tiles;
+    const int t_begin = s_begin + group * iters, T = KG > 1 ? max(min(s_tiles - group * iters, iters), 0) : s_tiles;
 
     // this lane's query row (column of the S^T tile); rows past the segment re-read its last row
     // (unconditional loads), are computed like any other and never stored
@@ -92,7 +106,7 @@ __global__ __launch_bounds__(FwdBf16Cfg<D>::NT, D == 64 ? 2 : 1) void fwd_bf16_k
     float m = -INFINITY, l = 0.f;                       // running maximum (log2 domain); this lane's half of the row sum
     const float c = kLog2e / sqrtf((float)D);
 
-    if (T > 0) {
+    if (s_tiles > 0) {
         const bf16_t *kbase = k + (int64_t)b * s.l_x * ld + (int64_t)h * D;
         const bf16_t *vbase = v + (int64_t)b * s.l_x * ld + (int64_t)h * D;
 
@@ -101,9 +115,9 @@ __global__ __launch_bounds__(FwdBf16Cfg<D>::NT, D == 64 ? 2 : 1) void fwd_bf16_k
         // a small ring behind the tiles -- published by the same barrier as the tile
         uint32_t drop_rk = 0u, drop_cs = 0u;
         if (DROP) { drop_rk = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + r)); drop_cs = drop_col_seed(dr.seed_hi); }
-        char *const ck_ring = smem + C::RING * C::SLOT;
+        char *const ck_ring = ring + C::RING;
 
-        // ---- tile loads, by all four wavefronts.  Branch-free on purpose: a branch inside a pipeline step
+        // ---- tile loads, by all wavefronts of the group.  Branch-free on purpose: a branch inside a pipeline step
         // splits it into basic blocks, and the vector work that was meant to sit between the step's
         // matrix instructions is then moved behind the branch in one lump.
         uint32_t offF[Tile::NI], offD[Tile::NI];        // this lane's global offsets within a full tile; and what
@@ -116,19 +130,28 @@ __global__ __launch_bounds__(FwdBf16Cfg<D>::NT, D == 64 ? 2 : 1) void fwd_bf16_k
             for (int i = 0; i < Tile::NI; ++i) offD[i] = offL[i] - offF[i];
         }
         const uint32_t tile_bytes = (uint32_t)(C::BC * ld * 2);
-        auto issue_tile = [&](int t, int slot) {
-            const int j0 = t * C::BC;
+        auto tile_off = [&](int t, uint32_t (&off)[Tile::NI]) __attribute__((always_inline)) {
             const uint32_t part = t == t_part ? ~0u : 0u;
-            uint32_t off[Tile::NI];
 #pragma unroll
             for (int i = 0; i < Tile::NI; ++i) off[i] = offF[i] + (offD[i] & part);
-            static_assert(C::OFF_V == Tile::BYTES, "V tile follows K tile");
-            Tile::issue_pair(tile_ptr(kbase, t, tile_bytes), tile_ptr(vbase, t, tile_bytes), off, smem + slot * C::SLOT, wave);
-            if (DROP && wave == 0)
-                reinterpret_cast<uint32_t *>(ck_ring)[(t & 3) * C::BC + lane] = drop_col_key(drop_cs, (uint32_t)(j0 + lane));
         };
-        // the loop's prefetch: tile t + 2, or once more the last tile into a slot nobody reads any more
-        auto issue_ahead = [&](int t, int slot) { issue_tile(t_begin + min(t + 2, T - 1), slot); };
+        // K of tile tk and V of tile tv (counted from t_begin on, the last one again past the end) into pair slot `slot`
+        auto issue = [&](int tk, int tv, int slot) __attribute__((always_inline)) {
+            const int gk = t_begin + min(tk, T - 1), gv = t_begin + min(tv, T - 1);
+            uint32_t offK[Tile::NI], offV[Tile::NI];
+            tile_off(gk, offK);
+            tile_off(gv, offV);
+            static_assert(C::OFF_V == Tile::BYTES, "V tile follows K tile");
+            Tile::issue_pair(tile_ptr(kbase, gk, tile_bytes), tile_ptr(vbase, gv, tile_bytes), offK, offV, ring + slot * C::PAIR, wave);
+            if (DROP && wave == 0)
+                reinterpret_cast<uint32_t *>(ck_ring)[(gk & 3) * C::BC + lane] = drop_col_key(drop_cs, (uint32_t)(gk * C::BC + lane));
+        };
+        auto k_tile = [&](int t) { return ring + (t & 1) * C::PAIR; };
+        auto v_tile = [&](int t) { return ring + ((t & 1) ^ 1) * C::PAIR + C::OFF_V; };
+        // Iteration t's loads, behind its barrier: K of tile t + 2 in the place of tile t's, whose last rows have been read
+        // by then, and V of tile t + 1 in the place of tile t - 1's.  (Past the end a tile is loaded once more: K where it
+        // lies already or where nobody reads any more, V where nobody reads any more.)
+        auto issue_ahead = [&](int t) __attribute__((always_inline)) { issue(t + 2, t + 1, t & 1); };
 
         // ---- per-lane LDS offsets (bytes, within a tile)
         int a_off[NU];                                  // A-operand chunk of row lq for operand step kb
@@ -138,13 +161,13 @@ __global__ __launch_bounds__(FwdBf16Cfg<D>::NT, D == 64 ? 2 : 1) void fwd_bf16_k
 #pragma unroll
         for (int db = 0; db < D / 32; ++db) t_off[db] = tr_lane_offset_sw<D>(lane, db);
 
-        // ---- stage pieces.  `tile` / `kb2` name a block: LDS address of its ring slot and which half of it.
+        // ---- stage pieces.  `tile` / `kb2` name a block: LDS address of its K or V tile and which half of it.
         auto load_a = [&](const char *tile, int kb2, int kb, Frag<bf16_t> &fk) __attribute__((always_inline)) {
             fk = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(tile + kb2 * 32 * (D * 2) + a_off[kb]));
         };
         auto load_c = [&](const char *tile, int kb2, int u, Frag<bf16_t> &fv) __attribute__((always_inline)) {
             const int half = u / (D / 32), db = u % (D / 32);
-            fv = load_frag_tr_sw<D>(tile + C::OFF_V, (kb2 * 2 + half) * 16, t_off[db]);
+            fv = load_frag_tr_sw<D>(tile, (kb2 * 2 + half) * 16, t_off[db]);
         };
         // Where the causal diagonal or the end of the sequence crosses a block (first key jb), the
         // masked elements of its finished S^T accumulator are set to -inf, which B turns into weight
@@ -267,119 +290,152 @@ __global__ __launch_bounds__(FwdBf16Cfg<D>::NT, D == 64 ? 2 : 1) void fwd_bf16_k
         using std::false_type;
 
         // ---- pipeline.  Block g = keys (t_begin + g/2) * 64 + (g%2) * 32 ..; tile t = blocks 2t, 2t+1.
-        issue_tile(t_begin, 0);
-        if (T > 1) issue_tile(t_begin + 1, 1);
+        if (T > 0) {
+            issue(0, 0, 0);                             // (K of tile 0; its V here is overwritten before anybody reads it)
+            issue(1, 0, 1);
+        }
         wait_vmem_all();
         __syncthreads();
 
         if (rw0 >= s.l_s) {
             // None of this wavefront's rows exists (a partly filled last query tile): it only keeps moving
             // tiles and meeting the loop's barriers.
-            int cur = 0;
             for (int t = 0; t < T; ++t) {
-                const int prv = cur == 0 ? C::RING - 1 : cur - 1;
                 wait_vmem_all();
                 __syncthreads();
-                issue_ahead(t, prv);
-                cur = cur == C::RING - 1 ? 0 : cur + 1;
+                issue_ahead(t);
             }
-            wait_vmem_all();                            // the last, redundant prefetches must land before the workgroup's LDS is given away
-            return;
-        }
-
-        f32x16 sc0, sc1;                                // even / odd blocks
-        Frag<bf16_t> pf0[2], pf1[2];
-        // step -1: A(0) alone.  The first loop step has no C(-1): it multiplies zeros with tile 0 instead.
-        load_a(smem, 0, 0, ak[0]);
-        auto nothing = [] {};
-        step(true_type{}, false_type{}, false_type{}, smem, 0, sc0, sc1, 0, pf0, smem, 0, pf1, smem, 1, smem, 1, nothing);
+        } else if (T > 0) {
+            f32x16 sc0, sc1;                            // even / odd blocks
+            Frag<bf16_t> pf0[2], pf1[2];
+            // step -1: A(0) alone.  The first loop step has no C(-1): it multiplies zeros with tile 0 instead.
+            load_a(k_tile(0), 0, 0, ak[0]);
+            auto nothing = [] {};
+            step(true_type{}, false_type{}, false_type{}, k_tile(0), 0, sc0, sc1, 0, pf0, v_tile(0), 0, pf1, k_tile(0), 1, v_tile(0), 1, nothing);
 #pragma unroll
-        for (int half = 0; half < 2; ++half)
+            for (int half = 0; half < 2; ++half)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) pf1[half].v[e] = (bf16_t)0.f;
+                for (int e = 0; e < 8; ++e) pf1[half].v[e] = (bf16_t)0.f;
 
-        int cur = 0;                                    // ring slot of tile t
-        for (int t = 0; t < T; ++t) {
-            const int nxt = cur == C::RING - 1 ? 0 : cur + 1, prv = cur == 0 ? C::RING - 1 : cur - 1;
-            const char *t_cur = smem + cur * C::SLOT, *t_nxt = smem + nxt * C::SLOT, *t_prv = smem + prv * C::SLOT;
-            const char *t_a2 = t + 1 < T ? t_nxt : t_cur;   // tile of A(2t+2), A(2t+3); past the end: any resident tile
-            const int j0 = (t_begin + t) * C::BC;
-            // even step g = 2t: A(2t+1) [tile t, second half], B(2t), C(2t-1) [tile t-1, second half;
-            // for t = 0 tile 0, times zero]
-            // Before its last reads (which may touch tile t+1): tile t+1's loads, issued one iteration
-            // ago, have landed for this wavefront; after the barrier for all, and every wavefront has
-            // requested its last operands from tile t-1, whose slot takes tile t+2.
-            step(true_type{}, true_type{}, true_type{}, t_cur, 1, sc1, sc0, j0, pf0, t > 0 ? t_prv : t_cur, 1, pf1, t_a2, 0,
-                 t_cur, 0, [&] {
-                     wait_vmem_all();
-                     __syncthreads();
-                     issue_ahead(t, prv);
-                 });
-            // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end result unused], B(2t+1),
-            // C(2t) [tile t, first half]
-            step(true_type{}, true_type{}, true_type{}, t_a2, 0, sc0, sc1, j0 + 32, pf1, t_cur, 0, pf0, t_a2, 1, t_cur, 1,
-                 nothing);
-            cur = nxt;
+            for (int t = 0; t < T; ++t) {
+                const char *k_cur = k_tile(t), *k_nxt = t + 1 < T ? k_tile(t + 1) : k_cur;     // past the end: any resident tile
+                const char *v_cur = v_tile(t), *v_prv = t > 0 ? v_tile(t - 1) : v_cur;
+                const int j0 = (t_begin + t) * C::BC;
+                // even step g = 2t: A(2t+1) [tile t, second half], B(2t), C(2t-1) [tile t-1, second half;
+                // for t = 0 tile 0, times zero]
+                // Before its last reads (which may touch tile t+1): K of tile t+1 and V of tile t, issued one iteration
+                // ago, have landed for this wavefront; after the barrier for all, and every wavefront has
+                // requested its last operands from K of tile t and V of tile t-1.
+                step(true_type{}, true_type{}, true_type{}, k_cur, 1, sc1, sc0, j0, pf0, v_prv, 1, pf1, k_nxt, 0, v_cur, 0, [&] {
+                    wait_vmem_all();
+                    __syncthreads();
+                    issue_ahead(t);
+                });
+                // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end result unused], B(2t+1),
+                // C(2t) [tile t, first half]
+                step(true_type{}, true_type{}, true_type{}, k_nxt, 0, sc0, sc1, j0 + 32, pf1, v_cur, 0, pf0, k_nxt, 1, v_cur, 1, nothing);
+            }
+            // step 2T: C(2T-1) [tile T-1, second half] alone
+            step(false_type{}, false_type{}, true_type{}, ring, 0, sc0, sc0, 0, pf0, v_tile(T - 1), 1, pf1, ring, 0, v_tile(T - 1), 1, nothing);
         }
-        // step 2T: C(2T-1) [tile T-1, second half] alone
-        {
-            const char *t_last = smem + (cur == 0 ? C::RING - 1 : cur - 1) * C::SLOT;
-            step(false_type{}, false_type{}, true_type{}, smem, 0, sc0, sc0, 0, pf0, t_last, 1, pf1, smem, 0, t_last, 1, nothing);
-        }
+        if (KG > 1)
+            for (int t = T; t < iters; ++t) __syncthreads();           // the barriers of the groups that have more tiles
         wait_vmem_all();                                // the last, redundant prefetches must land before the workgroup's LDS is given away
     }
 
-    const float l_tot = l + __shfl_xor(l, 32);
-    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    const float lse_nat = l_tot > 0.f ? (m + log2f(l_tot)) * kLn2 : -INFINITY;
-    if (!row_ok) return;
-    if (n_splits == 1) {
-        bf16_t *op = out + ((int64_t)b * s.l_s + r) * ld + (int64_t)h * D;
+    // this lane's row of the result: column group u, columns 8 u + 4 hh .. + 3 (a split's normalised output travels to the
+    // merge kernel in fp32: rounded to bf16 once, there)
+    const int64_t part_row = ((int64_t)split * bhs + bh) * s.l_s + r;
+    auto put = [&](int u, const f32x4 &val) __attribute__((always_inline)) {
+        if (n_splits == 1)
+            *reinterpret_cast<bf16x4 *>(out + ((int64_t)b * s.l_s + r) * ld + (int64_t)h * D + 8 * u + 4 * hh) = pack4(val[0], val[1], val[2], val[3]);
+        else *reinterpret_cast<f32x4 *>(o_part + part_row * D + 8 * u + 4 * hh) = val;
+    };
+    auto put_lse = [&](float v) {
+        if (n_splits == 1) lse[(int64_t)bh * s.l_s + r] = v;
+        else lse_part[part_row] = v;
+    };
+    const float l_own = l + __shfl_xor(l, 32);
+    if constexpr (KG == 1) {
+        const float inv = l_own > 0.f ? 1.f / l_own : 0.f;
+        if (!row_ok) return;
+        if (hh == 0) put_lse(l_own > 0.f ? (m + log2f(l_own)) * kLn2 : -INFINITY);
 #pragma unroll
         for (int db = 0; db < D / 32; ++db)
 #pragma unroll
             for (int e4 = 0; e4 < 4; ++e4)
-                *reinterpret_cast<bf16x4 *>(op + db * 32 + 8 * e4 + 4 * hh) =
-                    pack4(o[db][4 * e4] * inv, o[db][4 * e4 + 1] * inv, o[db][4 * e4 + 2] * inv, o[db][4 * e4 + 3] * inv);
-        if (hh == 0) lse[(int64_t)bh * s.l_s + r] = lse_nat;
+                put(db * 4 + e4, f32x4{o[db][4 * e4] * inv, o[db][4 * e4 + 1] * inv, o[db][4 * e4 + 2] * inv, o[db][4 * e4 + 3] * inv});
     } else {
-        // a split's normalised output travels to the merge kernel in fp32: rounded to bf16 once, there
-        const int64_t row = ((int64_t)split * bhs + bh) * s.l_s + r;
-        float *op = o_part + row * D;
+        // The groups' results meet in LDS, where the tiles were: group g adds up its share of the columns, in group order,
+        // weighted to the rows' maximum over all groups.
+        auto hand = [&](int g, int u) { return reinterpret_cast<f32x4 *>(smem + ((g * RB + wave) * C::UNITS + u) * 1024 + lane * 16); };
+        auto hand_ml = [&](int g) { return reinterpret_cast<float *>(smem + C::HAND_ML + (g * RB + wave) * 512 + lane * 8); };
+        __syncthreads();
 #pragma unroll
         for (int db = 0; db < D / 32; ++db)
 #pragma unroll
             for (int e4 = 0; e4 < 4; ++e4)
-                *reinterpret_cast<f32x4 *>(op + db * 32 + 8 * e4 + 4 * hh) =
-                    f32x4{o[db][4 * e4] * inv, o[db][4 * e4 + 1] * inv, o[db][4 * e4 + 2] * inv, o[db][4 * e4 + 3] * inv};
-        if (hh == 0) lse_part[row] = lse_nat;
+                *hand(group, db * 4 + e4) = f32x4{o[db][4 * e4], o[db][4 * e4 + 1], o[db][4 * e4 + 2], o[db][4 * e4 + 3]};
+        hand_ml(group)[0] = m;
+        hand_ml(group)[1] = l_own;
+        __syncthreads();
+        if (!row_ok) return;
+        float mg[KG], m_all = -INFINITY, l_all = 0.f;
+#pragma unroll
+        for (int g = 0; g < KG; ++g) { mg[g] = hand_ml(g)[0]; m_all = fmaxf(m_all, mg[g]); }
+#pragma unroll
+        for (int g = 0; g < KG; ++g) {
+            mg[g] = mg[g] == -INFINITY ? 0.f : fast_exp2(mg[g] - m_all);       // from here on: its weight
+            l_all += mg[g] * hand_ml(g)[1];
+        }
+        const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
+        if (group == 0 && hh == 0) put_lse(l_all > 0.f ? (m_all + log2f(l_all)) * kLn2 : -INFINITY);
+        constexpr int PER = C::UNITS / KG;
+        static_assert(C::UNITS % KG == 0, "");
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int u = group * PER + i;
+            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int g = 0; g < KG; ++g) {
+                const f32x4 v = *hand(g, u);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[e] += mg[g] * v[e];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] *= inv;
+            put(u, sum);
+        }
     }
 }
 
-int fwd_bf16_rows_per_workgroup(int d) { return d == 64 ? FwdBf16Cfg<64>::BR : FwdBf16Cfg<128>::BR; }
+int fwd_bf16_rows_per_workgroup(int d) { return d == 64 ? 128 : 256; }
 
-template <int D>
+template <int D, int RB, int KG>
 static hipError_t launch_fwd_main(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                   const bf16_t *v, bf16_t *out, float *lse, const Workspace &ws, int n_splits, hipStream_t st)
 {
-    using C = FwdBf16Cfg<D>;
+    using C = FwdBf16Cfg<D, RB, KG>;
     const int n_q_tiles = (s.l_s + C::BR - 1) / C::BR;
     dim3 grid((unsigned)xcd_grid(s.B * s.H, n_q_tiles * n_splits));
     TimedLaunch tl(K_FWD_BF16, st);
-    if (drop.thr != 0)
-        hipLaunchKernelGGL((fwd_bf16_kernel<D, true>), grid, dim3(C::NT), 0, st, s, drop, q, k, v, out, lse, ws.o_part,
-                           ws.lse_part, n_splits, n_q_tiles);
-    else
-        hipLaunchKernelGGL((fwd_bf16_kernel<D, false>), grid, dim3(C::NT), 0, st, s, drop, q, k, v, out, lse, ws.o_part,
-                           ws.lse_part, n_splits, n_q_tiles);
+    const auto kernel = drop.thr != 0 ? fwd_bf16_kernel<D, true, RB, KG> : fwd_bf16_kernel<D, false, RB, KG>;
+    hipLaunchKernelGGL(kernel, grid, dim3(C::NT), 0, st, s, drop, q, k, v, out, lse, ws.o_part, ws.lse_part, n_splits, n_q_tiles);
     return hipGetLastError();
 }
 
 hipError_t launch_fwd_bf16_main(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
-                                const bf16_t *v, bf16_t *out, float *lse, const Workspace &ws, int n_splits, hipStream_t st)
+                                const bf16_t *v, bf16_t *out, float *lse, const Workspace &ws, const FwdPlan &plan, hipStream_t st)
 {
-    if (s.d == 64) return launch_fwd_main<64>(s, drop, q, k, v, out, lse, ws, n_splits, st);
-    return launch_fwd_main<128>(s, drop, q, k, v, out, lse, ws, n_splits, st);
+    if (s.d == 64) {
+        switch (plan.form) {
+        case FWD_2x2: return launch_fwd_main<64, 2, 2>(s, drop, q, k, v, out, lse, ws, plan.splits, st);
+        case FWD_4x2: return launch_fwd_main<64, 4, 2>(s, drop, q, k, v, out, lse, ws, plan.splits, st);
+        default: return launch_fwd_main<64, 4, 1>(s, drop, q, k, v, out, lse, ws, plan.splits, st);
+        }
+    }
+    if (plan.form == FWD_4x2) return launch_fwd_main<128, 4, 2>(s, drop, q, k, v, out, lse, ws, plan.splits, st);
+    return launch_fwd_main<128, 8, 1>(s, drop, q, k, v, out, lse, ws, plan.splits, st);
 }
 
 } // namespace lss

@@ -34,7 +34,12 @@ int choose_splits(int l_s, int l_x, int B, int H, int rows_per_wg);
 // Forward: the largest split count the workspace is sized for (shape-only), and the count a launch
 // uses for the `kv_tiles` 64-key tiles its query tiles actually see (never above the former).
 int max_fwd_splits(int l_s, int l_x, int B, int H, int rows_per_wg);
-int pick_fwd_splits(int l_s, int B, int H, int rows_per_wg, int64_t kv_tiles, int max_splits, int elem_bytes, int d);
+int pick_fwd_splits(int l_s, int B, int H, int rows_per_wg, int64_t kv_tiles, int max_splits, int d);     // float kernels
+// bf16 forward: the workgroup's form -- blocks of 32 query rows x groups of wavefronts that have a part of the keys
+// each -- and the key splits.
+enum FwdForm { FWD_4x1, FWD_2x2, FWD_4x2, FWD_8x1 };
+struct FwdPlan { FwdForm form; int splits; };
+FwdPlan pick_fwd_plan(const SegShape &s, int max_splits);
 int fwd_rows_per_wg(int elem_bytes, int d);     // query rows per workgroup of the forward kernel
 int dq_rows_per_wg(int elem_bytes, int d);      // ... and of the dQ kernel
 
@@ -72,7 +77,7 @@ hipError_t launch_bwd(const SegShape &s, const DropArgs &drop, const T *q, const
 // tuned bf16 kernels (lss_fwd_bf16.hip)
 int fwd_bf16_rows_per_workgroup(int d);
 hipError_t launch_fwd_bf16_main(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
-                                const bf16_t *v, bf16_t *out, float *lse, const Workspace &ws, int n_splits, hipStream_t st);
+                                const bf16_t *v, bf16_t *out, float *lse, const Workspace &ws, const FwdPlan &plan, hipStream_t st);
 
 // single-precision kernels (lss_f32.hip); ws.D holds rowsum(dO * out)
 int f32_rows_per_workgroup();
