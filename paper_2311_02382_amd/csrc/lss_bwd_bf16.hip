@@ -27,8 +27,11 @@ struct DqBf16Cfg {
     static constexpr int NU = D / 16;                   // operand steps of the S/dP products; same for dQ
     using Tile = DirectTile<D, BC>;
     static constexpr int OFF_V = Tile::BYTES, SLOT = 2 * Tile::BYTES;   // one ring slot: K tile, V tile
+    // (dropout: behind the ring, the column keys of the last four tiles issued, 64 each)
+    static constexpr int group_lds(bool drop) { return RING * SLOT + (drop ? 4 * BC * 4 : 0); }
 };
 
+// KG: groups of wavefronts in the workgroup, see bwd_main_bf16_kernel.
 // Transposed formulation: S^T = K Q^T and dP^T = V dO^T put the wavefront's 32 queries on the lanes
 // (lse and D are per-lane scalars), and dS^T comes out of the accumulators in the layout the
 // dQ^T += K^T dS^T product wants as its second operand.  The keys are walked in blocks of 32 (two
@@ -41,7 +44,7 @@ struct DqBf16Cfg {
 // -D = -rowsum(dO * out) of the wavefront's rows comes from the preprocess kernel (`Dn`), or is computed here (OWN).
 // DROP: dropout on the weights (mask M = keep / (1 - p), decided by drop_keep() of (seed,
 // batch*head, global row, key)): dS = P * (M dP - D).
-template <int D, bool DROP, bool OWN>
+template <int D, bool DROP, bool OWN, int KG>
 __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const DropArgs &dr, const bf16_t *__restrict__ q,
                                             const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
                                             const bf16_t *__restrict__ out, const bf16_t *__restrict__ dO, const float *__restrict__ lse,
@@ -54,7 +57,9 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
     constexpr int NU = C::NU;
 
     const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int all_waves = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = KG > 1 ? all_waves / C::WAVES : 0, wave = KG > 1 ? all_waves % C::WAVES : all_waves;     // wave: within the group
+    char *const ring = smem + group * C::group_lds(DROP);
     const int b = bh / s.H, h = bh % s.H;
     // query tiles are dispatched last-first: under the causal mask the last tiles see the most
     // keys, and starting the longest workgroups first shortens the tail of the launch
@@ -66,8 +71,10 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
     const int kv_end = s.causal ? (int)min<int64_t>(s.l_x, s.s0 + r_last + 1) : s.l_x;
     const int n_tiles = (kv_end + C::BC - 1) / C::BC;
     const int per = (n_tiles + n_splits - 1) / n_splits;
-    const int t_begin = split * per, t_end = min(n_tiles, t_begin + per);
-    const int T = max(t_end - t_begin, 0);
+    const int s_begin = split * per, s_tiles = max(min(n_tiles, s_begin + per) - s_begin, 0);
+    // this group's tiles; the first group has `iters` of them, the other one fewer or none
+    const int iters = KG > 1 ? (s_tiles + KG - 1) / KG : s_tiles;
+    const int t_begin = s_begin + group * iters, T = KG > 1 ? max(min(s_tiles - group * iters, iters), 0) : s_tiles;
 
     // this lane's query row (column of the S^T tile); rows past the segment re-read its last row
     // (unconditional loads), get lse = +inf, which makes their P and dS exactly 0, and are never stored
@@ -109,7 +116,7 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
 #pragma unroll
     for (int db = 0; db < D / 32; ++db) acc[db] = zero16;
 
-    if (T > 0) {
+    if (s_tiles > 0) {
         const bf16_t *kbase = k + (int64_t)b * s.l_x * ld + (int64_t)h * D;
         const bf16_t *vbase = v + (int64_t)b * s.l_x * ld + (int64_t)h * D;
 
@@ -118,7 +125,7 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
         // a small ring behind the tiles -- published by the same barrier as the tile
         uint32_t drop_rk = 0u, drop_cs = 0u;
         if (DROP) { drop_rk = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + r)); drop_cs = drop_col_seed(dr.seed_hi); }
-        char *const ck_ring = smem + C::RING * C::SLOT;
+        char *const ck_ring = ring + C::RING * C::SLOT;
 
         // ---- tile loads, by all four wavefronts.  Branch-free on purpose: a branch inside a pipeline step
         // splits it into basic blocks, and the vector work that was meant to sit between the step's
@@ -140,7 +147,7 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
 #pragma unroll
             for (int i = 0; i < Tile::NI; ++i) off[i] = offF[i] + (offD[i] & part);
             static_assert(C::OFF_V == Tile::BYTES, "V tile follows K tile");
-            Tile::issue_pair(tile_ptr(kbase, t, tile_bytes), tile_ptr(vbase, t, tile_bytes), off, off, smem + slot * C::SLOT, wave);
+            Tile::issue_pair(tile_ptr(kbase, t, tile_bytes), tile_ptr(vbase, t, tile_bytes), off, off, ring + slot * C::SLOT, wave);
             if (DROP && wave == 0)
                 reinterpret_cast<uint32_t *>(ck_ring)[(t & 3) * C::BC + lane] = drop_col_key(drop_cs, (uint32_t)(j0 + lane));
         };
@@ -268,7 +275,7 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
         using std::false_type;
 
         // ---- pipeline.  Block g = keys (t_begin + g/2) * 64 + (g%2) * 32 ..; tile t = blocks 2t, 2t+1.
-        issue_tile(t_begin, 0);
+        if (T > 0) issue_tile(t_begin, 0);
         if (T > 1) issue_tile(t_begin + 1, 1);
         wait_vmem_all();
         __syncthreads();
@@ -284,68 +291,91 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
                 issue_ahead(t, prv);
                 cur = cur == C::RING - 1 ? 0 : cur + 1;
             }
-            wait_vmem_all();                            // the last, redundant prefetches must land before the workgroup's LDS is given away
-            return;
-        }
+        } else if (KG == 1 || T > 0) {
+            f32x16 sc0, dp0, sc1, dp1;                      // even / odd blocks
+            Frag<bf16_t> df0[2], df1[2];
+            // step -1: A(0) alone.  The first loop step has no C(-1): it multiplies zeros with tile 0 instead.
+            load_a(ring, 0, 0, ak[0], av[0]);
+            auto nothing = [] {};
+            step(true_type{}, false_type{}, false_type{}, ring, 0, sc0, dp0, sc1, dp1, 0, df0, ring, 0, df1, ring, 1, ring, 1, nothing);
+    #pragma unroll
+            for (int half = 0; half < 2; ++half)
+    #pragma unroll
+                for (int e = 0; e < 8; ++e) df1[half].v[e] = (bf16_t)0.f;
 
-        f32x16 sc0, dp0, sc1, dp1;                      // even / odd blocks
-        Frag<bf16_t> df0[2], df1[2];
-        // step -1: A(0) alone.  The first loop step has no C(-1): it multiplies zeros with tile 0 instead.
-        load_a(smem, 0, 0, ak[0], av[0]);
-        auto nothing = [] {};
-        step(true_type{}, false_type{}, false_type{}, smem, 0, sc0, dp0, sc1, dp1, 0, df0, smem, 0, df1, smem, 1, smem, 1, nothing);
-#pragma unroll
-        for (int half = 0; half < 2; ++half)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) df1[half].v[e] = (bf16_t)0.f;
-
-        int cur = 0;                                    // ring slot of tile t
-        for (int t = 0; t < T; ++t) {
-            const int nxt = cur == C::RING - 1 ? 0 : cur + 1, prv = cur == 0 ? C::RING - 1 : cur - 1;
-            const char *t_cur = smem + cur * C::SLOT, *t_nxt = smem + nxt * C::SLOT, *t_prv = smem + prv * C::SLOT;
-            const char *t_a2 = t + 1 < T ? t_nxt : t_cur;   // tile of A(2t+2), A(2t+3); past the end: any resident tile
-            const int j0 = (t_begin + t) * C::BC;
-            // even step g = 2t: A(2t+1) [tile t, second half], B(2t), C(2t-1) [tile t-1, second half;
-            // for t = 0 tile 0, times zero]
-            // Before its last reads (which may touch tile t+1): tile t+1's loads, issued one iteration
-            // ago, have landed for this wavefront; after the barrier for all, and every wavefront has
-            // requested its last operands from tile t-1, whose slot takes tile t+2.
-            step(true_type{}, true_type{}, true_type{}, t_cur, 1, sc1, dp1, sc0, dp0, j0, df0, t > 0 ? t_prv : t_cur, 1, df1,
-                 t_a2, 0, t_cur, 0, [&] {
-                     wait_vmem_all();
-                     __syncthreads();
-                     issue_ahead(t, prv);
-                 });
-            // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end result unused], B(2t+1),
-            // C(2t) [tile t, first half]
-            step(true_type{}, true_type{}, true_type{}, t_a2, 0, sc0, dp0, sc1, dp1, j0 + 32, df1, t_cur, 0, df0, t_a2, 1, t_cur,
-                 1, nothing);
-            cur = nxt;
+            int cur = 0;                                    // ring slot of tile t
+            for (int t = 0; t < T; ++t) {
+                const int nxt = cur == C::RING - 1 ? 0 : cur + 1, prv = cur == 0 ? C::RING - 1 : cur - 1;
+                const char *t_cur = ring + cur * C::SLOT, *t_nxt = ring + nxt * C::SLOT, *t_prv = ring + prv * C::SLOT;
+                const char *t_a2 = t + 1 < T ? t_nxt : t_cur;   // tile of A(2t+2), A(2t+3); past the end: any resident tile
+                const int j0 = (t_begin + t) * C::BC;
+                // even step g = 2t: A(2t+1) [tile t, second half], B(2t), C(2t-1) [tile t-1, second half;
+                // for t = 0 tile 0, times zero]
+                // Before its last reads (which may touch tile t+1): tile t+1's loads, issued one iteration
+                // ago, have landed for this wavefront; after the barrier for all, and every wavefront has
+                // requested its last operands from tile t-1, whose slot takes tile t+2.
+                step(true_type{}, true_type{}, true_type{}, t_cur, 1, sc1, dp1, sc0, dp0, j0, df0, t > 0 ? t_prv : t_cur, 1, df1,
+                     t_a2, 0, t_cur, 0, [&] {
+                         wait_vmem_all();
+                         __syncthreads();
+                         issue_ahead(t, prv);
+                     });
+                // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end result unused], B(2t+1),
+                // C(2t) [tile t, first half]
+                step(true_type{}, true_type{}, true_type{}, t_a2, 0, sc0, dp0, sc1, dp1, j0 + 32, df1, t_cur, 0, df0, t_a2, 1, t_cur,
+                     1, nothing);
+                cur = nxt;
+            }
+            // step 2T: C(2T-1) [tile T-1, second half] alone
+            {
+                const char *t_last = ring + (cur == 0 ? C::RING - 1 : cur - 1) * C::SLOT;
+                step(false_type{}, false_type{}, true_type{}, ring, 0, sc0, dp0, sc0, dp0, 0, df0, t_last, 1, df1, ring, 0, t_last,
+                     1, nothing);
+            }
         }
-        // step 2T: C(2T-1) [tile T-1, second half] alone
-        {
-            const char *t_last = smem + (cur == 0 ? C::RING - 1 : cur - 1) * C::SLOT;
-            step(false_type{}, false_type{}, true_type{}, smem, 0, sc0, dp0, sc0, dp0, 0, df0, t_last, 1, df1, smem, 0, t_last,
-                 1, nothing);
-        }
+        if (KG > 1)
+            for (int t = T; t < iters; ++t) __syncthreads();           // the barriers of the group that has more tiles
         wait_vmem_all();                                // the last, redundant prefetches must land before the workgroup's LDS is given away
     }
 
+    if constexpr (KG > 1) {
+        // The groups' sums meet in LDS, where the tiles were: each adds up half the columns, in group order.
+        static_assert(KG == 2 && D == 64, "");
+        auto hand = [&](int e4) { return reinterpret_cast<f32x4 *>(smem + ((group * C::WAVES + wave) * 4 + e4) * 1024 + lane * 16); };
+        auto other = [&](int e4) { return reinterpret_cast<f32x4 *>(smem + (((group ^ 1) * C::WAVES + wave) * 4 + e4) * 1024 + lane * 16); };
+        __syncthreads();
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {
+            f32x4 v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = group == 0 ? acc[1][4 * e4 + i] : acc[0][4 * e4 + i];
+            *hand(e4) = v;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {
+            const f32x4 v = *other(e4);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[0][4 * e4 + i] = (group == 0 ? acc[0][4 * e4 + i] : acc[1][4 * e4 + i]) + v[i];
+        }
+    }
     if (!row_ok) return;
     const float scale = 1.f / sqrtf((float)D);
+    constexpr int DB = KG > 1 ? 1 : D / 32;             // (two groups: column block `group`, in acc[0])
+    const int first_col = KG > 1 ? 32 * group : 0;
     if (n_splits == 1) {
-        bf16_t *dst0 = dq + ((int64_t)b * s.l_s + r) * ld + (int64_t)h * D;
+        bf16_t *dst0 = dq + ((int64_t)b * s.l_s + r) * ld + (int64_t)h * D + first_col;
 #pragma unroll
-        for (int db = 0; db < D / 32; ++db)
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int e4 = 0; e4 < 4; ++e4)
                 *reinterpret_cast<bf16x4 *>(dst0 + db * 32 + 8 * e4 + 4 * hh) =
                     pack4(acc[db][4 * e4] * scale, acc[db][4 * e4 + 1] * scale, acc[db][4 * e4 + 2] * scale,
                           acc[db][4 * e4 + 3] * scale);
     } else {
-        float *dst0 = dq_part + (int64_t)split * s.B * s.l_s * ld + ((int64_t)b * s.l_s + r) * ld + (int64_t)h * D;
+        float *dst0 = dq_part + (int64_t)split * s.B * s.l_s * ld + ((int64_t)b * s.l_s + r) * ld + (int64_t)h * D + first_col;
 #pragma unroll
-        for (int db = 0; db < D / 32; ++db)
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int e4 = 0; e4 < 4; ++e4) {
                 f32x4 val;
@@ -398,8 +428,8 @@ struct DkvBf16Cfg {
     // (with dropout also the 64 rows' generator keys)
     static constexpr int OFF_G = Tile::BYTES, OFF_L = 2 * Tile::BYTES, OFF_D = OFF_L + BQ * 4, OFF_R = OFF_D + BQ * 4;
     static constexpr int SLOT = OFF_R + (DROP ? BQ * 4 : 0);
-    // OWN workgroups: the start values (and keys) of all rows behind the ring, up to OWN_MAX rows and one more tile
-    static constexpr int OWN_MAX = 512, OWN_ROWS = OWN_MAX + BQ, OFF_OWN = RING * SLOT, OWN_BYTES = OWN_ROWS * 4 * (DROP ? 3 : 2);
+    // OWN workgroups: the start values (and keys) of all rows behind the rings, up to OWN_MAX rows and one more tile
+    static constexpr int OWN_MAX = 512, OWN_ROWS = OWN_MAX + BQ, OWN_BYTES = OWN_ROWS * 4 * (DROP ? 3 : 2);
 };
 
 // -D = -rowsum(dO * out) of a row from its parts: D/8 consecutive lanes hold one 16-byte chunk each.
@@ -413,13 +443,13 @@ __device__ __forceinline__ float neg_row_dot(const Frag<bf16_t> &g, const Frag<b
     for (int sh = 1; sh < D / 8; sh <<= 1) dsum += __shfl_xor(dsum, sh);
     return -dsum;
 }
-// The same for `n` rows that lie `ld` elements apart, by a workgroup of 256: put(row, -D, lse) on one lane per row.  The
+// The same for `n` rows that lie `ld` elements apart, by a workgroup of NT: put(row, -D, lse) on one lane per row.  The
 // loads of 128 (d = 64) or 64 rows are in flight at once.
-template <int D, typename Put>
+template <int D, int NT = 256, typename Put>
 __device__ __forceinline__ void neg_row_dots(const bf16_t *__restrict__ out, const bf16_t *__restrict__ dO,
                                              const float *__restrict__ lse, int64_t ld, int n, int tid, Put &&put)
 {
-    constexpr int CPR = D / 8, STEP = 256 / CPR, U = 4;
+    constexpr int CPR = D / 8, STEP = NT / CPR, U = 4;
     const int cpos = tid % CPR;
     for (int i0 = tid / CPR; i0 - tid / CPR < n; i0 += U * STEP) {
         Frag<bf16_t> g[U], o[U];
@@ -457,7 +487,7 @@ __device__ __forceinline__ void neg_row_dots(const bf16_t *__restrict__ out, con
 //
 // OWN: the workgroup computes the start values (and keys) of its rows itself, into LDS, while its first
 // tiles are on their way, instead of finding them in memory (bwd_own_values).
-template <int D, bool DROP, bool OWN>
+template <int D, bool DROP, bool OWN, int KG>
 __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, const DropArgs &dr, const bf16_t *__restrict__ q,
                                              const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
                                              const bf16_t *__restrict__ out, const bf16_t *__restrict__ dO,
@@ -470,7 +500,9 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     constexpr int NU = C::NU;
 
     const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int all_waves = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = KG > 1 ? all_waves / C::WAVES : 0, wave = KG > 1 ? all_waves % C::WAVES : all_waves;     // wave: within the group
+    char *const ring = smem + group * (C::RING * C::SLOT), *const own_values = smem + KG * (C::RING * C::SLOT);
     const int b = bh / s.H, h = bh % s.H;
     const int j0 = key_tile * C::BKV;
     const int jw0 = j0 + wave * C::KW;                  // first key of this wavefront
@@ -491,7 +523,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         if (s.skip_tail) return;
         constexpr int F4 = D / 4;                       // float4 per (row, head)
         const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-        for (int i = tid; i < C::BKV * F4; i += C::NT) {
+        for (int i = tid; i < C::BKV * F4; i += KG * C::NT) {
             const int row = j0 + i / F4, c4 = (i % F4) * 4;
             if (row < s.l_x) {
                 *reinterpret_cast<f32x4 *>(dk_part + kv_base + (int64_t)row * ld + c4) = z;
@@ -562,7 +594,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
 #pragma unroll
         for (int i = 0; i < Tile::NI; ++i) off[i] = offF[i] + (offD[i] & part);
         static_assert(C::OFF_G == Tile::BYTES, "dO tile follows Q tile");
-        char *dst = smem + slot * C::SLOT;
+        char *dst = ring + slot * C::SLOT;
         Tile::issue_pair(tile_ptr(qbase, tq, tile_bytes), tile_ptr(gbase, tq, tile_bytes), off, off, dst, wave);
         if constexpr (!OWN) {
             const uint32_t ro = (uint32_t)min(lane, s.l_s - rq0 - 1) * 4u;
@@ -597,7 +629,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     constexpr int SV_D = OWN ? C::OWN_ROWS * 4 : C::OFF_D - C::OFF_L, SV_R = 2 * SV_D;
     static_assert(OWN || SV_R == C::OFF_R - C::OFF_L, "start values lie in one row of arrays");
     auto start_values = [&](const char *tile, int qb, int row) __attribute__((always_inline)) {
-        return (OWN ? smem + C::OFF_OWN + row * 4 : tile + C::OFF_L + qb * 32 * 4) + 4 * hh * 4;
+        return (OWN ? own_values + row * 4 : tile + C::OFF_L + qb * 32 * 4) + 4 * hh * 4;
     };
     auto init_load = [&](const char *sv, int g0, int g1, f32x16 &sc, f32x16 &dp) __attribute__((always_inline)) {
 #pragma unroll
@@ -734,20 +766,23 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     using std::false_type;
 
     // ---- pipeline.  Block g of this workgroup = rows rq_begin + 32 g ..; tile t = blocks 2t, 2t+1.
-    const int T = (s.l_s - rq_begin + C::BQ - 1) / C::BQ, tq_begin = rq_begin / C::BQ;
+    // (two groups: the first has `iters` tiles, the other one fewer or none; row_base: of the group's first row, from rq_begin)
+    const int all_tiles = (s.l_s - rq_begin + C::BQ - 1) / C::BQ, iters = (all_tiles + KG - 1) / KG;
+    const int T = KG > 1 ? min(all_tiles - group * iters, iters) : all_tiles, row_base = group * iters * C::BQ;
+    const int tq_begin = (rq_begin + row_base) / C::BQ;
     // the loop's prefetch: tile t + 2, or once more the last tile into a slot nobody reads any more
     auto issue_ahead = [&](int t, int slot) { issue_tile(tq_begin + min(t + 2, T - 1), slot); };
-    issue_tile(tq_begin, 0);
+    if (KG == 1 || T > 0) issue_tile(tq_begin, 0);
     if (T > 1) issue_tile(tq_begin + 1, 1);
     if constexpr (OWN) {
-        float *const own = reinterpret_cast<float *>(smem + C::OFF_OWN);
+        float *const own = reinterpret_cast<float *>(own_values);
         const int n = s.l_s - rq_begin;
-        for (int i = n + tid; i < (T + 1) * C::BQ; i += C::NT) {    // rows past the segment, whose weights are 0: any finite values
+        for (int i = n + tid; i < (all_tiles + 1) * C::BQ; i += KG * C::NT) {    // rows past the segment, whose weights are 0: any finite values
             own[i] = own[C::OWN_ROWS + i] = 0.f;
             if constexpr (DROP) own[2 * C::OWN_ROWS + i] = 0.f;
         }
         const int64_t first = ((int64_t)b * s.l_s + rq_begin) * ld + (int64_t)h * D;
-        neg_row_dots<D>(out + first, dO + first, lse + (int64_t)bh * s.l_s + rq_begin, ld, n, tid, [&](int i, float nd, float l) {
+        neg_row_dots<D, KG * C::NT>(out + first, dO + first, lse + (int64_t)bh * s.l_s + rq_begin, ld, n, tid, [&](int i, float nd, float l) {
             own[i] = -l * sqrt_d;
             own[C::OWN_ROWS + i] = nd;
             if constexpr (DROP)
@@ -757,59 +792,87 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     wait_vmem_all();
     __syncthreads();
 
-    f32x16 sc0, dp0, sc1, dp1;                          // even / odd blocks
-    Frag<bf16_t> pf0[2], df0[2], pf1[2], df1[2];
-    // step -1: A(0) alone (leaves the first loop step's C operands in cq[0], cg[0]).  That step has
-    // no C(-1): it multiplies zeros with tile 0 instead.
-    auto nothing = [] {};
-    step(true_type{}, false_type{}, false_type{}, false_type{}, smem, 0, rq_begin, sc0, dp0, smem, sc1, dp1, pf0, df0, smem, 0,
-         pf1, df1, smem, 1, 32, smem, 1, nothing);
+    if (KG == 1 || T > 0) {
+        f32x16 sc0, dp0, sc1, dp1;                          // even / odd blocks
+        Frag<bf16_t> pf0[2], df0[2], pf1[2], df1[2];
+        // step -1: A(0) alone (leaves the first loop step's C operands in cq[0], cg[0]).  That step has
+        // no C(-1): it multiplies zeros with tile 0 instead.
+        auto nothing = [] {};
+        step(true_type{}, false_type{}, false_type{}, false_type{}, ring, 0, rq_begin + row_base, sc0, dp0, ring, sc1, dp1, pf0, df0, ring, 0,
+             pf1, df1, ring, 1, row_base + 32, ring, 1, nothing);
 #pragma unroll
-    for (int half = 0; half < 2; ++half)
+        for (int half = 0; half < 2; ++half)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) { pf1[half].v[e] = (bf16_t)0.f; df1[half].v[e] = (bf16_t)0.f; }
+            for (int e = 0; e < 8; ++e) { pf1[half].v[e] = (bf16_t)0.f; df1[half].v[e] = (bf16_t)0.f; }
 
-    int cur = 0;                                        // ring slot of tile t
-    for (int t = 0; t < T; ++t) {
-        const int nxt = cur == C::RING - 1 ? 0 : cur + 1, prv = cur == 0 ? C::RING - 1 : cur - 1;
-        const char *t_cur = smem + cur * C::SLOT, *t_nxt = smem + nxt * C::SLOT, *t_prv = smem + prv * C::SLOT;
-        const char *t_a2 = t + 1 < T ? t_nxt : t_cur;   // tile of A(2t+2) and A(2t+3); past the end: any resident tile
-        const int r0 = rq_begin + t * C::BQ;
-        // even step g = 2t: A(2t+1) [tile t, second half], B(2t), C(2t-1) [tile t-1, second half;
-        // for t = 0 tile 0, times zero]
-        // Before its last requests (which may touch tile t+1): tile t+1's loads, issued one iteration
-        // ago, have landed for this wavefront; after the barrier for all, and every wavefront has
-        // requested its last operands from tile t-1, whose slot takes tile t+2.
-        step(true_type{}, true_type{}, true_type{}, true_type{}, t_cur, 1, r0 + 32, sc1, dp1,
-             start_values(t_cur, 0, t * C::BQ), sc0, dp0, pf0, df0, t > 0 ? t_prv : t_cur, 1, pf1, df1, t_a2, 0, (t + 1) * C::BQ,
-             t_cur, 0, [&] {
-                 wait_vmem_all();
-                 __syncthreads();
-                 issue_ahead(t, prv);
-             });
-        // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end result unused], B(2t+1),
-        // C(2t) [tile t, first half]
-        step(true_type{}, true_type{}, true_type{}, true_type{}, t_a2, 0, r0 + C::BQ, sc0, dp0,
-             start_values(t_cur, 1, t * C::BQ + 32), sc1, dp1, pf1, df1, t_cur, 0, pf0, df0, t_a2, 1, (t + 1) * C::BQ + 32, t_cur, 1,
-             nothing);
-        cur = nxt;
+        int cur = 0;                                        // ring slot of tile t
+        for (int t = 0; t < T; ++t) {
+            const int nxt = cur == C::RING - 1 ? 0 : cur + 1, prv = cur == 0 ? C::RING - 1 : cur - 1;
+            const char *t_cur = ring + cur * C::SLOT, *t_nxt = ring + nxt * C::SLOT, *t_prv = ring + prv * C::SLOT;
+            const char *t_a2 = t + 1 < T ? t_nxt : t_cur;   // tile of A(2t+2) and A(2t+3); past the end: any resident tile
+            const int row = row_base + t * C::BQ, r0 = rq_begin + row;
+            // even step g = 2t: A(2t+1) [tile t, second half], B(2t), C(2t-1) [tile t-1, second half;
+            // for t = 0 tile 0, times zero]
+            // Before its last requests (which may touch tile t+1): tile t+1's loads, issued one iteration
+            // ago, have landed for this wavefront; after the barrier for all, and every wavefront has
+            // requested its last operands from tile t-1, whose slot takes tile t+2.
+            step(true_type{}, true_type{}, true_type{}, true_type{}, t_cur, 1, r0 + 32, sc1, dp1,
+                 start_values(t_cur, 0, row), sc0, dp0, pf0, df0, t > 0 ? t_prv : t_cur, 1, pf1, df1, t_a2, 0, row + C::BQ,
+                 t_cur, 0, [&] {
+                     wait_vmem_all();
+                     __syncthreads();
+                     issue_ahead(t, prv);
+                 });
+            // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end result unused], B(2t+1),
+            // C(2t) [tile t, first half]
+            step(true_type{}, true_type{}, true_type{}, true_type{}, t_a2, 0, r0 + C::BQ, sc0, dp0,
+                 start_values(t_cur, 1, row + 32), sc1, dp1, pf1, df1, t_cur, 0, pf0, df0, t_a2, 1, row + C::BQ + 32, t_cur, 1,
+                 nothing);
+            cur = nxt;
+        }
+        // step 2T: C(2T-1) [tile T-1, second half] alone
+        {
+            const char *t_last = ring + (cur == 0 ? C::RING - 1 : cur - 1) * C::SLOT;
+            step(false_type{}, false_type{}, true_type{}, false_type{}, ring, 0, 0, sc0, dp0, ring, sc0, dp0, pf0, df0, t_last, 1, pf1,
+                 df1, ring, 0, 0, t_last, 1, nothing);
+        }
     }
-    // step 2T: C(2T-1) [tile T-1, second half] alone
-    {
-        const char *t_last = smem + (cur == 0 ? C::RING - 1 : cur - 1) * C::SLOT;
-        step(false_type{}, false_type{}, true_type{}, false_type{}, smem, 0, 0, sc0, dp0, smem, sc0, dp0, pf0, df0, t_last, 1, pf1,
-             df1, smem, 0, 0, t_last, 1, nothing);
-    }
+    if (KG > 1)
+        for (int t = max(T, 0); t < iters; ++t) __syncthreads();       // the barriers of the group that has more tiles
 
     // the ring is free once every wavefront has made its last reads and the last, redundant prefetches have landed
     wait_vmem_all();
     __syncthreads();
     {
-        char *buf = smem + wave * (32 * D * 4);
+        // (a buffer per wavefront for its finished tile, see store_key_rows)
+        char *buf = smem + all_waves * (32 * D * 4);
         const int64_t off = kv_base + (int64_t)jw0 * ld;
         const int rows_ok = min(s.l_x - jw0, C::KW);
-        store_key_rows<D>(buf, dk, 1.f / sqrt_d, dk_part + off, ld, rows_ok, lane);
-        store_key_rows<D>(buf, dv, 1.f, dv_part + off, ld, rows_ok, lane);
+        if constexpr (KG == 1) {
+            store_key_rows<D>(buf, dk, 1.f / sqrt_d, dk_part + off, ld, rows_ok, lane);
+            store_key_rows<D>(buf, dv, 1.f, dv_part + off, ld, rows_ok, lane);
+        } else {
+            // The groups' sums meet in LDS: the first finishes dV, the second dK, adding in group order.  What a wavefront
+            // reads was written for it alone, into the buffer that is its own from then on.
+            static_assert(KG == 2 && D == 64, "");
+            char *const theirs = smem + (all_waves ^ C::WAVES) * (32 * D * 4);
+            f32x16 sum[D / 32];
+#pragma unroll
+            for (int u = 0; u < D / 8; ++u) {
+                f32x4 v;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = group == 0 ? dk[u / 4][u % 4 * 4 + i] : dv[u / 4][u % 4 * 4 + i];
+                *reinterpret_cast<f32x4 *>(theirs + u * 1024 + lane * 16) = v;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < D / 8; ++u) {
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(buf + u * 1024 + lane * 16);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sum[u / 4][u % 4 * 4 + i] = (group == 0 ? dv[u / 4][u % 4 * 4 + i] : dk[u / 4][u % 4 * 4 + i]) + v[i];
+            }
+            store_key_rows<D>(buf, sum, group == 0 ? 1.f : 1.f / sqrt_d, (group == 0 ? dv_part : dk_part) + off, ld, rows_ok, lane);
+        }
     }
 }
 
@@ -1345,8 +1408,11 @@ __global__ __launch_bounds__(256) void bwd_prep_bf16_kernel(SegShape s, DropArgs
 // SKINNY: segments of at most 64 rows that do not take the one-pass kernel, whose dK/dV workgroups take kSkinnyTilesPerWg key tiles each
 // (n_key_tiles then counts those groups).
 // OWN: no preprocess kernel ran, every workgroup computes what it needs of D itself (bwd_own_values).
-template <int D, bool DROP, bool OWN, bool SKINNY = false>
-__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_main_bf16_kernel(
+// KG = 2: a workgroup is two groups of four wavefronts, with tiles of their own in LDS, that walk half the key tiles (dQ) or query
+// tiles (dK/dV) each and add their sums up in LDS, in group order.  As many wavefronts per compute unit as two workgroups
+// of one group, each with half the walk: for launches that leave compute units idle or wait for their longest walk (pick_bwd_plan).
+template <int D, bool DROP, bool OWN, bool SKINNY = false, int KG = 1>
+__global__ __launch_bounds__(256 * KG, D == 64 ? 2 : 1) void bwd_main_bf16_kernel(
     SegShape s, DropArgs dr, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
     const bf16_t *__restrict__ out, const bf16_t *__restrict__ dO, const float *__restrict__ lse,
     const float *__restrict__ Ls, const float *__restrict__ Dn, const uint32_t *__restrict__ row_key, bf16_t *__restrict__ dq,
@@ -1354,9 +1420,8 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_main_bf16_kernel(
     int n_key_tiles)
 {
     using DkvC = DkvBf16Cfg<D, DROP>;
-    // (dropout: the dQ workgroups keep a ring of column keys, 4 x 64, behind their tiles)
-    constexpr int SMEM_DQ = DqBf16Cfg<D>::RING * DqBf16Cfg<D>::SLOT + (DROP ? 4 * DqBf16Cfg<D>::BC * 4 : 0);
-    constexpr int SMEM_DKV = DkvC::RING * DkvC::SLOT + (OWN && !SKINNY ? DkvC::OWN_BYTES : 0);
+    constexpr int SMEM_DQ = KG * DqBf16Cfg<D>::group_lds(DROP);
+    constexpr int SMEM_DKV = KG * DkvC::RING * DkvC::SLOT + (OWN && !SKINNY ? DkvC::OWN_BYTES : 0);
     constexpr int SMEM = SMEM_DQ > SMEM_DKV ? SMEM_DQ : SMEM_DKV;
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
     const int bhs = s.B * s.H;
@@ -1365,10 +1430,10 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_main_bf16_kernel(
     if (id >= n_dq) {
         if (!xcd_item(id - n_dq, bhs, n_key_tiles, s.causal, bh, inner)) return;
         if constexpr (SKINNY) bwd_dkv_skinny_body<D>(smem, s, q, k, v, out, dO, lse, dk_part, dv_part, bh, inner);
-        else bwd_dkv_body<D, DROP, OWN>(smem, s, dr, q, k, v, out, dO, lse, Ls, Dn, row_key, dk_part, dv_part, bh, inner);
+        else bwd_dkv_body<D, DROP, OWN, KG>(smem, s, dr, q, k, v, out, dO, lse, Ls, Dn, row_key, dk_part, dv_part, bh, inner);
     } else {
         if (!xcd_item(id, bhs, n_q_tiles * n_splits, s.causal && s.s0 < s.l_s, bh, inner)) return;
-        bwd_dq_body<D, DROP, OWN>(smem, s, dr, q, k, v, out, dO, lse, Dn, dq, dq_part, n_splits, inner % n_q_tiles, n_q_tiles, bh,
+        bwd_dq_body<D, DROP, OWN, KG>(smem, s, dr, q, k, v, out, dO, lse, Dn, dq, dq_part, n_splits, inner % n_q_tiles, n_q_tiles, bh,
                                   inner / n_q_tiles);
     }
 }
@@ -1381,7 +1446,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_main_bf16_kernel(
 // 4 heads of 256 queries against 512 keys: backward 14.4 us with the preprocess kernel, 12.3 without; 10 x 4 heads of 67
 // against 47,600: 450 and 469.
 template <int D>
-static bool bwd_own_values(const SegShape &s, int n_splits)
+static bool bwd_own_values(const SegShape &s, int n_splits, int groups)
 {
     if (s.l_s <= kSkinnyRows) return true;      // one tile: loaded once per workgroup in any case
     if (s.l_s > DkvBf16Cfg<D>::OWN_MAX) return false;
@@ -1389,7 +1454,7 @@ static bool bwd_own_values(const SegShape &s, int n_splits)
     constexpr int kChunkRows = D == 64 ? 128 : 64, kAtOnce = D == 64 ? 512 : 256;
     const int64_t seen = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
     const double own_us = kChunkUs * ((s.l_s + kChunkRows - 1) / kChunkRows);
-    const double walk_us = kRowTileUs * ((s.l_s + 63) / 64), dq_us = kKeyTileUs * (double)((seen + 63) / 64) / n_splits;
+    const double walk_us = kRowTileUs * ((s.l_s + 63) / 64) / groups, dq_us = kKeyTileUs * (double)((seen + 63) / 64) / (n_splits * groups);
     double rounds = (double)((seen + 127) / 128 * s.B * s.H) / kAtOnce;
     if (rounds < 1.0 && dq_us < walk_us + own_us) rounds = 1.0;
     return own_us * rounds <= 2.0;
@@ -1413,12 +1478,12 @@ static hipError_t launch_skinny(const SegShape &s, const bf16_t *q, const bf16_t
 template <int D>
 static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                     const bf16_t *v, const bf16_t *out, const float *lse, const bf16_t *dO, bf16_t *dq,
-                                    float *dk_part, float *dv_part, const Workspace &ws, int n_splits,
+                                    float *dk_part, float *dv_part, const Workspace &ws, int n_splits, int groups,
                                     bool one_pass, bool out_first, hipStream_t st)
 {
     hipError_t e;
     const bool with_drop = drop.thr != 0;
-    const bool own = !out_first && bwd_own_values<D>(s, n_splits), skinny = own && !with_drop && s.l_s <= kSkinnyRows;
+    const bool own = !out_first && bwd_own_values<D>(s, n_splits, groups), skinny = own && !with_drop && s.l_s <= kSkinnyRows;
     if constexpr (D == 64) {
         if (one_pass)
             return s.l_s <= 64 ? launch_skinny<2>(s, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, st)
@@ -1437,11 +1502,16 @@ static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, con
     int n_key_tiles = (s.l_x + DkvBf16Cfg<D>::BKV - 1) / DkvBf16Cfg<D>::BKV;
     if (skinny) n_key_tiles = (n_key_tiles + kSkinnyTilesPerWg - 1) / kSkinnyTilesPerWg;      // groups of key tiles
     const int n_dq = xcd_grid(s.B * s.H, n_q_tiles * n_splits), n_dkv = xcd_grid(s.B * s.H, n_key_tiles);
-    const auto kernel = skinny      ? bwd_main_bf16_kernel<D, false, true, true>
-                        : with_drop ? (own ? bwd_main_bf16_kernel<D, true, true> : bwd_main_bf16_kernel<D, true, false>)
-                                    : (own ? bwd_main_bf16_kernel<D, false, true> : bwd_main_bf16_kernel<D, false, false>);
+    auto kernel = skinny      ? bwd_main_bf16_kernel<D, false, true, true>
+                  : with_drop ? (own ? bwd_main_bf16_kernel<D, true, true> : bwd_main_bf16_kernel<D, true, false>)
+                              : (own ? bwd_main_bf16_kernel<D, false, true> : bwd_main_bf16_kernel<D, false, false>);
+    if constexpr (D == 64) {
+        if (groups == 2)
+            kernel = with_drop ? (own ? bwd_main_bf16_kernel<D, true, true, false, 2> : bwd_main_bf16_kernel<D, true, false, false, 2>)
+                               : (own ? bwd_main_bf16_kernel<D, false, true, false, 2> : bwd_main_bf16_kernel<D, false, false, false, 2>);
+    }
     TimedLaunch tl(K_BWD_MAIN_BF16, st);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_dkv + n_dq)), dim3(256), 0, st, s, drop, q, k, v, out, dO, lse, ws.Ls, ws.D, ws.row_key,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_dkv + n_dq)), dim3(256 * groups), 0, st, s, drop, q, k, v, out, dO, lse, ws.Ls, ws.D, ws.row_key,
                        dq, ws.dq_part, dk_part, dv_part, n_splits, n_dq, n_q_tiles, n_key_tiles);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return hipSuccess;
@@ -1451,11 +1521,11 @@ static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, con
 // launch; the caller runs the dQ split merge
 hipError_t launch_bwd_bf16_main(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                 const bf16_t *v, const bf16_t *out, const float *lse, const bf16_t *dO, bf16_t *dq,
-                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, bool one_pass, bool out_first,
+                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, int groups, bool one_pass, bool out_first,
                                 hipStream_t st)
 {
-    if (s.d == 64) return launch_bwd_bf16_d<64>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, one_pass, out_first, st);
-    return launch_bwd_bf16_d<128>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, one_pass, out_first, st);
+    if (s.d == 64) return launch_bwd_bf16_d<64>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, groups, one_pass, out_first, st);
+    return launch_bwd_bf16_d<128>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, groups, one_pass, out_first, st);
 }
 
 } // namespace lss

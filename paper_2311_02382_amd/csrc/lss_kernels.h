@@ -88,11 +88,11 @@ hipError_t launch_bwd_f32_main(const SegShape &s, const DropArgs &drop, const fl
                                int n_splits, hipStream_t st);
 
 // tuned bf16 kernels (lss_bwd_bf16.hip): all gradients in one launch, after one for D = rowsum(dO * out) where that
-// is not part of it; `out_first`: `out` must have been read before any gradient is written
+// is not part of it; `groups` of wavefronts per workgroup (two: d = 64, more than 128 rows); `out_first`: `out` must have been read before any gradient is written
 int dq_bf16_rows_per_workgroup(int d);
 hipError_t launch_bwd_bf16_main(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                 const bf16_t *v, const bf16_t *out, const float *lse, const bf16_t *dO, bf16_t *dq,
-                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, bool one_pass, bool out_first,
+                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, int groups, bool one_pass, bool out_first,
                                 hipStream_t st);
 
 // Whether [a, a + a_bytes) and [b, b + b_bytes) have a byte in common
