@@ -106,7 +106,7 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
         L2 = row_ok ? lv * kLog2e : INFINITY;
     }
     const float c = kLog2e / sqrtf((float)D);
-    // -D in all 16 accumulator slots: third operand of each block's first dP^T instruction
+    // -D in all 16 accumulator slots: third operand of each block's first dP^T instruction (not with dropout, whose mask comes between)
     f32x16 neg_d;
 #pragma unroll
     for (int e = 0; e < 16; ++e) neg_d[e] = -Dr;
@@ -180,10 +180,10 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
         u32x4 ck4;      // dropout: the column keys of four consecutive elements, read when the first is due
         auto b_elems = [&](f32x16 &sc, f32x16 &dp, int jb, int e0, int e1, Frag<bf16_t> (&df)[2]) __attribute__((always_inline)) {
             auto finish = [&](int i) __attribute__((always_inline)) {       // sc[i] holds P by now
-                if (DROP) {     // dp holds dP - D; element i of this lane is key jb + 8 (i / 4) + 4 hh + i % 4
+                if (DROP) {     // dp holds dP (else dP - D); element i of this lane is key jb + 8 (i / 4) + 4 hh + i % 4
                     if ((i & 3) == 0)
                         ck4 = *reinterpret_cast<const u32x4 *>(ck_ring + (((jb >> 6) & 3) * C::BC + (jb & 63) + 8 * (i >> 2) + 4 * hh) * 4);
-                    dp[i] = drop_keep(drop_rk, ck4[i & 3], dr.thr) ? (dp[i] + Dr) * dr.scale - Dr : -Dr;
+                    dp[i] = fmaf(dp[i], drop_keep(drop_rk, ck4[i & 3], dr.thr) ? dr.scale : 0.f, -Dr);
                 }
                 dp[i] = sc[i] * dp[i];
                 if (i & 1) { df[i >> 3].v[(i & 7) - 1] = (bf16_t)dp[i - 1]; df[i >> 3].v[i & 7] = (bf16_t)dp[i]; }
@@ -252,7 +252,7 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
                     b_slot(3 * u);
                     if (HA) sc_a = mma(ak[u & 1], qf[u], u == 0 ? zero16 : sc_a);
                     b_slot(3 * u + 1);
-                    if (HA) dp_a = mma(av[u & 1], gf[u], u == 0 ? neg_d : dp_a);
+                    if (HA) dp_a = mma(av[u & 1], gf[u], u == 0 ? (DROP ? zero16 : neg_d) : dp_a);
                     b_slot(3 * u + 2);
                 } else {
                     // last unit: A first, so that its results are there when the next step's B wants them
@@ -480,10 +480,9 @@ __device__ __forceinline__ void neg_row_dots(const bf16_t *__restrict__ out, con
 // ring of three tiles in LDS; tiles travel global -> LDS directly, a full loop iteration ahead.
 //
 // With dropout (DROP) the weight that enters dV is A = P * M (M = 1 / (1 - p) where the weight is
-// kept, else 0) and dS = A * dP - P * D; the dP accumulator still starts at -D, so with acc = dP - D
-// this is dS = A * acc + (P - A) * (-D).  The keep decision of an element needs its row's key
+// kept, else 0) and dS = P * (M * dP - D); the dP accumulator starts at 0.  The keep decision of an element needs its row's key
 // (precomputed per query row, travelling with the tile like the start values) and this lane's
-// column key; -D of the element's row is read from the tile's start values a second time.
+// column key; -D of the element's row is read from the tile's start values when it is due.
 //
 // OWN: the workgroup computes the start values (and keys) of its rows itself, into LDS, while its first
 // tiles are on their way, instead of finding them in memory (bwd_own_values).
@@ -635,9 +634,13 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
 #pragma unroll
         for (int e4 = g0; e4 < g1; ++e4) {
             const f32x4 l4 = *reinterpret_cast<const f32x4 *>(sv + 8 * e4 * 4);
-            const f32x4 d4 = *reinterpret_cast<const f32x4 *>(sv + SV_D + 8 * e4 * 4);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { sc[4 * e4 + i] = l4[i]; dp[4 * e4 + i] = d4[i]; }
+            for (int i = 0; i < 4; ++i) sc[4 * e4 + i] = l4[i];
+            if constexpr (!DROP) {
+                const f32x4 d4 = *reinterpret_cast<const f32x4 *>(sv + SV_D + 8 * e4 * 4);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dp[4 * e4 + i] = d4[i];
+            }
         }
     };
     // Where the causal diagonal or the end of the segment crosses the block (first row: local row
@@ -671,10 +674,9 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
                     rk4 = *reinterpret_cast<const u32x4 *>(sv_b + SV_R + 8 * (i >> 2) * 4);
                     nd4 = *reinterpret_cast<const f32x4 *>(sv_b + SV_D + 8 * (i >> 2) * 4);
                 }
-                const float p = sc[i];
-                const float a = drop_keep(rk4[i & 3], drop_ck, dr.thr) ? p * dr.scale : 0.f;
-                sc[i] = a;
-                dp[i] = a * dp[i] + (p - a) * nd4[i & 3];
+                const float p = sc[i], m = drop_keep(rk4[i & 3], drop_ck, dr.thr) ? dr.scale : 0.f;
+                sc[i] = p * m;
+                dp[i] = p * fmaf(dp[i], m, nd4[i & 3]);
             } else {
                 dp[i] = sc[i] * dp[i];
             }
@@ -741,7 +743,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
                 __builtin_amdgcn_sched_barrier(0);
                 if (HA) sc_a = mma(aq[u & 1], kf[u], sc_a);
                 b_slot(4 * u + 2);
-                if (HA) dp_a = mma(ag[u & 1], vf[u], dp_a);
+                if (HA) dp_a = mma(ag[u & 1], vf[u], DROP && u == 0 ? f32x16{} : dp_a);
                 b_slot(4 * u + 3);
             } else {
                 // last unit: A first, so that its results are there when the next step's B wants them

@@ -47,7 +47,7 @@ struct FwdBf16Cfg {
     static constexpr float kMaxBlockSum = 256.0f;       // 2^8: largest sum of a lane's weights of one block without a fix-up
 };
 
-// DROP: dropout on the weights (Section 2.2): the weight that multiplies V is dropped or scaled by
+// DROP: dropout on the weights (Section 2.2): the weight that multiplies V is dropped or (the finished sum) scaled by
 // 1 / (1 - p) according to drop_keep() of (seed, batch*head, global row, key); row sum and lse are
 // those of the softmax.
 template <int D, bool DROP, int RB, int KG>
@@ -199,8 +199,8 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
                 if (DROP) {     // element e of this lane is key jb + 8 (e / 4) + 4 hh + e % 4
                     if ((e & 3) == 0)
                         ck4 = *reinterpret_cast<const u32x4 *>(ck_ring + (((jb >> 6) & 3) * C::BC + (jb & 63) + 8 * (e >> 2) + 4 * hh) * 4);
-                    pf[e >> 3].v[e & 7] = (bf16_t)(drop_keep(drop_rk, ck4[e & 3], dr.thr) ? p0 * dr.scale : 0.f);
-                    pf[e >> 3].v[(e & 7) + 1] = (bf16_t)(drop_keep(drop_rk, ck4[(e & 3) + 1], dr.thr) ? p1 * dr.scale : 0.f);
+                    pf[e >> 3].v[e & 7] = (bf16_t)(drop_keep(drop_rk, ck4[e & 3], dr.thr) ? p0 : 0.f);
+                    pf[e >> 3].v[(e & 7) + 1] = (bf16_t)(drop_keep(drop_rk, ck4[(e & 3) + 1], dr.thr) ? p1 : 0.f);
                 } else {
                     pf[e >> 3].v[e & 7] = (bf16_t)p0; pf[e >> 3].v[(e & 7) + 1] = (bf16_t)p1;
                 }
@@ -356,8 +356,9 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
         else lse_part[part_row] = v;
     };
     const float l_own = l + __shfl_xor(l, 32);
+    const float kept = DROP ? dr.scale : 1.f;           // of the kept weights: applied to their sum
     if constexpr (KG == 1) {
-        const float inv = l_own > 0.f ? 1.f / l_own : 0.f;
+        const float inv = l_own > 0.f ? kept / l_own : 0.f;
         if (!row_ok) return;
         if (hh == 0) put_lse(l_own > 0.f ? (m + log2f(l_own)) * kLn2 : -INFINITY);
 #pragma unroll
@@ -388,7 +389,7 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
             mg[g] = mg[g] == -INFINITY ? 0.f : fast_exp2(mg[g] - m_all);       // from here on: its weight
             l_all += mg[g] * hand_ml(g)[1];
         }
-        const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
+        const float inv = l_all > 0.f ? kept / l_all : 0.f;
         if (group == 0 && hh == 0) put_lse(l_all > 0.f ? (m_all + log2f(l_all)) * kLn2 : -INFINITY);
         constexpr int PER = C::UNITS / KG;
         static_assert(C::UNITS % KG == 0, "");
