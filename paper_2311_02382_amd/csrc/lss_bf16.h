@@ -73,13 +73,14 @@ __device__ __forceinline__ void lds_dma_n(const void *g_uniform, const uint32_t 
 // rows of one plain fragment read and the 8 rows x 4 chunks of one transposing read each spread evenly.
 // D = 128 (a row covers all banks once): with r & 7 the 8 rows x 4 chunks of a transposing read fall on 4
 // bank groups per half of the rows (4-way conflicts: 6.4 cycles per instruction measured against 3.2);
-// ((r & 3) << 2) | ((r >> 2) & 3) is a bijection on 16 consecutive rows (plain reads) whose upper two
-// bits take every value twice on 8 consecutive rows (transposing reads).
+// bits 0, 1, 2 and 3 of r in the places 2, 3, 1 and 0: a bijection on 16 consecutive rows (plain reads) whose upper two
+// bits take every value twice on 8 consecutive rows (transposing reads of 64 bytes per row) and whose upper three every
+// value once (of 32 bytes per row, load_frag_tr16_sw).
 template <int D>
 __device__ __forceinline__ int tile_swizzle(int r)
 {
     static_assert(D == 64 || D == 128, "");
-    return D == 64 ? (r & 7) : (((r & 3) << 2) | ((r >> 2) & 3));
+    return D == 64 ? (r & 7) : (((r & 3) << 2) | (((r >> 2) & 1) << 1) | ((r >> 3) & 1));
 }
 
 // [ROWS][D] bf16 tile loaded global -> LDS directly (no registers in between), by WAVES wavefronts.
@@ -163,9 +164,9 @@ struct DirectTile {
 template <int D>
 __device__ __forceinline__ Frag<bf16_t> load_frag_tr_sw(const char *tile, int row0, int lane_off)
 {
-    // the second read's rows lie 8 further down: the same permutation for D = 64, chunk position ^ 2 for D = 128
+    // the second read's rows lie 8 further down: the same permutation for D = 64, chunk position ^ 1 for D = 128
     const char *p = tile + row0 * (D * 2) + lane_off;
-    const char *p8 = tile + row0 * (D * 2) + (D == 64 ? lane_off : (lane_off ^ 32)) + 8 * (D * 2);
+    const char *p8 = tile + row0 * (D * 2) + (D == 64 ? lane_off : (lane_off ^ 16)) + 8 * (D * 2);
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
     const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p8));
     const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -183,6 +184,28 @@ __device__ __forceinline__ int tr_lane_offset_sw(int lane, int db)
     const int grp = lane >> 4, hh = grp >> 1, nh = grp & 1, s = lane & 15;
     const int row = 4 * hh + (s >> 2), chunk = 4 * db + 2 * nh + ((s & 3) >> 1);
     return DirectTile<D, 64>::chunk_offset(row, chunk) + (s & 1) * 8;
+}
+
+// The same for 16 x 16 x 32 instructions: rows [row0, row0 + 32) become the contraction slots, the 16 columns of block `db` the
+// rows of the operand.  Lane s of group g of 16 addresses row 4 g + s / 4 (the second read: 16 further down, the same
+// permutation) and the 8-byte piece s % 4 of the block's 32 bytes, so that slot 4 i + t of group g carries row
+// 16 i + 4 g + t -- what the elements of two C blocks of 16 rows carry (mma16).
+template <int D>
+__device__ __forceinline__ int tr16_lane_offset_sw(int lane, int db)
+{
+    const int g = lane >> 4, s = lane & 15;
+    return DirectTile<D, 64>::chunk_offset(4 * g + (s >> 2), 2 * db + ((s & 3) >> 1)) + (s & 1) * 8;
+}
+template <int D>
+__device__ __forceinline__ Frag<bf16_t> load_frag_tr16_sw(const char *tile, int row0, int lane_off)
+{
+    const char *p = tile + row0 * (D * 2) + lane_off;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 16 * (D * 2)));
+    const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    Frag<bf16_t> f;
+    f.v = __builtin_bit_cast(bf16x8, both);
+    return f;
 }
 
 // Address of tile `tile` of a tensor whose tiles lie `tile_bytes` apart (below 2^32: 64 rows of at most 2^23

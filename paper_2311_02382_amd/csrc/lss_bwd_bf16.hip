@@ -1,9 +1,12 @@
 // Tuned bf16 backward of Eq. 2 (Section 3, Principle 3) for gfx950 (mathematics: lss_bwd.hip): dQ and dK/dV as two kinds of
 // workgroup that share one launch (bwd_main_bf16_kernel); short segments take one pass for all three gradients
 // (bwd_skinny_bf16_kernel).  In the former:
-//   * 32 x 32 blocks, three stages per block (score-side products, vector work, output-side
-//     products), software-pipelined so that the vector work of one block sits between the matrix
-//     instructions of its neighbours;
+//   * 32 x 32 blocks, dK/dV in 16 x 16 x 32 instructions, three stages per block (score-side products, vector
+//     work, output-side products), software-pipelined so that the vector work of one block sits between
+//     the matrix instructions of its neighbours.  Large launches are bound by the chip's power: per product
+//     the 16 x 16 x 32 form takes less of it than 32 x 32 x 16 (register loops on Gaussian bf16: 2,020 - 2,070
+//     against 1,800 - 1,840 TFLOP/s; with the backward's vector work between them 1,669 - 1,708 against 1,597).
+//     With it in dK/dV 8,192 x 8,192 causal passes fell from 1,014 to 994 us, 32,768 keys at d = 128 from 2,535 to 2,505;
 //   * 64-row tiles loaded global -> LDS directly into a ring of three unpadded, swizzled tiles, a
 //     full loop iteration ahead, one barrier per tile;
 //   * row-major LDS tiles read transposed with DS_READ_B64_TR_B16 where the contraction runs over
@@ -415,6 +418,30 @@ __device__ __forceinline__ void store_key_rows(char *buf, const f32x16 (&acc)[D 
     }
 }
 
+// The same for a tile held as 16 x 16 blocks: block (db, j), element v of a lane is key 16 j + lane % 16, column
+// 16 db + 4 (lane / 16) + v.
+template <int D>
+__device__ __forceinline__ void store_key_rows16(char *buf, const f32x4 (&acc)[D / 16][2], float scale, float *__restrict__ dst,
+                                                 int64_t ld, int rows_ok, int lane)
+{
+    constexpr int CH = D / 4;                           // 16-byte chunks per row
+#pragma unroll
+    for (int db = 0; db < D / 16; ++db)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int key = 16 * j + (lane & 15), c = 4 * db + (lane >> 4);
+            const f32x4 a = acc[db][j];
+            *reinterpret_cast<f32x4 *>(buf + key * (D * 4) + ((c ^ (key & (CH - 1))) * 16)) = f32x4{a[0] * scale, a[1] * scale, a[2] * scale, a[3] * scale};
+        }
+    constexpr int RPI = 64 / CH;                        // rows per store instruction
+#pragma unroll
+    for (int i = 0; i < 32 / RPI; ++i) {
+        const int row = i * RPI + lane / CH, c = lane % CH;
+        const f32x4 val = *reinterpret_cast<const f32x4 *>(buf + row * (D * 4) + ((c ^ (row & (CH - 1))) * 16));
+        if (row < rows_ok) *reinterpret_cast<f32x4 *>(dst + (int64_t)row * ld + c * 4) = val;
+    }
+}
+
 template <int D, bool DROP = false>
 struct DkvBf16Cfg {
     // One 32-row key block per wavefront.  Two blocks would halve the LDS traffic per flop but
@@ -498,7 +525,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     using Tile = typename C::Tile;
     constexpr int NU = C::NU;
 
-    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, lk = lane & 15, g = lane >> 4;
     const int all_waves = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int group = KG > 1 ? all_waves / C::WAVES : 0, wave = KG > 1 ? all_waves % C::WAVES : all_waves;     // wave: within the group
     char *const ring = smem + group * (C::RING * C::SLOT), *const own_values = smem + KG * (C::RING * C::SLOT);
@@ -532,16 +559,16 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         return;
     }
 
-    // this lane's key (column of the S tile); keys past the sequence re-read its last row
+    // this lane's two keys (columns of the S blocks), jw0 + 16 j + lk; keys past the sequence re-read its last row
     // (unconditional loads), take part in all the arithmetic and are never stored
-    const int j = jw0 + lq;
-    Frag<bf16_t> kf[NU], vf[NU];
-    {
-        const int64_t off = kv_base + (int64_t)min(j, s.l_x - 1) * ld + hh * 8;
+    Frag<bf16_t> kf[NU], vf[NU];                        // operand step ks (32 columns), key block j: [2 ks + j]
 #pragma unroll
-        for (int kb = 0; kb < NU; ++kb) {
-            kf[kb] = load_frag<bf16_t>(k + off + kb * 16);
-            vf[kb] = load_frag<bf16_t>(v + off + kb * 16);
+    for (int j = 0; j < 2; ++j) {
+        const int64_t off = kv_base + (int64_t)min(jw0 + 16 * j + lk, s.l_x - 1) * ld + g * 8;
+#pragma unroll
+        for (int ks = 0; ks < NU / 2; ++ks) {
+            kf[2 * ks + j] = load_frag<bf16_t>(k + off + ks * 32);
+            vf[2 * ks + j] = load_frag<bf16_t>(v + off + ks * 32);
         }
     }
     if constexpr (D == 128) {
@@ -556,11 +583,12 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         }
     }
 
-    f32x16 dk[D / 32], dv[D / 32];
+    const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+    f32x4 dk[NU][2], dv[NU][2];                         // 16 columns x 16 keys each, transposed
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
+    for (int db = 0; db < NU; ++db)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) { dk[db][e] = 0.f; dv[db][e] = 0.f; }
+        for (int j = 0; j < 2; ++j) dk[db][j] = dv[db][j] = zero4;
 
     const float sqrt_d = sqrtf((float)D);
     const float c = kLog2e / sqrt_d;
@@ -568,7 +596,10 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     const bf16_t *gbase = dO + (int64_t)b * s.l_s * ld + (int64_t)h * D;
     const float *lbase = Ls + (int64_t)bh * s.l_s, *dbase = Dn + (int64_t)bh * s.l_s;
     const uint32_t *rbase = DROP ? row_key + (int64_t)bh * s.l_s : nullptr;
-    const uint32_t drop_ck = DROP ? drop_col_key(drop_col_seed(dr.seed_hi), (uint32_t)j) : 0u;  // this lane's key
+    uint32_t drop_ck[2] = {0u, 0u};                     // this lane's keys
+    if (DROP)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) drop_ck[j] = drop_col_key(drop_col_seed(dr.seed_hi), (uint32_t)(jw0 + 16 * j + lk));
 
     // ---- tile loads: all four wavefronts move Q and dO, and the 64 start values of either kind (even
     // wavefronts -lse*sqrt(d), odd ones -D; each twice, which is cheaper than a branch inside a pipeline
@@ -603,162 +634,172 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     };
 
     // ---- per-lane LDS offsets (bytes, within a tile)
-    int a_off[NU];                                      // A-operand chunk of row lq for operand step kb
+    int a_off[NU / 2];                                  // A-operand chunk of row lk for operand step ks
 #pragma unroll
-    for (int kb = 0; kb < NU; ++kb) a_off[kb] = Tile::chunk_offset(lq, 2 * kb + hh);
-    int t_off[D / 32];                                  // transposed reads, column block db
+    for (int ks = 0; ks < NU / 2; ++ks) a_off[ks] = Tile::chunk_offset(lk, 4 * ks + g);
+    int t_off[NU];                                      // transposed reads, column block db
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db) t_off[db] = tr_lane_offset_sw<D>(lane, db);
+    for (int db = 0; db < NU; ++db) t_off[db] = tr16_lane_offset_sw<D>(lane, db);
 
-    // ---- stage pieces.  `tile` / `qb` name a block: LDS address of its ring slot and which half of it.
-    auto load_a = [&](const char *tile, int qb, int kb, Frag<bf16_t> &fq, Frag<bf16_t> &fg) __attribute__((always_inline)) {
-        const char *p = tile + qb * 32 * (D * 2) + a_off[kb];
+    // ---- stage pieces.  `tile` / `qb` name a block of 32 rows: LDS address of its ring slot and which half of it.
+    // Unit u: A operands of row block u % 2, operand step u / 2; C operands of column block u.
+    auto load_a = [&](const char *tile, int qb, int u, Frag<bf16_t> &fq, Frag<bf16_t> &fg) __attribute__((always_inline)) {
+        const char *p = tile + (qb * 32 + u % 2 * 16) * (D * 2) + a_off[u / 2];
         fq = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(p));
         fg = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(p + C::OFF_G));
     };
     auto load_c = [&](const char *tile, int qb, int u, Frag<bf16_t> &fq, Frag<bf16_t> &fg) __attribute__((always_inline)) {
-        const int half = u / (D / 32), db = u % (D / 32);
-        fq = load_frag_tr_sw<D>(tile, (qb * 2 + half) * 16, t_off[db]);
-        fg = load_frag_tr_sw<D>(tile + C::OFF_G, (qb * 2 + half) * 16, t_off[db]);
+        fq = load_frag_tr16_sw<D>(tile, qb * 32, t_off[u]);
+        fg = load_frag_tr16_sw<D>(tile + C::OFF_G, qb * 32, t_off[u]);
     };
-    // Accumulators of A start at -lse*sqrt(d) and -D of their rows: C-tile element e of this lane is
-    // query row 8*(e/4) + 4*hh + e%4 of the block.  init_load reads the values of element groups
-    // [g0, g1) (4 elements each).  `start_values`: those of a block, in its tile's slot, or with OWN by its
+    // Accumulators of A start at -lse*sqrt(d) and -D of their rows: element v of this lane's block (i, j) is
+    // query row 16 i + 4 g + v.  `start_values`: those of a block of 32 rows, in its tile's slot, or with OWN by its
     // first row counted from rq_begin; the -D and the row keys follow SV_D and SV_R bytes on.
     constexpr int SV_D = OWN ? C::OWN_ROWS * 4 : C::OFF_D - C::OFF_L, SV_R = 2 * SV_D;
     static_assert(OWN || SV_R == C::OFF_R - C::OFF_L, "start values lie in one row of arrays");
     auto start_values = [&](const char *tile, int qb, int row) __attribute__((always_inline)) {
-        return (OWN ? own_values + row * 4 : tile + C::OFF_L + qb * 32 * 4) + 4 * hh * 4;
+        return (OWN ? own_values + row * 4 : tile + C::OFF_L + qb * 32 * 4) + 4 * g * 4;
     };
-    auto init_load = [&](const char *sv, int g0, int g1, f32x16 &sc, f32x16 &dp) __attribute__((always_inline)) {
+    f32x4 sv_l[2], sv_d[2];
+    auto init_load = [&](const char *sv) __attribute__((always_inline)) {
 #pragma unroll
-        for (int e4 = g0; e4 < g1; ++e4) {
-            const f32x4 l4 = *reinterpret_cast<const f32x4 *>(sv + 8 * e4 * 4);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) sc[4 * e4 + i] = l4[i];
-            if constexpr (!DROP) {
-                const f32x4 d4 = *reinterpret_cast<const f32x4 *>(sv + SV_D + 8 * e4 * 4);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) dp[4 * e4 + i] = d4[i];
-            }
+        for (int i = 0; i < 2; ++i) {
+            sv_l[i] = *reinterpret_cast<const f32x4 *>(sv + i * 64);
+            if constexpr (!DROP) sv_d[i] = *reinterpret_cast<const f32x4 *>(sv + SV_D + i * 64);
         }
     };
     // Where the causal diagonal or the end of the segment crosses the block (first row: local row
-    // r0), the masked elements start at -inf instead, which B turns into P = dS = 0: rows before
+    // r0), the masked elements of its finished S are set to -inf, which B turns into P = dS = 0: rows before
     // the lane's key, and rows past the segment (whose loads re-read its last row).
-    auto init_mask = [&](int r0, f32x16 &sc) __attribute__((always_inline)) {
+    struct Block { f32x4 v[2][2]; };                    // [row block i][key block j]
+    auto mask_s = [&](int r0, Block &sc) __attribute__((always_inline)) {
         const bool diag = s.causal && (jw0 + C::KW - 1 > (int)s.s0 + r0);      // positions are below 2^30: 32-bit scalar compare
         if (diag || r0 + 32 > s.l_s) {
-            const int first = diag ? max(min(j - (int)s.s0 - r0 - 4 * hh, 64), 0) : 0;
-            const int end = min(s.l_s - r0, 32) - 4 * hh;
+            const int end = min(s.l_s - r0, 32) - 4 * g;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int rr = 8 * (e >> 2) + (e & 3);
-                if (rr < first || rr >= end) sc[e] = -INFINITY;
+            for (int j = 0; j < 2; ++j) {
+                const int first = diag ? max(min(jw0 + 16 * j + lk - (int)s.s0 - r0 - 4 * g, 64), 0) : 0;
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (16 * i + v < first || 16 * i + v >= end) sc.v[i][j][v] = -INFINITY;
             }
         }
     };
-    // B for elements [e0, e1): P = 2^(c * (S - lse*sqrt(d))), dS = P * (dP - D); finished pairs are
-    // rounded to bf16 into the operand fragments of C
-    // (dropout: `sv_b` are B's start values; the row keys and -D of four elements are read when
+    // B for elements [e0, e1), element e = (i, j, v) = (e / 8, e / 4 % 2, e % 4): P = 2^(c * (S - lse*sqrt(d))), dS = P * (dP - D);
+    // finished pairs are rounded to bf16 into the operand fragments of C: slots 4 i + v of key block j.
+    // (dropout: `sv_b` are B's start values; the row keys and -D of four rows are read when
     // the first of them is due)
     // (An element's exponential and the multiplies that consume it are issued one element apart, as in the dQ
     // workgroups: a transcendental's result may not be read by the very next instruction.)
     u32x4 rk4;
     f32x4 nd4;
-    auto b_elems = [&](const char *sv_b, f32x16 &sc, f32x16 &dp, int e0, int e1, Frag<bf16_t> (&pf)[2],
+    auto b_elems = [&](const char *sv_b, Block &sc, Block &dp, int e0, int e1, Frag<bf16_t> (&pf)[2],
                        Frag<bf16_t> (&df)[2]) __attribute__((always_inline)) {
-        auto finish = [&](int i) __attribute__((always_inline)) {           // sc[i] holds P by now
+        auto finish = [&](int e) __attribute__((always_inline)) {           // sc holds P by now
+            const int i = e >> 3, j = e >> 2 & 1, v = e & 3;
+            f32x4 &p4 = sc.v[i][j], &d4 = dp.v[i][j];
             if constexpr (DROP) {
-                if ((i & 3) == 0) {
-                    rk4 = *reinterpret_cast<const u32x4 *>(sv_b + SV_R + 8 * (i >> 2) * 4);
-                    nd4 = *reinterpret_cast<const f32x4 *>(sv_b + SV_D + 8 * (i >> 2) * 4);
+                if ((e & 7) == 0) {
+                    rk4 = *reinterpret_cast<const u32x4 *>(sv_b + SV_R + i * 64);
+                    nd4 = *reinterpret_cast<const f32x4 *>(sv_b + SV_D + i * 64);
                 }
-                const float p = sc[i], m = drop_keep(rk4[i & 3], drop_ck, dr.thr) ? dr.scale : 0.f;
-                sc[i] = p * m;
-                dp[i] = p * fmaf(dp[i], m, nd4[i & 3]);
+                const float p = p4[v], m = drop_keep(rk4[v], drop_ck[j], dr.thr) ? dr.scale : 0.f;
+                p4[v] = p * m;
+                d4[v] = p * fmaf(d4[v], m, nd4[v]);
             } else {
-                dp[i] = sc[i] * dp[i];
+                d4[v] = p4[v] * d4[v];
             }
-            if (i & 1) {
-                pf[i >> 3].v[(i & 7) - 1] = (bf16_t)sc[i - 1]; pf[i >> 3].v[i & 7] = (bf16_t)sc[i];
-                df[i >> 3].v[(i & 7) - 1] = (bf16_t)dp[i - 1]; df[i >> 3].v[i & 7] = (bf16_t)dp[i];
+            if (v & 1) {
+                pf[j].v[4 * i + v - 1] = (bf16_t)p4[v - 1]; pf[j].v[4 * i + v] = (bf16_t)p4[v];
+                df[j].v[4 * i + v - 1] = (bf16_t)d4[v - 1]; df[j].v[4 * i + v] = (bf16_t)d4[v];
             }
         };
 #pragma unroll
         for (int e = e0; e < e1; ++e) {
-            sc[e] = fast_exp2(sc[e] * c);
+            f32x4 &p4 = sc.v[e >> 3][e >> 2 & 1];
+            p4[e & 3] = fast_exp2(p4[e & 3] * c);
             if (e > 0) finish(e - 1);
             if (e == 15) finish(15);
         }
     };
-    // One pipeline step.  A: block (tile_a, qb_a), first row r0_a, into (sc_a, dp_a).  B: (sc_b, dp_b),
-    // packing into (pf_b, df_b).  C: block (tile_c, qb_c) from (pf_c, df_c) into dk, dv.  The matrix
-    // instructions alternate C, C, A, A (A, A, C, C in the last unit); after each one come the B
+    // One pipeline step.  A: block (tile_a, qb_a) into (sc_a, dp_a), from the start values in sv_l and sv_d.  B: (sc_b, dp_b),
+    // first row r0_b, packing into (pf_b, df_b).  C: block (tile_c, qb_c) from (pf_c, df_c) into dk, dv.  Per unit four matrix
+    // instructions of C and four of A (A first in the last unit), each pair on one operand fragment; after each come the B
     // elements that fall to its slot.
     // Everything read from LDS is requested well before its use: operand fragments one unit ahead;
     // for the next step (A on block (tile_an, qb_an), rows from rq_begin + row_an on, C on (tile_cn, qb_cn)) this step's last
-    // unit requests the fragments of C's first unit (cq[0], cg[0]) and, into the three quarters of
-    // B's registers that B is done with by then, the start values of A's accumulators (PRE says
-    // the step before did that for this one).  `mid` runs before those last requests: the even
+    // unit requests the fragments of both's first unit and the start values of A's
+    // accumulators.  `mid` runs before those last requests: the even
     // steps put the loop's barrier there, because the next step's A block may lie in the tile that
     // the barrier publishes.
-    Frag<bf16_t> cq[2], cg[2];
-    auto step = [&](auto has_a, auto has_b, auto has_c, auto pre, const char *tile_a, int qb_a, int r0_a, f32x16 &sc_a,
-                    f32x16 &dp_a, const char *sv_b, f32x16 &sc_b, f32x16 &dp_b, Frag<bf16_t> (&pf_b)[2],
+    Frag<bf16_t> cq[2], cg[2], aq[2], ag[2];
+    auto step = [&](auto has_a, auto has_b, auto has_c, const char *tile_a, int qb_a, Block &sc_a,
+                    Block &dp_a, const char *sv_b, int r0_b, Block &sc_b, Block &dp_b, Frag<bf16_t> (&pf_b)[2],
                     Frag<bf16_t> (&df_b)[2], const char *tile_c, int qb_c, Frag<bf16_t> (&pf_c)[2], Frag<bf16_t> (&df_c)[2],
                     const char *tile_an, int qb_an, int row_an, const char *tile_cn, int qb_cn, auto &&mid) __attribute__((always_inline)) {
         constexpr bool HA = decltype(has_a)::value, HB = decltype(has_b)::value, HC = decltype(has_c)::value;
-        constexpr bool PRE = decltype(pre)::value;
-        constexpr int NS = 4 * NU;                      // slots; 16 elements of B spread over them
+        constexpr int NS = 8 * NU;                      // slots; 16 elements of B spread over them
         static_assert(NU % 2 == 0, "fragment double buffers assume an even number of units");
         auto b_slot = [&](int slot) __attribute__((always_inline)) {
             if (HB) {
                 const int e0 = slot * 16 / NS, e1 = (slot + 1) * 16 / NS;
+                if (e0 == e1) return;
                 __builtin_amdgcn_sched_barrier(0);
                 b_elems(sv_b, sc_b, dp_b, e0, e1, pf_b, df_b);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        Frag<bf16_t> aq[2], ag[2];
-        if (HA) {
-            init_load(start_values(tile_a, qb_a, r0_a - rq_begin), PRE ? 3 : 0, 4, sc_a, dp_a);
-            load_a(tile_a, qb_a, 0, aq[0], ag[0]);
-            init_mask(r0_a, sc_a);
-        }
         // B's inputs pass through an empty asm here: its arithmetic depends on nothing else in this
         // step, and the compiler would otherwise move all of it out of the step, in one lump
-        if (HB) asm volatile("" : "+v"(sc_b), "+v"(dp_b));
+        if (HB) {
+            mask_s(r0_b, sc_b);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) asm volatile("" : "+v"(sc_b.v[i][0]), "+v"(sc_b.v[i][1]), "+v"(dp_b.v[i][0]), "+v"(dp_b.v[i][1]));
+        }
+        auto do_a = [&](int u, int slot) __attribute__((always_inline)) {
+            const int i = u % 2, ks = u / 2;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                if (HA) sc_a.v[i][j] = mma16(aq[u & 1], kf[2 * ks + j], ks == 0 ? sv_l[i] : sc_a.v[i][j]);
+                b_slot(slot + j);
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                if (HA) dp_a.v[i][j] = mma16(ag[u & 1], vf[2 * ks + j], ks == 0 ? (DROP ? zero4 : sv_d[i]) : dp_a.v[i][j]);
+                b_slot(slot + 2 + j);
+            }
+        };
+        auto do_c = [&](int u, int slot) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                if (HC) dv[u][j] = mma16(cg[u & 1], pf_c[j], dv[u][j]);
+                b_slot(slot + j);
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                if (HC) dk[u][j] = mma16(cq[u & 1], df_c[j], dk[u][j]);
+                b_slot(slot + 2 + j);
+            }
+        };
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
-            const int half = u / (D / 32), db = u % (D / 32);
             if (u + 1 < NU) {
                 if (HC) load_c(tile_c, qb_c, u + 1, cq[(u + 1) & 1], cg[(u + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-                if (HC) dv[db] = mma(cg[u & 1], pf_c[half], dv[db]);
-                b_slot(4 * u);
-                if (HC) dk[db] = mma(cq[u & 1], df_c[half], dk[db]);
-                b_slot(4 * u + 1);
                 if (HA) load_a(tile_a, qb_a, u + 1, aq[(u + 1) & 1], ag[(u + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);
-                if (HA) sc_a = mma(aq[u & 1], kf[u], sc_a);
-                b_slot(4 * u + 2);
-                if (HA) dp_a = mma(ag[u & 1], vf[u], DROP && u == 0 ? f32x16{} : dp_a);
-                b_slot(4 * u + 3);
+                do_c(u, 8 * u);
+                do_a(u, 8 * u + 4);
             } else {
                 // last unit: A first, so that its results are there when the next step's B wants them
-                if (HA) sc_a = mma(aq[u & 1], kf[u], sc_a);
-                b_slot(4 * u);
-                if (HA) dp_a = mma(ag[u & 1], vf[u], dp_a);
-                b_slot(4 * u + 1);
+                do_a(u, 8 * u);
                 mid();
                 load_c(tile_cn, qb_cn, 0, cq[0], cg[0]);
-                init_load(start_values(tile_an, qb_an, row_an), 0, 3, sc_b, dp_b);    // elements 0..11 of B are packed by now
+                load_a(tile_an, qb_an, 0, aq[0], ag[0]);
+                init_load(start_values(tile_an, qb_an, row_an));
                 __builtin_amdgcn_sched_barrier(0);
-                if (HC) dv[db] = mma(cg[u & 1], pf_c[half], dv[db]);
-                b_slot(4 * u + 2);
-                if (HC) dk[db] = mma(cq[u & 1], df_c[half], dk[db]);
-                b_slot(4 * u + 3);
+                do_c(u, 8 * u + 4);
             }
         }
         // ... and its results through another one, so that it is not sunk below the step either
@@ -795,19 +836,22 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     __syncthreads();
 
     if (KG == 1 || T > 0) {
-        f32x16 sc0, dp0, sc1, dp1;                          // even / odd blocks
+        Block sc0, dp0, sc1, dp1;                       // even / odd blocks
         Frag<bf16_t> pf0[2], df0[2], pf1[2], df1[2];
         // step -1: A(0) alone (leaves the first loop step's C operands in cq[0], cg[0]).  That step has
         // no C(-1): it multiplies zeros with tile 0 instead.
         auto nothing = [] {};
-        step(true_type{}, false_type{}, false_type{}, false_type{}, ring, 0, rq_begin + row_base, sc0, dp0, ring, sc1, dp1, pf0, df0, ring, 0,
+        load_a(ring, 0, 0, aq[0], ag[0]);
+        init_load(start_values(ring, 0, row_base));
+        step(true_type{}, false_type{}, false_type{}, ring, 0, sc0, dp0, ring, 0, sc1, dp1, pf0, df0, ring, 0,
              pf1, df1, ring, 1, row_base + 32, ring, 1, nothing);
 #pragma unroll
-        for (int half = 0; half < 2; ++half)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) { pf1[half].v[e] = (bf16_t)0.f; df1[half].v[e] = (bf16_t)0.f; }
+            for (int e = 0; e < 8; ++e) { pf1[j].v[e] = (bf16_t)0.f; df1[j].v[e] = (bf16_t)0.f; }
 
-        int cur = 0;                                        // ring slot of tile t
+        int cur = 0;                                    // ring slot of tile t
+#pragma nounroll    // (unrolled, two groups' registers spill: 84 spills against none)
         for (int t = 0; t < T; ++t) {
             const int nxt = cur == C::RING - 1 ? 0 : cur + 1, prv = cur == 0 ? C::RING - 1 : cur - 1;
             const char *t_cur = ring + cur * C::SLOT, *t_nxt = ring + nxt * C::SLOT, *t_prv = ring + prv * C::SLOT;
@@ -818,8 +862,8 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
             // Before its last requests (which may touch tile t+1): tile t+1's loads, issued one iteration
             // ago, have landed for this wavefront; after the barrier for all, and every wavefront has
             // requested its last operands from tile t-1, whose slot takes tile t+2.
-            step(true_type{}, true_type{}, true_type{}, true_type{}, t_cur, 1, r0 + 32, sc1, dp1,
-                 start_values(t_cur, 0, row), sc0, dp0, pf0, df0, t > 0 ? t_prv : t_cur, 1, pf1, df1, t_a2, 0, row + C::BQ,
+            step(true_type{}, true_type{}, true_type{}, t_cur, 1, sc1, dp1,
+                 start_values(t_cur, 0, row), r0, sc0, dp0, pf0, df0, t > 0 ? t_prv : t_cur, 1, pf1, df1, t_a2, 0, row + C::BQ,
                  t_cur, 0, [&] {
                      wait_vmem_all();
                      __syncthreads();
@@ -827,17 +871,15 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
                  });
             // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end result unused], B(2t+1),
             // C(2t) [tile t, first half]
-            step(true_type{}, true_type{}, true_type{}, true_type{}, t_a2, 0, r0 + C::BQ, sc0, dp0,
-                 start_values(t_cur, 1, row + 32), sc1, dp1, pf1, df1, t_cur, 0, pf0, df0, t_a2, 1, row + C::BQ + 32, t_cur, 1,
+            step(true_type{}, true_type{}, true_type{}, t_a2, 0, sc0, dp0,
+                 start_values(t_cur, 1, row + 32), r0 + 32, sc1, dp1, pf1, df1, t_cur, 0, pf0, df0, t_a2, 1, row + C::BQ + 32, t_cur, 1,
                  nothing);
             cur = nxt;
         }
         // step 2T: C(2T-1) [tile T-1, second half] alone
-        {
-            const char *t_last = ring + (cur == 0 ? C::RING - 1 : cur - 1) * C::SLOT;
-            step(false_type{}, false_type{}, true_type{}, false_type{}, ring, 0, 0, sc0, dp0, ring, sc0, dp0, pf0, df0, t_last, 1, pf1,
-                 df1, ring, 0, 0, t_last, 1, nothing);
-        }
+        const char *t_last = ring + (cur == 0 ? C::RING - 1 : cur - 1) * C::SLOT;
+        step(false_type{}, false_type{}, true_type{}, ring, 0, sc0, dp0, ring, 0, sc0, dp0, pf0, df0, t_last, 1, pf1,
+             df1, ring, 0, 0, t_last, 1, nothing);
     }
     if (KG > 1)
         for (int t = max(T, 0); t < iters; ++t) __syncthreads();       // the barriers of the group that has more tiles
@@ -851,29 +893,22 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         const int64_t off = kv_base + (int64_t)jw0 * ld;
         const int rows_ok = min(s.l_x - jw0, C::KW);
         if constexpr (KG == 1) {
-            store_key_rows<D>(buf, dk, 1.f / sqrt_d, dk_part + off, ld, rows_ok, lane);
-            store_key_rows<D>(buf, dv, 1.f, dv_part + off, ld, rows_ok, lane);
+            store_key_rows16<D>(buf, dk, 1.f / sqrt_d, dk_part + off, ld, rows_ok, lane);
+            store_key_rows16<D>(buf, dv, 1.f, dv_part + off, ld, rows_ok, lane);
         } else {
             // The groups' sums meet in LDS: the first finishes dV, the second dK, adding in group order.  What a wavefront
             // reads was written for it alone, into the buffer that is its own from then on.
             static_assert(KG == 2 && D == 64, "");
             char *const theirs = smem + (all_waves ^ C::WAVES) * (32 * D * 4);
-            f32x16 sum[D / 32];
+            f32x4 sum[NU][2];
 #pragma unroll
-            for (int u = 0; u < D / 8; ++u) {
-                f32x4 v;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = group == 0 ? dk[u / 4][u % 4 * 4 + i] : dv[u / 4][u % 4 * 4 + i];
-                *reinterpret_cast<f32x4 *>(theirs + u * 1024 + lane * 16) = v;
-            }
+            for (int u = 0; u < 2 * NU; ++u)
+                *reinterpret_cast<f32x4 *>(theirs + u * 1024 + lane * 16) = group == 0 ? dk[u / 2][u % 2] : dv[u / 2][u % 2];
             __syncthreads();
 #pragma unroll
-            for (int u = 0; u < D / 8; ++u) {
-                const f32x4 v = *reinterpret_cast<const f32x4 *>(buf + u * 1024 + lane * 16);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) sum[u / 4][u % 4 * 4 + i] = (group == 0 ? dv[u / 4][u % 4 * 4 + i] : dk[u / 4][u % 4 * 4 + i]) + v[i];
-            }
-            store_key_rows<D>(buf, sum, group == 0 ? 1.f : 1.f / sqrt_d, (group == 0 ? dv_part : dk_part) + off, ld, rows_ok, lane);
+            for (int u = 0; u < 2 * NU; ++u)
+                sum[u / 2][u % 2] = (group == 0 ? dv[u / 2][u % 2] : dk[u / 2][u % 2]) + *reinterpret_cast<const f32x4 *>(buf + u * 1024 + lane * 16);
+            store_key_rows16<D>(buf, sum, group == 0 ? 1.f : 1.f / sqrt_d, (group == 0 ? dv_part : dk_part) + off, ld, rows_ok, lane);
         }
     }
 }
