@@ -1,12 +1,13 @@
 // Tuned bf16 backward of Eq. 2 (Section 3, Principle 3) for gfx950 (mathematics: lss_bwd.hip): dQ and dK/dV as two kinds of
 // workgroup that share one launch (bwd_main_bf16_kernel); short segments take one pass for all three gradients
 // (bwd_skinny_bf16_kernel).  In the former:
-//   * 32 x 32 blocks, dK/dV in 16 x 16 x 32 instructions, three stages per block (score-side products, vector
+//   * 32 x 32 blocks, in 16 x 16 x 32 instructions, three stages per block (score-side products, vector
 //     work, output-side products), software-pipelined so that the vector work of one block sits between
 //     the matrix instructions of its neighbours.  Large launches are bound by the chip's power: per product
 //     the 16 x 16 x 32 form takes less of it than 32 x 32 x 16 (register loops on Gaussian bf16: 2,020 - 2,070
 //     against 1,800 - 1,840 TFLOP/s; with the backward's vector work between them 1,669 - 1,708 against 1,597).
 //     With it in dK/dV 8,192 x 8,192 causal passes fell from 1,014 to 994 us, 32,768 keys at d = 128 from 2,535 to 2,505;
+//     in dQ then to 984 and 2,464;
 //   * 64-row tiles loaded global -> LDS directly into a ring of three unpadded, swizzled tiles, a
 //     full loop iteration ahead, one barrier per tile;
 //   * row-major LDS tiles read transposed with DS_READ_B64_TR_B16 where the contraction runs over
@@ -59,7 +60,7 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
     using Tile = typename C::Tile;
     constexpr int NU = C::NU;
 
-    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 15, g = lane >> 4;
     const int all_waves = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int group = KG > 1 ? all_waves / C::WAVES : 0, wave = KG > 1 ? all_waves % C::WAVES : all_waves;     // wave: within the group
     char *const ring = smem + group * C::group_lds(DROP);
@@ -79,55 +80,58 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
     const int iters = KG > 1 ? (s_tiles + KG - 1) / KG : s_tiles;
     const int t_begin = s_begin + group * iters, T = KG > 1 ? max(min(s_tiles - group * iters, iters), 0) : s_tiles;
 
-    // this lane's query row (column of the S^T tile); rows past the segment re-read its last row
+    // this lane's two query rows (columns of the S^T blocks), rw0 + 16 j + lq; rows past the segment re-read its last row
     // (unconditional loads), get lse = +inf, which makes their P and dS exactly 0, and are never stored
-    const int r = rw0 + lq;
-    const bool row_ok = r < s.l_s;
-    Frag<bf16_t> qf[NU], gf[NU];
-    float L2, Dr;
-    {
-        const int rc = min(r, s.l_s - 1);
-        const int64_t off = ((int64_t)b * s.l_s + rc) * ld + (int64_t)h * D + hh * 8;
+    Frag<bf16_t> qf[NU], gf[NU];                        // operand step ks (32 columns), row block j: [2 ks + j]
+    float L2[2], Dr[2];
 #pragma unroll
-        for (int kb = 0; kb < NU; ++kb) {
-            qf[kb] = load_frag<bf16_t>(q + off + kb * 16);
-            gf[kb] = load_frag<bf16_t>(dO + off + kb * 16);
-        }
-        if constexpr (OWN) {        // the lane's half of the row, then the other half's sum
-            Dr = 0.f;
+    for (int j = 0; j < 2; ++j) {
+        const int r = rw0 + 16 * j + lq, rc = min(r, s.l_s - 1);
+        const int64_t off = ((int64_t)b * s.l_s + rc) * ld + (int64_t)h * D + g * 8;
+        Dr[j] = 0.f;
 #pragma unroll
-            for (int kb = 0; kb < NU; ++kb) {
-                const Frag<bf16_t> of = load_frag<bf16_t>(out + off + kb * 16);
+        for (int ks = 0; ks < NU / 2; ++ks) {
+            qf[2 * ks + j] = load_frag<bf16_t>(q + off + ks * 32);
+            gf[2 * ks + j] = load_frag<bf16_t>(dO + off + ks * 32);
+            if constexpr (OWN) {    // the lane's quarter of the row
+                const Frag<bf16_t> of = load_frag<bf16_t>(out + off + ks * 32);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) Dr += (float)gf[kb].v[e] * (float)of.v[e];
+                for (int e = 0; e < 8; ++e) Dr[j] += (float)gf[2 * ks + j].v[e] * (float)of.v[e];
             }
-            Dr += __shfl_xor(Dr, 32);
+        }
+        if constexpr (OWN) {
+            Dr[j] += __shfl_xor(Dr[j], 16);
+            Dr[j] += __shfl_xor(Dr[j], 32);
         } else {
-            Dr = -Dn[(int64_t)bh * s.l_s + rc];
+            Dr[j] = -Dn[(int64_t)bh * s.l_s + rc];
         }
         const float lv = lse[(int64_t)bh * s.l_s + rc];
-        L2 = row_ok ? lv * kLog2e : INFINITY;
+        L2[j] = r < s.l_s ? lv * kLog2e : INFINITY;
     }
     const float c = kLog2e / sqrtf((float)D);
-    // -D in all 16 accumulator slots: third operand of each block's first dP^T instruction (not with dropout, whose mask comes between)
-    f32x16 neg_d;
+    // -D in all accumulator slots: third operand of each block's first dP^T instructions (not with dropout, whose mask comes between)
+    const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+    f32x4 neg_d[2], acc[NU][2];                         // acc: 16 columns x 16 rows each, transposed
 #pragma unroll
-    for (int e = 0; e < 16; ++e) neg_d[e] = -Dr;
-    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-
-    f32x16 acc[D / 32];
+    for (int j = 0; j < 2; ++j) {
+        neg_d[j] = f32x4{-Dr[j], -Dr[j], -Dr[j], -Dr[j]};
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db) acc[db] = zero16;
+        for (int db = 0; db < NU; ++db) acc[db][j] = zero4;
+    }
 
     if (s_tiles > 0) {
         const bf16_t *kbase = k + (int64_t)b * s.l_x * ld + (int64_t)h * D;
         const bf16_t *vbase = v + (int64_t)b * s.l_x * ld + (int64_t)h * D;
 
-        // dropout: this lane's row key; the column seed; the column keys of tile t (global tile index)
+        // dropout: this lane's row keys; the column seed; the column keys of tile t (global tile index)
         // are computed once, by one wavefront when the tile's loads are issued, into quarter t % 4 of
         // a small ring behind the tiles -- published by the same barrier as the tile
-        uint32_t drop_rk = 0u, drop_cs = 0u;
-        if (DROP) { drop_rk = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + r)); drop_cs = drop_col_seed(dr.seed_hi); }
+        uint32_t drop_rk[2] = {0u, 0u}, drop_cs = 0u;
+        if (DROP) {
+            drop_cs = drop_col_seed(dr.seed_hi);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) drop_rk[j] = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + rw0 + 16 * j + lq));
+        }
         char *const ck_ring = ring + C::RING * C::SLOT;
 
         // ---- tile loads, by all four wavefronts.  Branch-free on purpose: a branch inside a pipeline step
@@ -158,81 +162,91 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
         auto issue_ahead = [&](int t, int slot) { issue_tile(t_begin + min(t + 2, T - 1), slot); };
 
         // ---- per-lane LDS offsets (bytes, within a tile)
-        int a_off[NU];                                  // A-operand chunk of row lq for operand step kb
+        int a_off[NU / 2];                              // A-operand chunk of row lq for operand step ks
 #pragma unroll
-        for (int kb = 0; kb < NU; ++kb) a_off[kb] = Tile::chunk_offset(lq, 2 * kb + hh);
-        int t_off[D / 32];                              // transposed reads, column block db
+        for (int ks = 0; ks < NU / 2; ++ks) a_off[ks] = Tile::chunk_offset(lq, 4 * ks + g);
+        int t_off[NU];                                  // transposed reads, column block db
 #pragma unroll
-        for (int db = 0; db < D / 32; ++db) t_off[db] = tr_lane_offset_sw<D>(lane, db);
+        for (int db = 0; db < NU; ++db) t_off[db] = tr16_lane_offset_sw<D>(lane, db);
 
-        // ---- stage pieces.  `tile` / `kb2` name a block: LDS address of its ring slot and which half of it.
-        auto load_a = [&](const char *tile, int kb2, int kb, Frag<bf16_t> &fk, Frag<bf16_t> &fv) __attribute__((always_inline)) {
-            const char *p = tile + kb2 * 32 * (D * 2) + a_off[kb];
+        // ---- stage pieces.  `tile` / `kb2` name a block of 32 keys: LDS address of its ring slot and which half of it.
+        // Unit u: A operands of key block u % 2, operand step u / 2; C operand of column block u.
+        auto load_a = [&](const char *tile, int kb2, int u, Frag<bf16_t> &fk, Frag<bf16_t> &fv) __attribute__((always_inline)) {
+            const char *p = tile + (kb2 * 32 + u % 2 * 16) * (D * 2) + a_off[u / 2];
             fk = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(p));
             fv = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(p + C::OFF_V));
         };
         auto load_c = [&](const char *tile, int kb2, int u, Frag<bf16_t> &fk) __attribute__((always_inline)) {
-            const int half = u / (D / 32), db = u % (D / 32);
-            fk = load_frag_tr_sw<D>(tile, (kb2 * 2 + half) * 16, t_off[db]);
+            fk = load_frag_tr16_sw<D>(tile, kb2 * 32, t_off[u]);
         };
-        // B for elements [e0, e1): P = 2^(c * S - lse * log2 e), dS = P * (dP - D); finished pairs are
-        // rounded to bf16 into the operand fragments of C
+        // B for elements [e0, e1), element e = (i, j, v) = (e / 8, e / 4 % 2, e % 4): P = 2^(c * S - lse * log2 e), dS = P * (dP - D);
+        // finished pairs are rounded to bf16 into the operand fragments of C: slots 4 i + v of row block j
         // An element's exponential and the multiply that consumes it are issued one element apart (the
         // multiply of element e - 1 follows the exponential of element e): a transcendental's result may not
         // be read by the very next instruction, and the slot that would otherwise idle is not free.
-        u32x4 ck4;      // dropout: the column keys of four consecutive elements, read when the first is due
-        auto b_elems = [&](f32x16 &sc, f32x16 &dp, int jb, int e0, int e1, Frag<bf16_t> (&df)[2]) __attribute__((always_inline)) {
-            auto finish = [&](int i) __attribute__((always_inline)) {       // sc[i] holds P by now
-                if (DROP) {     // dp holds dP (else dP - D); element i of this lane is key jb + 8 (i / 4) + 4 hh + i % 4
-                    if ((i & 3) == 0)
-                        ck4 = *reinterpret_cast<const u32x4 *>(ck_ring + (((jb >> 6) & 3) * C::BC + (jb & 63) + 8 * (i >> 2) + 4 * hh) * 4);
-                    dp[i] = fmaf(dp[i], drop_keep(drop_rk, ck4[i & 3], dr.thr) ? dr.scale : 0.f, -Dr);
+        struct Block { f32x4 v[2][2]; };                // [key block i][row block j]: element v of this lane is key 16 i + 4 g + v
+        u32x4 ck4;      // dropout: the column keys of four consecutive keys, read when the first is due
+        auto b_elems = [&](Block &sc, Block &dp, int jb, int e0, int e1, Frag<bf16_t> (&df)[2]) __attribute__((always_inline)) {
+            auto finish = [&](int e) __attribute__((always_inline)) {       // sc holds P by now
+                const int i = e >> 3, j = e >> 2 & 1, v = e & 3;
+                f32x4 &d4 = dp.v[i][j];
+                if (DROP) {     // d4 holds dP (else dP - D)
+                    if ((e & 7) == 0)
+                        ck4 = *reinterpret_cast<const u32x4 *>(ck_ring + (((jb >> 6) & 3) * C::BC + (jb & 63) + 16 * i + 4 * g) * 4);
+                    d4[v] = fmaf(d4[v], drop_keep(drop_rk[j], ck4[v], dr.thr) ? dr.scale : 0.f, -Dr[j]);
                 }
-                dp[i] = sc[i] * dp[i];
-                if (i & 1) { df[i >> 3].v[(i & 7) - 1] = (bf16_t)dp[i - 1]; df[i >> 3].v[i & 7] = (bf16_t)dp[i]; }
+                d4[v] = sc.v[i][j][v] * d4[v];
+                if (v & 1) { df[j].v[4 * i + v - 1] = (bf16_t)d4[v - 1]; df[j].v[4 * i + v] = (bf16_t)d4[v]; }
             };
 #pragma unroll
             for (int e = e0; e < e1; ++e) {
-                sc[e] = fast_exp2(sc[e] * c - L2);
+                f32x4 &p4 = sc.v[e >> 3][e >> 2 & 1];
+                p4[e & 3] = fast_exp2(p4[e & 3] * c - L2[e >> 2 & 1]);
                 if (e > 0) finish(e - 1);
                 if (e == 15) finish(15);
             }
         };
         // Where the causal diagonal or the end of the sequence crosses a block (first key jb), the
-        // masked elements of its finished S^T accumulator are set to -inf before B, which turns them
+        // masked elements of its finished S^T are set to -inf before B, which turns them
         // into P = dS = 0: keys after the lane's row, and keys past the sequence (whose loads
-        // re-read its last row).  C-tile element e of this lane is key 8*(e/4) + 4*hh + e%4 of the block.
-        auto mask_s = [&](int jb, f32x16 &sc) __attribute__((always_inline)) {
+        // re-read its last row).
+        auto mask_s = [&](int jb, Block &sc) __attribute__((always_inline)) {
             // (positions are below 2^30, checked on the host: 32-bit scalar compares, no vector work per step)
             const bool diag = s.causal && (jb + 31 > (int)s.s0 + rw0);
             if (diag || jb + 32 > s.l_x) {
-                const int last = s.causal ? min((int)s.s0 + r, s.l_x - 1) : s.l_x - 1;
-                const int rel = max(min(last - jb - 4 * hh, 64), -1);
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    if (8 * (e >> 2) + (e & 3) > rel) sc[e] = -INFINITY;
+                for (int j = 0; j < 2; ++j) {
+                    const int last = s.causal ? min((int)s.s0 + rw0 + 16 * j + lq, s.l_x - 1) : s.l_x - 1;
+                    const int rel = max(min(last - jb - 4 * g, 64), -1);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            if (16 * i + v > rel) sc.v[i][j][v] = -INFINITY;
+                }
             }
         };
 
         // One pipeline step.  A: block (tile_a, kb2_a) into (sc_a, dp_a).  B: (sc_b, dp_b), first key
-        // jb_b, packing into df_b.  C: block (tile_c, kb2_c) from df_c into acc.  Per unit the matrix
-        // instructions go C, A, A (A, A, C in the last unit); after each one come the B elements that fall to its slot.
+        // jb_b, packing into df_b.  C: block (tile_c, kb2_c) from df_c into acc.  Per unit two matrix
+        // instructions of C and four of A (A first in the last unit); after each one come the B elements that fall to its slot.
         // Operand fragments are read from LDS one unit ahead of their use; those of the first unit
         // by the step before (ak[0], av[0], ck[0] on entry), and this step leaves there those of
         // the next step: A on block (tile_an, kb2_an), C on (tile_cn, kb2_cn).  `mid` runs before
         // those last reads: the even steps put the loop's barrier there, because the next step's
         // blocks may lie in the tile that the barrier publishes.
         Frag<bf16_t> ak[2], av[2], ck[2];
-        auto step = [&](auto has_a, auto has_b, auto has_c, const char *tile_a, int kb2_a, f32x16 &sc_a, f32x16 &dp_a,
-                        f32x16 &sc_b, f32x16 &dp_b, int jb_b, Frag<bf16_t> (&df_b)[2], const char *tile_c, int kb2_c,
+        auto step = [&](auto has_a, auto has_b, auto has_c, const char *tile_a, int kb2_a, Block &sc_a, Block &dp_a,
+                        Block &sc_b, Block &dp_b, int jb_b, Frag<bf16_t> (&df_b)[2], const char *tile_c, int kb2_c,
                         Frag<bf16_t> (&df_c)[2], const char *tile_an, int kb2_an, const char *tile_cn, int kb2_cn, auto &&mid)
             __attribute__((always_inline)) {
             constexpr bool HA = decltype(has_a)::value, HB = decltype(has_b)::value, HC = decltype(has_c)::value;
-            constexpr int NS = 3 * NU;                  // slots; 16 elements of B spread over them
+            constexpr int NS = 6 * NU;                  // slots; 16 elements of B spread over them
             static_assert(NU % 2 == 0, "fragment double buffers assume an even number of units");
             auto b_slot = [&](int slot) __attribute__((always_inline)) {
                 if (HB) {
                     const int e0 = slot * 16 / NS, e1 = (slot + 1) * 16 / NS;
+                    if (e0 == e1) return;
                     __builtin_amdgcn_sched_barrier(0);
                     b_elems(sc_b, dp_b, jb_b, e0, e1, df_b);
                     __builtin_amdgcn_sched_barrier(0);
@@ -242,33 +256,45 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
                 mask_s(jb_b, sc_b);
                 // B's inputs pass through an empty asm here: its arithmetic depends on nothing else in
                 // this step, and the compiler would otherwise move all of it out of the step, in one lump
-                asm volatile("" : "+v"(sc_b), "+v"(dp_b));
+#pragma unroll
+                for (int i = 0; i < 2; ++i) asm volatile("" : "+v"(sc_b.v[i][0]), "+v"(sc_b.v[i][1]), "+v"(dp_b.v[i][0]), "+v"(dp_b.v[i][1]));
             }
+            auto do_a = [&](int u, int slot) __attribute__((always_inline)) {
+                const int i = u % 2, ks = u / 2;
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    if (HA) sc_a.v[i][j] = mma16(ak[u & 1], qf[2 * ks + j], ks == 0 ? zero4 : sc_a.v[i][j]);
+                    b_slot(slot + j);
+                }
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    if (HA) dp_a.v[i][j] = mma16(av[u & 1], gf[2 * ks + j], ks == 0 ? (DROP ? zero4 : neg_d[j]) : dp_a.v[i][j]);
+                    b_slot(slot + 2 + j);
+                }
+            };
+            auto do_c = [&](int u, int slot) __attribute__((always_inline)) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    if (HC) acc[u][j] = mma16(ck[u & 1], df_c[j], acc[u][j]);
+                    b_slot(slot + j);
+                }
+            };
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
-                const int half = u / (D / 32), db = u % (D / 32);
                 if (u + 1 < NU) {
                     if (HC) load_c(tile_c, kb2_c, u + 1, ck[(u + 1) & 1]);
                     if (HA) load_a(tile_a, kb2_a, u + 1, ak[(u + 1) & 1], av[(u + 1) & 1]);
                     __builtin_amdgcn_sched_barrier(0);
-                    if (HC) acc[db] = mma(ck[u & 1], df_c[half], acc[db]);
-                    b_slot(3 * u);
-                    if (HA) sc_a = mma(ak[u & 1], qf[u], u == 0 ? zero16 : sc_a);
-                    b_slot(3 * u + 1);
-                    if (HA) dp_a = mma(av[u & 1], gf[u], u == 0 ? (DROP ? zero16 : neg_d) : dp_a);
-                    b_slot(3 * u + 2);
+                    do_c(u, 6 * u);
+                    do_a(u, 6 * u + 2);
                 } else {
                     // last unit: A first, so that its results are there when the next step's B wants them
-                    if (HA) sc_a = mma(ak[u & 1], qf[u], sc_a);
-                    b_slot(3 * u);
-                    if (HA) dp_a = mma(av[u & 1], gf[u], dp_a);
-                    b_slot(3 * u + 1);
+                    do_a(u, 6 * u);
                     mid();
                     load_c(tile_cn, kb2_cn, 0, ck[0]);
                     load_a(tile_an, kb2_an, 0, ak[0], av[0]);
                     __builtin_amdgcn_sched_barrier(0);
-                    if (HC) acc[db] = mma(ck[u & 1], df_c[half], acc[db]);
-                    b_slot(3 * u + 2);
+                    do_c(u, 6 * u + 4);
                 }
             }
             // ... and its results through another one, so that it is not sunk below the step either
@@ -295,16 +321,16 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
                 cur = cur == C::RING - 1 ? 0 : cur + 1;
             }
         } else if (KG == 1 || T > 0) {
-            f32x16 sc0, dp0, sc1, dp1;                      // even / odd blocks
+            Block sc0, dp0, sc1, dp1;                       // even / odd blocks
             Frag<bf16_t> df0[2], df1[2];
             // step -1: A(0) alone.  The first loop step has no C(-1): it multiplies zeros with tile 0 instead.
             load_a(ring, 0, 0, ak[0], av[0]);
             auto nothing = [] {};
             step(true_type{}, false_type{}, false_type{}, ring, 0, sc0, dp0, sc1, dp1, 0, df0, ring, 0, df1, ring, 1, ring, 1, nothing);
     #pragma unroll
-            for (int half = 0; half < 2; ++half)
+            for (int j = 0; j < 2; ++j)
     #pragma unroll
-                for (int e = 0; e < 8; ++e) df1[half].v[e] = (bf16_t)0.f;
+                for (int e = 0; e < 8; ++e) df1[j].v[e] = (bf16_t)0.f;
 
             int cur = 0;                                    // ring slot of tile t
             for (int t = 0; t < T; ++t) {
@@ -344,48 +370,29 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
     if constexpr (KG > 1) {
         // The groups' sums meet in LDS, where the tiles were: each adds up half the columns, in group order.
         static_assert(KG == 2 && D == 64, "");
-        auto hand = [&](int e4) { return reinterpret_cast<f32x4 *>(smem + ((group * C::WAVES + wave) * 4 + e4) * 1024 + lane * 16); };
-        auto other = [&](int e4) { return reinterpret_cast<f32x4 *>(smem + (((group ^ 1) * C::WAVES + wave) * 4 + e4) * 1024 + lane * 16); };
+        auto hand = [&](int of, int u) { return reinterpret_cast<f32x4 *>(smem + ((of * C::WAVES + wave) * NU + u) * 1024 + lane * 16); };
         __syncthreads();
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-            f32x4 v;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = group == 0 ? acc[1][4 * e4 + i] : acc[0][4 * e4 + i];
-            *hand(e4) = v;
-        }
+        for (int u = 0; u < NU; ++u) *hand(group, u) = group == 0 ? acc[NU / 2 + u / 2][u % 2] : acc[u / 2][u % 2];
         __syncthreads();
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-            const f32x4 v = *other(e4);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[0][4 * e4 + i] = (group == 0 ? acc[0][4 * e4 + i] : acc[1][4 * e4 + i]) + v[i];
-        }
+        for (int u = 0; u < NU; ++u)
+            acc[u / 2][u % 2] = (group == 0 ? acc[u / 2][u % 2] : acc[NU / 2 + u / 2][u % 2]) + *hand(group ^ 1, u);
     }
-    if (!row_ok) return;
     const float scale = 1.f / sqrtf((float)D);
-    constexpr int DB = KG > 1 ? 1 : D / 32;             // (two groups: column block `group`, in acc[0])
-    const int first_col = KG > 1 ? 32 * group : 0;
-    if (n_splits == 1) {
-        bf16_t *dst0 = dq + ((int64_t)b * s.l_s + r) * ld + (int64_t)h * D + first_col;
+    constexpr int DB = KG > 1 ? NU / 2 : NU;            // (two groups: half the column blocks, in the first half of acc)
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+    for (int j = 0; j < 2; ++j) {
+        const int r = rw0 + 16 * j + lq;
+        if (r >= s.l_s) continue;
+        const int64_t at = ((int64_t)b * s.l_s + r) * ld + (int64_t)h * D + (KG > 1 ? 16 * DB * group : 0) + 4 * g;
 #pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4)
-                *reinterpret_cast<bf16x4 *>(dst0 + db * 32 + 8 * e4 + 4 * hh) =
-                    pack4(acc[db][4 * e4] * scale, acc[db][4 * e4 + 1] * scale, acc[db][4 * e4 + 2] * scale,
-                          acc[db][4 * e4 + 3] * scale);
-    } else {
-        float *dst0 = dq_part + (int64_t)split * s.B * s.l_s * ld + ((int64_t)b * s.l_s + r) * ld + (int64_t)h * D + first_col;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) {
-                f32x4 val;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) val[i] = acc[db][4 * e4 + i] * scale;
-                *reinterpret_cast<f32x4 *>(dst0 + db * 32 + 8 * e4 + 4 * hh) = val;
-            }
+        for (int db = 0; db < DB; ++db) {
+            const f32x4 a = acc[db][j];
+            const f32x4 val = {a[0] * scale, a[1] * scale, a[2] * scale, a[3] * scale};
+            if (n_splits == 1) *reinterpret_cast<bf16x4 *>(dq + at + 16 * db) = pack4(val[0], val[1], val[2], val[3]);
+            else *reinterpret_cast<f32x4 *>(dq_part + (int64_t)split * s.B * s.l_s * ld + at + 16 * db) = val;
+        }
     }
 }
 
