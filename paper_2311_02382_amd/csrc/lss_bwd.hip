@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void bwd_dq_merge_kernel(const float *__restri
     for (int e = 0; e < 4; ++e) dq[i * 4 + e] = (T)acc[e];
 }
 
-// (float, d = 128, and segments of at most 64 rows; see pick_bwd_plan for the others)
+// (bf16 at d = 128 or with at most 64 rows; see pick_bwd_plan and pick_float_splits for the others)
 // The dQ workgroups share their launch with the dK/dV ones and need not fill the chip alone: keys are split so far that
 // a dQ workgroup does not outlast the rest of the launch, never further than the workspace was sized for.  In 64-key
 // tiles of dQ, of which a lone workgroup takes one per 1.0 us (d = 64) or 1.4 us (d = 128):
@@ -65,32 +65,27 @@ __global__ __launch_bounds__(256) void bwd_dq_merge_kernel(const float *__restri
 //     compute unit works off per us, and the zero-filled rows), but 24 to 64 tiles: 130 rows against 13,000 keys
 //     take 54 us in ranges of 51 tiles and 38 in ranges of 26; in longer launches shorter ranges gain nothing.
 //     Where one workgroup fills a compute unit (d = 128), a launch that fits the chip keeps fitting it.
-//   * float: 16 tiles (each takes four times as long).
-static int pick_dq_splits(const SegShape &s, int most, int elem_bytes)
+static int pick_dq_splits(const SegShape &s, int most)
 {
-    const int rows_per_wg = dq_rows_per_wg(elem_bytes, s.d);
+    const int rows_per_wg = dq_rows_per_wg(2, s.d);
     if (most <= 1) return 1;
     const int64_t bhs = (int64_t)s.B * s.H, seen = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
     const int64_t tiles = (seen + 63) / 64;                                     // key tiles of a query tile
     const int64_t dq_wgs = bhs * ((s.l_s + rows_per_wg - 1) / rows_per_wg), dkv_wgs = bhs * ((seen + 127) / 128);
     int64_t want = 1;
-    if (elem_bytes == 4) {
-        want = (tiles + 15) / 16;
-    } else {
-        struct Rate { double tile_us, dkv, dq; };
-        const Rate rate = s.d == 64 ? Rate{1.0, 0.74, 1.25} : Rate{1.4, 0.5, 0.7};
-        const double q_tiles = (double)((s.l_s + 63) / 64), walk = s.l_s <= 64 ? 8.0 : 1.35 * q_tiles;
-        const double us = ((double)dkv_wgs * q_tiles / rate.dkv + (double)dq_wgs * tiles / rate.dq) / 256.0 +
-                          (double)(s.l_x - seen) * bhs * s.d * 8.0 / 5.5e6;
-        double longest = 1.5 * us / rate.tile_us;
-        if (longest < 24.0) longest = 24.0;
-        if (longest < walk) longest = walk;
-        if (longest > 64.0) longest = 64.0;
-        want = (int64_t)ceil((double)tiles / longest);
-        const int64_t idle = (256 - dkv_wgs - (s.l_x - seen) * bhs / 512) / dq_wgs, fill = (int64_t)((double)tiles / (walk > 4.0 ? walk : 4.0));
-        if (idle >= want) want = fill <= want ? want : idle < fill ? idle : fill;
-        else if (s.d == 128 && idle >= 1) want = idle;
-    }
+    struct Rate { double tile_us, dkv, dq; };
+    const Rate rate = s.d == 64 ? Rate{1.0, 0.74, 1.25} : Rate{1.4, 0.5, 0.7};
+    const double q_tiles = (double)((s.l_s + 63) / 64), walk = s.l_s <= 64 ? 8.0 : 1.35 * q_tiles;
+    const double us = ((double)dkv_wgs * q_tiles / rate.dkv + (double)dq_wgs * tiles / rate.dq) / 256.0 +
+                      (double)(s.l_x - seen) * bhs * s.d * 8.0 / 5.5e6;
+    double longest = 1.5 * us / rate.tile_us;
+    if (longest < 24.0) longest = 24.0;
+    if (longest < walk) longest = walk;
+    if (longest > 64.0) longest = 64.0;
+    want = (int64_t)ceil((double)tiles / longest);
+    const int64_t idle = (256 - dkv_wgs - (s.l_x - seen) * bhs / 512) / dq_wgs, fill = (int64_t)((double)tiles / (walk > 4.0 ? walk : 4.0));
+    if (idle >= want) want = fill <= want ? want : idle < fill ? idle : fill;
+    else if (s.d == 128 && idle >= 1) want = idle;
     return (int)(want < 1 ? 1 : want > most ? most : want);
 }
 
@@ -138,6 +133,48 @@ static BwdPlan pick_bwd_plan(const SegShape &s, int most)
     return best;
 }
 
+// float: a launch takes about, in us,
+//     start + (longest^6 + balance^6)^(1/6) + zeros / 5 MB + merge
+// as for bf16 above: the longer of a dQ workgroup's walk over its 64-key tiles and a dK/dV workgroup's over the 64-row query tiles
+// (half the time where two wavefronts share a key block), slower as two workgroups share a compute unit; all walks over 256 compute units,
+// and a part of a last dK/dV walk where the launch takes more than one round. Fitted to 290 launches (30 .. 12,661 rows, 512 .. 22,136
+// keys, 2 .. 32 heads, 1 .. 16 splits, after a forward call each). Ranges of 16 tiles, what every launch had, remain unless the estimate
+// is 5 % better: launches took 12.5 % more with them on average (4 heads of 100 rows against 1000 keys 66 us, in four ranges 31; 8 of 391 rows
+// against 1084 keys: 46 and 35), 5 % of them lose more than 2 %, the choice costs 4 % over the best.
+static int pick_float_splits(const SegShape &s, int most)
+{
+    struct Cost { double start, dq_us, dq_more, dkv_us, dkv_halves_us, dkv_more, dkv_slow, rate, last, merge_rate; };
+    static const Cost d64 = {4.3, 3.95, 0.0, 6.8, 3.3, 0.2, 0.136, 0.717, 0.36, 1.1}, d128 = {0.0, 7.0, 0.6, 7.8, 7.8, 1.5, 0.0, 0.97, 0.58, 1.5};
+    const Cost &c = s.d == 64 ? d64 : d128;
+    const double bhs = (double)s.B * s.H, room = s.d == 64 ? 512.0 : 256.0;      // workgroups that fit the chip
+    const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x, first = s.causal ? s.s0 + (s.l_s < 128 ? s.l_s : 128) : (int64_t)s.l_x;
+    const int64_t tiles = (seen + 63) / 64, q_tiles = (s.l_s + 63) / 64, dq_tiles = (s.l_s + 127) / 128;
+    const double mean_tiles = 0.5 * (double)(((first < seen ? first : seen) + 63) / 64 + tiles);
+    const double zeros_mb = (double)(s.l_x - seen) * bhs * s.d * 8e-6, dq_m = bhs * s.l_s * s.d * 1e-6;
+    auto estimate = [&](int sp) {
+        const bool halves = f32_bwd_halves(s, sp);
+        const int64_t keys = halves ? 64 : 128, key_tiles = (seen + keys - 1) / keys;
+        const int64_t full = s.causal && s.s0 / keys < key_tiles ? s.s0 / keys : key_tiles;     // key tiles that all rows see; the others half of them
+        const double dkv_us = halves ? c.dkv_halves_us : c.dkv_us, n_dq = (double)dq_tiles * bhs * sp, n_dkv = (double)key_tiles * bhs, N = n_dq + n_dkv;
+        const double shared = N < 256.0 ? 0.0 : N > 512.0 ? 1.0 : N / 256.0 - 1.0;
+        const double dq = ((double)((tiles + sp - 1) / sp) + c.dq_more) * c.dq_us, dkv = ((double)q_tiles + c.dkv_more) * dkv_us;
+        const double longest = (dq > dkv ? dq : dkv) * (1.0 + c.dkv_slow * shared);
+        double balance = c.rate / 256.0 * (((double)dq_tiles * bhs * mean_tiles + n_dq * c.dq_more) * c.dq_us +
+                                           (bhs * ((double)full + 0.5 * (double)(key_tiles - full)) * (double)q_tiles + n_dkv * c.dkv_more) * dkv_us);
+        if (N > room) balance += c.last * dkv;
+        const double t = c.start + pow(pow(longest, 6.0) + pow(balance, 6.0), 1.0 / 6.0) + zeros_mb / 5.0;
+        return sp > 1 ? t + 3.0 + dq_m * (8 * sp + 4) / c.merge_rate : t;
+    };
+    int best = (int)((tiles + 15) / 16);
+    if (best > most) best = most;
+    double best_t = 0.95 * estimate(best);
+    for (int sp = 1; sp <= most; ++sp) {
+        const double t = estimate(sp);
+        if (t < best_t) { best_t = t; best = sp; }
+    }
+    return best;
+}
+
 template <typename T, int D>
 static hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const T *q, const T *k, const T *v, const T *out,
                                const float *lse, const T *dO, T *dq, float *dk_part, float *dv_part,
@@ -150,7 +187,9 @@ static hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const T *q
     const size_t rows_bytes = (size_t)s.B * s.l_s * s.H * D * sizeof(T), part_bytes = (size_t)s.B * s.l_x * s.H * D * sizeof(float);
     const bool out_first = overlaps(dq, rows_bytes, out, rows_bytes) || overlaps(dk_part, part_bytes, out, rows_bytes) ||
                            overlaps(dv_part, part_bytes, out, rows_bytes);
-    const BwdPlan plan = sizeof(T) == 2 && D == 64 && s.l_s > 64 ? pick_bwd_plan(s, most) : BwdPlan{pick_dq_splits(s, most, (int)sizeof(T)), 1};
+    const BwdPlan plan = sizeof(T) == 4              ? BwdPlan{pick_float_splits(s, most), 1}
+                         : D == 64 && s.l_s > 64 ? pick_bwd_plan(s, most)
+                                                 : BwdPlan{pick_dq_splits(s, most), 1};
     const int dq_splits = plan.splits;
     const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x;
     const int dq_tiles = (int)(((seen + 63) / 64 + dq_splits - 1) / dq_splits + plan.groups - 1) / plan.groups;

@@ -9,15 +9,16 @@
 // floats is then nine products of parts, |x_i y_j| <= 2^-8(i+j) |x y|, each exact in the matrix core's fp32
 // accumulation.  The six with i + j <= 2 are added, smallest first; the three left out are together below 2^-23
 // of |x y|, the size of the rounding an fp32 multiply-add makes at every step, while a matrix instruction here
-// adds 16 products per rounding instead of two (with eight of the nine the errors below stay as they are).
-// Relative errors against fp64 (512 rows, 2000 keys, N(0, 1) inputs; in brackets those of V_MFMA_F32_32X32X2_F32,
-// which these kernels used before): out 4.4e-7 (5.8e-7), dq 4.9e-7 (6.4e-7), dk 5.4e-7 (7.0e-7), dv 5.4e-7 (6.8e-7);
-// at three times the standard deviation out 1.0e-6 (1.5e-6), dq 2.9e-6 (3.5e-6).
-// What it buys: six V_MFMA_F32_32X32X16_BF16 (192 cycles) do what eight 32x32x2 fp32 ones (512 cycles) did.
-// lx8k in single precision, eight segments: forward 1605 -> 910 us, backward 5460 -> 2750 us.  Each further
-// segment of lx8k costs 64 us backward (1.4 PFLOP/s of executed bf16 products, what the chip sustains on
-// random data); what is left is the chain of a workgroup's tiles in launches that fill the chip once or twice, and
-// in the forward the vector work (splitting costs 5.5 instructions for every float of a tile and every weight).
+// adds 32 products per rounding instead of two (with eight of the nine the errors below stay as they are).
+// Relative errors against fp64 (512 rows, 2000 keys, N(0, 1) inputs; in brackets those of V_MFMA_F32_32X32X2_F32, which these kernels
+// used at first): out 4.4e-7 (5.8e-7), dq 4.1e-7 (6.4e-7), dk 5.4e-7 (7.0e-7), dv 5.4e-7 (6.8e-7); at three times the standard
+// deviation out 1.0e-6 (1.5e-6), dq 2.8e-6 (3.5e-6).
+// What it buys: six V_MFMA_F32_16X16X32_BF16 (96 cycles) do what eight 16x16x4 fp32 ones (256 cycles) did: lx8k in single
+// precision, eight segments: forward 1605 -> 910 us, backward 5460 -> 2750 us (with 32x32x16 instructions).
+// 16x16x32 instructions take less power per product than 32x32x16 and add twice as many products per rounding: with them, operands read
+// one step ahead of their use and a maximum that is raised only when it must be, forward 892 -> 816 us, backward 2738 -> 2553
+// (the same eight segments, another card). What is left is the chain of a workgroup's tiles in launches that fill the chip
+// once or twice, and in the forward the vector work (splitting costs 5.5 instructions for every float of a tile and every weight).
 //
 // Operand roles, layouts and the online softmax are those of the bf16 kernels: scores transposed with one query
 // per lane in the forward and dQ workgroups, one key per lane in the dK/dV workgroups; K/V (or Q/dO) tiles go
@@ -87,47 +88,64 @@ __device__ __forceinline__ bool some_below(const f32x4 (&x)[N], float limit)
         for (int e = 0; e < 4; ++e) least_nonzero = min(least_nonzero, twice_magnitude(x[i][e]) - 1u);
     return least_nonzero < twice_magnitude(limit) - 1u;
 }
-// This lane's fragments of a row: D / 16 times 8 floats, 16 apart.  Returns whether some lane's row holds tiny values.
+// This lane's fragments of two rows: D / 32 times 8 floats of each, 32 apart.  Returns whether some lane's rows hold tiny values.
 template <int D>
-__device__ __forceinline__ bool split_row(const float *p, Frag3 (&f)[D / 16])
+__device__ __forceinline__ bool split_rows(const float *const (&p)[2], Frag3 (&f)[D / 32][2])
 {
     float least = INFINITY;
+    f32x4 v[D / 32][2][2];
 #pragma unroll
-    for (int kb = 0; kb < D / 16; ++kb) {
-        const f32x4 v[2] = {*reinterpret_cast<const f32x4 *>(p + kb * 16), *reinterpret_cast<const f32x4 *>(p + kb * 16 + 4)};
-        least = least_magnitude(v, least);
-        const float x[8] = {v[0][0], v[0][1], v[0][2], v[0][3], v[1][0], v[1][1], v[1][2], v[1][3]};
-        f[kb] = split8(x);
-    }
+    for (int ks = 0; ks < D / 32; ++ks)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int n = 0; n < 2; ++n) v[ks][j][n] = *reinterpret_cast<const f32x4 *>(p[j] + ks * 32 + 4 * n);
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const f32x4 *const w = v[ks][j];
+            least = least_magnitude(v[ks][j], least);
+            const float x[8] = {w[0][0], w[0][1], w[0][2], w[0][3], w[1][0], w[1][1], w[1][2], w[1][3]};
+            f[ks][j] = split8(x);
+        }
     bool tiny = false;
     if (__any(least < kTiny)) {
 #pragma unroll 1
-        for (int kb = 0; kb < D / 16; ++kb) {
-            const f32x4 v[2] = {*reinterpret_cast<const f32x4 *>(p + kb * 16), *reinterpret_cast<const f32x4 *>(p + kb * 16 + 4)};
-            tiny = tiny || some_below(v, kTiny);
-        }
+        for (int ks = 0; ks < D / 32; ++ks)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const f32x4 w[2] = {*reinterpret_cast<const f32x4 *>(p[j] + ks * 32), *reinterpret_cast<const f32x4 *>(p[j] + ks * 32 + 4)};
+                tiny = tiny || some_below(w, kTiny);
+            }
         tiny = __any(tiny);
     }
     return tiny;
 }
-__device__ __forceinline__ Frag3 split_acc(const f32x16 &c, int half)      // slots 8 half .. of a C tile
+// 32 tile rows against the wavefront's 32 queries (or keys) as 16 x 16 blocks: element e of block (i, j) is, in lane
+// l, tile row 16 i + 4 (l / 16) + e and query 16 j + l % 16.
+struct Block { f32x4 v[2][2]; };
+__device__ __forceinline__ Frag3 split_acc(const Block &c, int j)      // as the operand of a product over the tile rows
 {
     float x[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = c[8 * half + e];
+    for (int e = 0; e < 8; ++e) x[e] = c.v[e >> 2][j][e & 3];
     return split8(x);
 }
-__device__ __forceinline__ f32x16 mma_small(const Frag3 &a, const Frag3 &b, f32x16 c)       // the five products below x0 y0
+// The five products below x0 y0, of one operand with two others: two chains, so that no instruction waits for the one before
+__device__ __forceinline__ void mma_small(const Frag3 &a, const Frag3 (&b)[2], f32x4 (&c)[2])
 {
-    c = mma(a.p[2], b.p[0], c);
-    c = mma(a.p[0], b.p[2], c);
-    c = mma(a.p[1], b.p[1], c);
-    c = mma(a.p[1], b.p[0], c);
-    return mma(a.p[0], b.p[1], c);
+    constexpr int pa[5] = {2, 0, 1, 1, 0}, pb[5] = {0, 2, 1, 0, 1};
+#pragma unroll
+    for (int t = 0; t < 5; ++t)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) c[j] = mma16(a.p[pa[t]], b[j].p[pb[t]], c[j]);
 }
-__device__ __forceinline__ f32x16 mma6(const Frag3 &a, const Frag3 &b, f32x16 c)
+__device__ __forceinline__ void mma6(const Frag3 &a, const Frag3 (&b)[2], f32x4 (&c)[2])
 {
-    return mma(a.p[0], b.p[0], mma_small(a, b, c));
+    mma_small(a, b, c);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) c[j] = mma16(a.p[0], b[j].p[0], c[j]);
 }
 
 // A [ROWS][D] float tile as three bf16 planes in LDS, each laid out like a DirectTile<D, ROWS>.
@@ -169,7 +187,7 @@ struct PlaneTile {
             for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x8 *>(tile + p * PLANE + chunk_offset(c / CPR, c % CPR)) = f.p[p].v;
         }
     }
-    // A-operand fragment of rows [row0, row0 + 32), operand step kb
+    // A-operand fragment of rows [row0, row0 + 16)
     static __device__ __forceinline__ Frag3 rows_frag(const char *tile, int row0, int off)
     {
         Frag3 f;
@@ -177,29 +195,54 @@ struct PlaneTile {
         for (int p = 0; p < 3; ++p) f.p[p] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(tile + p * PLANE + row0 * (D * 2) + off));
         return f;
     }
-    static __device__ __forceinline__ Frag<bf16_t> rows_frag_high(const char *tile, int row0, int off)
+    // 32 tile rows against the operand `b` over the whole width: every step's small products first, the
+    // large ones at the end, so that the sum is rounded at its full size D / 32 times and not six times as often
+    // (scores and dP enter differences of large terms).
+    // Operands are read one step ahead of their use: `ahead` holds those of the first step on entry, and what `next` reads on return.
+    template <typename Next>
+    static __device__ __forceinline__ Block product(const char *tile, int row0, const int (&off)[D / 32], const Frag3 (&b)[D / 32][2], Frag3 &ahead,
+                                                    Next &&next)
     {
-        return load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(tile + row0 * (D * 2) + off));
-    }
-    // C tile of 32 tile rows against the operand `b` over the whole width: every step's small products first, the
-    // large ones at the end, so that the sum is rounded at its full size D / 16 times and not six times as often
-    // (scores and dP enter differences of large terms).  The large products read the first plane again.
-    static __device__ __forceinline__ f32x16 product(const char *tile, int row0, const int (&off)[D / 16], const Frag3 (&b)[D / 16])
-    {
-        f32x16 c = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        constexpr int NS = D / 32;
+        Block c;
+        Frag<bf16_t> high[NS];
 #pragma unroll
-        for (int kb = 0; kb < D / 16; ++kb) c = mma_small(rows_frag(tile, row0, off[kb]), b[kb], c);
+        for (int u = 0; u < 2 * NS; ++u) {
+            const int i = u / NS, ks = u % NS;
+            const Frag3 a = ahead;
+            ahead = u + 1 < 2 * NS ? rows_frag(tile, row0 + 16 * ((u + 1) / NS), off[(u + 1) % NS]) : next();
+            __builtin_amdgcn_sched_barrier(0);
+            if (ks == 0) c.v[i][0] = c.v[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            high[ks] = a.p[0];
+            mma_small(a, b[ks], c.v[i]);
+            if (ks == NS - 1) {
 #pragma unroll
-        for (int kb = 0; kb < D / 16; ++kb) c = mma(rows_frag_high(tile, row0, off[kb]), b[kb].p[0], c);
+                for (int k2 = 0; k2 < NS; ++k2)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) c.v[i][j] = mma16(high[k2], b[k2][j].p[0], c.v[i][j]);
+            }
+        }
         return c;
     }
-    // ... of the transposed tile: rows [row0, row0 + 16) are the contraction slots (load_frag_tr_sw)
+    // ... of the transposed tile: rows [row0, row0 + 32) are the contraction slots (load_frag_tr16_sw)
     static __device__ __forceinline__ Frag3 cols_frag(const char *tile, int row0, int off)
     {
         Frag3 f;
 #pragma unroll
-        for (int p = 0; p < 3; ++p) f.p[p] = load_frag_tr_sw<D>(tile + p * PLANE, row0, off);
+        for (int p = 0; p < 3; ++p) f.p[p] = load_frag_tr16_sw<D>(tile + p * PLANE, row0, off);
         return f;
+    }
+    // put(db, 16 columns of the transposed tile), each read one ahead, likewise
+    template <typename Put, typename Next>
+    static __device__ __forceinline__ void columns(const char *tile, int row0, const int (&off)[D / 16], Frag3 &ahead, Put &&put, Next &&next)
+    {
+#pragma unroll
+        for (int db = 0; db < D / 16; ++db) {
+            const Frag3 a = ahead;
+            ahead = db + 1 < D / 16 ? cols_frag(tile, row0, off[db + 1]) : next();
+            put(db, a);
+            if (db & 1) __builtin_amdgcn_sched_barrier(0);
+        }
     }
 };
 
@@ -209,67 +252,84 @@ constexpr int kRowsPerWg = 128;             // query rows of a workgroup: four w
 // twice as many workgroups, with chains half as long, for launches that do not fill the chip.
 template <int HALVES> constexpr int kKeysPerWg = 128 / HALVES;
 
-__device__ __forceinline__ void clear(f32x16 &a)
-{
+// A wavefront's sums, transposed: 16 columns x 16 rows (or keys) each
+template <int D> struct Sums {
+    f32x4 v[D / 16][2];
+    __device__ __forceinline__ void clear()
+    {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) a[e] = 0.f;
-}
+        for (int db = 0; db < D / 16; ++db)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) v[db][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+};
 
 // ---- The products on the fp32 matrix cores, operands straight from memory, for what three bf16 parts miss: `tiny` inputs,
 // and infinities, NaNs and values whose first part overflows (3.39e38), which all leave NaN in the results (an infinite x has
 // x - x0 = NaN).  A wavefront with such results, or with results so small that parts of the weights
 // were subnormal, does its rows or keys over again this way, without LDS or barriers (1024 rows against 8192 keys, 16 heads:
-// forward 231 us, over again 735; backward 595 and 2226).  Finding out costs 1.5 % of lx8k and 3 us of a launch of few tiles.
+// forward 206 us, over again 622; backward 556 and 1866).  Finding out costs 1.5 % of lx8k and 3 us of a launch of few tiles.
 
-// C tile of 32 rows of a matrix (this lane's: a) against 32 others (b) over the whole width
+// 32 rows of a matrix (this lane's two: a) against 32 others (b) over the whole width
 template <int D>
-__device__ __forceinline__ f32x16 product_f32(const float *a, const float *b)
+__device__ __forceinline__ Block product_f32(const float *const (&a)[2], const float *const (&b)[2])
 {
-    f32x16 c;
-    clear(c);
-#pragma unroll 1
-    for (int kb = 0; kb < D / 16; ++kb)
+    Block c;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[kb * 16 + e], b[kb * 16 + e], c, 0, 0, 0);
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) c.v[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int ks = 0; ks < D / 32; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    c.v[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][ks * 32 + e], b[j][ks * 32 + e], c.v[i][j], 0, 0, 0);
     return c;
 }
-// acc += transpose of 32 rows (from `rows` on, rows_ok of which exist) x the C tile w of weights
+// acc += transpose of 32 rows (from `rows` on, rows_ok of which exist) x the weights w
 template <int D>
-__device__ __forceinline__ void add_product_f32(const float *rows, int64_t ld, int rows_ok, const f32x16 &w, f32x16 (&acc)[D / 32], int lq,
-                                                int hh)
+__device__ __forceinline__ void add_product_f32(const float *rows, int64_t ld, int rows_ok, const Block &w, Sums<D> &acc, int lq, int g)
 {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const int row = 8 * (e >> 2) + 4 * hh + (e & 3);
+    for (int e = 0; e < 8; ++e) {
+        const int row = 16 * (e >> 2) + 4 * g + (e & 3);
         const float *const p = rows + (int64_t)min(row, rows_ok - 1) * ld + lq;
 #pragma unroll
-        for (int db = 0; db < D / 32; ++db) {
-            const uint32_t x = __builtin_bit_cast(uint32_t, p[db * 32]) & (row < rows_ok ? ~0u : 0u);       // 0 past the end
-            acc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, x), w[e], acc[db], 0, 0, 0);
+        for (int db = 0; db < D / 16; ++db) {
+            const uint32_t x = __builtin_bit_cast(uint32_t, p[db * 16]) & (row < rows_ok ? ~0u : 0u);       // 0 past the end
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc.v[db][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(float, x), w.v[e >> 2][j][e & 3], acc.v[db][j], 0, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);      // (a row at a time: its registers must not add to the main loop's)
     }
 }
 // Whether some result is not finite, or below 2^-100 and not 0 (again looked at closely only where the least magnitude is small)
-template <int N>
-__device__ __forceinline__ bool missed(const f32x16 (&acc)[N])
+template <int D>
+__device__ __forceinline__ bool missed(const Sums<D> &acc)
 {
     float least = INFINITY, zero = 0.f;
     bool small = false;
 #pragma unroll
-    for (int db = 0; db < N; ++db)
+    for (int n = 0; n < D / 8; ++n) {
+        const f32x4 a = acc.v[n >> 1][n & 1];
 #pragma unroll
-        for (int e = 0; e < 16; e += 2) {
-            asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(least) : "v"(acc[db][e]), "v"(acc[db][e + 1]));
-            zero = __builtin_fmaf(acc[db][e], 0.f, zero);               // NaN from infinities and NaNs on
-            zero = __builtin_fmaf(acc[db][e + 1], 0.f, zero);
+        for (int e = 0; e < 4; e += 2) {
+            asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(least) : "v"(a[e]), "v"(a[e + 1]));
+            zero = __builtin_fmaf(a[e], 0.f, zero);                     // NaN from infinities and NaNs on
+            zero = __builtin_fmaf(a[e + 1], 0.f, zero);
         }
+    }
     if (__any(least < 0x1p-100f)) {
         uint32_t least_nonzero = ~0u;
 #pragma unroll
-        for (int db = 0; db < N; ++db)
+        for (int n = 0; n < D / 8; ++n)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) least_nonzero = min(least_nonzero, twice_magnitude(acc[db][e]) - 1u);
+            for (int e = 0; e < 4; ++e) least_nonzero = min(least_nonzero, twice_magnitude(acc.v[n >> 1][n & 1][e]) - 1u);
         small = least_nonzero < twice_magnitude(0x1p-100f) - 1u;
     }
     return small || zero != zero;
@@ -284,12 +344,12 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_f32_kernel(SegShape 
                                                          int n_q_tiles)
 {
     using Tile = PlaneTile<D>;
-    constexpr int NU = D / 16, BC = Tile::ROWS;
+    constexpr int NS = D / 32, BC = Tile::ROWS;
     __shared__ __attribute__((aligned(1024))) char smem[2 * Tile::BYTES + 16];
     char *const sk = smem, *const sv = smem + Tile::BYTES;
     uint32_t *const tiny_word = reinterpret_cast<uint32_t *>(smem + 2 * Tile::BYTES);
 
-    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int bhs = s.B * s.H;
     int bh, inner;
@@ -304,78 +364,102 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_f32_kernel(SegShape 
     const int n_tiles = (kv_end + BC - 1) / BC, per = (n_tiles + n_splits - 1) / n_splits;
     const int t_begin = split * per, t_end = min(n_tiles, t_begin + per);
 
-    // this lane's query row; rows past the segment re-read its last row and are never stored
+    // this lane's two query rows, r + 16 j; rows past the segment re-read its last row and are never stored
     const int r = rw0 + lq;
-    const bool row_ok = r < s.l_s;
-    Frag3 qf[NU];
-    const float *const qp = q + ((int64_t)b * s.l_s + min(r, s.l_s - 1)) * ld + (int64_t)h * D + hh * 8;
-    const bool tiny = split_row<D>(qp, qf);
+    Frag3 qf[NS][2];
+    const float *const qp = q + (int64_t)b * s.l_s * ld + (int64_t)h * D + g * 8;
+    const bool tiny = split_rows<D>({qp + min(r, s.l_s - 1) * ld, qp + min(r + 16, s.l_s - 1) * ld}, qf);
     if (tid == 0) *tiny_word = 0u;
-    f32x16 o[D / 32];
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db) clear(o[db]);
-    float m = -INFINITY, l = 0.f;               // running maximum (log2 domain); this lane's half of the row sum
+    Sums<D> o;
+    o.clear();
+    float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f};     // running maximum (log2 domain); this lane's quarter of the row sum
     const float c = kLog2e / sqrtf((float)D);
-    uint32_t drop_rk = 0u, drop_cs = 0u;
-    if (DROP) { drop_rk = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + r)); drop_cs = drop_col_seed(dr.seed_hi); }
+    uint32_t drop_rk[2] = {0u, 0u}, drop_cs = 0u;
+    if (DROP) {
+        drop_cs = drop_col_seed(dr.seed_hi);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) drop_rk[j] = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + r + 16 * j));
+    }
 
     const float *kbase = k + (int64_t)b * s.l_x * ld + (int64_t)h * D, *vbase = v + (int64_t)b * s.l_x * ld + (int64_t)h * D;
-    int a_off[NU], t_off[D / 32];
+    int a_off[NS], t_off[D / 16];
 #pragma unroll
-    for (int kb = 0; kb < NU; ++kb) a_off[kb] = Tile::chunk_offset(lq, 2 * kb + hh);
+    for (int ks = 0; ks < NS; ++ks) a_off[ks] = Tile::chunk_offset(lq, 4 * ks + g);
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db) t_off[db] = tr_lane_offset_sw<D>(lane, db);
+    for (int db = 0; db < D / 16; ++db) t_off[db] = tr16_lane_offset_sw<D>(lane, db);
 
     // keys [jb, jb + 32): in half kb2 of the tile in LDS, or (EXACT) in memory
     auto block = [&](auto exact, int jb, int kb2) __attribute__((always_inline)) {
         constexpr bool EXACT = decltype(exact)::value;
         // a block no row of this wavefront sees
         if (jb >= s.l_x || (s.causal && jb > (int)s.s0 + rw0 + 31)) return;
-        f32x16 sc;
-        if constexpr (EXACT) sc = product_f32<D>(kbase + (int64_t)min(jb + lq, s.l_x - 1) * ld + hh * 8, qp);
-        else sc = Tile::product(sk, kb2 * 32, a_off, qf);
-        // element e of this lane is key jb + 8 (e / 4) + 4 hh + e % 4
+        Block sc;
+        Frag3 ahead;
+        if constexpr (EXACT) {
+            const float *const kr[2] = {kbase + (int64_t)min(jb + lq, s.l_x - 1) * ld + g * 8, kbase + (int64_t)min(jb + 16 + lq, s.l_x - 1) * ld + g * 8};
+            const float *const qr[2] = {qp + min(r, s.l_s - 1) * ld, qp + min(r + 16, s.l_s - 1) * ld};
+            sc = product_f32<D>(kr, qr);
+        } else {
+            ahead = Tile::rows_frag(sk, kb2 * 32, a_off[0]);
+            sc = Tile::product(sk, kb2 * 32, a_off, qf, ahead, [&] { return Tile::cols_frag(sv, kb2 * 32, t_off[0]); });
+        }
+        // element (i, e) of this lane is key jb + 16 i + 4 g + e
         if ((s.causal && jb + 31 > (int)s.s0 + rw0) || jb + 32 > s.l_x) {
-            const int last = s.causal ? min((int)s.s0 + r, s.l_x - 1) : s.l_x - 1, rel = last - jb - 4 * hh;
 #pragma unroll
-            for (int e = 0; e < 16; ++e)
-                if (8 * (e >> 2) + (e & 3) > rel) sc[e] = -INFINITY;
+            for (int j = 0; j < 2; ++j) {
+                const int last = s.causal ? min((int)s.s0 + r + 16 * j, s.l_x - 1) : s.l_x - 1, rel = last - jb - 4 * g;
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (16 * (e >> 2) + (e & 3) > rel) sc.v[e >> 2][j][e & 3] = -INFINITY;
+            }
         }
-        float mx = sc[0];
+        // The weights subtract the running maximum as it stands, until one would exceed 2^8 (or a row sees its first key): then it is
+        // raised to the exact one and what was accumulated is rescaled.  (The division by the row sum, which uses the
+        // same m, makes the result independent of when m was raised.  EXACT keeps all weights at 1 or below, so that sums of values
+        // near the largest float stay finite.)
+        float mx[2];
 #pragma unroll
-        for (int e = 1; e < 16; ++e) mx = fmaxf(mx, sc[e]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float m_new = fmaxf(m, mx * c);
-        if (__any(m_new > m)) {             // some row's maximum rises: rescale what was accumulated
-            const float alpha = m == -INFINITY ? 0.f : fast_exp2(m - m_new);
-            l *= alpha;
+        for (int j = 0; j < 2; ++j) {
+            mx[j] = sc.v[0][j][0];
 #pragma unroll
-            for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
-            m = m_new;
+            for (int e = 1; e < 8; ++e) mx[j] = fmaxf(mx[j], sc.v[e >> 2][j][e & 3]);
+            mx[j] *= c;
         }
-        const float m_use = m == -INFINITY ? 0.f : m;
+        constexpr float kOver = EXACT ? 0.f : 8.f;
+        if (__any(mx[0] > m[0] + kOver || mx[1] > m[1] + kOver)) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const float p = fast_exp2(sc[e] * c - m_use);
-            l += p;             // the row sum (hence lse and the normalisation) is that of the softmax
-            if (DROP) {
-                const int key = jb + 8 * (e >> 2) + 4 * hh + (e & 3);
-                sc[e] = drop_keep(drop_rk, drop_col_key(drop_cs, (uint32_t)key), dr.thr) ? p * dr.scale : 0.f;
-            } else {
-                sc[e] = p;
+            for (int j = 0; j < 2; ++j) {
+                mx[j] = fmaxf(mx[j], __shfl_xor(mx[j], 16));
+                const float m_new = fmaxf(m[j], fmaxf(mx[j], __shfl_xor(mx[j], 32)));
+                const float alpha = m_new > m[j] ? fast_exp2(m[j] - m_new) : 1.f;
+                l[j] *= alpha;
+#pragma unroll
+                for (int db = 0; db < D / 16; ++db)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o.v[db][j][e] *= alpha;
+                m[j] = m_new;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const float m_use = m[j] == -INFINITY ? 0.f : m[j];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float p = fast_exp2(sc.v[e >> 2][j][e & 3] * c - m_use);
+                l[j] += p;          // the row sum (hence lse and the normalisation) is that of the softmax
+                if (DROP) {
+                    const int key = jb + 16 * (e >> 2) + 4 * g + (e & 3);
+                    p = drop_keep(drop_rk[j], drop_col_key(drop_cs, (uint32_t)key), dr.thr) ? p * dr.scale : 0.f;
+                }
+                sc.v[e >> 2][j][e & 3] = p;
             }
         }
         if constexpr (EXACT) {
-            add_product_f32<D>(vbase + (int64_t)jb * ld, ld, s.l_x - jb, sc, o, lq, hh);
+            add_product_f32<D>(vbase + (int64_t)jb * ld, ld, s.l_x - jb, sc, o, lq, g);
         } else {
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const Frag3 pf = split_acc(sc, half);
-#pragma unroll
-                for (int db = 0; db < D / 32; ++db) o[db] = mma6(Tile::cols_frag(sv, kb2 * 32 + half * 16, t_off[db]), pf, o[db]);
-            }
+            const Frag3 pf[2] = {split_acc(sc, 0), split_acc(sc, 1)};
+            Tile::columns(sv, kb2 * 32, t_off, ahead, [&](int db, const Frag3 &a) __attribute__((always_inline)) { mma6(a, pf, o.v[db]); },
+                          [&] { return ahead; });
         }
     };
     for (int t = t_begin; t < t_end; ++t) {
@@ -394,28 +478,31 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_f32_kernel(SegShape 
         for (int kb2 = 0; kb2 < BC / 32; ++kb2) block(std::false_type{}, t * BC + kb2 * 32, kb2);
     }
     if (rw0 < s.l_s && t_begin < t_end && (tiny || __builtin_amdgcn_readfirstlane((int)*tiny_word) != 0 || __any(missed(o)))) {
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db) clear(o[db]);
-        m = -INFINITY;
-        l = 0.f;
+        o.clear();
+        m[0] = m[1] = -INFINITY;
+        l[0] = l[1] = 0.f;
         for (int jb = t_begin * BC; jb < t_end * BC; jb += 32) block(std::true_type{}, jb, 0);
     }
 
-    const float l_tot = l + __shfl_xor(l, 32);
-    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    const float lse_nat = l_tot > 0.f ? (m + log2f(l_tot)) * kLn2 : -INFINITY;
-    if (!row_ok) return;
-    const int64_t row = ((int64_t)split * bhs + bh) * s.l_s + r;
-    float *op = n_splits == 1 ? out + ((int64_t)b * s.l_s + r) * ld + (int64_t)h * D : o_part + row * D;
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
+    for (int j = 0; j < 2; ++j) {
+        float l_tot = l[j] + __shfl_xor(l[j], 16);
+        l_tot += __shfl_xor(l_tot, 32);
+        const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+        const float lse_nat = l_tot > 0.f ? (m[j] + log2f(l_tot)) * kLn2 : -INFINITY;
+        const int rj = r + 16 * j;
+        if (rj >= s.l_s) continue;
+        const int64_t row = ((int64_t)split * bhs + bh) * s.l_s + rj;
+        float *op = n_splits == 1 ? out + ((int64_t)b * s.l_s + rj) * ld + (int64_t)h * D : o_part + row * D;
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4)
-            *reinterpret_cast<f32x4 *>(op + db * 32 + 8 * e4 + 4 * hh) =
-                f32x4{o[db][4 * e4] * inv, o[db][4 * e4 + 1] * inv, o[db][4 * e4 + 2] * inv, o[db][4 * e4 + 3] * inv};
-    if (hh == 0) {
-        if (n_splits == 1) lse[(int64_t)bh * s.l_s + r] = lse_nat;
-        else lse_part[row] = lse_nat;
+        for (int db = 0; db < D / 16; ++db) {
+            const f32x4 a = o.v[db][j];
+            *reinterpret_cast<f32x4 *>(op + db * 16 + 4 * g) = f32x4{a[0] * inv, a[1] * inv, a[2] * inv, a[3] * inv};
+        }
+        if (g == 0) {
+            if (n_splits == 1) lse[(int64_t)bh * s.l_s + rj] = lse_nat;
+            else lse_part[row] = lse_nat;
+        }
     }
 }
 
@@ -429,10 +516,10 @@ __device__ __forceinline__ void bwd_dq_f32_body(char *smem, const SegShape &s, c
                                                 int n_splits, int q_tile, int n_q_tiles, int bh, int split)
 {
     using Tile = PlaneTile<D>;
-    constexpr int NU = D / 16, BC = Tile::ROWS;
+    constexpr int NS = D / 32, BC = Tile::ROWS;
     char *const sk = smem, *const sv = smem + Tile::BYTES;
     uint32_t *const tiny_word = reinterpret_cast<uint32_t *>(smem + 2 * Tile::BYTES);
-    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = bh / s.H, h = bh % s.H;
     const int r0 = (n_q_tiles - 1 - q_tile) * kRowsPerWg, rw0 = r0 + wave * 32;
@@ -442,87 +529,114 @@ __device__ __forceinline__ void bwd_dq_f32_body(char *smem, const SegShape &s, c
     const int n_tiles = (kv_end + BC - 1) / BC, per = (n_tiles + n_splits - 1) / n_splits;
     const int t_begin = split * per, t_end = min(n_tiles, t_begin + per);
 
-    // rows past the segment re-read its last row, get lse = +inf (P = dS = 0) and are never stored
-    const int r = rw0 + lq, rc = min(r, s.l_s - 1);
-    const bool row_ok = r < s.l_s;
-    Frag3 qf[NU], gf[NU];
+    // this lane's two rows, r + 16 j; rows past the segment re-read its last row, get lse = +inf (P = dS = 0) and are never stored
+    const int r = rw0 + lq;
+    Frag3 qf[NS][2], gf[NS][2];
     bool tiny;
     {
-        const int64_t off = ((int64_t)b * s.l_s + rc) * ld + (int64_t)h * D + hh * 8;
-        tiny = split_row<D>(q + off, qf);
-        tiny = split_row<D>(dO + off, gf) || tiny;
+        const int64_t head = (int64_t)b * s.l_s * ld + (int64_t)h * D + g * 8;
+        const int64_t off[2] = {head + min(r, s.l_s - 1) * ld, head + min(r + 16, s.l_s - 1) * ld};
+        tiny = split_rows<D>({q + off[0], q + off[1]}, qf);
+        tiny = split_rows<D>({dO + off[0], dO + off[1]}, gf) || tiny;
+    }
+    float L2[2], Dr[2], scale[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int rc = min(r + 16 * j, s.l_s - 1);
+        const float lv = lse[(int64_t)bh * s.l_s + rc], l2 = lv * kLog2e;
+        L2[j] = r + 16 * j < s.l_s ? l2 : INFINITY;
+        Dr[j] = Dv[(int64_t)bh * s.l_s + rc];
+        // what l2 was rounded off by (1.93e-8: of kLog2e) is a factor of all the row's weights, hence of its result: dq's
+        // error 4.3e-7 -> 3.9e-7
+        const float off_by = fmaf(lv, kLog2e, -l2) + lv * 1.925963e-8f;
+        scale[j] = (1.f - (fabsf(off_by) < 1.f ? off_by * kLn2 : 0.f)) / sqrtf((float)D);
     }
     if (tid == 0) *tiny_word = 0u;
     if constexpr (D == 128) {       // (operands live in the accumulation half of the register file: see the bf16 dK/dV workgroups)
 #pragma unroll
-        for (int kb = 0; kb < NU; ++kb)
+        for (int n = 0; n < 2 * NS; ++n)
 #pragma unroll
-            for (int p = 0; p < 3; ++p) { asm volatile("" : "+a"(qf[kb].p[p].v)); asm volatile("" : "+a"(gf[kb].p[p].v)); }
+            for (int p = 0; p < 3; ++p) { asm volatile("" : "+a"(qf[n >> 1][n & 1].p[p].v)); asm volatile("" : "+a"(gf[n >> 1][n & 1].p[p].v)); }
     }
-    const float L2 = row_ok ? lse[(int64_t)bh * s.l_s + rc] * kLog2e : INFINITY;
-    const float Dr = Dv[(int64_t)bh * s.l_s + rc];
     const float c = kLog2e / sqrtf((float)D);
-    uint32_t drop_rk = 0u, drop_cs = 0u;
-    if (DROP) { drop_rk = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + r)); drop_cs = drop_col_seed(dr.seed_hi); }
+    uint32_t drop_rk[2] = {0u, 0u}, drop_cs = 0u;
+    if (DROP) {
+        drop_cs = drop_col_seed(dr.seed_hi);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) drop_rk[j] = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + r + 16 * j));
+    }
 
-    f32x16 acc[D / 32];
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db) clear(acc[db]);
+    Sums<D> acc;
+    acc.clear();
     const float *kbase = k + (int64_t)b * s.l_x * ld + (int64_t)h * D, *vbase = v + (int64_t)b * s.l_x * ld + (int64_t)h * D;
-    int a_off[NU], t_off[D / 32];
+    int a_off[NS], t_off[D / 16];
 #pragma unroll
-    for (int kb = 0; kb < NU; ++kb) a_off[kb] = Tile::chunk_offset(lq, 2 * kb + hh);
+    for (int ks = 0; ks < NS; ++ks) a_off[ks] = Tile::chunk_offset(lq, 4 * ks + g);
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db) t_off[db] = tr_lane_offset_sw<D>(lane, db);
+    for (int db = 0; db < D / 16; ++db) t_off[db] = tr16_lane_offset_sw<D>(lane, db);
 
     // keys [jb, jb + 32): in half kb2 of the tile in LDS, or (EXACT) in memory
     auto block = [&](auto exact, int jb, int kb2) __attribute__((always_inline)) {
         constexpr bool EXACT = decltype(exact)::value;
         if (jb >= s.l_x || (s.causal && jb > (int)s.s0 + rw0 + 31)) return;
-        f32x16 sc, dp;
+        Block sc, dp;
+        Frag3 ahead;
         if constexpr (EXACT) {
             int row = r;
             asm volatile("" : "+v"(row));      // (so that its address is made here, not kept through the main loop)
-            const int64_t key_at = (int64_t)min(jb + lq, s.l_x - 1) * ld + hh * 8;
-            const int64_t row_at = ((int64_t)b * s.l_s + min(row, s.l_s - 1)) * ld + (int64_t)h * D + hh * 8;
-            sc = product_f32<D>(kbase + key_at, q + row_at);
-            dp = product_f32<D>(vbase + key_at, dO + row_at);
+            const int64_t key_at[2] = {(int64_t)min(jb + lq, s.l_x - 1) * ld + g * 8, (int64_t)min(jb + 16 + lq, s.l_x - 1) * ld + g * 8};
+            const int64_t head = (int64_t)b * s.l_s * ld + (int64_t)h * D + g * 8;
+            const int64_t row_at[2] = {head + min(row, s.l_s - 1) * ld, head + min(row + 16, s.l_s - 1) * ld};
+            const float *const kr[2] = {kbase + key_at[0], kbase + key_at[1]}, *const qr[2] = {q + row_at[0], q + row_at[1]};
+            sc = product_f32<D>(kr, qr);
+            const float *const vr[2] = {vbase + key_at[0], vbase + key_at[1]}, *const gr[2] = {dO + row_at[0], dO + row_at[1]};
+            dp = product_f32<D>(vr, gr);
         } else {
-            sc = Tile::product(sk, kb2 * 32, a_off, qf);
-            dp = Tile::product(sv, kb2 * 32, a_off, gf);
+            ahead = Tile::rows_frag(sk, kb2 * 32, a_off[0]);
+            sc = Tile::product(sk, kb2 * 32, a_off, qf, ahead, [&] { return Tile::rows_frag(sv, kb2 * 32, a_off[0]); });
+            dp = Tile::product(sv, kb2 * 32, a_off, gf, ahead, [&] { return ahead; });
         }
         if ((s.causal && jb + 31 > (int)s.s0 + rw0) || jb + 32 > s.l_x) {
-            const int last = s.causal ? min((int)s.s0 + r, s.l_x - 1) : s.l_x - 1, rel = last - jb - 4 * hh;
 #pragma unroll
-            for (int e = 0; e < 16; ++e)
-                if (8 * (e >> 2) + (e & 3) > rel) sc[e] = -INFINITY;
+            for (int j = 0; j < 2; ++j) {
+                const int last = s.causal ? min((int)s.s0 + r + 16 * j, s.l_x - 1) : s.l_x - 1, rel = last - jb - 4 * g;
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (16 * (e >> 2) + (e & 3) > rel) sc.v[e >> 2][j][e & 3] = -INFINITY;
+            }
         }
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const float p = fast_exp2(sc[e] * c - L2);
-            float dpe = dp[e];
-            if (DROP) {
-                const int key = jb + 8 * (e >> 2) + 4 * hh + (e & 3);
-                dpe = drop_keep(drop_rk, drop_col_key(drop_cs, (uint32_t)key), dr.thr) ? dpe * dr.scale : 0.f;
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t ck = DROP ? drop_col_key(drop_cs, (uint32_t)(jb + 16 * (e >> 2) + 4 * g + (e & 3))) : 0u;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float p = fast_exp2(sc.v[e >> 2][j][e & 3] * c - L2[j]);
+                float dpe = dp.v[e >> 2][j][e & 3];
+                if (DROP) dpe = drop_keep(drop_rk[j], ck, dr.thr) ? dpe * dr.scale : 0.f;
+                dp.v[e >> 2][j][e & 3] = p * (dpe - Dr[j]);
             }
-            dp[e] = p * (dpe - Dr);
+            if (DROP && (e & 1)) __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (EXACT) {
-            add_product_f32<D>(kbase + (int64_t)jb * ld, ld, s.l_x - jb, dp, acc, lq, hh);
+            add_product_f32<D>(kbase + (int64_t)jb * ld, ld, s.l_x - jb, dp, acc, lq, g);
         } else {
             // The block's 32 keys are added up before they meet the accumulator, which is rounded at its full size once
-            // per block and not twelve times: dq's error 6.6e-7 -> 4.9e-7, the launch's time the same.
-            const Frag3 df0 = split_acc(dp, 0), df1 = split_acc(dp, 1);
+            // per block and not six times.
+            const Frag3 df[2] = {split_acc(dp, 0), split_acc(dp, 1)};
+            ahead = Tile::cols_frag(sk, kb2 * 32, t_off[0]);
+            f32x4 sum[2][2];
+            auto add = [&](int db) __attribute__((always_inline)) {
 #pragma unroll
-            for (int db = 0; db < D / 32; ++db) {
-                const Frag3 k0 = Tile::cols_frag(sk, kb2 * 32, t_off[db]), k1 = Tile::cols_frag(sk, kb2 * 32 + 16, t_off[db]);
-                f32x16 sum;
-                clear(sum);
-                sum = mma_small(k1, df1, mma_small(k0, df0, sum));
-                sum = mma(k1.p[0], df1.p[0], mma(k0.p[0], df0.p[0], sum));
+                for (int j = 0; j < 2; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[db][e] += sum[e];
-            }
+                    for (int e = 0; e < 4; ++e) acc.v[db][j][e] += sum[db & 1][j][e];
+            };
+            Tile::columns(sk, kb2 * 32, t_off, ahead, [&](int db, const Frag3 &a) __attribute__((always_inline)) {
+                sum[db & 1][0] = sum[db & 1][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+                mma6(a, df, sum[db & 1]);
+                if (db > 0) add(db - 1);        // (not the one just issued: its result would be waited for)
+            }, [&] { return ahead; });
+            add(D / 16 - 1);
         }
     };
     for (int t = t_begin; t < t_end; ++t) {
@@ -540,19 +654,20 @@ __device__ __forceinline__ void bwd_dq_f32_body(char *smem, const SegShape &s, c
         for (int kb2 = 0; kb2 < BC / 32; ++kb2) block(std::false_type{}, j0 + kb2 * 32, kb2);
     }
     if (rw0 < s.l_s && t_begin < t_end && (tiny || __builtin_amdgcn_readfirstlane((int)*tiny_word) != 0 || __any(missed(acc)))) {
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db) clear(acc[db]);
+        acc.clear();
         for (int jb = t_begin * BC; jb < t_end * BC; jb += 32) block(std::true_type{}, jb, 0);
     }
-    if (!row_ok) return;
-    const float scale = 1.f / sqrtf((float)D);
-    float *dst = (n_splits == 1 ? dq : dq_part + (int64_t)split * s.B * s.l_s * ld) + ((int64_t)b * s.l_s + r) * ld + (int64_t)h * D;
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
+    for (int j = 0; j < 2; ++j) {
+        const int rj = r + 16 * j;
+        if (rj >= s.l_s) continue;
+        float *dst = (n_splits == 1 ? dq : dq_part + (int64_t)split * s.B * s.l_s * ld) + ((int64_t)b * s.l_s + rj) * ld + (int64_t)h * D;
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4)
-            *reinterpret_cast<f32x4 *>(dst + db * 32 + 8 * e4 + 4 * hh) =
-                f32x4{acc[db][4 * e4] * scale, acc[db][4 * e4 + 1] * scale, acc[db][4 * e4 + 2] * scale, acc[db][4 * e4 + 3] * scale};
+        for (int db = 0; db < D / 16; ++db) {
+            const f32x4 a = acc.v[db][j];
+            *reinterpret_cast<f32x4 *>(dst + db * 16 + 4 * g) = f32x4{a[0] * scale[j], a[1] * scale[j], a[2] * scale[j], a[3] * scale[j]};
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------ dK, dV
@@ -565,17 +680,17 @@ __device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, 
                                                  float *__restrict__ dv_part, int bh, int key_tile)
 {
     using Tile = PlaneTile<D>;
-    constexpr int NU = D / 16, BQ = Tile::ROWS;
+    constexpr int NS = D / 32, BQ = Tile::ROWS;
     char *const sq = smem, *const sg = smem + Tile::BYTES;
     float *const sl = reinterpret_cast<float *>(smem + 2 * Tile::BYTES), *const sd = sl + 64;
     uint32_t *const sr = reinterpret_cast<uint32_t *>(sd + 64), *const tiny_word = sr + 64;
-    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hh = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = bh / s.H, h = bh % s.H;
     constexpr int KEYS = kKeysPerWg<HALVES>;
     static_assert(HALVES == 1 || BQ == 64, "");
     const int key_block = wave / HALVES, my_half = wave % HALVES;
-    const int j0 = key_tile * KEYS, jw0 = j0 + key_block * 32, j = jw0 + lq;
+    const int j0 = key_tile * KEYS, jw0 = j0 + key_block * 32, key0 = jw0 + lq;
     const int64_t ld = (int64_t)s.H * D, kv_base = (int64_t)b * s.l_x * ld + (int64_t)h * D;
 
     if (s.causal && j0 >= s.s0 + s.l_s) {       // no query of the segment sees this tile: zeros, or (whole 128-key tiles) left unwritten
@@ -594,96 +709,106 @@ __device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, 
     int rq_begin = 0;
     if (s.causal) rq_begin = (int)min<int64_t>(max<int64_t>((int64_t)j0 - s.s0, 0), s.l_s) / BQ * BQ;
 
-    // this lane's key; keys past the sequence re-read its last row and are never stored
-    Frag3 kf[NU], vf[NU];
+    // this lane's two keys, key0 + 16 j; keys past the sequence re-read its last row and are never stored
+    Frag3 kf[NS][2], vf[NS][2];
     bool tiny;
     {
-        const int64_t off = kv_base + (int64_t)min(j, s.l_x - 1) * ld + hh * 8;
-        tiny = split_row<D>(k + off, kf);
-        tiny = split_row<D>(v + off, vf) || tiny;
+        const int64_t off[2] = {kv_base + (int64_t)min(key0, s.l_x - 1) * ld + g * 8, kv_base + (int64_t)min(key0 + 16, s.l_x - 1) * ld + g * 8};
+        tiny = split_rows<D>({k + off[0], k + off[1]}, kf);
+        tiny = split_rows<D>({v + off[0], v + off[1]}, vf) || tiny;
     }
     if (tid == 0) *tiny_word = 0u;
     if constexpr (D == 128) {
 #pragma unroll
-        for (int kb = 0; kb < NU; ++kb)
+        for (int n = 0; n < 2 * NS; ++n)
 #pragma unroll
-            for (int p = 0; p < 3; ++p) { asm volatile("" : "+a"(kf[kb].p[p].v)); asm volatile("" : "+a"(vf[kb].p[p].v)); }
+            for (int p = 0; p < 3; ++p) { asm volatile("" : "+a"(kf[n >> 1][n & 1].p[p].v)); asm volatile("" : "+a"(vf[n >> 1][n & 1].p[p].v)); }
     }
-    f32x16 dk[D / 32], dv[D / 32];
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db) { clear(dk[db]); clear(dv[db]); }
+    Sums<D> dk, dv;
+    dk.clear();
+    dv.clear();
     const float c = kLog2e / sqrtf((float)D);
     const float *qbase = q + (int64_t)b * s.l_s * ld + (int64_t)h * D, *gbase = dO + (int64_t)b * s.l_s * ld + (int64_t)h * D;
-    const uint32_t drop_ck = DROP ? drop_col_key(drop_col_seed(dr.seed_hi), (uint32_t)j) : 0u;
-    int a_off[NU], t_off[D / 32];
+    uint32_t drop_ck[2] = {0u, 0u};
+    if (DROP)
 #pragma unroll
-    for (int kb = 0; kb < NU; ++kb) a_off[kb] = Tile::chunk_offset(lq, 2 * kb + hh);
+        for (int j = 0; j < 2; ++j) drop_ck[j] = drop_col_key(drop_col_seed(dr.seed_hi), (uint32_t)(key0 + 16 * j));
+    int a_off[NS], t_off[D / 16];
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db) t_off[db] = tr_lane_offset_sw<D>(lane, db);
+    for (int ks = 0; ks < NS; ++ks) a_off[ks] = Tile::chunk_offset(lq, 4 * ks + g);
+#pragma unroll
+    for (int db = 0; db < D / 16; ++db) t_off[db] = tr16_lane_offset_sw<D>(lane, db);
 
     // rows [rb, rb + 32) of the segment: block qb of the tile in LDS, or (EXACT) in memory
     auto block = [&](auto exact, int rb, int qb) __attribute__((always_inline)) {
         constexpr bool EXACT = decltype(exact)::value;
         // a block none of whose rows sees a key of this wavefront, or past the segment
         if (rb >= s.l_s || (s.causal && (int)s.s0 + rb + 31 < jw0)) return;
-        f32x16 sc, dp;
+        Block sc, dp;
+        Frag3 ahead;
         if constexpr (EXACT) {
-            int key = j;
+            int key = key0;
             asm volatile("" : "+v"(key));      // (so that its address is made here, not kept through the main loop)
-            const int64_t row_at = (int64_t)min(rb + lq, s.l_s - 1) * ld + hh * 8, key_at = kv_base + (int64_t)min(key, s.l_x - 1) * ld + hh * 8;
-            sc = product_f32<D>(qbase + row_at, k + key_at);
-            dp = product_f32<D>(gbase + row_at, v + key_at);
+            const int64_t row_at[2] = {(int64_t)min(rb + lq, s.l_s - 1) * ld + g * 8, (int64_t)min(rb + 16 + lq, s.l_s - 1) * ld + g * 8};
+            const int64_t key_at[2] = {kv_base + (int64_t)min(key, s.l_x - 1) * ld + g * 8, kv_base + (int64_t)min(key + 16, s.l_x - 1) * ld + g * 8};
+            const float *const qr[2] = {qbase + row_at[0], qbase + row_at[1]}, *const kr[2] = {k + key_at[0], k + key_at[1]};
+            sc = product_f32<D>(qr, kr);
+            const float *const gr[2] = {gbase + row_at[0], gbase + row_at[1]}, *const vr[2] = {v + key_at[0], v + key_at[1]};
+            dp = product_f32<D>(gr, vr);
         } else {
-            sc = Tile::product(sq, qb * 32, a_off, kf);
-            dp = Tile::product(sg, qb * 32, a_off, vf);
+            ahead = Tile::rows_frag(sq, qb * 32, a_off[0]);
+            sc = Tile::product(sq, qb * 32, a_off, kf, ahead, [&] { return Tile::rows_frag(sg, qb * 32, a_off[0]); });
+            dp = Tile::product(sg, qb * 32, a_off, vf, ahead, [&] { return ahead; });
         }
         const bool diag = s.causal && jw0 + 31 > (int)s.s0 + rb;
-        // element e of this lane is row rb + 8 (e / 4) + 4 hh + e % 4
+        // element (i, e) of this lane is row rb + 16 i + 4 g + e
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-            const int rl = qb * 32 + 8 * e4 + 4 * hh, r4 = rb + 8 * e4 + 4 * hh;        // in the tile; in the segment
+        for (int i = 0; i < 2; ++i) {
+            const int rl = qb * 32 + 16 * i + 4 * g, r4 = rb + 16 * i + 4 * g;          // in the tile; in the segment
             f32x4 l4, d4;
             if constexpr (EXACT) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int64_t at = (int64_t)bh * s.l_s + min(r4 + i, s.l_s - 1);
-                    l4[i] = r4 + i < s.l_s ? lse[at] * kLog2e : INFINITY;
-                    d4[i] = Dv[at];
+                for (int e = 0; e < 4; ++e) {
+                    const int64_t at = (int64_t)bh * s.l_s + min(r4 + e, s.l_s - 1);
+                    l4[e] = r4 + e < s.l_s ? lse[at] * kLog2e : INFINITY;
+                    d4[e] = Dv[at];
                 }
             } else {
                 l4 = *reinterpret_cast<const f32x4 *>(sl + rl);
                 d4 = *reinterpret_cast<const f32x4 *>(sd + rl);
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int e = 4 * e4 + i;
-                float p = fast_exp2(sc[e] * c - l4[i]);
-                if (diag && j > (int)s.s0 + r4 + i) p = 0.f;
-                float pv = p, dpe = dp[e];
-                if (DROP) {
-                    const uint32_t rk = EXACT ? drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + r4 + i)) : sr[rl + i];
-                    const float mk = drop_keep(rk, drop_ck, dr.thr) ? dr.scale : 0.f;
-                    pv = p * mk;
-                    dpe *= mk;
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t rk = !DROP ? 0u : EXACT ? drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + r4 + e)) : sr[rl + e];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    float p = fast_exp2(sc.v[i][j][e] * c - l4[e]);
+                    if (diag && key0 + 16 * j > (int)s.s0 + r4 + e) p = 0.f;
+                    float pv = p, dpe = dp.v[i][j][e];
+                    if (DROP) {
+                        const float mk = drop_keep(rk, drop_ck[j], dr.thr) ? dr.scale : 0.f;
+                        pv = p * mk;
+                        dpe *= mk;
+                    }
+                    sc.v[i][j][e] = pv;
+                    dp.v[i][j][e] = p * (dpe - d4[e]);
                 }
-                sc[e] = pv;
-                dp[e] = p * (dpe - d4[i]);
+                if (DROP && (e & 1)) __builtin_amdgcn_sched_barrier(0);
             }
             if constexpr (EXACT) __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (EXACT) {
-            add_product_f32<D>(gbase + (int64_t)rb * ld, ld, s.l_s - rb, sc, dv, lq, hh);
-            add_product_f32<D>(qbase + (int64_t)rb * ld, ld, s.l_s - rb, dp, dk, lq, hh);
+            add_product_f32<D>(gbase + (int64_t)rb * ld, ld, s.l_s - rb, sc, dv, lq, g);
+            add_product_f32<D>(qbase + (int64_t)rb * ld, ld, s.l_s - rb, dp, dk, lq, g);
         } else {
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const Frag3 pf = split_acc(sc, half), df = split_acc(dp, half);
-#pragma unroll
-                for (int db = 0; db < D / 32; ++db) {
-                    dv[db] = mma6(Tile::cols_frag(sg, qb * 32 + half * 16, t_off[db]), pf, dv[db]);
-                    dk[db] = mma6(Tile::cols_frag(sq, qb * 32 + half * 16, t_off[db]), df, dk[db]);
-                }
-            }
+            ahead = Tile::cols_frag(sg, qb * 32, t_off[0]);
+            Frag3 wf[2] = {split_acc(sc, 0), split_acc(sc, 1)};
+            Tile::columns(sg, qb * 32, t_off, ahead, [&](int db, const Frag3 &a) __attribute__((always_inline)) { mma6(a, wf, dv.v[db]); },
+                          [&] { return Tile::cols_frag(sq, qb * 32, t_off[0]); });
+            wf[0] = split_acc(dp, 0);
+            wf[1] = split_acc(dp, 1);
+            Tile::columns(sq, qb * 32, t_off, ahead, [&](int db, const Frag3 &a) __attribute__((always_inline)) { mma6(a, wf, dk.v[db]); },
+                          [&] { return ahead; });
         }
     };
     for (int rq0 = rq_begin; rq0 < s.l_s; rq0 += BQ) {
@@ -709,45 +834,41 @@ __device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, 
     }
     tiny = tiny || (rq_begin < s.l_s && __builtin_amdgcn_readfirstlane((int)*tiny_word) != 0);
     if constexpr (HALVES == 2) {        // second half's results -> first half's wavefront, through the planes' LDS
-        static_assert(2 * 2 * (D / 32) * 4096 <= 2 * Tile::BYTES, "");
+        static_assert(2 * 2 * (D / 8) * 1024 <= 2 * Tile::BYTES, "");
         __syncthreads();
-        auto at = [&](int blk, int e4) { return reinterpret_cast<f32x4 *>(smem + ((key_block * 2 * (D / 32) + blk) * 4 + e4) * 1024 + lane * 16); };
+        auto at = [&](int n) { return reinterpret_cast<f32x4 *>(smem + (key_block * 2 * (D / 8) + n) * 1024 + lane * 16); };
+        if (my_half == 1)
 #pragma unroll
-        for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4)
-                if (my_half == 1) {
-                    *at(2 * db, e4) = f32x4{dk[db][4 * e4], dk[db][4 * e4 + 1], dk[db][4 * e4 + 2], dk[db][4 * e4 + 3]};
-                    *at(2 * db + 1, e4) = f32x4{dv[db][4 * e4], dv[db][4 * e4 + 1], dv[db][4 * e4 + 2], dv[db][4 * e4 + 3]};
-                }
+            for (int n = 0; n < D / 8; ++n) {
+                *at(2 * n) = dk.v[n >> 1][n & 1];
+                *at(2 * n + 1) = dv.v[n >> 1][n & 1];
+            }
         __syncthreads();
         if (my_half == 1) return;
 #pragma unroll
-        for (int db = 0; db < D / 32; ++db)
+        for (int n = 0; n < D / 8; ++n) {
+            const f32x4 a = *at(2 * n), d = *at(2 * n + 1);
 #pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) {
-                const f32x4 a = *at(2 * db, e4), g = *at(2 * db + 1, e4);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { dk[db][4 * e4 + i] += a[i]; dv[db][4 * e4 + i] += g[i]; }
-            }
+            for (int e = 0; e < 4; ++e) { dk.v[n >> 1][n & 1][e] += a[e]; dv.v[n >> 1][n & 1][e] += d[e]; }
+        }
     }
     if (jw0 < s.l_x && (tiny || __any(missed(dk) || missed(dv)))) {
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db) { clear(dk[db]); clear(dv[db]); }
+        dk.clear();
+        dv.clear();
         for (int rb = rq_begin; rb < s.l_s; rb += 32) block(std::true_type{}, rb, 0);
     }
-    if (j >= s.l_x) return;
     const float scale = 1.f / sqrtf((float)D);
-    const int64_t off = kv_base + (int64_t)j * ld;
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
+    for (int j = 0; j < 2; ++j) {
+        if (key0 + 16 * j >= s.l_x) continue;
+        const int64_t off = kv_base + (int64_t)(key0 + 16 * j) * ld + 4 * g;
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-            const int col = db * 32 + 8 * e4 + 4 * hh;
-            *reinterpret_cast<f32x4 *>(dk_part + off + col) =
-                f32x4{dk[db][4 * e4] * scale, dk[db][4 * e4 + 1] * scale, dk[db][4 * e4 + 2] * scale, dk[db][4 * e4 + 3] * scale};
-            *reinterpret_cast<f32x4 *>(dv_part + off + col) = f32x4{dv[db][4 * e4], dv[db][4 * e4 + 1], dv[db][4 * e4 + 2], dv[db][4 * e4 + 3]};
+        for (int db = 0; db < D / 16; ++db) {
+            const f32x4 a = dk.v[db][j];
+            *reinterpret_cast<f32x4 *>(dk_part + off + db * 16) = f32x4{a[0] * scale, a[1] * scale, a[2] * scale, a[3] * scale};
+            *reinterpret_cast<f32x4 *>(dv_part + off + db * 16) = dv.v[db][j];
         }
+    }
 }
 
 // Both kinds of workgroup in one launch, dQ first, in XCD order: see bwd_main_bf16_kernel.
@@ -786,14 +907,7 @@ template <int D>
 hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const float *q, const float *k, const float *v, const float *lse,
                         const float *dO, float *dq, float *dk_part, float *dv_part, const Workspace &ws, int n_splits, hipStream_t st)
 {
-    // Two wavefronts per key block where a dK/dV workgroup's walk over the queries is what the launch waits for: the key
-    // tiles fit the chip about once (two workgroups per compute unit) and a dQ workgroup does not walk much longer.  2048 rows,
-    // 8 heads, 2048 keys: 214 -> 148 us; but 600 rows, 4 heads, 8192 keys 109 -> 119 (dQ walks 16 tiles, the queries are 10), 64
-    // rows against 1664 key tiles 103 -> 121.  On 156 launches (64..2048 rows, 2..96 heads, 100..1700 key tiles) the
-    // rule costs 0.9 % over the better choice on average; never 2.3 %, always 3.4 %.
-    const int64_t seen = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
-    const int64_t dq_tiles = ((seen + 63) / 64 + n_splits - 1) / n_splits;
-    const bool halves = D == 64 && (seen + 127) / 128 * s.B * s.H <= 640 && 4 * ((s.l_s + 63) / 64) >= 3 * dq_tiles;
+    const bool halves = f32_bwd_halves(s, n_splits);
     const int keys = halves ? 64 : 128, n_q_tiles = (s.l_s + kRowsPerWg - 1) / kRowsPerWg, n_key_tiles = (s.l_x + keys - 1) / keys;
     const int n_dq = xcd_grid(s.B * s.H, n_q_tiles * n_splits), n_dkv = xcd_grid(s.B * s.H, n_key_tiles);
     constexpr int H2 = D == 64 ? 2 : 1;
@@ -808,6 +922,18 @@ hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const float *q, c
 } // namespace
 
 int f32_rows_per_workgroup() { return kRowsPerWg; }
+
+// Two wavefronts per key block where a dK/dV workgroup's walk over the queries is what the launch waits for: the key
+// tiles fit the chip about once (two workgroups per compute unit) and a dQ workgroup does not walk much longer.  2048 rows,
+// 8 heads, 2048 keys: 214 -> 148 us; but 600 rows, 4 heads, 8192 keys 109 -> 119 (dQ walks 16 tiles, the queries are 10), 64
+// rows against 1664 key tiles 103 -> 121.  On 156 launches (64..2048 rows, 2..96 heads, 100..1700 key tiles) the
+// rule costs 0.9 % over the better choice on average; never 2.3 %, always 3.4 %.
+bool f32_bwd_halves(const SegShape &s, int n_splits)
+{
+    const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x;
+    const int64_t dq_tiles = ((seen + 63) / 64 + n_splits - 1) / n_splits;
+    return s.d == 64 && (seen + 127) / 128 * s.B * s.H <= 640 && 4 * ((s.l_s + 63) / 64) >= 3 * dq_tiles;
+}
 
 hipError_t launch_fwd_f32_main(const SegShape &s, const DropArgs &drop, const float *q, const float *k, const float *v, float *out,
                                float *lse, const Workspace &ws, int n_splits, hipStream_t st)

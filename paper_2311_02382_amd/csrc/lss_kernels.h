@@ -81,6 +81,7 @@ hipError_t launch_fwd_bf16_main(const SegShape &s, const DropArgs &drop, const b
 
 // single-precision kernels (lss_f32.hip); ws.D holds rowsum(dO * out)
 int f32_rows_per_workgroup();
+bool f32_bwd_halves(const SegShape &s, int n_splits);     // two wavefronts per key block, see lss_f32.hip
 hipError_t launch_fwd_f32_main(const SegShape &s, const DropArgs &drop, const float *q, const float *k, const float *v, float *out,
                                float *lse, const Workspace &ws, int n_splits, hipStream_t st);
 hipError_t launch_bwd_f32_main(const SegShape &s, const DropArgs &drop, const float *q, const float *k, const float *v,
