@@ -11,6 +11,7 @@
 // dQ splits, and the launch sequence.  No atomics.
 #include "lss_common.h"
 #include "lss_kernels.h"
+#include <algorithm>
 
 namespace lss {
 
@@ -54,7 +55,7 @@ __global__ __launch_bounds__(256) void bwd_dq_merge_kernel(const float *__restri
     for (int e = 0; e < 4; ++e) dq[i * 4 + e] = (T)acc[e];
 }
 
-// (bf16 at d = 128 or with at most 64 rows; see pick_bwd_plan and pick_float_splits for the others)
+// (bf16 with at most 64 rows, and at d = 128 the base of pick_splits; see pick_bwd_plan for d = 64)
 // The dQ workgroups share their launch with the dK/dV ones and need not fill the chip alone: keys are split so far that
 // a dQ workgroup does not outlast the rest of the launch, never further than the workspace was sized for.  In 64-key
 // tiles of dQ, of which a lone workgroup takes one per 1.0 us (d = 64) or 1.4 us (d = 128):
@@ -133,26 +134,31 @@ static BwdPlan pick_bwd_plan(const SegShape &s, int most)
     return best;
 }
 
-// float: a launch takes about, in us,
-//     start + (longest^6 + balance^6)^(1/6) + zeros / 5 MB + merge
+// float, and bf16 at d = 128 with more than 64 rows: a launch takes about, in us,
+//     start + (longest^6 + balance^6)^(1/6) + zeros + merge
 // as for bf16 above: the longer of a dQ workgroup's walk over its 64-key tiles and a dK/dV workgroup's over the 64-row query tiles
 // (half the time where two wavefronts share a key block), slower as two workgroups share a compute unit; all walks over 256 compute units,
-// and a part of a last dK/dV walk where the launch takes more than one round. Fitted to 290 launches (30 .. 12,661 rows, 512 .. 22,136
-// keys, 2 .. 32 heads, 1 .. 16 splits, after a forward call each). Ranges of 16 tiles, what every launch had, remain unless the estimate
-// is 5 % better: launches took 12.5 % more with them on average (4 heads of 100 rows against 1000 keys 66 us, in four ranges 31; 8 of 391 rows
-// against 1084 keys: 46 and 35), 5 % of them lose more than 2 %, the choice costs 4 % over the best.
-static int pick_float_splits(const SegShape &s, int most)
+// and a part of a last dK/dV walk where the launch takes more than one round.
+// float: fitted to 290 launches (30 .. 12,661 rows, 512 .. 22,136 keys, 2 .. 32 heads, 1 .. 16 splits, after a forward call each).
+// Ranges of 16 tiles, what every launch had, are the base, left where the estimate of shorter ones is 5 % better or of longer ones 15 %: launches
+// took 12 % more with them on average (4 heads of 100 rows against 1000 keys 66 us, in four ranges 26), the choice costs 5 % over the best.
+// bf16: fitted to 104 such launches, base the count of pick_dq_splits, 5 % either way: launches take 4.4 % less time than with that one
+// on average (2 heads of 2214 rows against 10,610 keys 239 us, 130 now; 8 of 162 against 1162: 36 and 26), the choice costs 4 % over the best.
+static int pick_splits(const SegShape &s, int most, int elem_bytes)
 {
-    struct Cost { double start, dq_us, dq_more, dkv_us, dkv_halves_us, dkv_more, dkv_slow, rate, last, merge_rate; };
-    static const Cost d64 = {4.3, 3.95, 0.0, 6.8, 3.3, 0.2, 0.136, 0.717, 0.36, 1.1}, d128 = {0.0, 7.0, 0.6, 7.8, 7.8, 1.5, 0.0, 0.97, 0.58, 1.5};
-    const Cost &c = s.d == 64 ? d64 : d128;
+    struct Cost { double start, dq_us, dq_more, dkv_us, dkv_halves_us, dkv_more, dkv_slow, rate, last, zeros_rate, merge, merge_bytes, merge_rate; };
+    static const Cost f64 = {4.3, 3.95, 0.0, 6.8, 3.3, 0.2, 0.136, 0.717, 0.36, 5.0, 3.0, 4.0, 1.1},
+                      f128 = {0.0, 7.0, 0.6, 7.8, 7.8, 1.5, 0.0, 0.97, 0.58, 5.0, 3.0, 4.0, 1.5},
+                      b128 = {7.4, 1.305, 0.58, 1.42, 1.42, 2.6, 0.0, 1.243, 0.28, 9.0, 1.8, 2.0, 1.08};
+    const bool is_float = elem_bytes == 4;
+    const Cost &c = !is_float ? b128 : s.d == 64 ? f64 : f128;
     const double bhs = (double)s.B * s.H, room = s.d == 64 ? 512.0 : 256.0;      // workgroups that fit the chip
     const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x, first = s.causal ? s.s0 + (s.l_s < 128 ? s.l_s : 128) : (int64_t)s.l_x;
     const int64_t tiles = (seen + 63) / 64, q_tiles = (s.l_s + 63) / 64, dq_tiles = (s.l_s + 127) / 128;
     const double mean_tiles = 0.5 * (double)(((first < seen ? first : seen) + 63) / 64 + tiles);
     const double zeros_mb = (double)(s.l_x - seen) * bhs * s.d * 8e-6, dq_m = bhs * s.l_s * s.d * 1e-6;
     auto estimate = [&](int sp) {
-        const bool halves = f32_bwd_halves(s, sp);
+        const bool halves = is_float && f32_bwd_halves(s, sp);
         const int64_t keys = halves ? 64 : 128, key_tiles = (seen + keys - 1) / keys;
         const int64_t full = s.causal && s.s0 / keys < key_tiles ? s.s0 / keys : key_tiles;     // key tiles that all rows see; the others half of them
         const double dkv_us = halves ? c.dkv_halves_us : c.dkv_us, n_dq = (double)dq_tiles * bhs * sp, n_dkv = (double)key_tiles * bhs, N = n_dq + n_dkv;
@@ -162,15 +168,17 @@ static int pick_float_splits(const SegShape &s, int most)
         double balance = c.rate / 256.0 * (((double)dq_tiles * bhs * mean_tiles + n_dq * c.dq_more) * c.dq_us +
                                            (bhs * ((double)full + 0.5 * (double)(key_tiles - full)) * (double)q_tiles + n_dkv * c.dkv_more) * dkv_us);
         if (N > room) balance += c.last * dkv;
-        const double t = c.start + pow(pow(longest, 6.0) + pow(balance, 6.0), 1.0 / 6.0) + zeros_mb / 5.0;
-        return sp > 1 ? t + 3.0 + dq_m * (8 * sp + 4) / c.merge_rate : t;
+        const double t = c.start + pow(pow(longest, 6.0) + pow(balance, 6.0), 1.0 / 6.0) + zeros_mb / c.zeros_rate;
+        return sp > 1 ? t + c.merge + dq_m * (2 * sp + 1) * c.merge_bytes / c.merge_rate : t;
     };
-    int best = (int)((tiles + 15) / 16);
-    if (best > most) best = most;
-    double best_t = 0.95 * estimate(best);
+    const int base = is_float ? (int)std::min<int64_t>((tiles + 15) / 16, most) : pick_dq_splits(s, most);
+    const double base_t = estimate(base);
+    int best = base;
+    double best_t = base_t;
     for (int sp = 1; sp <= most; ++sp) {
+        if (sp == base) continue;
         const double t = estimate(sp);
-        if (t < best_t) { best_t = t; best = sp; }
+        if (t < (sp < base && is_float ? 0.85 : 0.95) * base_t && t < best_t) { best_t = t; best = sp; }
     }
     return best;
 }
@@ -187,9 +195,9 @@ static hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const T *q
     const size_t rows_bytes = (size_t)s.B * s.l_s * s.H * D * sizeof(T), part_bytes = (size_t)s.B * s.l_x * s.H * D * sizeof(float);
     const bool out_first = overlaps(dq, rows_bytes, out, rows_bytes) || overlaps(dk_part, part_bytes, out, rows_bytes) ||
                            overlaps(dv_part, part_bytes, out, rows_bytes);
-    const BwdPlan plan = sizeof(T) == 4              ? BwdPlan{pick_float_splits(s, most), 1}
-                         : D == 64 && s.l_s > 64 ? pick_bwd_plan(s, most)
-                                                 : BwdPlan{pick_dq_splits(s, most), 1};
+    const BwdPlan plan = sizeof(T) == 4 || (D == 128 && s.l_s > 64) ? BwdPlan{pick_splits(s, most, (int)sizeof(T)), 1}
+                         : s.l_s > 64                               ? pick_bwd_plan(s, most)
+                                                                    : BwdPlan{pick_dq_splits(s, most), 1};
     const int dq_splits = plan.splits;
     const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x;
     const int dq_tiles = (int)(((seen + 63) / 64 + dq_splits - 1) / dq_splits + plan.groups - 1) / plan.groups;

@@ -63,8 +63,7 @@ static hipError_t launch_fwd_d(const SegShape &s, const DropArgs &drop, const T 
         n_splits = plan.splits;
         e = launch_fwd_bf16_main(s, drop, q, k, v, out, lse, ws, plan, st);
     } else {
-        const int64_t kv_extent = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
-        n_splits = pick_fwd_splits(s.l_s, s.B, s.H, fwd_rows_per_wg(4, D), (kv_extent + 63) / 64, ws.fwd_splits, D);
+        n_splits = pick_float_fwd_splits(s, ws.fwd_splits);
         e = launch_fwd_f32_main(s, drop, q, k, v, out, lse, ws, n_splits, st);
     }
     if (e != hipSuccess || n_splits == 1) return e;

@@ -34,7 +34,7 @@ int choose_splits(int l_s, int l_x, int B, int H, int rows_per_wg);
 // Forward: the largest split count the workspace is sized for (shape-only), and the count a launch
 // uses for the `kv_tiles` 64-key tiles its query tiles actually see (never above the former).
 int max_fwd_splits(int l_s, int l_x, int B, int H, int rows_per_wg);
-int pick_fwd_splits(int l_s, int B, int H, int rows_per_wg, int64_t kv_tiles, int max_splits, int d);     // float kernels
+int pick_float_fwd_splits(const SegShape &s, int max_splits);
 // bf16 forward: the workgroup's form -- blocks of 32 query rows x groups of wavefronts that have a part of the keys
 // each -- and the key splits.
 enum FwdForm { FWD_4x1, FWD_2x2, FWD_4x2, FWD_8x1 };
