@@ -42,17 +42,24 @@ __global__ __launch_bounds__(256) void bwd_rowdot_kernel(SegShape s, const T *__
     }
 }
 
-// dq = sum over splits, in split order.
-template <typename T>
+// dq = sum over splits, in split order.  MAXS: compile-time bound of n_splits, so that a thread's loads are in flight together
+// (58 rows, 32 heads, 16 splits: 6.5 us in a loop over the splits, now 5.4; two splits: 4.9 either way).
+template <typename T, int MAXS>
 __global__ __launch_bounds__(256) void bwd_dq_merge_kernel(const float *__restrict__ dq_part, int n_splits,
                                                            int64_t n4, T *__restrict__ dq)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n4) return;
-    f32x4 acc = *reinterpret_cast<const f32x4 *>(dq_part + i * 4);
-    for (int sp = 1; sp < n_splits; ++sp) acc += *reinterpret_cast<const f32x4 *>(dq_part + (sp * n4 + i) * 4);
+    f32x4 part[MAXS];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) dq[i * 4 + e] = (T)acc[e];
+    for (int sp = 0; sp < MAXS; ++sp)
+        part[sp] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(dq_part + ((sp < n_splits ? sp : n_splits - 1) * n4 + i) * 4));
+    f32x4 acc = part[0];
+#pragma unroll
+    for (int sp = 1; sp < MAXS; ++sp)
+        if (sp < n_splits) acc += part[sp];
+    if constexpr (sizeof(T) == 2) *reinterpret_cast<bf16x4 *>(dq + i * 4) = bf16x4{(bf16_t)acc[0], (bf16_t)acc[1], (bf16_t)acc[2], (bf16_t)acc[3]};
+    else *reinterpret_cast<f32x4 *>(dq + i * 4) = acc;
 }
 
 // (bf16 with at most 64 rows, and at d = 128 the base of pick_splits; see pick_bwd_plan for d = 64)
@@ -219,8 +226,11 @@ static hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const T *q
     if (n_splits > 1) {
         const int64_t n4 = (int64_t)s.B * s.l_s * s.H * D / 4;
         TimedLaunch tl(K_DQ_MERGE, st);
-        hipLaunchKernelGGL((bwd_dq_merge_kernel<T>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st,
-                           ws.dq_part, n_splits, n4, dq);
+        const auto kernel = n_splits <= 2   ? bwd_dq_merge_kernel<T, 2>
+                            : n_splits <= 4 ? bwd_dq_merge_kernel<T, 4>
+                            : n_splits <= 8 ? bwd_dq_merge_kernel<T, 8>
+                                            : bwd_dq_merge_kernel<T, 16>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, ws.dq_part, n_splits, n4, dq);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
