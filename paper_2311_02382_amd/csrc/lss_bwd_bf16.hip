@@ -1154,9 +1154,12 @@ __global__ __launch_bounds__(256, QB == 2 ? 2 : 1) void bwd_skinny_bf16_kernel(
     const int kt0 = (int)((int64_t)kt_vis * split / n_splits), kt1 = (int)((int64_t)kt_vis * (split + 1) / n_splits);
 
     char *const k_slots = smem + C::OFF_K + wave * 3 * KTile::BYTES, *const v_slot = k_slots + 2 * KTile::BYTES;
-    // (a load instruction's rows start at a multiple of 8 whose permutation is the same: one offset serves them all)
+    // (a load instruction's rows start at a multiple of 8, the permutation goes by row % 16: one offset for the even ones, one for the odd)
     static_assert(D == 64, "");
-    const uint32_t offK = ((uint32_t)(lane / 8) * (uint32_t)ld + (uint32_t)((lane % 8) ^ (lane / 8)) * 8u) * 2u;
+    uint32_t offK[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        offK[i] = ((uint32_t)(lane / 8) * (uint32_t)ld + (uint32_t)((lane % 8) ^ tile_swizzle<D>(8 * i + lane / 8)) * 8u) * 2u;
     // the wavefront's block of key tile kt: rows past the sequence re-read its last row, are masked and never stored
     auto load_kv = [&](int kt, int slot) __attribute__((always_inline)) {
         const int jw0 = kt * C::BKV + wave * 32, j_first = min(jw0, s.l_x - 1);
@@ -1165,8 +1168,8 @@ __global__ __launch_bounds__(256, QB == 2 ? 2 : 1) void bwd_skinny_bf16_kernel(
         if (jw0 + 32 <= s.l_x) {
 #pragma unroll
             for (int i = 0; i < KTile::NI; ++i) {
-                lds_dma<16>(k + at + (int64_t)(8 * i) * ld, offK, dst + i * 1024);
-                lds_dma<16>(v + at + (int64_t)(8 * i) * ld, offK, v_slot + i * 1024);
+                lds_dma<16>(k + at + (int64_t)(8 * i) * ld, offK[i & 1], dst + i * 1024);
+                lds_dma<16>(v + at + (int64_t)(8 * i) * ld, offK[i & 1], v_slot + i * 1024);
             }
         } else {
             uint32_t off[KTile::NI];

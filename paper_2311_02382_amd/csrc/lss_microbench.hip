@@ -238,7 +238,7 @@ __device__ int chunk_off(int r, int c)
     constexpr int CPR = D / 8;
     int f;
     if (MODE == 0) f = r & 7;
-    else f = D == 64 ? (r & 7) : (((r & 3) << 2) | ((r >> 2) & 3));
+    else f = (D == 64 ? (r & 2) << 1 : (r & 3) << 2) ^ ((r & 4) >> 1) ^ ((r & 8) >> 2) ^ ((r & 8) >> 3);
     return r * (D * 2) + ((c ^ f) & (CPR - 1)) * 16;
 }
 
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(256) void lds_kernel(float *out, int iters)
         } else {
 #pragma unroll
             for (int db = 0; db < 4; ++db) {
-                const int hi = (MODE == 1 && D == 128) ? (off[db] ^ 32) : off[db];
+                const int hi = MODE == 1 ? (off[db] ^ 48) : off[db];
                 const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(base + off[db]));
                 const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(base + hi + 8 * D * 2));
                 acc[0] += (float)a[0];
@@ -336,9 +336,11 @@ int main()
     run_data<1, 6, 2>(d, "random, + 6 fma + 2 exp2, again");
     printf("# 4. LDS fragment reads, [rows][D] bf16 tiles, time per wave-instruction per compute unit\n");
     run_lds<0, 64, 0>(d, "ds_read_b128 by rows, D=64, r&7");
+    run_lds<1, 64, 0>(d, "ds_read_b128 by rows, D=64, tile_swizzle");
     run_lds<0, 128, 0>(d, "ds_read_b128 by rows, D=128, r&7");
     run_lds<1, 128, 0>(d, "ds_read_b128 by rows, D=128, tile_swizzle");
     run_lds<0, 64, 1>(d, "ds_read_b64_tr_b16, D=64, r&7");
+    run_lds<1, 64, 1>(d, "ds_read_b64_tr_b16, D=64, tile_swizzle");
     run_lds<0, 128, 1>(d, "ds_read_b64_tr_b16, D=128, r&7");
     run_lds<1, 128, 1>(d, "ds_read_b64_tr_b16, D=128, tile_swizzle");
     return 0;
