@@ -23,20 +23,20 @@
 namespace lss {
 
 // ------------------------------------------------------------------------------------------ dQ
-template <int D>
+template <int D, int NJ = 2>
 struct DqBf16Cfg {
-    static constexpr int WAVES = 4, RW = 32;            // query rows per wavefront
-    static constexpr int BR = WAVES * RW, BC = 64, NT = 256;
+    static constexpr int WAVES = 8 / NJ, RW = 16 * NJ;  // query rows per wavefront: NJ blocks of 16
+    static constexpr int BR = WAVES * RW, BC = 64, NT = 64 * WAVES;
     static constexpr int RING = 3;                      // K/V tiles resident in LDS
     static constexpr int NU = D / 16;                   // operand steps of the S/dP products; same for dQ
-    using Tile = DirectTile<D, BC>;
+    using Tile = DirectTile<D, BC, WAVES>;
     static constexpr int OFF_V = Tile::BYTES, SLOT = 2 * Tile::BYTES;   // one ring slot: K tile, V tile
     // (dropout: behind the ring, the column keys of the last four tiles issued, 64 each)
     static constexpr int group_lds(bool drop) { return RING * SLOT + (drop ? 4 * BC * 4 : 0); }
 };
 
 // KG: groups of wavefronts in the workgroup, see bwd_main_bf16_kernel.
-// Transposed formulation: S^T = K Q^T and dP^T = V dO^T put the wavefront's 32 queries on the lanes
+// Transposed formulation: S^T = K Q^T and dP^T = V dO^T put the wavefront's 16 NJ queries on the lanes
 // (lse and D are per-lane scalars), and dS^T comes out of the accumulators in the layout the
 // dQ^T += K^T dS^T product wants as its second operand.  The keys are walked in blocks of 32 (two
 // per 64-key K/V tile).  Per block g three stages:
@@ -48,7 +48,7 @@ struct DqBf16Cfg {
 // -D = -rowsum(dO * out) of the wavefront's rows comes from the preprocess kernel (`Dn`), or is computed here (OWN).
 // DROP: dropout on the weights (mask M = keep / (1 - p), decided by drop_keep() of (seed,
 // batch*head, global row, key)): dS = P * (M dP - D).
-template <int D, bool DROP, bool OWN, int KG>
+template <int D, bool DROP, bool OWN, int KG, int NJ>
 __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const DropArgs &dr, const bf16_t *__restrict__ q,
                                             const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
                                             const bf16_t *__restrict__ out, const bf16_t *__restrict__ dO, const float *__restrict__ lse,
@@ -56,7 +56,7 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
                                             float *__restrict__ dq_part, int n_splits, int q_tile, int n_q_tiles, int bh,
                                             int split)
 {
-    using C = DqBf16Cfg<D>;
+    using C = DqBf16Cfg<D, NJ>;
     using Tile = typename C::Tile;
     constexpr int NU = C::NU;
 
@@ -80,23 +80,23 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
     const int iters = KG > 1 ? (s_tiles + KG - 1) / KG : s_tiles;
     const int t_begin = s_begin + group * iters, T = KG > 1 ? max(min(s_tiles - group * iters, iters), 0) : s_tiles;
 
-    // this lane's two query rows (columns of the S^T blocks), rw0 + 16 j + lq; rows past the segment re-read its last row
+    // this lane's query rows (columns of the S^T blocks), rw0 + 16 j + lq; rows past the segment re-read its last row
     // (unconditional loads), get lse = +inf, which makes their P and dS exactly 0, and are never stored
-    Frag<bf16_t> qf[NU], gf[NU];                        // operand step ks (32 columns), row block j: [2 ks + j]
-    float L2[2], Dr[2];
+    Frag<bf16_t> qf[NU / 2][NJ], gf[NU / 2][NJ];        // operand step ks (32 columns), row block j
+    float L2[NJ], Dr[NJ];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < NJ; ++j) {
         const int r = rw0 + 16 * j + lq, rc = min(r, s.l_s - 1);
         const int64_t off = ((int64_t)b * s.l_s + rc) * ld + (int64_t)h * D + g * 8;
         Dr[j] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < NU / 2; ++ks) {
-            qf[2 * ks + j] = load_frag<bf16_t>(q + off + ks * 32);
-            gf[2 * ks + j] = load_frag<bf16_t>(dO + off + ks * 32);
+            qf[ks][j] = load_frag<bf16_t>(q + off + ks * 32);
+            gf[ks][j] = load_frag<bf16_t>(dO + off + ks * 32);
             if constexpr (OWN) {    // the lane's quarter of the row
                 const Frag<bf16_t> of = load_frag<bf16_t>(out + off + ks * 32);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) Dr[j] += (float)gf[2 * ks + j].v[e] * (float)of.v[e];
+                for (int e = 0; e < 8; ++e) Dr[j] += (float)gf[ks][j].v[e] * (float)of.v[e];
             }
         }
         if constexpr (OWN) {
@@ -111,9 +111,9 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
     const float c = kLog2e / sqrtf((float)D);
     // -D in all accumulator slots: third operand of each block's first dP^T instructions (not with dropout, whose mask comes between)
     const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-    f32x4 neg_d[2], acc[NU][2];                         // acc: 16 columns x 16 rows each, transposed
+    f32x4 neg_d[NJ], acc[NU][NJ];                         // acc: 16 columns x 16 rows each, transposed
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < NJ; ++j) {
         neg_d[j] = f32x4{-Dr[j], -Dr[j], -Dr[j], -Dr[j]};
 #pragma unroll
         for (int db = 0; db < NU; ++db) acc[db][j] = zero4;
@@ -126,15 +126,15 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
         // dropout: this lane's row keys; the column seed; the column keys of tile t (global tile index)
         // are computed once, by one wavefront when the tile's loads are issued, into quarter t % 4 of
         // a small ring behind the tiles -- published by the same barrier as the tile
-        uint32_t drop_rk[2] = {0u, 0u}, drop_cs = 0u;
+        uint32_t drop_rk[NJ], drop_cs = 0u;
         if (DROP) {
             drop_cs = drop_col_seed(dr.seed_hi);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) drop_rk[j] = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + rw0 + 16 * j + lq));
+            for (int j = 0; j < NJ; ++j) drop_rk[j] = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + rw0 + 16 * j + lq));
         }
         char *const ck_ring = ring + C::RING * C::SLOT;
 
-        // ---- tile loads, by all four wavefronts.  Branch-free on purpose: a branch inside a pipeline step
+        // ---- tile loads, by all wavefronts of the group.  Branch-free on purpose: a branch inside a pipeline step
         // splits it into basic blocks, and the vector work that was meant to sit between the step's
         // matrix instructions is then moved behind the branch in one lump.
         uint32_t offF[Tile::NI], offD[Tile::NI];        // this lane's global offsets within a full tile; and what
@@ -179,19 +179,20 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
         auto load_c = [&](const char *tile, int kb2, int u, Frag<bf16_t> &fk) __attribute__((always_inline)) {
             fk = load_frag_tr16_sw<D>(tile, kb2 * 32, t_off[u]);
         };
-        // B for elements [e0, e1), element e = (i, j, v) = (e / 8, e / 4 % 2, e % 4): P = 2^(c * S - lse * log2 e), dS = P * (dP - D);
+        // B for elements [e0, e1), element e = (i, j, v) = (e / (4 NJ), e / 4 % NJ, e % 4): P = 2^(c * S - lse * log2 e), dS = P * (dP - D);
         // finished pairs are rounded to bf16 into the operand fragments of C: slots 4 i + v of row block j
         // An element's exponential and the multiply that consumes it are issued one element apart (the
         // multiply of element e - 1 follows the exponential of element e): a transcendental's result may not
         // be read by the very next instruction, and the slot that would otherwise idle is not free.
-        struct Block { f32x4 v[2][2]; };                // [key block i][row block j]: element v of this lane is key 16 i + 4 g + v
+        constexpr int NE = 8 * NJ;
+        struct Block { f32x4 v[2][NJ]; };               // [key block i][row block j]: element v of this lane is key 16 i + 4 g + v
         u32x4 ck4;      // dropout: the column keys of four consecutive keys, read when the first is due
-        auto b_elems = [&](Block &sc, Block &dp, int jb, int e0, int e1, Frag<bf16_t> (&df)[2]) __attribute__((always_inline)) {
+        auto b_elems = [&](Block &sc, Block &dp, int jb, int e0, int e1, Frag<bf16_t> (&df)[NJ]) __attribute__((always_inline)) {
             auto finish = [&](int e) __attribute__((always_inline)) {       // sc holds P by now
-                const int i = e >> 3, j = e >> 2 & 1, v = e & 3;
+                const int i = e / (4 * NJ), j = e / 4 % NJ, v = e & 3;
                 f32x4 &d4 = dp.v[i][j];
                 if (DROP) {     // d4 holds dP (else dP - D)
-                    if ((e & 7) == 0)
+                    if (e % (4 * NJ) == 0)
                         ck4 = *reinterpret_cast<const u32x4 *>(ck_ring + (((jb >> 6) & 3) * C::BC + (jb & 63) + 16 * i + 4 * g) * 4);
                     d4[v] = fmaf(d4[v], drop_keep(drop_rk[j], ck4[v], dr.thr) ? dr.scale : 0.f, -Dr[j]);
                 }
@@ -200,10 +201,10 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
             };
 #pragma unroll
             for (int e = e0; e < e1; ++e) {
-                f32x4 &p4 = sc.v[e >> 3][e >> 2 & 1];
-                p4[e & 3] = fast_exp2(p4[e & 3] * c - L2[e >> 2 & 1]);
+                f32x4 &p4 = sc.v[e / (4 * NJ)][e / 4 % NJ];
+                p4[e & 3] = fast_exp2(p4[e & 3] * c - L2[e / 4 % NJ]);
                 if (e > 0) finish(e - 1);
-                if (e == 15) finish(15);
+                if (e == NE - 1) finish(e);
             }
         };
         // Where the causal diagonal or the end of the sequence crosses a block (first key jb), the
@@ -215,7 +216,7 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
             const bool diag = s.causal && (jb + 31 > (int)s.s0 + rw0);
             if (diag || jb + 32 > s.l_x) {
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
+                for (int j = 0; j < NJ; ++j) {
                     const int last = s.causal ? min((int)s.s0 + rw0 + 16 * j + lq, s.l_x - 1) : s.l_x - 1;
                     const int rel = max(min(last - jb - 4 * g, 64), -1);
 #pragma unroll
@@ -228,8 +229,8 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
         };
 
         // One pipeline step.  A: block (tile_a, kb2_a) into (sc_a, dp_a).  B: (sc_b, dp_b), first key
-        // jb_b, packing into df_b.  C: block (tile_c, kb2_c) from df_c into acc.  Per unit two matrix
-        // instructions of C and four of A (A first in the last unit); after each one come the B elements that fall to its slot.
+        // jb_b, packing into df_b.  C: block (tile_c, kb2_c) from df_c into acc.  Per unit NJ matrix
+        // instructions of C and 2 NJ of A (A first in the last unit); after each one come the B elements that fall to its slot.
         // Operand fragments are read from LDS one unit ahead of their use; those of the first unit
         // by the step before (ak[0], av[0], ck[0] on entry), and this step leaves there those of
         // the next step: A on block (tile_an, kb2_an), C on (tile_cn, kb2_cn).  `mid` runs before
@@ -237,15 +238,15 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
         // blocks may lie in the tile that the barrier publishes.
         Frag<bf16_t> ak[2], av[2], ck[2];
         auto step = [&](auto has_a, auto has_b, auto has_c, const char *tile_a, int kb2_a, Block &sc_a, Block &dp_a,
-                        Block &sc_b, Block &dp_b, int jb_b, Frag<bf16_t> (&df_b)[2], const char *tile_c, int kb2_c,
-                        Frag<bf16_t> (&df_c)[2], const char *tile_an, int kb2_an, const char *tile_cn, int kb2_cn, auto &&mid)
+                        Block &sc_b, Block &dp_b, int jb_b, Frag<bf16_t> (&df_b)[NJ], const char *tile_c, int kb2_c,
+                        Frag<bf16_t> (&df_c)[NJ], const char *tile_an, int kb2_an, const char *tile_cn, int kb2_cn, auto &&mid)
             __attribute__((always_inline)) {
             constexpr bool HA = decltype(has_a)::value, HB = decltype(has_b)::value, HC = decltype(has_c)::value;
-            constexpr int NS = 6 * NU;                  // slots; 16 elements of B spread over them
+            constexpr int PU = 3 * NJ, NS = PU * NU;    // slots per unit and in all; the elements of B spread over them
             static_assert(NU % 2 == 0, "fragment double buffers assume an even number of units");
             auto b_slot = [&](int slot) __attribute__((always_inline)) {
                 if (HB) {
-                    const int e0 = slot * 16 / NS, e1 = (slot + 1) * 16 / NS;
+                    const int e0 = slot * NE / NS, e1 = (slot + 1) * NE / NS;
                     if (e0 == e1) return;
                     __builtin_amdgcn_sched_barrier(0);
                     b_elems(sc_b, dp_b, jb_b, e0, e1, df_b);
@@ -257,24 +258,24 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
                 // B's inputs pass through an empty asm here: its arithmetic depends on nothing else in
                 // this step, and the compiler would otherwise move all of it out of the step, in one lump
 #pragma unroll
-                for (int i = 0; i < 2; ++i) asm volatile("" : "+v"(sc_b.v[i][0]), "+v"(sc_b.v[i][1]), "+v"(dp_b.v[i][0]), "+v"(dp_b.v[i][1]));
+                for (int n = 0; n < 2 * NJ; ++n) asm volatile("" : "+v"(sc_b.v[n / NJ][n % NJ]), "+v"(dp_b.v[n / NJ][n % NJ]));
             }
             auto do_a = [&](int u, int slot) __attribute__((always_inline)) {
                 const int i = u % 2, ks = u / 2;
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    if (HA) sc_a.v[i][j] = mma16(ak[u & 1], qf[2 * ks + j], ks == 0 ? zero4 : sc_a.v[i][j]);
+                for (int j = 0; j < NJ; ++j) {
+                    if (HA) sc_a.v[i][j] = mma16(ak[u & 1], qf[ks][j], ks == 0 ? zero4 : sc_a.v[i][j]);
                     b_slot(slot + j);
                 }
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    if (HA) dp_a.v[i][j] = mma16(av[u & 1], gf[2 * ks + j], ks == 0 ? (DROP ? zero4 : neg_d[j]) : dp_a.v[i][j]);
-                    b_slot(slot + 2 + j);
+                for (int j = 0; j < NJ; ++j) {
+                    if (HA) dp_a.v[i][j] = mma16(av[u & 1], gf[ks][j], ks == 0 ? (DROP ? zero4 : neg_d[j]) : dp_a.v[i][j]);
+                    b_slot(slot + NJ + j);
                 }
             };
             auto do_c = [&](int u, int slot) __attribute__((always_inline)) {
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
+                for (int j = 0; j < NJ; ++j) {
                     if (HC) acc[u][j] = mma16(ck[u & 1], df_c[j], acc[u][j]);
                     b_slot(slot + j);
                 }
@@ -285,20 +286,22 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
                     if (HC) load_c(tile_c, kb2_c, u + 1, ck[(u + 1) & 1]);
                     if (HA) load_a(tile_a, kb2_a, u + 1, ak[(u + 1) & 1], av[(u + 1) & 1]);
                     __builtin_amdgcn_sched_barrier(0);
-                    do_c(u, 6 * u);
-                    do_a(u, 6 * u + 2);
+                    do_c(u, PU * u);
+                    do_a(u, PU * u + NJ);
                 } else {
                     // last unit: A first, so that its results are there when the next step's B wants them
-                    do_a(u, 6 * u);
+                    do_a(u, PU * u);
                     mid();
                     load_c(tile_cn, kb2_cn, 0, ck[0]);
                     load_a(tile_an, kb2_an, 0, ak[0], av[0]);
                     __builtin_amdgcn_sched_barrier(0);
-                    do_c(u, 6 * u + 4);
+                    do_c(u, PU * u + 2 * NJ);
                 }
             }
             // ... and its results through another one, so that it is not sunk below the step either
-            if (HB) asm volatile("" : "+v"(df_b[0].v), "+v"(df_b[1].v));
+            if (HB)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) asm volatile("" : "+v"(df_b[j].v));
         };
         using std::true_type;
         using std::false_type;
@@ -322,13 +325,13 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
             }
         } else if (KG == 1 || T > 0) {
             Block sc0, dp0, sc1, dp1;                       // even / odd blocks
-            Frag<bf16_t> df0[2], df1[2];
+            Frag<bf16_t> df0[NJ], df1[NJ];
             // step -1: A(0) alone.  The first loop step has no C(-1): it multiplies zeros with tile 0 instead.
             load_a(ring, 0, 0, ak[0], av[0]);
             auto nothing = [] {};
             step(true_type{}, false_type{}, false_type{}, ring, 0, sc0, dp0, sc1, dp1, 0, df0, ring, 0, df1, ring, 1, ring, 1, nothing);
     #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < NJ; ++j)
     #pragma unroll
                 for (int e = 0; e < 8; ++e) df1[j].v[e] = (bf16_t)0.f;
 
@@ -369,7 +372,7 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
 
     if constexpr (KG > 1) {
         // The groups' sums meet in LDS, where the tiles were: each adds up half the columns, in group order.
-        static_assert(KG == 2 && D == 64, "");
+        static_assert(KG == 2 && D == 64 && NJ == 2, "");
         auto hand = [&](int of, int u) { return reinterpret_cast<f32x4 *>(smem + ((of * C::WAVES + wave) * NU + u) * 1024 + lane * 16); };
         __syncthreads();
 #pragma unroll
@@ -382,7 +385,7 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
     const float scale = 1.f / sqrtf((float)D);
     constexpr int DB = KG > 1 ? NU / 2 : NU;            // (two groups: half the column blocks, in the first half of acc)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < NJ; ++j) {
         const int r = rw0 + 16 * j + lq;
         if (r >= s.l_s) continue;
         const int64_t at = ((int64_t)b * s.l_s + r) * ld + (int64_t)h * D + (KG > 1 ? 16 * DB * group : 0) + 4 * g;
@@ -427,37 +430,37 @@ __device__ __forceinline__ void store_key_rows(char *buf, const f32x16 (&acc)[D 
 
 // The same for a tile held as 16 x 16 blocks: block (db, j), element v of a lane is key 16 j + lane % 16, column
 // 16 db + 4 (lane / 16) + v.
-template <int D>
-__device__ __forceinline__ void store_key_rows16(char *buf, const f32x4 (&acc)[D / 16][2], float scale, float *__restrict__ dst,
+template <int D, int NJ>
+__device__ __forceinline__ void store_key_rows16(char *buf, const f32x4 (&acc)[D / 16][NJ], float scale, float *__restrict__ dst,
                                                  int64_t ld, int rows_ok, int lane)
 {
     constexpr int CH = D / 4;                           // 16-byte chunks per row
 #pragma unroll
     for (int db = 0; db < D / 16; ++db)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < NJ; ++j) {
             const int key = 16 * j + (lane & 15), c = 4 * db + (lane >> 4);
             const f32x4 a = acc[db][j];
             *reinterpret_cast<f32x4 *>(buf + key * (D * 4) + ((c ^ (key & (CH - 1))) * 16)) = f32x4{a[0] * scale, a[1] * scale, a[2] * scale, a[3] * scale};
         }
     constexpr int RPI = 64 / CH;                        // rows per store instruction
 #pragma unroll
-    for (int i = 0; i < 32 / RPI; ++i) {
+    for (int i = 0; i < 16 * NJ / RPI; ++i) {
         const int row = i * RPI + lane / CH, c = lane % CH;
         const f32x4 val = *reinterpret_cast<const f32x4 *>(buf + row * (D * 4) + ((c ^ (row & (CH - 1))) * 16));
         if (row < rows_ok) *reinterpret_cast<f32x4 *>(dst + (int64_t)row * ld + c * 4) = val;
     }
 }
 
-template <int D, bool DROP = false>
+template <int D, bool DROP = false, int NJ = 2>
 struct DkvBf16Cfg {
     // One 32-row key block per wavefront.  Two blocks would halve the LDS traffic per flop but
     // their accumulators leave room for only one wavefront per SIMD, which measures slower.
-    static constexpr int WAVES = 4, KW = 32;            // key rows per wavefront
-    static constexpr int BKV = WAVES * KW, BQ = 64, NT = 256;
+    static constexpr int WAVES = 8 / NJ, KW = 16 * NJ;  // key rows per wavefront: NJ blocks of 16
+    static constexpr int BKV = WAVES * KW, BQ = 64, NT = 64 * WAVES;
     static constexpr int RING = 3;                      // Q/dO tiles resident in LDS
     static constexpr int NU = D / 16;                   // operand steps of the S/dP products; same for dV/dK
-    using Tile = DirectTile<D, BQ>;
+    using Tile = DirectTile<D, BQ, WAVES>;
     // one ring slot: Q tile, dO tile, 64 S-accumulator start values, 64 dP-accumulator start values
     // (with dropout also the 64 rows' generator keys)
     static constexpr int OFF_G = Tile::BYTES, OFF_L = 2 * Tile::BYTES, OFF_D = OFF_L + BQ * 4, OFF_R = OFF_D + BQ * 4;
@@ -520,7 +523,7 @@ __device__ __forceinline__ void neg_row_dots(const bf16_t *__restrict__ out, con
 //
 // OWN: the workgroup computes the start values (and keys) of its rows itself, into LDS, while its first
 // tiles are on their way, instead of finding them in memory (bwd_own_values).
-template <int D, bool DROP, bool OWN, int KG>
+template <int D, bool DROP, bool OWN, int KG, int NJ>
 __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, const DropArgs &dr, const bf16_t *__restrict__ q,
                                              const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
                                              const bf16_t *__restrict__ out, const bf16_t *__restrict__ dO,
@@ -528,7 +531,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
                                              const float *__restrict__ Dn, const uint32_t *__restrict__ row_key,
                                              float *__restrict__ dk_part, float *__restrict__ dv_part, int bh, int key_tile)
 {
-    using C = DkvBf16Cfg<D, DROP>;
+    using C = DkvBf16Cfg<D, DROP, NJ>;
     using Tile = typename C::Tile;
     constexpr int NU = C::NU;
 
@@ -566,36 +569,36 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         return;
     }
 
-    // this lane's two keys (columns of the S blocks), jw0 + 16 j + lk; keys past the sequence re-read its last row
+    // this lane's keys (columns of the S blocks), jw0 + 16 j + lk; keys past the sequence re-read its last row
     // (unconditional loads), take part in all the arithmetic and are never stored
-    Frag<bf16_t> kf[NU], vf[NU];                        // operand step ks (32 columns), key block j: [2 ks + j]
+    Frag<bf16_t> kf[NU / 2][NJ], vf[NU / 2][NJ];        // operand step ks (32 columns), key block j
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < NJ; ++j) {
         const int64_t off = kv_base + (int64_t)min(jw0 + 16 * j + lk, s.l_x - 1) * ld + g * 8;
 #pragma unroll
         for (int ks = 0; ks < NU / 2; ++ks) {
-            kf[2 * ks + j] = load_frag<bf16_t>(k + off + ks * 32);
-            vf[2 * ks + j] = load_frag<bf16_t>(v + off + ks * 32);
+            kf[ks][j] = load_frag<bf16_t>(k + off + ks * 32);
+            vf[ks][j] = load_frag<bf16_t>(v + off + ks * 32);
         }
     }
-    if constexpr (D == 128) {
+    if constexpr (D == 128 && NJ == 2) {
         // At d = 128 the kernel needs more than 256 registers and the allocator parks these 64 in the
         // accumulation half of the register file -- then copies each into a vector register before
         // every use (54 to 68 copies per 32 matrix instructions).  A matrix instruction can read its
         // B operand from that half directly: naming the class here makes it do so.
 #pragma unroll
-        for (int kb = 0; kb < NU; ++kb) {
-            asm volatile("" : "+a"(kf[kb].v));
-            asm volatile("" : "+a"(vf[kb].v));
+        for (int n = 0; n < NU; ++n) {
+            asm volatile("" : "+a"(kf[n / 2][n % 2].v));
+            asm volatile("" : "+a"(vf[n / 2][n % 2].v));
         }
     }
 
     const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-    f32x4 dk[NU][2], dv[NU][2];                         // 16 columns x 16 keys each, transposed
+    f32x4 dk[NU][NJ], dv[NU][NJ];                       // 16 columns x 16 keys each, transposed
 #pragma unroll
     for (int db = 0; db < NU; ++db)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) dk[db][j] = dv[db][j] = zero4;
+        for (int j = 0; j < NJ; ++j) dk[db][j] = dv[db][j] = zero4;
 
     const float sqrt_d = sqrtf((float)D);
     const float c = kLog2e / sqrt_d;
@@ -603,13 +606,13 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     const bf16_t *gbase = dO + (int64_t)b * s.l_s * ld + (int64_t)h * D;
     const float *lbase = Ls + (int64_t)bh * s.l_s, *dbase = Dn + (int64_t)bh * s.l_s;
     const uint32_t *rbase = DROP ? row_key + (int64_t)bh * s.l_s : nullptr;
-    uint32_t drop_ck[2] = {0u, 0u};                     // this lane's keys
+    uint32_t drop_ck[NJ];                                // this lane's keys
     if (DROP)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) drop_ck[j] = drop_col_key(drop_col_seed(dr.seed_hi), (uint32_t)(jw0 + 16 * j + lk));
+        for (int j = 0; j < NJ; ++j) drop_ck[j] = drop_col_key(drop_col_seed(dr.seed_hi), (uint32_t)(jw0 + 16 * j + lk));
 
-    // ---- tile loads: all four wavefronts move Q and dO, and the 64 start values of either kind (even
-    // wavefronts -lse*sqrt(d), odd ones -D; each twice, which is cheaper than a branch inside a pipeline
+    // ---- tile loads: all wavefronts of the group move Q and dO, and the 64 start values of either kind (even
+    // wavefronts -lse*sqrt(d), odd ones -D; each several times, which is cheaper than a branch inside a pipeline
     // step: a branch splits the step into basic blocks, and the vector work meant to sit between its
     // matrix instructions is then moved behind the branch in one lump)
     uint32_t offF[Tile::NI], offD[Tile::NI];            // this lane's global offsets within a full tile; and what
@@ -678,13 +681,14 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     // Where the causal diagonal or the end of the segment crosses the block (first row: local row
     // r0), the masked elements of its finished S are set to -inf, which B turns into P = dS = 0: rows before
     // the lane's key, and rows past the segment (whose loads re-read its last row).
-    struct Block { f32x4 v[2][2]; };                    // [row block i][key block j]
+    constexpr int NE = 8 * NJ;
+    struct Block { f32x4 v[2][NJ]; };                   // [row block i][key block j]
     auto mask_s = [&](int r0, Block &sc) __attribute__((always_inline)) {
         const bool diag = s.causal && (jw0 + C::KW - 1 > (int)s.s0 + r0);      // positions are below 2^30: 32-bit scalar compare
         if (diag || r0 + 32 > s.l_s) {
             const int end = min(s.l_s - r0, 32) - 4 * g;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < NJ; ++j) {
                 const int first = diag ? max(min(jw0 + 16 * j + lk - (int)s.s0 - r0 - 4 * g, 64), 0) : 0;
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
@@ -694,7 +698,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
             }
         }
     };
-    // B for elements [e0, e1), element e = (i, j, v) = (e / 8, e / 4 % 2, e % 4): P = 2^(c * (S - lse*sqrt(d))), dS = P * (dP - D);
+    // B for elements [e0, e1), element e = (i, j, v) = (e / (4 NJ), e / 4 % NJ, e % 4): P = 2^(c * (S - lse*sqrt(d))), dS = P * (dP - D);
     // finished pairs are rounded to bf16 into the operand fragments of C: slots 4 i + v of key block j.
     // (dropout: `sv_b` are B's start values; the row keys and -D of four rows are read when
     // the first of them is due)
@@ -702,13 +706,13 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     // workgroups: a transcendental's result may not be read by the very next instruction.)
     u32x4 rk4;
     f32x4 nd4;
-    auto b_elems = [&](const char *sv_b, Block &sc, Block &dp, int e0, int e1, Frag<bf16_t> (&pf)[2],
-                       Frag<bf16_t> (&df)[2]) __attribute__((always_inline)) {
+    auto b_elems = [&](const char *sv_b, Block &sc, Block &dp, int e0, int e1, Frag<bf16_t> (&pf)[NJ],
+                       Frag<bf16_t> (&df)[NJ]) __attribute__((always_inline)) {
         auto finish = [&](int e) __attribute__((always_inline)) {           // sc holds P by now
-            const int i = e >> 3, j = e >> 2 & 1, v = e & 3;
+            const int i = e / (4 * NJ), j = e / 4 % NJ, v = e & 3;
             f32x4 &p4 = sc.v[i][j], &d4 = dp.v[i][j];
             if constexpr (DROP) {
-                if ((e & 7) == 0) {
+                if (e % (4 * NJ) == 0) {
                     rk4 = *reinterpret_cast<const u32x4 *>(sv_b + SV_R + i * 64);
                     nd4 = *reinterpret_cast<const f32x4 *>(sv_b + SV_D + i * 64);
                 }
@@ -725,15 +729,15 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         };
 #pragma unroll
         for (int e = e0; e < e1; ++e) {
-            f32x4 &p4 = sc.v[e >> 3][e >> 2 & 1];
+            f32x4 &p4 = sc.v[e / (4 * NJ)][e / 4 % NJ];
             p4[e & 3] = fast_exp2(p4[e & 3] * c);
             if (e > 0) finish(e - 1);
-            if (e == 15) finish(15);
+            if (e == NE - 1) finish(e);
         }
     };
     // One pipeline step.  A: block (tile_a, qb_a) into (sc_a, dp_a), from the start values in sv_l and sv_d.  B: (sc_b, dp_b),
-    // first row r0_b, packing into (pf_b, df_b).  C: block (tile_c, qb_c) from (pf_c, df_c) into dk, dv.  Per unit four matrix
-    // instructions of C and four of A (A first in the last unit), each pair on one operand fragment; after each come the B
+    // first row r0_b, packing into (pf_b, df_b).  C: block (tile_c, qb_c) from (pf_c, df_c) into dk, dv.  Per unit 2 NJ matrix
+    // instructions of C and 2 NJ of A (A first in the last unit), each pair on one operand fragment; after each come the B
     // elements that fall to its slot.
     // Everything read from LDS is requested well before its use: operand fragments one unit ahead;
     // for the next step (A on block (tile_an, qb_an), rows from rq_begin + row_an on, C on (tile_cn, qb_cn)) this step's last
@@ -743,15 +747,15 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     // the barrier publishes.
     Frag<bf16_t> cq[2], cg[2], aq[2], ag[2];
     auto step = [&](auto has_a, auto has_b, auto has_c, const char *tile_a, int qb_a, Block &sc_a,
-                    Block &dp_a, const char *sv_b, int r0_b, Block &sc_b, Block &dp_b, Frag<bf16_t> (&pf_b)[2],
-                    Frag<bf16_t> (&df_b)[2], const char *tile_c, int qb_c, Frag<bf16_t> (&pf_c)[2], Frag<bf16_t> (&df_c)[2],
+                    Block &dp_a, const char *sv_b, int r0_b, Block &sc_b, Block &dp_b, Frag<bf16_t> (&pf_b)[NJ],
+                    Frag<bf16_t> (&df_b)[NJ], const char *tile_c, int qb_c, Frag<bf16_t> (&pf_c)[NJ], Frag<bf16_t> (&df_c)[NJ],
                     const char *tile_an, int qb_an, int row_an, const char *tile_cn, int qb_cn, auto &&mid) __attribute__((always_inline)) {
         constexpr bool HA = decltype(has_a)::value, HB = decltype(has_b)::value, HC = decltype(has_c)::value;
-        constexpr int NS = 8 * NU;                      // slots; 16 elements of B spread over them
+        constexpr int PU = 4 * NJ, NS = PU * NU;        // slots per unit and in all; the elements of B spread over them
         static_assert(NU % 2 == 0, "fragment double buffers assume an even number of units");
         auto b_slot = [&](int slot) __attribute__((always_inline)) {
             if (HB) {
-                const int e0 = slot * 16 / NS, e1 = (slot + 1) * 16 / NS;
+                const int e0 = slot * NE / NS, e1 = (slot + 1) * NE / NS;
                 if (e0 == e1) return;
                 __builtin_amdgcn_sched_barrier(0);
                 b_elems(sv_b, sc_b, dp_b, e0, e1, pf_b, df_b);
@@ -763,31 +767,31 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         if (HB) {
             mask_s(r0_b, sc_b);
 #pragma unroll
-            for (int i = 0; i < 2; ++i) asm volatile("" : "+v"(sc_b.v[i][0]), "+v"(sc_b.v[i][1]), "+v"(dp_b.v[i][0]), "+v"(dp_b.v[i][1]));
+            for (int n = 0; n < 2 * NJ; ++n) asm volatile("" : "+v"(sc_b.v[n / NJ][n % NJ]), "+v"(dp_b.v[n / NJ][n % NJ]));
         }
         auto do_a = [&](int u, int slot) __attribute__((always_inline)) {
             const int i = u % 2, ks = u / 2;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                if (HA) sc_a.v[i][j] = mma16(aq[u & 1], kf[2 * ks + j], ks == 0 ? sv_l[i] : sc_a.v[i][j]);
+            for (int j = 0; j < NJ; ++j) {
+                if (HA) sc_a.v[i][j] = mma16(aq[u & 1], kf[ks][j], ks == 0 ? sv_l[i] : sc_a.v[i][j]);
                 b_slot(slot + j);
             }
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                if (HA) dp_a.v[i][j] = mma16(ag[u & 1], vf[2 * ks + j], ks == 0 ? (DROP ? zero4 : sv_d[i]) : dp_a.v[i][j]);
-                b_slot(slot + 2 + j);
+            for (int j = 0; j < NJ; ++j) {
+                if (HA) dp_a.v[i][j] = mma16(ag[u & 1], vf[ks][j], ks == 0 ? (DROP ? zero4 : sv_d[i]) : dp_a.v[i][j]);
+                b_slot(slot + NJ + j);
             }
         };
         auto do_c = [&](int u, int slot) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < NJ; ++j) {
                 if (HC) dv[u][j] = mma16(cg[u & 1], pf_c[j], dv[u][j]);
                 b_slot(slot + j);
             }
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < NJ; ++j) {
                 if (HC) dk[u][j] = mma16(cq[u & 1], df_c[j], dk[u][j]);
-                b_slot(slot + 2 + j);
+                b_slot(slot + NJ + j);
             }
         };
 #pragma unroll
@@ -796,21 +800,23 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
                 if (HC) load_c(tile_c, qb_c, u + 1, cq[(u + 1) & 1], cg[(u + 1) & 1]);
                 if (HA) load_a(tile_a, qb_a, u + 1, aq[(u + 1) & 1], ag[(u + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);
-                do_c(u, 8 * u);
-                do_a(u, 8 * u + 4);
+                do_c(u, PU * u);
+                do_a(u, PU * u + 2 * NJ);
             } else {
                 // last unit: A first, so that its results are there when the next step's B wants them
-                do_a(u, 8 * u);
+                do_a(u, PU * u);
                 mid();
                 load_c(tile_cn, qb_cn, 0, cq[0], cg[0]);
                 load_a(tile_an, qb_an, 0, aq[0], ag[0]);
                 init_load(start_values(tile_an, qb_an, row_an));
                 __builtin_amdgcn_sched_barrier(0);
-                do_c(u, 8 * u + 4);
+                do_c(u, PU * u + 2 * NJ);
             }
         }
         // ... and its results through another one, so that it is not sunk below the step either
-        if (HB) asm volatile("" : "+v"(pf_b[0].v), "+v"(pf_b[1].v), "+v"(df_b[0].v), "+v"(df_b[1].v));
+        if (HB)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) asm volatile("" : "+v"(pf_b[j].v), "+v"(df_b[j].v));
     };
     using std::true_type;
     using std::false_type;
@@ -844,7 +850,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
 
     if (KG == 1 || T > 0) {
         Block sc0, dp0, sc1, dp1;                       // even / odd blocks
-        Frag<bf16_t> pf0[2], df0[2], pf1[2], df1[2];
+        Frag<bf16_t> pf0[NJ], df0[NJ], pf1[NJ], df1[NJ];
         // step -1: A(0) alone (leaves the first loop step's C operands in cq[0], cg[0]).  That step has
         // no C(-1): it multiplies zeros with tile 0 instead.
         auto nothing = [] {};
@@ -853,7 +859,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         step(true_type{}, false_type{}, false_type{}, ring, 0, sc0, dp0, ring, 0, sc1, dp1, pf0, df0, ring, 0,
              pf1, df1, ring, 1, row_base + 32, ring, 1, nothing);
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
             for (int e = 0; e < 8; ++e) { pf1[j].v[e] = (bf16_t)0.f; df1[j].v[e] = (bf16_t)0.f; }
 
@@ -896,16 +902,16 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     __syncthreads();
     {
         // (a buffer per wavefront for its finished tile, see store_key_rows)
-        char *buf = smem + all_waves * (32 * D * 4);
+        char *buf = smem + all_waves * (C::KW * D * 4);
         const int64_t off = kv_base + (int64_t)jw0 * ld;
         const int rows_ok = min(s.l_x - jw0, C::KW);
         if constexpr (KG == 1) {
-            store_key_rows16<D>(buf, dk, 1.f / sqrt_d, dk_part + off, ld, rows_ok, lane);
-            store_key_rows16<D>(buf, dv, 1.f, dv_part + off, ld, rows_ok, lane);
+            store_key_rows16<D, NJ>(buf, dk, 1.f / sqrt_d, dk_part + off, ld, rows_ok, lane);
+            store_key_rows16<D, NJ>(buf, dv, 1.f, dv_part + off, ld, rows_ok, lane);
         } else {
             // The groups' sums meet in LDS: the first finishes dV, the second dK, adding in group order.  What a wavefront
             // reads was written for it alone, into the buffer that is its own from then on.
-            static_assert(KG == 2 && D == 64, "");
+            static_assert(KG == 2 && D == 64 && NJ == 2, "");
             char *const theirs = smem + (all_waves ^ C::WAVES) * (32 * D * 4);
             f32x4 sum[NU][2];
 #pragma unroll
@@ -915,7 +921,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
 #pragma unroll
             for (int u = 0; u < 2 * NU; ++u)
                 sum[u / 2][u % 2] = (group == 0 ? dv[u / 2][u % 2] : dk[u / 2][u % 2]) + *reinterpret_cast<const f32x4 *>(buf + u * 1024 + lane * 16);
-            store_key_rows16<D>(buf, sum, group == 0 ? 1.f : 1.f / sqrt_d, (group == 0 ? dv_part : dk_part) + off, ld, rows_ok, lane);
+            store_key_rows16<D, NJ>(buf, sum, group == 0 ? 1.f : 1.f / sqrt_d, (group == 0 ? dv_part : dk_part) + off, ld, rows_ok, lane);
         }
     }
 }
@@ -1458,16 +1464,19 @@ __global__ __launch_bounds__(256) void bwd_prep_bf16_kernel(SegShape s, DropArgs
 // KG = 2: a workgroup is two groups of four wavefronts, with tiles of their own in LDS, that walk half the key tiles (dQ) or query
 // tiles (dK/dV) each and add their sums up in LDS, in group order.  As many wavefronts per compute unit as two workgroups
 // of one group, each with half the walk: for launches that leave compute units idle or wait for their longest walk (pick_bwd_plan).
-template <int D, bool DROP, bool OWN, bool SKINNY = false, int KG = 1>
-__global__ __launch_bounds__(256 * KG, D == 64 ? 2 : 1) void bwd_main_bf16_kernel(
+// NJ: blocks of 16 keys or query rows per wavefront.  One instead of two (D = 128): eight wavefronts of 16 rows instead of four of 32, in half
+// the registers, so that a SIMD has two of them and the matrix instructions of one run beside the vector work of the other;
+// but every operand read from LDS feeds one instruction instead of two.  See bwd_narrow.
+template <int D, bool DROP, bool OWN, bool SKINNY = false, int KG = 1, int NJ = 2>
+__global__ __launch_bounds__(64 * (8 / NJ) * KG, D == 64 || NJ == 1 ? 2 : 1) void bwd_main_bf16_kernel(
     SegShape s, DropArgs dr, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
     const bf16_t *__restrict__ out, const bf16_t *__restrict__ dO, const float *__restrict__ lse,
     const float *__restrict__ Ls, const float *__restrict__ Dn, const uint32_t *__restrict__ row_key, bf16_t *__restrict__ dq,
     float *__restrict__ dq_part, float *__restrict__ dk_part, float *__restrict__ dv_part, int n_splits, int n_dq, int n_q_tiles,
     int n_key_tiles)
 {
-    using DkvC = DkvBf16Cfg<D, DROP>;
-    constexpr int SMEM_DQ = KG * DqBf16Cfg<D>::group_lds(DROP);
+    using DkvC = DkvBf16Cfg<D, DROP, NJ>;
+    constexpr int SMEM_DQ = KG * DqBf16Cfg<D, NJ>::group_lds(DROP);
     constexpr int SMEM_DKV = KG * DkvC::RING * DkvC::SLOT + (OWN && !SKINNY ? DkvC::OWN_BYTES : 0);
     constexpr int SMEM = SMEM_DQ > SMEM_DKV ? SMEM_DQ : SMEM_DKV;
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
@@ -1477,12 +1486,23 @@ __global__ __launch_bounds__(256 * KG, D == 64 ? 2 : 1) void bwd_main_bf16_kerne
     if (id >= n_dq) {
         if (!xcd_item(id - n_dq, bhs, n_key_tiles, s.causal, bh, inner)) return;
         if constexpr (SKINNY) bwd_dkv_skinny_body<D>(smem, s, q, k, v, out, dO, lse, dk_part, dv_part, bh, inner);
-        else bwd_dkv_body<D, DROP, OWN, KG>(smem, s, dr, q, k, v, out, dO, lse, Ls, Dn, row_key, dk_part, dv_part, bh, inner);
+        else bwd_dkv_body<D, DROP, OWN, KG, NJ>(smem, s, dr, q, k, v, out, dO, lse, Ls, Dn, row_key, dk_part, dv_part, bh, inner);
     } else {
         if (!xcd_item(id, bhs, n_q_tiles * n_splits, s.causal && s.s0 < s.l_s, bh, inner)) return;
-        bwd_dq_body<D, DROP, OWN, KG>(smem, s, dr, q, k, v, out, dO, lse, Dn, dq, dq_part, n_splits, inner % n_q_tiles, n_q_tiles, bh,
+        bwd_dq_body<D, DROP, OWN, KG, NJ>(smem, s, dr, q, k, v, out, dO, lse, Dn, dq, dq_part, n_splits, inner % n_q_tiles, n_q_tiles, bh,
                                   inner / n_q_tiles);
     }
+}
+
+// Whether a launch at d = 128 takes eight wavefronts of 16 rows per workgroup (NJ = 1): where no compute unit gets more than 32 walks of 64 query
+// rows past 128 keys.  Longer ones are held by the chip's power, of which twice the LDS reads take more: with NJ = 1 a 32k segment's
+// compute units are busy 12 % fewer cycles, but at a lower clock, 2.40 ms instead of 2.36.  50 launches, forward and backward:
+// those of 24 walks and less 0 to 12 % faster, 4.3 % on average (8 heads of 770 rows behind 1654: 82 -> 72 us, 4 of 813: 52 -> 49); above, 2 %
+// slower on average.
+static bool bwd_narrow(const SegShape &s)
+{
+    const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x;
+    return s.d == 128 && (seen + 127) / 128 * s.B * s.H * ((s.l_s + 63) / 64) <= 32 * 256;
 }
 
 // Whether the workgroups compute D and the start values themselves (never where a gradient overlaps `out`, see
@@ -1557,8 +1577,16 @@ static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, con
             kernel = with_drop ? (own ? bwd_main_bf16_kernel<D, true, true, false, 2> : bwd_main_bf16_kernel<D, true, false, false, 2>)
                                : (own ? bwd_main_bf16_kernel<D, false, true, false, 2> : bwd_main_bf16_kernel<D, false, false, false, 2>);
     }
+    unsigned threads = 256 * groups;
+    if constexpr (D == 128) {
+        if (!skinny && bwd_narrow(s)) {
+            kernel = with_drop ? (own ? bwd_main_bf16_kernel<D, true, true, false, 1, 1> : bwd_main_bf16_kernel<D, true, false, false, 1, 1>)
+                               : (own ? bwd_main_bf16_kernel<D, false, true, false, 1, 1> : bwd_main_bf16_kernel<D, false, false, false, 1, 1>);
+            threads = 512;
+        }
+    }
     TimedLaunch tl(K_BWD_MAIN_BF16, st);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_dkv + n_dq)), dim3(256 * groups), 0, st, s, drop, q, k, v, out, dO, lse, ws.Ls, ws.D, ws.row_key,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_dkv + n_dq)), dim3(threads), 0, st, s, drop, q, k, v, out, dO, lse, ws.Ls, ws.D, ws.row_key,
                        dq, ws.dq_part, dk_part, dv_part, n_splits, n_dq, n_q_tiles, n_key_tiles);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return hipSuccess;
