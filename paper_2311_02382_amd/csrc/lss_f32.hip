@@ -11,8 +11,8 @@
 // of |x y|, the size of the rounding an fp32 multiply-add makes at every step, while a matrix instruction here
 // adds 32 products per rounding instead of two (with eight of the nine the errors below stay as they are).
 // Relative errors against fp64 (512 rows, 2000 keys, N(0, 1) inputs; in brackets those of V_MFMA_F32_32X32X2_F32, which these kernels
-// used at first): out 4.4e-7 (5.8e-7), dq 4.1e-7 (6.4e-7), dk 5.4e-7 (7.0e-7), dv 5.4e-7 (6.8e-7); at three times the standard
-// deviation out 1.0e-6 (1.5e-6), dq 2.8e-6 (3.5e-6).
+// used at first): out 4.3e-7 (5.8e-7), dq 3.9e-7 (6.4e-7), dk 4.8e-7 (7.0e-7), dv 4.8e-7 (6.8e-7); at three times the standard
+// deviation out 1.0e-6 (1.5e-6), dq 2.7e-6 (3.5e-6).
 // What it buys: six V_MFMA_F32_16X16X32_BF16 (96 cycles) do what eight 16x16x4 fp32 ones (256 cycles) did: lx8k in single
 // precision, eight segments: forward 1605 -> 910 us, backward 5460 -> 2750 us (with 32x32x16 instructions).
 // 16x16x32 instructions take less power per product than 32x32x16 and add twice as many products per rounding: with them, operands read
@@ -205,7 +205,7 @@ struct PlaneTile {
     // Operands are read one step ahead of their use: `ahead` holds those of the first step on entry, and what `next` reads on return.
     template <int NJ, typename Next>
     static __device__ __forceinline__ Block<NJ> product(const char *tile, int row0, const int (&off)[D / 32], const Frag3 (&b)[D / 32][NJ], Frag3 &ahead,
-                                                    Next &&next)
+                                                        Next &&next)
     {
         constexpr int NS = D / 32;
         Block<NJ> c;
@@ -257,6 +257,13 @@ constexpr int kRowsPerWg = 128;             // query rows of a workgroup: four w
 // two wavefronts that take one of the two 32-row halves of every Q/dO tile and add their results up at the end --
 // twice as many workgroups, with chains half as long, for launches that do not fill the chip.
 template <int HALVES> constexpr int kKeysPerWg = 128 / HALVES;
+
+// lse * log2 e less its rounded value l2 (1.93e-8: what kLog2e was rounded off by); 0 for infinities and NaNs
+__device__ __forceinline__ float rounded_off(float lse, float l2)
+{
+    const float r = fmaf(lse, kLog2e, -l2) + lse * 1.925963e-8f;
+    return fabsf(r) < 1.f ? r : 0.f;
+}
 
 // A wavefront's sums, transposed: 16 columns x 16 rows (or keys) each
 template <int D, int NJ> struct Sums {
@@ -553,10 +560,8 @@ __device__ __forceinline__ void bwd_dq_f32_body(char *smem, const SegShape &s, c
         const float lv = lse[(int64_t)bh * s.l_s + rc], l2 = lv * kLog2e;
         L2[j] = r + 16 * j < s.l_s ? l2 : INFINITY;
         Dr[j] = Dv[(int64_t)bh * s.l_s + rc];
-        // what l2 was rounded off by (1.93e-8: of kLog2e) is a factor of all the row's weights, hence of its result: dq's
-        // error 4.3e-7 -> 3.9e-7
-        const float off_by = fmaf(lv, kLog2e, -l2) + lv * 1.925963e-8f;
-        scale[j] = (1.f - (fabsf(off_by) < 1.f ? off_by * kLn2 : 0.f)) / sqrtf((float)D);
+        // (what l2 was rounded off by is a factor of all the row's weights, hence of its result: dq's error 4.3e-7 -> 3.4e-7)
+        scale[j] = (1.f - rounded_off(lv, l2) * kLn2) / sqrtf((float)D);
     }
     if (tid == 0) *tiny_word = 0u;
     if constexpr (D == 128 && NJ == 2) {       // (operands live in the accumulation half of the register file: see the bf16 dK/dV workgroups)
@@ -693,7 +698,7 @@ __device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, 
     constexpr int NS = D / 32, BQ = Tile::ROWS;
     char *const sq = smem, *const sg = smem + Tile::BYTES;
     float *const sl = reinterpret_cast<float *>(smem + 2 * Tile::BYTES), *const sd = sl + 64;
-    uint32_t *const sr = reinterpret_cast<uint32_t *>(sd + 64), *const tiny_word = sr + 64;
+    uint32_t *const sr = reinterpret_cast<uint32_t *>(sd + 64), *const tiny_word = sr + 128;
     const int tid = threadIdx.x, lane = tid & 63, lq = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = bh / s.H, h = bh % s.H;
@@ -777,24 +782,27 @@ __device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, 
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int rl = qb * 32 + 16 * i + 4 * g, r4 = rb + 16 * i + 4 * g;          // in the tile; in the segment
-            f32x4 l4, d4;
+            f32x4 l4, d4, lo4;
             if constexpr (EXACT) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int64_t at = (int64_t)bh * s.l_s + min(r4 + e, s.l_s - 1);
-                    l4[e] = r4 + e < s.l_s ? lse[at] * kLog2e : INFINITY;
+                    const float lv = lse[at], l2 = lv * kLog2e;
+                    l4[e] = r4 + e < s.l_s ? l2 : INFINITY;
+                    lo4[e] = rounded_off(lv, l2);
                     d4[e] = Dv[at];
                 }
             } else {
                 l4 = *reinterpret_cast<const f32x4 *>(sl + rl);
                 d4 = *reinterpret_cast<const f32x4 *>(sd + rl);
+                lo4 = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(sr) + 64 + rl);
             }
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const uint32_t rk = !DROP ? 0u : EXACT ? drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + r4 + e)) : sr[rl + e];
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
-                    float p = fast_exp2(sc.v[i][j][e] * c - l4[e]);
+                    float p = fast_exp2(fmaf(sc.v[i][j][e], c, -l4[e]) - lo4[e]);
                     if (diag && key0 + 16 * j > (int)s.s0 + r4 + e) p = 0.f;
                     float pv = p, dpe = dp.v[i][j][e];
                     if (DROP) {
@@ -835,7 +843,9 @@ __device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, 
         Tile::note_tiny(gq, gg, tiny_word);
         if (tid < BQ) {     // rows past the segment: lse = +inf makes P (hence dS) exactly 0
             const int rr = rq0 + tid;
-            sl[tid] = rr < s.l_s ? lse[(int64_t)bh * s.l_s + rr] * kLog2e : INFINITY;
+            const float lv = lse[(int64_t)bh * s.l_s + min(rr, s.l_s - 1)], l2 = lv * kLog2e, off_by = rounded_off(lv, l2);
+            sl[tid] = rr < s.l_s ? l2 : INFINITY;
+            reinterpret_cast<float *>(sr)[64 + tid] = off_by;   // subtracted too: dk's and dv's errors fall by 4 to 20 %, for 1 % of lx8k
             sd[tid] = rr < s.l_s ? Dv[(int64_t)bh * s.l_s + rr] : 0.f;
             if (DROP) sr[tid] = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + rr));
         }
@@ -896,7 +906,7 @@ __global__ __launch_bounds__(512 / NJ, D == 64 || NJ == 1 ? 2 : 1) void bwd_main
     float *__restrict__ dq_part, float *__restrict__ dk_part, float *__restrict__ dv_part, int n_splits, int n_dq, int n_q_tiles,
     int n_key_tiles)
 {
-    __shared__ __attribute__((aligned(1024))) char smem[2 * PlaneTile<D>::BYTES + 3 * 64 * 4 + 16];
+    __shared__ __attribute__((aligned(1024))) char smem[2 * PlaneTile<D>::BYTES + 4 * 64 * 4 + 16];
     const int bhs = s.B * s.H, id = blockIdx.x;
     int bh, inner;
     if (id >= n_dq) {
