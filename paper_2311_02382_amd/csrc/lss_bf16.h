@@ -73,8 +73,8 @@ __device__ __forceinline__ void lds_dma_n(const void *g_uniform, const uint32_t 
 // half -- and 32 lanes of an 8-byte one.  The permutation is linear in bits 0 .. 3 of r, picked by going over all such maps so that no
 // two chunks that are served at once share a bank group, for plain fragment reads of 32 rows (32 x 32 x 16
 // instructions) and of 16 (16 x 16 x 32) as for transposing reads of 64 and of 32 bytes per row (load_frag_tr_sw,
-// load_frag_tr16_sw).  With r & 7 for D = 64 the plain reads of 32 rows took twice as long (lx50k forward: half of the LDS' cycles were
-// conflicts); at D = 128 those of 16 rows did with the one that there was (a third of the backward's).  Those kernels do not wait for the LDS:
+// load_frag_tr16_sw).  With r & 7 for D = 64 half of the LDS' cycles of the lx50k forward were counted as conflicts; at D = 128, with the
+// one that there was, a third of the backward's.  Those kernels do not wait for the LDS:
 // 32k keys at d = 128 2350 -> 2339 us, lx24k sweep 21.80 -> 21.76 ms; what it buys is room for more reads.
 template <int D>
 __device__ __forceinline__ int tile_swizzle(int r)

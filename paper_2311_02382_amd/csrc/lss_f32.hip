@@ -815,7 +815,7 @@ __device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, 
                 }
                 if (DROP && (e & 1)) __builtin_amdgcn_sched_barrier(0);
             }
-            if constexpr (EXACT) __builtin_amdgcn_sched_barrier(0);
+            if constexpr (EXACT || D == 64) __builtin_amdgcn_sched_barrier(0);     // (one row block at a time: 1 and 3 spills instead of 12 and 7)
         }
         if constexpr (EXACT) {
             add_product_f32<D>(gbase + (int64_t)rb * ld, ld, s.l_s - rb, sc, dv, lq, g);
