@@ -31,8 +31,8 @@ struct DropArgs {
 // skinny segment (l_s << l_x) still fills the chip.  Shape-only, deterministic.
 // `rows_per_wg` is the query-tile height of the kernel that will run (it differs per dtype).
 int choose_splits(int l_s, int l_x, int B, int H, int rows_per_wg);
-// Forward: the largest split count the workspace is sized for (shape-only), and the count a launch
-// uses for the `kv_tiles` 64-key tiles its query tiles actually see (never above the former).
+// Forward: the largest split count the workspace is sized for (shape-only), and the count a float launch
+// uses for the keys its query tiles actually see (never above the former).
 int max_fwd_splits(int l_s, int l_x, int B, int H, int rows_per_wg);
 int pick_float_fwd_splits(const SegShape &s, int max_splits);
 // bf16 forward: the workgroup's form -- blocks of 32 query rows x groups of wavefronts that have a part of the keys
