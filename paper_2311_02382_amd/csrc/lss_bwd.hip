@@ -9,6 +9,7 @@
 // The dQ workgroups (query-tile owned, split over key ranges) and the dK/dV workgroups (key-tile owned) share one
 // launch (lss_bwd_bf16.hip, lss_f32.hip); here are the fp32 path's D = rowsum(dO * out), the merge of the
 // dQ splits, and the launch sequence.  No atomics.
+#include "lss_bwd_plan.h"
 #include "lss_common.h"
 #include "lss_kernels.h"
 #include <algorithm>
@@ -62,7 +63,7 @@ __global__ __launch_bounds__(256) void bwd_dq_merge_kernel(const float *__restri
     else *reinterpret_cast<f32x4 *>(dq + i * 4) = acc;
 }
 
-// (bf16 with at most 64 rows, and at d = 128 the base of pick_splits; see pick_bwd_plan for d = 64)
+// (bf16 with at most 64 rows, and at d = 128 the base of pick_splits; see pick_bwd_plan in lss_bwd_plan.h for d = 64)
 // The dQ workgroups share their launch with the dK/dV ones and need not fill the chip alone: keys are split so far that
 // a dQ workgroup does not outlast the rest of the launch, never further than the workspace was sized for.  In 64-key
 // tiles of dQ, of which a lone workgroup takes one per 1.0 us (d = 64) or 1.4 us (d = 128):
@@ -97,53 +98,9 @@ static int pick_dq_splits(const SegShape &s, int most)
     return (int)(want < 1 ? 1 : want > most ? most : want);
 }
 
-// bf16, d = 64, more than 64 rows: key splits of the dQ workgroups, and whether a workgroup is one or two groups of wavefronts
-// (bwd_main_bf16_kernel).  A launch takes about, in us,
-//     start + (longest^6 + balance^6)^(1/6) + zeros / 9 MB + merge
-// longest: the longer of a dQ workgroup's walk over its 64-key tiles and a dK/dV workgroup's over the 64-row query tiles, each a few
-// tiles more, the latter slower as two workgroups come to share a compute unit; balance: all walks over 256 compute units, and a part of a last
-// dK/dV walk where the launch takes more than one round; zeros: the rows no query sees; merge: 1.8 us and the partial dQ's
-// bytes at 11 MB per us where there is more than one split.  Fitted to 100 launches (65 .. 4096 rows, 512 .. 50,112 keys, 2 .. 64 heads, both forms
-// with 1 .. 16 splits, after a forward call each): the choice costs 1.4 % over the best of them on average and takes 4.9 % less time
-// than one group with splits that only keep a dQ workgroup from outlasting the launch (8 heads of 1044 rows against 26,100 keys: 214 us, four splits
-// 192; 4 heads of 3510 rows behind 1226: 83 us, in two groups 55; 2 heads of 1362 rows: 32 and 27).
-struct BwdPlan { int splits, groups; };
-static BwdPlan pick_bwd_plan(const SegShape &s, int most)
-{
-    struct Cost { int groups; double start, dq_us, dq_more, dkv_us, dkv_more, dkv_slow, rate, last; };
-    static const Cost forms[] = {{1, 5.8, 0.70, 1.7, 1.02, 3.7, 0.35, 0.85, 0.31}, {2, 3.4, 1.11, 2.6, 1.52, 4.6, 0.0, 1.06, 0.51}};
-    const double bhs = (double)s.B * s.H;
-    const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x, first = s.causal ? s.s0 + (s.l_s < 128 ? s.l_s : 128) : (int64_t)s.l_x;
-    const int64_t tiles = (seen + 63) / 64, q_tiles = (s.l_s + 63) / 64, dq_tiles = (s.l_s + 127) / 128, key_tiles = (seen + 127) / 128;
-    const int64_t full = s.causal && s.s0 / 128 < key_tiles ? s.s0 / 128 : key_tiles;      // key tiles that all rows see; the others half of them
-    const double mean_tiles = 0.5 * (double)((first + 63) / 64 + tiles);
-    const double zeros_mb = (double)(s.l_x - seen) * bhs * s.d * 8e-6, dq_mb = bhs * s.l_s * s.d * 1e-6;
-    BwdPlan best{1, 1};
-    double best_t = 0.0;
-    for (const Cost &c : forms) {
-        if (c.groups > 1 && s.l_s <= 128) break;        // two tiles of rows: nothing to share
-        for (int sp = 1; sp <= most; ++sp) {
-            if (sp > 1 && tiles / sp < 4) break;
-            const double n_dq = (double)dq_tiles * bhs * sp, n_dkv = (double)key_tiles * bhs, N = n_dq + n_dkv;
-            const double shared = N < 256.0 ? 0.0 : N > 512.0 ? 1.0 : N / 256.0 - 1.0;
-            const double dq = ((double)(((tiles + sp - 1) / sp + c.groups - 1) / c.groups) + c.dq_more + 1.0) * c.dq_us;
-            const double dkv = ((double)((q_tiles + c.groups - 1) / c.groups) + c.dkv_more) * c.dkv_us * (1.0 + c.dkv_slow * shared);
-            const double longest = dq > dkv ? dq : dkv;
-            double balance = c.rate / 256.0 * (((double)dq_tiles * bhs * mean_tiles / c.groups + n_dq * c.dq_more) * c.dq_us +
-                                               (bhs * ((double)full + 0.5 * (double)(key_tiles - full)) * (double)q_tiles / c.groups + n_dkv * c.dkv_more) * c.dkv_us);
-            if (N > 512.0 / c.groups) balance += c.last * dkv;
-            // (one group, up to 512 rows: the workgroups compute D themselves, a launch less)
-            double t = c.start - (c.groups == 1 && s.l_s <= 512 ? 1.8 : 0.0) + pow(pow(longest, 6.0) + pow(balance, 6.0), 1.0 / 6.0) + zeros_mb / 9.0;
-            if (sp > 1) t += 1.8 + dq_mb * (4 * sp + 2) / 11.0;
-            if (best_t == 0.0 || t < best_t) { best_t = t; best = {sp, c.groups}; }
-        }
-    }
-    return best;
-}
-
 // float, and bf16 at d = 128 with more than 64 rows: a launch takes about, in us,
 //     start + (longest^6 + balance^6)^(1/6) + zeros + merge
-// as for bf16 above: the longer of a dQ workgroup's walk over its 64-key tiles and a dK/dV workgroup's over the 64-row query tiles
+// as in pick_bwd_plan: the longer of a dQ workgroup's walk over its 64-key tiles and a dK/dV workgroup's over the 64-row query tiles
 // (half the time where two wavefronts share a key block), slower as two workgroups share a compute unit; all walks over 256 compute units,
 // and a part of a last dK/dV walk where the launch takes more than one round.
 // float: fitted to 290 launches (30 .. 12,661 rows, 512 .. 22,136 keys, 2 .. 32 heads, 1 .. 16 splits, after a forward call each).
@@ -202,8 +159,8 @@ static hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const T *q
     const size_t rows_bytes = (size_t)s.B * s.l_s * s.H * D * sizeof(T), part_bytes = (size_t)s.B * s.l_x * s.H * D * sizeof(float);
     const bool out_first = overlaps(dq, rows_bytes, out, rows_bytes) || overlaps(dk_part, part_bytes, out, rows_bytes) ||
                            overlaps(dv_part, part_bytes, out, rows_bytes);
-    const BwdPlan plan = sizeof(T) == 4 || (D == 128 && s.l_s > 64) ? BwdPlan{pick_splits(s, most, (int)sizeof(T)), 1}
-                         : s.l_s > 64                               ? pick_bwd_plan(s, most)
+    const BwdPlan plan = sizeof(T) == 4 || (D == 128 && s.l_s > kSkinnyRows) ? BwdPlan{pick_splits(s, most, (int)sizeof(T)), 1}
+                         : s.l_s > kSkinnyRows                      ? pick_bwd_plan(s, most, !out_first)
                                                                     : BwdPlan{pick_dq_splits(s, most), 1};
     const int dq_splits = plan.splits;
     const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x;
@@ -211,8 +168,9 @@ static hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const T *q
     const int one_pass = out_first ? 0 : skinny_splits(s, dr.thr != 0, (int)sizeof(T), most, dq_tiles);
     const int n_splits = one_pass > 0 ? one_pass : dq_splits;
     if constexpr (sizeof(T) == 2) {
-        if ((e = launch_bwd_bf16_main(s, dr, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, plan.groups, one_pass > 0, out_first,
-                                      st)) != hipSuccess)
+        const bool own = !out_first && bwd_own_values(s, n_splits, plan.groups);
+        if ((e = launch_bwd_bf16_main(s, dr, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, plan.groups, one_pass > 0, own, st)) !=
+            hipSuccess)
             return e;
     } else {
         {

@@ -16,6 +16,7 @@
 //     layout allows (-D and -lse * sqrt(d) per row come from a small kernel, or from the workgroup itself: bwd_own_values).
 #include "lss_bf16.h"
 #include <type_traits>
+#include "lss_bwd_plan.h"
 #include "lss_kernels.h"
 #include <algorithm>
 #include <cmath>
@@ -466,7 +467,7 @@ struct DkvBf16Cfg {
     static constexpr int OFF_G = Tile::BYTES, OFF_L = 2 * Tile::BYTES, OFF_D = OFF_L + BQ * 4, OFF_R = OFF_D + BQ * 4;
     static constexpr int SLOT = OFF_R + (DROP ? BQ * 4 : 0);
     // OWN workgroups: the start values (and keys) of all rows behind the rings, up to OWN_MAX rows and one more tile
-    static constexpr int OWN_MAX = 512, OWN_ROWS = OWN_MAX + BQ, OWN_BYTES = OWN_ROWS * 4 * (DROP ? 3 : 2);
+    static constexpr int OWN_MAX = kOwnRows, OWN_ROWS = OWN_MAX + BQ, OWN_BYTES = OWN_ROWS * 4 * (DROP ? 3 : 2);
 };
 
 // -D = -rowsum(dO * out) of a row from its parts: D/8 consecutive lanes hold one 16-byte chunk each.
@@ -932,7 +933,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
 // with it, one 32-key block per wavefront as above: both 32-row blocks' S and dP, then their weights,
 // then dV^T and dK^T, in program order; the next key tile's K and V rows are requested from memory
 // before the current one is computed.  After the first barrier the wavefronts never meet again.
-constexpr int kSkinnyRows = 64, kSkinnyTilesPerWg = 4;
+constexpr int kSkinnyTilesPerWg = 4;
 template <int D>
 __device__ __forceinline__ void bwd_dkv_skinny_body(char *smem, const SegShape &s, const bf16_t *__restrict__ q,
                                                     const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
@@ -1505,28 +1506,6 @@ static bool bwd_narrow(const SegShape &s)
     return s.d == 128 && (seen + 127) / 128 * s.B * s.H * ((s.l_s + 63) / 64) <= 32 * 256;
 }
 
-// Whether the workgroups compute D and the start values themselves (never where a gradient overlaps `out`, see
-// launch_bwd_d): a launch less (2.3 us), for each dK/dV workgroup
-// 0.75 us per 128 rows of 64 elements or 1.5 us per 64 of 128 ahead of its loop.  That is spread over the rounds of
-// workgroups the chip takes (512 or 256 at once); a launch of one round or less pays it in full only if a dK/dV
-// workgroup's walk over the queries, and not a dQ workgroup's over its keys, is what the launch waits for.
-// 4 heads of 256 queries against 512 keys: backward 14.4 us with the preprocess kernel, 12.3 without; 10 x 4 heads of 67
-// against 47,600: 450 and 469.
-template <int D>
-static bool bwd_own_values(const SegShape &s, int n_splits, int groups)
-{
-    if (s.l_s <= kSkinnyRows) return true;      // one tile: loaded once per workgroup in any case
-    if (s.l_s > DkvBf16Cfg<D>::OWN_MAX) return false;
-    constexpr double kChunkUs = D == 64 ? 0.75 : 1.5, kRowTileUs = D == 64 ? 1.35 : 1.9, kKeyTileUs = D == 64 ? 1.0 : 1.4;
-    constexpr int kChunkRows = D == 64 ? 128 : 64, kAtOnce = D == 64 ? 512 : 256;
-    const int64_t seen = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
-    const double own_us = kChunkUs * ((s.l_s + kChunkRows - 1) / kChunkRows);
-    const double walk_us = kRowTileUs * ((s.l_s + 63) / 64) / groups, dq_us = kKeyTileUs * (double)((seen + 63) / 64) / (n_splits * groups);
-    double rounds = (double)((seen + 127) / 128 * s.B * s.H) / kAtOnce;
-    if (rounds < 1.0 && dq_us < walk_us + own_us) rounds = 1.0;
-    return own_us * rounds <= 2.0;
-}
-
 template <int QB>
 static hipError_t launch_skinny(const SegShape &s, const bf16_t *q, const bf16_t *k, const bf16_t *v, const bf16_t *out, const float *lse,
                                 const bf16_t *dO, bf16_t *dq, float *dk_part, float *dv_part, const Workspace &ws, int n_splits,
@@ -1546,11 +1525,11 @@ template <int D>
 static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                     const bf16_t *v, const bf16_t *out, const float *lse, const bf16_t *dO, bf16_t *dq,
                                     float *dk_part, float *dv_part, const Workspace &ws, int n_splits, int groups,
-                                    bool one_pass, bool out_first, hipStream_t st)
+                                    bool one_pass, bool own, hipStream_t st)
 {
     hipError_t e;
     const bool with_drop = drop.thr != 0;
-    const bool own = !out_first && bwd_own_values<D>(s, n_splits, groups), skinny = own && !with_drop && s.l_s <= kSkinnyRows;
+    const bool skinny = own && !with_drop && s.l_s <= kSkinnyRows;
     if constexpr (D == 64) {
         if (one_pass)
             return s.l_s <= 64 ? launch_skinny<2>(s, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, st)
@@ -1596,11 +1575,11 @@ static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, con
 // launch; the caller runs the dQ split merge
 hipError_t launch_bwd_bf16_main(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                 const bf16_t *v, const bf16_t *out, const float *lse, const bf16_t *dO, bf16_t *dq,
-                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, int groups, bool one_pass, bool out_first,
+                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, int groups, bool one_pass, bool own,
                                 hipStream_t st)
 {
-    if (s.d == 64) return launch_bwd_bf16_d<64>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, groups, one_pass, out_first, st);
-    return launch_bwd_bf16_d<128>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, groups, one_pass, out_first, st);
+    if (s.d == 64) return launch_bwd_bf16_d<64>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, groups, one_pass, own, st);
+    return launch_bwd_bf16_d<128>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, groups, one_pass, own, st);
 }
 
 } // namespace lss

@@ -1,0 +1,88 @@
+// How a bf16 backward launch is laid out, from sizes alone.  Plain C++ without a HIP header, so that a host program can go over
+// the choices (tests/host/plan_check.cpp).
+#pragma once
+#include "lss_shape.h"
+
+#include <math.h>
+
+namespace lss {
+
+constexpr int kSkinnyRows = 64;     // a segment of so many rows is one tile
+constexpr int kOwnRows = 512;       // rows whose start values fit the LDS of a workgroup that computes them itself
+
+// Whether the workgroups compute D and the start values themselves (never where a gradient overlaps `out`, see
+// launch_bwd_d): a launch less (2.3 us), for each dK/dV workgroup
+// 0.75 us per 128 rows of 64 elements or 1.5 us per 64 of 128 ahead of its loop.  That is spread over the rounds of
+// workgroups the chip takes (512 or 256 at once); a launch of one round or less pays it in full only if a dK/dV
+// workgroup's walk over the queries, and not a dQ workgroup's over its keys, is what the launch waits for.
+// 4 heads of 256 queries against 512 keys: backward 14.4 us with the preprocess kernel, 12.3 without; 10 x 4 heads of 67
+// against 47,600: 450 and 469.  680 launches of 66 .. 4096 rows at d = 64, every split count and form: 0.4 % over the better one.
+inline bool bwd_own_values(const SegShape &s, int n_splits, int groups)
+{
+    if (s.l_s <= kSkinnyRows) return true;      // one tile: loaded once per workgroup in any case
+    if (s.l_s > kOwnRows) return false;
+    const double chunk_us = s.d == 64 ? 0.75 : 1.5, row_tile_us = s.d == 64 ? 1.35 : 1.9, key_tile_us = s.d == 64 ? 1.0 : 1.4;
+    const int chunk_rows = s.d == 64 ? 128 : 64, at_once = s.d == 64 ? 512 : 256;
+    const int64_t seen = s.causal ? (s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x) : (int64_t)s.l_x;
+    const double own_us = chunk_us * ((s.l_s + chunk_rows - 1) / chunk_rows);
+    const double walk_us = row_tile_us * ((s.l_s + 63) / 64) / groups, dq_us = key_tile_us * (double)((seen + 63) / 64) / (n_splits * groups);
+    double rounds = (double)((seen + 127) / 128 * s.B * s.H) / at_once;
+    if (rounds < 1.0 && dq_us < walk_us + own_us) rounds = 1.0;
+    return own_us * rounds <= 2.0;
+}
+
+// bf16, d = 64, more than 64 rows: key splits of the dQ workgroups, and whether a workgroup is one or two groups of wavefronts
+// (bwd_main_bf16_kernel).  A launch takes about, in us,
+//     start + (longest^6 + balance^6)^(1/6) + zeros / 9 MB + merge
+// longest: the longer of a dQ workgroup's walk over its 64-key tiles and a dK/dV workgroup's over the 64-row query tiles, each a few
+// tiles more, the latter slower as two workgroups come to share a compute unit; balance: all walks over 256 compute units, and a part of a last
+// dK/dV walk where the launch takes more than one round; zeros: the rows no query sees; merge: 1.6 us and the partial dQ's
+// bytes at 11 MB per us where there is more than one split.  Fitted to 100 launches (65 .. 4096 rows, 512 .. 50,112 keys, 2 .. 64 heads, both forms
+// with 1 .. 16 splits, after a forward call each): launches take 4.9 % less time
+// than with one group and splits that only keep a dQ workgroup from outlasting the launch (8 heads of 1044 rows against 26,100 keys: 214 us, four splits
+// 192; 4 heads of 3510 rows behind 1226: 83 us, in two groups 55; 2 heads of 1362 rows: 32 and 27).  The starts, what is saved where no
+// preprocess launch is made and the merge's 1.6 us are fitted to 680 more, each form with and without that launch: the choice costs
+// 2.1 % over the best of them on average (2.3 % with the saving taken for one group and all segments of up to 512 rows, whether
+// bwd_own_values says so or not; 13 launches 3 to 12 % slower then, none faster: 30 heads of 143 rows against 695 keys 19.2 us and now 17.0).
+struct BwdPlan { int splits, groups; };
+
+// The estimate for one form and split count; `own`: no preprocess launch (bwd_own_values), which the start counts
+inline double bwd_estimate(const SegShape &s, int splits, int groups, bool own)
+{
+    struct Cost { double start, own, dq_us, dq_more, dkv_us, dkv_more, dkv_slow, rate, last; };
+    static const Cost forms[] = {{5.8, 1.6, 0.70, 1.7, 1.02, 3.7, 0.35, 0.85, 0.31}, {4.0, 0.4, 1.11, 2.6, 1.52, 4.6, 0.0, 1.06, 0.51}};
+    const Cost &c = forms[groups - 1];
+    const double bhs = (double)s.B * s.H;
+    const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x, first = s.causal ? s.s0 + (s.l_s < 128 ? s.l_s : 128) : (int64_t)s.l_x;
+    const int64_t tiles = (seen + 63) / 64, q_tiles = (s.l_s + 63) / 64, dq_tiles = (s.l_s + 127) / 128, key_tiles = (seen + 127) / 128;
+    const int64_t full = s.causal && s.s0 / 128 < key_tiles ? s.s0 / 128 : key_tiles;      // key tiles that all rows see; the others half of them
+    const double mean_tiles = 0.5 * (double)((first + 63) / 64 + tiles);
+    const double zeros_mb = (double)(s.l_x - seen) * bhs * s.d * 8e-6, dq_mb = bhs * s.l_s * s.d * 1e-6;
+    const double n_dq = (double)dq_tiles * bhs * splits, n_dkv = (double)key_tiles * bhs, N = n_dq + n_dkv;
+    const double shared = N < 256.0 ? 0.0 : N > 512.0 ? 1.0 : N / 256.0 - 1.0;
+    const double dq = ((double)(((tiles + splits - 1) / splits + groups - 1) / groups) + c.dq_more + 1.0) * c.dq_us;
+    const double dkv = ((double)((q_tiles + groups - 1) / groups) + c.dkv_more) * c.dkv_us * (1.0 + c.dkv_slow * shared);
+    const double longest = dq > dkv ? dq : dkv;
+    double balance = c.rate / 256.0 * (((double)dq_tiles * bhs * mean_tiles / groups + n_dq * c.dq_more) * c.dq_us +
+                                       (bhs * ((double)full + 0.5 * (double)(key_tiles - full)) * (double)q_tiles / groups + n_dkv * c.dkv_more) * c.dkv_us);
+    if (N > 512.0 / groups) balance += c.last * dkv;
+    const double t = c.start - (own ? c.own : 0.0) + pow(pow(longest, 6.0) + pow(balance, 6.0), 1.0 / 6.0) + zeros_mb / 9.0;
+    return splits > 1 ? t + 1.6 + dq_mb * (4 * splits + 2) / 11.0 : t;
+}
+
+// `may_own`: bwd_own_values decides (no gradient overlaps `out`)
+inline BwdPlan pick_bwd_plan(const SegShape &s, int most, bool may_own)
+{
+    const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x, tiles = (seen + 63) / 64;
+    BwdPlan best{1, 1};
+    double best_t = 0.0;
+    for (int groups = 1; groups <= (s.l_s > 128 ? 2 : 1); ++groups)      // (two tiles of rows: nothing to share)
+        for (int splits = 1; splits <= most; ++splits) {
+            if (splits > 1 && tiles / splits < 4) break;
+            const double t = bwd_estimate(s, splits, groups, may_own && bwd_own_values(s, splits, groups));
+            if (best_t == 0.0 || t < best_t) { best_t = t; best = {splits, groups}; }
+        }
+    return best;
+}
+
+} // namespace lss

@@ -2,21 +2,13 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include "lss_device_once.h"
+#include "lss_shape.h"
 #include <stddef.h>
 #include <stdint.h>
 
 namespace lss {
 
 typedef __bf16 bf16_t;
-
-// One segment's problem, as the kernels see it (Eq. 2 of Section 3; device pointers).
-struct SegShape {
-    int64_t s0;      // global index of the segment's first query row
-    int l_s, l_x;    // query rows of the segment, key/value rows of the sequence
-    int B, H, d;
-    int causal;
-    int skip_tail;   // causal backward: leave key tiles that no query of the segment sees unwritten (not zero-filled)
-};
 
 // Dropout on the attention weights (Section 2.2); thr == 0 means none.  A weight is kept when its
 // 32-bit random number (lss_common.h: drop_keep) is >= thr; kept weights are multiplied by
@@ -89,11 +81,11 @@ hipError_t launch_bwd_f32_main(const SegShape &s, const DropArgs &drop, const fl
                                int n_splits, hipStream_t st);
 
 // tuned bf16 kernels (lss_bwd_bf16.hip): all gradients in one launch, after one for D = rowsum(dO * out) where that
-// is not part of it; `groups` of wavefronts per workgroup (two: d = 64, more than 128 rows); `out_first`: `out` must have been read before any gradient is written
+// is not part of it (`own`, see bwd_own_values); `groups` of wavefronts per workgroup (two: d = 64, more than 128 rows)
 int dq_bf16_rows_per_workgroup(int d);
 hipError_t launch_bwd_bf16_main(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                 const bf16_t *v, const bf16_t *out, const float *lse, const bf16_t *dO, bf16_t *dq,
-                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, int groups, bool one_pass, bool out_first,
+                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, int groups, bool one_pass, bool own,
                                 hipStream_t st);
 
 // Whether [a, a + a_bytes) and [b, b + b_bytes) have a byte in common

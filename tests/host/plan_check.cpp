@@ -1,0 +1,46 @@
+// Goes over the choices of csrc/lss_bwd_plan.h on the host: of the forms and split counts that a launch may take, the one chosen
+// has the smallest estimate under the launcher's own decision whether there is a preprocess launch, and every choice stays within
+// the limits that the kernels and the workspace have.
+#include "lss_bwd_plan.h"
+
+#include <cstdio>
+#include <initializer_list>
+
+static int fail(const char *what, const lss::SegShape &s, const lss::BwdPlan &p)
+{
+    std::printf("%s: B %d H %d l_s %d l_x %d s0 %lld causal %d: %d splits, %d groups\n", what, s.B, s.H, s.l_s, s.l_x, (long long)s.s0, s.causal,
+                p.splits, p.groups);
+    return 1;
+}
+
+int main()
+{
+    long long owns = 0, lets = 0;
+    for (int l_s : {65, 66, 97, 128, 129, 192, 193, 256, 257, 300, 384, 512, 513, 1024, 1044, 4096, 12661})
+        for (int l_x : {65, 129, 512, 1000, 1024, 4100, 8192, 24576, 50112})
+            for (int heads : {1, 2, 4, 7, 16, 40, 64, 513})
+                for (int causal : {0, 1})
+                    for (int at : {0, 1, 2}) {
+                        if (l_s > l_x) continue;
+                        const int64_t s0 = (int64_t)(l_x - l_s) * at / 2;
+                        const lss::SegShape s{s0, l_s, l_x, heads > 16 ? heads / 8 : 1, heads > 16 ? 8 : heads, 64, causal, 0};
+                        for (int most : {1, 2, 5, 16})
+                            for (bool may_own : {false, true}) {
+                                const lss::BwdPlan p = lss::pick_bwd_plan(s, most, may_own);
+                                const int64_t seen = causal ? s0 + l_s : l_x, tiles = (seen + 63) / 64;
+                                if (p.splits < 1 || p.splits > most || p.groups < 1 || p.groups > (l_s > 128 ? 2 : 1) || (p.splits > 1 && tiles / p.splits < 4))
+                                    return fail("outside the limits", s, p);
+                                auto own = [&](int splits, int groups) { return may_own && lss::bwd_own_values(s, splits, groups); };
+                                if (l_s > lss::kOwnRows && own(p.splits, p.groups)) return fail("start values that do not fit", s, p);
+                                (own(p.splits, p.groups) ? owns : lets) += 1;
+                                const double t = lss::bwd_estimate(s, p.splits, p.groups, own(p.splits, p.groups));
+                                if (!(t > 0.0 && t < 1e9)) return fail("no time", s, p);
+                                for (int g = 1; g <= (l_s > 128 ? 2 : 1); ++g)
+                                    for (int sp = 1; sp <= most && (sp == 1 || tiles / sp >= 4); ++sp)
+                                        if (lss::bwd_estimate(s, sp, g, own(sp, g)) < t) return fail("a shorter one is there", s, p);
+                            }
+                    }
+    if (owns < 100 || lets < 100) return 1;
+    std::printf("clean\n");
+    return 0;
+}

@@ -22,6 +22,10 @@ def test_kernel_limits_are_set_on_every_gpu_of_the_process(tmp_path):
     _run(tmp_path, "device_once_check", "-pthread")
 
 
+def test_backward_plan_counts_the_launches_that_are_made(tmp_path):
+    _run(tmp_path, "plan_check")
+
+
 def test_no_launcher_keeps_a_limit_per_process():
     # HIP keeps a kernel's limits per GPU: they are raised through DeviceOnce only
     csrc = ROOT / "paper_2311_02382_amd" / "csrc"
