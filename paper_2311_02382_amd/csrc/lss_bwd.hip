@@ -132,7 +132,7 @@ static int pick_splits(const SegShape &s, int most, int elem_bytes)
         double balance = c.rate / 256.0 * (((double)dq_tiles * bhs * mean_tiles + n_dq * c.dq_more) * c.dq_us +
                                            (bhs * ((double)full + 0.5 * (double)(key_tiles - full)) * (double)q_tiles + n_dkv * c.dkv_more) * dkv_us);
         if (N > room) balance += c.last * dkv;
-        const double t = c.start + pow(pow(longest, 6.0) + pow(balance, 6.0), 1.0 / 6.0) + zeros_mb / c.zeros_rate;
+        const double t = c.start + larger_or_both(longest, balance) + zeros_mb / c.zeros_rate;
         return sp > 1 ? t + c.merge + dq_m * (2 * sp + 1) * c.merge_bytes / c.merge_rate : t;
     };
     const int base = is_float ? (int)std::min<int64_t>((tiles + 15) / 16, most) : pick_dq_splits(s, most);

@@ -10,6 +10,14 @@ namespace lss {
 constexpr int kSkinnyRows = 64;     // a segment of so many rows is one tile
 constexpr int kOwnRows = 512;       // rows whose start values fit the LDS of a workgroup that computes them itself
 
+// (a^6 + b^6)^(1/6): the larger of two times, and a little more where they are close.  Without pow, of which each of a
+// call's up to 32 estimates took three (with that, and what they share computed per estimate, 2.6 us of host time; now 1.6).
+inline double larger_or_both(double a, double b)
+{
+    const double hi = a > b ? a : b, r = (a > b ? b : a) / hi, r3 = r * r * r;
+    return hi * cbrt(sqrt(1.0 + r3 * r3));
+}
+
 // Whether the workgroups compute D and the start values themselves (never where a gradient overlaps `out`, see
 // launch_bwd_d): a launch less (2.3 us), for each dK/dV workgroup
 // 0.75 us per 128 rows of 64 elements or 1.5 us per 64 of 128 ahead of its loop.  That is spread over the rounds of
@@ -46,40 +54,50 @@ inline bool bwd_own_values(const SegShape &s, int n_splits, int groups)
 // bwd_own_values says so or not; 13 launches 3 to 12 % slower then, none faster: 30 heads of 143 rows against 695 keys 19.2 us and now 17.0).
 struct BwdPlan { int splits, groups; };
 
-// The estimate for one form and split count; `own`: no preprocess launch (bwd_own_values), which the start counts
-inline double bwd_estimate(const SegShape &s, int splits, int groups, bool own)
+// What all estimates of a launch share
+struct BwdWork {
+    int64_t tiles, q_tiles;                                       // 64-key tiles that some row sees, 64-row query tiles
+    double n_dq, n_dkv, dq_walks, dkv_walks, zeros_us, dq_mb;      // workgroups (dQ: per split) and the tiles they walk
+};
+inline BwdWork bwd_work(const SegShape &s)
 {
-    struct Cost { double start, own, dq_us, dq_more, dkv_us, dkv_more, dkv_slow, rate, last; };
-    static const Cost forms[] = {{5.8, 1.6, 0.70, 1.7, 1.02, 3.7, 0.35, 0.85, 0.31}, {4.0, 0.4, 1.11, 2.6, 1.52, 4.6, 0.0, 1.06, 0.51}};
-    const Cost &c = forms[groups - 1];
     const double bhs = (double)s.B * s.H;
     const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x, first = s.causal ? s.s0 + (s.l_s < 128 ? s.l_s : 128) : (int64_t)s.l_x;
     const int64_t tiles = (seen + 63) / 64, q_tiles = (s.l_s + 63) / 64, dq_tiles = (s.l_s + 127) / 128, key_tiles = (seen + 127) / 128;
     const int64_t full = s.causal && s.s0 / 128 < key_tiles ? s.s0 / 128 : key_tiles;      // key tiles that all rows see; the others half of them
     const double mean_tiles = 0.5 * (double)((first + 63) / 64 + tiles);
-    const double zeros_mb = (double)(s.l_x - seen) * bhs * s.d * 8e-6, dq_mb = bhs * s.l_s * s.d * 1e-6;
-    const double n_dq = (double)dq_tiles * bhs * splits, n_dkv = (double)key_tiles * bhs, N = n_dq + n_dkv;
+    return {tiles, q_tiles, (double)dq_tiles * bhs, (double)key_tiles * bhs, (double)dq_tiles * bhs * mean_tiles,
+            bhs * ((double)full + 0.5 * (double)(key_tiles - full)) * (double)q_tiles, (double)(s.l_x - seen) * bhs * s.d * 8e-6 / 9.0,
+            bhs * s.l_s * s.d * 1e-6};
+}
+
+// The estimate for one form and split count; `own`: no preprocess launch (bwd_own_values), which the start counts
+inline double bwd_estimate(const BwdWork &w, int splits, int groups, bool own)
+{
+    struct Cost { double start, own, dq_us, dq_more, dkv_us, dkv_more, dkv_slow, rate, last; };
+    static const Cost forms[] = {{5.8, 1.6, 0.70, 1.7, 1.02, 3.7, 0.35, 0.85, 0.31}, {4.0, 0.4, 1.11, 2.6, 1.52, 4.6, 0.0, 1.06, 0.51}};
+    const Cost &c = forms[groups - 1];
+    const double n_dq = w.n_dq * splits, N = n_dq + w.n_dkv, per_group = groups == 1 ? 1.0 : 0.5;
     const double shared = N < 256.0 ? 0.0 : N > 512.0 ? 1.0 : N / 256.0 - 1.0;
-    const double dq = ((double)(((tiles + splits - 1) / splits + groups - 1) / groups) + c.dq_more + 1.0) * c.dq_us;
-    const double dkv = ((double)((q_tiles + groups - 1) / groups) + c.dkv_more) * c.dkv_us * (1.0 + c.dkv_slow * shared);
-    const double longest = dq > dkv ? dq : dkv;
-    double balance = c.rate / 256.0 * (((double)dq_tiles * bhs * mean_tiles / groups + n_dq * c.dq_more) * c.dq_us +
-                                       (bhs * ((double)full + 0.5 * (double)(key_tiles - full)) * (double)q_tiles / groups + n_dkv * c.dkv_more) * c.dkv_us);
-    if (N > 512.0 / groups) balance += c.last * dkv;
-    const double t = c.start - (own ? c.own : 0.0) + pow(pow(longest, 6.0) + pow(balance, 6.0), 1.0 / 6.0) + zeros_mb / 9.0;
-    return splits > 1 ? t + 1.6 + dq_mb * (4 * splits + 2) / 11.0 : t;
+    const double dq = ((double)((((int)w.tiles + splits - 1) / splits + groups - 1) / groups) + c.dq_more + 1.0) * c.dq_us;
+    const double dkv = ((double)((w.q_tiles + groups - 1) / groups) + c.dkv_more) * c.dkv_us * (1.0 + c.dkv_slow * shared);
+    double balance = c.rate / 256.0 * ((w.dq_walks * per_group + n_dq * c.dq_more) * c.dq_us +
+                                       (w.dkv_walks * per_group + w.n_dkv * c.dkv_more) * c.dkv_us);
+    if (N > 512.0 * per_group) balance += c.last * dkv;
+    const double t = c.start - (own ? c.own : 0.0) + larger_or_both(dq > dkv ? dq : dkv, balance) + w.zeros_us;
+    return splits > 1 ? t + 1.6 + w.dq_mb * (4 * splits + 2) / 11.0 : t;
 }
 
 // `may_own`: bwd_own_values decides (no gradient overlaps `out`)
 inline BwdPlan pick_bwd_plan(const SegShape &s, int most, bool may_own)
 {
-    const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x, tiles = (seen + 63) / 64;
+    const BwdWork w = bwd_work(s);
     BwdPlan best{1, 1};
     double best_t = 0.0;
     for (int groups = 1; groups <= (s.l_s > 128 ? 2 : 1); ++groups)      // (two tiles of rows: nothing to share)
         for (int splits = 1; splits <= most; ++splits) {
-            if (splits > 1 && tiles / splits < 4) break;
-            const double t = bwd_estimate(s, splits, groups, may_own && bwd_own_values(s, splits, groups));
+            if (splits > 1 && w.tiles < 4 * splits) break;
+            const double t = bwd_estimate(w, splits, groups, may_own && bwd_own_values(s, splits, groups));
             if (best_t == 0.0 || t < best_t) { best_t = t; best = {splits, groups}; }
         }
     return best;

@@ -15,6 +15,11 @@ static int fail(const char *what, const lss::SegShape &s, const lss::BwdPlan &p)
 
 int main()
 {
+    for (double a : {1e-3, 0.5, 1.0, 7.25, 900.0, 1e5})
+        for (double b : {1e-3, 0.5, 0.999, 1.0, 31.0, 1e5}) {
+            const double want = pow(pow(a, 6.0) + pow(b, 6.0), 1.0 / 6.0);
+            if (!(fabs(lss::larger_or_both(a, b) - want) <= 1e-13 * want)) return 1;
+        }
     long long owns = 0, lets = 0;
     for (int l_s : {65, 66, 97, 128, 129, 192, 193, 256, 257, 300, 384, 512, 513, 1024, 1044, 4096, 12661})
         for (int l_x : {65, 129, 512, 1000, 1024, 4100, 8192, 24576, 50112})
@@ -24,6 +29,7 @@ int main()
                         if (l_s > l_x) continue;
                         const int64_t s0 = (int64_t)(l_x - l_s) * at / 2;
                         const lss::SegShape s{s0, l_s, l_x, heads > 16 ? heads / 8 : 1, heads > 16 ? 8 : heads, 64, causal, 0};
+                        const lss::BwdWork w = lss::bwd_work(s);
                         for (int most : {1, 2, 5, 16})
                             for (bool may_own : {false, true}) {
                                 const lss::BwdPlan p = lss::pick_bwd_plan(s, most, may_own);
@@ -33,11 +39,11 @@ int main()
                                 auto own = [&](int splits, int groups) { return may_own && lss::bwd_own_values(s, splits, groups); };
                                 if (l_s > lss::kOwnRows && own(p.splits, p.groups)) return fail("start values that do not fit", s, p);
                                 (own(p.splits, p.groups) ? owns : lets) += 1;
-                                const double t = lss::bwd_estimate(s, p.splits, p.groups, own(p.splits, p.groups));
+                                const double t = lss::bwd_estimate(w, p.splits, p.groups, own(p.splits, p.groups));
                                 if (!(t > 0.0 && t < 1e9)) return fail("no time", s, p);
                                 for (int g = 1; g <= (l_s > 128 ? 2 : 1); ++g)
                                     for (int sp = 1; sp <= most && (sp == 1 || tiles / sp >= 4); ++sp)
-                                        if (lss::bwd_estimate(s, sp, g, own(sp, g)) < t) return fail("a shorter one is there", s, p);
+                                        if (lss::bwd_estimate(w, sp, g, own(sp, g)) < t) return fail("a shorter one is there", s, p);
                             }
                     }
     if (owns < 100 || lets < 100) return 1;
