@@ -44,14 +44,14 @@ inline bool bwd_own_values(const SegShape &s, int n_splits, int groups)
 //     start + (longest^6 + balance^6)^(1/6) + zeros / 9 MB + merge
 // longest: the longer of a dQ workgroup's walk over its 64-key tiles and a dK/dV workgroup's over the 64-row query tiles, each a few
 // tiles more, the latter slower as two workgroups come to share a compute unit; balance: all walks over 256 compute units, and a part of a last
-// dK/dV walk where the launch takes more than one round; zeros: the rows no query sees; merge: 1.6 us and the partial dQ's
+// dK/dV walk where the launch takes more than one round; zeros: the rows no query sees; merge: 1.8 us and the partial dQ's
 // bytes at 11 MB per us where there is more than one split.  Fitted to 100 launches (65 .. 4096 rows, 512 .. 50,112 keys, 2 .. 64 heads, both forms
 // with 1 .. 16 splits, after a forward call each): launches take 4.9 % less time
 // than with one group and splits that only keep a dQ workgroup from outlasting the launch (8 heads of 1044 rows against 26,100 keys: 214 us, four splits
-// 192; 4 heads of 3510 rows behind 1226: 83 us, in two groups 55; 2 heads of 1362 rows: 32 and 27).  The starts, what is saved where no
-// preprocess launch is made and the merge's 1.6 us are fitted to 680 more, each form with and without that launch: the choice costs
-// 2.1 % over the best of them on average (2.3 % with the saving taken for one group and all segments of up to 512 rows, whether
-// bwd_own_values says so or not; 13 launches 3 to 12 % slower then, none faster: 30 heads of 143 rows against 695 keys 19.2 us and now 17.0).
+// 192; 4 heads of 3510 rows behind 1226: 83 us, in two groups 55; 2 heads of 1362 rows: 32 and 27).  The starts and what is saved where no
+// preprocess launch is made are fitted to 680 more, each form with and without that launch: the choice costs
+// 2.2 % over the best of them on average (2.3 % with the saving taken for one group and all segments of up to 512 rows, whether
+// bwd_own_values says so or not; eleven launches 3 to 8 % slower then, two faster: 15 heads of 365 rows against 1873 keys 25.5 us and now 23.8).
 struct BwdPlan { int splits, groups; };
 
 // What all estimates of a launch share
@@ -85,7 +85,7 @@ inline double bwd_estimate(const BwdWork &w, int splits, int groups, bool own)
                                        (w.dkv_walks * per_group + w.n_dkv * c.dkv_more) * c.dkv_us);
     if (N > 512.0 * per_group) balance += c.last * dkv;
     const double t = c.start - (own ? c.own : 0.0) + larger_or_both(dq > dkv ? dq : dkv, balance) + w.zeros_us;
-    return splits > 1 ? t + 1.6 + w.dq_mb * (4 * splits + 2) / 11.0 : t;
+    return splits > 1 ? t + 1.8 + w.dq_mb * (4 * splits + 2) / 11.0 : t;
 }
 
 // `may_own`: bwd_own_values decides (no gradient overlaps `out`)
