@@ -42,7 +42,7 @@ int max_fwd_splits(int l_s, int l_x, int B, int H, int rows_per_wg)
     return most < 1 ? 1 : (int)most;
 }
 
-// float: a launch takes about what the bf16 forms below do, without a tail's share of `few`:
+// float: a launch takes about what the bf16 forms of lss_fwd_plan.h do, without a tail's share of `few`:
 //     start + tile_us (1 + shared (n - 1)) max(longest + few, (average + few) W / (256 n)) + tail (average + few) tile_us + merge
 // Fitted to 130 launches (37 .. 9,100 rows, 512 .. 20,000 keys, 2 .. 32 heads, 1 .. 16 splits, a backward call before each): the choice
 // costs 1 % over the best of them on average, and takes 12 % less time than with the estimate that there was (from loops of forward
@@ -66,52 +66,6 @@ int pick_float_fwd_splits(const SegShape &s, int max_splits)
         if (W > 256.0 * c.per_cu) t += c.tail * (average + c.few) * c.tile_us;
         if (sp > 1) t += c.merge + out_m * (8 * sp + 4) / c.mb_per_us;
         if (best_t == 0.0 || t < best_t) { best_t = t; best = sp; }
-    }
-    return best;
-}
-
-// A launch takes about, in us,
-//     start + tile_us (1 + shared (n - 1)) max(longest + few, (average + few) W / (256 n)) + tail (average + few) tile_us + merge
-// with W workgroups, n of them (rounded up, at most per_cu) on a compute unit at a time, `longest` and `average` the 64-key
-// tiles that a workgroup's group of wavefronts walks, the tail where W > 256 per_cu and the merge launch where the keys are
-// split: 2.8 us (2.4 at d = 128) and the partial results' bytes at 4.5 MB per us.  Fitted to 145 launches at d = 64 and 75 at
-// 128 (58 .. 4096 rows, 512 .. 50,112 keys, 2 .. 64 heads, each in every form with 1 .. 16 splits, a backward pass before each
-// call: alone, a loop of forward calls runs at a higher clock and flatters forms that load more): the choice costs 1.5 % (3.6 %) over the
-// best of them on average, and takes 10.5 % (3.9 %) less time than the best choice of splits of 128-row (256-row) workgroups with one group.
-FwdPlan pick_fwd_plan(const SegShape &s, int max_splits)
-{
-    // (not below K's and V's bytes at 4.4 TB/s, the fourth powers added: 32 heads of 58 rows against 25,058 keys read 205 MB,
-    // 47 us from HBM, and gain nothing from more than 8 splits)
-    struct Cost { FwdForm form; int rows, groups, per_cu; double start, few, tile_us, shared, tail; };
-    static const Cost d64[] = {{FWD_4x1, 128, 1, 3, 8.2, -3.3, 0.733, 0.51, 0.81}, {FWD_2x2, 64, 2, 2, 4.7, 1.2, 0.799, 0.51, 0.55},
-                               {FWD_4x2, 128, 2, 1, 4.8, 1.7, 1.068, 0.0, 0.64}};
-    static const Cost d128[] = {{FWD_8x1, 256, 1, 1, 10.2, -1.7, 1.364, 0.0, 1.05}, {FWD_4x2, 128, 2, 1, 4.9, 1.6, 1.925, 0.0, 0.65}};
-    const bool wide = s.d == 128;
-    const double out_mb = (double)s.B * s.H * s.l_s * s.d * 1e-6;     // elements
-    const double merge0 = wide ? 2.4 : 2.8, mb_per_us = 4.5;
-    const int64_t most = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x, tiles = (most + 63) / 64;
-    const double kv_us = (double)s.B * s.H * most * s.d * 4.0 / 4.4e6;
-    FwdPlan best{wide ? FWD_8x1 : FWD_4x1, 1};
-    double best_t = 0.0;
-    for (const Cost *c = wide ? d128 : d64, *end = c + (wide ? 2 : 3); c != end; ++c) {
-        const int64_t q_tiles = (s.l_s + c->rows - 1) / c->rows, first = s.causal ? s.s0 + (s.l_s < c->rows ? s.l_s : c->rows) : (int64_t)s.l_x;
-        const double mean_tiles = 0.5 * (double)((first + 63) / 64 + tiles);
-        for (int sp = 1; sp <= max_splits; ++sp) {
-            if (sp > 1 && tiles / (sp * c->groups) < 2) break;      // shorter ones cost more than they gain
-            const double W = (double)(q_tiles * s.B * s.H * sp);
-            // At most 16 workgroups for eight tiles and more: split in any case, as these launches always were and as the
-            // tests of the merge's rounding expect of them.  It costs them 0 to 1.5 us (4 heads of 256 rows behind 256: 9.7
-            // instead of 8.3) and 0.1 % over all those launches.
-            if (sp == 1 && max_splits > 1 && W <= 16.0 && tiles >= 8) continue;
-            const double longest = (double)(((tiles + sp - 1) / sp + c->groups - 1) / c->groups);
-            const double average = mean_tiles / (sp * c->groups) + (sp * c->groups > 1 ? 0.5 : 0.0);
-            const double n = std::min((double)c->per_cu, ceil(W / 256.0));
-            double t = c->start + c->tile_us * (1.0 + c->shared * (n - 1.0)) * std::max(longest + c->few, (average + c->few) * W / (256.0 * n));
-            if (W > 256.0 * c->per_cu) t += c->tail * (average + c->few) * c->tile_us;
-            t = sqrt(hypot(t * t, kv_us * kv_us));
-            if (sp > 1) t += merge0 + out_mb * (8 * sp + 2) / mb_per_us;
-            if (best_t == 0.0 || t < best_t) { best_t = t; best = {c->form, sp}; }
-        }
     }
     return best;
 }

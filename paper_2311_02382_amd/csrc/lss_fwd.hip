@@ -59,7 +59,7 @@ static hipError_t launch_fwd_d(const SegShape &s, const DropArgs &drop, const T 
     hipError_t e;
     int n_splits;
     if constexpr (sizeof(T) == 2) {
-        const FwdPlan plan = pick_fwd_plan(s, ws.fwd_splits);
+        const FwdPlan plan = pick_fwd_plan(s, drop.thr != 0, ws.fwd_splits);
         n_splits = plan.splits;
         e = launch_fwd_bf16_main(s, drop, q, k, v, out, lse, ws, plan, st);
     } else {

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include "lss_device_once.h"
+#include "lss_fwd_plan.h"
 #include "lss_shape.h"
 #include <stddef.h>
 #include <stdint.h>
@@ -27,11 +28,6 @@ int choose_splits(int l_s, int l_x, int B, int H, int rows_per_wg);
 // uses for the keys its query tiles actually see (never above the former).
 int max_fwd_splits(int l_s, int l_x, int B, int H, int rows_per_wg);
 int pick_float_fwd_splits(const SegShape &s, int max_splits);
-// bf16 forward: the workgroup's form -- blocks of 32 query rows x groups of wavefronts that have a part of the keys
-// each -- and the key splits.
-enum FwdForm { FWD_4x1, FWD_2x2, FWD_4x2, FWD_8x1 };
-struct FwdPlan { FwdForm form; int splits; };
-FwdPlan pick_fwd_plan(const SegShape &s, int max_splits);
 int fwd_rows_per_wg(int elem_bytes, int d);     // query rows per workgroup of the forward kernel
 int dq_rows_per_wg(int elem_bytes, int d);      // ... and of the dQ kernel
 

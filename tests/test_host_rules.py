@@ -26,6 +26,10 @@ def test_backward_plan_counts_the_launches_that_are_made(tmp_path):
     _run(tmp_path, "plan_check")
 
 
+def test_forward_plan_takes_a_short_one_of_the_measured_forms(tmp_path):
+    _run(tmp_path, "fwd_plan_check")
+
+
 def test_no_launcher_keeps_a_limit_per_process():
     # HIP keeps a kernel's limits per GPU: they are raised through DeviceOnce only
     csrc = ROOT / "paper_2311_02382_amd" / "csrc"
