@@ -88,7 +88,7 @@ __device__ __forceinline__ bool some_below(const f32x4 (&x)[N], float limit)
         for (int e = 0; e < 4; ++e) least_nonzero = min(least_nonzero, twice_magnitude(x[i][e]) - 1u);
     return least_nonzero < twice_magnitude(limit) - 1u;
 }
-// (NJ: blocks of 16 queries or keys that a wavefront holds, see bwd_main_f32_kernel)
+// (NJ: blocks of 16 queries or keys that a wavefront holds: two in the forward, kBlocks in the backward)
 // This lane's fragments of its NJ rows: D / 32 times 8 floats of each, 32 apart.  Returns whether some lane's rows hold tiny values.
 template <int D, int NJ>
 __device__ __forceinline__ bool split_rows(const float *p, const int64_t (&off)[NJ], Frag3 (&f)[D / 32][NJ])
@@ -257,6 +257,12 @@ constexpr int kRowsPerWg = 128;             // query rows of a workgroup: four w
 // two wavefronts that take one of the two 32-row halves of every Q/dO tile and add their results up at the end --
 // twice as many workgroups, with chains half as long, for launches that do not fill the chip.
 template <int HALVES> constexpr int kKeysPerWg = 128 / HALVES;
+
+// Blocks of 16 keys or query rows that a wavefront of a backward workgroup holds.  At d = 128 one, eight wavefronts per workgroup:
+// with two a wavefront needs 440 registers and is alone on its SIMD, vector work and matrix instructions take turns.  54 launches,
+// forward and backward, 3.4 % faster on average, 14 % at best, never 1 % slower (1024 rows behind 7168, 8 heads, dropout: backward
+// 618 -> 594 us).
+template <int D> constexpr int kBlocks = D == 64 ? 2 : 1;
 
 // lse * log2 e less its rounded value l2 (1.93e-8: what kLog2e was rounded off by); 0 for infinities and NaNs
 __device__ __forceinline__ float rounded_off(float lse, float l2)
@@ -520,13 +526,14 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_f32_kernel(SegShape 
 
 // ------------------------------------------------------------------------------------------ dQ
 // S^T = K Q^T, dP^T = V dO^T, dS = P (dP - D) (dropout: P (M dP - D)), dQ^T += K^T dS^T.
-template <int D, bool DROP, int NJ>
+template <int D, bool DROP>
 __device__ __forceinline__ void bwd_dq_f32_body(char *smem, const SegShape &s, const DropArgs &dr, const float *__restrict__ q,
                                                 const float *__restrict__ k, const float *__restrict__ v,
                                                 const float *__restrict__ dO, const float *__restrict__ lse,
                                                 const float *__restrict__ Dv, float *__restrict__ dq, float *__restrict__ dq_part,
                                                 int n_splits, int q_tile, int n_q_tiles, int bh, int split)
 {
+    constexpr int NJ = kBlocks<D>;
     using Tile = PlaneTile<D, 512 / NJ>;
     constexpr int NS = D / 32, BC = Tile::ROWS;
     char *const sk = smem, *const sv = smem + Tile::BYTES;
@@ -564,12 +571,6 @@ __device__ __forceinline__ void bwd_dq_f32_body(char *smem, const SegShape &s, c
         scale[j] = (1.f - rounded_off(lv, l2) * kLn2) / sqrtf((float)D);
     }
     if (tid == 0) *tiny_word = 0u;
-    if constexpr (D == 128 && NJ == 2) {       // (operands live in the accumulation half of the register file: see the bf16 dK/dV workgroups)
-#pragma unroll
-        for (int n = 0; n < 2 * NS; ++n)
-#pragma unroll
-            for (int p = 0; p < 3; ++p) { asm volatile("" : "+a"(qf[n >> 1][n & 1].p[p].v)); asm volatile("" : "+a"(gf[n >> 1][n & 1].p[p].v)); }
-    }
     const float c = kLog2e / sqrtf((float)D);
     uint32_t drop_rk[NJ], drop_cs = 0u;
     if (DROP) {
@@ -687,13 +688,14 @@ __device__ __forceinline__ void bwd_dq_f32_body(char *smem, const SegShape &s, c
 
 // ------------------------------------------------------------------------------------------ dK, dV
 // Key-owned: S = Q K^T, dP = dO V^T over the query tiles that see the keys, then dV^T += dO^T P, dK^T += Q^T dS.
-template <int D, bool DROP, int HALVES, int NJ>
+template <int D, bool DROP, int HALVES>
 __device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, const DropArgs &dr, const float *__restrict__ q,
                                                  const float *__restrict__ k, const float *__restrict__ v,
                                                  const float *__restrict__ dO, const float *__restrict__ lse,
                                                  const float *__restrict__ Dv, float *__restrict__ dk_part,
                                                  float *__restrict__ dv_part, int bh, int key_tile)
 {
+    constexpr int NJ = kBlocks<D>;
     using Tile = PlaneTile<D, 512 / NJ>;
     constexpr int NS = D / 32, BQ = Tile::ROWS;
     char *const sq = smem, *const sg = smem + Tile::BYTES;
@@ -735,12 +737,6 @@ __device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, 
         tiny = split_rows<D, NJ>(v, off, vf) || tiny;
     }
     if (tid == 0) *tiny_word = 0u;
-    if constexpr (D == 128 && NJ == 2) {
-#pragma unroll
-        for (int n = 0; n < 2 * NS; ++n)
-#pragma unroll
-            for (int p = 0; p < 3; ++p) { asm volatile("" : "+a"(kf[n >> 1][n & 1].p[p].v)); asm volatile("" : "+a"(vf[n >> 1][n & 1].p[p].v)); }
-    }
     Sums<D, NJ> dk, dv;
     dk.clear();
     dv.clear();
@@ -896,11 +892,8 @@ __device__ __forceinline__ void bwd_dkv_f32_body(char *smem, const SegShape &s, 
 }
 
 // Both kinds of workgroup in one launch, dQ first, in XCD order: see bwd_main_bf16_kernel.
-// NJ: blocks of 16 keys or query rows per wavefront.  At d = 128 one, eight wavefronts per workgroup: with two a wavefront needs 440
-// registers and is alone on its SIMD, vector work and matrix instructions take turns.  54 launches, forward and backward, 3.4 % faster
-// on average, 14 % at best, never 1 % slower (1024 rows behind 7168, 8 heads, dropout: backward 618 -> 594 us).
-template <int D, bool DROP, int HALVES, int NJ>
-__global__ __launch_bounds__(512 / NJ, D == 64 || NJ == 1 ? 2 : 1) void bwd_main_f32_kernel(
+template <int D, bool DROP, int HALVES>
+__global__ __launch_bounds__(512 / kBlocks<D>, 2) void bwd_main_f32_kernel(
     SegShape s, DropArgs dr, const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
     const float *__restrict__ dO, const float *__restrict__ lse, const float *__restrict__ Dv, float *__restrict__ dq,
     float *__restrict__ dq_part, float *__restrict__ dk_part, float *__restrict__ dv_part, int n_splits, int n_dq, int n_q_tiles,
@@ -911,10 +904,10 @@ __global__ __launch_bounds__(512 / NJ, D == 64 || NJ == 1 ? 2 : 1) void bwd_main
     int bh, inner;
     if (id >= n_dq) {
         if (!xcd_item(id - n_dq, bhs, n_key_tiles, s.causal, bh, inner)) return;
-        bwd_dkv_f32_body<D, DROP, HALVES, NJ>(smem, s, dr, q, k, v, dO, lse, Dv, dk_part, dv_part, bh, inner);
+        bwd_dkv_f32_body<D, DROP, HALVES>(smem, s, dr, q, k, v, dO, lse, Dv, dk_part, dv_part, bh, inner);
     } else {
         if (!xcd_item(id, bhs, n_q_tiles * n_splits, s.causal && s.s0 < s.l_s, bh, inner)) return;
-        bwd_dq_f32_body<D, DROP, NJ>(smem, s, dr, q, k, v, dO, lse, Dv, dq, dq_part, n_splits, inner % n_q_tiles, n_q_tiles, bh,
+        bwd_dq_f32_body<D, DROP>(smem, s, dr, q, k, v, dO, lse, Dv, dq, dq_part, n_splits, inner % n_q_tiles, n_q_tiles, bh,
                                  inner / n_q_tiles);
     }
 }
@@ -937,11 +930,11 @@ hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const float *q, c
     const bool halves = f32_bwd_halves(s, n_splits);
     const int keys = halves ? 64 : 128, n_q_tiles = (s.l_s + kRowsPerWg - 1) / kRowsPerWg, n_key_tiles = (s.l_x + keys - 1) / keys;
     const int n_dq = xcd_grid(s.B * s.H, n_q_tiles * n_splits), n_dkv = xcd_grid(s.B * s.H, n_key_tiles);
-    constexpr int H2 = D == 64 ? 2 : 1, NJ = D == 64 ? 2 : 1;
-    const auto kernel = dr.thr != 0 ? (halves ? bwd_main_f32_kernel<D, true, H2, NJ> : bwd_main_f32_kernel<D, true, 1, NJ>)
-                                    : (halves ? bwd_main_f32_kernel<D, false, H2, NJ> : bwd_main_f32_kernel<D, false, 1, NJ>);
+    constexpr int H2 = D == 64 ? 2 : 1;
+    const auto kernel = dr.thr != 0 ? (halves ? bwd_main_f32_kernel<D, true, H2> : bwd_main_f32_kernel<D, true, 1>)
+                                    : (halves ? bwd_main_f32_kernel<D, false, H2> : bwd_main_f32_kernel<D, false, 1>);
     TimedLaunch tl(K_BWD_MAIN_F32, st);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_dq + n_dkv)), dim3(512 / NJ), 0, st, s, dr, q, k, v, dO, lse, ws.D, dq, ws.dq_part, dk_part,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_dq + n_dkv)), dim3(512 / kBlocks<D>), 0, st, s, dr, q, k, v, dO, lse, ws.D, dq, ws.dq_part, dk_part,
                        dv_part, n_splits, n_dq, n_q_tiles, n_key_tiles);
     return hipGetLastError();
 }
