@@ -419,8 +419,12 @@ static hipError_t launch_fwd_main(const SegShape &s, const DropArgs &drop, const
     using C = FwdBf16Cfg<D, RB, KG>;
     const int n_q_tiles = (s.l_s + C::BR - 1) / C::BR;
     dim3 grid((unsigned)xcd_grid(s.B * s.H, n_q_tiles * n_splits));
+    auto kernel = fwd_bf16_kernel<D, false, RB, KG>;
+    if (drop.thr != 0) {
+        if constexpr (D == 64 && RB == 4 && KG == 2) return hipErrorInvalidConfiguration;      // (pick_fwd_plan: never with dropout)
+        else kernel = fwd_bf16_kernel<D, true, RB, KG>;
+    }
     TimedLaunch tl(K_FWD_BF16, st);
-    const auto kernel = drop.thr != 0 ? fwd_bf16_kernel<D, true, RB, KG> : fwd_bf16_kernel<D, false, RB, KG>;
     hipLaunchKernelGGL(kernel, grid, dim3(C::NT), 0, st, s, drop, q, k, v, out, lse, ws.o_part, ws.lse_part, n_splits, n_q_tiles);
     return hipGetLastError();
 }

@@ -21,7 +21,8 @@ struct FwdPlan { FwdForm form; int splits; };
 //   * The rest is `tail` of a workgroup's time; where a compute unit holds one workgroup and all are about as long (`even`), the
 //     launch takes whole rounds of them.
 //   * With dropout (tables of their own) a tile takes 1.5 to 2 times as long: the generator's work is in vector slots of which the
-//     forward has none to spare.
+//     forward has none to spare.  FWD_4x2 at d = 64 is not built with dropout: by its figures there (5.42, 0.87, 2.18 per
+//     tile) it is never the shortest, over 15 million sizes.
 // Fitted to 454 launches at d = 64 and 436 at 128 (58 .. 4096 rows, 512 .. 50,112 keys, 2 .. 64 heads, 45 % with dropout, each in every form with 1 .. 16
 // splits, a backward pass before each call: alone, a loop of forward calls runs at a higher clock and flatters forms that load more): the
 // choice costs 1.4 % over the best of them on average with dropout at d = 64, 1.1 % at d = 128 (4.7 % and 3.7 % by the figures for d = 64
@@ -37,7 +38,7 @@ inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
     static const Table tables[2][2] = {
         {{3, {{FWD_4x1, 128, 1, 3, 8.2, -3.3, 0.733, 0.51, 0.81, 1.0}, {FWD_2x2, 64, 2, 2, 4.7, 1.2, 0.799, 0.51, 0.55, 1.0}, {FWD_4x2, 128, 2, 1, 4.8, 1.7, 1.068, 0.0, 0.64, 1.0}},
           2.8, 4.5, false},
-         {3, {{FWD_4x1, 128, 1, 3, 8.07, -1.43, 1.32, 0.467, 0.412, 0.623}, {FWD_2x2, 64, 2, 2, 2.11, 2.53, 1.38, 0.417, 0.447, 0.0}, {FWD_4x2, 128, 2, 1, 5.42, 0.87, 2.18, 0.0, 0.45, 0.95}},
+         {2, {{FWD_4x1, 128, 1, 3, 8.07, -1.43, 1.32, 0.467, 0.412, 0.623}, {FWD_2x2, 64, 2, 2, 2.11, 2.53, 1.38, 0.417, 0.447, 0.0}},
           2.03, 3.41, true}},
         {{2, {{FWD_8x1, 256, 1, 1, 3.38, 3.02, 1.50, 0.0, 0.645, 0.468}, {FWD_4x2, 128, 2, 1, 3.92, 2.36, 1.787, 0.0, 0.63, 1.0}}, 2.5, 5.2, true},
          {2, {{FWD_8x1, 256, 1, 1, 3.38, 3.02, 2.385, 0.0, 0.645, 0.468}, {FWD_4x2, 128, 2, 1, 3.92, 2.36, 2.704, 0.0, 0.63, 1.0}}, 2.5, 5.2, true}}};

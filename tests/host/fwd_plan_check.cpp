@@ -62,7 +62,7 @@ int main()
                                     const FwdPlan p = pick_fwd_plan(s, drop, most);
                                     const int64_t seen = causal ? s.s0 + l_s : l_x;
                                     if (p.splits < 1 || p.splits > most || (p.splits > 1 && (seen + 63) / 64 / p.splits < 2)) return fail("outside the limits", s, drop, p);
-                                    if (d == 64 ? p.form == FWD_8x1 : p.form != FWD_8x1 && p.form != FWD_4x2) return fail("no such form", s, drop, p);
+                                    if (d == 64 ? p.form == FWD_8x1 || (drop && p.form == FWD_4x2) : p.form != FWD_8x1 && p.form != FWD_4x2) return fail("no such form", s, drop, p);
                                 }
     std::printf("clean\n");
     return 0;
