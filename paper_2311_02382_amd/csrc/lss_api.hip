@@ -3,6 +3,7 @@
 #include "lss_attn.h"
 #include "lss_common.h"
 #include "lss_kernels.h"
+#include "lss_plan.h"
 
 #include <cmath>
 #include <cstdarg>
@@ -780,6 +781,45 @@ int lss_reduce_partials(const float *const *parts, int n, const int64_t *rows_va
     }
     const hipError_t e = lss::launch_reduce(parts, n, rows_valid, l_x, B, H, d, out, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(LSS_ERR_LAUNCH, "reduce launch failed: %s", hipGetErrorString(e));
+    return LSS_OK;
+}
+
+// ---- lss_plan.h
+static int plan_shape(int64_t s0, int64_t l_s, int64_t l_x, int64_t B, int64_t H, int64_t d, int causal, int elem_bytes, const int *plan, lss::SegShape *s)
+{
+    if (int rc = check_shape(s0, l_s, l_x, B, H, d)) return rc;
+    if (l_s == 0 || B == 0 || (elem_bytes != 2 && elem_bytes != 4)) return fail(LSS_ERR_SHAPE, "plan: no launch of such a call");
+    if (!plan) return fail(LSS_ERR_NULL, "plan: NULL");
+    *s = {s0, (int)l_s, (int)l_x, (int)B, (int)H, (int)d, causal ? 1 : 0, 0};
+    return LSS_OK;
+}
+
+int lss_plan_fwd(int64_t s0, int64_t l_s, int64_t l_x, int64_t B, int64_t H, int64_t d, int causal, int with_dropout, int elem_bytes, int *plan)
+{
+    lss::SegShape s;
+    if (int rc = plan_shape(s0, l_s, l_x, B, H, d, causal, elem_bytes, plan, &s)) return rc;
+    const int most = lss::max_fwd_splits(s.l_s, s.l_x, s.B, s.H, lss::fwd_rows_per_wg(elem_bytes, s.d));
+    if (elem_bytes == 4) {
+        plan[0] = lss::f32_rows_per_workgroup() / 32;
+        plan[1] = 1;
+        plan[2] = lss::pick_float_fwd_splits(s, most);
+        return LSS_OK;
+    }
+    const lss::FwdPlan p = lss::pick_fwd_plan(s, with_dropout != 0, most);
+    plan[0] = p.form == lss::FWD_8x1 ? 8 : p.form == lss::FWD_2x2 ? 2 : 4;
+    plan[1] = p.form == lss::FWD_2x2 || p.form == lss::FWD_4x2 ? 2 : 1;
+    plan[2] = p.splits;
+    return LSS_OK;
+}
+
+int lss_plan_bwd(int64_t s0, int64_t l_s, int64_t l_x, int64_t B, int64_t H, int64_t d, int causal, int with_dropout, int elem_bytes, int over_out,
+                 int *plan)
+{
+    lss::SegShape s;
+    if (int rc = plan_shape(s0, l_s, l_x, B, H, d, causal, elem_bytes, plan, &s)) return rc;
+    const lss::BwdLaunch p = lss::plan_bwd(s, with_dropout != 0, elem_bytes, !over_out);
+    const int all[6] = {p.splits, p.groups, p.one_pass, p.own, p.skinny, p.narrow};
+    std::copy(all, all + 6, plan);
     return LSS_OK;
 }
 

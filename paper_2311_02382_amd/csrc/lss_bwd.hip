@@ -147,31 +147,36 @@ static int pick_splits(const SegShape &s, int most, int elem_bytes)
     return best;
 }
 
+BwdLaunch plan_bwd(const SegShape &s, bool with_drop, int elem_bytes, bool may_own)
+{
+    const int most = choose_splits(s.l_s, s.l_x, s.B, s.H, dq_rows_per_wg(elem_bytes, s.d));
+    if (elem_bytes == 4) return {pick_splits(s, most, elem_bytes), 1, false, false, false, false};
+    const BwdPlan plan = s.l_s <= kSkinnyRows ? BwdPlan{pick_dq_splits(s, most), 1}
+                         : s.d == 128         ? BwdPlan{pick_splits(s, most, elem_bytes), 1}
+                                              : pick_bwd_plan(s, most, may_own);
+    const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x;
+    const int dq_tiles = (int)(((seen + 63) / 64 + plan.splits - 1) / plan.splits + plan.groups - 1) / plan.groups;
+    const int one_pass = may_own ? skinny_splits(s, with_drop, elem_bytes, most, dq_tiles) : 0;
+    if (one_pass > 0) return {one_pass, 1, true, true, false, false};
+    const bool own = may_own && bwd_own_values(s, plan.splits, plan.groups), skinny = own && !with_drop && s.l_s <= kSkinnyRows;
+    return {plan.splits, plan.groups, false, own, skinny, !skinny && bwd_narrow(s)};
+}
+
 template <typename T, int D>
 static hipError_t launch_bwd_d(const SegShape &s, const DropArgs &dr, const T *q, const T *k, const T *v, const T *out,
                                const float *lse, const T *dO, T *dq, float *dk_part, float *dv_part,
                                const Workspace &ws, hipStream_t st)
 {
     hipError_t e;
-    const int most = choose_splits(s.l_s, s.l_x, s.B, s.H, dq_rows_per_wg((int)sizeof(T), D));
     // Gradients may be written over `out`, which nothing reads afterwards.  Workgroups that compute D themselves read all
     // rows of `out` while others write gradients: then a launch of its own reads it first.
     const size_t rows_bytes = (size_t)s.B * s.l_s * s.H * D * sizeof(T), part_bytes = (size_t)s.B * s.l_x * s.H * D * sizeof(float);
     const bool out_first = overlaps(dq, rows_bytes, out, rows_bytes) || overlaps(dk_part, part_bytes, out, rows_bytes) ||
                            overlaps(dv_part, part_bytes, out, rows_bytes);
-    const BwdPlan plan = sizeof(T) == 4 || (D == 128 && s.l_s > kSkinnyRows) ? BwdPlan{pick_splits(s, most, (int)sizeof(T)), 1}
-                         : s.l_s > kSkinnyRows                      ? pick_bwd_plan(s, most, !out_first)
-                                                                    : BwdPlan{pick_dq_splits(s, most), 1};
-    const int dq_splits = plan.splits;
-    const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x;
-    const int dq_tiles = (int)(((seen + 63) / 64 + dq_splits - 1) / dq_splits + plan.groups - 1) / plan.groups;
-    const int one_pass = out_first ? 0 : skinny_splits(s, dr.thr != 0, (int)sizeof(T), most, dq_tiles);
-    const int n_splits = one_pass > 0 ? one_pass : dq_splits;
+    const BwdLaunch plan = plan_bwd(s, dr.thr != 0, (int)sizeof(T), !out_first);
+    const int n_splits = plan.splits;
     if constexpr (sizeof(T) == 2) {
-        const bool own = !out_first && bwd_own_values(s, n_splits, plan.groups);
-        if ((e = launch_bwd_bf16_main(s, dr, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, plan.groups, one_pass > 0, own, st)) !=
-            hipSuccess)
-            return e;
+        if ((e = launch_bwd_bf16_main(s, dr, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, plan, st)) != hipSuccess) return e;
     } else {
         {
             const int64_t threads = (int64_t)s.B * s.l_s * s.H * 16;

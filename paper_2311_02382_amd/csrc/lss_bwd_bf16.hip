@@ -1495,17 +1495,6 @@ __global__ __launch_bounds__(64 * (8 / NJ) * KG, D == 64 || NJ == 1 ? 2 : 1) voi
     }
 }
 
-// Whether a launch at d = 128 takes eight wavefronts of 16 rows per workgroup (NJ = 1): where no compute unit gets more than 32 walks of 64 query
-// rows past 128 keys.  Longer ones are held by the chip's power, of which twice the LDS reads take more: with NJ = 1 a 32k segment's
-// compute units are busy 12 % fewer cycles, but at a lower clock, 2.40 ms instead of 2.36.  50 launches, forward and backward:
-// those of 24 walks and less 0 to 12 % faster, 4.3 % on average (8 heads of 770 rows behind 1654: 82 -> 72 us, 4 of 813: 52 -> 49); above, 2 %
-// slower on average.
-static bool bwd_narrow(const SegShape &s)
-{
-    const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x;
-    return s.d == 128 && (seen + 127) / 128 * s.B * s.H * ((s.l_s + 63) / 64) <= 32 * 256;
-}
-
 template <int QB>
 static hipError_t launch_skinny(const SegShape &s, const bf16_t *q, const bf16_t *k, const bf16_t *v, const bf16_t *out, const float *lse,
                                 const bf16_t *dO, bf16_t *dq, float *dk_part, float *dv_part, const Workspace &ws, int n_splits,
@@ -1524,14 +1513,13 @@ static hipError_t launch_skinny(const SegShape &s, const bf16_t *q, const bf16_t
 template <int D>
 static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                     const bf16_t *v, const bf16_t *out, const float *lse, const bf16_t *dO, bf16_t *dq,
-                                    float *dk_part, float *dv_part, const Workspace &ws, int n_splits, int groups,
-                                    bool one_pass, bool own, hipStream_t st)
+                                    float *dk_part, float *dv_part, const Workspace &ws, const BwdLaunch &plan, hipStream_t st)
 {
     hipError_t e;
-    const bool with_drop = drop.thr != 0;
-    const bool skinny = own && !with_drop && s.l_s <= kSkinnyRows;
+    const bool with_drop = drop.thr != 0, own = plan.own, skinny = plan.skinny;
+    const int n_splits = plan.splits, groups = plan.groups;
     if constexpr (D == 64) {
-        if (one_pass)
+        if (plan.one_pass)
             return s.l_s <= 64 ? launch_skinny<2>(s, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, st)
                  : s.l_s <= 96 ? launch_skinny<3>(s, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, st)
                                : launch_skinny<4>(s, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, st);
@@ -1558,7 +1546,7 @@ static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, con
     }
     unsigned threads = 256 * groups;
     if constexpr (D == 128) {
-        if (!skinny && bwd_narrow(s)) {
+        if (plan.narrow) {
             kernel = with_drop ? (own ? bwd_main_bf16_kernel<D, true, true, false, 1, 1> : bwd_main_bf16_kernel<D, true, false, false, 1, 1>)
                                : (own ? bwd_main_bf16_kernel<D, false, true, false, 1, 1> : bwd_main_bf16_kernel<D, false, false, false, 1, 1>);
             threads = 512;
@@ -1575,11 +1563,10 @@ static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, con
 // launch; the caller runs the dQ split merge
 hipError_t launch_bwd_bf16_main(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                 const bf16_t *v, const bf16_t *out, const float *lse, const bf16_t *dO, bf16_t *dq,
-                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, int groups, bool one_pass, bool own,
-                                hipStream_t st)
+                                float *dk_part, float *dv_part, const Workspace &ws, const BwdLaunch &plan, hipStream_t st)
 {
-    if (s.d == 64) return launch_bwd_bf16_d<64>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, groups, one_pass, own, st);
-    return launch_bwd_bf16_d<128>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, n_splits, groups, one_pass, own, st);
+    if (s.d == 64) return launch_bwd_bf16_d<64>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, plan, st);
+    return launch_bwd_bf16_d<128>(s, drop, q, k, v, out, lse, dO, dq, dk_part, dv_part, ws, plan, st);
 }
 
 } // namespace lss

@@ -1,4 +1,4 @@
-// How a bf16 backward launch is laid out, from sizes alone.  Plain C++ without a HIP header, so that a host program can go over
+// How a backward launch is laid out, from sizes alone: the bf16 rules.  Plain C++ without a HIP header, so that a host program can go over
 // the choices (tests/host/plan_check.cpp).
 #pragma once
 #include "lss_shape.h"
@@ -102,5 +102,20 @@ inline BwdPlan pick_bwd_plan(const SegShape &s, int most, bool may_own)
         }
     return best;
 }
+
+// Whether a launch at d = 128 takes eight wavefronts of 16 rows per workgroup (NJ = 1): where no compute unit gets more than 32 walks of 64 query
+// rows past 128 keys.  Longer ones are held by the chip's power, of which twice the LDS reads take more: with NJ = 1 a 32k segment's
+// compute units are busy 12 % fewer cycles, but at a lower clock, 2.40 ms instead of 2.36.  50 launches, forward and backward:
+// those of 24 walks and less 0 to 12 % faster, 4.3 % on average (8 heads of 770 rows behind 1654: 82 -> 72 us, 4 of 813: 52 -> 49); above, 2 %
+// slower on average.
+inline bool bwd_narrow(const SegShape &s)
+{
+    const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x;
+    return s.d == 128 && (seen + 127) / 128 * s.B * s.H * ((s.l_s + 63) / 64) <= 32 * 256;
+}
+
+// A whole backward launch.  one_pass: the kernel that makes all three gradients of a short segment (bf16, d = 64); own: no
+// preprocess launch; skinny: dK/dV workgroups for at most 64 rows; narrow: wavefronts of 16 rows (all three: bf16, else false)
+struct BwdLaunch { int splits, groups; bool one_pass, own, skinny, narrow; };
 
 } // namespace lss

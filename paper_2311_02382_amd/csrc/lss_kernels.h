@@ -1,6 +1,7 @@
 // Host-side launchers of the segment-attention kernels; called by the C ABI only.
 #pragma once
 #include <hip/hip_runtime.h>
+#include "lss_bwd_plan.h"
 #include "lss_device_once.h"
 #include "lss_fwd_plan.h"
 #include "lss_shape.h"
@@ -34,6 +35,9 @@ int dq_rows_per_wg(int elem_bytes, int d);      // ... and of the dQ kernel
 // Key splits of the backward kernel that makes all three gradients in one pass, 0 where another one is taken; at most `most`.
 // `dq_tiles`: key tiles of 64 that a dQ workgroup of that other one walks.
 int skinny_splits(const SegShape &s, bool with_drop, int elem_bytes, int most, int dq_tiles);
+
+// The backward launch of a call; `may_own`: no gradient overlaps `out`
+BwdLaunch plan_bwd(const SegShape &s, bool with_drop, int elem_bytes, bool may_own);
 
 struct Workspace {
     // forward
@@ -77,12 +81,11 @@ hipError_t launch_bwd_f32_main(const SegShape &s, const DropArgs &drop, const fl
                                int n_splits, hipStream_t st);
 
 // tuned bf16 kernels (lss_bwd_bf16.hip): all gradients in one launch, after one for D = rowsum(dO * out) where that
-// is not part of it (`own`, see bwd_own_values); `groups` of wavefronts per workgroup (two: d = 64, more than 128 rows)
+// is not part of it
 int dq_bf16_rows_per_workgroup(int d);
 hipError_t launch_bwd_bf16_main(const SegShape &s, const DropArgs &drop, const bf16_t *q, const bf16_t *k,
                                 const bf16_t *v, const bf16_t *out, const float *lse, const bf16_t *dO, bf16_t *dq,
-                                float *dk_part, float *dv_part, const Workspace &ws, int n_splits, int groups, bool one_pass, bool own,
-                                hipStream_t st);
+                                float *dk_part, float *dv_part, const Workspace &ws, const BwdLaunch &plan, hipStream_t st);
 
 // Whether [a, a + a_bytes) and [b, b + b_bytes) have a byte in common
 inline bool overlaps(const void *a, size_t a_bytes, const void *b, size_t b_bytes)

@@ -1,9 +1,12 @@
 """Helpers shared by the GPU parity tests: input staging and the error metrics."""
+import collections
+import ctypes
+
 import numpy as np
 import torch
 
 import oracle
-from paper_2311_02382_amd import synth
+from paper_2311_02382_amd import lss, synth
 
 # Tolerances: max |gpu - ref| / max |ref| per tensor (elementwise relative error is
 # undefined at zeros); lse: max |gpu - ref| / max(1, |ref|).
@@ -62,3 +65,24 @@ def to_np(t: torch.Tensor) -> np.ndarray:
 def stage_all(B, l_x, H, d, seed, kind, std=1.0):
     q, k, v, do = synth.make_inputs(B, l_x, H, d, seed, std)
     return tuple(Staged(a, kind) for a in (q, k, v, do))
+
+
+FwdPlan = collections.namedtuple("FwdPlan", "row_blocks groups splits")
+BwdPlan = collections.namedtuple("BwdPlan", "splits groups one_pass own skinny narrow")
+
+
+def _plan(name, cls, s0, l_s, l_x, B, H, d, causal, *flags):
+    plan, i64 = (ctypes.c_int * len(cls._fields))(), ctypes.c_int64
+    call = getattr(lss.load(), name)
+    lss._check(call(*map(i64, (s0, l_s, l_x, B, H, d)), *(ctypes.c_int(int(f)) for f in (causal, *flags)), plan))
+    return cls(*plan)
+
+
+def fwd_plan(B, l_x, H, d, s0, l_s, causal, drop=False, elem_bytes=2):
+    """What a forward call launches (csrc/lss_plan.h)."""
+    return _plan("lss_plan_fwd", FwdPlan, s0, l_s, l_x, B, H, d, causal, drop, elem_bytes)
+
+
+def bwd_plan(B, l_x, H, d, s0, l_s, causal, drop=False, elem_bytes=2, over_out=False):
+    """What a backward call launches (csrc/lss_plan.h)."""
+    return _plan("lss_plan_bwd", BwdPlan, s0, l_s, l_x, B, H, d, causal, drop, elem_bytes, over_out)

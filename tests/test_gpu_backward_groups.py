@@ -1,11 +1,12 @@
-"""Backward workgroups of two groups of wavefronts that walk half the key or query tiles each: sizes at which the second
-group has no tile, one, a partial one or one less than the first, start values computed in the workgroup or before, keys split or not."""
+"""Backward workgroups of one and of two groups of wavefronts, the latter with half the key or query tiles each: sizes at which the
+second group has no tile, one, a partial one or one less than the first, start values computed in the workgroup or before, keys
+split or not."""
 import pytest
 import torch
 
 import oracle
 from paper_2311_02382_amd import lss
-from _util import TOL, rel_err, stage_all, to_np
+from _util import TOL, bwd_plan, rel_err, stage_all, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -16,9 +17,18 @@ SHAPES = [  # B, l_x, H, s0, l_s, causal
 ]
 
 
-@pytest.mark.parametrize("p_drop", [0.0, 0.25])
-@pytest.mark.parametrize("B,l_x,H,s0,l_s,causal", SHAPES)
-def test_backward_against_the_oracle(B, l_x, H, s0, l_s, causal, p_drop):
+# Two groups (with dropout and without): start values in the workgroup or before, keys split or not
+TWO_GROUPS = [  # B, l_x, H, s0, l_s, causal, (own, split)
+    (1, 892, 1, 609, 283, True, (1, False)), (3, 2569, 4, 609, 390, True, (1, False)),
+    (1, 897, 2, 640, 257, True, (1, False)), (1, 1025, 1, 576, 449, True, (1, False)),      # last key tile: one query tile, of the first group
+    (1, 1756, 1, 1384, 372, True, (1, True)), (1, 1665, 2, 1344, 321, True, (1, True)),     # ... here too
+    (1, 17417, 1, 7155, 241, False, (1, True)),                                              # 16 ranges
+    (1, 325, 1, 0, 325, True, (0, False)), (1, 513, 2, 0, 513, True, (0, False)),           # first query tile: two key tiles
+    (1, 1232, 1, 894, 338, True, (0, True)), (1, 1153, 2, 832, 321, True, (0, True)),
+]
+
+
+def check(B, l_x, H, s0, l_s, causal, p_drop):
     Q, K, V, DO = stage_all(B, l_x, H, 64, 9400 + l_x + l_s, "bf16")
     sl = slice(s0, s0 + l_s)
     q, do = Q.dev[:, sl].contiguous(), DO.dev[:, sl].contiguous()
@@ -36,3 +46,17 @@ def test_backward_against_the_oracle(B, l_x, H, s0, l_s, causal, p_drop):
     dq, dk, dv = lss.lss_segment_attn_bwd(q, K.dev, V.dev, s0, over, lse, do, causal, dq=over, **drop)
     for name, got, want in zip(("dq", "dk", "dv"), (dq, dk, dv), ref):
         assert rel_err(to_np(got), want) <= TOL["bf16"]["t"], name
+
+
+@pytest.mark.parametrize("p_drop", [0.0, 0.25])
+@pytest.mark.parametrize("B,l_x,H,s0,l_s,causal", SHAPES)
+def test_backward_against_the_oracle(B, l_x, H, s0, l_s, causal, p_drop):
+    check(B, l_x, H, s0, l_s, causal, p_drop)
+
+
+@pytest.mark.parametrize("p_drop", [0.0, 0.25])
+@pytest.mark.parametrize("B,l_x,H,s0,l_s,causal,form", TWO_GROUPS)
+def test_two_groups_against_the_oracle(B, l_x, H, s0, l_s, causal, form, p_drop):
+    plan = bwd_plan(B, l_x, H, 64, s0, l_s, causal, p_drop > 0)
+    assert plan.groups == 2 and not plan.one_pass and (plan.own, plan.splits > 1) == form
+    check(B, l_x, H, s0, l_s, causal, p_drop)

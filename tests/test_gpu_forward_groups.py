@@ -4,29 +4,53 @@ import pytest
 
 import oracle
 from paper_2311_02382_amd import lss
-from _util import TOL, lse_err, rel_err, stage_all, to_np
+from _util import TOL, fwd_plan, lse_err, rel_err, stage_all, to_np
 
 pytestmark = pytest.mark.gpu
 
 SHAPES = [  # B, l_x, H, d, s0, l_s, causal
     (1, 1, 1, 64, 0, 1, True), (2, 64, 3, 64, 0, 64, True), (1, 65, 2, 64, 0, 65, False), (2, 190, 2, 64, 100, 33, True),
     (3, 257, 2, 64, 192, 65, True), (1, 320, 5, 64, 0, 320, True), (2, 448, 2, 64, 3, 97, False), (4, 700, 4, 64, 611, 70, True),
-    (2, 900, 9, 64, 200, 700, True),                                                     # 64-row and 128-row tiles, both in groups
+    (2, 900, 9, 64, 200, 700, True),
     (1, 1, 1, 128, 0, 1, False), (2, 65, 2, 128, 1, 33, True), (1, 129, 3, 128, 0, 129, True), (4, 330, 4, 128, 200, 130, False),
     (2, 1100, 8, 128, 100, 1000, True),
 ]
 
 
+# The workgroup's form by row blocks of 32 x groups, and whether the keys are split besides: every one that is built, with
+# rows past the end in the last query tile.  (At d = 64 and with dropout there is no 4 x 2.)
+FORMS = [  # B, l_x, H, d, s0, l_s, causal, p_drop, (row blocks, groups, split)
+    (1, 131, 2, 64, 34, 72, True, 0.0, (2, 2, False)), (1, 508, 1, 64, 442, 66, True, 0.0, (2, 2, True)),
+    (1, 258, 64, 64, 0, 258, False, 0.0, (4, 1, False)), (1, 3114, 16, 64, 2403, 711, True, 0.0, (4, 1, True)),
+    (1, 515, 32, 64, 0, 515, True, 0.0, (4, 2, False)), (1, 2153, 8, 64, 1502, 651, True, 0.0, (4, 2, True)),
+    (1, 130, 1, 64, 0, 66, True, 0.25, (2, 2, False)), (1, 477, 1, 64, 399, 78, True, 0.25, (2, 2, True)),
+    (1, 257, 64, 64, 0, 257, True, 0.25, (4, 1, False)), (1, 1533, 1, 64, 234, 375, True, 0.25, (4, 1, True)),
+    (1, 200, 1, 128, 62, 138, True, 0.0, (4, 2, False)), (1, 476, 1, 128, 320, 135, True, 0.0, (4, 2, True)),
+    (1, 644, 48, 128, 0, 644, False, 0.0, (8, 1, False)), (1, 943, 1, 128, 255, 297, True, 0.0, (8, 1, True)),
+    (1, 161, 1, 128, 0, 161, False, 0.25, (4, 2, False)), (1, 489, 1, 128, 359, 130, True, 0.25, (4, 2, True)),
+    (1, 642, 48, 128, 0, 642, True, 0.25, (8, 1, False)), (1, 736, 1, 128, 103, 262, True, 0.25, (8, 1, True)),
+]
+
+
+def check(B, l_x, H, d, s0, l_s, causal, p_drop, seed):
+    Q, K, V, _ = stage_all(B, l_x, H, d, seed, "bf16")
+    sl, heads = slice(s0, s0 + l_s), slice(0, 2 if B == 1 else H)      # (one batch's heads do not depend on each other: two are enough)
+    drop = {"p_drop": p_drop, "seed": 77} if p_drop else {}
+    out, lse = lss.lss_segment_attn_fwd(Q.dev[:, sl].contiguous(), K.dev, V.dev, s0, causal, **drop)
+    args = (Q.f64[:, sl, heads], K.f64[:, :, heads], V.f64[:, :, heads], s0, causal)
+    ref, ref_lse = oracle.segment_fwd_dropout(*args, p_drop, 77) if p_drop else oracle.segment_fwd(*args)
+    assert rel_err(to_np(out)[:, :, heads], ref) <= TOL["bf16"]["t"]
+    assert lse_err(to_np(lse)[:, heads], ref_lse) <= TOL["bf16"]["lse"]
+
+
 @pytest.mark.parametrize("p_drop", [0.0, 0.25])
 @pytest.mark.parametrize("B,l_x,H,d,s0,l_s,causal", SHAPES)
 def test_forward_against_the_oracle(B, l_x, H, d, s0, l_s, causal, p_drop):
-    Q, K, V, _ = stage_all(B, l_x, H, d, 9300 + l_x + d, "bf16")
-    sl = slice(s0, s0 + l_s)
-    drop = {"p_drop": p_drop, "seed": 77} if p_drop else {}
-    out, lse = lss.lss_segment_attn_fwd(Q.dev[:, sl].contiguous(), K.dev, V.dev, s0, causal, **drop)
-    if p_drop:
-        ref, ref_lse = oracle.segment_fwd_dropout(Q.f64[:, sl], K.f64, V.f64, s0, causal, p_drop, 77)
-    else:
-        ref, ref_lse = oracle.segment_fwd(Q.f64[:, sl], K.f64, V.f64, s0, causal)
-    assert rel_err(to_np(out), ref) <= TOL["bf16"]["t"]
-    assert lse_err(to_np(lse), ref_lse) <= TOL["bf16"]["lse"]
+    check(B, l_x, H, d, s0, l_s, causal, p_drop, 9300 + l_x + d)
+
+
+@pytest.mark.parametrize("B,l_x,H,d,s0,l_s,causal,p_drop,form", FORMS)
+def test_every_form_against_the_oracle(B, l_x, H, d, s0, l_s, causal, p_drop, form):
+    plan = fwd_plan(B, l_x, H, d, s0, l_s, causal, p_drop > 0)
+    assert (plan.row_blocks, plan.groups, plan.splits > 1) == form
+    check(B, l_x, H, d, s0, l_s, causal, p_drop, 9350 + l_x + d)
