@@ -1536,10 +1536,13 @@ static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, con
     int n_key_tiles = (s.l_x + DkvBf16Cfg<D>::BKV - 1) / DkvBf16Cfg<D>::BKV;
     if (skinny) n_key_tiles = (n_key_tiles + kSkinnyTilesPerWg - 1) / kSkinnyTilesPerWg;      // groups of key tiles
     const int n_dq = xcd_grid(s.B * s.H, n_q_tiles * n_splits), n_dkv = xcd_grid(s.B * s.H, n_key_tiles);
+    // (own start values for 65 to 512 rows: at d = 128 in narrow launches only -- the others have over 32 walks of 64 rows per compute unit,
+    // where bwd_own_values, at 1.5 us per 64 rows and round of workgroups, says no)
     auto kernel = skinny      ? bwd_main_bf16_kernel<D, false, true, true>
                   : with_drop ? (own ? bwd_main_bf16_kernel<D, true, true> : bwd_main_bf16_kernel<D, true, false>)
-                              : (own ? bwd_main_bf16_kernel<D, false, true> : bwd_main_bf16_kernel<D, false, false>);
+                              : bwd_main_bf16_kernel<D, false, false>;
     if constexpr (D == 64) {
+        if (own && !with_drop && !skinny) kernel = bwd_main_bf16_kernel<D, false, true>;
         if (groups == 2)
             kernel = with_drop ? (own ? bwd_main_bf16_kernel<D, true, true, false, 2> : bwd_main_bf16_kernel<D, true, false, false, 2>)
                                : (own ? bwd_main_bf16_kernel<D, false, true, false, 2> : bwd_main_bf16_kernel<D, false, false, false, 2>);
