@@ -3,11 +3,10 @@
 // (bwd_skinny_bf16_kernel).  In the former:
 //   * 32 x 32 blocks, in 16 x 16 x 32 instructions, three stages per block (score-side products, vector
 //     work, output-side products), software-pipelined so that the vector work of one block sits between
-//     the matrix instructions of its neighbours.  Large launches are bound by the chip's power: per product
-//     the 16 x 16 x 32 form takes less of it than 32 x 32 x 16 (register loops on Gaussian bf16: 2,020 - 2,070
-//     against 1,800 - 1,840 TFLOP/s; with the backward's vector work between them 1,669 - 1,708 against 1,597).
-//     With it in dK/dV 8,192 x 8,192 causal passes fell from 1,014 to 994 us, 32,768 keys at d = 128 from 2,535 to 2,505;
-//     in dQ then to 984 and 2,464;
+//     the matrix instructions of its neighbours.  16 x 16 x 32 and not 32 x 32 x 16 for what it measures on the kernels: with it in
+//     dK/dV 8,192 x 8,192 causal passes fell from 1,014 to 994 us, 32,768 keys at d = 128 from 2,535 to 2,505; in dQ then to 984 and
+//     2,464.  Loops on Gaussian bf16 (lss_microbench, section 7) do not show why: 1,700 against 1,630 TFLOP/s in registers, but 1,390
+//     either way with the backward's vector work in between, and 1,163 against 1,226 with an LDS read per 32,768 flop besides, as here;
 //   * 64-row tiles loaded global -> LDS directly into a ring of three unpadded, swizzled tiles, a
 //     full loop iteration ahead, one barrier per tile;
 //   * row-major LDS tiles read transposed with DS_READ_B64_TR_B16 where the contraction runs over

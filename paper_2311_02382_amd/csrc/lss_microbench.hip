@@ -231,6 +231,86 @@ static void run_data(float *d, const char *name)
            flops / (us * 1e-6) / (256.0 * 4 * 1024.0) / 1e9);
 }
 
+// ---- section 7: the two matrix instructions on Gaussian operands, in registers or read from LDS
+// A group is what one A fragment feeds: USE instructions' worth of 32768 flop each (one 32 x 32 x 16 or two 16 x 16 x 32), with NV fma
+// and NT exp2 beside each.  LDS: the fragment comes from LDS, read one group ahead.
+template <int SHAPE> struct MatrixAcc;
+template <> struct MatrixAcc<32> { f32x16 v[4]; };
+template <> struct MatrixAcc<16> { f32x4 v[8]; };
+template <int SHAPE, int NV, int NT, int USE, bool LDS>
+__global__ __launch_bounds__(256) void shape_kernel(float *out, int iters)
+{
+    __shared__ __attribute__((aligned(1024))) bf16x8 tile[8][256];
+    auto gauss = [&](uint32_t i) {
+        const float u = ((float)(mix_u32(i * 2u + threadIdx.x * 977u + blockIdx.x * 131071u) >> 8) + 0.5f) * (1.0f / 16777216.f);
+        const float w = ((float)(mix_u32(i * 2u + 1u + threadIdx.x * 977u + blockIdx.x * 131071u) >> 8) + 0.5f) * (1.0f / 16777216.f);
+        return (__bf16)(sqrtf(-2.f * logf(u)) * cosf(6.2831853f * w));
+    };
+    bf16x8 a[8], b[8];
+    for (int j = 0; j < 8; ++j)
+        for (int i = 0; i < 8; ++i) {
+            a[j][i] = gauss((j * 8 + i) * 4096u);
+            b[j][i] = gauss((64 + j * 8 + i) * 4096u);
+        }
+    if (LDS) {
+        for (int j = 0; j < 8; ++j) tile[j][threadIdx.x] = a[j];
+        __syncthreads();
+    }
+    MatrixAcc<SHAPE> c;
+    for (auto &v : c.v) v = {};
+    float x[16], y[16];
+    for (int i = 0; i < 16; ++i) { x[i] = threadIdx.x * 1e-3f + i; y[i] = threadIdx.x * 1e-4f + i * 0.01f; }
+    const float fa = 1.0001f, fb = 1e-4f;
+    bf16x8 f[2];
+    if (LDS) f[0] = tile[0][threadIdx.x];
+    for (int it = 0; it < iters; ++it) {
+        int vi = 0, ti = 0;
+        uint32_t at = threadIdx.x;
+        asm volatile("" : "+v"(at));        // (the reads stay in the loop)
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {
+            if (LDS) f[(g + 1) & 1] = tile[(g + 1) & 7][at];
+            const bf16x8 &fr = LDS ? f[g & 1] : a[g];
+#pragma unroll
+            for (int u = 0; u < USE; ++u) {
+                if constexpr (SHAPE == 32) c.v[(g * USE + u) & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr, b[(g + 3 * u) & 7], c.v[(g * USE + u) & 3], 0, 0, 0);
+                else {
+                    c.v[(2 * (g * USE + u)) & 7] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr, b[(g + 3 * u) & 7], c.v[(2 * (g * USE + u)) & 7], 0, 0, 0);
+                    c.v[(2 * (g * USE + u) + 1) & 7] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr, b[(g + 3 * u + 1) & 7], c.v[(2 * (g * USE + u) + 1) & 7], 0, 0, 0);
+                }
+#pragma unroll
+                for (int j = 0; j < NV; ++j) { x[vi & 15] = __builtin_fmaf(x[vi & 15], fa, fb); ++vi; }
+#pragma unroll
+                for (int j = 0; j < NT; ++j) { y[ti & 15] = __builtin_amdgcn_exp2f(y[ti & 15] * 0.5f - 1.0f); ++ti; }
+            }
+        }
+    }
+    float s = 0.f;
+    for (auto &v : c.v) for (int i = 0; i < SHAPE * SHAPE / 64; ++i) s += v[i];
+    for (int i = 0; i < 16; ++i) s += x[i] + y[i];
+    out[blockIdx.x * blockDim.x + threadIdx.x] = s;
+}
+
+template <int SHAPE, int NV, int NT, int USE, bool LDS>
+static double shape_rate(float *d)
+{
+    const int iters = 40000 / USE;      // x 8 USE x 32768 flop of 2048 wavefronts: 10 to 20 ms
+    shape_kernel<SHAPE, NV, NT, USE, LDS><<<512, 256>>>(d, 1000);
+    CHECK(hipDeviceSynchronize());
+    const auto w0 = std::chrono::steady_clock::now();
+    shape_kernel<SHAPE, NV, NT, USE, LDS><<<512, 256>>>(d, iters);
+    CHECK(hipDeviceSynchronize());
+    const double us = std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - w0).count();
+    return 512.0 * 4 * iters * 8 * USE * 32768.0 / (us * 1e-6) / 1e12;
+}
+template <int NV, int NT, int USE, bool LDS>
+static void run_shapes(float *d, const char *name)
+{
+    double r[2][3];
+    for (int i = 0; i < 3; ++i) { r[0][i] = shape_rate<32, NV, NT, USE, LDS>(d); r[1][i] = shape_rate<16, NV, NT, USE, LDS>(d); }
+    printf("%-60s  32x32x16: %5.0f %5.0f %5.0f   16x16x32: %5.0f %5.0f %5.0f TFLOP/s\n", name, r[0][0], r[0][1], r[0][2], r[1][0], r[1][1], r[1][2]);
+}
+
 // ---- section 4: LDS fragment reads
 template <int MODE, int D>
 __device__ int chunk_off(int r, int c)
@@ -334,6 +414,15 @@ int main()
     run_data<1>(d, "random operands in [-2, 2), again");
     run_data<1, 3, 1>(d, "random, + 3 fma + 1 exp2, again");
     run_data<1, 6, 2>(d, "random, + 6 fma + 2 exp2, again");
+    printf("# 7. both matrix instructions on Gaussian operands, two wavefronts per SIMD, three launches in turn; fma, exp2 and LDS reads per 32768 flop\n");
+    run_shapes<0, 0, 1, false>(d, "registers");
+    run_shapes<3, 1, 1, false>(d, "registers, 3 fma + 1 exp2 (backward)");
+    run_shapes<6, 2, 1, false>(d, "registers, 6 fma + 2 exp2 (forward, d=64)");
+    run_shapes<0, 0, 1, true>(d, "LDS, 1 ds_read_b128");
+    run_shapes<0, 0, 2, true>(d, "LDS, 1/2 ds_read_b128");
+    run_shapes<3, 1, 1, true>(d, "LDS, 1 ds_read_b128, 3 fma + 1 exp2 (backward)");
+    run_shapes<3, 1, 2, true>(d, "LDS, 1/2 ds_read_b128, 3 fma + 1 exp2");
+    run_shapes<3, 1, 4, true>(d, "LDS, 1/4 ds_read_b128, 3 fma + 1 exp2");
     printf("# 4. LDS fragment reads, [rows][D] bf16 tiles, time per wave-instruction per compute unit\n");
     run_lds<0, 64, 0>(d, "ds_read_b128 by rows, D=64, r&7");
     run_lds<1, 64, 0>(d, "ds_read_b128 by rows, D=64, tile_swizzle");
