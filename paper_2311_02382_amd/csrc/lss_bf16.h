@@ -227,6 +227,7 @@ __device__ __forceinline__ void wait_vmem()
     asm volatile("s_waitcnt vmcnt(%0)" :: "i"(N) : "memory");       // (also keeps the compiler from moving stores past it)
 }
 __device__ __forceinline__ void wait_vmem_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0), others untouched
+__device__ __forceinline__ void wait_lds_reads() { __builtin_amdgcn_s_waitcnt(0xC07F); }  // lgkmcnt(0), others untouched
 
 // 4 floats -> 4 bf16 (round to nearest even), as one 8-byte value
 __device__ __forceinline__ bf16x4 pack4(float a, float b, float c, float d)
