@@ -315,8 +315,11 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(Pro
     const int cols_here = min(J.N - n0, S::TN);                         // a multiple of 64
 
     auto put16 = [&](void *to, f32x4 v) __attribute__((always_inline)) {
-        if (args.stream) __builtin_nontemporal_store(v, static_cast<f32x4 *>(to));
-        else *static_cast<f32x4 *>(to) = v;
+        if (args.stream) {
+            asm volatile("");       // (two stores that differ in this respect only are merged into one plain store, ahead of the branch or behind it)
+            __builtin_nontemporal_store(v, static_cast<f32x4 *>(to));
+            asm volatile("");
+        } else *static_cast<f32x4 *>(to) = v;
     };
     auto store_tiles = [&](const f32x4 (&acc)[S::MB][S::NB], bool from_acc) {
         OutT *c0 = static_cast<OutT *>(J.c0) + (int64_t)batch * J.c_batch_stride + (int64_t)m0 * args.ldc;
@@ -648,9 +651,10 @@ hipError_t launch_proj_shape(ProjArgs &args, int kernel_id, hipStream_t st)
 
 // Whether C is written with non-temporal stores: where A and C together are more than half the last-level cache
 // (256 MB), results kept there and in the L2s only push out the operand tiles that other workgroups are about
-// to read again.  98304 x 1024 -> 2048 columns and -> 1024 more (projections of 4 x 24576 rows): 442 -> 393 us; 65536 x 512 -> 2048:
-// 175 -> 143, with a pass over the results right after it 273 -> 264; gradient of 4 x 12000 rows of 512 columns 97 -> 80.  Below
-// that it gains nothing and a reader of the results pays (16384 x 1024 -> 2048 and GeLU after it: 98.5 -> 100.8).
+// to read again.  The product and a pass over its results right after it: 32768 x 512 -> 2048 with GeLU in the product 205 -> 175 us, GeLU
+// behind it 141 -> 132; 98304 x 1024 -> 2048 and -> 1024 more (projections of 4 x 24576 rows) 446 -> 434 alone; the gradient of 4 x 12000 rows of 512
+// columns 92 -> 87; 19 such pairs of 138 MB and more 4 % less time on average, the worst 1.6 % more.  Below that the product gains
+// as much, but who reads its results pays more (8192 x 1024 -> 4096 with GeLU and the next product 155 -> 159, 4096 rows 84 -> 94).
 bool streams_results(const ProjArgs &args, bool out_f32)
 {
     double bytes = 0.0;

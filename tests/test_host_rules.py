@@ -1,4 +1,5 @@
 """Rules that host and device code share, driven by small host programs under the undefined-behaviour sanitizer (CPU)."""
+import re
 import subprocess
 from pathlib import Path
 
@@ -28,6 +29,20 @@ def test_backward_plan_counts_the_launches_that_are_made(tmp_path):
 
 def test_forward_plan_takes_a_short_one_of_the_measured_forms(tmp_path):
     _run(tmp_path, "fwd_plan_check")
+
+
+def test_results_of_large_products_are_stored_past_the_caches(tmp_path):
+    # Two stores that differ in the non-temporal hint only are one plain store to the compiler's middle end: what counts is the
+    # generated code.  Every kernel of the projection GEMM has both kinds.
+    from paper_2311_02382_amd import build
+    out = tmp_path / "proj.s"
+    subprocess.run([build._hipcc(), *build.HIPCC_FLAGS, f"-I{build.INCLUDE}", f"-I{build.CSRC}", "-S", "--offload-device-only", str(build.CSRC / "lss_proj.hip"),
+                    "-o", str(out)], check=True, capture_output=True, timeout=300)
+    bodies = re.findall(r"^(_Z\w*proj_gemm_kernel\w+):(.*?)s_endpgm\n", out.read_text(), re.S | re.M)
+    assert len(bodies) == 25
+    for name, body in bodies:
+        past = len(re.findall(r"global_store_dwordx4.*\bnt\b", body))
+        assert past > 0 and past <= len(re.findall(r"global_store_dwordx4", body)) - past, name
 
 
 def test_no_launcher_keeps_a_limit_per_process():
