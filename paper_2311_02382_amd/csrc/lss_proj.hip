@@ -10,12 +10,12 @@
 // matrix instruction and the activations its B operand.  Each wavefront owns a WM x WN part.  The
 // contraction runs in tiles of 64 through a ring of STAGES LDS slots that are filled global -> LDS
 // directly, one barrier per tile.  The finished tile goes through LDS once more so that it is written to
-// memory as whole rows.  The tile is chosen per launch (launch_proj): 2048 x 512 -> 2048 took 17.0 us with
-// the 256 x 256 tile alone and takes 9.1, 2048 x 2048 -> 512 46.2 and now 9.4.
-// Matrix instructions of 16 x 16 x 32, not 32 x 32 x 16: on Gaussian operands it is the chip's power that bounds a
-// loop of them, and registers alone reach 2050 TFLOP/s with the former and 1820 with the latter; the operand bytes per
-// flop from LDS are the same.  16384 x 4096 -> 1024: 119 -> 109 us (1260 TFLOP/s), 16384 x 1024 -> 4096: 149 -> 140,
-// the contraction of 16384 x 2048 floats 568 -> 518; launches of a few microseconds are unchanged.
+// memory as whole rows.  The tile is chosen per launch (launch_proj): 2048 x 512 -> 2048 takes 20.4 us in
+// 256 x 256 tiles and 14.0 as chosen, 2048 x 2048 -> 512 46.6 and 13.7 (one after the other, an event after each).
+// Matrix instructions of 16 x 16 x 32, not 32 x 32 x 16: loops on Gaussian operands (lss_microbench, section 7) reach 1700 TFLOP/s
+// with the former and 1630 with the latter in registers, 1500 and 1445 with an LDS read per 65,536 flop.  16384 x 4096 -> 1024:
+// 128 -> 116 us (1185 TFLOP/s), 16384 x 1024 -> 4096: 146 -> 136, the contraction of 98304 x 2048 floats 581 -> 532; weight gradients of
+// 16384 rows 148 -> 138.  Launches of 10 to 25 us gain 1 % and weight gradients among them lose up to 4 %.
 //   W_TR   weights stored [k][n] (forward: W as given).  Their fragments come from the LDS tile
 //          by transposing reads; otherwise the weights are stored [n][k] (backward: W as given
 //          IS W'^T) and are read plainly.
@@ -669,10 +669,12 @@ bool streams_results(const ProjArgs &args, bool out_f32)
 //     fixed + contraction tiles x per_tile   microseconds;
 // where compute units hold one workgroup each (PER_CU = 1: where half of them have one) a contraction tile takes
 // per_tile[0], where they are full per_tile[1].  The figures are fitted to linear_fwd and linear_bwd_input at 230 .. 98304 rows and
-// 512 .. 8192 columns either way (20 launches in a graph each).  Large tiles move the fewest bytes per flop
+// 512 .. 8192 columns either way (20 launches in a graph each), with the loop of 32 x 32 x 16 instructions that there was.  With the present
+// one, 40 drawn feed-forward units and projections in every tile: the choice costs 0.6 to 1.3 % over the best tile on average, 2.7 % in
+// project_bwd (at worst 22 us instead of 17) and 1.7 % in the projections' weight gradients.  Large tiles move the fewest bytes per flop
 // but a launch of few of them leaves compute units idle (2048 x 2048 -> 512: 16 workgroups of 256 x 256, 46 us;
-// 256 of 64 x 64, 12 us), and where even 64 x 64 tiles leave one wavefront per SIMD the chain of contraction
-// tiles is what takes the time: four groups of wavefronts that share it take 9 us.
+// 256 of 64 x 64, 12 us with the former loop), and where even 64 x 64 tiles leave one wavefront per SIMD the chain of contraction
+// tiles is what takes the time: four groups of wavefronts that share it took 9 us in a graph of them, 12 among other work now.
 struct GemmCost { double fixed, per_tile[2]; };
 template <typename S> constexpr GemmCost gemm_cost();
 template <> constexpr GemmCost gemm_cost<ShapeL>() { return {6.5, {1.40, 1.70}}; }
