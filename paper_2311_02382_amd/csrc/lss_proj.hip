@@ -653,7 +653,7 @@ hipError_t launch_proj_shape(ProjArgs &args, int kernel_id, hipStream_t st)
 // (256 MB), results kept there and in the L2s only push out the operand tiles that other workgroups are about
 // to read again.  The product and a pass over its results right after it: 32768 x 512 -> 2048 with GeLU in the product 205 -> 175 us, GeLU
 // behind it 141 -> 132; 98304 x 1024 -> 2048 and -> 1024 more (projections of 4 x 24576 rows) 446 -> 434 alone; the gradient of 4 x 12000 rows of 512
-// columns 92 -> 87; 19 such pairs of 138 MB and more 4 % less time on average, the worst 1.6 % more.  Below that the product gains
+// columns 92 -> 87; 31 such pairs of 138 MB and more 3.6 % less time on average, the worst 1.6 % more.  Below that the product gains
 // as much, but who reads its results pays more (8192 x 1024 -> 4096 with GeLU and the next product 155 -> 159, 4096 rows 84 -> 94).
 bool streams_results(const ProjArgs &args, bool out_f32)
 {
