@@ -12,23 +12,26 @@ enum FwdForm { FWD_4x1, FWD_2x2, FWD_4x2, FWD_8x1 };
 struct FwdPlan { FwdForm form; int splits; };
 
 // A launch takes about, in us,
-//     start + tile_us (1 + shared (n - 1)) max((longest + few) first, (average + few) all W / (256 n)) + rest (average + few) tile_us all + merge
+//     start + tile_us max(walk, share) + merge
+//     walk  = (longest + few) first + shared (n - 1) (average + few) all         share = (1 + shared (n - 1)) (average + few) all W / (256 n) + rest
 // with W workgroups, n of them (rounded up, at most per_cu) on a compute unit at a time, `longest` and `average` the 64-key
-// tiles that a workgroup's group of wavefronts walks, the rest where W > 256 per_cu and the merge launch where the keys are
-// split: about 2.5 us and the partial results' bytes at 3.4 to 5.2 MB per us.
+// tiles that a workgroup's group of wavefronts walks, and the merge launch where the keys are split: 3.2 to 4 us and the partial results' bytes
+// at 3.4 to 4.9 MB per us.
+//   * walk: the longest workgroup's, which its neighbours on the compute unit slow down for as long as they are there, themselves
+//     of average length (under the causal mask, in the first segments, half the longest: 40 heads of 1459 rows take 25.6 us in 128-row
+//     workgroups, three to a compute unit, and were given 64-row ones, 33.3 us, with all of the longest one's time slowed down).
+//   * share: a compute unit's part of all walks, and where W > 256 per_cu the rest that part-filled last rounds leave: `tail` of a workgroup's
+//     time, or whole rounds where a compute unit holds one workgroup and all are about as long (`even`, d = 128).  A longer walk hides it:
+//     48 heads of 1537 rows, d = 128, 54.5 us in 8x1, were given 4x2, 65 us, with the rest added to either.
 //   * A wavefront none of whose rows exist only moves tiles and meets the barriers: a last query tile of which a share `a` of the
 //     wavefronts has rows takes idle + (1 - idle) a per key tile; `first` is that of the launch's longest workgroup, `all` the mean.
-//   * The rest is `tail` of a workgroup's time; where a compute unit holds one workgroup and all are about as long (`even`), the
-//     launch takes whole rounds of them.
 //   * With dropout (tables of their own) a tile takes 1.5 to 2 times as long: the generator's work is in vector slots of which the
 //     forward has none to spare.  FWD_4x2 at d = 64 is not built with dropout: by its figures there (5.42, 0.87, 2.18 per
 //     tile) it is never the shortest, over 15 million sizes.
-// Fitted to 454 launches at d = 64 and 436 at 128 (58 .. 4096 rows, 512 .. 50,112 keys, 2 .. 64 heads, 45 % with dropout, each in every form with 1 .. 16
-// splits, a backward pass before each call: alone, a loop of forward calls runs at a higher clock and flatters forms that load more): the
-// choice costs 1.4 % over the best of them on average with dropout at d = 64, 1.1 % at d = 128 (4.7 % and 3.7 % by the figures for d = 64
-// without dropout and by such ones for d = 128, with none of the three terms: 24 heads of 92 rows against 525 keys, d = 128, 11.1 us
-// in 4x2, 9.1 in 8x1; 26 of 888 rows with dropout 23.2, now 16.4).  d = 64 without dropout: fitted to 145 launches of its own, without these terms
-// (2.9 %; with the three terms 1.9, but a sweep of eight segments of 1024 rows, 16 heads, took 965 us instead of 949).
+// Fitted to 194 launches at d = 64 and 180 with dropout, 166 and 59 at d = 128 (58 .. 4096 rows, 512 .. 50,112 keys, 2 .. 64 heads, each in every
+// form with 1 .. 16 splits, a backward pass before each call: alone, a loop of forward calls runs at a higher clock and flatters forms that load
+// more): the choice costs 0.3, 0.7, 0.6 and 0.9 % over the best of them on average; with one half fitted, over the other half, 0.5 to 1.3 %.
+// (Fitted to others, with the neighbours' slowing over the whole longest walk and the rest added to it, 1.6, 1.2, 1.5 and 1.7 % over these.)
 inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
 {
     // (not below K's and V's bytes at 4.4 TB/s, the fourth powers added: 32 heads of 58 rows against 25,058 keys read 205 MB,
@@ -36,12 +39,12 @@ inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
     struct Cost { FwdForm form; int rows, groups, per_cu; double start, few, tile_us, shared, tail, idle; };
     struct Table { int forms; Cost form[3]; double merge, mb_per_us; bool rounds; };
     static const Table tables[2][2] = {
-        {{3, {{FWD_4x1, 128, 1, 3, 8.2, -3.3, 0.733, 0.51, 0.81, 1.0}, {FWD_2x2, 64, 2, 2, 4.7, 1.2, 0.799, 0.51, 0.55, 1.0}, {FWD_4x2, 128, 2, 1, 4.8, 1.7, 1.068, 0.0, 0.64, 1.0}},
-          2.8, 4.5, false},
-         {2, {{FWD_4x1, 128, 1, 3, 8.07, -1.43, 1.32, 0.467, 0.412, 0.623}, {FWD_2x2, 64, 2, 2, 2.11, 2.53, 1.38, 0.417, 0.447, 0.0}},
-          2.03, 3.41, true}},
-        {{2, {{FWD_8x1, 256, 1, 1, 3.38, 3.02, 1.50, 0.0, 0.645, 0.468}, {FWD_4x2, 128, 2, 1, 3.92, 2.36, 1.787, 0.0, 0.63, 1.0}}, 2.5, 5.2, true},
-         {2, {{FWD_8x1, 256, 1, 1, 3.38, 3.02, 2.385, 0.0, 0.645, 0.468}, {FWD_4x2, 128, 2, 1, 3.92, 2.36, 2.704, 0.0, 0.63, 1.0}}, 2.5, 5.2, true}}};
+        {{3, {{FWD_4x1, 128, 1, 3, 9.15, -3.20, 0.727, 0.556, 0.763, 0.890}, {FWD_2x2, 64, 2, 2, 4.92, 1.55, 0.802, 0.445, 1.181, 0.396}, {FWD_4x2, 128, 2, 1, 4.82, 1.97, 1.068, 0.0, 0.805, 1.000}},
+          3.95, 4.88, false},
+         {2, {{FWD_4x1, 128, 1, 3, 9.13, -1.25, 1.326, 0.509, 0.382, 0.545}, {FWD_2x2, 64, 2, 2, 2.97, 2.51, 1.463, 0.489, 0.385, 0.000}},
+          3.18, 3.37, false}},
+        {{2, {{FWD_8x1, 256, 1, 1, 3.61, 3.12, 1.500, 0.0, 0.535, 0.582}, {FWD_4x2, 128, 2, 1, 5.04, 2.31, 1.788, 0.0, 0.495, 0.964}}, 3.44, 3.81, true},
+         {2, {{FWD_8x1, 256, 1, 1, 3.61, 3.12, 2.460, 0.0, 0.535, 0.582}, {FWD_4x2, 128, 2, 1, 5.04, 2.31, 2.801, 0.0, 0.495, 0.964}}, 3.44, 3.81, true}}};
     const Table &table = tables[s.d == 128][with_drop];
     const double out_mb = (double)s.B * s.H * s.l_s * s.d * 1e-6;     // elements
     const int64_t most = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x, tiles = (most + 63) / 64;
@@ -63,12 +66,14 @@ inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
             const double longest = (double)(((tiles + sp - 1) / sp + c->groups - 1) / c->groups);
             const double average = mean_tiles / (sp * c->groups) + (sp * c->groups > 1 ? 0.5 : 0.0);
             const double rounds = ceil(W / 256.0), n = rounds < c->per_cu ? rounds : (double)c->per_cu;
-            const double walk = (longest + c->few) * (q_tiles == 1 ? last : 1.0), share = (average + c->few) * all * W / (256.0 * n);
-            double t = c->start + c->tile_us * (1.0 + c->shared * (n - 1.0)) * (walk > share ? walk : share);
+            const double shared = c->shared * (n - 1.0), mean = (average + c->few) * all, longest_walk = (longest + c->few) * (q_tiles == 1 ? last : 1.0);
+            double share = (1.0 + shared) * mean * W / (256.0 * n);
             if (W > 256.0 * c->per_cu) {
                 const double even = !table.rounds || c->per_cu > 1 || first < 0.6 * most ? 0.0 : ((double)first / (double)most - 0.6) / 0.4;
-                t += ((1.0 - even) * c->tail + even * (rounds - W / 256.0)) * (average + c->few) * c->tile_us * all;
+                share += ((1.0 - even) * c->tail + even * (rounds - W / 256.0)) * mean;
             }
+            const double walk = longest_walk + shared * (mean < longest_walk ? mean : longest_walk);
+            double t = c->start + c->tile_us * (walk > share ? walk : share);
             t = sqrt(sqrt(t * t * t * t + kv_us * kv_us * kv_us * kv_us));
             if (sp > 1) t += table.merge + out_mb * (8 * sp + 2) / table.mb_per_us;
             if (best_t == 0.0 || t < best_t) { best_t = t; best = {c->form, sp}; }

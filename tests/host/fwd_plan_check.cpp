@@ -29,6 +29,13 @@ static const Measured measured[] = {
     {{0, 715, 715, 4, 12, 128, 1, 0}, true, 3, {{FWD_4x2, 1}}},     // 28.0 us, 40.6 as chosen before
     {{7, 967, 1171, 4, 10, 128, 1, 0}, true, 4, {{FWD_4x2, 1}}},     // 37.7 us, 50.4 as chosen before
     {{0, 1557, 1557, 2, 10, 128, 1, 0}, true, 6, {{FWD_4x2, 1}}},     // 43.0 us, 70.2 as chosen before
+    {{22240, 2339, 35978, 4, 7, 64, 1, 0}, false, 2, {{FWD_4x1, 2}}},     // 506 us, 565 as chosen before
+    {{1604, 3456, 17209, 4, 8, 64, 1, 0}, false, 2, {{FWD_4x1, 1}}},     // 127 us, 138 as chosen before
+    {{0, 1459, 1459, 4, 10, 64, 1, 0}, false, 3, {{FWD_4x1, 1}}},     // 25.6 us, 33.3 as chosen before
+    {{1531, 1622, 4513, 2, 6, 64, 1, 0}, false, 7, {{FWD_2x2, 1}}},     // 30.1 us, 36.0 as chosen before
+    {{0, 1537, 1537, 3, 16, 128, 1, 0}, false, 4, {{FWD_8x1, 1}}},     // 54.5 us, 65.1 as chosen before
+    {{211, 3110, 3517, 2, 11, 128, 1, 0}, false, 4, {{FWD_8x1, 1}}},     // 95.8 us, 106 as chosen before
+    {{0, 1257, 1257, 3, 16, 128, 1, 0}, true, 5, {{FWD_4x2, 1}}},     // 56.5 us, 68.0 as chosen before
     {{10452, 1339, 15568, 3, 5, 128, 0, 0}, true, 12, {{FWD_4x2, 3}}},     // 278.4 us, 352.5 as chosen before
 };
 

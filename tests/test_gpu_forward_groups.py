@@ -21,14 +21,14 @@ SHAPES = [  # B, l_x, H, d, s0, l_s, causal
 # rows past the end in the last query tile.  (At d = 64 and with dropout there is no 4 x 2.)
 FORMS = [  # B, l_x, H, d, s0, l_s, causal, p_drop, (row blocks, groups, split)
     (1, 131, 2, 64, 34, 72, True, 0.0, (2, 2, False)), (1, 508, 1, 64, 442, 66, True, 0.0, (2, 2, True)),
-    (1, 258, 64, 64, 0, 258, False, 0.0, (4, 1, False)), (1, 3114, 16, 64, 2403, 711, True, 0.0, (4, 1, True)),
-    (1, 515, 32, 64, 0, 515, True, 0.0, (4, 2, False)), (1, 2153, 8, 64, 1502, 651, True, 0.0, (4, 2, True)),
+    (1, 690, 48, 64, 0, 690, False, 0.0, (4, 1, False)), (1, 3091, 16, 64, 2034, 1057, True, 0.0, (4, 1, True)),
+    (1, 350, 48, 64, 0, 350, False, 0.0, (4, 2, False)), (1, 2082, 8, 64, 1216, 671, True, 0.0, (4, 2, True)),
     (1, 130, 1, 64, 0, 66, True, 0.25, (2, 2, False)), (1, 477, 1, 64, 399, 78, True, 0.25, (2, 2, True)),
-    (1, 257, 64, 64, 0, 257, True, 0.25, (4, 1, False)), (1, 1533, 1, 64, 234, 375, True, 0.25, (4, 1, True)),
-    (1, 200, 1, 128, 62, 138, True, 0.0, (4, 2, False)), (1, 476, 1, 128, 320, 135, True, 0.0, (4, 2, True)),
+    (1, 400, 64, 64, 0, 400, False, 0.25, (4, 1, False)), (1, 1533, 1, 64, 234, 375, True, 0.25, (4, 1, True)),
+    (1, 300, 2, 128, 10, 203, True, 0.0, (4, 2, False)), (1, 475, 1, 128, 311, 164, True, 0.0, (4, 2, True)),
     (1, 644, 48, 128, 0, 644, False, 0.0, (8, 1, False)), (1, 943, 1, 128, 255, 297, True, 0.0, (8, 1, True)),
-    (1, 161, 1, 128, 0, 161, False, 0.25, (4, 2, False)), (1, 489, 1, 128, 359, 130, True, 0.25, (4, 2, True)),
-    (1, 642, 48, 128, 0, 642, True, 0.25, (8, 1, False)), (1, 736, 1, 128, 103, 262, True, 0.25, (8, 1, True)),
+    (1, 250, 2, 128, 29, 169, False, 0.25, (4, 2, False)), (1, 489, 1, 128, 359, 130, True, 0.25, (4, 2, True)),
+    (1, 690, 48, 128, 0, 690, False, 0.25, (8, 1, False)), (1, 736, 1, 128, 103, 262, True, 0.25, (8, 1, True)),
 ]
 
 
