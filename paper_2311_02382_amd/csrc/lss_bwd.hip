@@ -153,7 +153,7 @@ BwdLaunch plan_bwd(const SegShape &s, bool with_drop, int elem_bytes, bool may_o
     if (elem_bytes == 4) return {pick_splits(s, most, elem_bytes), 1, false, false, false, false};
     const BwdPlan plan = s.l_s <= kSkinnyRows ? BwdPlan{pick_dq_splits(s, most), 1}
                          : s.d == 128         ? BwdPlan{pick_splits(s, most, elem_bytes), 1}
-                                              : pick_bwd_plan(s, most, may_own);
+                                              : pick_bwd_plan(s, with_drop, most, may_own);
     const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x;
     const int dq_tiles = (int)(((seen + 63) / 64 + plan.splits - 1) / plan.splits + plan.groups - 1) / plan.groups;
     const int one_pass = may_own ? skinny_splits(s, with_drop, elem_bytes, most, dq_tiles) : 0;

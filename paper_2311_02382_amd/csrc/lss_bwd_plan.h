@@ -52,6 +52,9 @@ inline bool bwd_own_values(const SegShape &s, int n_splits, int groups)
 // preprocess launch is made are fitted to 680 more, each form with and without that launch: the choice costs
 // 2.2 % over the best of them on average (2.3 % with the saving taken for one group and all segments of up to 512 rows, whether
 // bwd_own_values says so or not; eleven launches 3 to 8 % slower then, two faster: 15 heads of 365 rows against 1873 keys 25.5 us and now 23.8).
+// With dropout a tile takes longer, most in two groups, and splits pay sooner: starts and tile times fitted to 193 launches of their own, in
+// every form; the choice costs 1.9 % over the best of them on average, with half of them fitted 2.3 % over the other half, and 3.6 % by the figures
+// without dropout (6 heads of 1034 rows against 2121 keys: 53.4 us, in two ranges 40.6; 14 of 152 behind 401: 23.4 and 19.4).
 struct BwdPlan { int splits, groups; };
 
 // What all estimates of a launch share
@@ -72,11 +75,12 @@ inline BwdWork bwd_work(const SegShape &s)
 }
 
 // The estimate for one form and split count; `own`: no preprocess launch (bwd_own_values), which the start counts
-inline double bwd_estimate(const BwdWork &w, int splits, int groups, bool own)
+inline double bwd_estimate(const BwdWork &w, int splits, int groups, bool own, bool with_drop)
 {
     struct Cost { double start, own, dq_us, dq_more, dkv_us, dkv_more, dkv_slow, rate, last; };
-    static const Cost forms[] = {{5.8, 1.6, 0.70, 1.7, 1.02, 3.7, 0.35, 0.85, 0.31}, {4.0, 0.4, 1.11, 2.6, 1.52, 4.6, 0.0, 1.06, 0.51}};
-    const Cost &c = forms[groups - 1];
+    static const Cost forms[2][2] = {{{5.8, 1.6, 0.70, 1.7, 1.02, 3.7, 0.35, 0.85, 0.31}, {4.0, 0.4, 1.11, 2.6, 1.52, 4.6, 0.0, 1.06, 0.51}},
+                                     {{17.7, 2.1, 0.919, 1.7, 1.229, 3.7, 0.35, 0.85, 0.31}, {9.4, 0.43, 1.693, 2.6, 1.879, 4.6, 0.0, 1.06, 0.51}}};
+    const Cost &c = forms[with_drop][groups - 1];
     const double n_dq = w.n_dq * splits, N = n_dq + w.n_dkv, per_group = groups == 1 ? 1.0 : 0.5;
     const double shared = N < 256.0 ? 0.0 : N > 512.0 ? 1.0 : N / 256.0 - 1.0;
     const double dq = ((double)((((int)w.tiles + splits - 1) / splits + groups - 1) / groups) + c.dq_more + 1.0) * c.dq_us;
@@ -89,7 +93,7 @@ inline double bwd_estimate(const BwdWork &w, int splits, int groups, bool own)
 }
 
 // `may_own`: bwd_own_values decides (no gradient overlaps `out`)
-inline BwdPlan pick_bwd_plan(const SegShape &s, int most, bool may_own)
+inline BwdPlan pick_bwd_plan(const SegShape &s, bool with_drop, int most, bool may_own)
 {
     const BwdWork w = bwd_work(s);
     BwdPlan best{1, 1};
@@ -97,7 +101,7 @@ inline BwdPlan pick_bwd_plan(const SegShape &s, int most, bool may_own)
     for (int groups = 1; groups <= (s.l_s > 128 ? 2 : 1); ++groups)      // (two tiles of rows: nothing to share)
         for (int splits = 1; splits <= most; ++splits) {
             if (splits > 1 && w.tiles < 4 * splits) break;
-            const double t = bwd_estimate(w, splits, groups, may_own && bwd_own_values(s, splits, groups));
+            const double t = bwd_estimate(w, splits, groups, may_own && bwd_own_values(s, splits, groups), with_drop);
             if (best_t == 0.0 || t < best_t) { best_t = t; best = {splits, groups}; }
         }
     return best;

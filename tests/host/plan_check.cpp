@@ -1,10 +1,12 @@
 // Goes over the choices of csrc/lss_bwd_plan.h on the host: of the forms and split counts that a launch may take, the one chosen
-// has the smallest estimate under the launcher's own decision whether there is a preprocess launch, and every choice stays within
-// the limits that the kernels and the workspace have.
+// has the smallest estimate under the launcher's own decision whether there is a preprocess launch, every choice stays within
+// the limits that the kernels and the workspace have, and on launches with dropout that were measured in every form and split
+// count one of those within 6 % of the shortest is taken.
 #include "lss_bwd_plan.h"
 
 #include <cstdio>
 #include <initializer_list>
+#include <vector>
 
 static int fail(const char *what, const lss::SegShape &s, const lss::BwdPlan &p)
 {
@@ -20,6 +22,21 @@ int main()
             const double want = pow(pow(a, 6.0) + pow(b, 6.0), 1.0 / 6.0);
             if (!(fabs(lss::larger_or_both(a, b) - want) <= 1e-13 * want)) return 1;
         }
+    struct { lss::SegShape s; int most; std::vector<lss::BwdPlan> good; } measured[] = {
+        {{1080, 1034, 2121, 1, 6, 64, 0, 0}, 8, {{2, 2}}},     // 40.6 us, 53.5 as chosen before
+        {{1330, 1797, 13899, 1, 2, 64, 1, 0}, 16, {{2, 2}, {3, 2}, {4, 2}, {5, 2}, {6, 2}}},     // 56.1 us, 71.0 as chosen before
+        {{353, 124, 2363, 1, 5, 64, 1, 0}, 9, {{2, 1}}},     // 17.4 us, 21.5 as chosen before
+        {{571, 561, 1527, 3, 2, 64, 1, 0}, 6, {{2, 2}, {3, 2}, {4, 2}}},     // 29.1 us, 33.8 as chosen before
+        {{0, 1178, 1178, 2, 8, 64, 1, 0}, 4, {{1, 2}}},     // 41.7 us, 48.1 as chosen before
+        {{782, 214, 1031, 1, 11, 64, 1, 0}, 4, {{3, 1}, {3, 2}, {4, 2}}},     // 20.7 us, 23.8 as chosen before
+        {{2949, 759, 5697, 2, 2, 64, 1, 0}, 16, {{4, 2}, {5, 2}, {6, 2}}},     // 35.1 us, 40.3 as chosen before
+    };
+    for (const auto &m : measured) {
+        const lss::BwdPlan p = lss::pick_bwd_plan(m.s, true, m.most, true);
+        bool good = false;
+        for (const lss::BwdPlan &g : m.good) good = good || (g.splits == p.splits && g.groups == p.groups);
+        if (!good) return fail("not among the shortest", m.s, p);
+    }
     long long owns = 0, lets = 0;
     for (int l_s : {65, 66, 97, 128, 129, 192, 193, 256, 257, 300, 384, 512, 513, 1024, 1044, 4096, 12661})
         for (int l_x : {65, 129, 512, 1000, 1024, 4100, 8192, 24576, 50112})
@@ -31,19 +48,20 @@ int main()
                         const lss::SegShape s{s0, l_s, l_x, heads > 16 ? heads / 8 : 1, heads > 16 ? 8 : heads, 64, causal, 0};
                         const lss::BwdWork w = lss::bwd_work(s);
                         for (int most : {1, 2, 5, 16})
-                            for (bool may_own : {false, true}) {
-                                const lss::BwdPlan p = lss::pick_bwd_plan(s, most, may_own);
+                            for (int form = 0; form < 4; ++form) {
+                                const bool may_own = form & 1, with_drop = form & 2;
+                                const lss::BwdPlan p = lss::pick_bwd_plan(s, with_drop, most, may_own);
                                 const int64_t seen = causal ? s0 + l_s : l_x, tiles = (seen + 63) / 64;
                                 if (p.splits < 1 || p.splits > most || p.groups < 1 || p.groups > (l_s > 128 ? 2 : 1) || (p.splits > 1 && tiles / p.splits < 4))
                                     return fail("outside the limits", s, p);
                                 auto own = [&](int splits, int groups) { return may_own && lss::bwd_own_values(s, splits, groups); };
                                 if (l_s > lss::kOwnRows && own(p.splits, p.groups)) return fail("start values that do not fit", s, p);
                                 (own(p.splits, p.groups) ? owns : lets) += 1;
-                                const double t = lss::bwd_estimate(w, p.splits, p.groups, own(p.splits, p.groups));
+                                const double t = lss::bwd_estimate(w, p.splits, p.groups, own(p.splits, p.groups), with_drop);
                                 if (!(t > 0.0 && t < 1e9)) return fail("no time", s, p);
                                 for (int g = 1; g <= (l_s > 128 ? 2 : 1); ++g)
                                     for (int sp = 1; sp <= most && (sp == 1 || tiles / sp >= 4); ++sp)
-                                        if (lss::bwd_estimate(w, sp, g, own(sp, g)) < t) return fail("a shorter one is there", s, p);
+                                        if (lss::bwd_estimate(w, sp, g, own(sp, g), with_drop) < t) return fail("a shorter one is there", s, p);
                             }
                     }
     if (owns < 100 || lets < 100) return 1;
