@@ -30,7 +30,7 @@ struct FwdPlan { FwdForm form; int splits; };
 //     tile) it is never the shortest, over 15 million sizes.
 // Fitted to 194 launches at d = 64 and 180 with dropout, 166 and 59 at d = 128 (58 .. 4096 rows, 512 .. 50,112 keys, 2 .. 64 heads, each in every
 // form with 1 .. 16 splits, a backward pass before each call: alone, a loop of forward calls runs at a higher clock and flatters forms that load
-// more): the choice costs 0.3, 0.7, 0.6 and 0.9 % over the best of them on average; with one half fitted, over the other half, 0.5 to 1.3 %.
+// more): the choice costs 0.3, 0.7, 0.6 and 0.9 % over the best of them on average; over 140 others 1.8, 0.8, 0.8 and 1.7 %.
 // (Fitted to others, with the neighbours' slowing over the whole longest walk and the rest added to it, 1.6, 1.2, 1.5 and 1.7 % over these.)
 inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
 {

@@ -670,8 +670,8 @@ bool streams_results(const ProjArgs &args, bool out_f32)
 // where compute units hold one workgroup each (PER_CU = 1: where half of them have one) a contraction tile takes
 // per_tile[0], where they are full per_tile[1].  The figures are fitted to linear_fwd and linear_bwd_input at 230 .. 98304 rows and
 // 512 .. 8192 columns either way (20 launches in a graph each), with the loop of 32 x 32 x 16 instructions that there was.  With the present
-// one, 40 drawn feed-forward units and projections in every tile: the choice costs 0.6 to 1.3 % over the best tile on average, 2.7 % in
-// project_bwd (at worst 22 us instead of 17) and 1.7 % in the projections' weight gradients.  Large tiles move the fewest bytes per flop
+// one, 70 drawn feed-forward units and projections in every tile: the choice costs 0.5 to 1.3 % over the best tile on average, 3 % in
+// project_bwd (at worst 28 us instead of 16) and in the projections' weight gradients.  Large tiles move the fewest bytes per flop
 // but a launch of few of them leaves compute units idle (2048 x 2048 -> 512: 16 workgroups of 256 x 256, 46 us;
 // 256 of 64 x 64, 12 us with the former loop), and where even 64 x 64 tiles leave one wavefront per SIMD the chain of contraction
 // tiles is what takes the time: four groups of wavefronts that share it took 9 us in a graph of them, 12 among other work now.
