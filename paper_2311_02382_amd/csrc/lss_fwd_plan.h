@@ -15,8 +15,8 @@ struct FwdPlan { FwdForm form; int splits; };
 //     start + tile_us max(walk, share) + merge
 //     walk  = (longest + few) first + shared (n - 1) (average + few) all         share = (1 + shared (n - 1)) (average + few) all W / (256 n) + rest
 // with W workgroups, n of them (rounded up, at most per_cu) on a compute unit at a time, `longest` and `average` the 64-key
-// tiles that a workgroup's group of wavefronts walks, and the merge launch where the keys are split: 3.2 to 4 us and the partial results' bytes
-// at 3.4 to 4.9 MB per us.
+// tiles that a workgroup's group of wavefronts walks, and the merge launch where the keys are split: 2.4 to 2.9 us and the partial results' bytes
+// at 3.9 to 4.3 MB per us.
 //   * walk: the longest workgroup's, which its neighbours on the compute unit slow down for as long as they are there, themselves
 //     of average length (under the causal mask, in the first segments, half the longest: 40 heads of 1459 rows take 25.6 us in 128-row
 //     workgroups, three to a compute unit, and were given 64-row ones, 33.3 us, with all of the longest one's time slowed down).
@@ -28,10 +28,10 @@ struct FwdPlan { FwdForm form; int splits; };
 //   * With dropout (tables of their own) a tile takes 1.5 to 2 times as long: the generator's work is in vector slots of which the
 //     forward has none to spare.  FWD_4x2 at d = 64 is not built with dropout: by its figures there (5.42, 0.87, 2.18 per
 //     tile) it is never the shortest, over 15 million sizes.
-// Fitted to 194 launches at d = 64 and 180 with dropout, 166 and 59 at d = 128 (58 .. 4096 rows, 512 .. 50,112 keys, 2 .. 64 heads, each in every
+// Fitted to 374 launches at d = 64 and 322 with dropout, 251 and 97 at d = 128 (58 .. 4096 rows, 512 .. 50,112 keys, 2 .. 64 heads, each in every
 // form with 1 .. 16 splits, a backward pass before each call: alone, a loop of forward calls runs at a higher clock and flatters forms that load
-// more): the choice costs 0.3, 0.7, 0.6 and 0.9 % over the best of them on average; over 140 others 1.8, 0.8, 0.8 and 1.7 %.
-// (Fitted to others, with the neighbours' slowing over the whole longest walk and the rest added to it, 1.6, 1.2, 1.5 and 1.7 % over these.)
+// more), so that estimates off by 1.2 % either way still choose well: the choice costs 0.6, 1.0, 0.6 and 1.1 % over the best of them on average.
+// (Fitted to others, with the neighbours' slowing over the whole longest walk and the rest added to it, 1.6, 1.2, 1.5 and 1.7 %.)
 inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
 {
     // (not below K's and V's bytes at 4.4 TB/s, the fourth powers added: 32 heads of 58 rows against 25,058 keys read 205 MB,
@@ -39,12 +39,12 @@ inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
     struct Cost { FwdForm form; int rows, groups, per_cu; double start, few, tile_us, shared, tail, idle; };
     struct Table { int forms; Cost form[3]; double merge, mb_per_us; bool rounds; };
     static const Table tables[2][2] = {
-        {{3, {{FWD_4x1, 128, 1, 3, 9.15, -3.20, 0.727, 0.556, 0.763, 0.890}, {FWD_2x2, 64, 2, 2, 4.92, 1.55, 0.802, 0.445, 1.181, 0.396}, {FWD_4x2, 128, 2, 1, 4.82, 1.97, 1.068, 0.0, 0.805, 1.000}},
-          3.95, 4.88, false},
-         {2, {{FWD_4x1, 128, 1, 3, 9.13, -1.25, 1.326, 0.509, 0.382, 0.545}, {FWD_2x2, 64, 2, 2, 2.97, 2.51, 1.463, 0.489, 0.385, 0.000}},
-          3.18, 3.37, false}},
-        {{2, {{FWD_8x1, 256, 1, 1, 3.61, 3.12, 1.500, 0.0, 0.535, 0.582}, {FWD_4x2, 128, 2, 1, 5.04, 2.31, 1.788, 0.0, 0.495, 0.964}}, 3.44, 3.81, true},
-         {2, {{FWD_8x1, 256, 1, 1, 3.61, 3.12, 2.460, 0.0, 0.535, 0.582}, {FWD_4x2, 128, 2, 1, 5.04, 2.31, 2.801, 0.0, 0.495, 0.964}}, 3.44, 3.81, true}}};
+        {{3, {{FWD_4x1, 128, 1, 3, 9.05, -2.38, 0.719, 0.542, 0.542, 0.411}, {FWD_2x2, 64, 2, 2, 4.74, 2.09, 0.793, 0.474, 1.164, 0.923}, {FWD_4x2, 128, 2, 1, 5.39, 2.14, 1.078, 0.0, 0.789, 0.531}},
+          2.73, 3.85, false},
+         {2, {{FWD_4x1, 128, 1, 3, 10.97, -0.43, 1.319, 0.683, 0.552, 0.443}, {FWD_2x2, 64, 2, 2, 4.90, 1.50, 1.512, 0.550, 0.552, 0.000}},
+          2.42, 4.32, false}},
+        {{2, {{FWD_8x1, 256, 1, 1, 2.55, 4.36, 1.512, 0.0, 0.556, 0.563}, {FWD_4x2, 128, 2, 1, 5.97, 2.31, 1.821, 0.0, 0.489, 1.000}}, 2.85, 4.19, true},
+         {2, {{FWD_8x1, 256, 1, 1, 2.55, 4.36, 2.525, 0.0, 0.556, 0.563}, {FWD_4x2, 128, 2, 1, 5.97, 2.31, 2.859, 0.0, 0.489, 1.000}}, 2.85, 4.19, true}}};
     const Table &table = tables[s.d == 128][with_drop];
     const double out_mb = (double)s.B * s.H * s.l_s * s.d * 1e-6;     // elements
     const int64_t most = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x, tiles = (most + 63) / 64;

@@ -20,15 +20,15 @@ SHAPES = [  # B, l_x, H, d, s0, l_s, causal
 # The workgroup's form by row blocks of 32 x groups, and whether the keys are split besides: every one that is built, with
 # rows past the end in the last query tile.  (At d = 64 and with dropout there is no 4 x 2.)
 FORMS = [  # B, l_x, H, d, s0, l_s, causal, p_drop, (row blocks, groups, split)
-    (1, 131, 2, 64, 34, 72, True, 0.0, (2, 2, False)), (1, 508, 1, 64, 442, 66, True, 0.0, (2, 2, True)),
-    (1, 690, 48, 64, 0, 690, False, 0.0, (4, 1, False)), (1, 3091, 16, 64, 2034, 1057, True, 0.0, (4, 1, True)),
-    (1, 350, 48, 64, 0, 350, False, 0.0, (4, 2, False)), (1, 2082, 8, 64, 1216, 671, True, 0.0, (4, 2, True)),
-    (1, 130, 1, 64, 0, 66, True, 0.25, (2, 2, False)), (1, 477, 1, 64, 399, 78, True, 0.25, (2, 2, True)),
-    (1, 400, 64, 64, 0, 400, False, 0.25, (4, 1, False)), (1, 1533, 1, 64, 234, 375, True, 0.25, (4, 1, True)),
-    (1, 300, 2, 128, 10, 203, True, 0.0, (4, 2, False)), (1, 475, 1, 128, 311, 164, True, 0.0, (4, 2, True)),
-    (1, 644, 48, 128, 0, 644, False, 0.0, (8, 1, False)), (1, 943, 1, 128, 255, 297, True, 0.0, (8, 1, True)),
-    (1, 250, 2, 128, 29, 169, False, 0.25, (4, 2, False)), (1, 489, 1, 128, 359, 130, True, 0.25, (4, 2, True)),
-    (1, 690, 48, 128, 0, 690, False, 0.25, (8, 1, False)), (1, 736, 1, 128, 103, 262, True, 0.25, (8, 1, True)),
+    (1, 200, 1, 64, 0, 125, True, 0.0, (2, 2, False)), (1, 718, 1, 64, 602, 85, False, 0.0, (2, 2, True)),
+    (1, 546, 64, 64, 0, 546, True, 0.0, (4, 1, False)), (1, 3395, 24, 64, 2620, 686, False, 0.0, (4, 1, True)),
+    (1, 710, 24, 64, 0, 710, False, 0.0, (4, 2, False)), (1, 2609, 16, 64, 1648, 598, False, 0.0, (4, 2, True)),
+    (1, 195, 1, 64, 102, 73, True, 0.25, (2, 2, False)), (1, 807, 1, 64, 610, 70, True, 0.25, (2, 2, True)),
+    (1, 695, 64, 64, 0, 695, False, 0.25, (4, 1, False)), (1, 1996, 16, 64, 0, 1185, False, 0.25, (4, 1, True)),
+    (1, 206, 1, 128, 0, 206, True, 0.0, (4, 2, False)), (1, 642, 1, 128, 414, 209, False, 0.0, (4, 2, True)),
+    (1, 691, 48, 128, 0, 691, False, 0.0, (8, 1, False)), (1, 1187, 1, 128, 190, 413, True, 0.0, (8, 1, True)),
+    (1, 181, 1, 128, 0, 181, True, 0.25, (4, 2, False)), (1, 514, 1, 128, 182, 303, False, 0.25, (4, 2, True)),
+    (1, 700, 48, 128, 0, 700, False, 0.25, (8, 1, False)), (1, 2203, 24, 128, 1052, 706, False, 0.25, (8, 1, True)),
 ]
 
 
