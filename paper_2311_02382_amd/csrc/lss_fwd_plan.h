@@ -30,8 +30,9 @@ struct FwdPlan { FwdForm form; int splits; };
 //     tile) it is never the shortest, over 15 million sizes.
 // Fitted to 374 launches at d = 64 and 322 with dropout, 251 and 97 at d = 128 (58 .. 4096 rows, 512 .. 50,112 keys, 2 .. 64 heads, each in every
 // form with 1 .. 16 splits, a backward pass before each call: alone, a loop of forward calls runs at a higher clock and flatters forms that load
-// more), so that estimates off by 1.2 % either way still choose well: the choice costs 0.6, 1.0, 0.6 and 1.1 % over the best of them on average.
-// (Fitted to others, with the neighbours' slowing over the whole longest walk and the rest added to it, 1.6, 1.2, 1.5 and 1.7 %.)
+// more), so that estimates off by 1.2 % either way still choose well: the choice costs 0.6, 1.0, 0.6 and 1.1 % over the best of them on average,
+// over 140 launches that were not fitted 1.6, 1.9, 1.1 and 1.1 %.
+// (Fitted to others, with the neighbours' slowing over the whole longest walk and the rest added to it, 1.6, 1.2, 1.5 and 1.7 % over a part of those fitted.)
 inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
 {
     // (not below K's and V's bytes at 4.4 TB/s, the fourth powers added: 32 heads of 58 rows against 25,058 keys read 205 MB,
