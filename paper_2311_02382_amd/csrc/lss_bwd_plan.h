@@ -52,6 +52,8 @@ inline bool bwd_own_values(const SegShape &s, int n_splits, int groups)
 // preprocess launch is made are fitted to 680 more, each form with and without that launch: the choice costs
 // 2.2 % over the best of them on average (2.3 % with the saving taken for one group and all segments of up to 512 rows, whether
 // bwd_own_values says so or not; eleven launches 3 to 8 % slower then, two faster: 15 heads of 365 rows against 1873 keys 25.5 us and now 23.8).
+// Two groups gain nothing over their preprocess launch (a start of 4.0 with 0.4 saved fitted those launches as well, but gave 13 heads of
+// 1291 rows and 20 of 1363 to one group: 33 -> 37 and 42 -> 46 us).
 // With dropout a tile takes longer, most in two groups, and splits pay sooner: starts and tile times fitted to 193 launches of their own, in
 // every form; the choice costs 1.9 % over the best of them on average, with half of them fitted 2.3 % over the other half, and 3.6 % by the figures
 // without dropout (6 heads of 1034 rows against 2121 keys: 53.4 us, in two ranges 40.6; 14 of 152 behind 401: 23.4 and 19.4).
@@ -78,7 +80,7 @@ inline BwdWork bwd_work(const SegShape &s)
 inline double bwd_estimate(const BwdWork &w, int splits, int groups, bool own, bool with_drop)
 {
     struct Cost { double start, own, dq_us, dq_more, dkv_us, dkv_more, dkv_slow, rate, last; };
-    static const Cost forms[2][2] = {{{5.8, 1.6, 0.70, 1.7, 1.02, 3.7, 0.35, 0.85, 0.31}, {4.0, 0.4, 1.11, 2.6, 1.52, 4.6, 0.0, 1.06, 0.51}},
+    static const Cost forms[2][2] = {{{5.8, 1.6, 0.70, 1.7, 1.02, 3.7, 0.35, 0.85, 0.31}, {3.4, 0.0, 1.11, 2.6, 1.52, 4.6, 0.0, 1.06, 0.51}},
                                      {{17.7, 2.1, 0.919, 1.7, 1.229, 3.7, 0.35, 0.85, 0.31}, {9.4, 0.43, 1.693, 2.6, 1.879, 4.6, 0.0, 1.06, 0.51}}};
     const Cost &c = forms[with_drop][groups - 1];
     const double n_dq = w.n_dq * splits, N = n_dq + w.n_dkv, per_group = groups == 1 ? 1.0 : 0.5;

@@ -22,7 +22,7 @@ TWO_GROUPS = [  # B, l_x, H, s0, l_s, causal, p_drop, (own, split)
     (1, 892, 1, 609, 283, True, 0.0, (1, False)), (3, 2569, 4, 609, 390, True, 0.0, (1, False)),
     (1, 897, 2, 640, 257, True, 0.0, (1, False)), (1, 1025, 1, 576, 449, True, 0.0, (1, False)),     # last key tile: one query tile, of the first group
     (1, 276, 6, 64, 171, True, 0.25, (1, False)), (1, 257, 2, 64, 193, True, 0.25, (1, False)),      # (the second here too)
-    (1, 1756, 1, 1384, 372, True, 0.0, (1, True)), (1, 1665, 2, 1344, 321, True, 0.0, (1, True)),
+    (1, 1961, 1, 1536, 389, True, 0.0, (1, True)), (1, 14265, 8, 2176, 346, True, 0.0, (1, True)),
     (1, 1677, 3, 1449, 162, True, 0.25, (1, True)), (1, 1587, 4, 1381, 206, False, 0.25, (1, True)),
     (1, 17417, 1, 7155, 241, False, 0.0, (1, True)), (1, 17417, 1, 7155, 241, False, 0.25, (1, True)),       # 16 ranges
     (1, 325, 1, 0, 325, True, 0.0, (0, False)), (1, 513, 2, 0, 513, True, 0.0, (0, False)),         # first query tile: two key tiles
