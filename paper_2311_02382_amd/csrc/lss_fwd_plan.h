@@ -30,8 +30,8 @@ struct FwdPlan { FwdForm form; int splits; };
 //     tile) it is never the shortest, over 15 million sizes.
 // Fitted to 374 launches at d = 64 and 322 with dropout, 251 and 97 at d = 128 (58 .. 4096 rows, 512 .. 50,112 keys, 2 .. 64 heads, each in every
 // form with 1 .. 16 splits, a backward pass before each call: alone, a loop of forward calls runs at a higher clock and flatters forms that load
-// more), so that estimates off by 1.2 % either way still choose well: the choice costs 0.6, 1.0, 0.6 and 1.1 % over the best of them on average,
-// over 140 launches that were not fitted 1.6, 1.9, 1.1 and 1.1 %.
+// more), so that estimates off by 1.2 % either way still choose well: the choice costs 0.5, 1.0, 0.6 and 1.1 % over the best of them on average,
+// over 140 launches that were not fitted 1.5, 2.0, 1.1 and 1.1 %.
 // (Fitted to others, with the neighbours' slowing over the whole longest walk and the rest added to it, 1.6, 1.2, 1.5 and 1.7 % over a part of those fitted.)
 inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
 {
@@ -40,8 +40,8 @@ inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
     struct Cost { FwdForm form; int rows, groups, per_cu; double start, few, tile_us, shared, tail, idle; };
     struct Table { int forms; Cost form[3]; double merge, mb_per_us; bool rounds; };
     static const Table tables[2][2] = {
-        {{3, {{FWD_4x1, 128, 1, 3, 9.05, -2.38, 0.719, 0.542, 0.542, 0.411}, {FWD_2x2, 64, 2, 2, 4.74, 2.09, 0.793, 0.474, 1.164, 0.923}, {FWD_4x2, 128, 2, 1, 5.39, 2.14, 1.078, 0.0, 0.789, 0.531}},
-          2.73, 3.85, false},
+        {{3, {{FWD_4x1, 128, 1, 3, 9.05, -2.38, 0.719, 0.542, 0.542, 0.399}, {FWD_2x2, 64, 2, 2, 5.02, 2.09, 0.821, 0.401, 1.135, 0.688}, {FWD_4x2, 128, 2, 1, 5.39, 2.14, 1.078, 0.0, 0.789, 0.630}},
+          2.74, 3.85, false},
          {2, {{FWD_4x1, 128, 1, 3, 10.97, -0.43, 1.319, 0.683, 0.552, 0.443}, {FWD_2x2, 64, 2, 2, 4.90, 1.50, 1.512, 0.550, 0.552, 0.000}},
           2.42, 4.32, false}},
         {{2, {{FWD_8x1, 256, 1, 1, 2.55, 4.36, 1.512, 0.0, 0.556, 0.563}, {FWD_4x2, 128, 2, 1, 5.97, 2.31, 1.821, 0.0, 0.489, 1.000}}, 2.85, 4.19, true},
