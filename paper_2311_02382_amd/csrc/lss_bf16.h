@@ -111,40 +111,40 @@ struct DirectTile {
             off[i] = ((uint32_t)min(row, rows_ok - 1) * (uint32_t)row_stride + (uint32_t)chunk * 8u) * 2u;
         }
     }
-    // Issue the loads of two tensors' tiles, the second tile following the first in LDS (lds_tile + BYTES); off0 and off1
-    // may be the same.  Base pointers, `lds_tile` and `wave` must be wavefront-uniform.
-    // One assembly block (see lds_dma for why assembly), so that M0 is saved and restored once and
-    // merely stepped by WAVES KB (one KB per wavefront) from load to load.
-    static __device__ __forceinline__ void issue_pair(const bf16_t *g0_uniform, const bf16_t *g1_uniform, const uint32_t (&off0)[NI],
+    // Two tensors' tiles, the second following the first in LDS (lds_tile + BYTES), loaded by one assembly block (see lds_dma for
+    // why assembly).  Here a wavefront's NI load instructions fill NI consecutive KB of either tile: what the instruction adds to
+    // its LDS address it adds to the global one too, so that one LDS address (M0) serves a tile's loads -- each scalar
+    // instruction beside the matrix instructions costs a lone wavefront about 8 cycles.  pair_offsets() makes up for that on
+    // the global side: its offsets are counted from PAIR_BIAS bytes ahead of the tile's first element (pair_base()).
+    static constexpr uint32_t PAIR_BIAS = (NI - 1) * 1024;
+    static __device__ __forceinline__ void pair_offsets(uint32_t (&off)[NI], int64_t row_stride, int rows_ok, int wave, int lane)
+    {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int row = (wave * NI + i) * RPI + lane / CPR, chunk = (lane % CPR) ^ tile_swizzle<D>(row);
+            off[i] = ((uint32_t)min(row, rows_ok - 1) * (uint32_t)row_stride + (uint32_t)chunk * 8u) * 2u + PAIR_BIAS - (uint32_t)i * 1024u;
+        }
+    }
+    static __device__ __forceinline__ const char *pair_base(const bf16_t *first) { return reinterpret_cast<const char *>(first) - PAIR_BIAS; }
+    // off0 and off1 may be the same; base pointers (of pair_base()), `lds_tile` and `wave` must be wavefront-uniform
+    static __device__ __forceinline__ void issue_pair(const char *g0_uniform, const char *g1_uniform, const uint32_t (&off0)[NI],
                                                       const uint32_t (&off1)[NI], char *lds_tile, int wave)
     {
         static_assert(NI == 2 || NI == 4, "");
-        constexpr int STEP = WAVES * 1024;              // between two load instructions of one wavefront
-        const uint32_t lds_addr = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)(lds_tile + wave * 1024);
-        uint32_t saved;
+        const uint32_t lds0 = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)(lds_tile + wave * (NI * 1024));
+        const uint32_t lds1 = lds0 + BYTES;
         if constexpr (NI == 2) {
-            asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %2, %6\n\ts_add_u32 m0, m0, %8\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %3, %6\n\ts_add_u32 m0, m0, %8\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %4, %7\n\ts_add_u32 m0, m0, %8\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %5, %7\n\ts_mov_b32 m0, %0"
-                         : "=&s"(saved)
-                         : "s"(lds_addr), "v"(off0[0]), "v"(off0[1]), "v"(off1[0]), "v"(off1[1]), "s"(g0_uniform), "s"(g1_uniform), "i"(STEP)
-                         : "memory", "scc");
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %6\n\tglobal_load_lds_dwordx4 %3, %6 offset:1024\n\t"
+                         "s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %7\n\tglobal_load_lds_dwordx4 %5, %7 offset:1024"
+                         : : "s"(lds0), "s"(lds1), "v"(off0[0]), "v"(off0[1]), "v"(off1[0]), "v"(off1[1]), "s"(g0_uniform), "s"(g1_uniform) : "memory", "m0");
         } else {
-            asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %2, %10\n\ts_add_u32 m0, m0, %12\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %3, %10\n\ts_add_u32 m0, m0, %12\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %4, %10\n\ts_add_u32 m0, m0, %12\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %5, %10\n\ts_add_u32 m0, m0, %12\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %6, %11\n\ts_add_u32 m0, m0, %12\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %7, %11\n\ts_add_u32 m0, m0, %12\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %8, %11\n\ts_add_u32 m0, m0, %12\n\ts_nop 0\n\t"
-                         "global_load_lds_dwordx4 %9, %11\n\ts_mov_b32 m0, %0"
-                         : "=&s"(saved)
-                         : "s"(lds_addr), "v"(off0[0]), "v"(off0[1]), "v"(off0[2]), "v"(off0[3]), "v"(off1[0]), "v"(off1[1]), "v"(off1[2]),
-                           "v"(off1[3]), "s"(g0_uniform), "s"(g1_uniform), "i"(STEP)
-                         : "memory", "scc");
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %10\n\tglobal_load_lds_dwordx4 %3, %10 offset:1024\n\t"
+                         "global_load_lds_dwordx4 %4, %10 offset:2048\n\tglobal_load_lds_dwordx4 %5, %10 offset:3072\n\t"
+                         "s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %6, %11\n\tglobal_load_lds_dwordx4 %7, %11 offset:1024\n\t"
+                         "global_load_lds_dwordx4 %8, %11 offset:2048\n\tglobal_load_lds_dwordx4 %9, %11 offset:3072"
+                         : : "s"(lds0), "s"(lds1), "v"(off0[0]), "v"(off0[1]), "v"(off0[2]), "v"(off0[3]), "v"(off1[0]), "v"(off1[1]), "v"(off1[2]),
+                             "v"(off1[3]), "s"(g0_uniform), "s"(g1_uniform)
+                         : "memory", "m0");
         }
     }
     // byte offset inside the tile of the 16-byte chunk c of row r

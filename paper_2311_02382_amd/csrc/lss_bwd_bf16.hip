@@ -8,7 +8,12 @@
 //     2,464.  Loops on Gaussian bf16 (lss_microbench, section 7) do not show why: 1,700 against 1,630 TFLOP/s in registers, but 1,390
 //     either way with the backward's vector work in between, and 1,163 against 1,226 with an LDS read per 32,768 flop besides, as here;
 //   * 64-row tiles loaded global -> LDS directly into a ring of three unpadded, swizzled tiles, a
-//     full loop iteration ahead, one barrier per tile;
+//     full loop iteration ahead, one barrier per tile.  A ring of four, two iterations ahead, changed nothing;
+//   * as few scalar instructions per step as can be: beside matrix and vector work each costs a lone wavefront about 8 cycles
+//     (lss_microbench, section 3).  With tile addresses and ring slots that move on from iteration to iteration instead of being
+//     computed in each, one address register for the loads of a tile (DirectTile::issue_pair) and one compare for the masks a dK/dV
+//     iteration has 26 of them fewer, a dQ one 30, a forward one 27: forward and backward of 16 heads of 8,192 tokens in
+//     eight segments 953 -> 937 us, 64 of 24,576 in six 21.63 -> 21.16 ms, 32,768 keys at d = 128 2,347 -> 2,300;
 //   * row-major LDS tiles read transposed with DS_READ_B64_TR_B16 where the contraction runs over
 //     tile rows (K^T for dQ, Q^T and dO^T for dK and dV) -- no transposing stores;
 //   * lse, D = rowsum(dO * out) and the masks folded into accumulator start values where the
@@ -134,32 +139,43 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
         }
         char *const ck_ring = ring + C::RING * C::SLOT;
 
-        // ---- tile loads, by all wavefronts of the group.  Branch-free on purpose: a branch inside a pipeline step
-        // splits it into basic blocks, and the vector work that was meant to sit between the step's
-        // matrix instructions is then moved behind the branch in one lump.
-        uint32_t offF[Tile::NI], offD[Tile::NI];        // this lane's global offsets within a full tile; and what
-        Tile::offsets(offF, ld, C::BC, wave, lane);     // must be added to them in the sequence's last, partial tile
-        const int t_part = s.l_x % C::BC ? s.l_x / C::BC : -1;     // (rows past the end re-read the last row)
+        // ---- tile loads, by all wavefronts of the group.  No branch and few scalar instructions on purpose: a branch inside a
+        // pipeline step splits it into basic blocks, and the vector work that was meant to sit between the step's matrix
+        // instructions is then moved behind the branch in one lump; addresses move on between the iterations instead.
+        uint32_t off[Tile::NI], offD[Tile::NI];         // this lane's global offsets within a full tile; and what must be
+        Tile::pair_offsets(off, ld, C::BC, wave, lane); // added to them in the sequence's last, partial tile (rows past the end
+        const int t_part = s.l_x % C::BC ? s.l_x / C::BC : -1;     // re-read the last row)
         {
             uint32_t offL[Tile::NI];
-            Tile::offsets(offL, ld, t_part >= 0 ? s.l_x % C::BC : C::BC, wave, lane);
+            Tile::pair_offsets(offL, ld, t_part >= 0 ? s.l_x % C::BC : C::BC, wave, lane);
 #pragma unroll
-            for (int i = 0; i < Tile::NI; ++i) offD[i] = offL[i] - offF[i];
+            for (int i = 0; i < Tile::NI; ++i) offD[i] = offL[i] - off[i];
         }
         const uint32_t tile_bytes = (uint32_t)(C::BC * ld * 2);
-        auto issue_tile = [&](int t, int slot) {
-            const int j0 = t * C::BC;
-            const uint32_t part = t == t_part ? ~0u : 0u;
-            uint32_t off[Tile::NI];
+        // the next tile to load; past the group's last one that one again, into a slot that nobody reads any more
+        const int t_last = t_begin + max(T, 1) - 1;
+        int t_next = t_begin;
+        const char *k_next = tile_ptr(Tile::pair_base(kbase), t_begin, tile_bytes), *v_next = tile_ptr(Tile::pair_base(vbase), t_begin, tile_bytes);
+        auto to_part = [&] {
+            if (t_next == t_part)
 #pragma unroll
-            for (int i = 0; i < Tile::NI; ++i) off[i] = offF[i] + (offD[i] & part);
-            static_assert(C::OFF_V == Tile::BYTES, "V tile follows K tile");
-            Tile::issue_pair(tile_ptr(kbase, t, tile_bytes), tile_ptr(vbase, t, tile_bytes), off, off, ring + slot * C::SLOT, wave);
-            if (DROP && wave == 0)
-                reinterpret_cast<uint32_t *>(ck_ring)[(t & 3) * C::BC + lane] = drop_col_key(drop_cs, (uint32_t)(j0 + lane));
+                for (int i = 0; i < Tile::NI; ++i) off[i] += offD[i];
         };
-        // the loop's prefetch: tile t + 2, or once more the last tile into a slot nobody reads any more
-        auto issue_ahead = [&](int t, int slot) { issue_tile(t_begin + min(t + 2, T - 1), slot); };
+        to_part();
+        auto advance = [&] {
+            if (t_next < t_last) {
+                ++t_next;
+                k_next += tile_bytes;
+                v_next += tile_bytes;
+                to_part();
+            }
+        };
+        auto issue_next = [&](char *slot) __attribute__((always_inline)) {
+            static_assert(C::OFF_V == Tile::BYTES, "V tile follows K tile");
+            Tile::issue_pair(k_next, v_next, off, off, slot, wave);
+            if (DROP && wave == 0)
+                reinterpret_cast<uint32_t *>(ck_ring)[(t_next & 3) * C::BC + lane] = drop_col_key(drop_cs, (uint32_t)(t_next * C::BC + lane));
+        };
 
         // ---- per-lane LDS offsets (bytes, within a tile)
         int a_off[NU / 2];                              // A-operand chunk of row lq for operand step ks
@@ -211,10 +227,10 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
         // masked elements of its finished S^T are set to -inf before B, which turns them
         // into P = dS = 0: keys after the lane's row, and keys past the sequence (whose loads
         // re-read its last row).
+        // (positions are below 2^30, checked on the host: one 32-bit scalar compare, no vector work per step)
+        const int last_whole = min(s.causal ? (int)s.s0 + rw0 - 31 : s.l_x, s.l_x - 32);       // blocks from here on need no mask
         auto mask_s = [&](int jb, Block &sc) __attribute__((always_inline)) {
-            // (positions are below 2^30, checked on the host: 32-bit scalar compares, no vector work per step)
-            const bool diag = s.causal && (jb + 31 > (int)s.s0 + rw0);
-            if (diag || jb + 32 > s.l_x) {
+            if (jb > last_whole) {
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
                     const int last = s.causal ? min((int)s.s0 + rw0 + 16 * j + lq, s.l_x - 1) : s.l_x - 1;
@@ -307,21 +323,24 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
         using std::false_type;
 
         // ---- pipeline.  Block g = keys (t_begin + g/2) * 64 + (g%2) * 32 ..; tile t = blocks 2t, 2t+1.
-        if (T > 0) issue_tile(t_begin, 0);
-        if (T > 1) issue_tile(t_begin + 1, 1);
+        if (T > 0) issue_next(ring);
+        advance();
+        if (T > 1) issue_next(ring + C::SLOT);
+        advance();
         wait_vmem_all();
         __syncthreads();
 
         if (rw0 >= s.l_s) {
             // None of this wavefront's rows exists (a partly filled last query tile; half the workgroup for
             // a segment of at most 64 rows): it only keeps moving tiles and meeting the loop's barriers.
-            int cur = 0;
+            char *cur = ring, *nxt = ring + C::SLOT, *prv = ring + 2 * C::SLOT;
             for (int t = 0; t < T; ++t) {
-                const int prv = cur == 0 ? C::RING - 1 : cur - 1;
                 wait_vmem_all();
                 __syncthreads();
-                issue_ahead(t, prv);
-                cur = cur == C::RING - 1 ? 0 : cur + 1;
+                issue_next(prv);
+                advance();
+                char *const free = cur;
+                cur = nxt, nxt = prv, prv = free;
             }
         } else if (KG == 1 || T > 0) {
             Block sc0, dp0, sc1, dp1;                       // even / odd blocks
@@ -335,35 +354,31 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
     #pragma unroll
                 for (int e = 0; e < 8; ++e) df1[j].v[e] = (bf16_t)0.f;
 
-            int cur = 0;                                    // ring slot of tile t
+            // ring slots: of tile t, of the next, the one that takes the tile after that (tile t - 1's), the one C reads first (t = 0: any
+            // tile, times zero)
+            char *cur = ring, *nxt = ring + C::SLOT, *prv = ring + 2 * C::SLOT, *c_first = ring;
+            int j0 = t_begin * C::BC;
             for (int t = 0; t < T; ++t) {
-                const int nxt = cur == C::RING - 1 ? 0 : cur + 1, prv = cur == 0 ? C::RING - 1 : cur - 1;
-                const char *t_cur = ring + cur * C::SLOT, *t_nxt = ring + nxt * C::SLOT, *t_prv = ring + prv * C::SLOT;
-                const char *t_a2 = t + 1 < T ? t_nxt : t_cur;   // tile of A(2t+2), A(2t+3); past the end: any resident tile
-                const int j0 = (t_begin + t) * C::BC;
                 // even step g = 2t: A(2t+1) [tile t, second half], B(2t), C(2t-1) [tile t-1, second half;
                 // for t = 0 tile 0, times zero]
                 // Before its last reads (which may touch tile t+1): tile t+1's loads, issued one iteration
                 // ago, have landed for this wavefront; after the barrier for all, and every wavefront has
                 // requested its last operands from tile t-1, whose slot takes tile t+2.
-                step(true_type{}, true_type{}, true_type{}, t_cur, 1, sc1, dp1, sc0, dp0, j0, df0, t > 0 ? t_prv : t_cur, 1, df1,
-                     t_a2, 0, t_cur, 0, [&] {
-                         wait_vmem_all();
-                         __syncthreads();
-                         issue_ahead(t, prv);
-                     });
-                // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end result unused], B(2t+1),
-                // C(2t) [tile t, first half]
-                step(true_type{}, true_type{}, true_type{}, t_a2, 0, sc0, dp0, sc1, dp1, j0 + 32, df1, t_cur, 0, df0, t_a2, 1, t_cur,
-                     1, nothing);
-                cur = nxt;
+                step(true_type{}, true_type{}, true_type{}, cur, 1, sc1, dp1, sc0, dp0, j0, df0, c_first, 1, df1, nxt, 0, cur, 0, [&] {
+                    wait_vmem_all();
+                    __syncthreads();
+                    issue_next(prv);
+                });
+                // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end of whatever its slot holds, result unused],
+                // B(2t+1), C(2t) [tile t, first half]
+                step(true_type{}, true_type{}, true_type{}, nxt, 0, sc0, dp0, sc1, dp1, j0 + 32, df1, cur, 0, df0, nxt, 1, cur, 1, nothing);
+                advance();
+                c_first = cur;
+                cur = nxt, nxt = prv, prv = c_first;
+                j0 += C::BC;
             }
             // step 2T: C(2T-1) [tile T-1, second half] alone
-            {
-                const char *t_last = ring + (cur == 0 ? C::RING - 1 : cur - 1) * C::SLOT;
-                step(false_type{}, false_type{}, true_type{}, ring, 0, sc0, dp0, sc0, dp0, 0, df0, t_last, 1, df1, ring, 0, t_last,
-                     1, nothing);
-            }
+            step(false_type{}, false_type{}, true_type{}, ring, 0, sc0, dp0, sc0, dp0, 0, df0, c_first, 1, df1, ring, 0, c_first, 1, nothing);
         }
         if (KG > 1)
             for (int t = T; t < iters; ++t) __syncthreads();           // the barriers of the group that has more tiles
@@ -613,33 +628,52 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
 
     // ---- tile loads: all wavefronts of the group move Q and dO, and the 64 start values of either kind (even
     // wavefronts -lse*sqrt(d), odd ones -D; each several times, which is cheaper than a branch inside a pipeline
-    // step: a branch splits the step into basic blocks, and the vector work meant to sit between its
-    // matrix instructions is then moved behind the branch in one lump)
-    uint32_t offF[Tile::NI], offD[Tile::NI];            // this lane's global offsets within a full tile; and what
-    Tile::offsets(offF, ld, C::BQ, wave, lane);         // must be added to them in the segment's last, partial tile
-    const int tq_part = s.l_s % C::BQ ? s.l_s / C::BQ : -1;        // (rows past the end re-read the last row)
+    // step).  As in the dQ workgroups addresses move on between the iterations.
+    // (two groups: the first has `iters` tiles, the other one fewer or none; row_base: of the group's first row, from rq_begin)
+    const int all_tiles = (s.l_s - rq_begin + C::BQ - 1) / C::BQ, iters = (all_tiles + KG - 1) / KG;
+    const int T = KG > 1 ? min(all_tiles - group * iters, iters) : all_tiles, row_base = group * iters * C::BQ;
+    const int tq_begin = (rq_begin + row_base) / C::BQ;
+    uint32_t off[Tile::NI], offD[Tile::NI];             // this lane's global offsets within a full tile; and what must be
+    Tile::pair_offsets(off, ld, C::BQ, wave, lane);     // added to them in the segment's last, partial tile (rows past the end
+    const int tq_part = s.l_s % C::BQ ? s.l_s / C::BQ : -1;        // re-read the last row)
     {
         uint32_t offL[Tile::NI];
-        Tile::offsets(offL, ld, tq_part >= 0 ? s.l_s % C::BQ : C::BQ, wave, lane);
+        Tile::pair_offsets(offL, ld, tq_part >= 0 ? s.l_s % C::BQ : C::BQ, wave, lane);
 #pragma unroll
-        for (int i = 0; i < Tile::NI; ++i) offD[i] = offL[i] - offF[i];
+        for (int i = 0; i < Tile::NI; ++i) offD[i] = offL[i] - off[i];
     }
     const uint32_t tile_bytes = (uint32_t)(C::BQ * ld * 2);
     const float *const sv_base = (wave & 1) ? dbase : lbase;
-    const int sv_off = (wave & 1) ? C::OFF_D : C::OFF_L;
-    auto issue_tile = [&](int tq, int slot) {           // tile tq = query rows [64 tq, 64 tq + 64) of the segment
-        const int rq0 = tq * C::BQ;
-        const uint32_t part = tq == tq_part ? ~0u : 0u;
-        uint32_t off[Tile::NI];
+    const int sv_slot = (wave & 1) ? C::OFF_D : C::OFF_L;
+    // the next tile to load (tile tq: query rows [64 tq, 64 tq + 64) of the segment); past the group's last one that one again, into a
+    // slot that nobody reads any more.  (A second group without tiles loads nothing.)
+    const int tq_last = tq_begin + max(T, 1) - 1;
+    int tq_next = tq_begin;
+    const char *q_next = tile_ptr(Tile::pair_base(qbase), tq_begin, tile_bytes), *g_next = tile_ptr(Tile::pair_base(gbase), tq_begin, tile_bytes);
+    uint32_t sv_off = (uint32_t)(tq_begin * C::BQ + lane) * 4u;
+    const uint32_t sv_end = (uint32_t)(s.l_s - 1) * 4u;
+    auto to_part = [&] {
+        if (tq_next == tq_part)
 #pragma unroll
-        for (int i = 0; i < Tile::NI; ++i) off[i] = offF[i] + (offD[i] & part);
+            for (int i = 0; i < Tile::NI; ++i) off[i] += offD[i];
+    };
+    to_part();
+    auto advance = [&] {
+        if (tq_next < tq_last) {
+            ++tq_next;
+            q_next += tile_bytes;
+            g_next += tile_bytes;
+            sv_off += C::BQ * 4u;
+            to_part();
+        }
+    };
+    auto issue_next = [&](char *slot) __attribute__((always_inline)) {
         static_assert(C::OFF_G == Tile::BYTES, "dO tile follows Q tile");
-        char *dst = ring + slot * C::SLOT;
-        Tile::issue_pair(tile_ptr(qbase, tq, tile_bytes), tile_ptr(gbase, tq, tile_bytes), off, off, dst, wave);
+        Tile::issue_pair(q_next, g_next, off, off, slot, wave);
         if constexpr (!OWN) {
-            const uint32_t ro = (uint32_t)min(lane, s.l_s - rq0 - 1) * 4u;
-            lds_dma<4>(sv_base + rq0, ro, dst + sv_off);
-            if (DROP && wave == 2) lds_dma<4>(rbase + rq0, ro, dst + C::OFF_R);
+            const uint32_t so = min(sv_off, sv_end);
+            lds_dma<4>(sv_base, so, slot + sv_slot);
+            if (DROP && wave == 2) lds_dma<4>(rbase, so, slot + C::OFF_R);
         }
     };
 
@@ -683,9 +717,14 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     // the lane's key, and rows past the segment (whose loads re-read its last row).
     constexpr int NE = 8 * NJ;
     struct Block { f32x4 v[2][NJ]; };                   // [row block i][key block j]
+    // Blocks whose first row lies in [whole_from, whole_from + whole_span] need no mask (positions are below 2^30: one 32-bit scalar
+    // compare per step); where there is none, whole_from is out of every block's reach.
+    const int from = s.causal ? max(jw0 + C::KW - 1 - (int)s.s0, 0) : 0;
+    const int whole_from = from > s.l_s - 32 ? 0x7fffffff : from;
+    const uint32_t whole_span = from > s.l_s - 32 ? 0u : (uint32_t)(s.l_s - 32 - from);
     auto mask_s = [&](int r0, Block &sc) __attribute__((always_inline)) {
-        const bool diag = s.causal && (jw0 + C::KW - 1 > (int)s.s0 + r0);      // positions are below 2^30: 32-bit scalar compare
-        if (diag || r0 + 32 > s.l_s) {
+        if ((uint32_t)(r0 - whole_from) > whole_span) {
+            const bool diag = s.causal && (jw0 + C::KW - 1 > (int)s.s0 + r0);
             const int end = min(s.l_s - r0, 32) - 4 * g;
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
@@ -822,14 +861,10 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     using std::false_type;
 
     // ---- pipeline.  Block g of this workgroup = rows rq_begin + 32 g ..; tile t = blocks 2t, 2t+1.
-    // (two groups: the first has `iters` tiles, the other one fewer or none; row_base: of the group's first row, from rq_begin)
-    const int all_tiles = (s.l_s - rq_begin + C::BQ - 1) / C::BQ, iters = (all_tiles + KG - 1) / KG;
-    const int T = KG > 1 ? min(all_tiles - group * iters, iters) : all_tiles, row_base = group * iters * C::BQ;
-    const int tq_begin = (rq_begin + row_base) / C::BQ;
-    // the loop's prefetch: tile t + 2, or once more the last tile into a slot nobody reads any more
-    auto issue_ahead = [&](int t, int slot) { issue_tile(tq_begin + min(t + 2, T - 1), slot); };
-    if (KG == 1 || T > 0) issue_tile(tq_begin, 0);
-    if (T > 1) issue_tile(tq_begin + 1, 1);
+    if (KG == 1 || T > 0) issue_next(ring);
+    advance();
+    if (T > 1) issue_next(ring + C::SLOT);
+    advance();
     if constexpr (OWN) {
         float *const own = reinterpret_cast<float *>(own_values);
         const int n = s.l_s - rq_begin;
@@ -863,36 +898,35 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
 #pragma unroll
             for (int e = 0; e < 8; ++e) { pf1[j].v[e] = (bf16_t)0.f; df1[j].v[e] = (bf16_t)0.f; }
 
-        int cur = 0;                                    // ring slot of tile t
+        // ring slots: of tile t, of the next, the one that takes the tile after that (tile t - 1's), the one C reads first (t = 0: any
+        // tile, times zero)
+        char *cur = ring, *nxt = ring + C::SLOT, *prv = ring + 2 * C::SLOT, *c_first = ring;
+        int row = row_base, r0 = rq_begin + row_base;
 #pragma nounroll    // (unrolled, two groups' registers spill: 84 spills against none)
         for (int t = 0; t < T; ++t) {
-            const int nxt = cur == C::RING - 1 ? 0 : cur + 1, prv = cur == 0 ? C::RING - 1 : cur - 1;
-            const char *t_cur = ring + cur * C::SLOT, *t_nxt = ring + nxt * C::SLOT, *t_prv = ring + prv * C::SLOT;
-            const char *t_a2 = t + 1 < T ? t_nxt : t_cur;   // tile of A(2t+2) and A(2t+3); past the end: any resident tile
-            const int row = row_base + t * C::BQ, r0 = rq_begin + row;
             // even step g = 2t: A(2t+1) [tile t, second half], B(2t), C(2t-1) [tile t-1, second half;
             // for t = 0 tile 0, times zero]
             // Before its last requests (which may touch tile t+1): tile t+1's loads, issued one iteration
             // ago, have landed for this wavefront; after the barrier for all, and every wavefront has
             // requested its last operands from tile t-1, whose slot takes tile t+2.
-            step(true_type{}, true_type{}, true_type{}, t_cur, 1, sc1, dp1,
-                 start_values(t_cur, 0, row), r0, sc0, dp0, pf0, df0, t > 0 ? t_prv : t_cur, 1, pf1, df1, t_a2, 0, row + C::BQ,
-                 t_cur, 0, [&] {
+            step(true_type{}, true_type{}, true_type{}, cur, 1, sc1, dp1, start_values(cur, 0, row), r0, sc0, dp0, pf0, df0, c_first, 1, pf1,
+                 df1, nxt, 0, row + C::BQ, cur, 0, [&] {
                      wait_vmem_all();
                      __syncthreads();
-                     issue_ahead(t, prv);
+                     issue_next(prv);
                  });
-            // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end result unused], B(2t+1),
-            // C(2t) [tile t, first half]
-            step(true_type{}, true_type{}, true_type{}, t_a2, 0, sc0, dp0,
-                 start_values(t_cur, 1, row + 32), r0 + 32, sc1, dp1, pf1, df1, t_cur, 0, pf0, df0, t_a2, 1, row + C::BQ + 32, t_cur, 1,
-                 nothing);
-            cur = nxt;
+            // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end of whatever its slot holds, result unused],
+            // B(2t+1), C(2t) [tile t, first half]
+            step(true_type{}, true_type{}, true_type{}, nxt, 0, sc0, dp0, start_values(cur, 1, row + 32), r0 + 32, sc1, dp1, pf1, df1, cur, 0, pf0,
+                 df0, nxt, 1, row + C::BQ + 32, cur, 1, nothing);
+            advance();
+            c_first = cur;
+            cur = nxt, nxt = prv, prv = c_first;
+            row += C::BQ, r0 += C::BQ;
         }
         // step 2T: C(2T-1) [tile T-1, second half] alone
-        const char *t_last = ring + (cur == 0 ? C::RING - 1 : cur - 1) * C::SLOT;
-        step(false_type{}, false_type{}, true_type{}, ring, 0, sc0, dp0, ring, 0, sc0, dp0, pf0, df0, t_last, 1, pf1,
-             df1, ring, 0, 0, t_last, 1, nothing);
+        step(false_type{}, false_type{}, true_type{}, ring, 0, sc0, dp0, ring, 0, sc0, dp0, pf0, df0, c_first, 1, pf1,
+             df1, ring, 0, 0, c_first, 1, nothing);
     }
     if (KG > 1)
         for (int t = max(T, 0); t < iters; ++t) __syncthreads();       // the barriers of the group that has more tiles
@@ -958,10 +992,10 @@ __device__ __forceinline__ void bwd_dkv_skinny_body(char *smem, const SegShape &
     // ---- the segment's Q/dO tile and start values (slot 0), by all four wavefronts
     if (kt0 < kt_vis) {
         uint32_t off[Tile::NI];
-        Tile::offsets(off, ld, s.l_s, wave, lane);
+        Tile::pair_offsets(off, ld, s.l_s, wave, lane);
         const bf16_t *qbase = q + (int64_t)b * s.l_s * ld + (int64_t)h * D;
         const bf16_t *gbase = dO + (int64_t)b * s.l_s * ld + (int64_t)h * D;
-        Tile::issue_pair(qbase, gbase, off, off, smem, wave);
+        Tile::issue_pair(Tile::pair_base(qbase), Tile::pair_base(gbase), off, off, smem, wave);
     }
     auto load_kv = [&](int kt, Frag<bf16_t> (&kf)[NU], Frag<bf16_t> (&vf)[NU]) __attribute__((always_inline)) {
         const int jj = kt * C::BKV + wave * C::KW + lq;

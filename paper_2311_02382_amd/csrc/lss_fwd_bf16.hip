@@ -117,41 +117,45 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
         if (DROP) { drop_rk = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + r)); drop_cs = drop_col_seed(dr.seed_hi); }
         char *const ck_ring = ring + C::RING;
 
-        // ---- tile loads, by all wavefronts of the group.  Branch-free on purpose: a branch inside a pipeline step
-        // splits it into basic blocks, and the vector work that was meant to sit between the step's
-        // matrix instructions is then moved behind the branch in one lump.
-        uint32_t offF[Tile::NI], offD[Tile::NI];        // this lane's global offsets within a full tile; and what
-        Tile::offsets(offF, ld, C::BC, wave, lane);     // must be added to them in the sequence's last, partial tile
-        const int t_part = s.l_x % C::BC ? s.l_x / C::BC : -1;     // (rows past the end re-read the last row)
+        // ---- tile loads, by all wavefronts of the group.  No branch and few scalar instructions on purpose: a branch inside a
+        // pipeline step splits it into basic blocks, and the vector work that was meant to sit between the step's matrix
+        // instructions is then moved behind the branch in one lump; addresses move on between the iterations instead.
+        uint32_t offK[Tile::NI], offV[Tile::NI], offD[Tile::NI];    // this lane's global offsets within the next K and V tile; and
+        Tile::pair_offsets(offK, ld, C::BC, wave, lane);            // what must be added to them in the sequence's last, partial
+        const int t_part = s.l_x % C::BC ? s.l_x / C::BC : -1;     // tile (rows past the end re-read the last row)
         {
             uint32_t offL[Tile::NI];
-            Tile::offsets(offL, ld, t_part >= 0 ? s.l_x % C::BC : C::BC, wave, lane);
+            Tile::pair_offsets(offL, ld, t_part >= 0 ? s.l_x % C::BC : C::BC, wave, lane);
 #pragma unroll
-            for (int i = 0; i < Tile::NI; ++i) offD[i] = offL[i] - offF[i];
+            for (int i = 0; i < Tile::NI; ++i) { offD[i] = offL[i] - offK[i]; offV[i] = offK[i]; }
         }
         const uint32_t tile_bytes = (uint32_t)(C::BC * ld * 2);
-        auto tile_off = [&](int t, uint32_t (&off)[Tile::NI]) __attribute__((always_inline)) {
-            const uint32_t part = t == t_part ? ~0u : 0u;
+        // the next tile of K to load, and of V, one behind; past the group's last one that one again
+        const int t_last = t_begin + max(T, 1) - 1;
+        int k_tile_next = t_begin, v_tile_next = t_begin;
+        const char *k_next = tile_ptr(Tile::pair_base(kbase), t_begin, tile_bytes), *v_next = tile_ptr(Tile::pair_base(vbase), t_begin, tile_bytes);
+        auto to_part = [&](int t, uint32_t (&off)[Tile::NI]) __attribute__((always_inline)) {
+            if (t == t_part)
 #pragma unroll
-            for (int i = 0; i < Tile::NI; ++i) off[i] = offF[i] + (offD[i] & part);
+                for (int i = 0; i < Tile::NI; ++i) off[i] += offD[i];
         };
-        // K of tile tk and V of tile tv (counted from t_begin on, the last one again past the end) into pair slot `slot`
-        auto issue = [&](int tk, int tv, int slot) __attribute__((always_inline)) {
-            const int gk = t_begin + min(tk, T - 1), gv = t_begin + min(tv, T - 1);
-            uint32_t offK[Tile::NI], offV[Tile::NI];
-            tile_off(gk, offK);
-            tile_off(gv, offV);
-            static_assert(C::OFF_V == Tile::BYTES, "V tile follows K tile");
-            Tile::issue_pair(tile_ptr(kbase, gk, tile_bytes), tile_ptr(vbase, gv, tile_bytes), offK, offV, ring + slot * C::PAIR, wave);
-            if (DROP && wave == 0)
-                reinterpret_cast<uint32_t *>(ck_ring)[(gk & 3) * C::BC + lane] = drop_col_key(drop_cs, (uint32_t)(gk * C::BC + lane));
+        to_part(k_tile_next, offK);
+        to_part(v_tile_next, offV);
+        auto advance_k = [&] {
+            if (k_tile_next < t_last) { ++k_tile_next; k_next += tile_bytes; to_part(k_tile_next, offK); }
         };
-        auto k_tile = [&](int t) { return ring + (t & 1) * C::PAIR; };
-        auto v_tile = [&](int t) { return ring + ((t & 1) ^ 1) * C::PAIR + C::OFF_V; };
+        auto advance_v = [&] {
+            if (v_tile_next < t_last) { ++v_tile_next; v_next += tile_bytes; to_part(v_tile_next, offV); }
+        };
         // Iteration t's loads, behind its barrier: K of tile t + 2 in the place of tile t's, whose last rows have been read
         // by then, and V of tile t + 1 in the place of tile t - 1's.  (Past the end a tile is loaded once more: K where it
         // lies already or where nobody reads any more, V where nobody reads any more.)
-        auto issue_ahead = [&](int t) __attribute__((always_inline)) { issue(t + 2, t + 1, t & 1); };
+        auto issue_next = [&](char *pair_slot) __attribute__((always_inline)) {
+            static_assert(C::OFF_V == Tile::BYTES, "V tile follows K tile");
+            Tile::issue_pair(k_next, v_next, offK, offV, pair_slot, wave);
+            if (DROP && wave == 0)
+                reinterpret_cast<uint32_t *>(ck_ring)[(k_tile_next & 3) * C::BC + lane] = drop_col_key(drop_cs, (uint32_t)(k_tile_next * C::BC + lane));
+        };
 
         // ---- per-lane LDS offsets (bytes, within a tile)
         int a_off[NU];                                  // A-operand chunk of row lq for operand step kb
@@ -173,10 +177,10 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
         // masked elements of its finished S^T accumulator are set to -inf, which B turns into weight
         // 0: keys after the lane's row, and keys past the sequence (whose loads re-read its last
         // row).  C-tile element e of this lane is key 8*(e/4) + 4*hh + e%4 of the block.
+        // (positions are below 2^30, checked on the host: one 32-bit scalar compare, no vector work per step)
+        const int last_whole = min(s.causal ? (int)s.s0 + rw0 - 31 : s.l_x, s.l_x - 32);       // blocks from here on need no mask
         auto mask_s = [&](int jb, f32x16 &sc) __attribute__((always_inline)) {
-            // (positions are below 2^30, checked on the host: 32-bit scalar compares, no vector work per step)
-            const bool diag = s.causal && (jb + 31 > (int)s.s0 + rw0);
-            if (diag || jb + 32 > s.l_x) {
+            if (jb > last_whole) {
                 const int last = s.causal ? min((int)s.s0 + r, s.l_x - 1) : s.l_x - 1;
                 const int rel = max(min(last - jb - 4 * hh, 64), -1);
 #pragma unroll
@@ -291,8 +295,11 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
 
         // ---- pipeline.  Block g = keys (t_begin + g/2) * 64 + (g%2) * 32 ..; tile t = blocks 2t, 2t+1.
         if (T > 0) {
-            issue(0, 0, 0);                             // (K of tile 0; its V here is overwritten before anybody reads it)
-            issue(1, 0, 1);
+            issue_next(ring);                           // (K of tile 0; its V here is overwritten before anybody reads it)
+            advance_k();
+            issue_next(ring + C::PAIR);
+            advance_k();
+            advance_v();
         }
         wait_vmem_all();
         __syncthreads();
@@ -303,40 +310,47 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
             for (int t = 0; t < T; ++t) {
                 wait_vmem_all();
                 __syncthreads();
-                issue_ahead(t);
+                issue_next(ring + (t & 1) * C::PAIR);
+                advance_k();
+                advance_v();
             }
         } else if (T > 0) {
             f32x16 sc0, sc1;                            // even / odd blocks
             Frag<bf16_t> pf0[2], pf1[2];
             // step -1: A(0) alone.  The first loop step has no C(-1): it multiplies zeros with tile 0 instead.
-            load_a(k_tile(0), 0, 0, ak[0]);
+            // pair slots: K of tile t and V of tile t - 1 (at first of tile 0 too), K of t + 1 and V of t
+            char *even = ring, *odd = ring + C::PAIR;
+            load_a(even, 0, 0, ak[0]);
             auto nothing = [] {};
-            step(true_type{}, false_type{}, false_type{}, k_tile(0), 0, sc0, sc1, 0, pf0, v_tile(0), 0, pf1, k_tile(0), 1, v_tile(0), 1, nothing);
+            step(true_type{}, false_type{}, false_type{}, even, 0, sc0, sc1, 0, pf0, odd + C::OFF_V, 0, pf1, even, 1, odd + C::OFF_V, 1, nothing);
 #pragma unroll
             for (int half = 0; half < 2; ++half)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) pf1[half].v[e] = (bf16_t)0.f;
 
+            int j0 = t_begin * C::BC;
             for (int t = 0; t < T; ++t) {
-                const char *k_cur = k_tile(t), *k_nxt = t + 1 < T ? k_tile(t + 1) : k_cur;     // past the end: any resident tile
-                const char *v_cur = v_tile(t), *v_prv = t > 0 ? v_tile(t - 1) : v_cur;
-                const int j0 = (t_begin + t) * C::BC;
                 // even step g = 2t: A(2t+1) [tile t, second half], B(2t), C(2t-1) [tile t-1, second half;
-                // for t = 0 tile 0, times zero]
+                // for t = 0 V of tile 0, which lies in both slots, times zero]
                 // Before its last reads (which may touch tile t+1): K of tile t+1 and V of tile t, issued one iteration
                 // ago, have landed for this wavefront; after the barrier for all, and every wavefront has
                 // requested its last operands from K of tile t and V of tile t-1.
-                step(true_type{}, true_type{}, true_type{}, k_cur, 1, sc1, sc0, j0, pf0, v_prv, 1, pf1, k_nxt, 0, v_cur, 0, [&] {
+                step(true_type{}, true_type{}, true_type{}, even, 1, sc1, sc0, j0, pf0, even + C::OFF_V, 1, pf1, odd, 0, odd + C::OFF_V, 0, [&] {
                     wait_vmem_all();
                     __syncthreads();
-                    issue_ahead(t);
+                    issue_next(even);
                 });
-                // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end result unused], B(2t+1),
-                // C(2t) [tile t, first half]
-                step(true_type{}, true_type{}, true_type{}, k_nxt, 0, sc0, sc1, j0 + 32, pf1, v_cur, 0, pf0, k_nxt, 1, v_cur, 1, nothing);
+                // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end of whatever its slot holds, result unused],
+                // B(2t+1), C(2t) [tile t, first half]
+                step(true_type{}, true_type{}, true_type{}, odd, 0, sc0, sc1, j0 + 32, pf1, odd + C::OFF_V, 0, pf0, odd, 1, odd + C::OFF_V, 1, nothing);
+                advance_k();
+                advance_v();
+                char *const used = even;
+                even = odd, odd = used;
+                j0 += C::BC;
             }
             // step 2T: C(2T-1) [tile T-1, second half] alone
-            step(false_type{}, false_type{}, true_type{}, ring, 0, sc0, sc0, 0, pf0, v_tile(T - 1), 1, pf1, ring, 0, v_tile(T - 1), 1, nothing);
+            step(false_type{}, false_type{}, true_type{}, ring, 0, sc0, sc0, 0, pf0, even + C::OFF_V, 1, pf1, ring, 0, even + C::OFF_V, 1, nothing);
         }
         if (KG > 1)
             for (int t = T; t < iters; ++t) __syncthreads();           // the barriers of the groups that have more tiles
