@@ -15,20 +15,14 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 // Completion is counted like any vector-memory load (wait_vmem_all(), then a barrier, before any
 // wavefront reads the data).  Written as inline assembly on purpose: through the compiler builtin
 // every later LDS read that the compiler cannot prove disjoint would wait for the load at once,
-// which defeats loading a ring slot a whole loop iteration ahead.  M0 (the LDS address register of
-// the instruction) is saved and restored.
+// which defeats loading a ring slot a whole loop iteration ahead.
 template <int BYTES>
 __device__ __forceinline__ void lds_dma(const void *g_uniform, uint32_t voff, const void *lds_uniform)
 {
     static_assert(BYTES == 4 || BYTES == 16, "");
     const uint32_t lds_addr = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)lds_uniform;
-    uint32_t saved;
-    if (BYTES == 16)
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
-                     : "=&s"(saved) : "s"(lds_addr), "v"(voff), "s"(g_uniform) : "memory");
-    else
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %2, %3\n\ts_mov_b32 m0, %0"
-                     : "=&s"(saved) : "s"(lds_addr), "v"(voff), "s"(g_uniform) : "memory");
+    if (BYTES == 16) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(g_uniform) : "memory", "m0");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds_addr), "v"(voff), "s"(g_uniform) : "memory", "m0");
 }
 
 // N loads of 16 bytes per lane like lds_dma<16>, all from one wavefront-uniform base, load i to lds_uniform + i * STEP
@@ -161,18 +155,23 @@ struct DirectTile {
 // offset for that column block (tr_lane_offset_sw), `row0` a multiple of 16.  Over the two reads
 // the lane receives, for tile column (lane % 32), the 8 rows 8*a + 4*(lane/32) + t (a = 0, 1;
 // t = 0..3) -- exactly the rows that slots 4*a + t of a C-tile half carry (see lss_common.h).
+// The second read's rows lie 8 further down: chunk position ^ 3.
 template <int D>
-__device__ __forceinline__ Frag<bf16_t> load_frag_tr_sw(const char *tile, int row0, int lane_off)
+__device__ __forceinline__ Frag<bf16_t> load_frag_tr_sw(const char *tile, int row0, int lane_off, int lane_off_8)
 {
-    // the second read's rows lie 8 further down: chunk position ^ 3
     const char *p = tile + row0 * (D * 2) + lane_off;
-    const char *p8 = tile + row0 * (D * 2) + (lane_off ^ 48) + 8 * (D * 2);
+    const char *p8 = tile + row0 * (D * 2) + lane_off_8 + 8 * (D * 2);
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
     const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p8));
     const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     Frag<bf16_t> f;
     f.v = __builtin_bit_cast(bf16x8, both);
     return f;
+}
+template <int D>
+__device__ __forceinline__ Frag<bf16_t> load_frag_tr_sw(const char *tile, int row0, int lane_off)
+{
+    return load_frag_tr_sw<D>(tile, row0, lane_off, lane_off ^ 48);
 }
 // Byte offset for load_frag_tr_sw, columns [32 db, 32 db + 32): within its group of 16 lanes, lane
 // s addresses row 4*hh + s/4 (+ row0, a multiple of 16, which does not change the permutation; + 8 for the
@@ -227,6 +226,9 @@ __device__ __forceinline__ void wait_vmem()
     asm volatile("s_waitcnt vmcnt(%0)" :: "i"(N) : "memory");       // (also keeps the compiler from moving stores past it)
 }
 __device__ __forceinline__ void wait_vmem_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0), others untouched
+// at most N of the LDS reads (and scalar loads) on their way
+template <int N>
+__device__ __forceinline__ void wait_lds() { static_assert(N >= 0 && N < 16, ""); __builtin_amdgcn_s_waitcnt(0xC07F | N << 8); }
 __device__ __forceinline__ void wait_lds_reads() { __builtin_amdgcn_s_waitcnt(0xC07F); }  // lgkmcnt(0), others untouched
 
 // 4 floats -> 4 bf16 (round to nearest even), as one 8-byte value

@@ -13,7 +13,9 @@
 //     (lss_microbench, section 3).  With tile addresses and ring slots that move on from iteration to iteration instead of being
 //     computed in each, one address register for the loads of a tile (DirectTile::issue_pair) and one compare for the masks a dK/dV
 //     iteration has 26 of them fewer, a dQ one 30, a forward one 27: forward and backward of 16 heads of 8,192 tokens in
-//     eight segments 953 -> 937 us, 64 of 24,576 in six 21.63 -> 21.16 ms, 32,768 keys at d = 128 2,347 -> 2,300;
+//     eight segments 953 -> 937 us, 64 of 24,576 in six 21.63 -> 21.16 ms, 32,768 keys at d = 128 2,347 -> 2,300.  With LDS addresses that
+//     move on likewise, one wait for a unit's LDS reads instead of three or four and the vector work spread evenly (b_elems) 931 -> 907 us,
+//     21.38 -> 20.68 ms, 2,311 -> 2,240;
 //   * row-major LDS tiles read transposed with DS_READ_B64_TR_B16 where the contraction runs over
 //     tile rows (K^T for dQ, Q^T and dO^T for dK and dV) -- no transposing stores;
 //   * lse, D = rowsum(dO * out) and the masks folded into accumulator start values where the
@@ -177,33 +179,36 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
                 reinterpret_cast<uint32_t *>(ck_ring)[(t_next & 3) * C::BC + lane] = drop_col_key(drop_cs, (uint32_t)(t_next * C::BC + lane));
         };
 
-        // ---- per-lane LDS offsets (bytes, within a tile)
-        int a_off[NU / 2];                              // A-operand chunk of row lq for operand step ks
+        // ---- this lane's LDS addresses (bytes from smem) in the tile that A and in the one that C reads next; they move to the
+        // next tile once per iteration (one vector addition each, not one per use)
+        const int ring_at = group * C::group_lds(DROP);
+        int a_at[NU / 2];                               // A-operand chunk of row lq for operand step ks
 #pragma unroll
-        for (int ks = 0; ks < NU / 2; ++ks) a_off[ks] = Tile::chunk_offset(lq, 4 * ks + g);
-        int t_off[NU];                                  // transposed reads, column block db
+        for (int ks = 0; ks < NU / 2; ++ks) a_at[ks] = ring_at + Tile::chunk_offset(lq, 4 * ks + g);
+        int t_at[NU];                                   // transposed reads, column block db
 #pragma unroll
-        for (int db = 0; db < NU; ++db) t_off[db] = tr16_lane_offset_sw<D>(lane, db);
+        for (int db = 0; db < NU; ++db) t_at[db] = ring_at + tr16_lane_offset_sw<D>(lane, db);
 
-        // ---- stage pieces.  `tile` / `kb2` name a block of 32 keys: LDS address of its ring slot and which half of it.
+        // ---- stage pieces.  `kb2`: which half of the tile, a block of 32 keys.
         // Unit u: A operands of key block u % 2, operand step u / 2; C operand of column block u.
-        auto load_a = [&](const char *tile, int kb2, int u, Frag<bf16_t> &fk, Frag<bf16_t> &fv) __attribute__((always_inline)) {
-            const char *p = tile + (kb2 * 32 + u % 2 * 16) * (D * 2) + a_off[u / 2];
+        auto load_a = [&](int kb2, int u, Frag<bf16_t> &fk, Frag<bf16_t> &fv) __attribute__((always_inline)) {
+            const char *p = smem + a_at[u / 2] + (kb2 * 32 + u % 2 * 16) * (D * 2);
             fk = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(p));
             fv = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(p + C::OFF_V));
         };
-        auto load_c = [&](const char *tile, int kb2, int u, Frag<bf16_t> &fk) __attribute__((always_inline)) {
-            fk = load_frag_tr16_sw<D>(tile, kb2 * 32, t_off[u]);
+        auto load_c = [&](int kb2, int u, Frag<bf16_t> &fk) __attribute__((always_inline)) {
+            fk = load_frag_tr16_sw<D>(smem, kb2 * 32, t_at[u]);
         };
-        // B for elements [e0, e1), element e = (i, j, v) = (e / (4 NJ), e / 4 % NJ, e % 4): P = 2^(c * S - lse * log2 e), dS = P * (dP - D);
+        // B for halves [h0, h1) of elements, element e = (i, j, v) = (e / (4 NJ), e / 4 % NJ, e % 4): P = 2^(c * S - lse * log2 e), dS = P * (dP - D);
         // finished pairs are rounded to bf16 into the operand fragments of C: slots 4 i + v of row block j
-        // An element's exponential and the multiply that consumes it are issued one element apart (the
-        // multiply of element e - 1 follows the exponential of element e): a transcendental's result may not
-        // be read by the very next instruction, and the slot that would otherwise idle is not free.
+        // Nothing reads the result of the instruction before it, least of all a transcendental's: an exponent is made one element ahead of
+        // its exponential, which the multiply that consumes it follows one element behind.  Half an element's work at a time -- even h:
+        // exponential of element h / 2 and exponent of the next, odd h: the rest of the element before -- so that every
+        // matrix instruction has some of it beside it and no two stand back to back, where the second's issue waits for the first.
         constexpr int NE = 8 * NJ;
         struct Block { f32x4 v[2][NJ]; };               // [key block i][row block j]: element v of this lane is key 16 i + 4 g + v
         u32x4 ck4;      // dropout: the column keys of four consecutive keys, read when the first is due
-        auto b_elems = [&](Block &sc, Block &dp, int jb, int e0, int e1, Frag<bf16_t> (&df)[NJ]) __attribute__((always_inline)) {
+        auto b_elems = [&](Block &sc, Block &dp, int jb, int h0, int h1, Frag<bf16_t> (&df)[NJ]) __attribute__((always_inline)) {
             auto finish = [&](int e) __attribute__((always_inline)) {       // sc holds P by now
                 const int i = e / (4 * NJ), j = e / 4 % NJ, v = e & 3;
                 f32x4 &d4 = dp.v[i][j];
@@ -216,11 +221,18 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
                 if (v & 1) { df[j].v[4 * i + v - 1] = (bf16_t)d4[v - 1]; df[j].v[4 * i + v] = (bf16_t)d4[v]; }
             };
 #pragma unroll
-            for (int e = e0; e < e1; ++e) {
-                f32x4 &p4 = sc.v[e / (4 * NJ)][e / 4 % NJ];
-                p4[e & 3] = fast_exp2(p4[e & 3] * c - L2[e / 4 % NJ]);
-                if (e > 0) finish(e - 1);
-                if (e == NE - 1) finish(e);
+            for (int h = h0; h < h1; ++h) {
+                const int e = h / 2, n = e + 1;
+                if (h % 2 == 0) {
+                    f32x4 &p4 = sc.v[e / (4 * NJ)][e / 4 % NJ], &n4 = sc.v[n / (4 * NJ) % 2][n / 4 % NJ];
+                    if (e == 0) p4[0] = p4[0] * c - L2[0];
+                    const float next = n < NE ? n4[n & 3] * c - L2[n / 4 % NJ] : 0.f;
+                    p4[e & 3] = fast_exp2(p4[e & 3]);
+                    if (n < NE) n4[n & 3] = next;
+                } else {
+                    if (e > 0) finish(e - 1);
+                    if (n == NE) finish(e);
+                }
             }
         };
         // Where the causal diagonal or the end of the sequence crosses a block (first key jb), the
@@ -244,28 +256,26 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
             }
         };
 
-        // One pipeline step.  A: block (tile_a, kb2_a) into (sc_a, dp_a).  B: (sc_b, dp_b), first key
-        // jb_b, packing into df_b.  C: block (tile_c, kb2_c) from df_c into acc.  Per unit NJ matrix
+        // One pipeline step.  A: half kb2_a of its tile into (sc_a, dp_a).  B: (sc_b, dp_b), first key
+        // jb_b, packing into df_b.  C: half kb2_c of its tile from df_c into acc.  Per unit NJ matrix
         // instructions of C and 2 NJ of A (A first in the last unit); after each one come the B elements that fall to its slot.
         // Operand fragments are read from LDS one unit ahead of their use; those of the first unit
         // by the step before (ak[0], av[0], ck[0] on entry), and this step leaves there those of
-        // the next step: A on block (tile_an, kb2_an), C on (tile_cn, kb2_cn).  `mid` runs before
-        // those last reads: the even steps put the loop's barrier there, because the next step's
-        // blocks may lie in the tile that the barrier publishes.
+        // the next step: halves kb2_an and kb2_cn.  `mid` runs before those last reads: the even steps put the loop's barrier
+        // there, because the next step's blocks may lie in the tile that the barrier publishes, and move the addresses on.
         Frag<bf16_t> ak[2], av[2], ck[2];
-        auto step = [&](auto has_a, auto has_b, auto has_c, const char *tile_a, int kb2_a, Block &sc_a, Block &dp_a,
-                        Block &sc_b, Block &dp_b, int jb_b, Frag<bf16_t> (&df_b)[NJ], const char *tile_c, int kb2_c,
-                        Frag<bf16_t> (&df_c)[NJ], const char *tile_an, int kb2_an, const char *tile_cn, int kb2_cn, auto &&mid)
+        auto step = [&](auto has_a, auto has_b, auto has_c, int kb2_a, Block &sc_a, Block &dp_a, Block &sc_b, Block &dp_b,
+                        int jb_b, Frag<bf16_t> (&df_b)[NJ], int kb2_c, Frag<bf16_t> (&df_c)[NJ], int kb2_an, int kb2_cn, auto &&mid)
             __attribute__((always_inline)) {
             constexpr bool HA = decltype(has_a)::value, HB = decltype(has_b)::value, HC = decltype(has_c)::value;
             constexpr int PU = 3 * NJ, NS = PU * NU;    // slots per unit and in all; the elements of B spread over them
             static_assert(NU % 2 == 0, "fragment double buffers assume an even number of units");
             auto b_slot = [&](int slot) __attribute__((always_inline)) {
                 if (HB) {
-                    const int e0 = slot * NE / NS, e1 = (slot + 1) * NE / NS;
-                    if (e0 == e1) return;
+                    const int h0 = slot * 2 * NE / NS, h1 = (slot + 1) * 2 * NE / NS;
+                    if (h0 == h1) return;
                     __builtin_amdgcn_sched_barrier(0);
-                    b_elems(sc_b, dp_b, jb_b, e0, e1, df_b);
+                    b_elems(sc_b, dp_b, jb_b, h0, h1, df_b);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             };
@@ -299,8 +309,10 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
                 if (u + 1 < NU) {
-                    if (HC) load_c(tile_c, kb2_c, u + 1, ck[(u + 1) & 1]);
-                    if (HA) load_a(tile_a, kb2_a, u + 1, ak[(u + 1) & 1], av[(u + 1) & 1]);
+                    if (HC) load_c(kb2_c, u + 1, ck[(u + 1) & 1]);
+                    if (HA) load_a(kb2_a, u + 1, ak[(u + 1) & 1], av[(u + 1) & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    wait_lds<(HC ? 2 : 0) + (HA ? 2 : 0)>();        // this unit's are there (one wait, not one per fragment)
                     __builtin_amdgcn_sched_barrier(0);
                     do_c(u, PU * u);
                     do_a(u, PU * u + NJ);
@@ -308,8 +320,8 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
                     // last unit: A first, so that its results are there when the next step's B wants them
                     do_a(u, PU * u);
                     mid();
-                    load_c(tile_cn, kb2_cn, 0, ck[0]);
-                    load_a(tile_an, kb2_an, 0, ak[0], av[0]);
+                    load_c(kb2_cn, 0, ck[0]);
+                    load_a(kb2_an, 0, ak[0], av[0]);
                     __builtin_amdgcn_sched_barrier(0);
                     do_c(u, PU * u + 2 * NJ);
                 }
@@ -346,17 +358,16 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
             Block sc0, dp0, sc1, dp1;                       // even / odd blocks
             Frag<bf16_t> df0[NJ], df1[NJ];
             // step -1: A(0) alone.  The first loop step has no C(-1): it multiplies zeros with tile 0 instead.
-            load_a(ring, 0, 0, ak[0], av[0]);
+            load_a(0, 0, ak[0], av[0]);
             auto nothing = [] {};
-            step(true_type{}, false_type{}, false_type{}, ring, 0, sc0, dp0, sc1, dp1, 0, df0, ring, 0, df1, ring, 1, ring, 1, nothing);
+            step(true_type{}, false_type{}, false_type{}, 0, sc0, dp0, sc1, dp1, 0, df0, 0, df1, 1, 1, nothing);
     #pragma unroll
             for (int j = 0; j < NJ; ++j)
     #pragma unroll
                 for (int e = 0; e < 8; ++e) df1[j].v[e] = (bf16_t)0.f;
 
-            // ring slots: of tile t, of the next, the one that takes the tile after that (tile t - 1's), the one C reads first (t = 0: any
-            // tile, times zero)
-            char *cur = ring, *nxt = ring + C::SLOT, *prv = ring + 2 * C::SLOT, *c_first = ring;
+            // ring slots (bytes): of tile t, of the next, the one that takes the tile after that (tile t - 1's); C's way to tile t
+            int cur = 0, nxt = C::SLOT, prv = 2 * C::SLOT, c_step = 0;
             int j0 = t_begin * C::BC;
             for (int t = 0; t < T; ++t) {
                 // even step g = 2t: A(2t+1) [tile t, second half], B(2t), C(2t-1) [tile t-1, second half;
@@ -364,21 +375,26 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
                 // Before its last reads (which may touch tile t+1): tile t+1's loads, issued one iteration
                 // ago, have landed for this wavefront; after the barrier for all, and every wavefront has
                 // requested its last operands from tile t-1, whose slot takes tile t+2.
-                step(true_type{}, true_type{}, true_type{}, cur, 1, sc1, dp1, sc0, dp0, j0, df0, c_first, 1, df1, nxt, 0, cur, 0, [&] {
+                step(true_type{}, true_type{}, true_type{}, 1, sc1, dp1, sc0, dp0, j0, df0, 1, df1, 0, 0, [&] {
                     wait_vmem_all();
                     __syncthreads();
-                    issue_next(prv);
+                    issue_next(ring + prv);
+#pragma unroll
+                    for (int ks = 0; ks < NU / 2; ++ks) a_at[ks] += nxt - cur;
+#pragma unroll
+                    for (int db = 0; db < NU; ++db) t_at[db] += c_step;
                 });
                 // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end of whatever its slot holds, result unused],
                 // B(2t+1), C(2t) [tile t, first half]
-                step(true_type{}, true_type{}, true_type{}, nxt, 0, sc0, dp0, sc1, dp1, j0 + 32, df1, cur, 0, df0, nxt, 1, cur, 1, nothing);
+                step(true_type{}, true_type{}, true_type{}, 0, sc0, dp0, sc1, dp1, j0 + 32, df1, 0, df0, 1, 1, nothing);
                 advance();
-                c_first = cur;
-                cur = nxt, nxt = prv, prv = c_first;
+                c_step = nxt - cur;
+                const int used = cur;
+                cur = nxt, nxt = prv, prv = used;
                 j0 += C::BC;
             }
             // step 2T: C(2T-1) [tile T-1, second half] alone
-            step(false_type{}, false_type{}, true_type{}, ring, 0, sc0, dp0, sc0, dp0, 0, df0, c_first, 1, df1, ring, 0, c_first, 1, nothing);
+            step(false_type{}, false_type{}, true_type{}, 0, sc0, dp0, sc0, dp0, 0, df0, 1, df1, 0, 1, nothing);
         }
         if (KG > 1)
             for (int t = T; t < iters; ++t) __syncthreads();           // the barriers of the group that has more tiles
@@ -677,35 +693,36 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         }
     };
 
-    // ---- per-lane LDS offsets (bytes, within a tile)
-    int a_off[NU / 2];                                  // A-operand chunk of row lk for operand step ks
+    // ---- this lane's LDS addresses (bytes from smem) in the tile that A and in the one that C reads next; they move to the
+    // next tile once per iteration (one vector addition each, not one per use)
+    const int ring_at = group * (C::RING * C::SLOT);
+    int a_at[NU / 2];                                   // A-operand chunk of row lk for operand step ks
 #pragma unroll
-    for (int ks = 0; ks < NU / 2; ++ks) a_off[ks] = Tile::chunk_offset(lk, 4 * ks + g);
-    int t_off[NU];                                      // transposed reads, column block db
+    for (int ks = 0; ks < NU / 2; ++ks) a_at[ks] = ring_at + Tile::chunk_offset(lk, 4 * ks + g);
+    int t_at[NU];                                       // transposed reads, column block db
 #pragma unroll
-    for (int db = 0; db < NU; ++db) t_off[db] = tr16_lane_offset_sw<D>(lane, db);
+    for (int db = 0; db < NU; ++db) t_at[db] = ring_at + tr16_lane_offset_sw<D>(lane, db);
+    // Accumulators of A start at -lse*sqrt(d) and -D of their rows: element v of this lane's block (i, j) is
+    // query row 16 i + 4 g + v.  sv_at: those of A's tile, in its slot, or with OWN behind the rings in the order of the rows, counted
+    // from rq_begin; the -D and the row keys follow SV_D and SV_R bytes on.
+    constexpr int SV_D = OWN ? C::OWN_ROWS * 4 : C::OFF_D - C::OFF_L, SV_R = 2 * SV_D;
+    static_assert(OWN || SV_R == C::OFF_R - C::OFF_L, "start values lie in one row of arrays");
+    int sv_at = (OWN ? KG * (C::RING * C::SLOT) + row_base * 4 : ring_at + C::OFF_L) + 4 * g * 4;
 
-    // ---- stage pieces.  `tile` / `qb` name a block of 32 rows: LDS address of its ring slot and which half of it.
+    // ---- stage pieces.  `qb`: which half of the tile, a block of 32 rows.
     // Unit u: A operands of row block u % 2, operand step u / 2; C operands of column block u.
-    auto load_a = [&](const char *tile, int qb, int u, Frag<bf16_t> &fq, Frag<bf16_t> &fg) __attribute__((always_inline)) {
-        const char *p = tile + (qb * 32 + u % 2 * 16) * (D * 2) + a_off[u / 2];
+    auto load_a = [&](int qb, int u, Frag<bf16_t> &fq, Frag<bf16_t> &fg) __attribute__((always_inline)) {
+        const char *p = smem + a_at[u / 2] + (qb * 32 + u % 2 * 16) * (D * 2);
         fq = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(p));
         fg = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(p + C::OFF_G));
     };
-    auto load_c = [&](const char *tile, int qb, int u, Frag<bf16_t> &fq, Frag<bf16_t> &fg) __attribute__((always_inline)) {
-        fq = load_frag_tr16_sw<D>(tile, qb * 32, t_off[u]);
-        fg = load_frag_tr16_sw<D>(tile + C::OFF_G, qb * 32, t_off[u]);
-    };
-    // Accumulators of A start at -lse*sqrt(d) and -D of their rows: element v of this lane's block (i, j) is
-    // query row 16 i + 4 g + v.  `start_values`: those of a block of 32 rows, in its tile's slot, or with OWN by its
-    // first row counted from rq_begin; the -D and the row keys follow SV_D and SV_R bytes on.
-    constexpr int SV_D = OWN ? C::OWN_ROWS * 4 : C::OFF_D - C::OFF_L, SV_R = 2 * SV_D;
-    static_assert(OWN || SV_R == C::OFF_R - C::OFF_L, "start values lie in one row of arrays");
-    auto start_values = [&](const char *tile, int qb, int row) __attribute__((always_inline)) {
-        return (OWN ? own_values + row * 4 : tile + C::OFF_L + qb * 32 * 4) + 4 * g * 4;
+    auto load_c = [&](int qb, int u, Frag<bf16_t> &fq, Frag<bf16_t> &fg) __attribute__((always_inline)) {
+        fq = load_frag_tr16_sw<D>(smem, qb * 32, t_at[u]);
+        fg = load_frag_tr16_sw<D>(smem + C::OFF_G, qb * 32, t_at[u]);
     };
     f32x4 sv_l[2], sv_d[2];
-    auto init_load = [&](const char *sv) __attribute__((always_inline)) {
+    auto init_load = [&](int qb) __attribute__((always_inline)) {
+        const char *sv = smem + sv_at + qb * 32 * 4;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             sv_l[i] = *reinterpret_cast<const f32x4 *>(sv + i * 64);
@@ -737,23 +754,22 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
             }
         }
     };
-    // B for elements [e0, e1), element e = (i, j, v) = (e / (4 NJ), e / 4 % NJ, e % 4): P = 2^(c * (S - lse*sqrt(d))), dS = P * (dP - D);
+    // B for halves [h0, h1) of elements, element e = (i, j, v) = (e / (4 NJ), e / 4 % NJ, e % 4): P = 2^(c * (S - lse*sqrt(d))), dS = P * (dP - D);
     // finished pairs are rounded to bf16 into the operand fragments of C: slots 4 i + v of key block j.
     // (dropout: `sv_b` are B's start values; the row keys and -D of four rows are read when
     // the first of them is due)
-    // (An element's exponential and the multiplies that consume it are issued one element apart, as in the dQ
-    // workgroups: a transcendental's result may not be read by the very next instruction.)
+    // (Exponent, exponential and the multiplies that consume it one element apart, half an element at a time, as in the dQ workgroups.)
     u32x4 rk4;
     f32x4 nd4;
-    auto b_elems = [&](const char *sv_b, Block &sc, Block &dp, int e0, int e1, Frag<bf16_t> (&pf)[NJ],
+    auto b_elems = [&](int sv_b, Block &sc, Block &dp, int h0, int h1, Frag<bf16_t> (&pf)[NJ],
                        Frag<bf16_t> (&df)[NJ]) __attribute__((always_inline)) {
         auto finish = [&](int e) __attribute__((always_inline)) {           // sc holds P by now
             const int i = e / (4 * NJ), j = e / 4 % NJ, v = e & 3;
             f32x4 &p4 = sc.v[i][j], &d4 = dp.v[i][j];
             if constexpr (DROP) {
                 if (e % (4 * NJ) == 0) {
-                    rk4 = *reinterpret_cast<const u32x4 *>(sv_b + SV_R + i * 64);
-                    nd4 = *reinterpret_cast<const f32x4 *>(sv_b + SV_D + i * 64);
+                    rk4 = *reinterpret_cast<const u32x4 *>(smem + sv_b + SV_R + i * 64);
+                    nd4 = *reinterpret_cast<const f32x4 *>(smem + sv_b + SV_D + i * 64);
                 }
                 const float p = p4[v], m = drop_keep(rk4[v], drop_ck[j], dr.thr) ? dr.scale : 0.f;
                 p4[v] = p * m;
@@ -767,37 +783,41 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
             }
         };
 #pragma unroll
-        for (int e = e0; e < e1; ++e) {
-            f32x4 &p4 = sc.v[e / (4 * NJ)][e / 4 % NJ];
-            p4[e & 3] = fast_exp2(p4[e & 3] * c);
-            if (e > 0) finish(e - 1);
-            if (e == NE - 1) finish(e);
+        for (int h = h0; h < h1; ++h) {
+            const int e = h / 2, n = e + 1;
+            if (h % 2 == 0) {
+                f32x4 &p4 = sc.v[e / (4 * NJ)][e / 4 % NJ], &n4 = sc.v[n / (4 * NJ) % 2][n / 4 % NJ];
+                if (e == 0) p4[0] = p4[0] * c;
+                const float next = n < NE ? n4[n & 3] * c : 0.f;
+                p4[e & 3] = fast_exp2(p4[e & 3]);
+                if (n < NE) n4[n & 3] = next;
+            } else {
+                if (e > 0) finish(e - 1);
+                if (n == NE) finish(e);
+            }
         }
     };
-    // One pipeline step.  A: block (tile_a, qb_a) into (sc_a, dp_a), from the start values in sv_l and sv_d.  B: (sc_b, dp_b),
-    // first row r0_b, packing into (pf_b, df_b).  C: block (tile_c, qb_c) from (pf_c, df_c) into dk, dv.  Per unit 2 NJ matrix
+    // One pipeline step.  A: half qb_a of its tile into (sc_a, dp_a), from the start values in sv_l and sv_d.  B: (sc_b, dp_b),
+    // first row r0_b, packing into (pf_b, df_b).  C: half qb_c of its tile from (pf_c, df_c) into dk, dv.  Per unit 2 NJ matrix
     // instructions of C and 2 NJ of A (A first in the last unit), each pair on one operand fragment; after each come the B
     // elements that fall to its slot.
     // Everything read from LDS is requested well before its use: operand fragments one unit ahead;
-    // for the next step (A on block (tile_an, qb_an), rows from rq_begin + row_an on, C on (tile_cn, qb_cn)) this step's last
-    // unit requests the fragments of both's first unit and the start values of A's
-    // accumulators.  `mid` runs before those last requests: the even
-    // steps put the loop's barrier there, because the next step's A block may lie in the tile that
-    // the barrier publishes.
+    // for the next step (halves qb_an and qb_cn) this step's last unit requests the fragments of both's first unit and the start
+    // values of A's accumulators.  `mid` runs before those last requests: the even steps put the loop's barrier there, because
+    // the next step's A block may lie in the tile that the barrier publishes, and move the addresses on.
     Frag<bf16_t> cq[2], cg[2], aq[2], ag[2];
-    auto step = [&](auto has_a, auto has_b, auto has_c, const char *tile_a, int qb_a, Block &sc_a,
-                    Block &dp_a, const char *sv_b, int r0_b, Block &sc_b, Block &dp_b, Frag<bf16_t> (&pf_b)[NJ],
-                    Frag<bf16_t> (&df_b)[NJ], const char *tile_c, int qb_c, Frag<bf16_t> (&pf_c)[NJ], Frag<bf16_t> (&df_c)[NJ],
-                    const char *tile_an, int qb_an, int row_an, const char *tile_cn, int qb_cn, auto &&mid) __attribute__((always_inline)) {
+    auto step = [&](auto has_a, auto has_b, auto has_c, int qb_a, Block &sc_a, Block &dp_a, int sv_b, int r0_b, Block &sc_b,
+                    Block &dp_b, Frag<bf16_t> (&pf_b)[NJ], Frag<bf16_t> (&df_b)[NJ], int qb_c, Frag<bf16_t> (&pf_c)[NJ],
+                    Frag<bf16_t> (&df_c)[NJ], int qb_an, int qb_cn, auto &&mid) __attribute__((always_inline)) {
         constexpr bool HA = decltype(has_a)::value, HB = decltype(has_b)::value, HC = decltype(has_c)::value;
         constexpr int PU = 4 * NJ, NS = PU * NU;        // slots per unit and in all; the elements of B spread over them
         static_assert(NU % 2 == 0, "fragment double buffers assume an even number of units");
         auto b_slot = [&](int slot) __attribute__((always_inline)) {
             if (HB) {
-                const int e0 = slot * NE / NS, e1 = (slot + 1) * NE / NS;
-                if (e0 == e1) return;
+                const int h0 = slot * 2 * NE / NS, h1 = (slot + 1) * 2 * NE / NS;
+                if (h0 == h1) return;
                 __builtin_amdgcn_sched_barrier(0);
-                b_elems(sv_b, sc_b, dp_b, e0, e1, pf_b, df_b);
+                b_elems(sv_b, sc_b, dp_b, h0, h1, pf_b, df_b);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
@@ -836,8 +856,10 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             if (u + 1 < NU) {
-                if (HC) load_c(tile_c, qb_c, u + 1, cq[(u + 1) & 1], cg[(u + 1) & 1]);
-                if (HA) load_a(tile_a, qb_a, u + 1, aq[(u + 1) & 1], ag[(u + 1) & 1]);
+                if (HC) load_c(qb_c, u + 1, cq[(u + 1) & 1], cg[(u + 1) & 1]);
+                if (HA) load_a(qb_a, u + 1, aq[(u + 1) & 1], ag[(u + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                wait_lds<(HC ? 4 : 0) + (HA ? 2 : 0)>();            // this unit's are there (one wait, not one per fragment)
                 __builtin_amdgcn_sched_barrier(0);
                 do_c(u, PU * u);
                 do_a(u, PU * u + 2 * NJ);
@@ -845,9 +867,9 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
                 // last unit: A first, so that its results are there when the next step's B wants them
                 do_a(u, PU * u);
                 mid();
-                load_c(tile_cn, qb_cn, 0, cq[0], cg[0]);
-                load_a(tile_an, qb_an, 0, aq[0], ag[0]);
-                init_load(start_values(tile_an, qb_an, row_an));
+                load_c(qb_cn, 0, cq[0], cg[0]);
+                load_a(qb_an, 0, aq[0], ag[0]);
+                init_load(qb_an);
                 __builtin_amdgcn_sched_barrier(0);
                 do_c(u, PU * u + 2 * NJ);
             }
@@ -889,44 +911,46 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         // step -1: A(0) alone (leaves the first loop step's C operands in cq[0], cg[0]).  That step has
         // no C(-1): it multiplies zeros with tile 0 instead.
         auto nothing = [] {};
-        load_a(ring, 0, 0, aq[0], ag[0]);
-        init_load(start_values(ring, 0, row_base));
-        step(true_type{}, false_type{}, false_type{}, ring, 0, sc0, dp0, ring, 0, sc1, dp1, pf0, df0, ring, 0,
-             pf1, df1, ring, 1, row_base + 32, ring, 1, nothing);
+        load_a(0, 0, aq[0], ag[0]);
+        init_load(0);
+        step(true_type{}, false_type{}, false_type{}, 0, sc0, dp0, 0, 0, sc1, dp1, pf0, df0, 0, pf1, df1, 1, 1, nothing);
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
             for (int e = 0; e < 8; ++e) { pf1[j].v[e] = (bf16_t)0.f; df1[j].v[e] = (bf16_t)0.f; }
 
-        // ring slots: of tile t, of the next, the one that takes the tile after that (tile t - 1's), the one C reads first (t = 0: any
-        // tile, times zero)
-        char *cur = ring, *nxt = ring + C::SLOT, *prv = ring + 2 * C::SLOT, *c_first = ring;
-        int row = row_base, r0 = rq_begin + row_base;
+        // ring slots (bytes): of tile t, of the next, the one that takes the tile after that (tile t - 1's); C's way to tile t
+        int cur = 0, nxt = C::SLOT, prv = 2 * C::SLOT, c_step = 0;
+        int r0 = rq_begin + row_base;
 #pragma nounroll    // (unrolled, two groups' registers spill: 84 spills against none)
         for (int t = 0; t < T; ++t) {
+            const int sv_b = sv_at;                     // (dropout: B's rows, of tile t)
             // even step g = 2t: A(2t+1) [tile t, second half], B(2t), C(2t-1) [tile t-1, second half;
             // for t = 0 tile 0, times zero]
             // Before its last requests (which may touch tile t+1): tile t+1's loads, issued one iteration
             // ago, have landed for this wavefront; after the barrier for all, and every wavefront has
             // requested its last operands from tile t-1, whose slot takes tile t+2.
-            step(true_type{}, true_type{}, true_type{}, cur, 1, sc1, dp1, start_values(cur, 0, row), r0, sc0, dp0, pf0, df0, c_first, 1, pf1,
-                 df1, nxt, 0, row + C::BQ, cur, 0, [&] {
-                     wait_vmem_all();
-                     __syncthreads();
-                     issue_next(prv);
-                 });
+            step(true_type{}, true_type{}, true_type{}, 1, sc1, dp1, sv_b, r0, sc0, dp0, pf0, df0, 1, pf1, df1, 0, 0, [&] {
+                wait_vmem_all();
+                __syncthreads();
+                issue_next(ring + prv);
+#pragma unroll
+                for (int ks = 0; ks < NU / 2; ++ks) a_at[ks] += nxt - cur;
+#pragma unroll
+                for (int db = 0; db < NU; ++db) t_at[db] += c_step;
+                sv_at += OWN ? C::BQ * 4 : nxt - cur;
+            });
             // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end of whatever its slot holds, result unused],
             // B(2t+1), C(2t) [tile t, first half]
-            step(true_type{}, true_type{}, true_type{}, nxt, 0, sc0, dp0, start_values(cur, 1, row + 32), r0 + 32, sc1, dp1, pf1, df1, cur, 0, pf0,
-                 df0, nxt, 1, row + C::BQ + 32, cur, 1, nothing);
+            step(true_type{}, true_type{}, true_type{}, 0, sc0, dp0, sv_b + 32 * 4, r0 + 32, sc1, dp1, pf1, df1, 0, pf0, df0, 1, 1, nothing);
             advance();
-            c_first = cur;
-            cur = nxt, nxt = prv, prv = c_first;
-            row += C::BQ, r0 += C::BQ;
+            c_step = nxt - cur;
+            const int used = cur;
+            cur = nxt, nxt = prv, prv = used;
+            r0 += C::BQ;
         }
         // step 2T: C(2T-1) [tile T-1, second half] alone
-        step(false_type{}, false_type{}, true_type{}, ring, 0, sc0, dp0, ring, 0, sc0, dp0, pf0, df0, c_first, 1, pf1,
-             df1, ring, 0, 0, c_first, 1, nothing);
+        step(false_type{}, false_type{}, true_type{}, 0, sc0, dp0, 0, 0, sc0, dp0, pf0, df0, 1, pf1, df1, 0, 1, nothing);
     }
     if (KG > 1)
         for (int t = max(T, 0); t < iters; ++t) __syncthreads();       // the barriers of the group that has more tiles

@@ -104,6 +104,7 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
 #pragma unroll
     for (int db = 0; db < D / 32; ++db) o[db] = zero16;
     float m = -INFINITY, l = 0.f;                       // running maximum (log2 domain); this lane's half of the row sum
+    float m_sub = -1e30f;                               // what B subtracts: m, or as long as the row has seen no key a huge negative number
     const float c = kLog2e / sqrtf((float)D);
 
     if (s_tiles > 0) {
@@ -157,21 +158,27 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
                 reinterpret_cast<uint32_t *>(ck_ring)[(k_tile_next & 3) * C::BC + lane] = drop_col_key(drop_cs, (uint32_t)(k_tile_next * C::BC + lane));
         };
 
-        // ---- per-lane LDS offsets (bytes, within a tile)
-        int a_off[NU];                                  // A-operand chunk of row lq for operand step kb
+        // ---- this lane's LDS addresses (bytes from smem) in the K tile that A and in the V tile that C reads next; they move to
+        // the next tile once per iteration, to the other pair slot and back
+        const int ring_at = group * C::group_lds(DROP);
+        int a_at[NU];                                   // A-operand chunk of row lq for operand step kb
 #pragma unroll
-        for (int kb = 0; kb < NU; ++kb) a_off[kb] = Tile::chunk_offset(lq, 2 * kb + hh);
-        int t_off[D / 32];                              // transposed reads, column block db
+        for (int kb = 0; kb < NU; ++kb) a_at[kb] = ring_at + Tile::chunk_offset(lq, 2 * kb + hh);
+        int t_at[D / 32][2];                            // transposed reads, column block db: either read's
 #pragma unroll
-        for (int db = 0; db < D / 32; ++db) t_off[db] = tr_lane_offset_sw<D>(lane, db);
+        for (int db = 0; db < D / 32; ++db) {
+            const int off = tr_lane_offset_sw<D>(lane, db);
+            t_at[db][0] = ring_at + C::OFF_V + off;
+            t_at[db][1] = ring_at + C::OFF_V + (off ^ 48);
+        }
 
-        // ---- stage pieces.  `tile` / `kb2` name a block: LDS address of its K or V tile and which half of it.
-        auto load_a = [&](const char *tile, int kb2, int kb, Frag<bf16_t> &fk) __attribute__((always_inline)) {
-            fk = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(tile + kb2 * 32 * (D * 2) + a_off[kb]));
+        // ---- stage pieces.  `kb2`: which half of the tile, a block of 32 keys.
+        auto load_a = [&](int kb2, int kb, Frag<bf16_t> &fk) __attribute__((always_inline)) {
+            fk = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(smem + a_at[kb] + kb2 * 32 * (D * 2)));
         };
-        auto load_c = [&](const char *tile, int kb2, int u, Frag<bf16_t> &fv) __attribute__((always_inline)) {
+        auto load_c = [&](int kb2, int u, Frag<bf16_t> &fv) __attribute__((always_inline)) {
             const int half = u / (D / 32), db = u % (D / 32);
-            fv = load_frag_tr_sw<D>(tile, (kb2 * 2 + half) * 16, t_off[db]);
+            fv = load_frag_tr_sw<D>(smem, (kb2 * 2 + half) * 16, t_at[db][0], t_at[db][1]);
         };
         // Where the causal diagonal or the end of the sequence crosses a block (first key jb), the
         // masked elements of its finished S^T accumulator are set to -inf, which B turns into weight
@@ -188,16 +195,16 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
                     if (8 * (e >> 2) + (e & 3) > rel) sc[e] = -INFINITY;
             }
         };
-        // B for elements [e0, e1) (pairs): weight = 2^(c * S - m); the pair is added to the row sum
-        // and rounded to bf16 into the operand fragment of C.
-        // A row that has seen no key yet (m = -inf) subtracts a huge negative number instead, so that
+        // B for the pairs [n0, n1) of elements 2 n, 2 n + 1: weight = 2^(c * S - m); the pair is added to the row sum
+        // and rounded to bf16 into the operand fragment of C.  What a pair's instructions wait for was made with the pair before:
+        // its exponents come a pair ahead of its exponentials, sum and rounding a pair behind.
+        // A row that has seen no key yet (m = -inf) subtracts a huge negative number instead (m_sub), so that
         // any real score gives weight +inf and forces the fix-up, while masked scores still give 0.
         u32x4 ck4;      // dropout: the column keys of four consecutive elements, read when the first is due
-        auto b_elems = [&](const f32x16 &sc, float m_sub, int jb, int e0, int e1, float &psum, Frag<bf16_t> (&pf)[2])
+        float x0, x1, p0, p1;
+        auto b_pairs = [&](const f32x16 &sc, int jb, int n0, int n1, float &psum, Frag<bf16_t> (&pf)[2])
             __attribute__((always_inline)) {
-#pragma unroll
-            for (int e = e0; e < e1; e += 2) {
-                const float p0 = fast_exp2(sc[e] * c - m_sub), p1 = fast_exp2(sc[e + 1] * c - m_sub);
+            auto finish = [&](int e) __attribute__((always_inline)) {       // p0, p1: the weights of elements e, e + 1
                 psum += p0;
                 psum += p1;
                 if (DROP) {     // element e of this lane is key jb + 8 (e / 4) + 4 hh + e % 4
@@ -208,9 +215,17 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
                 } else {
                     pf[e >> 3].v[e & 7] = (bf16_t)p0; pf[e >> 3].v[(e & 7) + 1] = (bf16_t)p1;
                 }
+            };
+#pragma unroll
+            for (int n = n0; n < n1; ++n) {
+                if (n == 0) { x0 = sc[0] * c - m_sub; x1 = sc[1] * c - m_sub; }
+                const float e0 = fast_exp2(x0), e1 = fast_exp2(x1);
+                if (n < 7) { x0 = sc[2 * n + 2] * c - m_sub; x1 = sc[2 * n + 3] * c - m_sub; }
+                if (n > 0) finish(2 * n - 2);
+                p0 = e0, p1 = e1;
+                if (n == 7) finish(14);
             }
         };
-        auto m_sub_of = [](float mm) { return mm == -INFINITY ? -1e30f : mm; };
         // The fix-up: raise m to the exact maximum over what the row has seen including this block,
         // rescale what was accumulated under the old m (row sum l0 before this block; accumulator,
         // to which this block has not been added yet) and redo the block's weights.
@@ -222,36 +237,34 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
             const float m_new = fmaxf(m, mx * c);
             const float alpha = (m == -INFINITY) ? 0.f : fast_exp2(m - m_new);
             m = m_new;
+            m_sub = m == -INFINITY ? -1e30f : m;
             l = l0 * alpha;
 #pragma unroll
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
-            b_elems(sc, m_sub_of(m), jb, 0, 16, l, pf);
+            b_pairs(sc, jb, 0, 8, l, pf);
         };
 
-        // One pipeline step.  A: block (tile_a, kb2_a) into sc_a.  B: sc_b, first key jb_b, packing
-        // into pf_b.  C: block (tile_c, kb2_c) from pf_c into o.  Per unit the matrix instructions
+        // One pipeline step.  A: half kb2_a of its tile into sc_a.  B: sc_b, first key jb_b, packing
+        // into pf_b.  C: half kb2_c of its tile from pf_c into o.  Per unit the matrix instructions
         // go C, A (A, C in the last unit); after each one come the B elements that fall to its slot.  Operand fragments are
         // read from LDS one unit ahead of their use; those of the first unit by the step before
-        // (ak[0], cv[0] on entry), and this step leaves there those of the next step: A on block
-        // (tile_an, kb2_an), C on (tile_cn, kb2_cn).  `mid` runs before those last reads: the even
-        // steps put the loop's barrier there, because the next step's blocks may lie in the tile
-        // that the barrier publishes.
+        // (ak[0], cv[0] on entry), and this step leaves there those of the next step: halves kb2_an and kb2_cn.  `mid` runs
+        // before those last reads: the even steps put the loop's barrier there, because the next step's blocks may lie in the
+        // tile that the barrier publishes, and move the addresses on.
         Frag<bf16_t> ak[2], cv[2];
-        auto step = [&](auto has_a, auto has_b, auto has_c, const char *tile_a, int kb2_a, f32x16 &sc_a, f32x16 &sc_b,
-                        int jb_b, Frag<bf16_t> (&pf_b)[2], const char *tile_c, int kb2_c, Frag<bf16_t> (&pf_c)[2],
-                        const char *tile_an, int kb2_an, const char *tile_cn, int kb2_cn, auto &&mid)
+        auto step = [&](auto has_a, auto has_b, auto has_c, int kb2_a, f32x16 &sc_a, f32x16 &sc_b,
+                        int jb_b, Frag<bf16_t> (&pf_b)[2], int kb2_c, Frag<bf16_t> (&pf_c)[2], int kb2_an, int kb2_cn, auto &&mid)
             __attribute__((always_inline)) {
             constexpr bool HA = decltype(has_a)::value, HB = decltype(has_b)::value, HC = decltype(has_c)::value;
-            constexpr int NS = 2 * NU;                  // slots; 8 element pairs of B spread over them
+            constexpr int NS = 2 * NU;                  // slots; the 8 element pairs of B spread over them
             static_assert(NU % 2 == 0, "fragment double buffers assume an even number of units");
-            const float l0 = l, m_sub = m_sub_of(m);
+            const float l0 = l;
             auto b_slot = [&](int slot) __attribute__((always_inline)) {
                 if (HB) {
-                    const int e0 = 2 * (slot * 8 / NS), e1 = 2 * ((slot + 1) * 8 / NS);
                     __builtin_amdgcn_sched_barrier(0);
-                    b_elems(sc_b, m_sub, jb_b, e0, e1, l, pf_b);
+                    b_pairs(sc_b, jb_b, slot * 8 / NS, (slot + 1) * 8 / NS, l, pf_b);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             };
@@ -265,8 +278,10 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
             for (int u = 0; u < NU; ++u) {
                 const int half = u / (D / 32), db = u % (D / 32);
                 if (u + 1 < NU) {
-                    if (HC) load_c(tile_c, kb2_c, u + 1, cv[(u + 1) & 1]);
-                    if (HA) load_a(tile_a, kb2_a, u + 1, ak[(u + 1) & 1]);
+                    if (HC) load_c(kb2_c, u + 1, cv[(u + 1) & 1]);
+                    if (HA) load_a(kb2_a, u + 1, ak[(u + 1) & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    wait_lds<(HC ? 2 : 0) + (HA ? 1 : 0)>();        // this unit's are there
                     __builtin_amdgcn_sched_barrier(0);
                     if (HC) o[db] = mma(cv[u & 1], pf_c[half], o[db]);
                     b_slot(2 * u);
@@ -277,8 +292,8 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
                     if (HA) sc_a = mma(ak[u & 1], qf[u], sc_a);
                     b_slot(2 * u);
                     mid();
-                    load_c(tile_cn, kb2_cn, 0, cv[0]);
-                    load_a(tile_an, kb2_an, 0, ak[0]);
+                    load_c(kb2_cn, 0, cv[0]);
+                    load_a(kb2_an, 0, ak[0]);
                     __builtin_amdgcn_sched_barrier(0);
                     if (HC) o[db] = mma(cv[u & 1], pf_c[half], o[db]);
                     b_slot(2 * u + 1);
@@ -318,16 +333,16 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
             f32x16 sc0, sc1;                            // even / odd blocks
             Frag<bf16_t> pf0[2], pf1[2];
             // step -1: A(0) alone.  The first loop step has no C(-1): it multiplies zeros with tile 0 instead.
-            // pair slots: K of tile t and V of tile t - 1 (at first of tile 0 too), K of t + 1 and V of t
-            char *even = ring, *odd = ring + C::PAIR;
-            load_a(even, 0, 0, ak[0]);
+            load_a(0, 0, ak[0]);
             auto nothing = [] {};
-            step(true_type{}, false_type{}, false_type{}, even, 0, sc0, sc1, 0, pf0, odd + C::OFF_V, 0, pf1, even, 1, odd + C::OFF_V, 1, nothing);
+            step(true_type{}, false_type{}, false_type{}, 0, sc0, sc1, 0, pf0, 0, pf1, 1, 1, nothing);
 #pragma unroll
             for (int half = 0; half < 2; ++half)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) pf1[half].v[e] = (bf16_t)0.f;
 
+            // the pair slot (bytes) of K of tile t and V of tile t - 1, and the way to that of K of t + 1 and V of t
+            int slot = 0, other = C::PAIR;
             int j0 = t_begin * C::BC;
             for (int t = 0; t < T; ++t) {
                 // even step g = 2t: A(2t+1) [tile t, second half], B(2t), C(2t-1) [tile t-1, second half;
@@ -335,22 +350,25 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
                 // Before its last reads (which may touch tile t+1): K of tile t+1 and V of tile t, issued one iteration
                 // ago, have landed for this wavefront; after the barrier for all, and every wavefront has
                 // requested its last operands from K of tile t and V of tile t-1.
-                step(true_type{}, true_type{}, true_type{}, even, 1, sc1, sc0, j0, pf0, even + C::OFF_V, 1, pf1, odd, 0, odd + C::OFF_V, 0, [&] {
+                step(true_type{}, true_type{}, true_type{}, 1, sc1, sc0, j0, pf0, 1, pf1, 0, 0, [&] {
                     wait_vmem_all();
                     __syncthreads();
-                    issue_next(even);
+                    issue_next(ring + slot);
+#pragma unroll
+                    for (int kb = 0; kb < NU; ++kb) a_at[kb] += other;
+#pragma unroll
+                    for (int db = 0; db < D / 32; ++db) { t_at[db][0] += other; t_at[db][1] += other; }
                 });
                 // odd step g = 2t+1: A(2t+2) [tile t+1, first half; past the end of whatever its slot holds, result unused],
                 // B(2t+1), C(2t) [tile t, first half]
-                step(true_type{}, true_type{}, true_type{}, odd, 0, sc0, sc1, j0 + 32, pf1, odd + C::OFF_V, 0, pf0, odd, 1, odd + C::OFF_V, 1, nothing);
+                step(true_type{}, true_type{}, true_type{}, 0, sc0, sc1, j0 + 32, pf1, 0, pf0, 1, 1, nothing);
                 advance_k();
                 advance_v();
-                char *const used = even;
-                even = odd, odd = used;
+                slot += other, other = -other;
                 j0 += C::BC;
             }
             // step 2T: C(2T-1) [tile T-1, second half] alone
-            step(false_type{}, false_type{}, true_type{}, ring, 0, sc0, sc0, 0, pf0, even + C::OFF_V, 1, pf1, ring, 0, even + C::OFF_V, 1, nothing);
+            step(false_type{}, false_type{}, true_type{}, 0, sc0, sc0, 0, pf0, 1, pf1, 0, 1, nothing);
         }
         if (KG > 1)
             for (int t = T; t < iters; ++t) __syncthreads();           // the barriers of the groups that have more tiles
