@@ -806,8 +806,8 @@ int lss_plan_fwd(int64_t s0, int64_t l_s, int64_t l_x, int64_t B, int64_t H, int
         return LSS_OK;
     }
     const lss::FwdPlan p = lss::pick_fwd_plan(s, with_dropout != 0, most);
-    plan[0] = p.form == lss::FWD_8x1 ? 8 : p.form == lss::FWD_2x2 ? 2 : 4;
-    plan[1] = p.form == lss::FWD_2x2 || p.form == lss::FWD_4x2 ? 2 : 1;
+    plan[0] = p.form == lss::FWD_8x1 ? 8 : p.form == lss::FWD_2x2 || p.form == lss::FWD_2x4 ? 2 : p.form == lss::FWD_1x4 ? 1 : 4;
+    plan[1] = p.form == lss::FWD_2x4 || p.form == lss::FWD_1x4 ? 4 : p.form == lss::FWD_2x2 || p.form == lss::FWD_4x2 ? 2 : 1;
     plan[2] = p.splits;
     return LSS_OK;
 }

@@ -110,13 +110,14 @@ struct DirectTile {
     // its LDS address it adds to the global one too, so that one LDS address (M0) serves a tile's loads -- each scalar
     // instruction beside the matrix instructions costs a lone wavefront about 8 cycles.  pair_offsets() makes up for that on
     // the global side: its offsets are counted from PAIR_BIAS bytes ahead of the tile's first element (pair_base()).
-    static constexpr uint32_t PAIR_BIAS = (NI - 1) * 1024;
+    static constexpr int PAIR_GROUP = NI < 4 ? NI : 4;        // (what an offset field reaches)
+    static constexpr uint32_t PAIR_BIAS = (PAIR_GROUP - 1) * 1024;
     static __device__ __forceinline__ void pair_offsets(uint32_t (&off)[NI], int64_t row_stride, int rows_ok, int wave, int lane)
     {
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const int row = (wave * NI + i) * RPI + lane / CPR, chunk = (lane % CPR) ^ tile_swizzle<D>(row);
-            off[i] = ((uint32_t)min(row, rows_ok - 1) * (uint32_t)row_stride + (uint32_t)chunk * 8u) * 2u + PAIR_BIAS - (uint32_t)i * 1024u;
+            off[i] = ((uint32_t)min(row, rows_ok - 1) * (uint32_t)row_stride + (uint32_t)chunk * 8u) * 2u + PAIR_BIAS - (uint32_t)(i % PAIR_GROUP) * 1024u;
         }
     }
     static __device__ __forceinline__ const char *pair_base(const bf16_t *first) { return reinterpret_cast<const char *>(first) - PAIR_BIAS; }
@@ -124,21 +125,26 @@ struct DirectTile {
     static __device__ __forceinline__ void issue_pair(const char *g0_uniform, const char *g1_uniform, const uint32_t (&off0)[NI],
                                                       const uint32_t (&off1)[NI], char *lds_tile, int wave)
     {
-        static_assert(NI == 2 || NI == 4, "");
+        static_assert(NI == 1 || NI == 2 || NI == 4 || NI == 8, "");
         const uint32_t lds0 = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)(lds_tile + wave * (NI * 1024));
         const uint32_t lds1 = lds0 + BYTES;
-        if constexpr (NI == 2) {
+        if constexpr (NI == 1) {
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %4\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %5"
+                         : : "s"(lds0), "s"(lds1), "v"(off0[0]), "v"(off1[0]), "s"(g0_uniform), "s"(g1_uniform) : "memory", "m0");
+        } else if constexpr (NI == 2) {
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %6\n\tglobal_load_lds_dwordx4 %3, %6 offset:1024\n\t"
                          "s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %7\n\tglobal_load_lds_dwordx4 %5, %7 offset:1024"
                          : : "s"(lds0), "s"(lds1), "v"(off0[0]), "v"(off0[1]), "v"(off1[0]), "v"(off1[1]), "s"(g0_uniform), "s"(g1_uniform) : "memory", "m0");
         } else {
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %10\n\tglobal_load_lds_dwordx4 %3, %10 offset:1024\n\t"
-                         "global_load_lds_dwordx4 %4, %10 offset:2048\n\tglobal_load_lds_dwordx4 %5, %10 offset:3072\n\t"
-                         "s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %6, %11\n\tglobal_load_lds_dwordx4 %7, %11 offset:1024\n\t"
-                         "global_load_lds_dwordx4 %8, %11 offset:2048\n\tglobal_load_lds_dwordx4 %9, %11 offset:3072"
-                         : : "s"(lds0), "s"(lds1), "v"(off0[0]), "v"(off0[1]), "v"(off0[2]), "v"(off0[3]), "v"(off1[0]), "v"(off1[1]), "v"(off1[2]),
-                             "v"(off1[3]), "s"(g0_uniform), "s"(g1_uniform)
-                         : "memory", "m0");
+#pragma unroll
+            for (int i = 0; i < NI; i += 4)
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %10\n\tglobal_load_lds_dwordx4 %3, %10 offset:1024\n\t"
+                             "global_load_lds_dwordx4 %4, %10 offset:2048\n\tglobal_load_lds_dwordx4 %5, %10 offset:3072\n\t"
+                             "s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %6, %11\n\tglobal_load_lds_dwordx4 %7, %11 offset:1024\n\t"
+                             "global_load_lds_dwordx4 %8, %11 offset:2048\n\tglobal_load_lds_dwordx4 %9, %11 offset:3072"
+                             : : "s"(lds0 + i * 1024), "s"(lds1 + i * 1024), "v"(off0[i]), "v"(off0[i + 1]), "v"(off0[i + 2]), "v"(off0[i + 3]), "v"(off1[i]),
+                                 "v"(off1[i + 1]), "v"(off1[i + 2]), "v"(off1[i + 3]), "s"(g0_uniform), "s"(g1_uniform)
+                             : "memory", "m0");
         }
     }
     // byte offset inside the tile of the 16-byte chunk c of row r

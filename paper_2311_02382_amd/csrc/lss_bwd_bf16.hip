@@ -1522,8 +1522,8 @@ __global__ __launch_bounds__(256) void bwd_prep_bf16_kernel(SegShape s, DropArgs
 // KG = 2: a workgroup is two groups of four wavefronts, with tiles of their own in LDS, that walk half the key tiles (dQ) or query
 // tiles (dK/dV) each and add their sums up in LDS, in group order.  As many wavefronts per compute unit as two workgroups
 // of one group, each with half the walk: for launches that leave compute units idle or wait for their longest walk (pick_bwd_plan).
-// NJ: blocks of 16 keys or query rows per wavefront.  One instead of two (D = 128): eight wavefronts of 16 rows instead of four of 32, in half
-// the registers, so that a SIMD has two of them and the matrix instructions of one run beside the vector work of the other;
+// NJ: blocks of 16 keys or query rows per wavefront.  One instead of two: eight wavefronts of 16 rows instead of four of 32, in half
+// the registers, so that a SIMD has two of them (at D = 64: two where there is one workgroup per compute unit) and the matrix instructions of one run beside the vector work of the other;
 // but every operand read from LDS feeds one instruction instead of two.  See bwd_narrow.
 template <int D, bool DROP, bool OWN, bool SKINNY = false, int KG = 1, int NJ = 2>
 __global__ __launch_bounds__(64 * (8 / NJ) * KG, D == 64 || NJ == 1 ? 2 : 1) void bwd_main_bf16_kernel(
@@ -1605,12 +1605,10 @@ static hipError_t launch_bwd_bf16_d(const SegShape &s, const DropArgs &drop, con
                                : (own ? bwd_main_bf16_kernel<D, false, true, false, 2> : bwd_main_bf16_kernel<D, false, false, false, 2>);
     }
     unsigned threads = 256 * groups;
-    if constexpr (D == 128) {
-        if (plan.narrow) {
-            kernel = with_drop ? (own ? bwd_main_bf16_kernel<D, true, true, false, 1, 1> : bwd_main_bf16_kernel<D, true, false, false, 1, 1>)
-                               : (own ? bwd_main_bf16_kernel<D, false, true, false, 1, 1> : bwd_main_bf16_kernel<D, false, false, false, 1, 1>);
-            threads = 512;
-        }
+    if (plan.narrow) {
+        kernel = with_drop ? (own ? bwd_main_bf16_kernel<D, true, true, false, 1, 1> : bwd_main_bf16_kernel<D, true, false, false, 1, 1>)
+                           : (own ? bwd_main_bf16_kernel<D, false, true, false, 1, 1> : bwd_main_bf16_kernel<D, false, false, false, 1, 1>);
+        threads = 512;
     }
     TimedLaunch tl(K_BWD_MAIN_BF16, st);
     hipLaunchKernelGGL(kernel, dim3((unsigned)(n_dkv + n_dq)), dim3(threads), 0, st, s, drop, q, k, v, out, dO, lse, ws.Ls, ws.D, ws.row_key,

@@ -109,15 +109,21 @@ inline BwdPlan pick_bwd_plan(const SegShape &s, bool with_drop, int most, bool m
     return best;
 }
 
-// Whether a launch at d = 128 takes eight wavefronts of 16 rows per workgroup (NJ = 1): where no compute unit gets more than 32 walks of 64 query
+// Whether a launch takes eight wavefronts of 16 rows per workgroup (NJ = 1).  At d = 128 where no compute unit gets more than 32 walks of 64 query
 // rows past 128 keys.  Longer ones are held by the chip's power, of which twice the LDS reads take more: with NJ = 1 a 32k segment's
 // compute units are busy 12 % fewer cycles, but at a lower clock, 2.40 ms instead of 2.36.  50 launches, forward and backward:
 // those of 24 walks and less 0 to 12 % faster, 4.3 % on average (8 heads of 770 rows behind 1654: 82 -> 72 us, 4 of 813: 52 -> 49); above, 2 %
 // slower on average.
-inline bool bwd_narrow(const SegShape &s)
+// At d = 64 where the launch has no more than one workgroup of one group per compute unit, rows that no query sees not counted: wavefronts that are
+// alone on their SIMD wait for their own chains, which are half as long with 16 rows, and the LDS has time for twice the reads.  Of 55 such
+// launches (65 .. 4096 rows) one took 11 % longer, the others 3 to 14 % less, 5.4 % on average (4 heads of 256 rows behind 768: 15.6 us, 14.2;
+// with dropout 13 launches 7 %); of 256 to 320 workgroups 8 % more on average, past 1024 24 %.
+inline bool bwd_narrow(const SegShape &s, int n_splits, int groups)
 {
-    const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x;
-    return s.d == 128 && (seen + 127) / 128 * s.B * s.H * ((s.l_s + 63) / 64) <= 32 * 256;
+    const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x, bhs = (int64_t)s.B * s.H;
+    const int64_t dkv = (seen + 127) / 128 * bhs, dq = (int64_t)((s.l_s + 127) / 128) * bhs * n_splits;
+    if (s.d == 64) return s.l_s > kSkinnyRows && groups == 1 && dq + dkv <= 256;
+    return dkv * ((s.l_s + 63) / 64) <= 32 * 256;
 }
 
 // A whole backward launch.  one_pass: the kernel that makes all three gradients of a short segment (bf16, d = 64); own: no

@@ -14,7 +14,8 @@
 // in LDS, and meet there at the end: what fills the chip in launches of few rows without partial results in memory and
 // a launch to merge them, and shortens the walk that each wavefront is alone with.  Between backward passes, 8 x 2 heads of 1024
 // rows behind 0, 2048 and 4096 others: 128-row workgroups with the best split and its merge 21.1, 29.6 and 38.2 us, 64 rows in two
-// groups 14.9, 27.4 and 38.2, 128 rows in two groups 18.4, 28.5 and 35.9; 4 heads of 256 rows behind 512: 11.3, 9.7 and 12.4.  Large
+// groups 14.9, 27.4 and 38.2, 128 rows in two groups 18.4, 28.5 and 35.9; 4 heads of 256 rows behind 512: 11.3, 9.7 and 12.4.  Four groups
+// of one or two row blocks (d = 64) go on where that leaves off (figures: pick_fwd_plan).  Large
 // launches keep one group (64 heads of 4096 rows: 1692 us, in two groups
 // 1829): three workgroups per compute unit hide each other's waits.  The form is chosen per launch (pick_fwd_plan).
 //
@@ -468,6 +469,8 @@ hipError_t launch_fwd_bf16_main(const SegShape &s, const DropArgs &drop, const b
         switch (plan.form) {
         case FWD_2x2: return launch_fwd_main<64, 2, 2>(s, drop, q, k, v, out, lse, ws, plan.splits, st);
         case FWD_4x2: return launch_fwd_main<64, 4, 2>(s, drop, q, k, v, out, lse, ws, plan.splits, st);
+        case FWD_2x4: return launch_fwd_main<64, 2, 4>(s, drop, q, k, v, out, lse, ws, plan.splits, st);
+        case FWD_1x4: return launch_fwd_main<64, 1, 4>(s, drop, q, k, v, out, lse, ws, plan.splits, st);
         default: return launch_fwd_main<64, 4, 1>(s, drop, q, k, v, out, lse, ws, plan.splits, st);
         }
     }

@@ -8,7 +8,7 @@
 namespace lss {
 
 // The workgroup's form -- blocks of 32 query rows x groups of wavefronts that have a part of the keys each -- and the key splits
-enum FwdForm { FWD_4x1, FWD_2x2, FWD_4x2, FWD_8x1 };
+enum FwdForm { FWD_4x1, FWD_2x2, FWD_4x2, FWD_8x1, FWD_2x4, FWD_1x4 };
 struct FwdPlan { FwdForm form; int splits; };
 
 // A launch takes about, in us,
@@ -25,6 +25,11 @@ struct FwdPlan { FwdForm form; int splits; };
 //     48 heads of 1537 rows, d = 128, 54.5 us in 8x1, were given 4x2, 65 us, with the rest added to either.
 //   * A wavefront none of whose rows exist only moves tiles and meets the barriers: a last query tile of which a share `a` of the
 //     wavefronts has rows takes idle + (1 - idle) a per key tile; `first` is that of the launch's longest workgroup, `all` the mean.
+//   * Four groups (FWD_1x4: 32 query rows, FWD_2x4: 64): a launch whose query tiles alone leave most compute units idle shortens its walks without
+//     partial results and their merge.  28 heads of 226 rows behind 834 others take 12.8 us in 1x4, 14.5 in 2x2; 16 heads of 1024 rows behind 3072 28.6 us in 2x4, 31.3 in 4x2 and two ranges, behind 7168 49.2 in 4x2, 53.0 in 2x4, whose
+//     workgroups read every K and V tile for half as many rows.  Only where all workgroups run at once, one per compute unit: 312 of 2x4 (12 heads of
+//     1622 rows behind 1531) take 34.3 us, as many of 2x2 29.4.  359 launches as below: 2.4 % less time on average than without these two, the
+//     choice costs 1.1 % over the best (3.6 % without them); 200 with dropout 2.7 %, 0.9 and 4.3.
 //   * With dropout (tables of their own) a tile takes 1.5 to 2 times as long: the generator's work is in vector slots of which the
 //     forward has none to spare.  FWD_4x2 at d = 64 is not built with dropout: by its figures there (5.42, 0.87, 2.18 per
 //     tile) it is never the shortest, over 15 million sizes.
@@ -38,11 +43,13 @@ inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
     // (not below K's and V's bytes at 4.4 TB/s, the fourth powers added: 32 heads of 58 rows against 25,058 keys read 205 MB,
     // 47 us from HBM, and gain nothing from more than 8 splits)
     struct Cost { FwdForm form; int rows, groups, per_cu; double start, few, tile_us, shared, tail, idle; };
-    struct Table { int forms; Cost form[3]; double merge, mb_per_us; bool rounds; };
+    struct Table { int forms; Cost form[5]; double merge, mb_per_us; bool rounds; };
     static const Table tables[2][2] = {
-        {{3, {{FWD_4x1, 128, 1, 3, 9.05, -2.38, 0.719, 0.542, 0.542, 0.399}, {FWD_2x2, 64, 2, 2, 5.02, 2.09, 0.821, 0.401, 1.135, 0.688}, {FWD_4x2, 128, 2, 1, 5.39, 2.14, 1.078, 0.0, 0.789, 0.630}},
+        {{5, {{FWD_4x1, 128, 1, 3, 9.05, -2.38, 0.719, 0.542, 0.542, 0.399}, {FWD_2x2, 64, 2, 2, 5.02, 2.09, 0.821, 0.401, 1.135, 0.688}, {FWD_4x2, 128, 2, 1, 5.39, 2.14, 1.078, 0.0, 0.789, 0.630},
+              {FWD_2x4, 64, 4, 1, 5.93, 1.89, 1.300, 0.0, 0.0, 0.807}, {FWD_1x4, 32, 4, 1, 4.61, 1.38, 1.164, 0.0, 0.0, 1.000}},
           2.74, 3.85, false},
-         {2, {{FWD_4x1, 128, 1, 3, 10.97, -0.43, 1.319, 0.683, 0.552, 0.443}, {FWD_2x2, 64, 2, 2, 4.90, 1.50, 1.512, 0.550, 0.552, 0.000}},
+         {4, {{FWD_4x1, 128, 1, 3, 10.97, -0.43, 1.319, 0.683, 0.552, 0.443}, {FWD_2x2, 64, 2, 2, 4.90, 1.50, 1.512, 0.550, 0.552, 0.000},
+              {FWD_2x4, 64, 4, 1, 5.33, 1.52, 2.440, 0.0, 0.0, 0.300}, {FWD_1x4, 32, 4, 1, 4.80, 1.11, 1.944, 0.0, 0.0, 1.000}},
           2.42, 4.32, false}},
         {{2, {{FWD_8x1, 256, 1, 1, 2.55, 4.36, 1.512, 0.0, 0.556, 0.563}, {FWD_4x2, 128, 2, 1, 5.97, 2.31, 1.821, 0.0, 0.489, 1.000}}, 2.85, 4.19, true},
          {2, {{FWD_8x1, 256, 1, 1, 2.55, 4.36, 2.525, 0.0, 0.556, 0.563}, {FWD_4x2, 128, 2, 1, 5.97, 2.31, 2.859, 0.0, 0.489, 1.000}}, 2.85, 4.19, true}}};
@@ -50,6 +57,7 @@ inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
     const double out_mb = (double)s.B * s.H * s.l_s * s.d * 1e-6;     // elements
     const int64_t most = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x, tiles = (most + 63) / 64;
     const double kv_us = (double)s.B * s.H * most * s.d * 4.0 / 4.4e6;
+    const bool few_rows = (int64_t)((s.l_s + 63) / 64) * s.B * s.H <= 16;       // at most 16 workgroups of 64 rows
     FwdPlan best{table.form[0].form, 1};
     double best_t = 0.0;
     for (const Cost *c = table.form, *end = c + table.forms; c != end; ++c) {
@@ -64,6 +72,7 @@ inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
             // tests of the merge's rounding expect of them.  It costs them 0 to 1.5 us (4 heads of 256 rows behind 256: 9.7
             // instead of 8.3) and 0.1 % over all those launches.
             if (sp == 1 && max_splits > 1 && W <= 16.0 && tiles >= 8) continue;
+            if (c->groups == 4 && (W <= 16.0 || W > 256.0 || (few_rows && tiles >= 8))) continue;      // (nor do those few change their form; see above)
             const double longest = (double)(((tiles + sp - 1) / sp + c->groups - 1) / c->groups);
             const double average = mean_tiles / (sp * c->groups) + (sp * c->groups > 1 ? 0.5 : 0.0);
             const double rounds = ceil(W / 256.0), n = rounds < c->per_cu ? rounds : (double)c->per_cu;
