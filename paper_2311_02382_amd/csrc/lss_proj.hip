@@ -492,15 +492,18 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
     const int wm = wave % S::MW, wn = wave / S::MW;
     char *const ring = smem + group * S::RING;
 
-    // an XCD walks the output tiles of one chunk of rows, so that chunk's rows of A and dC are read from
-    // HBM once per XCD
+    // An XCD walks the output tiles of one chunk of rows after the other, so that the chunk's rows of A and dC are read from HBM
+    // once per XCD, and those in blocks of four tiles down, tile by tile of a column: where an XCD has only some of a chunk's tiles,
+    // its workgroups read few strips of either.  Row by row of tiles -> in these blocks: dW of 512 x 2048 from 2048 rows
+    // 15.5 -> 11.8 us, 1024 x 4096 from 4096 47.6 -> 40.5, 640 x 2560 from 1000 12.8 -> 11.3, 2048 x 512 from 2048 11.1 -> 11.4.
     const int splits = g.batches * g.splits_per_batch;
     const int tiles = g.m_tiles * g.n_tiles, per_xcd = (splits * tiles + kXcds - 1) / kXcds;
     const int item = blockIdx.x % kXcds * per_xcd + blockIdx.x / kXcds;
     if ((int)blockIdx.x / kXcds >= per_xcd || item >= splits * tiles) return;
     const int split = item / tiles, tile = item % tiles;
     const int batch = split / g.splits_per_batch;
-    const int m0 = (tile / g.n_tiles) * S::TM, n0 = (tile % g.n_tiles) * S::TN;
+    const int block = tile / (4 * g.n_tiles), in = tile % (4 * g.n_tiles), down = min(g.m_tiles - 4 * block, 4);
+    const int m0 = (4 * block + in % down) * S::TM, n0 = in / down * S::TN;
     const int r0 = (split % g.splits_per_batch) * g.chunk_rows, r1 = min(r0 + g.chunk_rows, g.rows);
     const int T = (r1 - r0 + PK - 1) / PK;          // >= 1: the host sizes the splits so
     const int tail = (r1 - r0) - (T - 1) * PK;      // rows of the last tile, 1 .. 64
