@@ -110,7 +110,7 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
             Dr[j] += __shfl_xor(Dr[j], 16);
             Dr[j] += __shfl_xor(Dr[j], 32);
         } else {
-            Dr[j] = -Dn[(int64_t)bh * s.l_s + rc];
+            Dr[j] = -Dn[(int64_t)bh * s.l_s + rc] * (DROP ? dr.scale : 1.f);
         }
         const float lv = lse[(int64_t)bh * s.l_s + rc];
         L2[j] = r < s.l_s ? lv * kLog2e : INFINITY;
@@ -207,16 +207,22 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
         // matrix instruction has some of it beside it and no two stand back to back, where the second's issue waits for the first.
         constexpr int NE = 8 * NJ;
         struct Block { f32x4 v[2][NJ]; };               // [key block i][row block j]: element v of this lane is key 16 i + 4 g + v
-        u32x4 ck4;      // dropout: the column keys of four consecutive keys, read when the first is due
+        // Dropout: a decision is a chain of eight instructions; its first round stands half an element ahead of the exponential, the second
+        // beside it, the comparison and the choice beside the next one.  (All behind the exponential, and the factor 1 / (1 - p) in every dK/dV
+        // element: 16 heads x 2 of 4096 rows behind 16384, 2765 us for the whole backward; 2690 so.)
+        u32x4 ck4;      // the column keys of four consecutive keys
+        uint32_t r1, r2;
+        float mask;                 // M of the element that finish() is about to do
+        auto load_keys = [&](int jb, int i) __attribute__((always_inline)) {
+            if (DROP) ck4 = *reinterpret_cast<const u32x4 *>(ck_ring + (((jb >> 6) & 3) * C::BC + (jb & 63) + 16 * i + 4 * g) * 4);
+        };
+        auto round1 = [&](int e) __attribute__((always_inline)) { r1 = drop_round1(drop_rk[e / 4 % NJ], ck4[e & 3]); };
+        auto choose = [&] __attribute__((always_inline)) { mask = drop_decide(r2, dr.thr) ? dr.scale : 0.f; };
         auto b_elems = [&](Block &sc, Block &dp, int jb, int h0, int h1, Frag<bf16_t> (&df)[NJ]) __attribute__((always_inline)) {
             auto finish = [&](int e) __attribute__((always_inline)) {       // sc holds P by now
                 const int i = e / (4 * NJ), j = e / 4 % NJ, v = e & 3;
                 f32x4 &d4 = dp.v[i][j];
-                if (DROP) {     // d4 holds dP (else dP - D)
-                    if (e % (4 * NJ) == 0)
-                        ck4 = *reinterpret_cast<const u32x4 *>(ck_ring + (((jb >> 6) & 3) * C::BC + (jb & 63) + 16 * i + 4 * g) * 4);
-                    d4[v] = fmaf(d4[v], drop_keep(drop_rk[j], ck4[v], dr.thr) ? dr.scale : 0.f, -Dr[j]);
-                }
+                if (DROP) d4[v] = fmaf(d4[v], mask, -Dr[j]);            // (d4 holds dP, else dP - D)
                 d4[v] = sc.v[i][j][v] * d4[v];
                 if (v & 1) { df[j].v[4 * i + v - 1] = (bf16_t)d4[v - 1]; df[j].v[4 * i + v] = (bf16_t)d4[v]; }
             };
@@ -226,12 +232,22 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
                 if (h % 2 == 0) {
                     f32x4 &p4 = sc.v[e / (4 * NJ)][e / 4 % NJ], &n4 = sc.v[n / (4 * NJ) % 2][n / 4 % NJ];
                     if (e == 0) p4[0] = p4[0] * c - L2[0];
+                    if (DROP && e == 0) round1(0);
                     const float next = n < NE ? n4[n & 3] * c - L2[n / 4 % NJ] : 0.f;
                     p4[e & 3] = fast_exp2(p4[e & 3]);
                     if (n < NE) n4[n & 3] = next;
+                    if (DROP) {
+                        if (e > 0) choose();
+                        r2 = drop_round2(r1);
+                    }
                 } else {
                     if (e > 0) finish(e - 1);
-                    if (n == NE) finish(e);
+                    if (DROP && n < NE) round1(n);
+                    if (n == 4 * NJ - 1) load_keys(jb, 1);              // (the four before are done with)
+                    if (n == NE) {
+                        if (DROP) choose();
+                        finish(e);
+                    }
                 }
             }
         };
@@ -280,6 +296,7 @@ __device__ __forceinline__ void bwd_dq_body(char *smem, const SegShape &s, const
                 }
             };
             if (HB) {
+                load_keys(jb_b, 0);
                 mask_s(jb_b, sc_b);
                 // B's inputs pass through an empty asm here: its arithmetic depends on nothing else in
                 // this step, and the compiler would otherwise move all of it out of the step, in one lump
@@ -548,9 +565,9 @@ __device__ __forceinline__ void neg_row_dots(const bf16_t *__restrict__ out, con
 // ring of three tiles in LDS; tiles travel global -> LDS directly, a full loop iteration ahead.
 //
 // With dropout (DROP) the weight that enters dV is A = P * M (M = 1 / (1 - p) where the weight is
-// kept, else 0) and dS = P * (M * dP - D); the dP accumulator starts at 0.  The keep decision of an element needs its row's key
-// (precomputed per query row, travelling with the tile like the start values) and this lane's
-// column key; -D of the element's row is read from the tile's start values when it is due.
+// kept, else 0) and dS = P * (M * dP - D); the dP accumulator starts at 0.  Both are made without the factor 1 / (1 - p), which the
+// finished sums get: K (kept) = P or 0, dS = K * dP - P * D (1 - p).  The keep decision of an element needs its row's key
+// (precomputed per query row, travelling with the tile like the start values) and this lane's column key; -D (1 - p) of the element's row is read from the tile's start values.
 //
 // OWN: the workgroup computes the start values (and keys) of its rows itself, into LDS, while its first
 // tiles are on their way, instead of finding them in memory (bwd_own_values).
@@ -756,24 +773,33 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
     };
     // B for halves [h0, h1) of elements, element e = (i, j, v) = (e / (4 NJ), e / 4 % NJ, e % 4): P = 2^(c * (S - lse*sqrt(d))), dS = P * (dP - D);
     // finished pairs are rounded to bf16 into the operand fragments of C: slots 4 i + v of key block j.
-    // (dropout: `sv_b` are B's start values; the row keys and -D of four rows are read when
-    // the first of them is due)
-    // (Exponent, exponential and the multiplies that consume it one element apart, half an element at a time, as in the dQ workgroups.)
+    // (Exponent, exponential and the multiplies that consume it one element apart, half an element at a time, and a decision's pieces
+    // likewise, as in the dQ workgroups.)
+    // (dropout: `sv_b` are B's start values, from which the row keys and -D of four rows come ahead of the first of them)
     u32x4 rk4;
     f32x4 nd4;
+    uint32_t r1, r2;
+    float kept;                 // the weight in front of finish(), or 0
+    auto load_keys = [&](int sv_b, int i) __attribute__((always_inline)) {
+        if constexpr (DROP) rk4 = *reinterpret_cast<const u32x4 *>(smem + sv_b + SV_R + i * 64);
+    };
+    auto load_d = [&](int sv_b, int i) __attribute__((always_inline)) {
+        if constexpr (DROP) nd4 = *reinterpret_cast<const f32x4 *>(smem + sv_b + SV_D + i * 64);
+    };
+    auto round1 = [&](int e) __attribute__((always_inline)) {
+        if constexpr (DROP) r1 = drop_round1(rk4[e & 3], drop_ck[e / 4 % NJ]);
+    };
+    auto choose = [&](float p) __attribute__((always_inline)) {
+        if constexpr (DROP) kept = drop_decide(r2, dr.thr) ? p : 0.f;
+    };
     auto b_elems = [&](int sv_b, Block &sc, Block &dp, int h0, int h1, Frag<bf16_t> (&pf)[NJ],
                        Frag<bf16_t> (&df)[NJ]) __attribute__((always_inline)) {
         auto finish = [&](int e) __attribute__((always_inline)) {           // sc holds P by now
             const int i = e / (4 * NJ), j = e / 4 % NJ, v = e & 3;
             f32x4 &p4 = sc.v[i][j], &d4 = dp.v[i][j];
             if constexpr (DROP) {
-                if (e % (4 * NJ) == 0) {
-                    rk4 = *reinterpret_cast<const u32x4 *>(smem + sv_b + SV_R + i * 64);
-                    nd4 = *reinterpret_cast<const f32x4 *>(smem + sv_b + SV_D + i * 64);
-                }
-                const float p = p4[v], m = drop_keep(rk4[v], drop_ck[j], dr.thr) ? dr.scale : 0.f;
-                p4[v] = p * m;
-                d4[v] = p * fmaf(d4[v], m, nd4[v]);
+                d4[v] = fmaf(kept, d4[v], p4[v] * nd4[v]);
+                p4[v] = kept;
             } else {
                 d4[v] = p4[v] * d4[v];
             }
@@ -787,13 +813,27 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
             const int e = h / 2, n = e + 1;
             if (h % 2 == 0) {
                 f32x4 &p4 = sc.v[e / (4 * NJ)][e / 4 % NJ], &n4 = sc.v[n / (4 * NJ) % 2][n / 4 % NJ];
-                if (e == 0) p4[0] = p4[0] * c;
+                if (e == 0) {
+                    p4[0] = p4[0] * c;
+                    load_d(sv_b, 0);
+                    round1(0);
+                }
                 const float next = n < NE ? n4[n & 3] * c : 0.f;
                 p4[e & 3] = fast_exp2(p4[e & 3]);
                 if (n < NE) n4[n & 3] = next;
+                if constexpr (DROP) {
+                    if (e > 0) choose(sc.v[(e - 1) / (4 * NJ)][(e - 1) / 4 % NJ][(e - 1) & 3]);
+                    r2 = drop_round2(r1);
+                }
             } else {
                 if (e > 0) finish(e - 1);
-                if (n == NE) finish(e);
+                if (n < NE) round1(n);
+                if (n == 4 * NJ - 1) load_keys(sv_b, 1);                // (the four before are done with)
+                if (e == 4 * NJ) load_d(sv_b, 1);
+                if (n == NE) {
+                    choose(sc.v[1][NJ - 1][3]);
+                    finish(e);
+                }
             }
         }
     };
@@ -824,6 +864,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         // B's inputs pass through an empty asm here: its arithmetic depends on nothing else in this
         // step, and the compiler would otherwise move all of it out of the step, in one lump
         if (HB) {
+            load_keys(sv_b, 0);
             mask_s(r0_b, sc_b);
 #pragma unroll
             for (int n = 0; n < 2 * NJ; ++n) asm volatile("" : "+v"(sc_b.v[n / NJ][n % NJ]), "+v"(dp_b.v[n / NJ][n % NJ]));
@@ -897,7 +938,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         const int64_t first = ((int64_t)b * s.l_s + rq_begin) * ld + (int64_t)h * D;
         neg_row_dots<D, KG * C::NT>(out + first, dO + first, lse + (int64_t)bh * s.l_s + rq_begin, ld, n, tid, [&](int i, float nd, float l) {
             own[i] = -l * sqrt_d;
-            own[C::OWN_ROWS + i] = nd;
+            own[C::OWN_ROWS + i] = DROP ? nd / dr.scale : nd;
             if constexpr (DROP)
                 reinterpret_cast<uint32_t *>(own)[2 * C::OWN_ROWS + i] = drop_row_key(dr.seed_lo, (uint32_t)bh, (uint32_t)(s.s0 + rq_begin + i));
         });
@@ -963,9 +1004,10 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
         char *buf = smem + all_waves * (C::KW * D * 4);
         const int64_t off = kv_base + (int64_t)jw0 * ld;
         const int rows_ok = min(s.l_x - jw0, C::KW);
+        const float m = DROP ? dr.scale : 1.f;          // of the kept weights: applied to their sums
         if constexpr (KG == 1) {
-            store_key_rows16<D, NJ>(buf, dk, 1.f / sqrt_d, dk_part + off, ld, rows_ok, lane);
-            store_key_rows16<D, NJ>(buf, dv, 1.f, dv_part + off, ld, rows_ok, lane);
+            store_key_rows16<D, NJ>(buf, dk, m / sqrt_d, dk_part + off, ld, rows_ok, lane);
+            store_key_rows16<D, NJ>(buf, dv, m, dv_part + off, ld, rows_ok, lane);
         } else {
             // The groups' sums meet in LDS: the first finishes dV, the second dK, adding in group order.  What a wavefront
             // reads was written for it alone, into the buffer that is its own from then on.
@@ -979,7 +1021,7 @@ __device__ __forceinline__ void bwd_dkv_body(char *smem, const SegShape &s, cons
 #pragma unroll
             for (int u = 0; u < 2 * NU; ++u)
                 sum[u / 2][u % 2] = (group == 0 ? dv[u / 2][u % 2] : dk[u / 2][u % 2]) + *reinterpret_cast<const f32x4 *>(buf + u * 1024 + lane * 16);
-            store_key_rows16<D, NJ>(buf, sum, group == 0 ? 1.f : 1.f / sqrt_d, (group == 0 ? dv_part : dk_part) + off, ld, rows_ok, lane);
+            store_key_rows16<D, NJ>(buf, sum, group == 0 ? m : m / sqrt_d, (group == 0 ? dv_part : dk_part) + off, ld, rows_ok, lane);
         }
     }
 }
@@ -1486,7 +1528,7 @@ int dq_bf16_rows_per_workgroup(int d) { return d == 64 ? DqBf16Cfg<64>::BR : DqB
 // ------------------------------------------------------------------------------------------ launch
 // Start values of the dK/dV accumulators, per query row: -D = -rowsum(dO * out) and -lse * sqrt(d).
 // One 16-byte chunk of a row per thread, D/8 consecutive lanes per row.
-// (dropout: also the generator's key of the row, for the dK/dV workgroups.)
+// (dropout: -D (1 - p), and the generator's key of the row, for the dK/dV workgroups.)
 template <int D, bool DROP>
 __global__ __launch_bounds__(256) void bwd_prep_bf16_kernel(SegShape s, DropArgs dr, const bf16_t *__restrict__ out,
                                                             const bf16_t *__restrict__ dO, const float *__restrict__ lse,
@@ -1502,7 +1544,7 @@ __global__ __launch_bounds__(256) void bwd_prep_bf16_kernel(SegShape s, DropArgs
     if (cpos == 0 && idx / CPR < rows) {
         const int h = (int)(row % s.H), r = (int)((row / s.H) % s.l_s), b = (int)(row / ((int64_t)s.H * s.l_s));
         const int64_t o_idx = ((int64_t)b * s.H + h) * s.l_s + r;
-        Dn[o_idx] = nd;
+        Dn[o_idx] = DROP ? nd / dr.scale : nd;
         Ls[o_idx] = -lse[o_idx] * sqrtf((float)D);
         if constexpr (DROP) row_key[o_idx] = drop_row_key(dr.seed_lo, (uint32_t)(b * s.H + h), (uint32_t)(s.s0 + r));
     }

@@ -80,6 +80,16 @@ __device__ __forceinline__ bool drop_keep(uint32_t row_key, uint32_t col_key, ui
 {
     return mix32(row_key + col_key) >= thr;
 }
+// ... in three pieces: drop_keep(r, c, thr) = drop_decide(drop_round2(drop_round1(r, c)), thr).  The mixing function's last
+// step, x ^ (x >> 16), leaves the upper half of x as it is: the lower half of what is compared matters only where the upper one equals
+// thr's, so that x ^ (thr >> 16) compares alike (an xor with a constant takes 3 cycles, one with the shifted value 5).
+__device__ __forceinline__ uint32_t drop_round1(uint32_t row_key, uint32_t col_key)
+{
+    const uint32_t x = row_key + col_key;
+    return (x ^ (x >> 16)) * 0x7feb352du;
+}
+__device__ __forceinline__ uint32_t drop_round2(uint32_t x) { return (x ^ (x >> 15)) * 0x846ca68bu; }
+__device__ __forceinline__ bool drop_decide(uint32_t x, uint32_t thr) { return (x ^ (thr >> 16)) >= thr; }
 
 // Exact GeLU, u Phi(u), and its derivative Phi(u) + u phi(u) (Phi, phi: the standard normal's distribution function and
 // density).  For u <= 0, Phi(u) = exp(-u^2/2) Q(t) t with t = 1 / (1 + 0.45 |u| / sqrt 2), Q the polynomial of degree 9 that

@@ -201,28 +201,46 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
         // its exponents come a pair ahead of its exponentials, sum and rounding a pair behind.
         // A row that has seen no key yet (m = -inf) subtracts a huge negative number instead (m_sub), so that
         // any real score gives weight +inf and forces the fix-up, while masked scores still give 0.
-        u32x4 ck4;      // dropout: the column keys of four consecutive elements, read when the first is due
+        // Dropout: a decision is a chain of eight instructions, which goes over three pairs' slots: first round a pair ahead of the exponential,
+        // second beside it, the rest a pair behind.  (All in one slot, with two conversions and a permutation per pair and the keys read when they
+        // were due: 16 heads x 2 of 4096 rows behind 16384, 1212 us; 1134 so.)
+        u32x4 ck4;      // the column keys of four consecutive elements: element e of this lane is key jb + 8 (e / 4) + 4 hh + e % 4
+        uint32_t r1_0, r1_1, r2_0, r2_1;
         float x0, x1, p0, p1;
+        auto load_keys = [&](int jb, int e) __attribute__((always_inline)) {
+            if (DROP) ck4 = *reinterpret_cast<const u32x4 *>(ck_ring + (((jb >> 6) & 3) * C::BC + (jb & 63) + 8 * (e >> 2) + 4 * hh) * 4);
+        };
+        auto round1 = [&](int e) __attribute__((always_inline)) {
+            r1_0 = drop_round1(drop_rk, ck4[e & 3]);
+            r1_1 = drop_round1(drop_rk, ck4[(e & 3) + 1]);
+        };
         auto b_pairs = [&](const f32x16 &sc, int jb, int n0, int n1, float &psum, Frag<bf16_t> (&pf)[2])
             __attribute__((always_inline)) {
             auto finish = [&](int e) __attribute__((always_inline)) {       // p0, p1: the weights of elements e, e + 1
                 psum += p0;
                 psum += p1;
-                if (DROP) {     // element e of this lane is key jb + 8 (e / 4) + 4 hh + e % 4
-                    if ((e & 3) == 0)
-                        ck4 = *reinterpret_cast<const u32x4 *>(ck_ring + (((jb >> 6) & 3) * C::BC + (jb & 63) + 8 * (e >> 2) + 4 * hh) * 4);
-                    pf[e >> 3].v[e & 7] = (bf16_t)(drop_keep(drop_rk, ck4[e & 3], dr.thr) ? p0 : 0.f);
-                    pf[e >> 3].v[(e & 7) + 1] = (bf16_t)(drop_keep(drop_rk, ck4[(e & 3) + 1], dr.thr) ? p1 : 0.f);
-                } else {
-                    pf[e >> 3].v[e & 7] = (bf16_t)p0; pf[e >> 3].v[(e & 7) + 1] = (bf16_t)p1;
+                if (DROP) {
+                    p0 = drop_decide(r2_0, dr.thr) ? p0 : 0.f;
+                    p1 = drop_decide(r2_1, dr.thr) ? p1 : 0.f;
+                    asm("" : "+v"(p0), "+v"(p1));       // (or each is rounded by itself ahead of the choice: five instructions for three)
                 }
+                pf[e >> 3].v[e & 7] = (bf16_t)p0; pf[e >> 3].v[(e & 7) + 1] = (bf16_t)p1;
             };
 #pragma unroll
             for (int n = n0; n < n1; ++n) {
-                if (n == 0) { x0 = sc[0] * c - m_sub; x1 = sc[1] * c - m_sub; }
+                if (n == 0) {
+                    x0 = sc[0] * c - m_sub; x1 = sc[1] * c - m_sub;
+                    if (DROP) round1(0);
+                }
                 const float e0 = fast_exp2(x0), e1 = fast_exp2(x1);
                 if (n < 7) { x0 = sc[2 * n + 2] * c - m_sub; x1 = sc[2 * n + 3] * c - m_sub; }
                 if (n > 0) finish(2 * n - 2);
+                if (DROP) {
+                    r2_0 = drop_round2(r1_0);
+                    r2_1 = drop_round2(r1_1);
+                    if (n < 7) round1(2 * n + 2);
+                    if (n % 2 == 0 && n < 6) load_keys(jb, 2 * n + 4);     // (the four before are done with)
+                }
                 p0 = e0, p1 = e1;
                 if (n == 7) finish(14);
             }
@@ -244,6 +262,7 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
+            load_keys(jb, 0);
             b_pairs(sc, jb, 0, 8, l, pf);
         };
 
@@ -270,6 +289,7 @@ __global__ __launch_bounds__(64 * RB * KG, D == 64 ? 2 : 1) void fwd_bf16_kernel
                 }
             };
             if (HB) {
+                load_keys(jb_b, 0);
                 mask_s(jb_b, sc_b);
                 // B's inputs pass through an empty asm here: its arithmetic depends on nothing else in
                 // this step, and the compiler would otherwise move all of it out of the step, in one lump
