@@ -79,7 +79,7 @@ struct ProjArgs {
 };
 
 // Operand tile [64 k][COLS], to be read transposed.  Loaded directly like a DirectTile.  Its rows start
-// at the same LDS bank (COLS >= 128) or alternate between two (COLS = 64), so the 16-byte chunk c of row
+// at the same LDS bank (COLS >= 128) or alternate between two or four (COLS = 64, 32), so the 16-byte chunk c of row
 // r sits at chunk position c ^ swizzle(r): the rows of which one transposing read takes 32 bytes each (four
 // consecutive ones per 16 lanes, eight further down the next four) then spread evenly over the 64 banks.
 template <int COLS, int WAVES>
@@ -87,7 +87,10 @@ struct TrTile {
     static constexpr int CPR = COLS / 8;                        // 16-byte chunks per row
     static constexpr int NI = PK * CPR / 64 / WAVES;            // load instructions per wavefront
     static_assert(PK * CPR % (64 * WAVES) == 0 && NI >= 1, "");
-    static __device__ __forceinline__ int swizzle(int r) { return (COLS >= 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1)) ^ (2 * ((r >> 3) & 1)); }
+    static __device__ __forceinline__ int swizzle(int r)
+    {
+        return (COLS >= 128 ? 4 * (r & 3) : COLS == 64 ? 4 * ((r >> 1) & 1) : 0) ^ (2 * ((r >> 3) & 1));
+    }
     static __device__ __forceinline__ int row_of(int i, int wave, int lane) { return ((i * WAVES + wave) * 64 + lane) / CPR; }
     // chunks >= chunks_ok (columns past the matrix) re-read chunk chunks_ok - 1; rows >= rows_ok re-read row
     // rows_ok - 1
@@ -626,8 +629,14 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
 using ShapeL = GemmShape<256, 256, 128, 64, 2>;         // eight wavefronts, one workgroup per compute unit
 using ShapeM = GemmShape<128, 128, 64, 64, 2>;          // four wavefronts, two workgroups per compute unit
 using ShapeM2 = GemmShape<128, 128, 64, 64, 2, 2>;      // ... two such groups share the contraction
+using ShapeM8 = GemmShape<128, 128, 64, 32, 4>;         // ... eight wavefronts of one group, four tiles on their way
 using ShapeS = GemmShape<64, 64, 32, 32, 4>;
 using ShapeS4 = GemmShape<64, 64, 32, 32, 2, 4>;
+// Where 64 x 64 tiles leave most compute units without one, what a launch waits for is a workgroup's own operand bytes, of which a compute unit
+// gets 40 to 60 per cycle: smaller tiles spread them, although there are more of them.  58 x 4096 -> 1024: S4 14.7 us, T4 11.2, T8 8.6;
+// 256 x 2048 -> 2048 9.7, 8.0, 13.2; dW of 512 x 512 from 1024 rows 7.6 and 5.6 in either.
+using ShapeT4 = GemmShape<32, 64, 32, 32, 2, 4>;        // two wavefronts, four such groups
+using ShapeT8 = GemmShape<32, 32, 32, 32, 2, 8>;        // one wavefront, eight such groups
 
 template <typename S, bool A_ANY, bool W_TR, bool OUT_F32, int EPI>
 hipError_t launch_proj_shape(ProjArgs &args, int kernel_id, hipStream_t st)
@@ -674,7 +683,9 @@ bool streams_results(const ProjArgs &args, bool out_f32)
 // per_tile[0], where they are full per_tile[1].  The figures are fitted to linear_fwd and linear_bwd_input at 230 .. 98304 rows and
 // 512 .. 8192 columns either way (20 launches in a graph each), with the loop of 32 x 32 x 16 instructions that there was.  With the present
 // one, 70 drawn feed-forward units and projections in every tile: the choice costs 0.5 to 1.3 % over the best tile on average, 3 % in
-// project_bwd (at worst 28 us instead of 16) and in the projections' weight gradients.  Large tiles move the fewest bytes per flop
+// project_bwd (at worst 28 us instead of 16) and in the projections' weight gradients.  (ShapeM8, ShapeT4 and ShapeT8 came later, fitted to
+// linear_fwd, bwd_input and bwd_weight at 58 .. 2048 rows and 256 .. 7680 columns: of 26 such maps in four products each none is slower than without
+// them, 40 are 5 to 42 % faster.)  Large tiles move the fewest bytes per flop
 // but a launch of few of them leaves compute units idle (2048 x 2048 -> 512: 16 workgroups of 256 x 256, 46 us;
 // 256 of 64 x 64, 12 us with the former loop), and where even 64 x 64 tiles leave one wavefront per SIMD the chain of contraction
 // tiles is what takes the time: four groups of wavefronts that share it took 9 us in a graph of them, 12 among other work now.
@@ -685,6 +696,9 @@ template <> constexpr GemmCost gemm_cost<ShapeM>() { return {2.8, {0.62, 1.00}};
 template <> constexpr GemmCost gemm_cost<ShapeM2>() { return {3.0, {0.50, 0.58}}; }
 template <> constexpr GemmCost gemm_cost<ShapeS>() { return {2.5, {0.30, 0.40}}; }
 template <> constexpr GemmCost gemm_cost<ShapeS4>() { return {3.3, {0.165, 0.22}}; }
+template <> constexpr GemmCost gemm_cost<ShapeM8>() { return {2.5, {0.51, 0.585}}; }
+template <> constexpr GemmCost gemm_cost<ShapeT4>() { return {3.0, {0.117, 0.165}}; }
+template <> constexpr GemmCost gemm_cost<ShapeT8>() { return {3.2, {0.069, 0.107}}; }
 
 // `tiles`: contraction tiles of a workgroup on average, `rest_tiles`: of those in the last, part-filled round
 template <typename S>
@@ -725,17 +739,25 @@ hipError_t launch_proj(ProjArgs &args, int kernel_id, hipStream_t st)
         const double room = 256.0 * S::PER_CU, rest = wgs - room * (double)(int64_t)(wgs / room), tiles = work / wgs;
         return gemm_estimate<S>(wgs, tiles, rest <= last_n ? last_tiles : tiles);     // (the last job's workgroups start last)
     };
+    // 128 x 128 tiles of which a compute unit holds one: a short contraction is all on its way at once in four slots, and nothing is left to add up
+    // (linear_fwd and bwd_input of 2048 x 512 -> 2048 9.9 -> 9.2 us, 9.7 -> 9.1; from 64 tiles on within 1 %).  Not with a float A, whose
+    // tiles travel through registers one at a time (project_bwd of 1500 x 2048 50.6 us in two groups, 54.2 so), nor for the weight
+    // gradients, both of whose operands are read transposed, more often in smaller parts (2048 x 2048 from 2048 rows 24.8 and 26.0).
+    using Mid = typename std::conditional<A_ANY, ShapeM2, ShapeM8>::type;
     args.stream = streams_results(args, OUT_F32);
-    const double t[5] = {estimate(ShapeL{}), estimate(ShapeM{}), estimate(ShapeM2{}), estimate(ShapeS{}), estimate(ShapeS4{})};
+    const double t[7] = {estimate(ShapeL{}), estimate(ShapeM{}), estimate(Mid{}), estimate(ShapeS{}), estimate(ShapeS4{}), estimate(ShapeT4{}),
+                         estimate(ShapeT8{})};
     int best = 0;
-    for (int i = 1; i < 5; ++i)
+    for (int i = 1; i < 7; ++i)
         if (t[i] < t[best]) best = i;
     switch (best) {
     case 0: return launch_proj_shape<ShapeL, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
     case 1: return launch_proj_shape<ShapeM, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
-    case 2: return launch_proj_shape<ShapeM2, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    case 2: return launch_proj_shape<Mid, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
     case 3: return launch_proj_shape<ShapeS, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
-    default: return launch_proj_shape<ShapeS4, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    case 4: return launch_proj_shape<ShapeS4, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    case 5: return launch_proj_shape<ShapeT4, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    default: return launch_proj_shape<ShapeT8, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
     }
 }
 
@@ -859,8 +881,9 @@ static WgradPlan wgrad_plan(int rows, int batches, int K, int N)
             const double tiles = chunk_tiles * (S::TM == 256 ? 1.0 : 1.2);
             return sum + gemm_estimate<S>(parts * ((K + S::TM - 1) / S::TM) * ((N + S::TN - 1) / S::TN), tiles, tiles);
         };
-        const double t[5] = {estimate(ShapeL{}), estimate(ShapeM{}), estimate(ShapeM2{}), estimate(ShapeS{}), estimate(ShapeS4{})};
-        for (int i = 0; i < 5; ++i)
+        const double t[7] = {estimate(ShapeL{}), estimate(ShapeM{}), estimate(ShapeM2{}), estimate(ShapeS{}), estimate(ShapeS4{}), estimate(ShapeT4{}),
+                             estimate(ShapeT8{})};
+        for (int i = 0; i < 7; ++i)
             if (best_t == 0.0 || t[i] < best_t) { best_t = t[i]; best = {i, splits, chunk_tiles * PK}; }
     }
     return best;
@@ -900,7 +923,9 @@ static hipError_t launch_wgrad(WgradArgs &g, float *dw, float *scratch, hipStrea
     case 1: e = launch_wgrad_shape<ShapeM, DC_F32>(g, st); break;
     case 2: e = launch_wgrad_shape<ShapeM2, DC_F32>(g, st); break;
     case 3: e = launch_wgrad_shape<ShapeS, DC_F32>(g, st); break;
-    default: e = launch_wgrad_shape<ShapeS4, DC_F32>(g, st); break;
+    case 4: e = launch_wgrad_shape<ShapeS4, DC_F32>(g, st); break;
+    case 5: e = launch_wgrad_shape<ShapeT4, DC_F32>(g, st); break;
+    default: e = launch_wgrad_shape<ShapeT8, DC_F32>(g, st); break;
     }
     if (e != hipSuccess || splits == 1) return e;
     std::vector<const float *> parts(splits);
