@@ -866,7 +866,7 @@ static int wgrad_most_chunks(int rows, int batches, int K, int N)
 // (3.5 us and their bytes at 4 TB/s) included; a chunk never crosses batch entries.  Shape-only,
 // deterministic.
 struct WgradPlan { int shape, splits_per_batch, chunk_rows; };
-static WgradPlan wgrad_plan(int rows, int batches, int K, int N)
+static WgradPlan wgrad_plan(int rows, int batches, int K, int N, bool dc_f32)
 {
     const int R = (rows + PK - 1) / PK, most = wgrad_most_chunks(rows, batches, K, N);
     WgradPlan best{0, 1, PK};
@@ -878,7 +878,11 @@ static WgradPlan wgrad_plan(int rows, int batches, int K, int N)
         auto estimate = [&](auto shape) {
             using S = decltype(shape);
             // (both operands through transposing reads: a fifth slower per tile, but for the largest)
-            const double tiles = chunk_tiles * (S::TM == 256 ? 1.0 : 1.2);
+            // (32-wide tiles read every operand more often, from the last-level cache where it has just been written -- behind two copies, which
+            // the tables' launches were not: dW of 256 x 1024 from 2000 rows 17.9 -> 16.5 us, copies included, but from 4000, which larger tiles
+            // share out in chunks, 24.2 -> 26.9.  A float dC travels through registers, a tile at a time: of 256 x 512 from 1512 rows
+            // 25.3 -> 20.7, from 4064 27.8 -> 33.2)
+            const double tiles = chunk_tiles * (S::TM == 256 ? 1.0 : 1.2) * (S::TM == 32 ? (dc_f32 ? 2.2 : 1.3) : 1.0);
             return sum + gemm_estimate<S>(parts * ((K + S::TM - 1) / S::TM) * ((N + S::TN - 1) / S::TN), tiles, tiles);
         };
         const double t[7] = {estimate(ShapeL{}), estimate(ShapeM{}), estimate(ShapeM2{}), estimate(ShapeS{}), estimate(ShapeS4{}), estimate(ShapeT4{}),
@@ -912,7 +916,7 @@ static hipError_t launch_wgrad_shape(WgradArgs &g, hipStream_t st)
 template <bool DC_F32>
 static hipError_t launch_wgrad(WgradArgs &g, float *dw, float *scratch, hipStream_t st)
 {
-    const WgradPlan p = wgrad_plan(g.rows, g.batches, g.K, g.N);
+    const WgradPlan p = wgrad_plan(g.rows, g.batches, g.K, g.N, DC_F32);
     g.splits_per_batch = p.splits_per_batch;
     g.chunk_rows = p.chunk_rows;
     const int splits = g.batches * g.splits_per_batch;
