@@ -148,6 +148,45 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const bf16_t *__rest
 // wavefront 8 rows in turn, short segments run on a handful of compute units.  Bound by the latency of one load and the two
 // row sums, then by memory.  61 rows of 1152: 20.0 -> 4.8 us, 1826 of 1664: 30 -> 7.5, 16384 of 1024 (100 MB): 29 -> 26.5.
 constexpr int LN_ROWS = 32, LN_COLS = 128, LN_ROW_WGS = LN_ROWS / 4;
+// One row's dx, by a wavefront
+template <int NCH>
+__device__ __forceinline__ void layernorm_bwd_row(const bf16_t *x, const float *__restrict__ gamma, const float *__restrict__ mean,
+                                                  const float *__restrict__ rstd, const bf16_t *dy, int64_t row, int64_t rows, int E,
+                                                  bf16_t *dx, int lane)
+{
+    if (row >= rows) return;
+    const int cpr = E / 8;
+            const float mu = mean[row], rs = rstd[row];
+            float xh[NCH][8], g[NCH][8];
+            float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+            for (int k = 0; k < NCH; ++k) {
+                const int c = lane + 64 * k;
+                if (c < cpr) {
+                    float xv[8], dv[8];
+                    unpack8(*reinterpret_cast<const bf16x8 *>(x + (row * cpr + c) * 8), xv);
+                    unpack8(*reinterpret_cast<const bf16x8 *>(dy + (row * cpr + c) * 8), dv);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        xh[k][e] = (xv[e] - mu) * rs;
+                        g[k][e] = dv[e] * gamma[c * 8 + e];
+                        s1 += g[k][e];
+                        s2 += g[k][e] * xh[k][e];
+                    }
+                }
+            }
+            const float m1 = wave_sum(s1) / (float)E, m2 = wave_sum(s2) / (float)E;
+#pragma unroll
+            for (int k = 0; k < NCH; ++k) {
+                const int c = lane + 64 * k;
+                if (c < cpr) {
+                    float o[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) o[e] = rs * (g[k][e] - m1 - xh[k][e] * m2);
+                    *reinterpret_cast<bf16x8 *>(dx + (row * cpr + c) * 8) = pack8(o);
+                }
+            }
+}
 // workgroups [first, first + gridDim.x) of those of a part; all of them by default, or one kind after the other if dx
 // stands in x's or dy's place
 template <int NCH>
@@ -160,39 +199,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const bf16_t *x, con
     const int64_t in_part = (int64_t)blockIdx.z * gridDim.y + blockIdx.y, row0 = in_part * LN_ROWS;
     if (row0 >= rows) return;
     if (kind < LN_ROW_WGS) {
-        const int lane = tid & 63;
-        const int64_t row = row0 + kind * 4 + (tid >> 6);
-        if (row >= rows) return;
-        const float mu = mean[row], rs = rstd[row];
-        float xh[NCH][8], g[NCH][8];
-        float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-        for (int k = 0; k < NCH; ++k) {
-            const int c = lane + 64 * k;
-            if (c < cpr) {
-                float xv[8], dv[8];
-                unpack8(*reinterpret_cast<const bf16x8 *>(x + (row * cpr + c) * 8), xv);
-                unpack8(*reinterpret_cast<const bf16x8 *>(dy + (row * cpr + c) * 8), dv);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    xh[k][e] = (xv[e] - mu) * rs;
-                    g[k][e] = dv[e] * gamma[c * 8 + e];
-                    s1 += g[k][e];
-                    s2 += g[k][e] * xh[k][e];
-                }
-            }
-        }
-        const float m1 = wave_sum(s1) / (float)E, m2 = wave_sum(s2) / (float)E;
-#pragma unroll
-        for (int k = 0; k < NCH; ++k) {
-            const int c = lane + 64 * k;
-            if (c < cpr) {
-                float o[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] = rs * (g[k][e] - m1 - xh[k][e] * m2);
-                *reinterpret_cast<bf16x8 *>(dx + (row * cpr + c) * 8) = pack8(o);
-            }
-        }
+        layernorm_bwd_row<NCH>(x, gamma, mean, rstd, dy, row0 + kind * 4 + (tid >> 6), rows, E, dx, tid & 63);
         return;
     }
     __shared__ f32x4 red[16][4][16];            // [rows i, i + 16][dgamma, dgamma, dbeta, dbeta][chunk]
@@ -250,6 +257,80 @@ __global__ __launch_bounds__(256) void layernorm_bwd_params_kernel(const float *
 #pragma unroll
         for (int j = 1; j < 8; ++j) acc += red[j][cc];
         *reinterpret_cast<f32x4 *>(col < E ? dgamma + col : dbeta + (col - E)) = acc;
+    }
+}
+
+// The same for short segments, dgamma and dbeta included: the second kernel is a launch that waits for this one, 4 us whatever its size.  Column
+// workgroups own 32 columns over all rows (thread (group, chunk): every 256th row, four at a time on their way; the 256 groups' sums meet in LDS,
+// in order), and what a compute unit gets per cycle bounds them: 64 bytes per row and operand.
+constexpr int LN_SHORT_COLS = 32, LN_SHORT_ROWS = 16;
+// Where one launch is the shorter way.  x and dy just written by the launches before (two copies, timed along: 8.5 us), two launches and one, us:
+// 58 rows of 512 columns 15.0, 10.4; 512 of 1024 14.6, 10.6; 512 of 2048 15.1, 11.7; 1000 of 1024 14.8, 13.3; 2048 of 512 15.0, 17.4: a column
+// workgroup's bytes then come from the last-level cache at half the rate, which a call on its own inputs again does not show (2048 of 512 6.1, 5.5).
+bool layernorm_bwd_short(int64_t rows, int E) { return rows <= 1024 && E <= 2048 && rows * E <= 1024 * 1024; }
+template <int NCH>
+__global__ __launch_bounds__(1024) void layernorm_bwd_short_kernel(const bf16_t *x, const float *__restrict__ gamma,
+                                                                   const float *__restrict__ mean, const float *__restrict__ rstd,
+                                                                   const bf16_t *dy, int rows, int E, bf16_t *dx,
+                                                                   float *__restrict__ dgamma, float *__restrict__ dbeta, int col_wgs, int first)
+{
+    const int tid = threadIdx.x, id = (int)blockIdx.x + first;
+    if (id >= col_wgs) {
+        layernorm_bwd_row<NCH>(x, gamma, mean, rstd, dy, (int64_t)(id - col_wgs) * LN_SHORT_ROWS + (tid >> 6), rows, E, dx, tid & 63);
+        return;
+    }
+    __shared__ f32x4 red[4][1024];              // [dgamma, dgamma, dbeta, dbeta][4 * group + chunk]
+    const int cpr = E / 8, c = id * 4 + (tid & 3);
+    f32x4 acc[4] = {};
+    if (c < cpr)
+        for (int r = tid >> 2; r < rows; r += 1024) {
+            bf16x8 xr[4], dr[4];
+            float mu[4], rs[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t row = min(r + 256 * u, rows - 1);
+                xr[u] = *reinterpret_cast<const bf16x8 *>(x + (row * cpr + c) * 8);
+                dr[u] = *reinterpret_cast<const bf16x8 *>(dy + (row * cpr + c) * 8);
+                mu[u] = mean[row];
+                rs[u] = rstd[row];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (r + 256 * u >= rows) break;
+                float xv[8], dv[8];
+                unpack8(xr[u], xv);
+                unpack8(dr[u], dv);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    acc[e / 4][e % 4] += dv[e] * ((xv[e] - mu[u]) * rs[u]);
+                    acc[2 + e / 4][e % 4] += dv[e];
+                }
+            }
+        }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) red[k][tid] = acc[k];
+    __syncthreads();
+    // 16 quadruples of columns, (k, chunk): 64 threads each add up four groups, then 8 of them 8 such sums, then one the rest
+    const int k = (tid >> 2) & 3, cc = tid & 3, p = tid >> 4;
+    f32x4 sum = red[k][16 * p + cc];
+#pragma unroll
+    for (int g = 1; g < 4; ++g) sum += red[k][16 * p + 4 * g + cc];
+    __syncthreads();
+    red[0][tid] = sum;                          // [p][k][cc]
+    __syncthreads();
+    if (p < 8) {
+        sum = red[0][128 * p + (tid & 15)];
+#pragma unroll
+        for (int j = 1; j < 8; ++j) sum += red[0][128 * p + 16 * j + (tid & 15)];
+        red[1][tid] = sum;
+    }
+    __syncthreads();
+    if (p == 0 && c < cpr) {
+#pragma unroll
+        for (int j = 1; j < 8; ++j) sum += red[1][16 * j + tid];
+        float *const to = (k < 2 ? dgamma : dbeta) + c * 8 + (k & 1) * 4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) to[e] = sum[e];
     }
 }
 
@@ -333,7 +414,27 @@ hipError_t launch_layernorm_bwd(const bf16_t *x, const float *gamma, const float
     if (rows > 0) {
         TimedLaunch tl(K_LN_BWD, st);
         const int all = LN_ROW_WGS + (E + LN_COLS - 1) / LN_COLS;
-        const size_t bytes = (size_t)rows * E * sizeof(bf16_t);
+        const size_t bytes = (size_t)rows * E * sizeof(bf16_t), cols = (size_t)E * sizeof(float);
+        if (layernorm_bwd_short(rows, E)) {     // (not where something it reads is overwritten: there the launches' order matters)
+            const size_t per_row = (size_t)rows * sizeof(float);
+            bool clash = overlaps(dx, bytes, gamma, cols) || overlaps(dx, bytes, mean, per_row) || overlaps(dx, bytes, rstd, per_row);
+            for (const float *d : {dgamma, dbeta})
+                clash = clash || overlaps(d, cols, x, bytes) || overlaps(d, cols, dy, bytes) || overlaps(d, cols, dx, bytes) || overlaps(d, cols, gamma, cols) ||
+                        overlaps(d, cols, mean, per_row) || overlaps(d, cols, rstd, per_row);
+            if (!clash) {
+                const int col_wgs = (E + LN_SHORT_COLS - 1) / LN_SHORT_COLS, all = col_wgs + (int)((rows + LN_SHORT_ROWS - 1) / LN_SHORT_ROWS);
+                const bool apart = overlaps(dx, bytes, x, bytes) || overlaps(dx, bytes, dy, bytes);         // the column kind alone first
+                for (int first = 0, end = apart ? col_wgs : all; first < all; first = end, end = all) {
+                    const dim3 grid((unsigned)(end - first));
+#define LSS_LN_BWD(NCH) hipLaunchKernelGGL(layernorm_bwd_short_kernel<NCH>, grid, dim3(1024), 0, st, x, gamma, mean, rstd, dy, (int)rows, E, dx, dgamma, dbeta, col_wgs, first)
+                    if (E <= 512) LSS_LN_BWD(1);
+                    else if (E <= 1024) LSS_LN_BWD(2);
+                    else LSS_LN_BWD(4);
+#undef LSS_LN_BWD
+                }
+                return hipGetLastError();
+            }
+        }
         const int apart = overlaps(dx, bytes, x, bytes) || overlaps(dx, bytes, dy, bytes) ? LN_ROW_WGS : 0;     // the column kind alone first
         for (int first = apart, end = all; end > 0; end = first, first = 0) {
             const dim3 grid((unsigned)(end - first), (unsigned)std::min(n_parts, 32768), (unsigned)((n_parts + 32767) / 32768));
