@@ -41,7 +41,8 @@ struct FwdPlan { FwdForm form; int splits; };
 inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
 {
     // (not below K's and V's bytes at 4.4 TB/s, the fourth powers added: 32 heads of 58 rows against 25,058 keys read 205 MB,
-    // 47 us from HBM, and gain nothing from more than 8 splits)
+    // 47 us from HBM, and gain nothing from more than 8 splits: 41.6 us in 2x2, whose groups walk 25 and 24 tiles, 43.1 in 2x4, 13, 13, 13 and 10,
+    // or with 7 splits, 224 workgroups)
     struct Cost { FwdForm form; int rows, groups, per_cu; double start, few, tile_us, shared, tail, idle; };
     struct Table { int forms; Cost form[5]; double merge, mb_per_us; bool rounds; };
     static const Table tables[2][2] = {
@@ -84,7 +85,9 @@ inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
             }
             const double walk = longest_walk + shared * (mean < longest_walk ? mean : longest_walk);
             double t = c->start + c->tile_us * (walk > share ? walk : share);
-            t = sqrt(sqrt(t * t * t * t + kv_us * kv_us * kv_us * kv_us));
+            // (four groups that do not all have a tile at the end, or not on every compute unit, read less at once)
+            const double kv = kv_us * (c->groups == 4 ? sqrt(sqrt(256.0 / W)) * (longest * 4.0 * sp / (double)tiles) : 1.0);
+            t = sqrt(sqrt(t * t * t * t + kv * kv * kv * kv));
             if (sp > 1) t += table.merge + out_mb * (8 * sp + 2) / table.mb_per_us;
             if (best_t == 0.0 || t < best_t) { best_t = t; best = {c->form, sp}; }
         }
