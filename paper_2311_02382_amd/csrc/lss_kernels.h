@@ -109,7 +109,8 @@ hipError_t allow_lds(K kernel, int bytes, DeviceOnce &once)
 // function (per role where several entry points share one).
 enum KernelId { K_FWD_F32 = 0, K_FWD_MERGE, K_ROWDOT, K_BWD_MAIN_F32, K_DQ_MERGE, K_REDUCE, K_BWD_MAIN_BF16, K_PROJ_FWD, K_PROJ_BWD,
                 K_PE_FWD, K_PE_BWD, K_LN_FWD, K_LN_BWD, K_LN_PARAMS, K_GELU_FWD, K_GELU_BWD, K_LINEAR_FWD, K_LINEAR_BWD, K_RESIDUAL, K_LINEAR_WGRAD,
-                K_FWD_BF16, K_BWD_PREP_BF16, K_BWD_SKINNY_BF16, K_COUNT };
+                K_FWD_BF16, K_BWD_PREP_BF16, K_BWD_SKINNY_BF16, K_LN_BWD_SHORT, K_PROJ_FWD_SMALL, K_PROJ_BWD_SMALL, K_LINEAR_FWD_SMALL,
+                K_LINEAR_BWD_SMALL, K_COUNT };
 void timing_begin(int id, hipStream_t st);
 void timing_end(int id, hipStream_t st);
 struct TimedLaunch {    // RAII bracket around one kernel launch

@@ -283,8 +283,9 @@ struct GemmStore {
     }
 };
 
-template <typename S, bool A_ANY, bool W_TR, bool OUT_F32, int EPI>
-__global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(ProjArgs args)
+// STREAMS: whether args.stream may be set (not where launches are small)
+template <typename S, bool A_ANY, bool W_TR, bool OUT_F32, int EPI, bool STREAMS>
+__device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
 {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     using OutT = typename std::conditional<OUT_F32, float, bf16_t>::type;
@@ -318,7 +319,7 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(Pro
     const int cols_here = min(J.N - n0, S::TN);                         // a multiple of 64
 
     auto put16 = [&](void *to, f32x4 v) __attribute__((always_inline)) {
-        if (args.stream) {
+        if (STREAMS && args.stream) {
             asm volatile("");       // (two stores that differ in this respect only are merged into one plain store, ahead of the branch or behind it)
             __builtin_nontemporal_store(v, static_cast<f32x4 *>(to));
             asm volatile("");
@@ -459,6 +460,16 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(Pro
     gemm_loop<S, LOADS, !A_ANY>(acc, T, group, a_f32, issue, load, [](int, int) {}, fetch_a, [&](int, int slot) { stash_a(slot); });
     gemm_add_groups<S>(smem, acc, group, wave, lane);
     store_tiles(acc, true);
+}
+template <typename S, bool A_ANY, bool W_TR, bool OUT_F32, int EPI>
+__global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(ProjArgs args)
+{
+    proj_gemm_body<S, A_ANY, W_TR, OUT_F32, EPI, true>(args);
+}
+template <typename S, bool A_ANY, bool W_TR, bool OUT_F32, int EPI>
+__global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_small_gemm_kernel(ProjArgs args)
+{
+    proj_gemm_body<S, A_ANY, W_TR, OUT_F32, EPI, false>(args);
 }
 
 // Weight gradient of a linear map: dW[k, n] = sum_r A[r, k] dC[r, n], the contraction running over
@@ -654,7 +665,12 @@ hipError_t launch_proj_shape(ProjArgs &args, int kernel_id, hipStream_t st)
     wgs += xcd_tile_grid(args.job[0].batches * (args.job[0].m_tiles - args.job[0].m_data), args.job[0].n_tiles);
     if (wgs == 0) return hipSuccess;
     static DeviceOnce once;
-    const auto kernel = proj_gemm_kernel<S, A_ANY, W_TR, OUT_F32, EPI>;
+    constexpr bool SMALL = S::TM == 32;
+    void (*kernel)(ProjArgs);
+    if constexpr (SMALL) kernel = proj_small_gemm_kernel<S, A_ANY, W_TR, OUT_F32, EPI>;
+    else kernel = proj_gemm_kernel<S, A_ANY, W_TR, OUT_F32, EPI>;
+    if (SMALL)
+        kernel_id = kernel_id == K_PROJ_FWD ? K_PROJ_FWD_SMALL : kernel_id == K_PROJ_BWD ? K_PROJ_BWD_SMALL : kernel_id == K_LINEAR_FWD ? K_LINEAR_FWD_SMALL : K_LINEAR_BWD_SMALL;
     if (const hipError_t e = allow_lds(kernel, S::LDS, once); e != hipSuccess) return e;
     TimedLaunch tl(kernel_id, st);
     hipLaunchKernelGGL(kernel, dim3(wgs), dim3(S::NT), S::LDS, st, args);
@@ -748,7 +764,7 @@ hipError_t launch_proj(ProjArgs &args, int kernel_id, hipStream_t st)
     const double t[7] = {estimate(ShapeL{}), estimate(ShapeM{}), estimate(Mid{}), estimate(ShapeS{}), estimate(ShapeS4{}), estimate(ShapeT4{}),
                          estimate(ShapeT8{})};
     int best = 0;
-    for (int i = 1; i < 7; ++i)
+    for (int i = 1; i < (args.stream ? 5 : 7); ++i)
         if (t[i] < t[best]) best = i;
     switch (best) {
     case 0: return launch_proj_shape<ShapeL, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
@@ -882,7 +898,7 @@ static WgradPlan wgrad_plan(int rows, int batches, int K, int N, bool dc_f32)
             // the tables' launches were not: dW of 256 x 1024 from 2000 rows 17.9 -> 16.5 us, copies included, but from 4000, which larger tiles
             // share out in chunks, 24.2 -> 26.9.  A float dC travels through registers, a tile at a time: of 256 x 512 from 1512 rows
             // 25.3 -> 20.7, from 4064 27.8 -> 33.2)
-            const double tiles = chunk_tiles * (S::TM == 256 ? 1.0 : 1.2) * (S::TM == 32 ? (dc_f32 ? 2.2 : 1.3) : 1.0);
+            const double tiles = chunk_tiles * (S::TM == 256 ? 1.0 : 1.2) * (S::TM != 32 ? 1.0 : dc_f32 ? 2.2 : chunk_tiles > 32 ? 1.3 : 1.0);
             return sum + gemm_estimate<S>(parts * ((K + S::TM - 1) / S::TM) * ((N + S::TN - 1) / S::TN), tiles, tiles);
         };
         const double t[7] = {estimate(ShapeL{}), estimate(ShapeM{}), estimate(ShapeM2{}), estimate(ShapeS{}), estimate(ShapeS4{}), estimate(ShapeT4{}),

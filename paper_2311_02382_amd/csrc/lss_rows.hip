@@ -412,7 +412,6 @@ hipError_t launch_layernorm_bwd(const bf16_t *x, const float *gamma, const float
 {
     const int n_parts = (int)((rows + LN_ROWS - 1) / LN_ROWS);
     if (rows > 0) {
-        TimedLaunch tl(K_LN_BWD, st);
         const int all = LN_ROW_WGS + (E + LN_COLS - 1) / LN_COLS;
         const size_t bytes = (size_t)rows * E * sizeof(bf16_t), cols = (size_t)E * sizeof(float);
         if (layernorm_bwd_short(rows, E)) {     // (not where something it reads is overwritten: there the launches' order matters)
@@ -424,6 +423,7 @@ hipError_t launch_layernorm_bwd(const bf16_t *x, const float *gamma, const float
             if (!clash) {
                 const int col_wgs = (E + LN_SHORT_COLS - 1) / LN_SHORT_COLS, all = col_wgs + (int)((rows + LN_SHORT_ROWS - 1) / LN_SHORT_ROWS);
                 const bool apart = overlaps(dx, bytes, x, bytes) || overlaps(dx, bytes, dy, bytes);         // the column kind alone first
+                TimedLaunch tl(K_LN_BWD_SHORT, st);
                 for (int first = 0, end = apart ? col_wgs : all; first < all; first = end, end = all) {
                     const dim3 grid((unsigned)(end - first));
 #define LSS_LN_BWD(NCH) hipLaunchKernelGGL(layernorm_bwd_short_kernel<NCH>, grid, dim3(1024), 0, st, x, gamma, mean, rstd, dy, (int)rows, E, dx, dgamma, dbeta, col_wgs, first)
@@ -435,6 +435,7 @@ hipError_t launch_layernorm_bwd(const bf16_t *x, const float *gamma, const float
                 return hipGetLastError();
             }
         }
+        TimedLaunch tl(K_LN_BWD, st);
         const int apart = overlaps(dx, bytes, x, bytes) || overlaps(dx, bytes, dy, bytes) ? LN_ROW_WGS : 0;     // the column kind alone first
         for (int first = apart, end = all; end > 0; end = first, first = 0) {
             const dim3 grid((unsigned)(end - first), (unsigned)std::min(n_parts, 32768), (unsigned)((n_parts + 32767) / 32768));

@@ -29,7 +29,8 @@ const char *const kNames[K_COUNT] = {"fwd_f32_kernel", "fwd_merge_kernel", "bwd_
                                      "layernorm_bwd_kernel", "layernorm_bwd_params_kernel", "gelu_fwd_kernel",
                                      "gelu_bwd_kernel", "proj_gemm_kernel:linear_fwd", "proj_gemm_kernel:linear_bwd_input",
                                      "residual_add_kernel", "wgrad_gemm_kernel", "fwd_bf16_kernel", "bwd_prep_bf16_kernel",
-                                     "bwd_skinny_bf16_kernel"};
+                                     "bwd_skinny_bf16_kernel", "layernorm_bwd_short_kernel", "proj_small_gemm_kernel:project_qkv",
+                                     "proj_small_gemm_kernel:project_bwd", "proj_small_gemm_kernel:linear_fwd", "proj_small_gemm_kernel:linear_bwd_input"};
 
 hipEvent_t get_event()
 {
