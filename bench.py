@@ -166,7 +166,8 @@ def layer_ops(args, w) -> int:
     torch.cuda.synchronize()
     timing.enable(False)
     kernels = read_kernels(2)
-    dom = max(("proj_gemm_kernel:linear_fwd", "proj_gemm_kernel:linear_bwd_input"), key=lambda n_: kernels[n_]["ms_per_step"])
+    linear = [n_ for n_ in kernels if n_.endswith((":linear_fwd", ":linear_bwd_input"))]       # (small tiles are a kernel of their own)
+    dom = max(linear, key=lambda n_: kernels[n_]["ms_per_step"])
     timing.reset()
     timing.select([k_ for k_, n_ in names.items() if n_ == dom])
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -192,6 +193,7 @@ def layer_ops(args, w) -> int:
         "layernorm_fwd_kernel": 4 * rows * E + 8 * rows + 8 * E,
         "layernorm_bwd_kernel": 6 * rows * E + 8 * rows + 4 * E + 8 * E * ((rows + 31) // 32),
         "layernorm_bwd_params_kernel": 8 * E * ((rows + 31) // 32) + 8 * E,
+        "layernorm_bwd_short_kernel": 6 * rows * E + 8 * rows + 12 * E,
         "gelu_fwd_kernel": 4 * rows * F, "gelu_bwd_kernel": 6 * rows * F,
         "residual_add_kernel": 16 * rows * E / 3.0,        # three launches: 3, 2 and 3 tensors of rows * E bf16
     }
@@ -199,7 +201,7 @@ def layer_ops(args, w) -> int:
         if name in bytes_per_launch:
             kk["algorithmic_GBps"] = round(bytes_per_launch[name] / (kk["avg_us"] * 1e-6) / 1e9, 1)
             kk["frac_of_hbm_peak"] = round(kk["algorithmic_GBps"] / PEAK_HBM_GBS, 4)
-        elif name.startswith("proj_gemm_kernel:linear_") or name == "wgrad_gemm_kernel":
+        elif name in linear or name == "wgrad_gemm_kernel":
             kk["algorithmic_tflops"] = round(lin_flops / (kk["avg_us"] * 1e-6) / 1e12, 2)
         kk["avg_us"] = round(kk["avg_us"], 2)
         kk["ms_per_step"] = round(kk["ms_per_step"], 4)
@@ -490,11 +492,13 @@ def attention(args, w, steps, warmup, with_cpu_baseline, min_warm_ms=0.0, min_ti
                 gbs = byts / (timed[dom]["avg_us"] * 1e-6) / 1e9
                 roofline.update({"bound": "hbm", "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                                  "frac": round(gbs / PEAK_HBM_GBS, 4), "achieved_tflops": round(achieved, 2)})
+        for name, flops in proj_flops.items():
+            ran = [n_ for n_ in (name, name.replace("proj_gemm", "proj_small_gemm")) if n_ in kernels]
+            if len(ran) == 1:       # (segments of one workload may take either tile kernel: no rate of one then)
+                kernels[ran[0]]["algorithmic_tflops"] = round(flops / (kernels[ran[0]]["ms_per_step"] * 1e-3) / 1e12, 2)
         for name, kk in kernels.items():
             if name in ALGO_PRODUCTS:
                 kk["algorithmic_tflops"] = round(ALGO_PRODUCTS[name] * 2.0 * w.d * pairs / (kk["ms_per_step"] * 1e-3) / 1e12, 2)
-            if name in proj_flops:
-                kk["algorithmic_tflops"] = round(proj_flops[name] / (kk["ms_per_step"] * 1e-3) / 1e12, 2)
             kk["avg_us"] = round(kk["avg_us"], 2)
             kk["ms_per_step"] = round(kk["ms_per_step"], 4)
         if "reduce_partials_kernel" in kernels and not (args.projections and args.weight_grads):   # (there it also adds row chunks)
