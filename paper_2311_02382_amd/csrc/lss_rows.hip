@@ -156,36 +156,36 @@ __device__ __forceinline__ void layernorm_bwd_row(const bf16_t *x, const float *
 {
     if (row >= rows) return;
     const int cpr = E / 8;
-            const float mu = mean[row], rs = rstd[row];
-            float xh[NCH][8], g[NCH][8];
-            float s1 = 0.f, s2 = 0.f;
+    const float mu = mean[row], rs = rstd[row];
+    float xh[NCH][8], g[NCH][8];
+    float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-            for (int k = 0; k < NCH; ++k) {
-                const int c = lane + 64 * k;
-                if (c < cpr) {
-                    float xv[8], dv[8];
-                    unpack8(*reinterpret_cast<const bf16x8 *>(x + (row * cpr + c) * 8), xv);
-                    unpack8(*reinterpret_cast<const bf16x8 *>(dy + (row * cpr + c) * 8), dv);
+    for (int k = 0; k < NCH; ++k) {
+        const int c = lane + 64 * k;
+        if (c < cpr) {
+            float xv[8], dv[8];
+            unpack8(*reinterpret_cast<const bf16x8 *>(x + (row * cpr + c) * 8), xv);
+            unpack8(*reinterpret_cast<const bf16x8 *>(dy + (row * cpr + c) * 8), dv);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        xh[k][e] = (xv[e] - mu) * rs;
-                        g[k][e] = dv[e] * gamma[c * 8 + e];
-                        s1 += g[k][e];
-                        s2 += g[k][e] * xh[k][e];
-                    }
-                }
+            for (int e = 0; e < 8; ++e) {
+                xh[k][e] = (xv[e] - mu) * rs;
+                g[k][e] = dv[e] * gamma[c * 8 + e];
+                s1 += g[k][e];
+                s2 += g[k][e] * xh[k][e];
             }
-            const float m1 = wave_sum(s1) / (float)E, m2 = wave_sum(s2) / (float)E;
+        }
+    }
+    const float m1 = wave_sum(s1) / (float)E, m2 = wave_sum(s2) / (float)E;
 #pragma unroll
-            for (int k = 0; k < NCH; ++k) {
-                const int c = lane + 64 * k;
-                if (c < cpr) {
-                    float o[8];
+    for (int k = 0; k < NCH; ++k) {
+        const int c = lane + 64 * k;
+        if (c < cpr) {
+            float o[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) o[e] = rs * (g[k][e] - m1 - xh[k][e] * m2);
-                    *reinterpret_cast<bf16x8 *>(dx + (row * cpr + c) * 8) = pack8(o);
-                }
-            }
+            for (int e = 0; e < 8; ++e) o[e] = rs * (g[k][e] - m1 - xh[k][e] * m2);
+            *reinterpret_cast<bf16x8 *>(dx + (row * cpr + c) * 8) = pack8(o);
+        }
+    }
 }
 // workgroups [first, first + gridDim.x) of those of a part; all of them by default, or one kind after the other if dx
 // stands in x's or dy's place
