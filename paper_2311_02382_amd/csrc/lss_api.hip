@@ -823,4 +823,25 @@ int lss_plan_bwd(int64_t s0, int64_t l_s, int64_t l_x, int64_t B, int64_t H, int
     return LSS_OK;
 }
 
+int lss_plan_linear(int op, int64_t rows, int64_t K, int64_t N, int *plan)
+{
+    if (op < 0 || op > 2 || rows < 1 || rows > INT32_MAX || K < 128 || N < 128 || K % 128 != 0 || N % 128 != 0 || K > 65536 || N > 65536)
+        return fail(LSS_ERR_SHAPE, "plan: no launch of such a call");
+    if (!plan) return fail(LSS_ERR_NULL, "plan: NULL");
+    plan[0] = lss::plan_linear(op, (int)rows, (int)K, (int)N, plan + 1);
+    return LSS_OK;
+}
+
+int lss_plan_project(int op, int64_t l_s, int64_t l_x, int64_t rows_valid, int64_t B, int64_t H, int64_t d, int *plan)
+{
+    if (int rc = check_shape(0, l_s, l_x, B, H, d)) return rc;
+    const int64_t E = H * d;
+    if (op < 0 || op > 2 || l_s == 0 || B == 0 || E % 128 != 0 || E > 65536 || (op > 0 && (rows_valid < 1 || rows_valid > l_x)))
+        return fail(LSS_ERR_SHAPE, "plan: no launch of such a call");
+    if (!plan) return fail(LSS_ERR_NULL, "plan: NULL");
+    if (op == 2) lss::plan_project_bwd_weight((int)l_s, (int)rows_valid, (int)B, (int)E, plan);
+    else plan[0] = lss::plan_project(op, (int)l_s, (int)l_x, (int)rows_valid, (int)B, (int)E);
+    return LSS_OK;
+}
+
 } // extern "C"

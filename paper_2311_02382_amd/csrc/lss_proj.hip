@@ -10,7 +10,7 @@
 // matrix instruction and the activations its B operand.  Each wavefront owns a WM x WN part.  The
 // contraction runs in tiles of 64 through a ring of STAGES LDS slots that are filled global -> LDS
 // directly, one barrier per tile.  The finished tile goes through LDS once more so that it is written to
-// memory as whole rows.  The tile is chosen per launch (launch_proj): 2048 x 512 -> 2048 takes 20.4 us in
+// memory as whole rows.  The tile is chosen per launch (pick_gemm_tile): 2048 x 512 -> 2048 takes 20.4 us in
 // 256 x 256 tiles and 14.0 as chosen, 2048 x 2048 -> 512 46.6 and 13.7 (one after the other, an event after each).
 // Matrix instructions of 16 x 16 x 32, not 32 x 32 x 16: loops on Gaussian operands (lss_microbench, section 7) reach 1700 TFLOP/s
 // with the former and 1630 with the latter in registers, 1500 and 1445 with an LDS read per 65,536 flop.  16384 x 4096 -> 1024:
@@ -25,6 +25,7 @@
 //          way into LDS, through registers; the contraction index runs over dK's columns, then
 //          dV's.  Jobs with bf16 A (dQ) share the launch.
 #include "lss_bf16.h"
+#include "lss_gemm_plan.h"
 #include "lss_kernels.h"
 
 #include <algorithm>
@@ -35,7 +36,7 @@ namespace lss {
 
 namespace {
 
-constexpr int PK = 64;                          // contraction tile
+constexpr int PK = kGemmK;                      // contraction tile
 constexpr int kLdsPerCu = 160 * 1024;
 
 // A workgroup's tile of C, its wavefronts' parts and its ring.  KG > 1: KG groups of wavefronts, each with a
@@ -74,7 +75,7 @@ enum { EPI_NONE = 0, EPI_GELU = 1, EPI_GELU_BWD = 2 };
 struct ProjArgs {
     ProjJob job[2];
     int n_jobs, lda, ldc, skip_tail;
-    int stream;                 // C is written past the caches (streams_results)
+    int stream;                 // C is written past the caches (gemm_streams)
     int zero_begin;             // first workgroup id of the tiles without data (of job 0; the others have none)
 };
 
@@ -677,110 +678,69 @@ hipError_t launch_proj_shape(ProjArgs &args, int kernel_id, hipStream_t st)
     return hipGetLastError();
 }
 
-// Whether C is written with non-temporal stores: where A and C together are more than half the last-level cache
-// (256 MB), results kept there and in the L2s only push out the operand tiles that other workgroups are about
-// to read again.  The product and a pass over its results right after it: 32768 x 512 -> 2048 with GeLU in the product 205 -> 175 us, GeLU
-// behind it 141 -> 132; 98304 x 1024 -> 2048 and -> 1024 more (projections of 4 x 24576 rows) 446 -> 434 alone; the gradient of 4 x 12000 rows of 512
-// columns 92 -> 87; 31 such pairs of 138 MB and more 3.6 % less time on average, the worst 1.6 % more.  Below that the product gains
-// as much, but who reads its results pays more (8192 x 1024 -> 4096 with GeLU and the next product 155 -> 159, 4096 rows 84 -> 94).
-bool streams_results(const ProjArgs &args, bool out_f32)
+// The shapes of lss_gemm_plan.h's tiles
+template <GemmTile T> struct TileShape;
+template <> struct TileShape<TILE_L> { using type = ShapeL; };
+template <> struct TileShape<TILE_M> { using type = ShapeM; };
+template <> struct TileShape<TILE_M2> { using type = ShapeM2; };
+template <> struct TileShape<TILE_M8> { using type = ShapeM8; };
+template <> struct TileShape<TILE_S> { using type = ShapeS; };
+template <> struct TileShape<TILE_S4> { using type = ShapeS4; };
+template <> struct TileShape<TILE_T4> { using type = ShapeT4; };
+template <> struct TileShape<TILE_T8> { using type = ShapeT8; };
+template <GemmTile T>
+constexpr bool tile_agrees()
 {
-    double bytes = 0.0;
+    using S = typename TileShape<T>::type;
+    return S::TM == kGemmTiles[T].tm && S::TN == kGemmTiles[T].tn && S::KG == kGemmTiles[T].groups && S::PER_CU == kGemmTiles[T].per_cu;
+}
+static_assert(tile_agrees<TILE_L>() && tile_agrees<TILE_M>() && tile_agrees<TILE_M2>() && tile_agrees<TILE_M8>() && tile_agrees<TILE_S>() &&
+              tile_agrees<TILE_S4>() && tile_agrees<TILE_T4>() && tile_agrees<TILE_T8>(), "the plan's table is about other shapes");
+
+int proj_work(const ProjArgs &args, GemmWork (&work)[2])
+{
     for (int j = 0; j < args.n_jobs; ++j) {
         const ProjJob &J = args.job[j];
-        bytes += (double)J.batches * ((double)std::min(J.rows, J.rows_ok) * J.K * (J.a_f32 ? 4 : 2) + (double)J.rows * J.N * (out_f32 ? 4 : 2));
+        work[j] = {J.batches, J.rows, J.rows_ok, J.N, J.K, J.a_f32};
     }
-    return bytes > 128e6;
+    return args.n_jobs;
 }
-
-// Which tile a launch takes: the one with the smallest estimated time.  A round of workgroups costs
-//     fixed + contraction tiles x per_tile   microseconds;
-// where compute units hold one workgroup each (PER_CU = 1: where half of them have one) a contraction tile takes
-// per_tile[0], where they are full per_tile[1].  The figures are fitted to linear_fwd and linear_bwd_input at 230 .. 98304 rows and
-// 512 .. 8192 columns either way (20 launches in a graph each), with the loop of 32 x 32 x 16 instructions that there was.  With the present
-// one, 70 drawn feed-forward units and projections in every tile: the choice costs 0.5 to 1.3 % over the best tile on average, 3 % in
-// project_bwd (at worst 28 us instead of 16) and in the projections' weight gradients.  (ShapeM8, ShapeT4 and ShapeT8 came later, fitted to
-// linear_fwd, bwd_input and bwd_weight at 58 .. 2048 rows and 256 .. 7680 columns: of 26 such maps in four products each none is slower than without
-// them, 40 are 5 to 42 % faster.)  Large tiles move the fewest bytes per flop
-// but a launch of few of them leaves compute units idle (2048 x 2048 -> 512: 16 workgroups of 256 x 256, 46 us;
-// 256 of 64 x 64, 12 us with the former loop), and where even 64 x 64 tiles leave one wavefront per SIMD the chain of contraction
-// tiles is what takes the time: four groups of wavefronts that share it took 9 us in a graph of them, 12 among other work now.
-struct GemmCost { double fixed, per_tile[2]; };
-template <typename S> constexpr GemmCost gemm_cost();
-template <> constexpr GemmCost gemm_cost<ShapeL>() { return {6.5, {1.40, 1.70}}; }
-template <> constexpr GemmCost gemm_cost<ShapeM>() { return {2.8, {0.62, 1.00}}; }
-template <> constexpr GemmCost gemm_cost<ShapeM2>() { return {3.0, {0.50, 0.58}}; }
-template <> constexpr GemmCost gemm_cost<ShapeS>() { return {2.5, {0.30, 0.40}}; }
-template <> constexpr GemmCost gemm_cost<ShapeS4>() { return {3.3, {0.165, 0.22}}; }
-template <> constexpr GemmCost gemm_cost<ShapeM8>() { return {2.5, {0.51, 0.585}}; }
-template <> constexpr GemmCost gemm_cost<ShapeT4>() { return {3.0, {0.117, 0.165}}; }
-template <> constexpr GemmCost gemm_cost<ShapeT8>() { return {3.2, {0.069, 0.107}}; }
-
-// `tiles`: contraction tiles of a workgroup on average, `rest_tiles`: of those in the last, part-filled round
-template <typename S>
-double gemm_estimate(double wgs, double tiles, double rest_tiles)
+bool proj_streams(const ProjArgs &args, bool out_f32)
 {
-    constexpr GemmCost c = gemm_cost<S>();
-    constexpr double room = 256.0 * S::PER_CU;
-    const double full = (double)(int64_t)(wgs / room), rest = wgs - full * room;
-    return full * (c.fixed + tiles * c.per_tile[1]) + (rest > 0 ? c.fixed + rest_tiles * c.per_tile[rest > (S::PER_CU == 1 ? 128 : 256)] : 0.0);
+    GemmWork work[2];
+    const int n = proj_work(args, work);
+    return gemm_streams(work, n, out_f32);
+}
+GemmTile proj_tile(const ProjArgs &args, bool a_any, bool streams)
+{
+    GemmWork work[2];
+    const int n = proj_work(args, work);
+    return pick_gemm_tile(work, n, a_any, args.skip_tail, streams);
 }
 
 template <bool A_ANY, bool W_TR, bool OUT_F32, int EPI = EPI_NONE>
 hipError_t launch_proj(ProjArgs &args, int kernel_id, hipStream_t st)
 {
-    auto estimate = [&](auto shape) {
-        using S = decltype(shape);
-        double wgs = 0, work = 0, last_n = 0, last_tiles = 0;
-        for (int j = 0; j < args.n_jobs; ++j) {
-            const ProjJob &J = args.job[j];
-            const double n = (double)J.batches * ((std::min(J.rows, J.rows_ok) + S::TM - 1) / S::TM) * ((J.N + S::TN - 1) / S::TN);
-            // A float A costs more the smaller the tile, whose workgroups re-read it more often, and the less of it
-            // fits the last-level cache (project_bwd, 1024 columns: 256 x 256 against 128 x 128 tiles take 64 and
-            // 57 us at 8192 rows, 102 and 97 at 16384, 156 and 165 at 24000)
-            double slow = 1.0, more = 0.0;
-            if (J.a_f32) {
-                const int zero_rows = args.skip_tail ? 0 : J.rows - std::min(J.rows, J.rows_ok);       // their stores pass through it too
-                const double bytes = (double)J.batches * ((double)J.rows_ok * J.K + (double)zero_rows * J.N) * 4.0;
-                const double far = bytes < 256e6 ? bytes / 256e6 : 1.0;
-                slow = S::TM == 256 ? 1.05 + 0.35 * far : S::TM == 128 ? 1.15 + 0.35 * far : 1.6 + 0.5 * far;
-                more = S::TM == 256 ? 1.5 : S::TM == 128 ? 6.0 + 2.0 * far : 0.0;
-            }
-            wgs += n;
-            last_n = n;
-            last_tiles = J.K / PK * slow + more;
-            work += n * last_tiles;
-        }
-        if (wgs <= 0) return 0.0;
-        const double room = 256.0 * S::PER_CU, rest = wgs - room * (double)(int64_t)(wgs / room), tiles = work / wgs;
-        return gemm_estimate<S>(wgs, tiles, rest <= last_n ? last_tiles : tiles);     // (the last job's workgroups start last)
-    };
-    // 128 x 128 tiles of which a compute unit holds one: a short contraction is all on its way at once in four slots, and nothing is left to add up
-    // (linear_fwd and bwd_input of 2048 x 512 -> 2048 9.9 -> 9.2 us, 9.7 -> 9.1; from 64 tiles on within 1 %).  Not with a float A, whose
-    // tiles travel through registers one at a time (project_bwd of 1500 x 2048 50.6 us in two groups, 54.2 so), nor for the weight
-    // gradients, both of whose operands are read transposed, more often in smaller parts (2048 x 2048 from 2048 rows 24.8 and 26.0).
-    using Mid = typename std::conditional<A_ANY, ShapeM2, ShapeM8>::type;
-    args.stream = streams_results(args, OUT_F32);
-    const double t[7] = {estimate(ShapeL{}), estimate(ShapeM{}), estimate(Mid{}), estimate(ShapeS{}), estimate(ShapeS4{}), estimate(ShapeT4{}),
-                         estimate(ShapeT8{})};
-    int best = 0;
-    for (int i = 1; i < (args.stream ? 5 : 7); ++i)
-        if (t[i] < t[best]) best = i;
-    switch (best) {
-    case 0: return launch_proj_shape<ShapeL, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
-    case 1: return launch_proj_shape<ShapeM, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
-    case 2: return launch_proj_shape<Mid, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
-    case 3: return launch_proj_shape<ShapeS, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
-    case 4: return launch_proj_shape<ShapeS4, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
-    case 5: return launch_proj_shape<ShapeT4, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
-    default: return launch_proj_shape<ShapeT8, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    args.stream = proj_streams(args, OUT_F32);
+    switch (proj_tile(args, A_ANY, args.stream)) {
+    case TILE_L: return launch_proj_shape<ShapeL, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    case TILE_M: return launch_proj_shape<ShapeM, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    case TILE_M2:
+        if constexpr (A_ANY) return launch_proj_shape<ShapeM2, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+        break;
+    case TILE_M8:
+        if constexpr (!A_ANY) return launch_proj_shape<ShapeM8, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+        break;
+    case TILE_S: return launch_proj_shape<ShapeS, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    case TILE_S4: return launch_proj_shape<ShapeS4, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    case TILE_T4: return launch_proj_shape<ShapeT4, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    case TILE_T8: return launch_proj_shape<ShapeT8, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    default: break;
     }
+    return hipErrorInvalidConfiguration;        // (pick_gemm_tile: none of the others)
 }
 
-} // namespace
-
-hipError_t launch_project_qkv(const bf16_t *x, const bf16_t *w_q, const bf16_t *w_kv, int64_t s0, int l_s, int l_x,
-                              int B, int E, bf16_t *q_seg, bf16_t *k, bf16_t *v, hipStream_t st)
+ProjArgs qkv_args(const bf16_t *x, const bf16_t *w_q, const bf16_t *w_kv, int64_t s0, int l_s, int l_x, int B, int E, bf16_t *q_seg, bf16_t *k, bf16_t *v)
 {
     ProjArgs args{};
     args.lda = args.ldc = E;
@@ -795,18 +755,17 @@ hipError_t launch_project_qkv(const bf16_t *x, const bf16_t *w_q, const bf16_t *
     }
     if (l_s > 0) {  // Q_i = x_i W_q
         ProjJob &J = args.job[n++];
-        J.a0 = x + s0 * E; J.a1 = nullptr; J.w = w_q; J.c0 = q_seg; J.c1 = nullptr;
+        J.a0 = x ? x + s0 * E : nullptr; J.a1 = nullptr; J.w = w_q; J.c0 = q_seg; J.c1 = nullptr;
         J.a_batch_stride = (int64_t)l_x * E; J.c_batch_stride = (int64_t)l_s * E;
         J.rows = J.rows_ok = l_s; J.batches = B;
         J.N = E; J.K = E; J.k_split = E; J.n_split = E; J.ldw = E;
     }
     args.n_jobs = n;
-    return launch_proj<false, true, false>(args, K_PROJ_FWD, st);
+    return args;
 }
 
-hipError_t launch_project_bwd(const bf16_t *dq, const float *dk_part, const float *dv_part, const bf16_t *w_q,
-                              const bf16_t *w_kv, int l_s, int l_x, int rows_valid, int B, int E, int skip_tail,
-                              float *dx_q, float *dx_part, hipStream_t st)
+ProjArgs bwd_args(const bf16_t *dq, const float *dk_part, const float *dv_part, const bf16_t *w_q, const bf16_t *w_kv, int l_s, int l_x, int rows_valid,
+                  int B, int E, int skip_tail, float *dx_q, float *dx_part)
 {
     ProjArgs args{};
     args.lda = args.ldc = E;
@@ -829,12 +788,11 @@ hipError_t launch_project_bwd(const bf16_t *dq, const float *dk_part, const floa
         J.a_f32 = 0;
     }
     args.n_jobs = n;
-    return launch_proj<true, false, true>(args, K_PROJ_BWD, st);
+    return args;
 }
 
 // c = a w for any row count: one job, one tall matrix; with gelu_c also gelu_c = GeLU(c)
-hipError_t launch_linear_fwd(const bf16_t *a, const bf16_t *w, int rows, int K, int N, bf16_t *c, bf16_t *gelu_c,
-                             hipStream_t st)
+ProjArgs linear_fwd_args(const bf16_t *a, const bf16_t *w, int rows, int K, int N, bf16_t *c, bf16_t *gelu_c)
 {
     ProjArgs args{};
     args.lda = K; args.ldc = N; args.skip_tail = 0; args.n_jobs = 1;
@@ -843,14 +801,12 @@ hipError_t launch_linear_fwd(const bf16_t *a, const bf16_t *w, int rows, int K, 
     J.a_batch_stride = J.c_batch_stride = 0;
     J.rows = J.rows_ok = rows; J.batches = 1;
     J.N = N; J.K = K; J.k_split = K; J.n_split = N; J.ldw = N;
-    if (gelu_c) return launch_proj<false, true, false, EPI_GELU>(args, K_LINEAR_FWD, st);
-    return launch_proj<false, true, false>(args, K_LINEAR_FWD, st);
+    return args;
 }
 
 // da = dc w^T: w as stored, [K][N], is the [output column][contraction index] layout read plainly;
 // with gelu_u, da = (dc w^T) * GeLU'(gelu_u)
-hipError_t launch_linear_bwd_input(const bf16_t *dc, const bf16_t *w, const bf16_t *gelu_u, int rows, int K, int N,
-                                   bf16_t *da, hipStream_t st)
+ProjArgs linear_bwd_input_args(const bf16_t *dc, const bf16_t *w, const bf16_t *gelu_u, int rows, int K, int N, bf16_t *da)
 {
     ProjArgs args{};
     args.lda = N; args.ldc = K; args.skip_tail = 0; args.n_jobs = 1;
@@ -859,54 +815,64 @@ hipError_t launch_linear_bwd_input(const bf16_t *dc, const bf16_t *w, const bf16
     J.a_batch_stride = J.c_batch_stride = 0;
     J.rows = J.rows_ok = rows; J.batches = 1;
     J.N = K; J.K = N; J.k_split = N; J.n_split = K; J.ldw = N;
+    return args;
+}
+
+} // namespace
+
+hipError_t launch_project_qkv(const bf16_t *x, const bf16_t *w_q, const bf16_t *w_kv, int64_t s0, int l_s, int l_x,
+                              int B, int E, bf16_t *q_seg, bf16_t *k, bf16_t *v, hipStream_t st)
+{
+    ProjArgs args = qkv_args(x, w_q, w_kv, s0, l_s, l_x, B, E, q_seg, k, v);
+    return launch_proj<false, true, false>(args, K_PROJ_FWD, st);
+}
+
+hipError_t launch_project_bwd(const bf16_t *dq, const float *dk_part, const float *dv_part, const bf16_t *w_q,
+                              const bf16_t *w_kv, int l_s, int l_x, int rows_valid, int B, int E, int skip_tail,
+                              float *dx_q, float *dx_part, hipStream_t st)
+{
+    ProjArgs args = bwd_args(dq, dk_part, dv_part, w_q, w_kv, l_s, l_x, rows_valid, B, E, skip_tail, dx_q, dx_part);
+    return launch_proj<true, false, true>(args, K_PROJ_BWD, st);
+}
+
+hipError_t launch_linear_fwd(const bf16_t *a, const bf16_t *w, int rows, int K, int N, bf16_t *c, bf16_t *gelu_c,
+                             hipStream_t st)
+{
+    ProjArgs args = linear_fwd_args(a, w, rows, K, N, c, gelu_c);
+    if (gelu_c) return launch_proj<false, true, false, EPI_GELU>(args, K_LINEAR_FWD, st);
+    return launch_proj<false, true, false>(args, K_LINEAR_FWD, st);
+}
+
+hipError_t launch_linear_bwd_input(const bf16_t *dc, const bf16_t *w, const bf16_t *gelu_u, int rows, int K, int N,
+                                   bf16_t *da, hipStream_t st)
+{
+    ProjArgs args = linear_bwd_input_args(dc, w, gelu_u, rows, K, N, da);
     if (gelu_u) return launch_proj<false, false, false, EPI_GELU_BWD>(args, K_LINEAR_BWD, st);
     return launch_proj<false, false, false>(args, K_LINEAR_BWD, st);
 }
 
-// The most chunks of rows a weight gradient is split into, per batch entry: what two 256 x 256 workgroups per
-// compute unit would take (wgrad_max_chunks: for any number of rows), of at least eight 64-row tiles each.
-// The scratch sizes the header promises follow from it.
-static int wgrad_max_chunks(int batches, int K, int N)
+int plan_linear(int op, int rows, int K, int N, int *chunks)
 {
-    const int tiles = ((K + 255) / 256) * ((N + 255) / 256);
-    return ((512 + tiles - 1) / tiles + batches - 1) / batches;
-}
-static int wgrad_most_chunks(int rows, int batches, int K, int N)
-{
-    const int R = (rows + PK - 1) / PK, want = wgrad_max_chunks(batches, K, N);
-    int chunk_tiles = (R + want - 1) / want;
-    if (chunk_tiles < 8) chunk_tiles = R < 8 ? R : 8;
-    return chunk_tiles < 1 ? 1 : (R + chunk_tiles - 1) / chunk_tiles;
-}
-// Tile and split of the rows: the pair with the smallest estimated time, the sum of the chunks' partial results
-// (3.5 us and their bytes at 4 TB/s) included; a chunk never crosses batch entries.  Shape-only,
-// deterministic.
-struct WgradPlan { int shape, splits_per_batch, chunk_rows; };
-static WgradPlan wgrad_plan(int rows, int batches, int K, int N, bool dc_f32)
-{
-    const int R = (rows + PK - 1) / PK, most = wgrad_most_chunks(rows, batches, K, N);
-    WgradPlan best{0, 1, PK};
-    double best_t = 0.0;
-    for (int want = 1; want <= most; want = want < 4 ? want + 1 : want + want / 3) {
-        const int chunk_tiles = (R + want - 1) / want, splits = (R + chunk_tiles - 1) / chunk_tiles;      // splits <= want
-        const double parts = (double)batches * splits;
-        const double sum = parts > 1 ? 3.5 + (parts + 1) * K * N * 4e-6 / 4.0 : 0.0;
-        auto estimate = [&](auto shape) {
-            using S = decltype(shape);
-            // (both operands through transposing reads: a fifth slower per tile, but for the largest)
-            // (32-wide tiles read every operand more often, from the last-level cache where it has just been written -- behind two copies, which
-            // the tables' launches were not: dW of 256 x 1024 from 2000 rows 17.9 -> 16.5 us, copies included, but from 4000, which larger tiles
-            // share out in chunks, 24.2 -> 26.9.  A float dC travels through registers, a tile at a time: of 256 x 512 from 1512 rows
-            // 25.3 -> 20.7, from 4064 27.8 -> 33.2)
-            const double tiles = chunk_tiles * (S::TM == 256 ? 1.0 : 1.2) * (S::TM != 32 ? 1.0 : dc_f32 ? 2.2 : chunk_tiles > 32 ? 1.3 : 1.0);
-            return sum + gemm_estimate<S>(parts * ((K + S::TM - 1) / S::TM) * ((N + S::TN - 1) / S::TN), tiles, tiles);
-        };
-        const double t[7] = {estimate(ShapeL{}), estimate(ShapeM{}), estimate(ShapeM2{}), estimate(ShapeS{}), estimate(ShapeS4{}), estimate(ShapeT4{}),
-                             estimate(ShapeT8{})};
-        for (int i = 0; i < 7; ++i)
-            if (best_t == 0.0 || t[i] < best_t) { best_t = t[i]; best = {i, splits, chunk_tiles * PK}; }
+    *chunks = 1;
+    if (op == 2) {
+        const WgradPlan p = pick_wgrad_plan(rows, 1, K, N, false);
+        *chunks = p.splits_per_batch;
+        return p.tile;
     }
-    return best;
+    const ProjArgs args = op == 0 ? linear_fwd_args(nullptr, nullptr, rows, K, N, nullptr, nullptr) : linear_bwd_input_args(nullptr, nullptr, nullptr, rows, K, N, nullptr);
+    return proj_tile(args, false, proj_streams(args, false));
+}
+int plan_project(int op, int l_s, int l_x, int rows_valid, int B, int E)
+{
+    const ProjArgs args = op == 0 ? qkv_args(nullptr, nullptr, nullptr, 0, l_s, l_x, B, E, nullptr, nullptr, nullptr)
+                                  : bwd_args(nullptr, nullptr, nullptr, nullptr, nullptr, l_s, l_x, rows_valid, B, E, 0, nullptr, nullptr);
+    return proj_tile(args, op == 1, proj_streams(args, op == 1));
+}
+void plan_project_bwd_weight(int l_s, int rows_valid, int B, int E, int *plan)
+{
+    const WgradPlan q = pick_wgrad_plan(l_s, B, E, E, false), kv = pick_wgrad_plan(rows_valid, B, E, 2 * E, true);
+    const int all[4] = {q.tile, q.splits_per_batch, kv.tile, kv.splits_per_batch};
+    std::copy(all, all + 4, plan);
 }
 
 static size_t wgrad_scratch_bytes(int rows, int batches, int K, int N)
@@ -932,20 +898,21 @@ static hipError_t launch_wgrad_shape(WgradArgs &g, hipStream_t st)
 template <bool DC_F32>
 static hipError_t launch_wgrad(WgradArgs &g, float *dw, float *scratch, hipStream_t st)
 {
-    const WgradPlan p = wgrad_plan(g.rows, g.batches, g.K, g.N, DC_F32);
+    const WgradPlan p = pick_wgrad_plan(g.rows, g.batches, g.K, g.N, DC_F32);
     g.splits_per_batch = p.splits_per_batch;
     g.chunk_rows = p.chunk_rows;
     const int splits = g.batches * g.splits_per_batch;
     g.out = splits > 1 ? scratch : dw;
     hipError_t e;
-    switch (p.shape) {
-    case 0: e = launch_wgrad_shape<ShapeL, DC_F32>(g, st); break;
-    case 1: e = launch_wgrad_shape<ShapeM, DC_F32>(g, st); break;
-    case 2: e = launch_wgrad_shape<ShapeM2, DC_F32>(g, st); break;
-    case 3: e = launch_wgrad_shape<ShapeS, DC_F32>(g, st); break;
-    case 4: e = launch_wgrad_shape<ShapeS4, DC_F32>(g, st); break;
-    case 5: e = launch_wgrad_shape<ShapeT4, DC_F32>(g, st); break;
-    default: e = launch_wgrad_shape<ShapeT8, DC_F32>(g, st); break;
+    switch (p.tile) {
+    case TILE_L: e = launch_wgrad_shape<ShapeL, DC_F32>(g, st); break;
+    case TILE_M: e = launch_wgrad_shape<ShapeM, DC_F32>(g, st); break;
+    case TILE_M2: e = launch_wgrad_shape<ShapeM2, DC_F32>(g, st); break;
+    case TILE_S: e = launch_wgrad_shape<ShapeS, DC_F32>(g, st); break;
+    case TILE_S4: e = launch_wgrad_shape<ShapeS4, DC_F32>(g, st); break;
+    case TILE_T4: e = launch_wgrad_shape<ShapeT4, DC_F32>(g, st); break;
+    case TILE_T8: e = launch_wgrad_shape<ShapeT8, DC_F32>(g, st); break;
+    default: e = hipErrorInvalidConfiguration; break;       // (pick_wgrad_plan: no other)
     }
     if (e != hipSuccess || splits == 1) return e;
     std::vector<const float *> parts(splits);

@@ -1,0 +1,46 @@
+// Goes over the choices of csrc/lss_gemm_plan.h on the host: a launch takes a tile that it has a kernel for, none of the others is estimated
+// shorter, and a weight gradient's chunks cover its rows within the scratch that the header promises.
+#include "lss_gemm_plan.h"
+
+#include <cstdio>
+#include <initializer_list>
+
+using namespace lss;
+
+static int fail(const char *what, const GemmWork &w, int tile)
+{
+    std::printf("%s: %d x %d of %d rows, K %d, N %d, float %d: tile %d\n", what, w.batches, w.rows_ok, w.rows, w.K, w.N, w.a_f32, tile);
+    return 1;
+}
+
+int main()
+{
+    for (int batches : {1, 4, 65535})
+        for (int rows : {1, 31, 58, 256, 1000, 2048, 16384, 98304, 0x7fffffff})
+            for (int ok : {1, 64, 0x7fffffff})
+                for (int K : {128, 512, 2048, 65536})
+                    for (int N : {128, 640, 4096, 65536})
+                        for (int form = 0; form < 4; ++form) {
+                            if (ok < rows && ok > 64) ok = rows;
+                            const bool any = form & 1, skip = form & 2;
+                            const GemmWork work[2] = {{batches, rows, ok, N, K, any}, {batches, rows, rows, N, K, 0}};
+                            for (int n : {1, 2})
+                                for (bool streams : {false, true}) {
+                                    const GemmTile t = pick_gemm_tile(work, n, any, skip, streams);
+                                    if (t < 0 || t >= TILE_COUNT || t == (any ? TILE_M8 : TILE_M2) || (streams && kGemmTiles[t].tm == 32)) return fail("no such kernel", work[0], t);
+                                    const double us = gemm_launch_estimate(t, work, n, skip);
+                                    if (!(us > 0.0)) return fail("no time", work[0], t);
+                                    for (int o = 0; o < TILE_COUNT; ++o)
+                                        if (o != (any ? TILE_M8 : TILE_M2) && !(streams && kGemmTiles[o].tm == 32) && gemm_launch_estimate((GemmTile)o, work, n, skip) < us)
+                                            return fail("a shorter one is there", work[0], t);
+                                }
+                            if (rows > 1 << 20) continue;
+                            const WgradPlan p = pick_wgrad_plan(rows, batches, K, N, any);
+                            if (p.tile < 0 || p.tile >= TILE_COUNT || p.tile == TILE_M8) return fail("no such weight gradient", work[0], p.tile);
+                            if (p.splits_per_batch < 1 || p.splits_per_batch > wgrad_most_chunks(rows, batches, K, N) || p.splits_per_batch > wgrad_max_chunks(batches, K, N) ||
+                                p.chunk_rows % kGemmK != 0 || (int64_t)p.splits_per_batch * p.chunk_rows < rows || (int64_t)(p.splits_per_batch - 1) * p.chunk_rows >= rows)
+                                return fail("chunks", work[0], p.tile);
+                        }
+    std::printf("clean\n");
+    return 0;
+}

@@ -31,6 +31,10 @@ def test_forward_plan_takes_a_short_one_of_the_measured_forms(tmp_path):
     _run(tmp_path, "fwd_plan_check")
 
 
+def test_product_plan_takes_a_tile_there_is_a_kernel_for(tmp_path):
+    _run(tmp_path, "gemm_plan_check")
+
+
 def test_results_of_large_products_are_stored_past_the_caches(tmp_path):
     # Two stores that differ in the non-temporal hint only are one plain store to the compiler's middle end: what counts is the
     # generated code.  Every kernel of the projection GEMM has both kinds.
