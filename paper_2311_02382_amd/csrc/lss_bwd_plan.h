@@ -114,16 +114,24 @@ inline BwdPlan pick_bwd_plan(const SegShape &s, bool with_drop, int most, bool m
 // compute units are busy 12 % fewer cycles, but at a lower clock, 2.40 ms instead of 2.36.  50 launches, forward and backward:
 // those of 24 walks and less 0 to 12 % faster, 4.3 % on average (8 heads of 770 rows behind 1654: 82 -> 72 us, 4 of 813: 52 -> 49); above, 2 %
 // slower on average.
-// At d = 64 where the launch has no more than one workgroup of one group per compute unit, rows that no query sees not counted: wavefronts that are
-// alone on their SIMD wait for their own chains, which are half as long with 16 rows, and the LDS has time for twice the reads.  Of 55 such
-// launches (65 .. 4096 rows) one took 11 % longer, the others 3 to 14 % less, 5.4 % on average (4 heads of 256 rows behind 768: 15.6 us, 14.2;
-// with dropout 13 launches 7 %); of 256 to 320 workgroups 8 % more on average, past 1024 24 %.
+// At d = 64 where every compute unit gets at most one workgroup of one group, rows that no query sees aside: wavefronts that are
+// alone on their SIMD wait for their own chains, which are half as long with 16 rows, and the LDS has time for twice the reads (4 heads of 256
+// rows behind 768: 15.6 us, 14.2).  But not with
+//   * more than 32 workgroups of either kind on an XCD, which waits for the one that comes last: with 252 to 256 of them and 33 on some
+//     XCD 7 % more time on average, at worst 20 % (15 heads of 374 rows against 1351: 26.4 us, 30.4), with 32 on each 3.6 % less;
+//   * many tiles to clear: a compute unit holds one workgroup of this form and two of the other, beside which they are cleared from the start; here the
+//     idle ones have to clear them in the others' time, some 1.8 us a tile -- and the others a few of them at the end, which 32 idle ones stand for
+//     (6 heads of 339 rows behind 3069 of 34,850, 1470 tiles on four idle units: 24.6 us, 31.7; 24 of 123 behind 103 of 3718, 648 on 184: 17.1, 15.3).
+// 11,200 launches of 65 .. 4096 rows that pass the first line, in either form: 5 % less time than the wider one, 0.2 % over the better one (0.6 % without the second line).
 inline bool bwd_narrow(const SegShape &s, int n_splits, int groups)
 {
     const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x, bhs = (int64_t)s.B * s.H;
     const int64_t dkv = (seen + 127) / 128 * bhs, dq = (int64_t)((s.l_s + 127) / 128) * bhs * n_splits;
-    if (s.d == 64) return s.l_s > kSkinnyRows && groups == 1 && dq + dkv <= 256;
-    return dkv * ((s.l_s + 63) / 64) <= 32 * 256;
+    if (s.d != 64) return dkv * ((s.l_s + 63) / 64) <= 32 * 256;
+    if (s.l_s <= kSkinnyRows || groups != 1 || (dq + 7) / 8 + (dkv + 7) / 8 > 32) return false;
+    const int64_t zeros = s.skip_tail ? 0 : (s.l_x - seen) / 128 * bhs;
+    const double row_us = 1.35 * (double)((s.l_s + 63) / 64), key_us = (double)(((seen + 63) / 64 + n_splits - 1) / n_splits);
+    return (double)zeros * 1.8 <= ((row_us > key_us ? row_us : key_us) + 4.0) * (double)(dq + dkv < 224 ? 256 - dq - dkv : 32);
 }
 
 // A whole backward launch.  one_pass: the kernel that makes all three gradients of a short segment (bf16, d = 64); own: no
