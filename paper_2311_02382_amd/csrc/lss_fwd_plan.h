@@ -56,7 +56,8 @@ inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
          {2, {{FWD_8x1, 256, 1, 1, 2.55, 4.36, 2.525, 0.0, 0.556, 0.563}, {FWD_4x2, 128, 2, 1, 5.97, 2.31, 2.859, 0.0, 0.489, 1.000}}, 2.85, 4.19, true}}};
     const Table &table = tables[s.d == 128][with_drop];
     const double out_mb = (double)s.B * s.H * s.l_s * s.d * 1e-6;     // elements
-    const int64_t most = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x, tiles = (most + 63) / 64;
+    const int64_t most = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x;
+    const int tiles = (int)((most + 63) / 64);
     const double kv_us = (double)s.B * s.H * most * s.d * 4.0 / 4.4e6;
     const bool few_rows = (int64_t)((s.l_s + 63) / 64) * s.B * s.H <= 16;       // at most 16 workgroups of 64 rows
     FwdPlan best{table.form[0].form, 1};
@@ -67,13 +68,14 @@ inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
         const int rest = s.l_s - (int)(q_tiles - 1) * c->rows;
         const double last = c->idle + (1.0 - c->idle) * (double)((rest + 31) / 32) * 32.0 / c->rows, all = ((double)(q_tiles - 1) + last) / (double)q_tiles;
         for (int sp = 1; sp <= max_splits; ++sp) {
-            if (sp > 1 && tiles / (sp * c->groups) < 2) break;      // shorter ones cost more than they gain
             const double W = (double)(q_tiles * s.B * s.H * sp);
+            if (c->groups == 4 && W > 256.0) break;                 // (see above)
+            if (sp > 1 && tiles / (sp * c->groups) < 2) break;      // shorter ones cost more than they gain
             // At most 16 workgroups for eight tiles and more: split in any case, as these launches always were and as the
             // tests of the merge's rounding expect of them.  It costs them 0 to 1.5 us (4 heads of 256 rows behind 256: 9.7
             // instead of 8.3) and 0.1 % over all those launches.
             if (sp == 1 && max_splits > 1 && W <= 16.0 && tiles >= 8) continue;
-            if (c->groups == 4 && (W <= 16.0 || W > 256.0 || (few_rows && tiles >= 8))) continue;      // (nor do those few change their form; see above)
+            if (c->groups == 4 && (W <= 16.0 || (few_rows && tiles >= 8))) continue;      // (nor do those few change their form)
             const double longest = (double)(((tiles + sp - 1) / sp + c->groups - 1) / c->groups);
             const double average = mean_tiles / (sp * c->groups) + (sp * c->groups > 1 ? 0.5 : 0.0);
             const double rounds = ceil(W / 256.0), n = rounds < c->per_cu ? rounds : (double)c->per_cu;
@@ -87,8 +89,9 @@ inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
             double t = c->start + c->tile_us * (walk > share ? walk : share);
             // (four groups that do not all have a tile at the end, or not on every compute unit, read less at once)
             const double kv = kv_us * (c->groups == 4 ? sqrt(sqrt(256.0 / W)) * (longest * 4.0 * sp / (double)tiles) : 1.0);
-            t = sqrt(sqrt(t * t * t * t + kv * kv * kv * kv));
-            if (sp > 1) t += table.merge + out_mb * (8 * sp + 2) / table.mb_per_us;
+            const double merge = sp > 1 ? table.merge + out_mb * (8 * sp + 2) / table.mb_per_us : 0.0;
+            if (best_t > 0.0 && (t > kv ? t : kv) + merge >= best_t) continue;      // (most of a call's up to 60 estimates: two roots each, half the time)
+            t = sqrt(sqrt(t * t * t * t + kv * kv * kv * kv)) + merge;
             if (best_t == 0.0 || t < best_t) { best_t = t; best = {c->form, sp}; }
         }
     }

@@ -80,6 +80,24 @@ inline double gemm_launch_estimate(GemmTile t, const GemmWork *work, int n, bool
     return gemm_estimate(c, wgs, tiles, rest <= last_n ? last_tiles : tiles);     // (the last job's workgroups start last)
 }
 
+// Rows of C without data are cleared by workgroups of their own, 64 KB each whatever the tile.  By tiles, those of the 32- and
+// 64-wide ones -- 512 or 1024 threads that store 4 to 16 KB, one of which fills a compute unit's LDS -- took longer than their bytes: project_bwd of
+// 43,186 rows of 128 columns of which 2081 have data, 10.6 us in 64 x 64 tiles and 20.0 in 32 x 32 ones, which the estimates then chose: they leave these
+// rows out, whose time hardly depends on the tile now.
+// gemm_zero_end: the end of the rows to clear (skip_tail leaves those from the next multiple of 256 on unwritten); gemm_zero_tiles: workgroups per
+// batch entry and tile of columns, gemm_zero_rows() rows each.  The last tile of rows with data clears its own rest.
+constexpr int gemm_zero_rows(int tn) { return 16384 / tn; }
+inline int gemm_zero_end(int rows, int rows_ok, bool skip_tail)
+{
+    const int64_t next = ((int64_t)rows_ok + 255) / 256 * 256;
+    return skip_tail && next < rows ? (int)next : rows;
+}
+inline int gemm_zero_tiles(int rows, int rows_ok, bool skip_tail, int tm, int tn)
+{
+    const int64_t done = ((int64_t)(rows < rows_ok ? rows : rows_ok) + tm - 1) / tm * tm, left = gemm_zero_end(rows, rows_ok, skip_tail) - done;
+    return left > 0 ? (int)((left + gemm_zero_rows(tn) - 1) / gemm_zero_rows(tn)) : 0;
+}
+
 // The tile of a launch: the one with the smallest estimate.
 // 128 x 128 tiles of which a compute unit holds one: a short contraction is all on its way at once in four slots, and nothing is left to add up
 // (linear_fwd and bwd_input of 2048 x 512 -> 2048 9.9 -> 9.2 us, 9.7 -> 9.1; from 64 tiles on within 1 %).  Not with a float A, whose

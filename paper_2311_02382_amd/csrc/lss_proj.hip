@@ -64,7 +64,7 @@ struct ProjJob {
     int rows, rows_ok;          // rows per batch; leading rows of A that hold data (the rest count as 0)
     int batches, N, K, k_split, n_split, ldw;
     int a_f32;                  // A is float (only in kernels compiled with A_ANY)
-    int wg_begin, m_tiles, m_data, n_tiles;     // first workgroup id of the job; row tiles per batch, those with data; column tiles
+    int wg_begin, m_data, n_tiles;              // first workgroup id of the job; row tiles with data per batch; column tiles
 };
 // What happens to a finished bf16 tile on its way to memory (the feed-forward unit, whose GeLU
 // would otherwise be a pass over memory of its own):
@@ -76,7 +76,8 @@ struct ProjArgs {
     ProjJob job[2];
     int n_jobs, lda, ldc, skip_tail;
     int stream;                 // C is written past the caches (gemm_streams)
-    int zero_begin;             // first workgroup id of the tiles without data (of job 0; the others have none)
+    // rows of job 0 that have no data (the others have none): first workgroup id, workgroups per batch and column tile, end of the rows to clear
+    int zero_begin, zero_tiles, zero_end;
 };
 
 // Operand tile [64 k][COLS], to be read transposed.  Loaded directly like a DirectTile.  Its rows start
@@ -309,56 +310,72 @@ __device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
     // Row tiles with data first, of all batches and jobs, then those without, each kind spread over all XCDs: with 28 % of two
     // batches' rows valid (59,486 x 1024 floats) a plain numbering left all products to three or four of the
     // eight XCDs, 375 us.
-    const bool data = (int)blockIdx.x < args.zero_begin;
-    const int per_batch = data ? J.m_data : J.m_tiles - J.m_data;
+    const bool data = !A_ANY || (int)blockIdx.x < args.zero_begin;      // (no other product has rows without data)
+    const int per_batch = data ? J.m_data : args.zero_tiles;
     const TileId tile = xcd_tile(blockIdx.x - (data ? J.wg_begin : args.zero_begin), J.batches * per_batch, J.n_tiles);
     if (!tile.ok) return;
-    const int batch = tile.m / per_batch, m0 = (tile.m % per_batch + (data ? 0 : J.m_data)) * S::TM, n0 = tile.n * S::TN;
+    const int batch = tile.m / per_batch, n0 = tile.n * S::TN;
+    const int m0 = data ? tile.m % per_batch * S::TM : J.m_data * S::TM + tile.m % per_batch * gemm_zero_rows(S::TN);
 
-    const int rows_here = min(J.rows - m0, S::TM);                      // rows of C this tile owns
+    const int rows_here = data ? min(J.rows - m0, S::TM) : min(args.zero_end - m0, gemm_zero_rows(S::TN));      // rows of C this workgroup owns
     const int rows_data = min(min(J.rows, J.rows_ok) - m0, S::TM);      // of which this many have data in A
-    const int cols_here = min(J.N - n0, S::TN);                         // a multiple of 64
+    const int cols_here = min(J.N - n0, S::TN);                         // a multiple of 32
+
+    // (copies: the loads' assembly counts as a write to memory, after which what is read through `J` is fetched again, by scalar loads that a
+    // finished tile would wait for before its first store: 1 % of all launches)
+    const int ldc = args.ldc, n_split = J.n_split;
+    int stream = STREAMS ? args.stream : 0;
+    asm("" : "+s"(stream));
+    const int64_t c_tile0 = (int64_t)batch * J.c_batch_stride + (int64_t)m0 * ldc;
+    OutT *const c0 = static_cast<OutT *>(J.c0) + c_tile0, *const c1 = static_cast<OutT *>(J.c1) + c_tile0;
+    const bf16_t *const gelu_u = static_cast<const bf16_t *>(J.a1) + c_tile0;         // (EPI_GELU_BWD)
 
     auto put16 = [&](void *to, f32x4 v) __attribute__((always_inline)) {
-        if (STREAMS && args.stream) {
+        if (STREAMS && stream) {
             asm volatile("");       // (two stores that differ in this respect only are merged into one plain store, ahead of the branch or behind it)
             __builtin_nontemporal_store(v, static_cast<f32x4 *>(to));
             asm volatile("");
         } else *static_cast<f32x4 *>(to) = v;
     };
-    auto store_tiles = [&](const f32x4 (&acc)[S::MB][S::NB], bool from_acc) {
-        OutT *c0 = static_cast<OutT *>(J.c0) + (int64_t)batch * J.c_batch_stride + (int64_t)m0 * args.ldc;
-        OutT *c1 = static_cast<OutT *>(J.c1) + (int64_t)batch * J.c_batch_stride + (int64_t)m0 * args.ldc;
+    if (!data) {
+        constexpr int CPR = S::TN / Store::CW, ROWS_PER_IT = S::NT / CPR;
+        int t = tid;
+        asm("" : "+v"(t));      // (or column and row are worked out ahead of the branch and kept in registers for the other side's stores)
+        const int col = t % CPR * Store::CW;
+        if (col < cols_here)
+            for (int m = t / CPR; m < rows_here; m += ROWS_PER_IT) put16(c0 + n0 + col + (int64_t)m * ldc, f32x4{0.f, 0.f, 0.f, 0.f});
+        return;
+    }
+    auto store_tiles = [&](const f32x4 (&acc)[S::MB][S::NB]) {
+        int t = tid;
+        if constexpr (A_ANY && S::TM == 256) asm("" : "+v"(t));       // (what is worked out from it is not kept through the loop, which spills)
 #pragma unroll
         for (int pass = 0; pass < Store::PASSES; ++pass) {
-            if (from_acc) {
-                __syncthreads();        // every wavefront is done with what the LDS held
-                if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, lane, rows_data);
-                __syncthreads();
-            }
-            const int c = tid % Store::CPR, col = pass * Store::CPP + c * Store::CW;
+            __syncthreads();        // every wavefront is done with what the LDS held
+            if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, t & 63, rows_data);
+            __syncthreads();
+            const int c = t % Store::CPR, col = pass * Store::CPP + c * Store::CW;
             const int n = n0 + col;         // column of C; a chunk never straddles n_split
-            OutT *dst = n < J.n_split ? c0 + n : c1 + (n - J.n_split);
+            OutT *dst = n < n_split ? c0 + n : c1 + (n - n_split);
 #pragma unroll
             for (int i = 0; i < Store::ITS; ++i) {
-                const int m = i * Store::ROWS_PER_IT + tid / Store::CPR;
+                const int m = i * Store::ROWS_PER_IT + t / Store::CPR;
                 f32x4 raw = {0.f, 0.f, 0.f, 0.f};
-                if (from_acc && m < S::TM) raw = *reinterpret_cast<const f32x4 *>(smem + Store::offset(m, c));
+                if (m < S::TM) raw = *reinterpret_cast<const f32x4 *>(smem + Store::offset(m, c));
                 if (col < cols_here && m < rows_here) {
                     if constexpr (EPI == EPI_GELU_BWD) {
-                        const bf16_t *u = static_cast<const bf16_t *>(J.a1) + (int64_t)batch * J.c_batch_stride + (int64_t)(m0 + m) * args.ldc + n;
-                        const bf16x8 uu = *reinterpret_cast<const bf16x8 *>(u);
+                        const bf16x8 uu = *reinterpret_cast<const bf16x8 *>(gelu_u + (int64_t)m * ldc + n);
                         bf16x8 cv = __builtin_bit_cast(bf16x8, raw);
 #pragma unroll
                         for (int e = 0; e < 8; ++e) cv[e] = (bf16_t)((float)cv[e] * gelu_slope((float)uu[e]));
                         raw = __builtin_bit_cast(f32x4, cv);
                     }
-                    put16(dst + (int64_t)m * args.ldc, raw);
+                    put16(dst + (int64_t)m * ldc, raw);
                     if constexpr (EPI == EPI_GELU) {
                         bf16x8 cv = __builtin_bit_cast(bf16x8, raw);
 #pragma unroll
                         for (int e = 0; e < 8; ++e) cv[e] = (bf16_t)gelu_value((float)cv[e]);
-                        put16(c1 + n + (int64_t)m * args.ldc, __builtin_bit_cast(f32x4, cv));
+                        put16(c1 + n + (int64_t)m * ldc, __builtin_bit_cast(f32x4, cv));
                     }
                 }
             }
@@ -367,11 +384,6 @@ __device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
 
     f32x4 acc[S::MB][S::NB];
     gemm_clear<S>(acc);
-    if (rows_data <= 0) {       // no row of this tile has data: its rows of C are zero
-        // (skip_tail leaves the rows unwritten from the next multiple of 256 on, whatever the tile)
-        if (!args.skip_tail || m0 < (J.rows_ok + 255) / 256 * 256) store_tiles(acc, false);
-        return;
-    }
 
     const int T = J.K / PK;
     const int t_split = J.k_split / PK;
@@ -460,7 +472,7 @@ __device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
     };
     gemm_loop<S, LOADS, !A_ANY>(acc, T, group, a_f32, issue, load, [](int, int) {}, fetch_a, [&](int, int slot) { stash_a(slot); });
     gemm_add_groups<S>(smem, acc, group, wave, lane);
-    store_tiles(acc, true);
+    store_tiles(acc);
 }
 template <typename S, bool A_ANY, bool W_TR, bool OUT_F32, int EPI>
 __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void proj_gemm_kernel(ProjArgs args)
@@ -656,14 +668,16 @@ hipError_t launch_proj_shape(ProjArgs &args, int kernel_id, hipStream_t st)
     int wgs = 0;
     for (int j = 0; j < args.n_jobs; ++j) {
         ProjJob &J = args.job[j];
-        J.m_tiles = (J.rows + S::TM - 1) / S::TM;
         J.n_tiles = (J.N + S::TN - 1) / S::TN;
         J.m_data = (std::min(J.rows, J.rows_ok) + S::TM - 1) / S::TM;
         J.wg_begin = wgs;
         wgs += xcd_tile_grid(J.batches * J.m_data, J.n_tiles);
     }
+    const ProjJob &first = args.job[0];
     args.zero_begin = wgs;
-    wgs += xcd_tile_grid(args.job[0].batches * (args.job[0].m_tiles - args.job[0].m_data), args.job[0].n_tiles);
+    args.zero_end = gemm_zero_end(first.rows, first.rows_ok, args.skip_tail);
+    args.zero_tiles = gemm_zero_tiles(first.rows, first.rows_ok, args.skip_tail, S::TM, S::TN);
+    wgs += xcd_tile_grid(first.batches * args.zero_tiles, first.n_tiles);
     if (wgs == 0) return hipSuccess;
     static DeviceOnce once;
     constexpr bool SMALL = S::TM == 32;

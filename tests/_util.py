@@ -86,3 +86,21 @@ def fwd_plan(B, l_x, H, d, s0, l_s, causal, drop=False, elem_bytes=2):
 def bwd_plan(B, l_x, H, d, s0, l_s, causal, drop=False, elem_bytes=2, over_out=False):
     """What a backward call launches (csrc/lss_plan.h)."""
     return _plan("lss_plan_bwd", BwdPlan, s0, l_s, l_x, B, H, d, causal, drop, elem_bytes, over_out)
+
+
+# Tiles of the products (GemmTile of csrc/lss_gemm_plan.h)
+TILES = ("256x256", "128x128", "128x128 by two", "128x128 of eight", "64x64", "64x64 by four", "32x64", "32x32")
+
+
+def linear_plan(op, rows, K, N):
+    """(tile, chunks of rows) of linear_fwd (op 0), linear_bwd_input (1) or linear_bwd_weight (2)."""
+    plan, i64 = (ctypes.c_int * 2)(), ctypes.c_int64
+    lss._check(lss.load().lss_plan_linear(ctypes.c_int(op), i64(rows), i64(K), i64(N), plan))
+    return TILES[plan[0]], plan[1]
+
+
+def project_plan(op, B, l_x, H, d, l_s, rows_valid):
+    """The tile of project_qkv (op 0) or project_bwd (1); tile and chunks of dW_q, tile and chunks of dW_kv (2)."""
+    plan, i64 = (ctypes.c_int * 4)(), ctypes.c_int64
+    lss._check(lss.load().lss_plan_project(ctypes.c_int(op), *map(i64, (l_s, l_x, rows_valid, B, H, d)), plan))
+    return (TILES[plan[0]], plan[1], TILES[plan[2]], plan[3]) if op == 2 else TILES[plan[0]]

@@ -1,5 +1,6 @@
 // Goes over the choices of csrc/lss_gemm_plan.h on the host: a launch takes a tile that it has a kernel for, none of the others is estimated
-// shorter, and a weight gradient's chunks cover its rows within the scratch that the header promises.
+// shorter, a weight gradient's chunks cover its rows within the scratch that the header promises, and the rows without data are cleared 16384 elements at a
+// time whatever the tile.
 #include "lss_gemm_plan.h"
 
 #include <cstdio>
@@ -41,6 +42,17 @@ int main()
                                 p.chunk_rows % kGemmK != 0 || (int64_t)p.splits_per_batch * p.chunk_rows < rows || (int64_t)(p.splits_per_batch - 1) * p.chunk_rows >= rows)
                                 return fail("chunks", work[0], p.tile);
                         }
+    for (int rows : {1, 31, 32, 33, 255, 256, 257, 511, 4096, 50112, 0x7fffffff})
+        for (int ok : {0, 1, 31, 32, 64, 200, 256, 300, 4095, 4096, 50112, 0x7fffffff})
+            for (bool skip : {false, true})
+                for (const GemmTileCost &c : kGemmTiles) {
+                    if (ok > rows) continue;
+                    const int64_t done = ((int64_t)ok + c.tm - 1) / c.tm * c.tm, end = skip ? ((int64_t)ok + 255) / 256 * 256 : rows;
+                    const int tiles = gemm_zero_tiles(rows, ok, skip, c.tm, c.tn), zero_end = gemm_zero_end(rows, ok, skip), each = gemm_zero_rows(c.tn);
+                    if (zero_end != (end < rows ? end : rows) || each * c.tn != 16384 || tiles > ((int64_t)rows - ok + each - 1) / each ||
+                        done + (int64_t)tiles * each < zero_end || (tiles > 0 && done + (int64_t)(tiles - 1) * each >= zero_end))
+                        return fail("rows without data", {1, rows, ok, 128, 128, 1}, c.tm);
+                }
     std::printf("clean\n");
     return 0;
 }

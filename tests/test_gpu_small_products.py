@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2311_02382_amd import lss, synth
-from _util import Staged, TOL, rel_err, to_np
+from _util import Staged, TOL, project_plan, rel_err, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -62,3 +62,32 @@ def test_projections_in_small_tiles(B, l_x, H, s0, l_s):
     assert rel_err(to_np(dwkv[:, :E]), rows.T @ dkf.reshape(-1, E)) <= t
     assert rel_err(to_np(dwkv[:, E:]), rows.T @ dvf.reshape(-1, E)) <= t
     assert rel_err(to_np(dwq), X.f64[:, s0:rv].reshape(-1, E).T @ DQ.f64.reshape(-1, E)) <= t
+
+
+@pytest.mark.parametrize("skip_tail", [False, True])
+@pytest.mark.parametrize("tile,B,l_x,H,l_s,rows_valid", [
+    ("32x32", 1, 340, 2, 22, 24), ("32x32", 3, 700, 2, 32, 32), ("32x64", 1, 1280, 2, 89, 931), ("64x64 by four", 1, 612, 14, 14, 292),
+    ("64x64", 2, 2276, 2, 98, 1946), ("128x128 by two", 1, 2303, 16, 88, 1988), ("128x128", 2, 2449, 16, 117, 2124), ("256x256", 1, 17000, 8, 200, 16500),
+])
+def test_rows_without_data_are_cleared(tile, B, l_x, H, l_s, rows_valid, skip_tail):
+    """project_bwd clears them 64 KB at a time, whatever its tile: to the last row and no further, and with skip_masked_tail to the next multiple of 256."""
+    d, E = 64, 64 * H
+    assert project_plan(1, B, l_x, H, d, l_s, rows_valid) == tile
+    gen = torch.Generator(device="cuda").manual_seed(l_x + rows_valid)
+    WQ, WKV, DQ = ((torch.randn(shape, generator=gen, device="cuda") * std).to(torch.bfloat16)
+                   for shape, std in (((E, E), E ** -0.5), ((E, 2 * E), E ** -0.5), ((B, l_s, H, d), 1.0)))
+    dk, dv = (torch.randn((B, l_x, H, d), generator=gen, device="cuda") for _ in range(2))
+    dk[:, rows_valid:] = float("nan")
+    dv[:, rows_valid:] = float("nan")
+    canary = -7.25
+    room = torch.full((B * l_x + 512, E), canary, device="cuda")
+    dx_q, dx = lss.lss_project_bwd(DQ, dk, dv, WQ, WKV, rows_valid, dx_partial=room[:B * l_x].view(B, l_x, E), skip_masked_tail=skip_tail)
+    end = min(l_x, -(-rows_valid // 256) * 256) if skip_tail else l_x
+    assert not dx[:, rows_valid:end].any() and (dx[:, end:] == canary).all() and (room[B * l_x:] == canary).all()
+    W = WKV.double()
+    for b in range(B):
+        rows = torch.cat([t[b, :rows_valid].reshape(-1, E).to(torch.bfloat16).double() for t in (dk, dv)], 1)
+        want = rows @ torch.cat([W[:, :E], W[:, E:]], 1).T
+        assert (dx[b, :rows_valid].double() - want).abs().max() <= TOL["f32"]["t"] * want.abs().max()
+        want = DQ[b].reshape(-1, E).double() @ WQ.double().T
+        assert (dx_q[b].double() - want).abs().max() <= TOL["f32"]["t"] * want.abs().max()
