@@ -17,7 +17,7 @@ struct GemmTileCost { int tm, tn, groups, per_cu; double fixed, per_tile[2]; };
 // The figures are fitted to linear_fwd and linear_bwd_input at 230 .. 98304 rows and
 // 512 .. 8192 columns either way (20 launches in a graph each), with the loop of 32 x 32 x 16 instructions that there was.  With the present
 // one, 70 drawn feed-forward units and projections in every tile: the choice costs 0.5 to 1.3 % over the best tile on average, 3 % in
-// project_bwd (at worst 28 us instead of 16) and in the projections' weight gradients.  (M8, T4 and T8 came later, fitted to
+// project_bwd and in the projections' weight gradients.  (M8, T4 and T8 came later, fitted to
 // linear_fwd, bwd_input and bwd_weight at 58 .. 2048 rows and 256 .. 7680 columns: of 26 such maps in four products each none is slower than without
 // them, 40 are 5 to 42 % faster.)  Large tiles move the fewest bytes per flop
 // but a launch of few of them leaves compute units idle (2048 x 2048 -> 512: 16 workgroups of 256 x 256, 46 us;
@@ -52,13 +52,25 @@ inline bool gemm_streams(const GemmWork *work, int n, bool out_f32)
     return bytes > 128e6;
 }
 
+// Workgroups of one product in tiles `c`; on_xcds: eight times those of the XCD that has the most (xcd_tile in lss_grid.h deals a product's tiles out evenly)
+inline double gemm_workgroups(const GemmTileCost &c, const GemmWork &w, bool on_xcds)
+{
+    const int64_t tiles = (int64_t)w.batches * ((gemm_rows_ok(w) + c.tm - 1) / c.tm) * ((w.N + c.tn - 1) / c.tn);
+    return (double)(on_xcds ? (tiles + 7) / 8 * 8 : tiles);
+}
+
 // What a launch of the products `work` takes in tiles `t`
 inline double gemm_launch_estimate(GemmTile t, const GemmWork *work, int n, bool skip_tail)
 {
     const GemmTileCost &c = kGemmTiles[t];
-    double wgs = 0, sum = 0, last_n = 0, last_tiles = 0;
+    // A launch waits for the XCD that has the most workgroups: projections of 3 x 5193 rows of 128 columns and 500 of each have 33 of 128 x 128 for the
+    // 32 compute units of some, 12.6 us, and where each holds two of them 10.2.  2159 drawn projections in every tile: 0.13 % over the best one on
+    // average and at worst 8 %, 0.32 and 47 % with both products' workgroups just added up.  (Not with a float A, whose figures fit the plain sum:
+    // 4737 drawn calls, 1.90 % over the best tile and 19 more than 3 % slower than without 32-wide tiles, 1.89 and 3 so.)
+    const bool on_xcds = !work->a_f32;
+    double wgs = 0, tiles_all = 0, sum = 0, last_n = 0, last_tiles = 0;
     for (const GemmWork *w = work; w != work + n; ++w) {
-        const double count = (double)w->batches * ((gemm_rows_ok(*w) + c.tm - 1) / c.tm) * ((w->N + c.tn - 1) / c.tn);
+        const double count = gemm_workgroups(c, *w, false);
         // A float A costs more the smaller the tile, whose workgroups re-read it more often, and the less of it
         // fits the last-level cache (project_bwd, 1024 columns: 256 x 256 against 128 x 128 tiles take 64 and
         // 57 us at 8192 rows, 102 and 97 at 16384, 156 and 165 at 24000)
@@ -70,13 +82,14 @@ inline double gemm_launch_estimate(GemmTile t, const GemmWork *work, int n, bool
             slow = c.tm == 256 ? 1.05 + 0.35 * far : c.tm == 128 ? 1.15 + 0.35 * far : 1.6 + 0.5 * far;
             more = c.tm == 256 ? 1.5 : c.tm == 128 ? 6.0 + 2.0 * far : 0.0;
         }
-        wgs += count;
+        wgs += gemm_workgroups(c, *w, on_xcds);
+        tiles_all += count;
         last_n = count;
         last_tiles = w->K / kGemmK * slow + more;
         sum += count * last_tiles;
     }
     if (wgs <= 0) return 0.0;
-    const double room = 256.0 * c.per_cu, rest = wgs - room * (double)(int64_t)(wgs / room), tiles = sum / wgs;
+    const double room = 256.0 * c.per_cu, rest = wgs - room * (double)(int64_t)(wgs / room), tiles = sum / tiles_all;
     return gemm_estimate(c, wgs, tiles, rest <= last_n ? last_tiles : tiles);     // (the last job's workgroups start last)
 }
 
@@ -98,6 +111,19 @@ inline int gemm_zero_tiles(int rows, int rows_ok, bool skip_tail, int tm, int tn
     return left > 0 ? (int)((left + gemm_zero_rows(tn) - 1) / gemm_zero_rows(tn)) : 0;
 }
 
+// Whether a launch may take tiles `t`.  32-wide ones only where one round of workgroups takes them all (of 4000 drawn linear maps that need more none is
+// faster in them, which take 1.4 times as long at two rounds: the weights come once more from the last-level cache, which the estimate does not know;
+// 644 x 6144 -> 1536, 504 workgroups, 49.1 us, in 64 x 64 tiles 41.1), and never with results past the caches, without which their kernel is built
+inline bool gemm_takes(GemmTile t, const GemmWork *work, int n, bool a_any, bool streams)
+{
+    const GemmTileCost &c = kGemmTiles[t];
+    if (t == (a_any ? TILE_M8 : TILE_M2)) return false;
+    if (c.tm != 32) return true;
+    double wgs = 0.0;
+    for (const GemmWork *w = work; w != work + n; ++w) wgs += gemm_workgroups(c, *w, true);
+    return !streams && wgs <= 256.0;
+}
+
 // The tile of a launch: the one with the smallest estimate.
 // 128 x 128 tiles of which a compute unit holds one: a short contraction is all on its way at once in four slots, and nothing is left to add up
 // (linear_fwd and bwd_input of 2048 x 512 -> 2048 9.9 -> 9.2 us, 9.7 -> 9.1; from 64 tiles on within 1 %).  Not with a float A, whose
@@ -109,8 +135,7 @@ inline GemmTile pick_gemm_tile(const GemmWork *work, int n, bool a_any, bool ski
     GemmTile best = TILE_L;
     double best_t = gemm_launch_estimate(TILE_L, work, n, skip_tail);
     for (int i = TILE_M; i < TILE_COUNT; ++i) {
-        if (i == (a_any ? TILE_M8 : TILE_M2)) continue;
-        if (streams && kGemmTiles[i].tm == 32) continue;        // (a kernel without the stores past the caches)
+        if (!gemm_takes((GemmTile)i, work, n, a_any, streams)) continue;
         const double t = gemm_launch_estimate((GemmTile)i, work, n, skip_tail);
         if (t < best_t) { best_t = t; best = (GemmTile)i; }
     }

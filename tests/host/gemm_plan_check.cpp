@@ -1,10 +1,11 @@
 // Goes over the choices of csrc/lss_gemm_plan.h on the host: a launch takes a tile that it has a kernel for, none of the others is estimated
-// shorter, a weight gradient's chunks cover its rows within the scratch that the header promises, and the rows without data are cleared 16384 elements at a
-// time whatever the tile.
+// shorter, and launches that were measured in every tile take one of the shortest; a weight gradient's chunks cover its rows within the scratch
+// that the header promises; the rows without data are cleared 16384 elements at a time whatever the tile.
 #include "lss_gemm_plan.h"
 
 #include <cstdio>
 #include <initializer_list>
+#include <vector>
 
 using namespace lss;
 
@@ -14,8 +15,32 @@ static int fail(const char *what, const GemmWork &w, int tile)
     return 1;
 }
 
+// Launches that were timed in every tile, behind a launch that writes their operands: one within 6 % of the shortest is taken
+struct Measured {
+    GemmWork work[2];
+    int n;
+    std::vector<GemmTile> good;
+};
+static const Measured measured[] = {
+    {{{1, 644, 644, 1536, 6144, 0}}, 1, {TILE_S}},                                                  // 41.1 us, 49.1 in 32 x 64 tiles
+    {{{1, 581, 581, 1664, 6656, 0}}, 1, {TILE_S}},                                                  // 44.0, 50.2
+    {{{1, 120, 120, 1280, 1280, 0}}, 1, {TILE_T4, TILE_T8}},                                        // 8.6 and 9.5, 10.7 in 64 x 64 ones
+    {{{1, 15579, 15579, 256, 128, 0}, {3, 500, 500, 128, 128, 0}}, 2, {TILE_M}},                    // projections: 10.2, 12.6 in 128 x 128 ones of eight wavefronts
+    {{{1, 3699, 3699, 2816, 1408, 0}, {3, 1233, 1233, 1408, 1408, 0}}, 2, {TILE_M}},                // 50.4, 74.0 in 256 x 256 ones
+    {{{1, 11969, 11969, 1280, 640, 0}, {1, 1426, 1426, 640, 640, 0}}, 2, {TILE_M}},                 // 30.2, 43.2
+    {{{4, 2262, 1768, 1280, 2560, 1}, {4, 1463, 1463, 1280, 1280, 0}}, 2, {TILE_L}},                // project_bwd: 80.2, 98.1 in 128 x 128 ones
+    {{{3, 653, 610, 640, 1280, 1}, {3, 403, 403, 640, 640, 0}}, 2, {TILE_S}},                       // 19.3, 23.1 in 128 x 128 ones of two groups
+    {{{1, 43186, 2081, 128, 256, 1}, {1, 689, 689, 128, 128, 0}}, 2, {TILE_S, TILE_S4, TILE_T4, TILE_T8}},  // their rows without data cost the same in all
+};
+
 int main()
 {
+    for (const Measured &m : measured) {
+        const GemmTile t = pick_gemm_tile(m.work, m.n, m.work[0].a_f32, false, false);
+        bool good = false;
+        for (const GemmTile g : m.good) good = good || g == t;
+        if (!good) return fail("not among the shortest", m.work[0], t);
+    }
     for (int batches : {1, 4, 65535})
         for (int rows : {1, 31, 58, 256, 1000, 2048, 16384, 98304, 0x7fffffff})
             for (int ok : {1, 64, 0x7fffffff})
@@ -29,10 +54,13 @@ int main()
                                 for (bool streams : {false, true}) {
                                     const GemmTile t = pick_gemm_tile(work, n, any, skip, streams);
                                     if (t < 0 || t >= TILE_COUNT || t == (any ? TILE_M8 : TILE_M2) || (streams && kGemmTiles[t].tm == 32)) return fail("no such kernel", work[0], t);
+                                    double wgs = 0.0;
+                                    for (int i = 0; i < n; ++i) wgs += gemm_workgroups(kGemmTiles[t], work[i], true);
+                                    if (kGemmTiles[t].tm == 32 && wgs > 256.0) return fail("small tiles, more than one round", work[0], t);
                                     const double us = gemm_launch_estimate(t, work, n, skip);
                                     if (!(us > 0.0)) return fail("no time", work[0], t);
                                     for (int o = 0; o < TILE_COUNT; ++o)
-                                        if (o != (any ? TILE_M8 : TILE_M2) && !(streams && kGemmTiles[o].tm == 32) && gemm_launch_estimate((GemmTile)o, work, n, skip) < us)
+                                        if (gemm_takes((GemmTile)o, work, n, any, streams) && gemm_launch_estimate((GemmTile)o, work, n, skip) < us)
                                             return fail("a shorter one is there", work[0], t);
                                 }
                             if (rows > 1 << 20) continue;
