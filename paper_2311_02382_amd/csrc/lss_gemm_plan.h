@@ -175,11 +175,13 @@ inline WgradPlan pick_wgrad_plan(int rows, int batches, int K, int N, bool dc_f3
             if (i == TILE_M8) continue;
             const GemmTileCost &c = kGemmTiles[i];
             // (both operands through transposing reads: a fifth slower per tile, but for the largest)
-            // (32-wide tiles read every operand more often, from the last-level cache where it has just been written -- behind two copies, which
-            // the tables' launches were not: dW of 256 x 1024 from 2000 rows 17.9 -> 16.5 us, copies included, but from 4000, which larger tiles
-            // share out in chunks, 24.2 -> 26.9.  A float dC travels through registers, a tile at a time: of 256 x 512 from 1512 rows
-            // 25.3 -> 20.7, from 4064 27.8 -> 33.2)
-            const double tiles = chunk_tiles * (c.tm == 256 ? 1.0 : 1.2) * (c.tm != 32 ? 1.0 : dc_f32 ? 2.2 : chunk_tiles > 32 ? 1.3 : 1.0);
+            // (32-wide tiles: not for fewer contraction tiles than groups of wavefronts, which gain nothing -- dW of 256 x 1024 from 130 to 190 rows 6.5 us in
+            // 64 x 64 ones, 7.0 -- and dearer the longer the chunk: they read every operand more often, from the last-level cache where it has just been
+            // written -- behind two copies dW of 256 x 1024 from 2000 rows 17.9 -> 16.5 us, copies included, but from 4000, which larger tiles share out in
+            // chunks, 24.2 -> 26.9.  A float dC travels through registers, a tile at a time: of 256 x 512 from 1512 rows 25.3 -> 20.7, from 4064 27.8 -> 33.2)
+            if (c.tm == 32 && chunk_tiles < 4) continue;
+            const double dearer = c.tm != 32 ? 1.0 : dc_f32 ? 2.2 : 1.0 + 0.015 * (chunk_tiles > 24 ? chunk_tiles - 24 : 0);
+            const double tiles = chunk_tiles * (c.tm == 256 ? 1.0 : 1.2) * dearer;
             const double t = sum + gemm_estimate(c, parts * ((K + c.tm - 1) / c.tm) * ((N + c.tn - 1) / c.tn), tiles, tiles);
             if (best_t == 0.0 || t < best_t) { best_t = t; best = {(GemmTile)i, splits, chunk_tiles * kGemmK}; }
         }

@@ -530,7 +530,8 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
     const int split = item / tiles, tile = item % tiles;
     const int batch = split / g.splits_per_batch;
     const int block = tile / (4 * g.n_tiles), in = tile % (4 * g.n_tiles), down = min(g.m_tiles - 4 * block, 4);
-    const int m0 = (4 * block + in % down) * S::TM, n0 = in / down * S::TN;
+    const int col = down == 4 ? in >> 2 : in / down;       // (a division is some 40 instructions, 1 % of a launch of 64 x 64 tiles)
+    const int m0 = (4 * block + in - col * down) * S::TM, n0 = col * S::TN;
     const int r0 = (split % g.splits_per_batch) * g.chunk_rows, r1 = min(r0 + g.chunk_rows, g.rows);
     const int T = (r1 - r0 + PK - 1) / PK;          // >= 1: the host sizes the splits so
     const int tail = (r1 - r0) - (T - 1) * PK;      // rows of the last tile, 1 .. 64

@@ -41,6 +41,21 @@ int main()
         for (const GemmTile g : m.good) good = good || g == t;
         if (!good) return fail("not among the shortest", m.work[0], t);
     }
+    const struct { int rows, batches, K, N; bool dc_f32; std::vector<GemmTile> good; } gradients[] = {
+        {142, 1, 256, 1024, false, {TILE_S}},                       // 6.5 us, 7.0 in 32 x 64 tiles
+        {161, 1, 1024, 256, false, {TILE_S}},                       // 6.5, 7.0
+        {250, 1, 384, 384, false, {TILE_S, TILE_T4, TILE_T8}},      // 6.5, 6.8
+        {815, 1, 1024, 256, false, {TILE_T4, TILE_T8}},             // 8.9, 9.9 in 64 x 64 ones by four
+        {2964, 1, 256, 256, false, {TILE_T4, TILE_T8, TILE_S, TILE_S4}},
+        {3040, 1, 1024, 256, false, {TILE_S4, TILE_S}},             // 13.9, 15.0 in 32 x 32 ones
+        {1512, 1, 256, 512, true, {TILE_T4, TILE_T8}},              // 20.7, 25.3 in 64 x 64 ones by four
+    };
+    for (const auto &g : gradients) {
+        const WgradPlan p = pick_wgrad_plan(g.rows, g.batches, g.K, g.N, g.dc_f32);
+        bool good = false;
+        for (const GemmTile t : g.good) good = good || t == p.tile;
+        if (!good || (kGemmTiles[p.tile].tm == 32 && p.chunk_rows < 4 * kGemmK)) return fail("weight gradient not in one of the shortest", {g.batches, g.rows, g.rows, g.N, g.K, g.dc_f32}, p.tile);
+    }
     for (int batches : {1, 4, 65535})
         for (int rows : {1, 31, 58, 256, 1000, 2048, 16384, 98304, 0x7fffffff})
             for (int ok : {1, 64, 0x7fffffff})
@@ -65,7 +80,7 @@ int main()
                                 }
                             if (rows > 1 << 20) continue;
                             const WgradPlan p = pick_wgrad_plan(rows, batches, K, N, any);
-                            if (p.tile < 0 || p.tile >= TILE_COUNT || p.tile == TILE_M8) return fail("no such weight gradient", work[0], p.tile);
+                            if (p.tile < 0 || p.tile >= TILE_COUNT || p.tile == TILE_M8 || (kGemmTiles[p.tile].tm == 32 && p.chunk_rows < 4 * kGemmK)) return fail("no such weight gradient", work[0], p.tile);
                             if (p.splits_per_batch < 1 || p.splits_per_batch > wgrad_most_chunks(rows, batches, K, N) || p.splits_per_batch > wgrad_max_chunks(batches, K, N) ||
                                 p.chunk_rows % kGemmK != 0 || (int64_t)p.splits_per_batch * p.chunk_rows < rows || (int64_t)(p.splits_per_batch - 1) * p.chunk_rows >= rows)
                                 return fail("chunks", work[0], p.tile);
