@@ -126,7 +126,8 @@ inline bool gemm_takes(GemmTile t, const GemmWork *work, int n, bool a_any, bool
 
 // The tile of a launch: the one with the smallest estimate.
 // 128 x 128 tiles of which a compute unit holds one: a short contraction is all on its way at once in four slots, and nothing is left to add up
-// (linear_fwd and bwd_input of 2048 x 512 -> 2048 9.9 -> 9.2 us, 9.7 -> 9.1; from 64 tiles on within 1 %).  Not with a float A, whose
+// (linear_fwd and bwd_input of 2048 x 512 -> 2048 9.9 -> 9.2 us, 9.7 -> 9.1; linear_fwd of long contractions whose A has just been written takes 1 to 4 %
+// longer so, 1047 x 8192 -> 2048 67 -> 70, but among the other launches of a layer, from colder operands, less: 1828 x 8192 -> 2048 92 -> 77).  Not with a float A, whose
 // tiles travel through registers one at a time (project_bwd of 1500 x 2048 50.6 us in two groups, 54.2 so), nor for the weight
 // gradients, both of whose operands are read transposed, more often in smaller parts (2048 x 2048 from 2048 rows 24.8 and 26.0).
 // a_any: the kernels that take a float A, in any of the products
@@ -180,6 +181,7 @@ inline WgradPlan pick_wgrad_plan(int rows, int batches, int K, int N, bool dc_f3
             // written -- behind two copies dW of 256 x 1024 from 2000 rows 17.9 -> 16.5 us, copies included, but from 4000, which larger tiles share out in
             // chunks, 24.2 -> 26.9.  A float dC travels through registers, a tile at a time: of 256 x 512 from 1512 rows 25.3 -> 20.7, from 4064 27.8 -> 33.2)
             if (c.tm == 32 && chunk_tiles < 4) continue;
+            if (dc_f32 && i == TILE_T4) continue;       // (never the shortest of the others, and not built)
             const double dearer = c.tm != 32 ? 1.0 : dc_f32 ? 2.2 : 1.0 + 0.015 * (chunk_tiles > 24 ? chunk_tiles - 24 : 0);
             const double tiles = chunk_tiles * (c.tm == 256 ? 1.0 : 1.2) * dearer;
             const double t = sum + gemm_estimate(c, parts * ((K + c.tm - 1) / c.tm) * ((N + c.tn - 1) / c.tn), tiles, tiles);

@@ -925,7 +925,10 @@ static hipError_t launch_wgrad(WgradArgs &g, float *dw, float *scratch, hipStrea
     case TILE_M2: e = launch_wgrad_shape<ShapeM2, DC_F32>(g, st); break;
     case TILE_S: e = launch_wgrad_shape<ShapeS, DC_F32>(g, st); break;
     case TILE_S4: e = launch_wgrad_shape<ShapeS4, DC_F32>(g, st); break;
-    case TILE_T4: e = launch_wgrad_shape<ShapeT4, DC_F32>(g, st); break;
+    case TILE_T4:
+        if constexpr (!DC_F32) e = launch_wgrad_shape<ShapeT4, DC_F32>(g, st);
+        else e = hipErrorInvalidConfiguration;              // (pick_wgrad_plan: not with a float dC)
+        break;
     case TILE_T8: e = launch_wgrad_shape<ShapeT8, DC_F32>(g, st); break;
     default: e = hipErrorInvalidConfiguration; break;       // (pick_wgrad_plan: no other)
     }

@@ -80,7 +80,7 @@ int main()
                                 }
                             if (rows > 1 << 20) continue;
                             const WgradPlan p = pick_wgrad_plan(rows, batches, K, N, any);
-                            if (p.tile < 0 || p.tile >= TILE_COUNT || p.tile == TILE_M8 || (kGemmTiles[p.tile].tm == 32 && p.chunk_rows < 4 * kGemmK)) return fail("no such weight gradient", work[0], p.tile);
+                            if (p.tile < 0 || p.tile >= TILE_COUNT || p.tile == TILE_M8 || (any && p.tile == TILE_T4) || (kGemmTiles[p.tile].tm == 32 && p.chunk_rows < 4 * kGemmK)) return fail("no such weight gradient", work[0], p.tile);
                             if (p.splits_per_batch < 1 || p.splits_per_batch > wgrad_most_chunks(rows, batches, K, N) || p.splits_per_batch > wgrad_max_chunks(batches, K, N) ||
                                 p.chunk_rows % kGemmK != 0 || (int64_t)p.splits_per_batch * p.chunk_rows < rows || (int64_t)(p.splits_per_batch - 1) * p.chunk_rows >= rows)
                                 return fail("chunks", work[0], p.tile);
