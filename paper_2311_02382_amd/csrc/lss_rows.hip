@@ -8,6 +8,7 @@
 // the table rows, of gamma and of beta) are taken in a fixed order: no atomics.
 #include "lss_common.h"
 #include "lss_kernels.h"
+#include "lss_rows_plan.h"
 
 #include <algorithm>
 
@@ -262,12 +263,8 @@ __global__ __launch_bounds__(256) void layernorm_bwd_params_kernel(const float *
 
 // The same for short segments, dgamma and dbeta included: the second kernel is a launch that waits for this one, 4 us whatever its size.  Column
 // workgroups own 32 columns over all rows (thread (group, chunk): every 256th row, four at a time on their way; the 256 groups' sums meet in LDS,
-// in order), and what a compute unit gets per cycle bounds them: 64 bytes per row and operand.
+// in order), and what a compute unit gets per cycle bounds them: 64 bytes per row and operand.  Where it is the shorter way: layernorm_bwd_short().
 constexpr int LN_SHORT_COLS = 32, LN_SHORT_ROWS = 16;
-// Where one launch is the shorter way.  x and dy just written by the launches before (two copies, timed along: 8.5 us), two launches and one, us:
-// 58 rows of 512 columns 15.0, 10.4; 512 of 1024 14.6, 10.6; 512 of 2048 15.1, 11.7; 1000 of 1024 14.8, 13.3; 2048 of 512 15.0, 17.4: a column
-// workgroup's bytes then come from the last-level cache at half the rate, which a call on its own inputs again does not show (2048 of 512 6.1, 5.5).
-bool layernorm_bwd_short(int64_t rows, int E) { return rows <= 1024 && E <= 2048 && rows * E <= 1024 * 1024; }
 template <int NCH>
 __global__ __launch_bounds__(1024) void layernorm_bwd_short_kernel(const bf16_t *x, const float *__restrict__ gamma,
                                                                    const float *__restrict__ mean, const float *__restrict__ rstd,

@@ -1,9 +1,10 @@
 """LayerNorm's backward of short segments, one launch for dx, dgamma and dbeta: rows on either side of its 16 per row workgroup and 256 x 4 per
-column thread, columns that do not fill a column workgroup, either side of the sizes at which it is taken, and gradients written over what is read."""
+column thread, columns that do not fill a column workgroup, either side of the sizes at which it is taken, and gradients written over what is read.
+Which kernels ran is read from the launch counters."""
 import pytest
 import torch
 
-from paper_2311_02382_amd import lss
+from paper_2311_02382_amd import lss, timing
 
 pytestmark = pytest.mark.gpu
 
@@ -16,11 +17,26 @@ def _case(rows, E):
     return x, dy, gamma, mean, rstd
 
 
-@pytest.mark.parametrize("rows,E", [(1, 8), (15, 40), (17, 512), (255, 128), (256, 1032), (257, 2048), (511, 2048), (1023, 520), (1024, 1024),
-                                    (1024, 8), (1025, 8), (513, 2048), (40, 2056)])
-def test_gradients_against_64_bits(rows, E):
+def _launches(call):
+    """What call() returns, and how often the kernel of one launch ran, and the first of two."""
+    ids = {name: k for k, name in timing.kernel_names().items()}
+    timing.reset()
+    timing.enable(True)
+    try:
+        result = call()
+        torch.cuda.synchronize()
+    finally:
+        timing.enable(False)
+    return result, [timing.read(ids[name])[1] for name in ("layernorm_bwd_short_kernel", "layernorm_bwd_kernel")]
+
+
+@pytest.mark.parametrize("rows,E,one", [(1, 8, True), (15, 40, True), (17, 512, True), (255, 128, True), (256, 1032, True), (257, 2048, True),
+                                        (511, 2048, True), (719, 520, True), (720, 1024, True), (720, 8, True), (1008, 1040, True), (721, 8, False),
+                                        (1023, 520, False), (1024, 1024, False), (1025, 8, False), (513, 2048, False), (40, 2056, False)])
+def test_gradients_against_64_bits(rows, E, one):
     x, dy, gamma, mean, rstd = _case(rows, E)
-    dx, dg, db = lss.lss_layernorm_bwd(x, gamma, mean, rstd, dy)
+    (dx, dg, db), launches = _launches(lambda: lss.lss_layernorm_bwd(x, gamma, mean, rstd, dy))
+    assert launches == ([1, 0] if one else [0, 1])
     xh, d = (x.double() - mean.double()[:, None]) * rstd.double()[:, None], dy.double()
     g = d * gamma.double()
     want = rstd.double()[:, None] * (g - g.mean(1, keepdim=True) - xh * (g * xh).mean(1, keepdim=True))
@@ -33,12 +49,17 @@ def test_gradients_against_64_bits(rows, E):
     assert all(torch.equal(a, b) for a, b in zip((dx, dg, db), again))
 
 
-@pytest.mark.parametrize("over", ["dx on x", "dx on dy", "dgamma on gamma", "dbeta on gamma"])
-def test_gradients_written_over_inputs(over):
+@pytest.mark.parametrize("over,launch", [("dx on x", 0), ("dx on dy", 0), ("dgamma on gamma", 1), ("dbeta on gamma", 1)])
+def test_gradients_written_over_inputs(over, launch):
+    # (dx in an input's place: the one launch's two kinds of workgroup one after the other; a sum in the place of what is read: the two
+    # launches, which add up in another order)
     x, dy, gamma, mean, rstd = _case(300, 512)
     want = lss.lss_layernorm_bwd(x.clone(), gamma.clone(), mean, rstd, dy.clone())
     to = {over.split()[0]: {"x": x, "dy": dy, "gamma": gamma}[over.split()[2]]}
-    got = lss.lss_layernorm_bwd(x, gamma, mean, rstd, dy, **to)
+    got, launches = _launches(lambda: lss.lss_layernorm_bwd(x, gamma, mean, rstd, dy, **to))
+    assert launches[launch] == 1 and launches[1 - launch] == 0
     assert torch.equal(got[0], want[0])
     for a, b in zip(got[1:], want[1:]):
+        if launch == 0:
+            assert torch.equal(a, b)
         assert (a - b).norm() <= 1e-5 * b.norm()

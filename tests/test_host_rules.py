@@ -35,6 +35,10 @@ def test_product_plan_takes_a_tile_there_is_a_kernel_for(tmp_path):
     _run(tmp_path, "gemm_plan_check")
 
 
+def test_layernorm_backward_takes_one_launch_where_it_is_shorter(tmp_path):
+    _run(tmp_path, "rows_plan_check")
+
+
 def test_results_of_large_products_are_stored_past_the_caches(tmp_path):
     # Two stores that differ in the non-temporal hint only are one plain store to the compiler's middle end: what counts is the
     # generated code.  Every kernel of the projection GEMM has both kinds.
