@@ -361,10 +361,12 @@ int lss_residual_dropout_add(const void *x, const void *delta, int64_t seg_offse
  *     y = (x - mean) * rstd * gamma + beta,   rstd = 1 / sqrt(var + eps).
  *   x, y    [rows, E_m] bf16;  gamma, beta [E_m] float;  mean, rstd [rows] float
  *           (written by the forward, read by the backward)
- * Backward: dx [rows, E_m] bf16, dgamma, dbeta [E_m] float; the sums over rows are
- * taken in a fixed order (within blocks of 32 rows, then over the blocks), through
+ * Backward: dx [rows, E_m] bf16, dgamma, dbeta [E_m] float.  The sums over rows are
+ * taken in an order that is fixed for the sizes, but for one case: where dgamma or
+ * dbeta overlaps another operand, or dx overlaps gamma, mean or rstd, it may be another
+ * one, and the last bits of the sums with it.  dx may be written over x or dy.
  *   scratch  DEVICE buffer of lss_layernorm_bwd_scratch_bytes(rows, E_m) bytes,
- *            caller-owned, overwritten.
+ *            caller-owned, overwritten or left as it is (short inputs need none of it).
  * E_m <= 4096 (LSS_ERR_SHAPE otherwise); rows = 0 writes zeros to dgamma, dbeta.
  */
 int lss_layernorm_fwd(const void *x, const float *gamma, const float *beta, double eps,
