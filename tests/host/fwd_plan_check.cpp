@@ -56,10 +56,11 @@ int main()
         if (!good) bad += fail("not among the shortest", m.s, m.with_drop, p);
     }
     if (bad) return 1;
+    int fours = 0;
     for (int d : {64, 128})
         for (int l_s : {1, 31, 32, 33, 64, 65, 127, 128, 129, 256, 257, 1044, 4096, 70001})
             for (int l_x : {1, 64, 65, 512, 1000, 8192, 50112, 1 << 20})
-                for (int heads : {1, 7, 64, 65535})
+                for (int heads : {1, 5, 7, 16, 28, 64, 65535})
                     for (int causal : {0, 1})
                         for (int at : {0, 1})
                             for (int most : {1, 2, 3, 16})
@@ -70,7 +71,12 @@ int main()
                                     const int64_t seen = causal ? s.s0 + l_s : l_x;
                                     if (p.splits < 1 || p.splits > most || (p.splits > 1 && (seen + 63) / 64 / p.splits < 2)) return fail("outside the limits", s, drop, p);
                                     if (d == 64 ? p.form == FWD_8x1 || (drop && p.form == FWD_4x2) : p.form != FWD_8x1 && p.form != FWD_4x2) return fail("no such form", s, drop, p);
+                                    // four groups: only where all workgroups run at once, one per compute unit, and not for launches of a few
+                                    const int64_t wgs = ((int64_t)l_s + (p.form == FWD_1x4 ? 31 : 63)) / (p.form == FWD_1x4 ? 32 : 64) * heads * p.splits;
+                                    if ((p.form == FWD_1x4 || p.form == FWD_2x4) && (wgs <= 16 || wgs > 256)) return fail("four groups in too few or too many workgroups", s, drop, p);
+                                    fours += p.form == FWD_1x4 || p.form == FWD_2x4;
                                 }
+    if (fours < 100) return 1;
     std::printf("clean\n");
     return 0;
 }

@@ -1,6 +1,6 @@
 """The GEMM's tile sizes: a launch takes 256-, 128- or 64-wide tiles, with or without wavefront groups that share the
-contraction, by its size.  Sizes here fall on either side of those choices, with remainders in rows, a
-contraction shorter than the number of groups, and rows that do not fill a contraction tile (weight gradient)."""
+contraction, by its size.  Sizes here have remainders in rows, a contraction shorter than the number of groups, and rows that
+do not fill a contraction tile (weight gradient).  (test_gpu_product_tiles.py names the tile of every size.)"""
 import pytest
 import torch
 
@@ -10,10 +10,10 @@ from _util import Staged, TOL, rel_err, to_np
 pytestmark = pytest.mark.gpu
 
 SHAPES = [  # rows, K, N
-    (1, 128, 128), (33, 128, 1024), (65, 2048, 128), (129, 4096, 256),      # 64 x 64 tiles, groups share long contractions
-    (700, 1024, 1024), (2049, 512, 512),                                    # about one workgroup per compute unit
-    (1300, 640, 2560), (4100, 1280, 640),                                   # 128 x 128
-    (8200, 1024, 2048),                                                     # 256 x 256
+    (1, 128, 128), (33, 128, 1024), (65, 2048, 128), (129, 4096, 256),      # 64 x 64 and 32 x 32 tiles, whose groups share long contractions
+    (700, 1024, 1024), (2049, 512, 512),                                    # 64 x 64, about one workgroup per compute unit
+    (1300, 640, 2560), (4100, 1280, 640),                                   # 128 x 128 in one direction
+    (8200, 1024, 2048),                                                     # 128 x 128 in all
 ]
 
 

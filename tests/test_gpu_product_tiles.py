@@ -1,0 +1,139 @@
+"""Every tile that a matrix product has a kernel for, in every product that takes it, against 64-bit products of the same operands.  The tile that a size
+takes is asked of the library (csrc/lss_plan.h), so that a change to the rule shows which sizes have left theirs.  Rows and columns end inside a
+tile wherever there is such a size; contractions are longer than what is on its way at once, and shared by groups of wavefronts unevenly."""
+import pytest
+import torch
+
+from paper_2311_02382_amd import lss
+from _util import TOL, linear_plan, project_plan
+
+LINEAR = {  # tile: rows, K, N  (contraction over K)
+    "fwd": {"32x32": (45, 1152, 384), "32x64": (58, 512, 4480), "64x64": (70, 512, 5504), "64x64 by four": (67, 768, 6016),
+            "128x128 of eight": (1925, 640, 1920), "128x128": (658, 512, 5760), "256x256": (2224, 512, 5504)},
+    # (contraction over N)
+    "bwd_input": {"32x32": (45, 384, 1152), "32x64": (58, 4224, 512), "64x64": (66, 5760, 512), "64x64 by four": (70, 5504, 768),
+                  "128x128 of eight": (1925, 1920, 640), "128x128": (772, 4736, 512), "256x256": (2698, 4480, 512)},
+}
+LINEAR["fwd"]["128x128 of eight, whole rows"], LINEAR["bwd_input"]["128x128 of eight, whole rows"] = (2048, 512, 2048), (2048, 2048, 512)
+WEIGHT = {  # (tile, rows in chunks): rows, K, N  (contraction over the rows)
+    ("32x32", False): (450, 128, 256), ("32x32", True): (2567, 128, 128), ("32x64", False): (450, 384, 384), ("32x64", True): (6161, 128, 128),
+    ("64x64", False): (515, 640, 1664), ("64x64", True): (2571, 128, 1152), ("64x64 by four", False): (517, 384, 1408),
+    ("64x64 by four", True): (3077, 384, 384), ("128x128 by two", False): (533, 384, 5504), ("128x128 by two", True): (6277, 128, 2176),
+    ("128x128", False): (517, 4736, 896), ("128x128", True): (3411, 384, 3712), ("256x256", False): (515, 1664, 5248), ("256x256", True): (2507, 4736, 896),
+}
+PROJECT = {  # B, l_x, H, l_s, rows_valid
+    "qkv": {"32x32": (1, 125, 6, 49, 115), "32x64": (1, 135, 4, 75, 81), "64x64": (2, 342, 4, 323, 338), "64x64 by four": (1, 228, 12, 187, 195),
+            "128x128 of eight": (2, 1429, 4, 1244, 1322), "128x128": (3, 2001, 4, 1368, 1422), "256x256": (3, 7527, 4, 1421, 5412)},
+    "bwd": {"32x32": (1, 135, 4, 75, 81), "32x64": (2, 142, 4, 108, 132), "64x64": (3, 376, 4, 329, 373), "64x64 by four": (2, 765, 4, 299, 747),
+            "128x128 by two": (3, 1569, 4, 1305, 1552), "128x128": (3, 2341, 6, 1415, 2279), "256x256": (3, 7967, 6, 1476, 7384)},
+}
+PARTIALS = {  # (tile of dW_kv, rows in chunks): B, l_x, H, l_s, rows_valid
+    ("32x32", False): (1, 206, 4, 100, 204), ("64x64", False): (1, 135, 4, 75, 81), ("64x64", True): (3, 535, 4, 286, 531),
+    ("64x64 by four", False): (2, 267, 4, 148, 261), ("64x64 by four", True): (2, 519, 4, 429, 514), ("128x128 by two", False): (2, 269, 12, 163, 266),
+    ("128x128 by two", True): (3, 971, 8, 873, 971), ("128x128", False): (2, 135, 12, 43, 76), ("128x128", True): (2, 1047, 12, 413, 1040),
+    ("256x256", True): (3, 1448, 14, 335, 1426),
+}
+
+
+def _rand(seed, *shapes, dtype=torch.bfloat16):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    return [(torch.randn(shape, generator=gen, device="cuda") * (shape[0] ** -0.5 if len(shape) == 2 else 1.0)).to(dtype) for shape in shapes]
+
+
+def _close(got, want, kind):
+    return (got.double() - want).abs().max() <= TOL[kind]["t"] * want.abs().max()
+
+
+def test_sizes_take_the_tiles_they_are_about():
+    """(needs no GPU)"""
+    for op, name in enumerate(LINEAR):
+        for tile, size in LINEAR[name].items():
+            assert linear_plan(op, *size) == (tile.split(",")[0], 1), (name, tile)
+    for (tile, chunks), size in WEIGHT.items():
+        got = linear_plan(2, *size)
+        assert (got[0], got[1] > 1) == (tile, chunks), (tile, chunks)
+    for op, name in enumerate(PROJECT):
+        for tile, (B, l_x, H, l_s, rv) in PROJECT[name].items():
+            assert project_plan(op, B, l_x, H, 64, l_s, rv) == tile, (name, tile)
+    for (tile, chunks), (B, l_x, H, l_s, rv) in PARTIALS.items():
+        got = project_plan(2, B, l_x, H, 64, l_s, rv)
+        assert (got[2], got[3] > 1) == (tile, chunks), (tile, chunks)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile", LINEAR["fwd"])
+def test_linear_forward(tile):
+    rows, K, N = LINEAR["fwd"][tile]
+    a, w = _rand(rows + K, (rows, K), (K, N))
+    c = lss.lss_linear_fwd(a, w)
+    assert _close(c, a.double() @ w.double(), "bf16")
+    u, g = lss.lss_linear_gelu_fwd(a, w)
+    assert torch.equal(u, c) and torch.equal(g, lss.lss_gelu_fwd(c))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile", LINEAR["bwd_input"])
+def test_linear_input_gradient(tile):
+    rows, K, N = LINEAR["bwd_input"][tile]
+    dc, w, u = _rand(rows + N, (rows, N), (K, N), (rows, K))
+    da = lss.lss_linear_bwd_input(dc, w)
+    assert _close(da, dc.double() @ w.double().T, "bf16")
+    assert torch.equal(lss.lss_linear_bwd_input_gelu(dc, w, u), lss.lss_gelu_bwd(u, da))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile,chunks", WEIGHT)
+def test_linear_weight_gradient(tile, chunks):
+    rows, K, N = WEIGHT[tile, chunks]
+    a, dc = _rand(rows + K + N, (rows, K), (rows, N))
+    dw = lss.lss_linear_bwd_weight(a, dc)
+    assert _close(dw, a.double().T @ dc.double(), "f32")
+    assert torch.equal(dw, lss.lss_linear_bwd_weight(a, dc))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile", PROJECT["qkv"])
+def test_projections(tile):
+    B, l_x, H, l_s, rv = PROJECT["qkv"][tile]
+    E, s0 = 64 * H, rv - l_s
+    x, w_q, w_kv = _rand(l_x, (B, l_x, E), (E, E), (E, 2 * E))
+    q, k, v = lss.lss_project_qkv(x, w_q, w_kv, s0, l_s, H)
+    for b in range(B):
+        kv = x[b].double() @ w_kv.double()
+        assert _close(q[b].view(l_s, E), x[b, s0:rv].double() @ w_q.double(), "bf16")
+        assert _close(k[b].view(l_x, E), kv[:, :E], "bf16") and _close(v[b].view(l_x, E), kv[:, E:], "bf16")
+
+
+def _partials(seed, B, l_x, H, rv):
+    dk, dv = _rand(seed, (B, l_x, H, 64), (B, l_x, H, 64), dtype=torch.float32)
+    for t in (dk, dv):
+        t[:, rv:] = float("nan")        # never read
+    rounded = torch.cat([t[:, :rv].reshape(B, rv, -1).to(torch.bfloat16).double() for t in (dk, dv)], 2)
+    return dk, dv, rounded
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile", PROJECT["bwd"])
+def test_projections_input_gradient(tile):
+    B, l_x, H, l_s, rv = PROJECT["bwd"][tile]
+    E = 64 * H
+    w_q, w_kv, dq = _rand(l_x + 1, (E, E), (E, 2 * E), (B, l_s, H, 64))
+    dk, dv, rounded = _partials(l_x, B, l_x, H, rv)
+    dx_q, dx = lss.lss_project_bwd(dq, dk, dv, w_q, w_kv, rv)
+    assert not dx[:, rv:].any()
+    for b in range(B):
+        assert _close(dx_q[b], dq[b].reshape(l_s, E).double() @ w_q.double().T, "f32")
+        assert _close(dx[b, :rv], rounded[b] @ w_kv.double().T, "f32")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile,chunks", PARTIALS)
+def test_projections_weight_gradient_of_float_partials(tile, chunks):
+    B, l_x, H, l_s, rv = PARTIALS[tile, chunks]
+    E = 64 * H
+    x, dq = _rand(l_x + 2, (B, l_x, E), (B, l_s, H, 64))
+    dk, dv, rounded = _partials(l_x + 3, B, l_x, H, rv)
+    dw_q, dw_kv = lss.lss_project_bwd_weight(x, dq, dk, dv, rv - l_s, rv)
+    assert _close(dw_kv, sum(x[b, :rv].double().T @ rounded[b] for b in range(B)), "f32")
+    assert _close(dw_q, sum(x[b, rv - l_s:rv].double().T @ dq[b].reshape(l_s, E).double() for b in range(B)), "f32")
+    assert torch.equal(dw_kv, lss.lss_project_bwd_weight(x, dq, dk, dv, rv - l_s, rv)[1])

@@ -1,6 +1,6 @@
 """Products of few rows or columns: tiles of 32 x 64 and 32 x 32 whose groups of wavefronts share the contraction, and 128 x 128 tiles of eight
 wavefronts with four contraction tiles on their way.  Remainders in rows, columns that end inside a block of tiles, contractions shorter than
-the number of groups, and rows that do not fill a contraction tile (weight gradient)."""
+the number of groups, and rows that do not fill a contraction tile (weight gradient).  (test_gpu_product_tiles.py names the tile of every size.)"""
 import pytest
 import torch
 
@@ -11,8 +11,8 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [  # rows, K, N
     (1, 256, 640), (31, 512, 128), (33, 1152, 384), (58, 4096, 256), (97, 128, 1024), (200, 384, 1536),     # 32 rows, 64 or 32 columns
-    (63, 640, 640), (450, 512, 512), (600, 1024, 256),                                                      # weight gradients in them too
-    (2047, 512, 2048), (1921, 640, 1920),                                                                   # 128 x 128, one per compute unit
+    (63, 640, 640), (450, 512, 512), (600, 1024, 256),                                                      # the last two's weight gradients in them too
+    (2047, 512, 2048), (1921, 640, 1920),                                                                   # forward in 128 x 128, one per compute unit
 ]
 
 
