@@ -1565,7 +1565,8 @@ __global__ __launch_bounds__(256) void bwd_prep_bf16_kernel(SegShape s, DropArgs
 // tiles (dK/dV) each and add their sums up in LDS, in group order.  As many wavefronts per compute unit as two workgroups
 // of one group, each with half the walk: for launches that leave compute units idle or wait for their longest walk (pick_bwd_plan).
 // NJ: blocks of 16 keys or query rows per wavefront.  One instead of two: eight wavefronts of 16 rows instead of four of 32, in half
-// the registers, so that a SIMD has two of them (at D = 64: two where there is one workgroup per compute unit) and the matrix instructions of one run beside the vector work of the other;
+// the registers, so that a SIMD has two of them (at D = 64: two where there is one workgroup per compute unit) and the matrix instructions of
+// one run beside the vector work of the other;
 // but every operand read from LDS feeds one instruction instead of two.  See bwd_narrow.
 template <int D, bool DROP, bool OWN, bool SKINNY = false, int KG = 1, int NJ = 2>
 __global__ __launch_bounds__(64 * (8 / NJ) * KG, D == 64 || NJ == 1 ? 2 : 1) void bwd_main_bf16_kernel(

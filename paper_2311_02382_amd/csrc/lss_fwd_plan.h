@@ -26,10 +26,16 @@ struct FwdPlan { FwdForm form; int splits; };
 //   * A wavefront none of whose rows exist only moves tiles and meets the barriers: a last query tile of which a share `a` of the
 //     wavefronts has rows takes idle + (1 - idle) a per key tile; `first` is that of the launch's longest workgroup, `all` the mean.
 //   * Four groups (FWD_1x4: 32 query rows, FWD_2x4: 64): a launch whose query tiles alone leave most compute units idle shortens its walks without
-//     partial results and their merge.  28 heads of 226 rows behind 834 others take 12.8 us in 1x4, 14.5 in 2x2; 16 heads of 1024 rows behind 3072 28.6 us in 2x4, 31.3 in 4x2 and two ranges, behind 7168 49.2 in 4x2, 53.0 in 2x4, whose
+//     partial results and their merge.  28 heads of 226 rows behind 834 others take 12.8 us in 1x4, 14.5 in 2x2; 16 heads of 1024 rows behind
+//     3072 28.6 us in 2x4, 31.3 in 4x2 and two ranges, behind 7168 49.2 in 4x2, 53.0 in 2x4, whose
 //     workgroups read every K and V tile for half as many rows.  Only where all workgroups run at once, one per compute unit: 312 of 2x4 (12 heads of
 //     1622 rows behind 1531) take 34.3 us, as many of 2x2 29.4.  359 launches as below: 2.4 % less time on average than without these two, the
-//     choice costs 1.1 % over the best (3.6 % without them); 200 with dropout 2.7 %, 0.9 and 4.3.
+//     choice costs 1.1 % over the best (3.6 % without them); 200 with dropout 2.7 %, 0.9 and 4.3.  3634 more that are given four groups, in every form:
+//     7.2 % less time than without, 0.5 % over the best, 96 more than 3 % slower than without (at worst 47.7 us for 36.4: 2 x 16 heads of 357
+//     rows, 2 KB from one row of a head to the next).
+//   * Their K and V bytes count for more (`kv` below), by the fourth root of 256 / workgroups and by how unevenly the groups share the keys: what fits
+//     the launch of 32 heads that is named there.  On those 3634 the exact factor hardly matters: once to twice as much of it, or all
+//     tiles' bytes at 12 to 25 MB per us in its place, and the choice costs 0.48 to 0.55 % over the best.
 //   * With dropout (tables of their own) a tile takes 1.5 to 2 times as long: the generator's work is in vector slots of which the
 //     forward has none to spare.  FWD_4x2 at d = 64 is not built with dropout: by its figures there (5.42, 0.87, 2.18 per
 //     tile) it is never the shortest, over 15 million sizes.
@@ -46,8 +52,9 @@ inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
     struct Cost { FwdForm form; int rows, groups, per_cu; double start, few, tile_us, shared, tail, idle; };
     struct Table { int forms; Cost form[5]; double merge, mb_per_us; bool rounds; };
     static const Table tables[2][2] = {
-        {{5, {{FWD_4x1, 128, 1, 3, 9.05, -2.38, 0.719, 0.542, 0.542, 0.399}, {FWD_2x2, 64, 2, 2, 5.02, 2.09, 0.821, 0.401, 1.135, 0.688}, {FWD_4x2, 128, 2, 1, 5.39, 2.14, 1.078, 0.0, 0.789, 0.630},
-              {FWD_2x4, 64, 4, 1, 5.93, 1.89, 1.300, 0.0, 0.0, 0.807}, {FWD_1x4, 32, 4, 1, 4.61, 1.38, 1.164, 0.0, 0.0, 1.000}},
+        {{5, {{FWD_4x1, 128, 1, 3, 9.05, -2.38, 0.719, 0.542, 0.542, 0.399}, {FWD_2x2, 64, 2, 2, 5.02, 2.09, 0.821, 0.401, 1.135, 0.688},
+              {FWD_4x2, 128, 2, 1, 5.39, 2.14, 1.078, 0.0, 0.789, 0.630}, {FWD_2x4, 64, 4, 1, 5.93, 1.89, 1.300, 0.0, 0.0, 0.807},
+              {FWD_1x4, 32, 4, 1, 4.61, 1.38, 1.164, 0.0, 0.0, 1.000}},
           2.74, 3.85, false},
          {4, {{FWD_4x1, 128, 1, 3, 10.97, -0.43, 1.319, 0.683, 0.552, 0.443}, {FWD_2x2, 64, 2, 2, 4.90, 1.50, 1.512, 0.550, 0.552, 0.000},
               {FWD_2x4, 64, 4, 1, 5.33, 1.52, 2.440, 0.0, 0.0, 0.300}, {FWD_1x4, 32, 4, 1, 4.80, 1.11, 1.944, 0.0, 0.0, 1.000}},
@@ -90,7 +97,7 @@ inline FwdPlan pick_fwd_plan(const SegShape &s, bool with_drop, int max_splits)
             // (four groups that do not all have a tile at the end, or not on every compute unit, read less at once)
             const double kv = kv_us * (c->groups == 4 ? sqrt(sqrt(256.0 / W)) * (longest * 4.0 * sp / (double)tiles) : 1.0);
             const double merge = sp > 1 ? table.merge + out_mb * (8 * sp + 2) / table.mb_per_us : 0.0;
-            if (best_t > 0.0 && (t > kv ? t : kv) + merge >= best_t) continue;      // (most of a call's up to 60 estimates: two roots each, half the time)
+            if (best_t > 0.0 && (t > kv ? t : kv) + merge >= best_t) continue;      // (spares most estimates the two roots)
             t = sqrt(sqrt(t * t * t * t + kv * kv * kv * kv)) + merge;
             if (best_t == 0.0 || t < best_t) { best_t = t; best = {c->form, sp}; }
         }

@@ -15,11 +15,10 @@ constexpr int kGemmK = 64;          // contraction tile
 enum GemmTile { TILE_L, TILE_M, TILE_M2, TILE_M8, TILE_S, TILE_S4, TILE_T4, TILE_T8, TILE_COUNT };
 struct GemmTileCost { int tm, tn, groups, per_cu; double fixed, per_tile[2]; };
 // The figures are fitted to linear_fwd and linear_bwd_input at 230 .. 98304 rows and
-// 512 .. 8192 columns either way (20 launches in a graph each), with the loop of 32 x 32 x 16 instructions that there was.  With the present
-// one, 70 drawn feed-forward units and projections in every tile: the choice costs 0.5 to 1.3 % over the best tile on average, 3 % in
-// project_bwd and in the projections' weight gradients.  (M8, T4 and T8 came later, fitted to
-// linear_fwd, bwd_input and bwd_weight at 58 .. 2048 rows and 256 .. 7680 columns: of 26 such maps in four products each none is slower than without
-// them, 40 are 5 to 42 % faster.)  Large tiles move the fewest bytes per flop
+// 512 .. 8192 columns either way (20 launches in a graph each), with the loop of 32 x 32 x 16 instructions that there was; those of M8, T4 and T8 came
+// later, fitted to linear_fwd, bwd_input and bwd_weight at 58 .. 2048 rows and 256 .. 7680 columns.  With the present loop, behind a launch that writes
+// their operands, 5747 drawn linear maps in every tile: the choice costs 0.5 and 0.8 % over the best one on average (7.2 and 9.5 % without the last
+// three), 0.8 % over 3744 weight gradients, 1.9 % in project_bwd, 2.4 % in the weight gradients of its float partials.  Large tiles move the fewest bytes per flop
 // but a launch of few of them leaves compute units idle (2048 x 2048 -> 512: 16 workgroups of 256 x 256, 46 us;
 // 256 of 64 x 64, 12 us with the former loop), and where even 64 x 64 tiles leave one wavefront per SIMD the chain of contraction
 // tiles is what takes the time: four groups of wavefronts that share it took 9 us in a graph of them, 12 among other work now.
