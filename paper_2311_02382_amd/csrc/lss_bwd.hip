@@ -159,7 +159,7 @@ BwdLaunch plan_bwd(const SegShape &s, bool with_drop, int elem_bytes, bool may_o
     const int one_pass = may_own ? skinny_splits(s, with_drop, elem_bytes, most, dq_tiles) : 0;
     if (one_pass > 0) return {one_pass, 1, true, true, false, false};
     const bool own = may_own && bwd_own_values(s, plan.splits, plan.groups), skinny = own && !with_drop && s.l_s <= kSkinnyRows;
-    return {plan.splits, plan.groups, false, own, skinny, !skinny && bwd_narrow(s, plan.splits, plan.groups)};
+    return {plan.splits, plan.groups, false, own, skinny, !skinny && bwd_narrow(s, plan.splits, plan.groups, with_drop)};
 }
 
 template <typename T, int D>

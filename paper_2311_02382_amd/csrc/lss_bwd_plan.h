@@ -122,8 +122,9 @@ inline BwdPlan pick_bwd_plan(const SegShape &s, bool with_drop, int most, bool m
 //   * many tiles to clear: a compute unit holds one workgroup of this form and two of the other, beside which they are cleared from the start; here the
 //     idle ones have to clear them in the others' time, some 1.8 us a tile -- and the others a few of them at the end, which 32 idle ones stand for
 //     (6 heads of 339 rows behind 3069 of 34,850, 1470 tiles on four idle units: 24.6 us, 31.7; 24 of 123 behind 103 of 3718, 648 on 184: 17.1, 15.3).
-// 11,200 launches of 65 .. 4096 rows that pass the first line, in either form: 5 % less time than the wider one, 0.2 % over the better one (0.6 % without the second line).
-inline bool bwd_narrow(const SegShape &s, int n_splits, int groups)
+// 11,200 launches of 65 .. 4096 rows that pass the first line, in either form: 5 % less time than the wider one, 0.1 % over the better one (0.6 % without
+// the second line; a walk with dropout taken for as long as one without, 0.24 % over the better one in those).
+inline bool bwd_narrow(const SegShape &s, int n_splits, int groups, bool with_drop)
 {
     const int64_t seen = s.causal && s.s0 + s.l_s < s.l_x ? s.s0 + s.l_s : (int64_t)s.l_x, bhs = (int64_t)s.B * s.H;
     const int64_t dkv = (seen + 127) / 128 * bhs, dq = (int64_t)((s.l_s + 127) / 128) * bhs * n_splits;
@@ -131,7 +132,8 @@ inline bool bwd_narrow(const SegShape &s, int n_splits, int groups)
     if (s.l_s <= kSkinnyRows || groups != 1 || (dq + 7) / 8 + (dkv + 7) / 8 > 32) return false;
     const int64_t zeros = s.skip_tail ? 0 : (s.l_x - seen) / 128 * bhs;
     const double row_us = 1.35 * (double)((s.l_s + 63) / 64), key_us = (double)(((seen + 63) / 64 + n_splits - 1) / n_splits);
-    return (double)zeros * 1.8 <= ((row_us > key_us ? row_us : key_us) + 4.0) * (double)(dq + dkv < 224 ? 256 - dq - dkv : 32);
+    const double walk_us = (row_us > key_us ? row_us : key_us) * (with_drop ? 2.0 : 1.0) + 4.0;
+    return (double)zeros * 1.8 <= walk_us * (double)(dq + dkv < 224 ? 256 - dq - dkv : 32);
 }
 
 // A whole backward launch.  one_pass: the kernel that makes all three gradients of a short segment (bf16, d = 64); own: no

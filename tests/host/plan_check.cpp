@@ -38,23 +38,25 @@ int main()
         for (const lss::BwdPlan &g : m.good) good = good || (g.splits == p.splits && g.groups == p.groups);
         if (!good) return fail("not among the shortest", m.s, p);
     }
-    const struct { lss::SegShape s; int splits; bool narrow; } forms[] = {
-        {{768, 256, 1024, 1, 4, 64, 1, 0}, 2, true},           // 15.6 us without, 14.2
-        {{2080, 89, 3523, 1, 6, 64, 0, 0}, 14, true},          // 252 workgroups, 32 on each XCD: 18.0, 17.4
-        {{2066, 126, 2317, 2, 5, 64, 1, 0}, 7, true},          // 20.0, 19.0
-        {{876, 71, 1474, 1, 15, 64, 0, 0}, 5, false},          // 255, 33 on some XCD: 17.3, 19.8
-        {{337, 374, 1351, 1, 15, 64, 0, 0}, 2, false},         // 26.4, 30.4
-        {{2040, 381, 2458, 1, 9, 64, 1, 0}, 3, false},         // 23.9, 26.2
-        {{103, 123, 3718, 2, 12, 64, 1, 0}, 1, true},          // 648 tiles to clear, 184 idle compute units: 17.1, 15.3
-        {{42, 137, 4155, 1, 11, 64, 1, 0}, 1, true},           // 14.5, 12.8
-        {{3477, 174, 49122, 1, 5, 64, 1, 0}, 9, false},        // 1775, 21: 26.1, 31.4
-        {{3111, 124, 19970, 1, 6, 64, 1, 0}, 11, false},       // 18.4, 21.8
-        {{2217, 378, 29126, 1, 8, 64, 1, 0}, 3, false},        // 25.2, 33.4
-        {{2217, 378, 29126, 1, 8, 64, 1, 1}, 3, true},         // (left as they are, they cost nothing)
-        {{639, 78, 6356, 3, 8, 64, 1, 0}, 3, false},           // with dropout 21.6, 24.4
+    const struct { lss::SegShape s; int splits; bool narrow, with_drop; } forms[] = {
+        {{768, 256, 1024, 1, 4, 64, 1, 0}, 2, true, false},    // 15.6 us without, 14.2
+        {{2080, 89, 3523, 1, 6, 64, 0, 0}, 14, true, false},          // 252 workgroups, 32 on each XCD: 18.0, 17.4
+        {{2066, 126, 2317, 2, 5, 64, 1, 0}, 7, true, false},          // 20.0, 19.0
+        {{876, 71, 1474, 1, 15, 64, 0, 0}, 5, false, false},          // 255, 33 on some XCD: 17.3, 19.8
+        {{337, 374, 1351, 1, 15, 64, 0, 0}, 2, false, false},         // 26.4, 30.4
+        {{2040, 381, 2458, 1, 9, 64, 1, 0}, 3, false, false},         // 23.9, 26.2
+        {{103, 123, 3718, 2, 12, 64, 1, 0}, 1, true, false},          // 648 tiles to clear, 184 idle compute units: 17.1, 15.3
+        {{42, 137, 4155, 1, 11, 64, 1, 0}, 1, true, false},           // 14.5, 12.8
+        {{3477, 174, 49122, 1, 5, 64, 1, 0}, 9, false, false},        // 1775, 21: 26.1, 31.4
+        {{3111, 124, 19970, 1, 6, 64, 1, 0}, 11, false, false},       // 18.4, 21.8
+        {{2217, 378, 29126, 1, 8, 64, 1, 0}, 3, false, false},        // 25.2, 33.4
+        {{2217, 378, 29126, 1, 8, 64, 1, 1}, 3, true, false},         // (left as they are, they cost nothing)
+        {{639, 78, 6356, 3, 8, 64, 1, 0}, 3, false, true},     // with dropout 21.6, 24.4
+        {{288, 73, 27279, 1, 7, 64, 1, 0}, 1, true, true},     // 19.6, 17.0
+        {{44, 116, 7838, 1, 8, 64, 1, 0}, 1, true, true},      // 14.8, 13.2
     };
     for (const auto &f : forms)
-        if (lss::bwd_narrow(f.s, f.splits, 1) != f.narrow) return fail("wavefronts of 16 rows", f.s, {f.splits, 1});
+        if (lss::bwd_narrow(f.s, f.splits, 1, f.with_drop) != f.narrow) return fail("wavefronts of 16 rows", f.s, {f.splits, 1});
     long long owns = 0, lets = 0;
     for (int l_s : {65, 66, 97, 128, 129, 192, 193, 256, 257, 300, 384, 512, 513, 1024, 1044, 4096, 12661})
         for (int l_x : {65, 129, 512, 1000, 1024, 4100, 8192, 24576, 50112})
@@ -74,7 +76,7 @@ int main()
                                     return fail("outside the limits", s, p);
                                 auto own = [&](int splits, int groups) { return may_own && lss::bwd_own_values(s, splits, groups); };
                                 const int64_t heads64 = (int64_t)s.B * s.H, dq_wgs = (l_s + 127) / 128 * heads64 * p.splits, dkv_wgs = (seen + 127) / 128 * heads64;
-                                if (lss::bwd_narrow(s, p.splits, p.groups) && (p.groups != 1 || l_s <= lss::kSkinnyRows || (dq_wgs + 7) / 8 + (dkv_wgs + 7) / 8 > 32))
+                                if (lss::bwd_narrow(s, p.splits, p.groups, with_drop) && (p.groups != 1 || l_s <= lss::kSkinnyRows || (dq_wgs + 7) / 8 + (dkv_wgs + 7) / 8 > 32))
                                     return fail("wavefronts of 16 rows, more than one workgroup per compute unit", s, p);
                                 if (l_s > lss::kOwnRows && own(p.splits, p.groups)) return fail("start values that do not fit", s, p);
                                 (own(p.splits, p.groups) ? owns : lets) += 1;
