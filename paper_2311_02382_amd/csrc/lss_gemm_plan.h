@@ -92,13 +92,14 @@ inline double gemm_launch_estimate(GemmTile t, const GemmWork *work, int n, bool
     return gemm_estimate(c, wgs, tiles, rest <= last_n ? last_tiles : tiles);     // (the last job's workgroups start last)
 }
 
-// Rows of C without data are cleared by workgroups of their own, 64 KB each whatever the tile.  By tiles, those of the 32- and
+// Rows of C without data are cleared by workgroups of their own, 64 KB each or a tile where that is more.  By tiles, those of the 32- and
 // 64-wide ones -- 512 or 1024 threads that store 4 to 16 KB, one of which fills a compute unit's LDS -- took longer than their bytes: project_bwd of
 // 43,186 rows of 128 columns of which 2081 have data, 10.6 us in 64 x 64 tiles and 20.0 in 32 x 32 ones, which the estimates then chose: they leave these
-// rows out, whose time hardly depends on the tile now.
+// rows out, whose time hardly depends on the tile now.  A 256 x 256 one is 256 KB: by 64 KB, 4 x 16,919 rows of 768 columns of which 3949 each have data
+// took 100 us, 91 by tiles (2431 workgroups and 608, each with a compute unit's whole LDS).
 // gemm_zero_end: the end of the rows to clear (skip_tail leaves those from the next multiple of 256 on unwritten); gemm_zero_tiles: workgroups per
 // batch entry and tile of columns, gemm_zero_rows() rows each.  The last tile of rows with data clears its own rest.
-constexpr int gemm_zero_rows(int tn) { return 16384 / tn; }
+constexpr int gemm_zero_rows(int tm, int tn) { return tm * tn > 16384 ? tm : 16384 / tn; }
 inline int gemm_zero_end(int rows, int rows_ok, bool skip_tail)
 {
     const int64_t next = ((int64_t)rows_ok + 255) / 256 * 256;
@@ -107,7 +108,7 @@ inline int gemm_zero_end(int rows, int rows_ok, bool skip_tail)
 inline int gemm_zero_tiles(int rows, int rows_ok, bool skip_tail, int tm, int tn)
 {
     const int64_t done = ((int64_t)(rows < rows_ok ? rows : rows_ok) + tm - 1) / tm * tm, left = gemm_zero_end(rows, rows_ok, skip_tail) - done;
-    return left > 0 ? (int)((left + gemm_zero_rows(tn) - 1) / gemm_zero_rows(tn)) : 0;
+    return left > 0 ? (int)((left + gemm_zero_rows(tm, tn) - 1) / gemm_zero_rows(tm, tn)) : 0;
 }
 
 // Whether a launch may take tiles `t`.  32-wide ones only where one round of workgroups takes them all (of 4000 drawn linear maps that need more none is

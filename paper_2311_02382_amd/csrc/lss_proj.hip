@@ -315,9 +315,9 @@ __device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
     const TileId tile = xcd_tile(blockIdx.x - (data ? J.wg_begin : args.zero_begin), J.batches * per_batch, J.n_tiles);
     if (!tile.ok) return;
     const int batch = tile.m / per_batch, n0 = tile.n * S::TN;
-    const int m0 = data ? tile.m % per_batch * S::TM : J.m_data * S::TM + tile.m % per_batch * gemm_zero_rows(S::TN);
+    const int m0 = data ? tile.m % per_batch * S::TM : J.m_data * S::TM + tile.m % per_batch * gemm_zero_rows(S::TM, S::TN);
 
-    const int rows_here = data ? min(J.rows - m0, S::TM) : min(args.zero_end - m0, gemm_zero_rows(S::TN));      // rows of C this workgroup owns
+    const int rows_here = data ? min(J.rows - m0, S::TM) : min(args.zero_end - m0, gemm_zero_rows(S::TM, S::TN));      // rows of C this workgroup owns
     const int rows_data = min(min(J.rows, J.rows_ok) - m0, S::TM);      // of which this many have data in A
     const int cols_here = min(J.N - n0, S::TN);                         // a multiple of 32
 

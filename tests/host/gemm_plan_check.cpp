@@ -1,6 +1,6 @@
 // Goes over the choices of csrc/lss_gemm_plan.h on the host: a launch takes a tile that it has a kernel for, none of the others is estimated
 // shorter, and launches that were measured in every tile take one of the shortest; a weight gradient's chunks cover its rows within the scratch
-// that the header promises; the rows without data are cleared 16384 elements at a time whatever the tile.
+// that the header promises; the rows without data are cleared 16384 elements at a time, or a tile where that is more.
 #include "lss_gemm_plan.h"
 
 #include <cstdio>
@@ -91,8 +91,8 @@ int main()
                 for (const GemmTileCost &c : kGemmTiles) {
                     if (ok > rows) continue;
                     const int64_t done = ((int64_t)ok + c.tm - 1) / c.tm * c.tm, end = skip ? ((int64_t)ok + 255) / 256 * 256 : rows;
-                    const int tiles = gemm_zero_tiles(rows, ok, skip, c.tm, c.tn), zero_end = gemm_zero_end(rows, ok, skip), each = gemm_zero_rows(c.tn);
-                    if (zero_end != (end < rows ? end : rows) || each * c.tn != 16384 || tiles > ((int64_t)rows - ok + each - 1) / each ||
+                    const int tiles = gemm_zero_tiles(rows, ok, skip, c.tm, c.tn), zero_end = gemm_zero_end(rows, ok, skip), each = gemm_zero_rows(c.tm, c.tn);
+                    if (zero_end != (end < rows ? end : rows) || each * c.tn != (c.tm * c.tn > 16384 ? c.tm * c.tn : 16384) || tiles > ((int64_t)rows - ok + each - 1) / each ||
                         done + (int64_t)tiles * each < zero_end || (tiles > 0 && done + (int64_t)(tiles - 1) * each >= zero_end))
                         return fail("rows without data", {1, rows, ok, 128, 128, 1}, c.tm);
                 }

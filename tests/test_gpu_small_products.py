@@ -70,7 +70,7 @@ def test_projections_in_small_tiles(B, l_x, H, s0, l_s):
     ("64x64", 2, 2276, 2, 98, 1946), ("128x128 by two", 1, 2303, 16, 88, 1988), ("128x128", 2, 2449, 16, 117, 2124), ("256x256", 1, 17000, 8, 200, 16500),
 ])
 def test_rows_without_data_are_cleared(tile, B, l_x, H, l_s, rows_valid, skip_tail):
-    """project_bwd clears them 64 KB at a time, whatever its tile: to the last row and no further, and with skip_masked_tail to the next multiple of 256."""
+    """project_bwd clears them 64 KB at a time, or a tile where that is more: to the last row and no further, and with skip_masked_tail to the next multiple of 256."""
     d, E = 64, 64 * H
     assert project_plan(1, B, l_x, H, d, l_s, rows_valid) == tile
     gen = torch.Generator(device="cuda").manual_seed(l_x + rows_valid)
