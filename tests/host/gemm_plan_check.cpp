@@ -30,6 +30,7 @@ static const Measured measured[] = {
     {{{1, 11969, 11969, 1280, 640, 0}, {1, 1426, 1426, 640, 640, 0}}, 2, {TILE_M}},                 // 30.2, 43.2
     {{{4, 2262, 1768, 1280, 2560, 1}, {4, 1463, 1463, 1280, 1280, 0}}, 2, {TILE_L}},                // project_bwd: 80.2, 98.1 in 128 x 128 ones
     {{{3, 653, 610, 640, 1280, 1}, {3, 403, 403, 640, 640, 0}}, 2, {TILE_S}},                       // 19.3, 23.1 in 128 x 128 ones of two groups
+    {{{1, 870, 282, 1152, 2304, 1}, {1, 152, 152, 1152, 1152, 0}}, 2, {TILE_T4}},                   // 16.2 (252 workgroups), 18.4 in 64 x 64 ones
     {{{1, 43186, 2081, 128, 256, 1}, {1, 689, 689, 128, 128, 0}}, 2, {TILE_S, TILE_S4, TILE_T4, TILE_T8}},  // their rows without data cost the same in all
 };
 
