@@ -114,7 +114,8 @@ inline int gemm_zero_tiles(int rows, int rows_ok, bool skip_tail, int tm, int tn
 // Whether a launch may take tiles `t`.  32-wide ones only where one round of workgroups takes them all (of 4000 drawn linear maps that need more none is
 // faster in them, which take 1.4 times as long at two rounds: the weights come once more from the last-level cache, which the estimate does not know;
 // 644 x 6144 -> 1536, 504 workgroups, 49.1 us, in 64 x 64 tiles 41.1; counted as the launch's estimate counts them, per XCD unless A is float:
-// project_bwd's 252 for 282 x 2304 floats -> 1152 and 152 x 1152 -> 1152 16.2 us, in 64 x 64 tiles 18.4), and never with results past the caches, without which their kernel is built
+// project_bwd's 252 for 282 x 2304 floats -> 1152 and 152 x 1152 -> 1152 16.2 us, in 64 x 64 tiles 18.4), and never with results past the caches,
+// without which their kernel is built
 inline bool gemm_takes(GemmTile t, const GemmWork *work, int n, bool a_any, bool streams)
 {
     const GemmTileCost &c = kGemmTiles[t];

@@ -55,7 +55,8 @@ int main()
         const WgradPlan p = pick_wgrad_plan(g.rows, g.batches, g.K, g.N, g.dc_f32);
         bool good = false;
         for (const GemmTile t : g.good) good = good || t == p.tile;
-        if (!good || (kGemmTiles[p.tile].tm == 32 && p.chunk_rows < 4 * kGemmK)) return fail("weight gradient not in one of the shortest", {g.batches, g.rows, g.rows, g.N, g.K, g.dc_f32}, p.tile);
+        if (!good || (kGemmTiles[p.tile].tm == 32 && p.chunk_rows < 4 * kGemmK))
+            return fail("weight gradient not in one of the shortest", {g.batches, g.rows, g.rows, g.N, g.K, g.dc_f32}, p.tile);
     }
     for (int batches : {1, 4, 65535})
         for (int rows : {1, 31, 58, 256, 1000, 2048, 16384, 98304, 0x7fffffff})
@@ -69,9 +70,10 @@ int main()
                             for (int n : {1, 2})
                                 for (bool streams : {false, true}) {
                                     const GemmTile t = pick_gemm_tile(work, n, any, skip, streams);
-                                    if (t < 0 || t >= TILE_COUNT || t == (any ? TILE_M8 : TILE_M2) || (streams && kGemmTiles[t].tm == 32)) return fail("no such kernel", work[0], t);
+                                    if (t < 0 || t >= TILE_COUNT || t == (any ? TILE_M8 : TILE_M2) || (streams && kGemmTiles[t].tm == 32))
+                                        return fail("no such kernel", work[0], t);
                                     double wgs = 0.0;
-                                    for (int i = 0; i < n; ++i) wgs += gemm_workgroups(kGemmTiles[t], work[i], true);
+                                    for (int i = 0; i < n; ++i) wgs += gemm_workgroups(kGemmTiles[t], work[i], !work->a_f32);
                                     if (kGemmTiles[t].tm == 32 && wgs > 256.0) return fail("small tiles, more than one round", work[0], t);
                                     const double us = gemm_launch_estimate(t, work, n, skip);
                                     if (!(us > 0.0)) return fail("no time", work[0], t);
@@ -81,7 +83,9 @@ int main()
                                 }
                             if (rows > 1 << 20) continue;
                             const WgradPlan p = pick_wgrad_plan(rows, batches, K, N, any);
-                            if (p.tile < 0 || p.tile >= TILE_COUNT || p.tile == TILE_M8 || (any && p.tile == TILE_T4) || (kGemmTiles[p.tile].tm == 32 && p.chunk_rows < 4 * kGemmK)) return fail("no such weight gradient", work[0], p.tile);
+                            if (p.tile < 0 || p.tile >= TILE_COUNT || p.tile == TILE_M8 || (any && p.tile == TILE_T4) ||
+                                (kGemmTiles[p.tile].tm == 32 && p.chunk_rows < 4 * kGemmK))
+                                return fail("no such weight gradient", work[0], p.tile);
                             if (p.splits_per_batch < 1 || p.splits_per_batch > wgrad_most_chunks(rows, batches, K, N) || p.splits_per_batch > wgrad_max_chunks(batches, K, N) ||
                                 p.chunk_rows % kGemmK != 0 || (int64_t)p.splits_per_batch * p.chunk_rows < rows || (int64_t)(p.splits_per_batch - 1) * p.chunk_rows >= rows)
                                 return fail("chunks", work[0], p.tile);
