@@ -43,6 +43,7 @@ constexpr int kLdsPerCu = 160 * 1024;
 // ring of its own, take every KG-th contraction tile and add their results up (in group order) at the end.
 template <int TM_, int TN_, int WM_, int WN_, int STAGES_, int KG_ = 1>
 struct GemmShape {
+    static constexpr bool WIDE = false;
     static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, STAGES = STAGES_, KG = KG_;
     static constexpr int MW = TM / WM, NW = TN / WN, GW = MW * NW;      // wavefronts of a group
     static constexpr int WAVES = KG * GW, NT = 64 * WAVES, GT = 64 * GW;
@@ -54,6 +55,22 @@ struct GemmShape {
     static constexpr int PER_CU = kLdsPerCu / LDS;              // workgroups a compute unit holds at once
     static constexpr int WAVES_PER_SIMD = PER_CU * WAVES / 4;   // what the register count has to allow
     static_assert(STAGES >= 2 && LDS <= kLdsPerCu && (KG - 1) * GW * MB * NB * 1024 <= LDS && STEPS % 2 == 0, "");
+};
+
+// The 256 x 256 tile: four wavefronts of 128 x 128, one per SIMD, which take all 512 registers of theirs (the accumulators are half of them).  A
+// compute unit's LDS serves 128 bytes a cycle; eight wavefronts of 128 x 64 read 24 KB a piece per contraction tile, and with the 64 KB that the loads
+// write that is 2048 cycles, as many as the matrix instructions take.  Four of 128 x 128 read 128 KB in all.  Three slots for the activations, which
+// come from memory, two for the weights, which other workgroups have just read: all 160 KB.
+struct GemmWide {
+    static constexpr bool WIDE = true;
+    static constexpr int TM = 256, TN = 256, WM = 128, WN = 128, KG = 1;
+    static constexpr int MW = TM / WM, NW = TN / WN, GW = MW * NW;
+    static constexpr int WAVES = GW, NT = 64 * WAVES, GT = NT;
+    static constexpr int MB = WM / 16, NB = WN / 16;
+    static constexpr int A_SLOTS = 3, W_SLOTS = 2;
+    static constexpr int ABYTES = TM * PK * 2, WBYTES = TN * PK * 2, W_RING = A_SLOTS * ABYTES, LDS = W_RING + W_SLOTS * WBYTES;
+    static constexpr int PER_CU = 1, WAVES_PER_SIMD = 1;
+    static_assert(LDS <= kLdsPerCu && MB == 8 && NB == 8 && PK == 64, "");
 };
 
 struct ProjJob {
@@ -214,6 +231,109 @@ __device__ __forceinline__ void gemm_loop(f32x4 (&acc)[S::MB][S::NB], int T, int
         slot = nxt;
     }
 }
+// The contraction of a GemmWide tile.  A contraction tile is two phases of 32 indices, 64 matrix instructions each, between which everything else is
+// placed one by one: a wavefront alone on its SIMD hides what it issues between two of them and nothing else.  Phase 0 of tile t multiplies the fragments read ahead and
+// reads those of phase 1; then comes the barrier that publishes tile t + 1, behind which no wavefront reads tile t any more, and phase 1 reads the first fragments
+// of t + 1.  Tile t + 2 of A is requested in phase 0 (its slot was tile t - 1's), that of the weights in phase 1 (tile t's own slot).
+//   issue_a(t, slot, i), issue_w(t, slot, i)    load instruction i of a wavefront's NI
+//   load_a(slot, ks, mb), load_w(slot, ks, nb)  a fragment of phase ks
+//   publish(t, aslot, wslot)                    what is left to do for tile t before the barrier that publishes it
+//   REG: the operand that is float and travels through registers instead, in CHUNKS parts of two 16-byte loads per lane: in phase 0 of tile t part c of
+//   tile t + 1 is converted and written to LDS (stash(t + 1, slot, c)) and that of t + 2 requested in its place (fetch(t + 2, c)), a whole tile ahead
+// The matrix instructions are assembly, with accumulators in the accumulation half of the registers: left to itself the compiler rotates the accumulators through
+// the register file, 132 copies per 128 matrix instructions.  An accumulator comes up again 64 instructions later; the wait states before other instructions may read
+// one stand at the end.
+// 16384 x 4096 -> 1024 102 -> 94 us, its input gradient 110 -> 95 (1444 TFLOP/s), 8192 x 8192 -> 8192 777 -> 710 (1548 TFLOP/s), against eight wavefronts
+// of 128 x 64 whose loads started all at once behind one barrier per tile, two slots for either operand.
+enum WideReg { REG_NONE, REG_A, REG_W };
+struct WideFrags { Frag<bf16_t> a[GemmWide::MB], w[GemmWide::NB]; };
+template <WideReg REG, int A_NI, int W_NI, int CHUNKS, typename IssueA, typename IssueW, typename LoadA, typename LoadW, typename Publish, typename Fetch,
+          typename Stash>
+__device__ __forceinline__ void gemm_wide_loop(f32x4 (&acc)[GemmWide::MB][GemmWide::NB], int T, IssueA &&issue_a, IssueW &&issue_w, LoadA &&load_a,
+                                               LoadW &&load_w, Publish &&publish, Fetch &&fetch, Stash &&stash)
+{
+    using S = GemmWide;
+    constexpr int SLOTS = S::MB * S::NB, READS = S::MB + S::NB;
+    constexpr bool DIRECT_A = REG != REG_A, DIRECT_W = REG != REG_W;
+    constexpr int FETCHES = REG == REG_NONE ? 0 : 2 * CHUNKS;
+    constexpr int A_LOADS = DIRECT_A ? A_NI : 0, W_LOADS = DIRECT_W ? W_NI : 0;
+    auto issue_all = [&](int t) __attribute__((always_inline)) {
+        if constexpr (DIRECT_A)
+#pragma unroll
+            for (int i = 0; i < A_NI; ++i) issue_a(t, t, i);
+        if constexpr (DIRECT_W)
+#pragma unroll
+            for (int i = 0; i < W_NI; ++i) issue_w(t, t, i);
+    };
+    auto fetch_all = [&](int t) __attribute__((always_inline)) {
+        if constexpr (REG != REG_NONE)
+#pragma unroll
+            for (int c = 0; c < CHUNKS; ++c) fetch(t, c);
+    };
+    fetch_all(0);
+    issue_all(0);
+    if (T > 1) issue_all(1);
+    if constexpr (REG != REG_NONE)
+#pragma unroll
+        for (int c = 0; c < CHUNKS; ++c) stash(0, 0, c);
+    if (T > 1) {
+        fetch_all(1);
+        wait_vmem<A_LOADS + W_LOADS + FETCHES>();
+    } else wait_vmem_all();
+    publish(0, 0, 0);
+    __syncthreads();
+    WideFrags f[2];
+#pragma unroll
+    for (int i = 0; i < S::NB; ++i) f[0].w[i] = load_w(0, 0, i);
+#pragma unroll
+    for (int i = 0; i < S::MB; ++i) f[0].a[i] = load_a(0, 0, i);
+    int a_slot = 0, w_slot = 0;
+    // AHEAD: there is a tile t + 2, NEXT: a tile t + 1
+    auto tile = [&](int t, auto ahead, auto next) __attribute__((always_inline)) {
+        constexpr bool AHEAD = decltype(ahead)::value, NEXT = decltype(next)::value;
+        const int a_next = a_slot == 2 ? 0 : a_slot + 1, a_free = a_slot == 0 ? 2 : a_slot - 1, w_next = w_slot ^ 1;
+#pragma unroll
+        for (int ph = 0; ph < 2; ++ph) {
+            if (ph == 1 && NEXT) {
+                wait_lds_reads();
+                if constexpr (AHEAD) wait_vmem<A_LOADS + FETCHES>();        // (all but what phase 0 has requested of tile t + 2)
+                else wait_vmem_all();
+                publish(t + 1, a_next, w_next);
+                __syncthreads();
+            }
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s) {
+                const int mb = s / S::NB, nb = s % S::NB;
+                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[mb][nb]) : "v"(f[ph].w[nb].v), "v"(f[ph].a[mb].v));
+                if ((ph == 0 || NEXT) && s % 2 == 0 && s / 2 < READS) {
+                    const int r = s / 2;
+                    if (r < S::NB) f[ph ^ 1].w[r] = load_w(ph == 0 ? w_slot : w_next, ph ^ 1, r);
+                    else f[ph ^ 1].a[r - S::NB] = load_a(ph == 0 ? a_slot : a_next, ph ^ 1, r - S::NB);
+                }
+                if constexpr (REG != REG_NONE) {
+                    constexpr int PER = SLOTS / CHUNKS;
+                    if (ph == 0 && NEXT && s % PER == PER - 1) {
+                        stash(t + 1, REG == REG_A ? a_next : w_next, s / PER);
+                        if (AHEAD) fetch(t + 2, s / PER);
+                    }
+                }
+                if (DIRECT_A && AHEAD && ph == 0 && s % (SLOTS / A_NI) == SLOTS / A_NI / 2 + 1) issue_a(t + 2, a_free, s / (SLOTS / A_NI));
+                if (DIRECT_W && AHEAD && ph == 1 && s % (SLOTS / W_NI) == SLOTS / W_NI / 2 + 1) issue_w(t + 2, w_slot, s / (SLOTS / W_NI));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        a_slot = a_next;
+        w_slot = w_next;
+    };
+    int t = 0;
+    for (; t + 2 < T; ++t) tile(t, std::true_type{}, std::true_type{});
+    if (t + 1 < T) tile(t++, std::false_type{}, std::true_type{});
+    tile(t, std::false_type{}, std::false_type{});
+#pragma unroll
+    for (int mb = 0; mb < S::MB; ++mb)
+        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[mb][0]), "+a"(acc[mb][1]), "+a"(acc[mb][2]), "+a"(acc[mb][3]), "+a"(acc[mb][4]), "+a"(acc[mb][5]),
+                     "+a"(acc[mb][6]), "+a"(acc[mb][7]));
+}
 // Adds the groups' accumulators up into group 0's, in group order, through the (now free) LDS.
 template <typename S>
 __device__ __forceinline__ void gemm_add_groups(char *smem, f32x4 (&acc)[S::MB][S::NB], int group, int gwave, int lane)
@@ -302,7 +422,6 @@ __device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
     const int all_waves = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int group = all_waves / S::GW, wave = all_waves % S::GW, gtid = tid % S::GT;     // wave, gtid: within the group
     const int wm = wave % S::MW, wn = wave / S::MW;
-    char *const ring = smem + group * S::RING;
 
     int ji = 0;
     if (args.n_jobs > 1 && (int)blockIdx.x >= args.job[1].wg_begin && (int)blockIdx.x < args.zero_begin) ji = 1;
@@ -405,40 +524,26 @@ __device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
     auto a_src = [&](int t) -> const char * {   // first element of contraction tile t of this row tile
         return (t < t_split ? a0 + (int64_t)t * PK * AE : a1 + (int64_t)(t - t_split) * PK * AE) + a_tile0;
     };
-    auto issue_w = [&](int t, int slot) {
-        const bf16_t *src = w0 + (W_TR ? (int64_t)t * PK * ldw : (int64_t)t * PK);
-        lds_dma_n<W_NI, S::GW * 1024>(src, offW, ring + slot * S::SLOT + S::ABYTES + wave * 1024);
-    };
-    auto issue_a = [&](int t, int slot) {       // bf16 A: direct
-        lds_dma_n<ATile::NI, S::GW * 1024>(a_src(t), offA, ring + slot * S::SLOT + wave * 1024);
-    };
+    auto w_src = [&](int t) -> const bf16_t * { return w0 + (W_TR ? (int64_t)t * PK * ldw : (int64_t)t * PK); };
     // float A: thread `gtid` converts the 8-element chunks gtid, gtid + GT, ... of the tile
     // (chunk c is columns 8 (c % 8) .. + 7 of row c / 8) and writes them where the direct load would
     constexpr int FCH = S::TM * 8 / S::GT;      // chunks per thread
     f32x4 stage[A_ANY ? 2 * FCH : 1];
-    auto fetch_a = [&](int t) {
+    auto fetch_a = [&](int t, int i) __attribute__((always_inline)) {
         if constexpr (A_ANY) {
-            const char *src = a_src(t);
-#pragma unroll
-            for (int i = 0; i < FCH; ++i) {
-                const int c = i * S::GT + gtid, row = min(c >> 3, rows_data - 1);
-                const f32x4 *p = reinterpret_cast<const f32x4 *>(src + ((int64_t)row * lda + (c & 7) * 8) * 4);
-                stage[2 * i] = p[0];       // (re-read from L2 by the workgroups of the other column tiles)
-                stage[2 * i + 1] = p[1];
-            }
+            const int c = i * S::GT + gtid, row = min(c >> 3, rows_data - 1);
+            const f32x4 *p = reinterpret_cast<const f32x4 *>(a_src(t) + (uint32_t)(row * lda + (c & 7) * 8) * 4u);
+            stage[2 * i] = p[0];       // (re-read from L2 by the workgroups of the other column tiles)
+            stage[2 * i + 1] = p[1];
         }
     };
-    auto stash_a = [&](int slot) {
+    auto stash_a = [&](char *tile_a, int i) __attribute__((always_inline)) {
         if constexpr (A_ANY) {
-            char *dst = ring + slot * S::SLOT;
+            const int c = i * S::GT + gtid;
+            bf16x8 v;
 #pragma unroll
-            for (int i = 0; i < FCH; ++i) {
-                const int c = i * S::GT + gtid;
-                bf16x8 v;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) { v[e] = (bf16_t)stage[2 * i][e]; v[4 + e] = (bf16_t)stage[2 * i + 1][e]; }
-                *reinterpret_cast<bf16x8 *>(dst + ATile::chunk_offset(c >> 3, c & 7)) = v;
-            }
+            for (int e = 0; e < 4; ++e) { v[e] = (bf16_t)stage[2 * i][e]; v[4 + e] = (bf16_t)stage[2 * i + 1][e]; }
+            *reinterpret_cast<bf16x8 *>(tile_a + ATile::chunk_offset(c >> 3, c & 7)) = v;
         }
     };
 
@@ -452,26 +557,57 @@ __device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
     }
 #pragma unroll
     for (int nb = 0; nb < S::NB; ++nb) wt_off[nb] = WTr::lane_offset(lane, S::NB * wn + nb);
-    auto load = [&](int slot, int j, GemmFrags<S> &f) __attribute__((always_inline)) {
-        const char *at = ring + slot * S::SLOT, *wt = at + S::ABYTES;
-        const int ks = j / S::MH, first = j % S::MH * S::HB;
-        if (first == 0) {
+    if constexpr (S::WIDE) {
+        auto load_a = [&](int slot, int ks, int mb) __attribute__((always_inline)) {
+            return load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(smem + slot * S::ABYTES + b_off[ks] + mb * 16 * PK * 2));
+        };
+        auto load_w = [&](int slot, int ks, int nb) __attribute__((always_inline)) {
+            const char *wt = smem + S::W_RING + slot * S::WBYTES;
+            if constexpr (W_TR) return WTr::load_frag(wt, ks, wt_off[nb]);
+            else return load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(wt + w_off[ks] + nb * 16 * PK * 2));
+        };
+        auto issue_a = [&](int t, int slot, int i) __attribute__((always_inline)) {
+            lds_dma<16>(a_src(t), offA[i], smem + slot * S::ABYTES + (i * S::GW + wave) * 1024);
+        };
+        auto issue_w = [&](int t, int slot, int i) __attribute__((always_inline)) {
+            lds_dma<16>(w_src(t), offW[i], smem + S::W_RING + slot * S::WBYTES + (i * S::GW + wave) * 1024);
+        };
+        auto stash = [&](int, int slot, int i) __attribute__((always_inline)) { stash_a(smem + slot * S::ABYTES, i); };
+        auto publish = [](int, int, int) {};
+        if (a_f32) gemm_wide_loop<REG_A, ATile::NI, W_NI, FCH>(acc, T, issue_a, issue_w, load_a, load_w, publish, fetch_a, stash);
+        else gemm_wide_loop<REG_NONE, ATile::NI, W_NI, FCH>(acc, T, issue_a, issue_w, load_a, load_w, publish, fetch_a, stash);
+    } else {
+        char *const ring = smem + group * S::RING;
+        auto load = [&](int slot, int j, GemmFrags<S> &f) __attribute__((always_inline)) {
+            const char *at = ring + slot * S::SLOT, *wt = at + S::ABYTES;
+            const int ks = j / S::MH, first = j % S::MH * S::HB;
+            if (first == 0) {
 #pragma unroll
-            for (int nb = 0; nb < S::NB; ++nb) {
-                if constexpr (W_TR) f.fw[ks & 1][nb] = WTr::load_frag(wt, ks, wt_off[nb]);
-                else f.fw[ks & 1][nb] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(wt + w_off[ks] + nb * 16 * PK * 2));
+                for (int nb = 0; nb < S::NB; ++nb) {
+                    if constexpr (W_TR) f.fw[ks & 1][nb] = WTr::load_frag(wt, ks, wt_off[nb]);
+                    else f.fw[ks & 1][nb] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(wt + w_off[ks] + nb * 16 * PK * 2));
+                }
             }
-        }
 #pragma unroll
-        for (int mb = 0; mb < S::HB; ++mb)
-            f.fb[j & 1][mb] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(at + b_off[ks] + (first + mb) * 16 * PK * 2));
-    };
-    auto issue = [&](int t, int slot) {
-        if (!a_f32) issue_a(t, slot);
-        issue_w(t, slot);
-    };
-    gemm_loop<S, LOADS, !A_ANY>(acc, T, group, a_f32, issue, load, [](int, int) {}, fetch_a, [&](int, int slot) { stash_a(slot); });
-    gemm_add_groups<S>(smem, acc, group, wave, lane);
+            for (int mb = 0; mb < S::HB; ++mb)
+                f.fb[j & 1][mb] = load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(at + b_off[ks] + (first + mb) * 16 * PK * 2));
+        };
+        auto issue = [&](int t, int slot) {
+            char *const dst = ring + slot * S::SLOT + wave * 1024;
+            if (!a_f32) lds_dma_n<ATile::NI, S::GW * 1024>(a_src(t), offA, dst);        // bf16 A: direct
+            lds_dma_n<W_NI, S::GW * 1024>(w_src(t), offW, dst + S::ABYTES);
+        };
+        auto fetch = [&](int t) {
+#pragma unroll
+            for (int i = 0; i < FCH; ++i) fetch_a(t, i);
+        };
+        auto stash = [&](int, int slot) {
+#pragma unroll
+            for (int i = 0; i < FCH; ++i) stash_a(ring + slot * S::SLOT, i);
+        };
+        gemm_loop<S, LOADS, !A_ANY>(acc, T, group, a_f32, issue, load, [](int, int) {}, fetch, stash);
+        gemm_add_groups<S>(smem, acc, group, wave, lane);
+    }
     store_tiles(acc);
 }
 template <typename S, bool A_ANY, bool W_TR, bool OUT_F32, int EPI>
@@ -517,7 +653,6 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
     const int all_waves = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int group = all_waves / S::GW, wave = all_waves % S::GW, gtid = tid % S::GT;     // wave, gtid: within the group
     const int wm = wave % S::MW, wn = wave / S::MW;
-    char *const ring = smem + group * S::RING;
 
     // An XCD walks the output tiles of one chunk of rows after the other, so that the chunk's rows of A and dC are read from HBM
     // once per XCD, and those in blocks of four tiles down, tile by tile of a column: where an XCD has only some of a chunk's tiles,
@@ -545,66 +680,51 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
         WTile::offsets(offW_last, g.ldc, wave, lane, cols_n / 8, tail);
     }
     const bf16_t *a_base = g.a + (int64_t)batch * g.a_batch_stride + (int64_t)r0 * g.lda + m0;
-    auto issue = [&](int t, int slot) {
-        char *dst = ring + slot * S::SLOT + wave * 1024;
-        const bf16_t *pa = a_base + (int64_t)t * PK * g.lda;
-        if (t == T - 1) lds_dma_n<ATile::NI, S::GW * 1024>(pa, offA_last, dst);
-        else lds_dma_n<ATile::NI, S::GW * 1024>(pa, offA, dst);
-        if constexpr (!DC_F32) {
-            const bf16_t *pw = static_cast<const bf16_t *>(g.dc0) + (int64_t)batch * g.dc_batch_stride + (int64_t)(r0 + t * PK) * g.ldc + n0;
-            if (t == T - 1) lds_dma_n<WTile::NI, S::GW * 1024>(pw, offW_last, dst + S::ABYTES);
-            else lds_dma_n<WTile::NI, S::GW * 1024>(pw, offW, dst + S::ABYTES);
-        }
+    auto a_src = [&](int t) -> const bf16_t * { return a_base + (int64_t)t * PK * g.lda; };
+    auto w_src = [&](int t) -> const bf16_t * {
+        return static_cast<const bf16_t *>(g.dc0) + (int64_t)batch * g.dc_batch_stride + (int64_t)(r0 + t * PK) * g.ldc + n0;
     };
     // Rows past the end of the chunk re-read its last row; their copies in the tiles are replaced
     // by zeros, each lane clearing exactly the 16 bytes its own loads wrote (after waiting for them).
-    auto clear_tail = [&](int slot) {
+    auto clear_tail = [&](char *tile_a, char *tile_w) {
         if (tail == PK) return;
-        char *dst = ring + slot * S::SLOT;
 #pragma unroll
         for (int i = 0; i < ATile::NI; ++i)
             if (ATile::row_of(i, wave, lane) >= tail)
-                *reinterpret_cast<f32x4 *>(dst + (i * S::GW + wave) * 1024 + lane * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+                *reinterpret_cast<f32x4 *>(tile_a + (i * S::GW + wave) * 1024 + lane * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
         if constexpr (!DC_F32) {
 #pragma unroll
             for (int i = 0; i < WTile::NI; ++i)
                 if (WTile::row_of(i, wave, lane) >= tail)
-                    *reinterpret_cast<f32x4 *>(dst + S::ABYTES + (i * S::GW + wave) * 1024 + lane * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+                    *reinterpret_cast<f32x4 *>(tile_w + (i * S::GW + wave) * 1024 + lane * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
         }
     };
     // float dC: thread `gtid` converts the 8-column chunks gtid, gtid + GT, ... of the [64][TN] tile and
     // writes them where the direct load would; rows past the end of the chunk are written as zeros
     constexpr int FCH = PK * (S::TN / 8) / S::GT;   // chunks per thread
     f32x4 stage[DC_F32 ? 2 * FCH : 1];
-    auto fetch_w = [&](int t) {
+    auto fetch_w = [&](int t, int i) __attribute__((always_inline)) {
         if constexpr (DC_F32) {
             const int rows_here = t == T - 1 ? tail : PK;
-#pragma unroll
-            for (int i = 0; i < FCH; ++i) {
-                const int c = i * S::GT + gtid, row = min(c / WTile::CPR, rows_here - 1), col = min(c % WTile::CPR, cols_n / 8 - 1);
-                const int n = n0 + col * 8;
-                const float *src = n < g.n_split ? static_cast<const float *>(g.dc0) + n : static_cast<const float *>(g.dc1) + (n - g.n_split);
-                const f32x4 *p = reinterpret_cast<const f32x4 *>(src + (int64_t)batch * g.dc_batch_stride + (int64_t)(r0 + t * PK + row) * g.ldc);
-                stage[2 * i] = p[0];
-                stage[2 * i + 1] = p[1];
-            }
+            const int c = i * S::GT + gtid, row = min(c / WTile::CPR, rows_here - 1), col = min(c % WTile::CPR, cols_n / 8 - 1);
+            const int n = n0 + col * 8;
+            const float *src = n < g.n_split ? static_cast<const float *>(g.dc0) + n : static_cast<const float *>(g.dc1) + (n - g.n_split);
+            const f32x4 *p = reinterpret_cast<const f32x4 *>(src + (int64_t)batch * g.dc_batch_stride + (int64_t)(r0 + t * PK + row) * g.ldc);
+            stage[2 * i] = p[0];
+            stage[2 * i + 1] = p[1];
         }
     };
-    auto stash_w = [&](int t, int slot) {
+    auto stash_w = [&](int t, char *tile_w, int i) __attribute__((always_inline)) {
         if constexpr (DC_F32) {
             const int rows_here = t == T - 1 ? tail : PK;
-            char *dst = ring + slot * S::SLOT + S::ABYTES;
+            const int c = i * S::GT + gtid, row = c / WTile::CPR, col = c % WTile::CPR;
+            bf16x8 v;
 #pragma unroll
-            for (int i = 0; i < FCH; ++i) {
-                const int c = i * S::GT + gtid, row = c / WTile::CPR, col = c % WTile::CPR;
-                bf16x8 v;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    v[e] = row < rows_here ? (bf16_t)stage[2 * i][e] : (bf16_t)0.f;
-                    v[4 + e] = row < rows_here ? (bf16_t)stage[2 * i + 1][e] : (bf16_t)0.f;
-                }
-                *reinterpret_cast<bf16x8 *>(dst + WTile::chunk_offset(row, col)) = v;
+            for (int e = 0; e < 4; ++e) {
+                v[e] = row < rows_here ? (bf16_t)stage[2 * i][e] : (bf16_t)0.f;
+                v[4 + e] = row < rows_here ? (bf16_t)stage[2 * i + 1][e] : (bf16_t)0.f;
             }
+            *reinterpret_cast<bf16x8 *>(tile_w + WTile::chunk_offset(row, col)) = v;
         }
     };
 
@@ -616,21 +736,57 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
     for (int nb = 0; nb < S::NB; ++nb) wt_off[nb] = WTile::lane_offset(lane, S::NB * wn + nb);
     f32x4 acc[S::MB][S::NB];
     gemm_clear<S>(acc);
-    auto load = [&](int slot, int j, GemmFrags<S> &f) __attribute__((always_inline)) {
-        const char *at = ring + slot * S::SLOT, *wt = at + S::ABYTES;
-        const int ks = j / S::MH, first = j % S::MH * S::HB;
-        if (first == 0) {
+    if constexpr (S::WIDE) {
+        auto load_a = [&](int slot, int ks, int mb) __attribute__((always_inline)) { return ATile::load_frag(smem + slot * S::ABYTES, ks, at_off ^ (mb * 32)); };
+        auto load_w = [&](int slot, int ks, int nb) __attribute__((always_inline)) {
+            return WTile::load_frag(smem + S::W_RING + slot * S::WBYTES, ks, wt_off[nb]);
+        };
+        auto issue_a = [&](int t, int slot, int i) __attribute__((always_inline)) {
+            lds_dma<16>(a_src(t), t == T - 1 ? offA_last[i] : offA[i], smem + slot * S::ABYTES + (i * S::GW + wave) * 1024);
+        };
+        auto issue_w = [&](int t, int slot, int i) __attribute__((always_inline)) {
+            if constexpr (!DC_F32) lds_dma<16>(w_src(t), t == T - 1 ? offW_last[i] : offW[i], smem + S::W_RING + slot * S::WBYTES + (i * S::GW + wave) * 1024);
+        };
+        auto publish = [&](int t, int a_slot, int w_slot) __attribute__((always_inline)) {
+            if (t == T - 1) clear_tail(smem + a_slot * S::ABYTES, smem + S::W_RING + w_slot * S::WBYTES);
+        };
+        auto stash = [&](int t, int slot, int i) __attribute__((always_inline)) { stash_w(t, smem + S::W_RING + slot * S::WBYTES, i); };
+        gemm_wide_loop<DC_F32 ? REG_W : REG_NONE, ATile::NI, WTile::NI, FCH>(acc, T, issue_a, issue_w, load_a, load_w, publish, fetch_w, stash);
+    } else {
+        char *const ring = smem + group * S::RING;
+        auto load = [&](int slot, int j, GemmFrags<S> &f) __attribute__((always_inline)) {
+            const char *at = ring + slot * S::SLOT, *wt = at + S::ABYTES;
+            const int ks = j / S::MH, first = j % S::MH * S::HB;
+            if (first == 0) {
 #pragma unroll
-            for (int nb = 0; nb < S::NB; ++nb) f.fw[ks & 1][nb] = WTile::load_frag(wt, ks, wt_off[nb]);
-        }
+                for (int nb = 0; nb < S::NB; ++nb) f.fw[ks & 1][nb] = WTile::load_frag(wt, ks, wt_off[nb]);
+            }
 #pragma unroll
-        for (int mb = 0; mb < S::HB; ++mb) f.fb[j & 1][mb] = ATile::load_frag(at, ks, at_off ^ ((first + mb) * 32));
-    };
-    auto publish = [&](int t, int slot) {
-        if (t == T - 1) clear_tail(slot);
-    };
-    gemm_loop<S, LOADS, false>(acc, T, group, DC_F32, issue, load, publish, fetch_w, stash_w);
-    gemm_add_groups<S>(smem, acc, group, wave, lane);
+            for (int mb = 0; mb < S::HB; ++mb) f.fb[j & 1][mb] = ATile::load_frag(at, ks, at_off ^ ((first + mb) * 32));
+        };
+        auto issue = [&](int t, int slot) {
+            char *const dst = ring + slot * S::SLOT + wave * 1024;
+            if (t == T - 1) lds_dma_n<ATile::NI, S::GW * 1024>(a_src(t), offA_last, dst);
+            else lds_dma_n<ATile::NI, S::GW * 1024>(a_src(t), offA, dst);
+            if constexpr (!DC_F32) {
+                if (t == T - 1) lds_dma_n<WTile::NI, S::GW * 1024>(w_src(t), offW_last, dst + S::ABYTES);
+                else lds_dma_n<WTile::NI, S::GW * 1024>(w_src(t), offW, dst + S::ABYTES);
+            }
+        };
+        auto publish = [&](int t, int slot) {
+            if (t == T - 1) clear_tail(ring + slot * S::SLOT, ring + slot * S::SLOT + S::ABYTES);
+        };
+        auto fetch = [&](int t) {
+#pragma unroll
+            for (int i = 0; i < FCH; ++i) fetch_w(t, i);
+        };
+        auto stash = [&](int t, int slot) {
+#pragma unroll
+            for (int i = 0; i < FCH; ++i) stash_w(t, ring + slot * S::SLOT + S::ABYTES, i);
+        };
+        gemm_loop<S, LOADS, false>(acc, T, group, DC_F32, issue, load, publish, fetch, stash);
+        gemm_add_groups<S>(smem, acc, group, wave, lane);
+    }
 
     float *out = g.out + (int64_t)split * g.K * g.N + (int64_t)m0 * g.N + n0;
 #pragma unroll
@@ -651,7 +807,7 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
 }
 
 // ---- the tiles a launch may take
-using ShapeL = GemmShape<256, 256, 128, 64, 2>;         // eight wavefronts, one workgroup per compute unit
+using ShapeL = GemmWide;                                // four wavefronts, one workgroup per compute unit
 using ShapeM = GemmShape<128, 128, 64, 64, 2>;          // four wavefronts, two workgroups per compute unit
 using ShapeM2 = GemmShape<128, 128, 64, 64, 2, 2>;      // ... two such groups share the contraction
 using ShapeM8 = GemmShape<128, 128, 64, 32, 4>;         // ... eight wavefronts of one group, four tiles on their way

@@ -137,3 +137,51 @@ def test_projections_weight_gradient_of_float_partials(tile, chunks):
     assert _close(dw_kv, sum(x[b, :rv].double().T @ rounded[b] for b in range(B)), "f32")
     assert _close(dw_q, sum(x[b, rv - l_s:rv].double().T @ dq[b].reshape(l_s, E).double() for b in range(B)), "f32")
     assert torch.equal(dw_kv, lss.lss_project_bwd_weight(x, dq, dk, dv, rv - l_s, rv)[1])
+
+
+# The 256 x 256 tile's loop takes its last two contraction tiles by themselves and goes round three slots of one operand and two of the other: every
+# length modulo 6, last tiles of one, some and all rows; and the shortest contraction it meets (four tiles; eight of the floats).
+SHORT = {"qkv": (1, 60001, 4, 100, 59998), "bwd": (1, 60001, 4, 100, 59998)}
+LENGTHS = (513, 575, 640, 641, 704, 768, 769, 832)
+FLOAT_LENGTHS = (1409, 1472, 1473, 1536, 1600, 1664, 1728)
+
+
+def test_lengths_take_the_256x256_tile():
+    """(needs no GPU)"""
+    for op, name in enumerate(SHORT):
+        B, l_x, H, l_s, rv = SHORT[name]
+        assert project_plan(op, B, l_x, H, 64, l_s, rv) == "256x256", name
+    for rows in LENGTHS:
+        assert linear_plan(2, rows, 1664, 5248) == ("256x256", 1), rows
+    for rv in FLOAT_LENGTHS:
+        assert project_plan(2, 3, rv + 10, 14, 64, 335, rv)[2] == "256x256", rv
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", LENGTHS)
+def test_weight_gradient_of_every_length_of_the_loop(rows):
+    a, dc = _rand(rows, (rows, 1664), (rows, 5248))
+    assert _close(lss.lss_linear_bwd_weight(a, dc), a.double().T @ dc.double(), "f32")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rv", FLOAT_LENGTHS)
+def test_float_weight_gradient_of_every_length_of_the_loop(rv):
+    x, dq = _rand(rv, (3, rv + 10, 896), (3, 335, 14, 64))
+    dk, dv, rounded = _partials(rv, 3, rv + 10, 14, rv)
+    dw_kv = lss.lss_project_bwd_weight(x, dq, dk, dv, rv - 335, rv)[1]
+    assert _close(dw_kv, sum(x[b, :rv].double().T @ rounded[b] for b in range(3)), "f32")
+
+
+@pytest.mark.gpu
+def test_projections_of_the_shortest_contractions_of_the_loop():
+    B, l_x, H, l_s, rv = SHORT["qkv"]
+    E, s0 = 64 * H, rv - l_s
+    x, w_q, w_kv, dq = _rand(l_x, (B, l_x, E), (E, E), (E, 2 * E), (B, l_s, H, 64))
+    _, k, v = lss.lss_project_qkv(x, w_q, w_kv, s0, l_s, H)
+    kv = x[0].double() @ w_kv.double()
+    assert _close(k.view(l_x, E), kv[:, :E], "bf16") and _close(v.view(l_x, E), kv[:, E:], "bf16")
+    dk, dv, rounded = _partials(l_x, B, l_x, H, rv)
+    dx_q, dx = lss.lss_project_bwd(dq, dk, dv, w_q, w_kv, rv)
+    assert _close(dx_q[0], dq[0].reshape(l_s, E).double() @ w_q.double().T, "f32")
+    assert _close(dx[0, :rv], rounded[0] @ w_kv.double().T, "f32") and not dx[:, rv:].any()
