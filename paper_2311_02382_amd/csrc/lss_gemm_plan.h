@@ -21,10 +21,10 @@ struct GemmTileCost { int tm, tn, groups, per_cu; double fixed, per_tile[2]; };
 // three), 0.8 % over 3744 weight gradients, 1.9 % in project_bwd, 2.4 % in the weight gradients of its float partials.  Large tiles move the fewest bytes per flop
 // but a launch of few of them leaves compute units idle (2048 x 2048 -> 512: 16 workgroups of 256 x 256, 46 us;
 // 256 of 64 x 64, 12 us with the former loop), and where even 64 x 64 tiles leave one wavefront per SIMD the chain of contraction
-// tiles is what takes the time: four groups of wavefronts that share it took 9 us in a graph of them, 12 among other work now.
+// tiles is what takes the time, which groups of wavefronts share (S4: two, four when the figures were fitted).
 constexpr GemmTileCost kGemmTiles[TILE_COUNT] = {
     {256, 256, 1, 1, 6.5, {1.40, 1.70}}, {128, 128, 1, 2, 2.8, {0.62, 1.00}}, {128, 128, 2, 1, 3.0, {0.50, 0.58}}, {128, 128, 1, 1, 2.5, {0.51, 0.585}},
-    {64, 64, 1, 2, 2.5, {0.30, 0.40}}, {64, 64, 4, 1, 3.3, {0.165, 0.22}}, {32, 64, 4, 1, 3.0, {0.117, 0.165}}, {32, 32, 8, 1, 3.2, {0.069, 0.107}}};
+    {64, 64, 1, 2, 2.5, {0.30, 0.40}}, {64, 64, 2, 1, 3.3, {0.165, 0.22}}, {32, 64, 4, 1, 3.0, {0.117, 0.165}}, {32, 32, 4, 1, 3.2, {0.069, 0.107}}};
 
 // `tiles`: contraction tiles of a workgroup on average, `rest_tiles`: of those in the last, part-filled round
 inline double gemm_estimate(const GemmTileCost &c, double wgs, double tiles, double rest_tiles)

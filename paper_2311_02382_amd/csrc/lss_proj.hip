@@ -470,23 +470,36 @@ __device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
         if constexpr (A_ANY && S::TM == 256) asm("" : "+v"(t));       // (what is worked out from it is not kept through the loop, which spills)
 #pragma unroll
         for (int pass = 0; pass < Store::PASSES; ++pass) {
-            __syncthreads();        // every wavefront is done with what the LDS held
-            if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, t & 63, rows_data);
-            __syncthreads();
             const int c = t % Store::CPR, col = pass * Store::CPP + c * Store::CW;
             const int n = n0 + col;         // column of C; a chunk never straddles n_split
             OutT *dst = n < n_split ? c0 + n : c1 + (n - n_split);
+            // (U is read eight chunks ahead, the first ahead of the results' way through LDS.  Chunk by chunk a wavefront waited 1.3 us for each: input
+            // gradient with GeLU' of 2048 x 512 -> 2048 11.4 -> 11.1 us, its operands in the caches)
+            constexpr int AHEAD = Store::ITS < 8 ? Store::ITS : 8;
+            bf16x8 uu[AHEAD];
+            auto fetch_u = [&](int i0) __attribute__((always_inline)) {
+                if constexpr (EPI == EPI_GELU_BWD)
+#pragma unroll
+                    for (int k = 0; k < AHEAD; ++k) {
+                        const int m = min((i0 + k) * Store::ROWS_PER_IT + t / Store::CPR, rows_here - 1);
+                        uu[k] = *reinterpret_cast<const bf16x8 *>(gelu_u + (int64_t)m * ldc + min(n, n0 + cols_here - Store::CW));
+                    }
+            };
+            fetch_u(0);
+            __syncthreads();        // every wavefront is done with what the LDS held
+            if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, t & 63, rows_data);
+            __syncthreads();
 #pragma unroll
             for (int i = 0; i < Store::ITS; ++i) {
                 const int m = i * Store::ROWS_PER_IT + t / Store::CPR;
+                if (i > 0 && i % AHEAD == 0) fetch_u(i);
                 f32x4 raw = {0.f, 0.f, 0.f, 0.f};
                 if (m < S::TM) raw = *reinterpret_cast<const f32x4 *>(smem + Store::offset(m, c));
                 if (col < cols_here && m < rows_here) {
                     if constexpr (EPI == EPI_GELU_BWD) {
-                        const bf16x8 uu = *reinterpret_cast<const bf16x8 *>(gelu_u + (int64_t)m * ldc + n);
                         bf16x8 cv = __builtin_bit_cast(bf16x8, raw);
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) cv[e] = (bf16_t)((float)cv[e] * gelu_slope((float)uu[e]));
+                        for (int e = 0; e < 8; ++e) cv[e] = (bf16_t)((float)cv[e] * gelu_slope((float)uu[i % AHEAD][e]));
                         raw = __builtin_bit_cast(f32x4, cv);
                     }
                     put16(dst + (int64_t)m * ldc, raw);
@@ -812,12 +825,15 @@ using ShapeM = GemmShape<128, 128, 64, 64, 2>;          // four wavefronts, two 
 using ShapeM2 = GemmShape<128, 128, 64, 64, 2, 2>;      // ... two such groups share the contraction
 using ShapeM8 = GemmShape<128, 128, 64, 32, 4>;         // ... eight wavefronts of one group, four tiles on their way
 using ShapeS = GemmShape<64, 64, 32, 32, 4>;
-using ShapeS4 = GemmShape<64, 64, 32, 32, 2, 4>;
+// The smaller tiles wait for their operands' bytes, of which two or four groups of wavefronts with three or four tiles each on their way ask for more at a time
+// than twice the groups with two: the six products of a feed-forward unit in a row, 2048 x 512 67.2 -> 60.5 us in 64 x 64 tiles (one group with eight
+// 70.5), 500 x 1024 75.4 -> 68.4 in 32 x 64 ones (two groups with five 69.8), 232 x 1024 58.3 -> 53.3 in 32 x 32 ones (two groups with eight 56.0).
+using ShapeS4 = GemmShape<64, 64, 32, 32, 4, 2>;        // two groups of four wavefronts
 // Where 64 x 64 tiles leave most compute units without one, what a launch waits for is a workgroup's own operand bytes, of which a compute unit
 // gets 40 to 60 per cycle: smaller tiles spread them, although there are more of them.  58 x 4096 -> 1024: S4 14.7 us, T4 11.2, T8 8.6;
-// 256 x 2048 -> 2048 9.7, 8.0, 13.2; dW of 512 x 512 from 1024 rows 7.6 and 5.6 in either.
-using ShapeT4 = GemmShape<32, 64, 32, 32, 2, 4>;        // two wavefronts, four such groups
-using ShapeT8 = GemmShape<32, 32, 32, 32, 2, 8>;        // one wavefront, eight such groups
+// 256 x 2048 -> 2048 9.7, 8.0, 13.2; dW of 512 x 512 from 1024 rows 7.6 and 5.6 in either (all three with the groups and slots there were before).
+using ShapeT4 = GemmShape<32, 64, 32, 32, 3, 4>;        // two wavefronts, four such groups
+using ShapeT8 = GemmShape<32, 32, 32, 32, 4, 4>;        // one wavefront, four such groups
 
 template <typename S, bool A_ANY, bool W_TR, bool OUT_F32, int EPI>
 hipError_t launch_proj_shape(ProjArgs &args, int kernel_id, hipStream_t st)
