@@ -25,17 +25,21 @@ __device__ __forceinline__ void lds_dma(const void *g_uniform, uint32_t voff, co
     else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds_addr), "v"(voff), "s"(g_uniform) : "memory", "m0");
 }
 
+// A pointer that is wavefront-uniform by contract; said again so that it is kept in scalar registers
+__device__ __forceinline__ const void *uniform_ptr(const void *ptr)
+{
+    const uint64_t p = (uint64_t)ptr;
+    return reinterpret_cast<const void *>((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p) |
+                                          (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) << 32);
+}
+
 // N loads of 16 bytes per lane like lds_dma<16>, all from one wavefront-uniform base, load i to lds_uniform + i * STEP
 // bytes: one assembly block, so that M0 is saved and restored once and merely stepped from load to load.
 template <int N, int STEP>
 __device__ __forceinline__ void lds_dma_n(const void *g_uniform, const uint32_t (&off)[N], const void *lds_uniform)
 {
     static_assert(N == 1 || N == 2 || N == 4 || N == 8, "");
-    {   // (uniform by contract; said again so that it is kept in scalar registers)
-        const uint64_t p = (uint64_t)g_uniform;
-        g_uniform = reinterpret_cast<const void *>((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p) |
-                                                   (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) << 32);
-    }
+    g_uniform = uniform_ptr(g_uniform);
     const uint32_t lds_addr = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)lds_uniform;
     uint32_t saved;
 #define LSS_FIRST "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %2\n\t"

@@ -375,7 +375,8 @@ __device__ __forceinline__ void gemm_clear(f32x4 (&acc)[S::MB][S::NB])
 // pieces: the 16-byte chunk c of row m sits at chunk position c ^ (m % chunks per row).
 // Accumulator block (mb, nb), element v of a lane: row m = WM wm + 16 mb + lane % 16, column n = WN wn +
 // 16 nb + 4 (lane / 16) + v.  Rows >= rows_data are written as zeros.
-template <typename S, bool OUT_F32>
+// (ZEROS: whether rows >= rows_data are.)
+template <typename S, bool OUT_F32, bool ZEROS>
 struct GemmStore {
     static constexpr int EB = OUT_F32 ? 4 : 2, CW = 16 / EB;            // bytes per element, columns per chunk
     static constexpr int PASSES = S::TM * S::TN * EB > S::LDS ? 2 : 1;
@@ -394,12 +395,63 @@ struct GemmStore {
             const bool data = m < rows_data;
 #pragma unroll
             for (int nb = 0; nb < S::NB; ++nb) {
-                f32x4 val = {0.f, 0.f, 0.f, 0.f};
-                if (data) val = acc[mb][nb];
+                f32x4 val = acc[mb][nb];
+                if (ZEROS && !data) val = f32x4{0.f, 0.f, 0.f, 0.f};
                 if constexpr (OUT_F32)
                     *reinterpret_cast<f32x4 *>(smem + offset(m, c_first + 4 * nb + g)) = val;
                 else
                     *reinterpret_cast<bf16x4 *>(smem + offset(m, c_first + 2 * nb + (g >> 1)) + (g & 1) * 8) = pack4(val[0], val[1], val[2], val[3]);
+            }
+        }
+    }
+};
+
+// A finished GemmWide tile goes out in four quarters of 64 rows, 32 from either pair of wavefronts, through two regions of LDS by turns: a quarter's stores
+// are on their way while the next one is converted, and one barrier per quarter will do.  (In one piece, or floats in halves by columns, which left two of the
+// four wavefronts idle at a time, a tile took 2.1 us to get into LDS and 3.1 out of it, one after the other.)
+//   begin(rows)        ahead of a quarter; rows(k) is the row of its k-th chunk
+//   put(m, k, raw)     16 bytes of row m, the thread's k-th chunk of the quarter; their column is CW (t % CPR)
+template <bool OUT_F32, bool ZEROS>
+struct WideStore {
+    using S = GemmWide;
+    static constexpr int EB = OUT_F32 ? 4 : 2, CW = 16 / EB, CPR = S::TN / CW;      // bytes per element, columns per chunk, chunks per row
+    static constexpr int REGION = 64 * S::TN * EB, ITS = 64 * CPR / S::NT, RPI = S::NT / CPR;
+    static_assert(2 * REGION <= S::LDS, "");
+    static __device__ __forceinline__ int offset(int r, int c) { return r * (S::TN * EB) + ((c ^ (r & (CPR - 1))) * 16); }
+    template <typename Begin, typename Put>
+    static __device__ __forceinline__ void store(char *smem, const f32x4 (&acc)[S::MB][S::NB], int wm, int wn, int t, int rows_data, Begin &&begin, Put &&put)
+    {
+        const int lane = t & 63, g = lane >> 4;
+        __syncthreads();        // every wavefront is done with what the LDS held
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            char *const region = smem + (q & 1) * REGION;
+            auto row = [&](int k) { const int r = k * RPI + t / CPR; return S::WM * (r >> 5) + 32 * q + (r & 31); };
+            begin(row);
+#pragma unroll
+            for (int mb = 2 * q; mb < 2 * q + 2; ++mb) {
+                const int r = 32 * wm + 16 * (mb & 1) + (lane & 15);
+                const bool data = S::WM * wm + 16 * mb + (lane & 15) < rows_data;
+#pragma unroll
+                for (int nb = 0; nb < S::NB; ++nb) {
+                    f32x4 val = acc[mb][nb];
+                    if (ZEROS && !data) val = f32x4{0.f, 0.f, 0.f, 0.f};
+                    const int c = (S::WN * wn + 16 * nb) / CW;
+                    if constexpr (OUT_F32) *reinterpret_cast<f32x4 *>(region + offset(r, c + g)) = val;
+                    else *reinterpret_cast<bf16x4 *>(region + offset(r, c + (g >> 1)) + (g & 1) * 8) = pack4(val[0], val[1], val[2], val[3]);
+                }
+            }
+            __syncthreads();
+            f32x4 raw[8];
+#pragma unroll
+            for (int k = 0; k < ITS; ++k) {
+                if (k % 8 == 0) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) raw[i] = *reinterpret_cast<const f32x4 *>(region + offset((k + i) * RPI + t / CPR, t % CPR));
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(raw[i]));        // (not read one by one, each ahead of its store)
+                }
+                put(row(k), k, raw[k % 8]);
             }
         }
     }
@@ -411,7 +463,6 @@ __device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
 {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     using OutT = typename std::conditional<OUT_F32, float, bf16_t>::type;
-    using Store = GemmStore<S, OUT_F32>;
     using ATile = DirectTile<PK, S::TM, S::GW>;         // activations [TM m][64 k]
     using WPlain = DirectTile<PK, S::TN, S::GW>;        // weights [TN n][64 k]
     using WTr = TrTile<S::TN, S::GW>;                   // weights [64 k][TN n]
@@ -457,58 +508,78 @@ __device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
         } else *static_cast<f32x4 *>(to) = v;
     };
     if (!data) {
-        constexpr int CPR = S::TN / Store::CW, ROWS_PER_IT = S::NT / CPR;
+        constexpr int CW = OUT_F32 ? 4 : 8, CPR = S::TN / CW, ROWS_PER_IT = S::NT / CPR;
         int t = tid;
         asm("" : "+v"(t));      // (or column and row are worked out ahead of the branch and kept in registers for the other side's stores)
-        const int col = t % CPR * Store::CW;
+        const int col = t % CPR * CW;
         if (col < cols_here)
             for (int m = t / CPR; m < rows_here; m += ROWS_PER_IT) put16(c0 + n0 + col + (int64_t)m * ldc, f32x4{0.f, 0.f, 0.f, 0.f});
         return;
     }
-    auto store_tiles = [&](const f32x4 (&acc)[S::MB][S::NB]) {
+    // 16 bytes of results, the element `at` of the tile's rows of C, to `to`
+    auto put_chunk = [&](OutT *to, int64_t at, f32x4 raw, const bf16x8 &uu) __attribute__((always_inline)) {
+        if constexpr (EPI == EPI_GELU_BWD) {
+            bf16x8 cv = __builtin_bit_cast(bf16x8, raw);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) cv[e] = (bf16_t)((float)cv[e] * gelu_slope((float)uu[e]));
+            raw = __builtin_bit_cast(f32x4, cv);
+        }
+        put16(to, raw);
+        if constexpr (EPI == EPI_GELU) {
+            bf16x8 cv = __builtin_bit_cast(bf16x8, raw);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) cv[e] = (bf16_t)gelu_value((float)cv[e]);
+            put16(c1 + at, __builtin_bit_cast(f32x4, cv));
+        }
+    };
+    // U of a chunk, read ahead of the results' way through LDS.  (Behind it, chunk by chunk, a wavefront waited 1.3 us for each: input
+    // gradient with GeLU' of 2048 x 512 -> 2048 11.4 -> 11.1 us, its operands in the caches.)
+    auto fetch_u = [&](int m, int n) __attribute__((always_inline)) {
+        return *reinterpret_cast<const bf16x8 *>(gelu_u + (int64_t)min(m, rows_here - 1) * ldc + min(n, n0 + cols_here - 8));
+    };
+    auto store_tiles = [&](const f32x4 (&acc)[S::MB][S::NB]) __attribute__((always_inline)) {
         int t = tid;
-        if constexpr (A_ANY && S::TM == 256) asm("" : "+v"(t));       // (what is worked out from it is not kept through the loop, which spills)
+        if constexpr (S::WIDE) {
+            using Store = WideStore<OUT_F32, A_ANY>;
+            if constexpr (A_ANY) asm("" : "+v"(t));       // (what is worked out from it is not kept through the loop, which spills)
+            const int n = n0 + t % Store::CPR * Store::CW;          // column of C; a chunk never straddles n_split
+            OutT *const dst = n < n_split ? c0 + n : c1 + (n - n_split);
+            const bool column = n < n0 + cols_here;
+            bf16x8 uu[8];
+            Store::store(smem, acc, wm, wn, t, rows_data,
+                         [&](auto &&row) __attribute__((always_inline)) {
+                             if constexpr (EPI == EPI_GELU_BWD)
 #pragma unroll
-        for (int pass = 0; pass < Store::PASSES; ++pass) {
-            const int c = t % Store::CPR, col = pass * Store::CPP + c * Store::CW;
-            const int n = n0 + col;         // column of C; a chunk never straddles n_split
-            OutT *dst = n < n_split ? c0 + n : c1 + (n - n_split);
-            // (U is read eight chunks ahead, the first ahead of the results' way through LDS.  Chunk by chunk a wavefront waited 1.3 us for each: input
-            // gradient with GeLU' of 2048 x 512 -> 2048 11.4 -> 11.1 us, its operands in the caches)
-            constexpr int AHEAD = Store::ITS < 8 ? Store::ITS : 8;
-            bf16x8 uu[AHEAD];
-            auto fetch_u = [&](int i0) __attribute__((always_inline)) {
-                if constexpr (EPI == EPI_GELU_BWD)
+                                 for (int k = 0; k < Store::ITS; ++k) uu[k] = fetch_u(row(k), n);
+                         },
+                         [&](int m, int k, f32x4 raw) __attribute__((always_inline)) {
+                             if (column && m < rows_here) put_chunk(dst + (int64_t)m * ldc, (int64_t)m * ldc + n, raw, uu[k % 8]);
+                         });
+        } else {
+            using Store = GemmStore<S, OUT_F32, A_ANY>;
 #pragma unroll
-                    for (int k = 0; k < AHEAD; ++k) {
-                        const int m = min((i0 + k) * Store::ROWS_PER_IT + t / Store::CPR, rows_here - 1);
-                        uu[k] = *reinterpret_cast<const bf16x8 *>(gelu_u + (int64_t)m * ldc + min(n, n0 + cols_here - Store::CW));
-                    }
-            };
-            fetch_u(0);
-            __syncthreads();        // every wavefront is done with what the LDS held
-            if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, t & 63, rows_data);
-            __syncthreads();
+            for (int pass = 0; pass < Store::PASSES; ++pass) {
+                const int c = t % Store::CPR, col = pass * Store::CPP + c * Store::CW;
+                const int n = n0 + col;         // column of C; a chunk never straddles n_split
+                OutT *dst = n < n_split ? c0 + n : c1 + (n - n_split);
+                constexpr int AHEAD = Store::ITS < 8 ? Store::ITS : 8;
+                bf16x8 uu[AHEAD];
+                auto begin = [&](int i0) __attribute__((always_inline)) {
+                    if constexpr (EPI == EPI_GELU_BWD)
 #pragma unroll
-            for (int i = 0; i < Store::ITS; ++i) {
-                const int m = i * Store::ROWS_PER_IT + t / Store::CPR;
-                if (i > 0 && i % AHEAD == 0) fetch_u(i);
-                f32x4 raw = {0.f, 0.f, 0.f, 0.f};
-                if (m < S::TM) raw = *reinterpret_cast<const f32x4 *>(smem + Store::offset(m, c));
-                if (col < cols_here && m < rows_here) {
-                    if constexpr (EPI == EPI_GELU_BWD) {
-                        bf16x8 cv = __builtin_bit_cast(bf16x8, raw);
+                        for (int k = 0; k < AHEAD; ++k) uu[k] = fetch_u((i0 + k) * Store::ROWS_PER_IT + t / Store::CPR, n);
+                };
+                begin(0);
+                __syncthreads();        // every wavefront is done with what the LDS held
+                if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, t & 63, rows_data);
+                __syncthreads();
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) cv[e] = (bf16_t)((float)cv[e] * gelu_slope((float)uu[i % AHEAD][e]));
-                        raw = __builtin_bit_cast(f32x4, cv);
-                    }
-                    put16(dst + (int64_t)m * ldc, raw);
-                    if constexpr (EPI == EPI_GELU) {
-                        bf16x8 cv = __builtin_bit_cast(bf16x8, raw);
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) cv[e] = (bf16_t)gelu_value((float)cv[e]);
-                        put16(c1 + n + (int64_t)m * ldc, __builtin_bit_cast(f32x4, cv));
-                    }
+                for (int i = 0; i < Store::ITS; ++i) {
+                    const int m = i * Store::ROWS_PER_IT + t / Store::CPR;
+                    if (i > 0 && i % AHEAD == 0) begin(i);
+                    f32x4 raw = {0.f, 0.f, 0.f, 0.f};
+                    if (m < S::TM) raw = *reinterpret_cast<const f32x4 *>(smem + Store::offset(m, c));
+                    if (col < cols_here && m < rows_here) put_chunk(dst + (int64_t)m * ldc, (int64_t)m * ldc + n, raw, uu[i % AHEAD]);
                 }
             }
         }
@@ -580,10 +651,10 @@ __device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
             else return load_frag<bf16_t>(reinterpret_cast<const bf16_t *>(wt + w_off[ks] + nb * 16 * PK * 2));
         };
         auto issue_a = [&](int t, int slot, int i) __attribute__((always_inline)) {
-            lds_dma<16>(a_src(t), offA[i], smem + slot * S::ABYTES + (i * S::GW + wave) * 1024);
+            lds_dma<16>(uniform_ptr(a_src(t)), offA[i], smem + slot * S::ABYTES + (i * S::GW + wave) * 1024);
         };
         auto issue_w = [&](int t, int slot, int i) __attribute__((always_inline)) {
-            lds_dma<16>(w_src(t), offW[i], smem + S::W_RING + slot * S::WBYTES + (i * S::GW + wave) * 1024);
+            lds_dma<16>(uniform_ptr(w_src(t)), offW[i], smem + S::W_RING + slot * S::WBYTES + (i * S::GW + wave) * 1024);
         };
         auto stash = [&](int, int slot, int i) __attribute__((always_inline)) { stash_a(smem + slot * S::ABYTES, i); };
         auto publish = [](int, int, int) {};
@@ -658,7 +729,6 @@ template <typename S, bool DC_F32>
 __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(WgradArgs g)
 {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
-    using Store = GemmStore<S, true>;
     using ATile = TrTile<S::TM, S::GW>;
     using WTile = TrTile<S::TN, S::GW>;
     constexpr int LOADS = ATile::NI + (DC_F32 ? 0 : WTile::NI);
@@ -755,10 +825,10 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
             return WTile::load_frag(smem + S::W_RING + slot * S::WBYTES, ks, wt_off[nb]);
         };
         auto issue_a = [&](int t, int slot, int i) __attribute__((always_inline)) {
-            lds_dma<16>(a_src(t), t == T - 1 ? offA_last[i] : offA[i], smem + slot * S::ABYTES + (i * S::GW + wave) * 1024);
+            lds_dma<16>(uniform_ptr(a_src(t)), t == T - 1 ? offA_last[i] : offA[i], smem + slot * S::ABYTES + (i * S::GW + wave) * 1024);
         };
         auto issue_w = [&](int t, int slot, int i) __attribute__((always_inline)) {
-            if constexpr (!DC_F32) lds_dma<16>(w_src(t), t == T - 1 ? offW_last[i] : offW[i], smem + S::W_RING + slot * S::WBYTES + (i * S::GW + wave) * 1024);
+            if constexpr (!DC_F32) lds_dma<16>(uniform_ptr(w_src(t)), t == T - 1 ? offW_last[i] : offW[i], smem + S::W_RING + slot * S::WBYTES + (i * S::GW + wave) * 1024);
         };
         auto publish = [&](int t, int a_slot, int w_slot) __attribute__((always_inline)) {
             if (t == T - 1) clear_tail(smem + a_slot * S::ABYTES, smem + S::W_RING + w_slot * S::WBYTES);
@@ -802,18 +872,29 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
     }
 
     float *out = g.out + (int64_t)split * g.K * g.N + (int64_t)m0 * g.N + n0;
+    if constexpr (S::WIDE) {
+        using Store = WideStore<true, false>;
+        int t = tid;
+        if constexpr (DC_F32) asm("" : "+v"(t));       // (what is worked out from it is not kept through the loop, which spills)
+        const int col = t % Store::CPR * Store::CW;
+        Store::store(smem, acc, wm, wn, t, S::TM, [](auto &&) {}, [&](int m, int, f32x4 raw) __attribute__((always_inline)) {
+            if (col < cols_n && m < cols_m) *reinterpret_cast<f32x4 *>(out + (int64_t)m * g.N + col) = raw;
+        });
+    } else {
+        using Store = GemmStore<S, true, false>;
 #pragma unroll
-    for (int pass = 0; pass < Store::PASSES; ++pass) {
-        __syncthreads();
-        if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, lane, S::TM);
-        __syncthreads();
-        const int c = tid % Store::CPR, col = pass * Store::CPP + c * Store::CW;
-        if (col < cols_n) {
+        for (int pass = 0; pass < Store::PASSES; ++pass) {
+            __syncthreads();
+            if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, lane, S::TM);
+            __syncthreads();
+            const int c = tid % Store::CPR, col = pass * Store::CPP + c * Store::CW;
+            if (col < cols_n) {
 #pragma unroll
-            for (int i = 0; i < Store::ITS; ++i) {
-                const int m = i * Store::ROWS_PER_IT + tid / Store::CPR;
-                if (m < cols_m)
-                    *reinterpret_cast<f32x4 *>(out + (int64_t)m * g.N + col) = *reinterpret_cast<const f32x4 *>(smem + Store::offset(m, c));
+                for (int i = 0; i < Store::ITS; ++i) {
+                    const int m = i * Store::ROWS_PER_IT + tid / Store::CPR;
+                    if (m < cols_m)
+                        *reinterpret_cast<f32x4 *>(out + (int64_t)m * g.N + col) = *reinterpret_cast<const f32x4 *>(smem + Store::offset(m, c));
+                }
             }
         }
     }
