@@ -185,3 +185,23 @@ def test_projections_of_the_shortest_contractions_of_the_loop():
     dx_q, dx = lss.lss_project_bwd(dq, dk, dv, w_q, w_kv, rv)
     assert _close(dx_q[0], dq[0].reshape(l_s, E).double() @ w_q.double().T, "f32")
     assert _close(dx[0, :rv], rounded[0] @ w_kv.double().T, "f32") and not dx[:, rv:].any()
+
+
+LONG = {"64x64 by four": (1, 1709, 6, 1700), "32x32": (1, 1130, 2, 1127)}      # B, l_x, H, rows_valid: float chunks of more than 1536 and 1024 rows
+
+
+def test_long_float_chunks_take_their_tiles():
+    """(needs no GPU)"""
+    for tile, (B, l_x, H, rv) in LONG.items():
+        assert project_plan(2, B, l_x, H, 64, 90, rv)[2:4] == (tile, 1), tile
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile", LONG)
+def test_weight_gradient_of_long_float_chunks(tile):
+    B, l_x, H, rv = LONG[tile]
+    x, dq = _rand(rv, (B, l_x, 64 * H), (B, 90, H, 64))
+    dk, dv, rounded = _partials(rv, B, l_x, H, rv)
+    dw_kv = lss.lss_project_bwd_weight(x, dq, dk, dv, rv - 90, rv)[1]
+    assert _close(dw_kv, sum(x[b, :rv].double().T @ rounded[b] for b in range(B)), "f32")
+    assert torch.equal(dw_kv, lss.lss_project_bwd_weight(x, dq, dk, dv, rv - 90, rv)[1])
