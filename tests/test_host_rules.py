@@ -58,3 +58,44 @@ def test_no_launcher_keeps_a_limit_per_process():
     csrc = ROOT / "paper_2311_02382_amd" / "csrc"
     sets = [p.name for p in csrc.iterdir() if "hipFuncSetAttribute" in p.read_text()]
     assert sets == ["lss_kernels.h"]
+
+
+def test_assembly_matrix_instructions_have_their_wait_states(tmp_path):
+    # The products' wide tiles issue their matrix instructions as assembly, whose operands the compiler's hazard recognizer does not look at: no vector
+    # instruction may write an operand (copies of accumulators around a loop, of fragments ahead of their use) within two wait states, and the
+    # accumulators are read behind the wait at the end only.
+    from paper_2311_02382_amd import build
+    out = tmp_path / "proj.s"
+    subprocess.run([build._hipcc(), *build.HIPCC_FLAGS, f"-I{build.INCLUDE}", f"-I{build.CSRC}", "-S", "--offload-device-only", str(build.CSRC / "lss_proj.hip"),
+                    "-o", str(out)], check=True, capture_output=True, timeout=300)
+
+    def registers(operand):
+        m = re.fullmatch(r"([av])(?:(\d+)|\[(\d+):(\d+)\])", operand.strip())
+        if not m:
+            return set()
+        first, last = (int(m[2]), int(m[2])) if m[2] else (int(m[3]), int(m[4]))
+        return {(m[1], i) for i in range(first, last + 1)}
+
+    bodies = re.findall(r"^(_Z\w*gemm_kernel\w*GemmWide\w+):(.*?)\.Lfunc_end", out.read_text(), re.S | re.M)
+    assert bodies
+    for name, body in bodies:
+        code = [re.sub(r";.*", "", line).strip() for line in body.splitlines() if re.match(r"\t[a-z]", line)]
+        products = 0
+        for i, line in enumerate(code):
+            if not line.startswith("v_mfma"):
+                continue
+            products += 1
+            used = set().union(*(registers(x) for x in line.split(None, 1)[1].split(",")))
+            states = 0
+            for before in reversed(code[max(i - 2, 0):i]):
+                if states >= 2:
+                    break
+                op = before.split()[0]
+                if op.startswith("v_") and not op.startswith("v_mfma"):
+                    assert not registers(before.split(None, 1)[1].split(",")[0]) & used, (name, before, line)
+                states += int(before.split()[1]) + 1 if op == "s_nop" else 1
+        # (read as soon as none is a matrix instruction's any more)
+        for i, line in enumerate(code):
+            if line.startswith("v_accvgpr_read") and any(x.startswith("v_mfma") for x in code[max(i - 8, 0):i]):
+                assert "s_nop 15" in code[max(i - 8, 0):i], (name, line)
+        assert products >= 96 and code.count("s_nop 15") >= 2, name
