@@ -915,12 +915,13 @@ using ShapeS4 = GemmShape<64, 64, 32, 32, 4, 2>;        // two groups of four wa
 // 256 x 2048 -> 2048 9.7, 8.0, 13.2; dW of 512 x 512 from 1024 rows 7.6 and 5.6 in either (all three with the groups and slots there were before).
 using ShapeT4 = GemmShape<32, 64, 32, 32, 3, 4>;        // two wavefronts, four such groups
 using ShapeT8 = GemmShape<32, 32, 32, 32, 4, 4>;        // one wavefront, four such groups
-// Weight gradients of float partials, which travel through registers a tile per group at a time: long chunks are better off with more groups.  dW_kv of 512
+// Float operands travel through registers a tile per group at a time: their long contractions are better off with more groups.  dW_kv of 512
 // columns from 3000 rows in 64 x 64 tiles 25.0 us in two groups and 23.6 in four, from 1000 12.5 and 13.5; of 256 columns from 2000 in 32 x 32
-// ones 13.1 in four and 11.9 in eight, from 300 7.8 and 8.5.
+// ones 13.1 in four and 11.9 in eight, from 300 7.8 and 8.5.  project_bwd of 300 rows and 2048 contraction indices 14.7 and 14.1 in 64 x 64 ones, 1280 9.2 and
+// 9.3 (four groups for all); of 120 rows and 2048 in 32 x 32 ones 8.2 and 7.5, of 556 and 1024 8.7 and 9.1.
 using ShapeS4F = GemmShape<64, 64, 32, 32, 2, 4>;
 using ShapeT8F = GemmShape<32, 32, 32, 32, 2, 8>;
-constexpr int kLongFloatRowsS4 = 1536, kLongFloatRowsT8 = 1024;
+constexpr int kLongFloatS4 = 1536, kLongFloatT8 = 1024;
 
 template <typename S, bool A_ANY, bool W_TR, bool OUT_F32, int EPI>
 hipError_t launch_proj_shape(ProjArgs &args, int kernel_id, hipStream_t st)
@@ -1006,9 +1007,14 @@ hipError_t launch_proj(ProjArgs &args, int kernel_id, hipStream_t st)
         if constexpr (!A_ANY) return launch_proj_shape<ShapeM8, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
         break;
     case TILE_S: return launch_proj_shape<ShapeS, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
-    case TILE_S4: return launch_proj_shape<ShapeS4, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    case TILE_S4:
+        if constexpr (A_ANY) return launch_proj_shape<ShapeS4F, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+        else return launch_proj_shape<ShapeS4, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
     case TILE_T4: return launch_proj_shape<ShapeT4, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
-    case TILE_T8: return launch_proj_shape<ShapeT8, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    case TILE_T8:
+        if constexpr (A_ANY)
+            if (args.job[0].K > kLongFloatT8) return launch_proj_shape<ShapeT8F, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+        return launch_proj_shape<ShapeT8, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
     default: break;
     }
     return hipErrorInvalidConfiguration;        // (pick_gemm_tile: none of the others)
@@ -1185,7 +1191,7 @@ static hipError_t launch_wgrad(WgradArgs &g, float *dw, float *scratch, hipStrea
     case TILE_S: e = launch_wgrad_shape<ShapeS, DC_F32>(g, st); break;
     case TILE_S4:
         if constexpr (DC_F32)
-            if (g.chunk_rows > kLongFloatRowsS4) { e = launch_wgrad_shape<ShapeS4F, DC_F32>(g, st); break; }
+            if (g.chunk_rows > kLongFloatS4) { e = launch_wgrad_shape<ShapeS4F, DC_F32>(g, st); break; }
         e = launch_wgrad_shape<ShapeS4, DC_F32>(g, st);
         break;
     case TILE_T4:
@@ -1194,7 +1200,7 @@ static hipError_t launch_wgrad(WgradArgs &g, float *dw, float *scratch, hipStrea
         break;
     case TILE_T8:
         if constexpr (DC_F32)
-            if (g.chunk_rows > kLongFloatRowsT8) { e = launch_wgrad_shape<ShapeT8F, DC_F32>(g, st); break; }
+            if (g.chunk_rows > kLongFloatT8) { e = launch_wgrad_shape<ShapeT8F, DC_F32>(g, st); break; }
         e = launch_wgrad_shape<ShapeT8, DC_F32>(g, st);
         break;
     default: e = hipErrorInvalidConfiguration; break;       // (pick_wgrad_plan: no other)

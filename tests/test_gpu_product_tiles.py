@@ -190,8 +190,13 @@ def test_projections_of_the_shortest_contractions_of_the_loop():
 LONG = {"64x64 by four": (1, 1709, 6, 1700), "32x32": (1, 1130, 2, 1127)}      # B, l_x, H, rows_valid: float chunks of more than 1536 and 1024 rows
 
 
-def test_long_float_chunks_take_their_tiles():
+LONG_MAPS = {"64x64 by four": (1, 1110, 16, 284, 344), "32x32": (1, 300, 16, 60, 120)}       # B, l_x, H, l_s, rows_valid: float contractions of 2048
+
+
+def test_long_float_contractions_take_their_tiles():
     """(needs no GPU)"""
+    for tile, (B, l_x, H, l_s, rv) in LONG_MAPS.items():
+        assert project_plan(1, B, l_x, H, 64, l_s, rv) == tile, tile
     for tile, (B, l_x, H, rv) in LONG.items():
         assert project_plan(2, B, l_x, H, 64, 90, rv)[2:4] == (tile, 1), tile
 
@@ -205,3 +210,15 @@ def test_weight_gradient_of_long_float_chunks(tile):
     dw_kv = lss.lss_project_bwd_weight(x, dq, dk, dv, rv - 90, rv)[1]
     assert _close(dw_kv, sum(x[b, :rv].double().T @ rounded[b] for b in range(B)), "f32")
     assert torch.equal(dw_kv, lss.lss_project_bwd_weight(x, dq, dk, dv, rv - 90, rv)[1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile", LONG_MAPS)
+def test_input_gradient_of_long_float_contractions(tile):
+    B, l_x, H, l_s, rv = LONG_MAPS[tile]
+    E = 64 * H
+    w_q, w_kv, dq = _rand(l_x + 5, (E, E), (E, 2 * E), (B, l_s, H, 64))
+    dk, dv, rounded = _partials(l_x + 6, B, l_x, H, rv)
+    dx_q, dx = lss.lss_project_bwd(dq, dk, dv, w_q, w_kv, rv)
+    assert _close(dx_q[0], dq[0].reshape(l_s, E).double() @ w_q.double().T, "f32")
+    assert _close(dx[0, :rv], rounded[0] @ w_kv.double().T, "f32") and not dx[:, rv:].any()
