@@ -25,7 +25,9 @@ __device__ __forceinline__ void lds_dma(const void *g_uniform, uint32_t voff, co
     else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds_addr), "v"(voff), "s"(g_uniform) : "memory", "m0");
 }
 
-// A pointer that is wavefront-uniform by contract; said again so that it is kept in scalar registers
+// A pointer that is wavefront-uniform by contract; said again so that it is kept in scalar registers.  Not a way to bring one there from vector registers
+// right before lds_dma(): a vector-memory instruction may read a scalar register that a vector instruction wrote five wait states later at the earliest,
+// and the compiler, which keeps to that elsewhere, does not look into assembly.  (tests/test_generated_code.py looks at every kernel of the build.)
 __device__ __forceinline__ const void *uniform_ptr(const void *ptr)
 {
     const uint64_t p = (uint64_t)ptr;

@@ -745,12 +745,15 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
     const int tiles = g.m_tiles * g.n_tiles, per_xcd = (splits * tiles + kXcds - 1) / kXcds;
     const int item = blockIdx.x % kXcds * per_xcd + blockIdx.x / kXcds;
     if ((int)blockIdx.x / kXcds >= per_xcd || item >= splits * tiles) return;
-    const int split = item / tiles, tile = item % tiles;
-    const int batch = split / g.splits_per_batch;
-    const int block = tile / (4 * g.n_tiles), in = tile % (4 * g.n_tiles), down = min(g.m_tiles - 4 * block, 4);
-    const int col = down == 4 ? in >> 2 : in / down;       // (a division is some 40 instructions, 1 % of a launch of 64 x 64 tiles)
+    // (The compiler leaves some of these divisions in vector registers.  Read out here, what follows from them, the bases of the loads among it, is scalar
+    // arithmetic: see uniform_ptr.)
+    auto scalar = [](int v) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(v); };
+    const int split = scalar(item / tiles), tile = item - split * tiles;
+    const int batch = scalar(split / g.splits_per_batch);
+    const int block = scalar(tile / (4 * g.n_tiles)), in = tile - block * 4 * g.n_tiles, down = min(g.m_tiles - 4 * block, 4);
+    const int col = scalar(down == 4 ? in >> 2 : in / down);       // (a division is some 40 instructions, 1 % of a launch of 64 x 64 tiles)
     const int m0 = (4 * block + in - col * down) * S::TM, n0 = col * S::TN;
-    const int r0 = (split % g.splits_per_batch) * g.chunk_rows, r1 = min(r0 + g.chunk_rows, g.rows);
+    const int r0 = (split - batch * g.splits_per_batch) * g.chunk_rows, r1 = min(r0 + g.chunk_rows, g.rows);
     const int T = (r1 - r0 + PK - 1) / PK;          // >= 1: the host sizes the splits so
     const int tail = (r1 - r0) - (T - 1) * PK;      // rows of the last tile, 1 .. 64
     const int cols_m = min(g.K - m0, S::TM), cols_n = min(g.N - n0, S::TN);
