@@ -409,8 +409,7 @@ struct GemmStore {
 // A finished GemmWide tile goes out in four quarters of 64 rows, 32 from either pair of wavefronts, through two regions of LDS by turns: a quarter's stores
 // are on their way while the next one is converted, and one barrier per quarter will do.  (In one piece, or floats in halves by columns, which left two of the
 // four wavefronts idle at a time, a tile took 2.1 us to get into LDS and 3.1 out of it, one after the other.)
-//   begin(rows)        ahead of a quarter; rows(k) is the row of its k-th chunk
-//   put(m, k, raw)     16 bytes of row m, the thread's k-th chunk of the quarter; their column is CW (t % CPR)
+//   put(m, raw)        16 bytes of row m; their column is CW (t % CPR)
 template <bool OUT_F32, bool ZEROS>
 struct WideStore {
     using S = GemmWide;
@@ -418,8 +417,8 @@ struct WideStore {
     static constexpr int REGION = 64 * S::TN * EB, ITS = 64 * CPR / S::NT, RPI = S::NT / CPR;
     static_assert(2 * REGION <= S::LDS, "");
     static __device__ __forceinline__ int offset(int r, int c) { return r * (S::TN * EB) + ((c ^ (r & (CPR - 1))) * 16); }
-    template <typename Begin, typename Put>
-    static __device__ __forceinline__ void store(char *smem, const f32x4 (&acc)[S::MB][S::NB], int wm, int wn, int t, int rows_data, Begin &&begin, Put &&put)
+    template <typename Put>
+    static __device__ __forceinline__ void store(char *smem, const f32x4 (&acc)[S::MB][S::NB], int wm, int wn, int t, int rows_data, Put &&put)
     {
         const int lane = t & 63, g = lane >> 4;
         __syncthreads();        // every wavefront is done with what the LDS held
@@ -427,7 +426,6 @@ struct WideStore {
         for (int q = 0; q < 4; ++q) {
             char *const region = smem + (q & 1) * REGION;
             auto row = [&](int k) { const int r = k * RPI + t / CPR; return S::WM * (r >> 5) + 32 * q + (r & 31); };
-            begin(row);
 #pragma unroll
             for (int mb = 2 * q; mb < 2 * q + 2; ++mb) {
                 const int r = 32 * wm + 16 * (mb & 1) + (lane & 15);
@@ -451,7 +449,7 @@ struct WideStore {
 #pragma unroll
                     for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(raw[i]));        // (not read one by one, each ahead of its store)
                 }
-                put(row(k), k, raw[k % 8]);
+                put(row(k), raw[k % 8]);
             }
         }
     }
@@ -545,16 +543,10 @@ __device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
             const int n = n0 + t % Store::CPR * Store::CW;          // column of C; a chunk never straddles n_split
             OutT *const dst = n < n_split ? c0 + n : c1 + (n - n_split);
             const bool column = n < n0 + cols_here;
-            bf16x8 uu[8];
-            Store::store(smem, acc, wm, wn, t, rows_data,
-                         [&](auto &&row) __attribute__((always_inline)) {
-                             if constexpr (EPI == EPI_GELU_BWD)
-#pragma unroll
-                                 for (int k = 0; k < Store::ITS; ++k) uu[k] = fetch_u(row(k), n);
-                         },
-                         [&](int m, int k, f32x4 raw) __attribute__((always_inline)) {
-                             if (column && m < rows_here) put_chunk(dst + (int64_t)m * ldc, (int64_t)m * ldc + n, raw, uu[k % 8]);
-                         });
+            static_assert(EPI == EPI_NONE, "");
+            Store::store(smem, acc, wm, wn, t, rows_data, [&](int m, f32x4 raw) __attribute__((always_inline)) {
+                if (column && m < rows_here) put16(dst + (int64_t)m * ldc, raw);
+            });
         } else {
             using Store = GemmStore<S, OUT_F32, A_ANY>;
 #pragma unroll
@@ -880,7 +872,7 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
         int t = tid;
         if constexpr (DC_F32) asm("" : "+v"(t));       // (what is worked out from it is not kept through the loop, which spills)
         const int col = t % Store::CPR * Store::CW;
-        Store::store(smem, acc, wm, wn, t, S::TM, [](auto &&) {}, [&](int m, int, f32x4 raw) __attribute__((always_inline)) {
+        Store::store(smem, acc, wm, wn, t, S::TM, [&](int m, f32x4 raw) __attribute__((always_inline)) {
             if (col < cols_n && m < cols_m) *reinterpret_cast<f32x4 *>(out + (int64_t)m * g.N + col) = raw;
         });
     } else {
@@ -905,6 +897,10 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
 
 // ---- the tiles a launch may take
 using ShapeL = GemmWide;                                // four wavefronts, one workgroup per compute unit
+// ... eight of 128 x 64 where a feed-forward unit's epilogue follows: GeLU is some twenty vector instructions per element, of which a wavefront alone on its
+// SIMD issues one in 7.5 cycles and two together twice as many.  linear_gelu_fwd of 6000 x 640 -> 2560 by four and by eight 38.0 and 34.9 us in a layer's pass,
+// 3244 x 1152 -> 4608 51.1 and 48.4, 16384 x 1024 -> 4096 188 and 177; linear_bwd_input_gelu of the first two 38.9 and 35.6, 51.2 and 49.2.
+using ShapeL8 = GemmShape<256, 256, 128, 64, 2>;
 using ShapeM = GemmShape<128, 128, 64, 64, 2>;          // four wavefronts, two workgroups per compute unit
 using ShapeM2 = GemmShape<128, 128, 64, 64, 2, 2>;      // ... two such groups share the contraction
 using ShapeM8 = GemmShape<128, 128, 64, 32, 4>;         // ... eight wavefronts of one group, four tiles on their way
@@ -1001,7 +997,7 @@ hipError_t launch_proj(ProjArgs &args, int kernel_id, hipStream_t st)
 {
     args.stream = proj_streams(args, OUT_F32);
     switch (proj_tile(args, A_ANY, args.stream)) {
-    case TILE_L: return launch_proj_shape<ShapeL, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    case TILE_L: return launch_proj_shape<typename std::conditional<EPI == EPI_NONE, ShapeL, ShapeL8>::type, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
     case TILE_M: return launch_proj_shape<ShapeM, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
     case TILE_M2:
         if constexpr (A_ANY) return launch_proj_shape<ShapeM2, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);

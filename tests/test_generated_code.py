@@ -25,3 +25,9 @@ def test_loads_from_a_scalar_base_wait_for_the_vector_instruction_that_wrote_it(
                 for before, waited in flow.within(i, 5) if base else ():
                     assert not (before.startswith("v_") and _asm.written(before) & base), (source, name, before, waited, line)
     assert seen > 1000
+
+
+def test_feed_forward_epilogues_have_two_wavefronts_per_simd(code):
+    # GeLU is vector work behind the contraction: a wavefront alone on its SIMD, as in the wide tiles, issues it at half the rate
+    names = [name for name in _asm.kernels(code["lss_proj.hip"]) if "proj_" in name and not name.endswith("ELi0EEEvNS0_8ProjArgsE")]
+    assert len(names) == 14 and not [name for name in names if "GemmWide" in name]
