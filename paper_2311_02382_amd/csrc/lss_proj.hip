@@ -273,6 +273,14 @@ __device__ __forceinline__ void gemm_wide_loop(f32x4 (&acc)[GemmWide::MB][GemmWi
     fetch_all(0);
     issue_all(0);
     if (T > 1) issue_all(1);
+    // Cleared while the loads are on their way, by the shortest matrix instruction that writes four registers (of zeros).  Left to the compiler that is 256
+    // vector instructions behind the barrier, 0.8 us of a lone wavefront's time, and in the weight gradients as many copies of a cleared register again.
+    float zero;
+    asm volatile("v_mov_b32 %0, 0\n\ts_nop 1" : "=v"(zero));
+#pragma unroll
+    for (int mb = 0; mb < S::MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < S::NB; ++nb) asm volatile("v_mfma_f32_4x4x1_16b_f32 %0, %1, %1, 0" : "=a"(acc[mb][nb]) : "v"(zero));
     if constexpr (REG != REG_NONE)
 #pragma unroll
         for (int c = 0; c < CHUNKS; ++c) stash(0, 0, c);
@@ -578,7 +586,7 @@ __device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
     };
 
     f32x4 acc[S::MB][S::NB];
-    gemm_clear<S>(acc);
+    if constexpr (!S::WIDE) gemm_clear<S>(acc);
 
     const int T = J.K / PK;
     const int t_split = J.k_split / PK;
@@ -813,7 +821,7 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
 #pragma unroll
     for (int nb = 0; nb < S::NB; ++nb) wt_off[nb] = WTile::lane_offset(lane, S::NB * wn + nb);
     f32x4 acc[S::MB][S::NB];
-    gemm_clear<S>(acc);
+    if constexpr (!S::WIDE) gemm_clear<S>(acc);
     if constexpr (S::WIDE) {
         auto load_a = [&](int slot, int ks, int mb) __attribute__((always_inline)) { return ATile::load_frag(smem + slot * S::ABYTES, ks, at_off ^ (mb * 32)); };
         auto load_w = [&](int slot, int ks, int nb) __attribute__((always_inline)) {

@@ -31,3 +31,27 @@ def test_feed_forward_epilogues_have_two_wavefronts_per_simd(code):
     # GeLU is vector work behind the contraction: a wavefront alone on its SIMD, as in the wide tiles, issues it at half the rate
     names = [name for name in _asm.kernels(code["lss_proj.hip"]) if "proj_" in name and not name.endswith("ELi0EEEvNS0_8ProjArgsE")]
     assert len(names) == 14 and not [name for name in names if "GemmWide" in name]
+
+
+def test_wide_tiles_accumulators_belong_to_matrix_instructions(code):
+    # They are cleared, summed up and read, never copied (a lone wavefront takes 0.8 us to go over them); and since their matrix instructions are assembly, along every
+    # path: no vector instruction writes an operand within two wait states ahead, no other kind of matrix instruction an accumulator and nothing else
+    # touches one within twenty behind it (the longest that any matrix instruction of the architecture asks for).
+    wide = 0
+    for name, lines in _asm.kernels(code["lss_proj.hip"]).items():
+        if "GemmWide" not in name:
+            continue
+        wide += 1
+        flow = _asm.Flow(lines)
+        products = [i for i, line in enumerate(flow.code) if line.startswith("v_mfma")]
+        assert not [x for x in flow.code[products[0]:products[-1]] if x.startswith(("v_accvgpr_write", "v_accvgpr_mov"))], name
+        for i, line in enumerate(flow.code):
+            op, used = line.split()[0], set().union(*_asm.operands(line))
+            if op.startswith("v_mfma"):
+                for before, waited in flow.within(i, 2):
+                    assert not (before.startswith("v_") and not before.startswith("v_mfma") and _asm.written(before) & used), (name, before, waited, line)
+            acc = {r for r in used if r[0] == "a"}
+            for before, waited in flow.within(i, 20) if acc else ():
+                if before.startswith("v_mfma") and before.split()[0] != op:
+                    assert not _asm.written(before) & acc, (name, before, waited, line)
+    assert wide == 5
