@@ -828,7 +828,7 @@ int lss_plan_linear(int op, int64_t rows, int64_t K, int64_t N, int *plan)
     if (op < 0 || op > 2 || rows < 1 || rows > INT32_MAX || K < 128 || N < 128 || K % 128 != 0 || N % 128 != 0 || K > 65536 || N > 65536)
         return fail(LSS_ERR_SHAPE, "plan: no launch of such a call");
     if (!plan) return fail(LSS_ERR_NULL, "plan: NULL");
-    plan[0] = lss::plan_linear(op, (int)rows, (int)K, (int)N, plan + 1);
+    lss::plan_linear(op, (int)rows, (int)K, (int)N, plan);
     return LSS_OK;
 }
 
@@ -840,7 +840,7 @@ int lss_plan_project(int op, int64_t l_s, int64_t l_x, int64_t rows_valid, int64
         return fail(LSS_ERR_SHAPE, "plan: no launch of such a call");
     if (!plan) return fail(LSS_ERR_NULL, "plan: NULL");
     if (op == 2) lss::plan_project_bwd_weight((int)l_s, (int)rows_valid, (int)B, (int)E, plan);
-    else plan[0] = lss::plan_project(op, (int)l_s, (int)l_x, (int)rows_valid, (int)B, (int)E);
+    else lss::plan_project(op, (int)l_s, (int)l_x, (int)rows_valid, (int)B, (int)E, plan);
     return LSS_OK;
 }
 

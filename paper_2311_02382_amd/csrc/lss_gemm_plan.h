@@ -26,6 +26,20 @@ constexpr GemmTileCost kGemmTiles[TILE_COUNT] = {
     {256, 256, 1, 1, 6.5, {1.40, 1.70}}, {128, 128, 1, 2, 2.8, {0.62, 1.00}}, {128, 128, 2, 1, 3.0, {0.50, 0.58}}, {128, 128, 1, 1, 2.5, {0.51, 0.585}},
     {64, 64, 1, 2, 2.5, {0.30, 0.40}}, {64, 64, 2, 1, 3.3, {0.165, 0.22}}, {32, 64, 4, 1, 3.0, {0.117, 0.165}}, {32, 32, 4, 1, 3.2, {0.069, 0.107}}};
 
+// What a kernel's contraction goes through: groups of wavefronts, and slots of the LDS ring of each (of the activations, where a 256 x 256 tile has fewer for
+// the weights).  `length`: of a map's contraction, or the rows of a chunk of a weight gradient.
+struct GemmForm { int groups, slots; };
+constexpr int kLongFloatS4 = 1536, kLongFloatT8 = 1024;
+// Float operands travel through registers a tile per group at a time: more slots gain them nothing, and their long contractions are better off with more groups.
+constexpr GemmForm gemm_form(GemmTile t, bool weight_gradient, bool floats, int length)
+{
+    if (floats && t == TILE_S4 && (!weight_gradient || length > kLongFloatS4)) return {4, 2};
+    if (floats && t == TILE_T4) return {4, 2};
+    if (floats && t == TILE_T8 && length > kLongFloatT8) return {8, 2};
+    constexpr int slots[TILE_COUNT] = {3, 2, 2, 4, 4, 4, 3, 4};
+    return {kGemmTiles[t].groups, slots[t]};
+}
+
 // `tiles`: contraction tiles of a workgroup on average, `rest_tiles`: of those in the last, part-filled round
 inline double gemm_estimate(const GemmTileCost &c, double wgs, double tiles, double rest_tiles)
 {

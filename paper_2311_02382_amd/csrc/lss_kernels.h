@@ -151,8 +151,8 @@ hipError_t launch_project_bwd_weight(const bf16_t *x, const bf16_t *dq, const fl
                                      int l_s, int l_x, int rows_valid, int B, int E, float *dw_q, float *dw_kv, float *scratch,
                                      hipStream_t st);
 // (lss_plan.h; rows, l_s, rows_valid, B >= 1)
-int plan_linear(int op, int rows, int K, int N, int *chunks);
-int plan_project(int op, int l_s, int l_x, int rows_valid, int B, int E);
+void plan_linear(int op, int rows, int K, int N, int *plan);
+void plan_project(int op, int l_s, int l_x, int rows_valid, int B, int E, int *plan);
 void plan_project_bwd_weight(int l_s, int rows_valid, int B, int E, int *plan);
 
 // segment-local row operations (lss_rows.hip); E a multiple of 8

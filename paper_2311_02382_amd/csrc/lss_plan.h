@@ -9,9 +9,10 @@
  *                 64 rows, plan[5] wavefronts of 16 rows
  *
  *   lss_plan_linear   op 0 lss_linear_fwd, 1 lss_linear_bwd_input, 2 lss_linear_bwd_weight (fused forms take the same tiles).  plan[0] tile (GemmTile
- *                     of lss_gemm_plan.h), plan[1] chunks of rows
- *   lss_plan_project  op 0 lss_project_qkv, 1 lss_project_bwd: plan[0] tile;  op 2 lss_project_bwd_weight: plan[0] tile and plan[1] chunks of rows per
- *                     batch entry of dW_q, plan[2] and plan[3] of dW_kv.  `rows_valid` is not looked at for op 0; at least one row of all kinds
+ *                     of lss_gemm_plan.h), plan[1] chunks of rows, plan[2] groups of wavefronts that share a contraction, plan[3] slots of their rings
+ *   lss_plan_project  op 0 lss_project_qkv, 1 lss_project_bwd: plan[0] tile, plan[1] groups, plan[2] slots;  op 2 lss_project_bwd_weight: plan[0] tile and
+ *                     plan[1] chunks of rows per batch entry of dW_q, plan[2] and plan[3] of dW_kv, plan[4] groups and plan[5] slots of dW_q, plan[6] and
+ *                     plan[7] of dW_kv.  `rows_valid` is not looked at for op 0; at least one row of all kinds
  *
  * Returns LSS_OK or a negative lss_status.
  */

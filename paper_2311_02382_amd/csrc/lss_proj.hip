@@ -922,13 +922,14 @@ using ShapeS4 = GemmShape<64, 64, 32, 32, 4, 2>;        // two groups of four wa
 // 256 x 2048 -> 2048 9.7, 8.0, 13.2; dW of 512 x 512 from 1024 rows 7.6 and 5.6 in either (all three with the groups and slots there were before).
 using ShapeT4 = GemmShape<32, 64, 32, 32, 3, 4>;        // two wavefronts, four such groups
 using ShapeT8 = GemmShape<32, 32, 32, 32, 4, 4>;        // one wavefront, four such groups
-// Float operands travel through registers a tile per group at a time: their long contractions are better off with more groups.  dW_kv of 512
+// ... as gemm_form() says for float operands: dW_kv of 512
 // columns from 3000 rows in 64 x 64 tiles 25.0 us in two groups and 23.6 in four, from 1000 12.5 and 13.5; of 256 columns from 2000 in 32 x 32
 // ones 13.1 in four and 11.9 in eight, from 300 7.8 and 8.5.  project_bwd of 300 rows and 2048 contraction indices 14.7 and 14.1 in 64 x 64 ones, 1280 9.2 and
-// 9.3 (four groups for all); of 120 rows and 2048 in 32 x 32 ones 8.2 and 7.5, of 556 and 1024 8.7 and 9.1.
+// 9.3 (four groups for all); of 120 rows and 2048 in 32 x 32 ones 8.2 and 7.5, of 556 and 1024 8.7 and 9.1.  32 x 64 ones with two slots and with three: 145 rows
+// and 3584 15.7 and 16.1, 96 and 4096 16.2 and 16.9, 337 and 1280 6.0 and 6.0.
 using ShapeS4F = GemmShape<64, 64, 32, 32, 2, 4>;
+using ShapeT4F = GemmShape<32, 64, 32, 32, 2, 4>;
 using ShapeT8F = GemmShape<32, 32, 32, 32, 2, 8>;
-constexpr int kLongFloatS4 = 1536, kLongFloatT8 = 1024;
 
 template <typename S, bool A_ANY, bool W_TR, bool OUT_F32, int EPI>
 hipError_t launch_proj_shape(ProjArgs &args, int kernel_id, hipStream_t st)
@@ -970,14 +971,25 @@ template <> struct TileShape<TILE_S> { using type = ShapeS; };
 template <> struct TileShape<TILE_S4> { using type = ShapeS4; };
 template <> struct TileShape<TILE_T4> { using type = ShapeT4; };
 template <> struct TileShape<TILE_T8> { using type = ShapeT8; };
+template <typename S>
+constexpr bool is_form(const GemmForm &f)
+{
+    if constexpr (S::WIDE) return f.groups == S::KG && f.slots == S::A_SLOTS;
+    else return f.groups == S::KG && f.slots == S::STAGES;
+}
 template <GemmTile T>
 constexpr bool tile_agrees()
 {
     using S = typename TileShape<T>::type;
-    return S::TM == kGemmTiles[T].tm && S::TN == kGemmTiles[T].tn && S::KG == kGemmTiles[T].groups && S::PER_CU == kGemmTiles[T].per_cu;
+    return S::TM == kGemmTiles[T].tm && S::TN == kGemmTiles[T].tn && S::KG == kGemmTiles[T].groups && S::PER_CU == kGemmTiles[T].per_cu &&
+           is_form<S>(gemm_form(T, false, false, kGemmK));
 }
 static_assert(tile_agrees<TILE_L>() && tile_agrees<TILE_M>() && tile_agrees<TILE_M2>() && tile_agrees<TILE_M8>() && tile_agrees<TILE_S>() &&
               tile_agrees<TILE_S4>() && tile_agrees<TILE_T4>() && tile_agrees<TILE_T8>(), "the plan's table is about other shapes");
+
+static_assert(is_form<ShapeS4F>(gemm_form(TILE_S4, false, true, kGemmK)) && is_form<ShapeS4>(gemm_form(TILE_S4, true, true, kLongFloatS4)) &&
+              is_form<ShapeS4F>(gemm_form(TILE_S4, true, true, kLongFloatS4 + 1)) && is_form<ShapeT4F>(gemm_form(TILE_T4, false, true, kGemmK)) &&
+              is_form<ShapeT8>(gemm_form(TILE_T8, false, true, kLongFloatT8)) && is_form<ShapeT8F>(gemm_form(TILE_T8, false, true, kLongFloatT8 + 1)), "");
 
 int proj_work(const ProjArgs &args, GemmWork (&work)[2])
 {
@@ -1000,11 +1012,13 @@ GemmTile proj_tile(const ProjArgs &args, bool a_any, bool streams)
     return pick_gemm_tile(work, n, a_any, args.skip_tail, streams);
 }
 
+GemmForm proj_form(const ProjArgs &args, GemmTile tile, bool a_any) { return gemm_form(tile, false, a_any, args.job[0].K); }
 template <bool A_ANY, bool W_TR, bool OUT_F32, int EPI = EPI_NONE>
 hipError_t launch_proj(ProjArgs &args, int kernel_id, hipStream_t st)
 {
     args.stream = proj_streams(args, OUT_F32);
-    switch (proj_tile(args, A_ANY, args.stream)) {
+    const GemmTile tile = proj_tile(args, A_ANY, args.stream);
+    switch (tile) {
     case TILE_L: return launch_proj_shape<typename std::conditional<EPI == EPI_NONE, ShapeL, ShapeL8>::type, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
     case TILE_M: return launch_proj_shape<ShapeM, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
     case TILE_M2:
@@ -1017,10 +1031,12 @@ hipError_t launch_proj(ProjArgs &args, int kernel_id, hipStream_t st)
     case TILE_S4:
         if constexpr (A_ANY) return launch_proj_shape<ShapeS4F, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
         else return launch_proj_shape<ShapeS4, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
-    case TILE_T4: return launch_proj_shape<ShapeT4, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+    case TILE_T4:
+        if constexpr (A_ANY) return launch_proj_shape<ShapeT4F, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+        else return launch_proj_shape<ShapeT4, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
     case TILE_T8:
         if constexpr (A_ANY)
-            if (args.job[0].K > kLongFloatT8) return launch_proj_shape<ShapeT8F, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
+            if (is_form<ShapeT8F>(proj_form(args, tile, A_ANY))) return launch_proj_shape<ShapeT8F, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
         return launch_proj_shape<ShapeT8, A_ANY, W_TR, OUT_F32, EPI>(args, kernel_id, st);
     default: break;
     }
@@ -1138,28 +1154,37 @@ hipError_t launch_linear_bwd_input(const bf16_t *dc, const bf16_t *w, const bf16
     return launch_proj<false, false, false>(args, K_LINEAR_BWD, st);
 }
 
-int plan_linear(int op, int rows, int K, int N, int *chunks)
+// plan: what lss_plan.h says
+void plan_linear(int op, int rows, int K, int N, int *plan)
 {
-    *chunks = 1;
     if (op == 2) {
         const WgradPlan p = pick_wgrad_plan(rows, 1, K, N, false);
-        *chunks = p.splits_per_batch;
-        return p.tile;
+        const GemmForm f = gemm_form(p.tile, true, false, p.chunk_rows);
+        const int all[4] = {p.tile, p.splits_per_batch, f.groups, f.slots};
+        std::copy(all, all + 4, plan);
+        return;
     }
     const ProjArgs args = op == 0 ? linear_fwd_args(nullptr, nullptr, rows, K, N, nullptr, nullptr) : linear_bwd_input_args(nullptr, nullptr, nullptr, rows, K, N, nullptr);
-    return proj_tile(args, false, proj_streams(args, false));
+    const GemmTile tile = proj_tile(args, false, proj_streams(args, false));
+    const GemmForm f = proj_form(args, tile, false);
+    const int all[4] = {tile, 1, f.groups, f.slots};
+    std::copy(all, all + 4, plan);
 }
-int plan_project(int op, int l_s, int l_x, int rows_valid, int B, int E)
+void plan_project(int op, int l_s, int l_x, int rows_valid, int B, int E, int *plan)
 {
     const ProjArgs args = op == 0 ? qkv_args(nullptr, nullptr, nullptr, 0, l_s, l_x, B, E, nullptr, nullptr, nullptr)
                                   : bwd_args(nullptr, nullptr, nullptr, nullptr, nullptr, l_s, l_x, rows_valid, B, E, 0, nullptr, nullptr);
-    return proj_tile(args, op == 1, proj_streams(args, op == 1));
+    const GemmTile tile = proj_tile(args, op == 1, proj_streams(args, op == 1));
+    const GemmForm f = proj_form(args, tile, op == 1);
+    const int all[3] = {tile, f.groups, f.slots};
+    std::copy(all, all + 3, plan);
 }
 void plan_project_bwd_weight(int l_s, int rows_valid, int B, int E, int *plan)
 {
     const WgradPlan q = pick_wgrad_plan(l_s, B, E, E, false), kv = pick_wgrad_plan(rows_valid, B, E, 2 * E, true);
-    const int all[4] = {q.tile, q.splits_per_batch, kv.tile, kv.splits_per_batch};
-    std::copy(all, all + 4, plan);
+    const GemmForm fq = gemm_form(q.tile, true, false, q.chunk_rows), fkv = gemm_form(kv.tile, true, true, kv.chunk_rows);
+    const int all[8] = {q.tile, q.splits_per_batch, kv.tile, kv.splits_per_batch, fq.groups, fq.slots, fkv.groups, fkv.slots};
+    std::copy(all, all + 8, plan);
 }
 
 static size_t wgrad_scratch_bytes(int rows, int batches, int K, int N)
@@ -1198,7 +1223,7 @@ static hipError_t launch_wgrad(WgradArgs &g, float *dw, float *scratch, hipStrea
     case TILE_S: e = launch_wgrad_shape<ShapeS, DC_F32>(g, st); break;
     case TILE_S4:
         if constexpr (DC_F32)
-            if (g.chunk_rows > kLongFloatS4) { e = launch_wgrad_shape<ShapeS4F, DC_F32>(g, st); break; }
+            if (is_form<ShapeS4F>(gemm_form(p.tile, true, true, g.chunk_rows))) { e = launch_wgrad_shape<ShapeS4F, DC_F32>(g, st); break; }
         e = launch_wgrad_shape<ShapeS4, DC_F32>(g, st);
         break;
     case TILE_T4:
@@ -1207,7 +1232,7 @@ static hipError_t launch_wgrad(WgradArgs &g, float *dw, float *scratch, hipStrea
         break;
     case TILE_T8:
         if constexpr (DC_F32)
-            if (g.chunk_rows > kLongFloatT8) { e = launch_wgrad_shape<ShapeT8F, DC_F32>(g, st); break; }
+            if (is_form<ShapeT8F>(gemm_form(p.tile, true, true, g.chunk_rows))) { e = launch_wgrad_shape<ShapeT8F, DC_F32>(g, st); break; }
         e = launch_wgrad_shape<ShapeT8, DC_F32>(g, st);
         break;
     default: e = hipErrorInvalidConfiguration; break;       // (pick_wgrad_plan: no other)

@@ -92,15 +92,36 @@ def bwd_plan(B, l_x, H, d, s0, l_s, causal, drop=False, elem_bytes=2, over_out=F
 TILES = ("256x256", "128x128", "128x128 by two", "128x128 of eight", "64x64", "64x64 by four", "32x64", "32x32")
 
 
+def _linear_plan(op, rows, K, N):
+    plan, i64 = (ctypes.c_int * 4)(), ctypes.c_int64
+    lss._check(lss.load().lss_plan_linear(ctypes.c_int(op), i64(rows), i64(K), i64(N), plan))
+    return plan
+
+
+def _project_plan(op, B, l_x, H, d, l_s, rows_valid):
+    plan, i64 = (ctypes.c_int * 8)(), ctypes.c_int64
+    lss._check(lss.load().lss_plan_project(ctypes.c_int(op), *map(i64, (l_s, l_x, rows_valid, B, H, d)), plan))
+    return plan
+
+
 def linear_plan(op, rows, K, N):
     """(tile, chunks of rows) of linear_fwd (op 0), linear_bwd_input (1) or linear_bwd_weight (2)."""
-    plan, i64 = (ctypes.c_int * 2)(), ctypes.c_int64
-    lss._check(lss.load().lss_plan_linear(ctypes.c_int(op), i64(rows), i64(K), i64(N), plan))
+    plan = _linear_plan(op, rows, K, N)
     return TILES[plan[0]], plan[1]
+
+
+def linear_form(op, rows, K, N):
+    """(groups of wavefronts that share a contraction, slots of their rings) of the same."""
+    return tuple(_linear_plan(op, rows, K, N)[2:4])
 
 
 def project_plan(op, B, l_x, H, d, l_s, rows_valid):
     """The tile of project_qkv (op 0) or project_bwd (1); tile and chunks of dW_q, tile and chunks of dW_kv (2)."""
-    plan, i64 = (ctypes.c_int * 4)(), ctypes.c_int64
-    lss._check(lss.load().lss_plan_project(ctypes.c_int(op), *map(i64, (l_s, l_x, rows_valid, B, H, d)), plan))
+    plan = _project_plan(op, B, l_x, H, d, l_s, rows_valid)
     return (TILES[plan[0]], plan[1], TILES[plan[2]], plan[3]) if op == 2 else TILES[plan[0]]
+
+
+def project_form(op, B, l_x, H, d, l_s, rows_valid):
+    """(groups of wavefronts that share a contraction, slots of their rings) of project_qkv (op 0), project_bwd (1) or dW_kv (2)."""
+    plan = _project_plan(op, B, l_x, H, d, l_s, rows_valid)
+    return tuple(plan[6:8] if op == 2 else plan[1:3])

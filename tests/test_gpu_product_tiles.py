@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2311_02382_amd import lss
-from _util import TOL, linear_plan, project_plan
+from _util import TOL, linear_form, linear_plan, project_form, project_plan
 
 LINEAR = {  # tile: rows, K, N  (contraction over K)
     "fwd": {"32x32": (45, 1152, 384), "32x64": (58, 512, 4480), "64x64": (70, 512, 5504), "64x64 by four": (67, 768, 6016),
@@ -219,6 +219,34 @@ def test_input_gradient_of_long_float_contractions(tile):
     E = 64 * H
     w_q, w_kv, dq = _rand(l_x + 5, (E, E), (E, 2 * E), (B, l_s, H, 64))
     dk, dv, rounded = _partials(l_x + 6, B, l_x, H, rv)
+    dx_q, dx = lss.lss_project_bwd(dq, dk, dv, w_q, w_kv, rv)
+    assert _close(dx_q[0], dq[0].reshape(l_s, E).double() @ w_q.double().T, "f32")
+    assert _close(dx[0, :rv], rounded[0] @ w_kv.double().T, "f32") and not dx[:, rv:].any()
+
+
+# Maps of float partials in the small tiles, whose groups and slots are not those of bf16 operands: (tile, groups, slots, H): B, l_x, l_s, rows_valid.  32 x 32 ones on
+# either side of a contraction of 1024.
+FLOAT_MAPS = {("32x64", 4, 2, 16): (1, 209, 40, 200), ("32x64", 4, 2, 32): (1, 79, 33, 70), ("32x32", 4, 4, 8): (1, 49, 33, 40), ("32x32", 8, 2, 10): (1, 49, 33, 40),
+              ("64x64 by four", 4, 2, 32): (1, 209, 40, 200)}
+
+
+def test_float_maps_take_their_groups_and_slots():
+    """(needs no GPU)"""
+    for (tile, groups, slots, H), (B, l_x, l_s, rv) in FLOAT_MAPS.items():
+        assert (project_plan(1, B, l_x, H, 64, l_s, rv), project_form(1, B, l_x, H, 64, l_s, rv)) == (tile, (groups, slots)), (tile, H)
+    bf16 = {"32x32": (4, 4), "32x64": (4, 3), "64x64": (1, 4), "64x64 by four": (2, 4), "128x128 of eight": (1, 4), "128x128": (1, 2), "256x256": (1, 3)}
+    for op, name in enumerate(LINEAR):
+        for tile, size in LINEAR[name].items():
+            assert linear_form(op, *size) == bf16[tile.split(",")[0]], (name, tile)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile,groups,slots,H", FLOAT_MAPS)
+def test_input_gradient_of_float_maps(tile, groups, slots, H):
+    B, l_x, l_s, rv = FLOAT_MAPS[tile, groups, slots, H]
+    E = 64 * H
+    w_q, w_kv, dq = _rand(E + 7, (E, E), (E, 2 * E), (B, l_s, H, 64))
+    dk, dv, rounded = _partials(E + 8, B, l_x, H, rv)
     dx_q, dx = lss.lss_project_bwd(dq, dk, dv, w_q, w_kv, rv)
     assert _close(dx_q[0], dq[0].reshape(l_s, E).double() @ w_q.double().T, "f32")
     assert _close(dx[0, :rv], rounded[0] @ w_kv.double().T, "f32") and not dx[:, rv:].any()
