@@ -922,11 +922,8 @@ using ShapeS4 = GemmShape<64, 64, 32, 32, 4, 2>;        // two groups of four wa
 // 256 x 2048 -> 2048 9.7, 8.0, 13.2; dW of 512 x 512 from 1024 rows 7.6 and 5.6 in either (all three with the groups and slots there were before).
 using ShapeT4 = GemmShape<32, 64, 32, 32, 3, 4>;        // two wavefronts, four such groups
 using ShapeT8 = GemmShape<32, 32, 32, 32, 4, 4>;        // one wavefront, four such groups
-// ... as gemm_form() says for float operands: dW_kv of 512
-// columns from 3000 rows in 64 x 64 tiles 25.0 us in two groups and 23.6 in four, from 1000 12.5 and 13.5; of 256 columns from 2000 in 32 x 32
-// ones 13.1 in four and 11.9 in eight, from 300 7.8 and 8.5.  project_bwd of 300 rows and 2048 contraction indices 14.7 and 14.1 in 64 x 64 ones, 1280 9.2 and
-// 9.3 (four groups for all); of 120 rows and 2048 in 32 x 32 ones 8.2 and 7.5, of 556 and 1024 8.7 and 9.1.  32 x 64 ones with two slots and with three: 145 rows
-// and 3584 15.7 and 16.1, 96 and 4096 16.2 and 16.9, 337 and 1280 6.0 and 6.0.
+// ... as gemm_form() says for float operands.  project_bwd in 32 x 64 tiles with two slots and with three: 145 rows and contractions of 3584 15.7 and 16.1 us,
+// 96 and 4096 16.2 and 16.9, 337 and 1280 6.0 and 6.0.
 using ShapeS4F = GemmShape<64, 64, 32, 32, 2, 4>;
 using ShapeT4F = GemmShape<32, 64, 32, 32, 2, 4>;
 using ShapeT8F = GemmShape<32, 32, 32, 32, 2, 8>;

@@ -250,3 +250,26 @@ def test_input_gradient_of_float_maps(tile, groups, slots, H):
     dx_q, dx = lss.lss_project_bwd(dq, dk, dv, w_q, w_kv, rv)
     assert _close(dx_q[0], dq[0].reshape(l_s, E).double() @ w_q.double().T, "f32")
     assert _close(dx[0, :rv], rounded[0] @ w_kv.double().T, "f32") and not dx[:, rv:].any()
+
+
+# dW_kv by chunks of rows on either side of where more groups of wavefronts share a float contraction: (tile, rows_valid): H, groups, slots
+FLOAT_CHUNKS = {("64x64 by four", 832): (6, 2, 4), ("64x64 by four", 833): (6, 4, 2), ("32x32", 1024): (2, 4, 4), ("32x32", 1025): (2, 8, 2)}
+
+
+def test_float_chunks_take_their_groups_and_slots():
+    """(needs no GPU)"""
+    for (tile, rv), (H, groups, slots) in FLOAT_CHUNKS.items():
+        assert project_plan(2, 1, rv + 7, H, 64, 90, rv)[2:4] == (tile, 1) and project_form(2, 1, rv + 7, H, 64, 90, rv) == (groups, slots), (tile, rv)
+    # measured shorter with four groups, 15.2 us instead of 15.8
+    assert project_plan(2, 1, 1352, 6, 64, 90, 1352)[2:4] == ("64x64 by four", 1) and project_form(2, 1, 1352, 6, 64, 90, 1352) == (4, 2)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile,rv", FLOAT_CHUNKS)
+def test_weight_gradient_where_groups_change(tile, rv):
+    E = 64 * FLOAT_CHUNKS[tile, rv][0]
+    x, dq = _rand(rv + E, (1, rv + 7, E), (1, 90, E // 64, 64))
+    dk, dv, rounded = _partials(rv + E, 1, rv + 7, E // 64, rv)
+    dw_kv = lss.lss_project_bwd_weight(x, dq, dk, dv, rv - 90, rv)[1]
+    assert _close(dw_kv, x[0, :rv].double().T @ rounded[0], "f32")
+    assert torch.equal(dw_kv, lss.lss_project_bwd_weight(x, dq, dk, dv, rv - 90, rv)[1])
