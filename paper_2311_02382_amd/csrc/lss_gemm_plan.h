@@ -29,7 +29,7 @@ constexpr GemmTileCost kGemmTiles[TILE_COUNT] = {
 // What a kernel's contraction goes through: groups of wavefronts, and slots of the LDS ring of each (of the activations, where a 256 x 256 tile has fewer for
 // the weights).  `length`: of a map's contraction, or the rows of a chunk of a weight gradient.
 struct GemmForm { int groups, slots; };
-constexpr int kLongFloatS4 = 832, kLongFloatT8 = 1024;
+constexpr int kLongFloat = 832;
 // Float operands travel through registers a tile per group at a time: more slots gain them nothing, and their long contractions are better off with more groups.
 // project_bwd_weight with dW_kv in 64 x 64 tiles of two and of four groups, us: chunks of 367 rows 8.8 and 9.2, 584 12.2 and 12.8, 746 11.7 and 12.0, 905 13.0 and
 // 12.7, 1106 14.9 and 14.6, 1352 15.8 and 15.2, 1855 20.0 and 19.3, 2983 27.0 and 24.7; in 32 x 32 ones of four and of eight 346 6.9 and 7.1, 569 7.3 and 7.5, 850 8.6 and
@@ -37,9 +37,9 @@ constexpr int kLongFloatS4 = 832, kLongFloatT8 = 1024;
 // 15.1 and 12.2; in 64 x 64 ones 512 5.9 and 6.6, 1024 8.3 and 8.5, 1536 10.1 and 9.6, 2816 20.0 and 18.6 (four groups for all).
 constexpr GemmForm gemm_form(GemmTile t, bool weight_gradient, bool floats, int length)
 {
-    if (floats && t == TILE_S4 && (!weight_gradient || length > kLongFloatS4)) return {4, 2};
+    if (floats && t == TILE_S4 && (!weight_gradient || length > kLongFloat)) return {4, 2};
     if (floats && t == TILE_T4) return {4, 2};
-    if (floats && t == TILE_T8 && length > kLongFloatT8) return {8, 2};
+    if (floats && t == TILE_T8 && length > kLongFloat) return {8, 2};
     constexpr int slots[TILE_COUNT] = {3, 2, 2, 4, 4, 4, 3, 4};
     return {kGemmTiles[t].groups, slots[t]};
 }

@@ -984,9 +984,9 @@ constexpr bool tile_agrees()
 static_assert(tile_agrees<TILE_L>() && tile_agrees<TILE_M>() && tile_agrees<TILE_M2>() && tile_agrees<TILE_M8>() && tile_agrees<TILE_S>() &&
               tile_agrees<TILE_S4>() && tile_agrees<TILE_T4>() && tile_agrees<TILE_T8>(), "the plan's table is about other shapes");
 
-static_assert(is_form<ShapeS4F>(gemm_form(TILE_S4, false, true, kGemmK)) && is_form<ShapeS4>(gemm_form(TILE_S4, true, true, kLongFloatS4)) &&
-              is_form<ShapeS4F>(gemm_form(TILE_S4, true, true, kLongFloatS4 + 1)) && is_form<ShapeT4F>(gemm_form(TILE_T4, false, true, kGemmK)) &&
-              is_form<ShapeT8>(gemm_form(TILE_T8, false, true, kLongFloatT8)) && is_form<ShapeT8F>(gemm_form(TILE_T8, false, true, kLongFloatT8 + 1)), "");
+static_assert(is_form<ShapeS4F>(gemm_form(TILE_S4, false, true, kGemmK)) && is_form<ShapeS4>(gemm_form(TILE_S4, true, true, kLongFloat)) &&
+              is_form<ShapeS4F>(gemm_form(TILE_S4, true, true, kLongFloat + 1)) && is_form<ShapeT4F>(gemm_form(TILE_T4, false, true, kGemmK)) &&
+              is_form<ShapeT8>(gemm_form(TILE_T8, false, true, kLongFloat)) && is_form<ShapeT8F>(gemm_form(TILE_T8, false, true, kLongFloat + 1)), "");
 
 int proj_work(const ProjArgs &args, GemmWork (&work)[2])
 {

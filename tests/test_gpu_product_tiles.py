@@ -225,8 +225,8 @@ def test_input_gradient_of_long_float_contractions(tile):
 
 
 # Maps of float partials in the small tiles, whose groups and slots are not those of bf16 operands: (tile, groups, slots, H): B, l_x, l_s, rows_valid.  32 x 32 ones on
-# either side of a contraction of 1024.
-FLOAT_MAPS = {("32x64", 4, 2, 16): (1, 209, 40, 200), ("32x64", 4, 2, 32): (1, 79, 33, 70), ("32x32", 4, 4, 8): (1, 49, 33, 40), ("32x32", 8, 2, 10): (1, 49, 33, 40),
+# either side of where more groups share a contraction, 832.
+FLOAT_MAPS = {("32x64", 4, 2, 16): (1, 209, 40, 200), ("32x64", 4, 2, 32): (1, 79, 33, 70), ("32x32", 4, 4, 6): (1, 49, 33, 40), ("32x32", 8, 2, 8): (1, 49, 33, 40),
               ("64x64 by four", 4, 2, 32): (1, 209, 40, 200)}
 
 
@@ -253,7 +253,7 @@ def test_input_gradient_of_float_maps(tile, groups, slots, H):
 
 
 # dW_kv by chunks of rows on either side of where more groups of wavefronts share a float contraction: (tile, rows_valid): H, groups, slots
-FLOAT_CHUNKS = {("64x64 by four", 832): (6, 2, 4), ("64x64 by four", 833): (6, 4, 2), ("32x32", 1024): (2, 4, 4), ("32x32", 1025): (2, 8, 2)}
+FLOAT_CHUNKS = {("64x64 by four", 832): (6, 2, 4), ("64x64 by four", 833): (6, 4, 2), ("32x32", 832): (2, 4, 4), ("32x32", 833): (2, 8, 2)}
 
 
 def test_float_chunks_take_their_groups_and_slots():
