@@ -1,4 +1,6 @@
 """What assembly blocks ask of the code around them, which the compiler does not look into, in the code of every kernel (CPU)."""
+import re
+
 import pytest
 
 import _asm
@@ -55,3 +57,9 @@ def test_wide_tiles_accumulators_belong_to_matrix_instructions(code):
                 if before.startswith("v_mfma") and before.split()[0] != op:
                     assert not _asm.written(before) & acc, (name, before, waited, line)
     assert wide == 5
+
+
+def test_products_keep_their_registers(code):
+    # (the float weight gradient in wide tiles had one in scratch memory: 512 registers are all there are)
+    sizes = re.findall(r"\.amdhsa_kernel (\S+).*?\.amdhsa_private_segment_fixed_size (\d+)", code["lss_proj.hip"], re.S)
+    assert len(sizes) == len(_asm.kernels(code["lss_proj.hip"])) and not [name for name, size in sizes if size != "0"]
