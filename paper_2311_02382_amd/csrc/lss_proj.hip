@@ -379,24 +379,18 @@ __device__ __forceinline__ void gemm_clear(f32x4 (&acc)[S::MB][S::NB])
             for (int e = 0; e < 4; ++e) acc[mb][nb][e] = 0.f;
 }
 
-// The finished tile -> LDS, a pass of CPP columns at a time, from where every wavefront reads whole row
-// pieces: the 16-byte chunk c of row m sits at chunk position c ^ (m % chunks per row).
+// The finished tile -> LDS, from where every wavefront reads whole row pieces: the 16-byte chunk c of row m sits at chunk position c ^ (m % chunks per row).
 // Accumulator block (mb, nb), element v of a lane: row m = WM wm + 16 mb + lane % 16, column n = WN wn +
-// 16 nb + 4 (lane / 16) + v.  Rows >= rows_data are written as zeros.
-// (ZEROS: whether rows >= rows_data are.)
+// 16 nb + 4 (lane / 16) + v.  ZEROS: rows >= rows_data are written as zeros.
 template <typename S, bool OUT_F32, bool ZEROS>
 struct GemmStore {
-    static constexpr int EB = OUT_F32 ? 4 : 2, CW = 16 / EB;            // bytes per element, columns per chunk
-    static constexpr int PASSES = S::TM * S::TN * EB > S::LDS ? 2 : 1;
-    static constexpr int CPP = S::TN / PASSES, CPR = CPP / CW;          // columns and chunks per row of a pass
-    static_assert(CPP % S::WN == 0 && S::TM * CPP * EB <= S::LDS && S::NT % CPR == 0, "");
+    static constexpr int EB = OUT_F32 ? 4 : 2, CW = 16 / EB, CPR = S::TN / CW;      // bytes per element, columns per chunk, chunks per row
+    static_assert(S::TM * S::TN * EB <= S::LDS && S::NT % CPR == 0, "");
     static constexpr int ROWS_PER_IT = S::NT / CPR, ITS = (S::TM + ROWS_PER_IT - 1) / ROWS_PER_IT;
-    static __device__ __forceinline__ int offset(int m, int c) { return m * (CPP * EB) + ((c ^ (m & (CPR - 1))) * 16); }
-    static __device__ __forceinline__ void to_lds(char *smem, const f32x4 (&acc)[S::MB][S::NB], int pass, int wm, int wn, int lane,
-                                                  int rows_data)
+    static __device__ __forceinline__ int offset(int m, int c) { return m * (S::TN * EB) + ((c ^ (m & (CPR - 1))) * 16); }
+    static __device__ __forceinline__ void to_lds(char *smem, const f32x4 (&acc)[S::MB][S::NB], int wm, int wn, int lane, int rows_data)
     {
-        if (PASSES > 1 && wn * S::WN / CPP != pass) return;
-        const int c_first = wn * S::WN % CPP / CW;
+        const int c_first = wn * S::WN / CW;
 #pragma unroll
         for (int mb = 0; mb < S::MB; ++mb) {
             const int m = S::WM * wm + 16 * mb + (lane & 15), g = lane >> 4;
@@ -557,30 +551,27 @@ __device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
             });
         } else {
             using Store = GemmStore<S, OUT_F32, A_ANY>;
+            const int c = t % Store::CPR, col = c * Store::CW;
+            const int n = n0 + col;         // column of C; a chunk never straddles n_split
+            OutT *const dst = n < n_split ? c0 + n : c1 + (n - n_split);
+            constexpr int AHEAD = Store::ITS < 8 ? Store::ITS : 8;
+            bf16x8 uu[AHEAD];
+            auto begin = [&](int i0) __attribute__((always_inline)) {
+                if constexpr (EPI == EPI_GELU_BWD)
 #pragma unroll
-            for (int pass = 0; pass < Store::PASSES; ++pass) {
-                const int c = t % Store::CPR, col = pass * Store::CPP + c * Store::CW;
-                const int n = n0 + col;         // column of C; a chunk never straddles n_split
-                OutT *dst = n < n_split ? c0 + n : c1 + (n - n_split);
-                constexpr int AHEAD = Store::ITS < 8 ? Store::ITS : 8;
-                bf16x8 uu[AHEAD];
-                auto begin = [&](int i0) __attribute__((always_inline)) {
-                    if constexpr (EPI == EPI_GELU_BWD)
+                    for (int k = 0; k < AHEAD; ++k) uu[k] = fetch_u((i0 + k) * Store::ROWS_PER_IT + t / Store::CPR, n);
+            };
+            begin(0);
+            __syncthreads();        // every wavefront is done with what the LDS held
+            if (group == 0) Store::to_lds(smem, acc, wm, wn, t & 63, rows_data);
+            __syncthreads();
 #pragma unroll
-                        for (int k = 0; k < AHEAD; ++k) uu[k] = fetch_u((i0 + k) * Store::ROWS_PER_IT + t / Store::CPR, n);
-                };
-                begin(0);
-                __syncthreads();        // every wavefront is done with what the LDS held
-                if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, t & 63, rows_data);
-                __syncthreads();
-#pragma unroll
-                for (int i = 0; i < Store::ITS; ++i) {
-                    const int m = i * Store::ROWS_PER_IT + t / Store::CPR;
-                    if (i > 0 && i % AHEAD == 0) begin(i);
-                    f32x4 raw = {0.f, 0.f, 0.f, 0.f};
-                    if (m < S::TM) raw = *reinterpret_cast<const f32x4 *>(smem + Store::offset(m, c));
-                    if (col < cols_here && m < rows_here) put_chunk(dst + (int64_t)m * ldc, (int64_t)m * ldc + n, raw, uu[i % AHEAD]);
-                }
+            for (int i = 0; i < Store::ITS; ++i) {
+                const int m = i * Store::ROWS_PER_IT + t / Store::CPR;
+                if (i > 0 && i % AHEAD == 0) begin(i);
+                f32x4 raw = {0.f, 0.f, 0.f, 0.f};
+                if (m < S::TM) raw = *reinterpret_cast<const f32x4 *>(smem + Store::offset(m, c));
+                if (col < cols_here && m < rows_here) put_chunk(dst + (int64_t)m * ldc, (int64_t)m * ldc + n, raw, uu[i % AHEAD]);
             }
         }
     };
@@ -840,15 +831,13 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
         gemm_wide_loop<DC_F32 ? REG_W : REG_NONE, ATile::NI, WTile::NI, FCH>(acc, T, issue_a, issue_w, load_a, load_w, publish, fetch_w, stash);
     } else {
         char *const ring = smem + group * S::RING;
-        auto load = [&](int slot, int j, GemmFrags<S> &f) __attribute__((always_inline)) {
+        static_assert(S::MH == 1, "");
+        auto load = [&](int slot, int ks, GemmFrags<S> &f) __attribute__((always_inline)) {
             const char *at = ring + slot * S::SLOT, *wt = at + S::ABYTES;
-            const int ks = j / S::MH, first = j % S::MH * S::HB;
-            if (first == 0) {
 #pragma unroll
-                for (int nb = 0; nb < S::NB; ++nb) f.fw[ks & 1][nb] = WTile::load_frag(wt, ks, wt_off[nb]);
-            }
+            for (int nb = 0; nb < S::NB; ++nb) f.fw[ks & 1][nb] = WTile::load_frag(wt, ks, wt_off[nb]);
 #pragma unroll
-            for (int mb = 0; mb < S::HB; ++mb) f.fb[j & 1][mb] = ATile::load_frag(at, ks, at_off ^ ((first + mb) * 32));
+            for (int mb = 0; mb < S::HB; ++mb) f.fb[ks & 1][mb] = ATile::load_frag(at, ks, at_off ^ (mb * 32));
         };
         auto issue = [&](int t, int slot) {
             char *const dst = ring + slot * S::SLOT + wave * 1024;
@@ -885,19 +874,16 @@ __global__ __launch_bounds__(S::NT, S::WAVES_PER_SIMD) void wgrad_gemm_kernel(Wg
         });
     } else {
         using Store = GemmStore<S, true, false>;
+        __syncthreads();
+        if (group == 0) Store::to_lds(smem, acc, wm, wn, lane, S::TM);
+        __syncthreads();
+        const int c = tid % Store::CPR, col = c * Store::CW;
+        if (col < cols_n) {
 #pragma unroll
-        for (int pass = 0; pass < Store::PASSES; ++pass) {
-            __syncthreads();
-            if (group == 0) Store::to_lds(smem, acc, pass, wm, wn, lane, S::TM);
-            __syncthreads();
-            const int c = tid % Store::CPR, col = pass * Store::CPP + c * Store::CW;
-            if (col < cols_n) {
-#pragma unroll
-                for (int i = 0; i < Store::ITS; ++i) {
-                    const int m = i * Store::ROWS_PER_IT + tid / Store::CPR;
-                    if (m < cols_m)
-                        *reinterpret_cast<f32x4 *>(out + (int64_t)m * g.N + col) = *reinterpret_cast<const f32x4 *>(smem + Store::offset(m, c));
-                }
+            for (int i = 0; i < Store::ITS; ++i) {
+                const int m = i * Store::ROWS_PER_IT + tid / Store::CPR;
+                if (m < cols_m)
+                    *reinterpret_cast<f32x4 *>(out + (int64_t)m * g.N + col) = *reinterpret_cast<const f32x4 *>(smem + Store::offset(m, c));
             }
         }
     }
