@@ -16,6 +16,10 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 // wavefront reads the data).  Written as inline assembly on purpose: through the compiler builtin
 // every later LDS read that the compiler cannot prove disjoint would wait for the load at once,
 // which defeats loading a ring slot a whole loop iteration ahead.
+// M0 is not saved (two scalar instructions more per load): nothing but these assembly blocks uses it, which tests/test_generated_code.py looks at.  The compiler
+// warns of every copy that a reserved register stands among the clobbers.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <int BYTES>
 __device__ __forceinline__ void lds_dma(const void *g_uniform, uint32_t voff, const void *lds_uniform)
 {
@@ -156,6 +160,7 @@ struct DirectTile {
     // byte offset inside the tile of the 16-byte chunk c of row r
     static __device__ __forceinline__ int chunk_offset(int r, int c) { return r * (D * 2) + ((c ^ tile_swizzle<D>(r)) * 16); }
 };
+#pragma clang diagnostic pop
 
 // DS_READ_B64_TR_B16: within each group of 16 lanes, lane i receives element (i % 4) of the
 // 8-byte rows addressed by lanes (i / 4) + 4 * t, t = 0..3.  With lane s of a group addressing

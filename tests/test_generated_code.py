@@ -63,3 +63,16 @@ def test_products_keep_their_registers(code):
     # (the float weight gradient in wide tiles had one in scratch memory: 512 registers are all there are)
     sizes = re.findall(r"\.amdhsa_kernel (\S+).*?\.amdhsa_private_segment_fixed_size (\d+)", code["lss_proj.hip"], re.S)
     assert len(sizes) == len(_asm.kernels(code["lss_proj.hip"])) and not [name for name, size in sizes if size != "0"]
+
+
+def test_scalar_register_m0_belongs_to_assembly_blocks(code):
+    # The direct loads set it and do not restore it
+    seen = 0
+    for source, text in code.items():
+        inside = False
+        for line in text.splitlines():
+            inside = "#ASMSTART" in line or inside and "#ASMEND" not in line
+            if re.match(r"\t[a-z]", line) and re.search(r"\bm0\b", line):
+                seen += 1
+                assert inside, (source, line)
+    assert seen > 1000
