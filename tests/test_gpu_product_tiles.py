@@ -1,6 +1,7 @@
 """Every tile that a matrix product has a kernel for, in every product that takes it, against 64-bit products of the same operands.  The tile that a size
 takes is asked of the library (csrc/lss_plan.h), so that a change to the rule shows which sizes have left theirs.  Rows and columns end inside a
-tile wherever there is such a size; contractions are longer than what is on its way at once, and shared by groups of wavefronts unevenly."""
+tile wherever there is such a size.  Contractions longer than what is on its way at once, shared by groups of wavefronts unevenly, are those of the larger tiles
+everywhere, and of the 32-wide ones in ROUNDS below."""
 import pytest
 import torch
 
@@ -139,8 +140,9 @@ def test_projections_weight_gradient_of_float_partials(tile, chunks):
     assert torch.equal(dw_kv, lss.lss_project_bwd_weight(x, dq, dk, dv, rv - l_s, rv)[1])
 
 
-# The 256 x 256 tile's loop takes its last two contraction tiles by themselves and goes round three slots of one operand and two of the other: every
-# length modulo 6, last tiles of one, some and all rows; and the shortest contraction it meets (four tiles; eight of the floats).
+# The 256 x 256 tile's loop takes its last two contraction tiles by themselves and goes round three slots of one operand and two of the other: 9 to 13 contraction tiles of
+# bf16 and 7 to 9 of floats (chunks of them, the last one shorter), last tiles of one, some and all rows; and the maps' shortest (four tiles; eight of the floats).
+# FEW_TILES below has the others.
 SHORT = {"qkv": (1, 60001, 4, 100, 59998), "bwd": (1, 60001, 4, 100, 59998)}
 LENGTHS = (513, 575, 640, 641, 704, 768, 769, 832)
 FLOAT_LENGTHS = (1409, 1472, 1473, 1536, 1600, 1664, 1728)
@@ -273,3 +275,89 @@ def test_weight_gradient_where_groups_change(tile, rv):
     dw_kv = lss.lss_project_bwd_weight(x, dq, dk, dv, rv - 90, rv)[1]
     assert _close(dw_kv, x[0, :rv].double().T @ rounded[0], "f32")
     assert torch.equal(dw_kv, lss.lss_project_bwd_weight(x, dq, dk, dv, rv - 90, rv)[1])
+
+
+# Weight gradients in 256 x 256 tiles of few contraction tiles (two never enter the loop's body) and the lengths modulo 6 that LENGTHS leaves out, ragged rows and whole ones, tiles
+# that end outside the matrix: rows: contraction tiles.  Floats: rows_valid: B, H, contraction tiles, in one chunk.
+FEW_TILES = {100: 2, 128: 2, 190: 3, 250: 4, 300: 5, 896: 14}
+FEW_FLOAT_TILES = {66: (3, 24, 2), 128: (3, 24, 2), 129: (3, 24, 3), 213: (2, 24, 4), 276: (2, 24, 5), 384: (2, 24, 6), 591: (2, 24, 10)}
+
+
+def test_few_contraction_tiles_take_the_256x256_tile():
+    """(needs no GPU)"""
+    for rows, tiles in FEW_TILES.items():
+        assert linear_plan(2, rows, 1920, 8064) == ("256x256", 1) and -(-rows // 64) == tiles, rows
+    for rv, (B, H, tiles) in FEW_FLOAT_TILES.items():
+        assert project_plan(2, B, rv + 10, H, 64, 60, rv)[2:4] == ("256x256", 1) and -(-rv // 64) == tiles, rv
+    assert [project_plan(2, 3, rv + 10, 14, 64, 335, rv)[3] for rv in FLOAT_LENGTHS] == [3] * len(FLOAT_LENGTHS)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", FEW_TILES)
+def test_weight_gradient_of_few_contraction_tiles(rows):
+    a, dc = _rand(rows + 1, (rows, 1920), (rows, 8064))
+    assert _close(lss.lss_linear_bwd_weight(a, dc), a.double().T @ dc.double(), "f32")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rv", FEW_FLOAT_TILES)
+def test_float_weight_gradient_of_few_contraction_tiles(rv):
+    B, H, _ = FEW_FLOAT_TILES[rv]
+    x, dq = _rand(rv + 1, (B, rv + 10, 64 * H), (B, 60, H, 64))
+    dk, dv, rounded = _partials(rv + 1, B, rv + 10, H, rv)
+    dw_kv = lss.lss_project_bwd_weight(x, dq, dk, dv, rv - 60, rv)[1]
+    assert _close(dw_kv, sum(x[b, :rv].double().T @ rounded[b] for b in range(B)), "f32")
+
+
+# 32-wide tiles whose groups of wavefronts go round their rings, unevenly: (product, tile): rows, K, N, or B, l_x, H, l_s, rows_valid
+ROUNDS = {("fwd", "32x64"): (45, 896, 2176), ("fwd", "32x32"): (45, 1152, 384), ("bwd_input", "32x64"): (58, 2176, 896), ("bwd_input", "32x32"): (45, 384, 1152),
+          ("weight", "32x64"): (780, 384, 640), ("weight", "32x32"): (1065, 256, 384), ("qkv", "32x64"): (1, 90, 14, 40, 85), ("qkv", "32x32"): (1, 90, 18, 20, 85),
+          ("bwd", "32x64"): (1, 409, 6, 33, 400), ("bwd", "32x32"): (1, 99, 10, 33, 90), ("partials", "32x32"): (1, 1130, 2, 90, 1127)}
+
+
+def test_rounds_are_longer_than_what_is_on_its_way():
+    """(needs no GPU)"""
+    for (name, tile), size in ROUNDS.items():
+        if len(size) == 3:
+            op = ("fwd", "bwd_input", "weight").index(name)
+            rows, K, N = size
+            got, (groups, slots), length = linear_plan(op, *size)[0], linear_form(op, *size), (K, N, rows)[op]
+            assert linear_plan(op, *size)[1] == 1
+        else:
+            op = ("qkv", "bwd", "partials").index(name)
+            B, l_x, H, l_s, rv = size
+            plan = project_plan(op, B, l_x, H, 64, l_s, rv)
+            got, (groups, slots), length = plan[2] if op == 2 else plan, project_form(op, B, l_x, H, 64, l_s, rv), (64 * H, 128 * H, rv)[op]
+        tiles = -(-length // 64)
+        assert got == tile and tiles > groups * slots and (tiles % groups or name == "bwd"), (name, tile)       # (project_bwd's come in fours)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,tile", ROUNDS)
+def test_rounds(name, tile):
+    size = ROUNDS[name, tile]
+    if len(size) == 3:
+        rows, K, N = size
+        a, w, dc = _rand(rows + K + 3, (rows, K), (K, N), (rows, N))
+        if name == "fwd":
+            assert _close(lss.lss_linear_fwd(a, w), a.double() @ w.double(), "bf16")
+        elif name == "bwd_input":
+            assert _close(lss.lss_linear_bwd_input(dc, w), dc.double() @ w.double().T, "bf16")
+        else:
+            assert _close(lss.lss_linear_bwd_weight(a, dc), a.double().T @ dc.double(), "f32")
+        return
+    B, l_x, H, l_s, rv = size
+    E, s0 = 64 * H, rv - l_s
+    x, w_q, w_kv, dq = _rand(l_x + H, (B, l_x, E), (E, E), (E, 2 * E), (B, l_s, H, 64))
+    dk, dv, rounded = _partials(l_x + H, B, l_x, H, rv)
+    if name == "qkv":
+        q, k, v = lss.lss_project_qkv(x, w_q, w_kv, s0, l_s, H)
+        kv = x[0].double() @ w_kv.double()
+        assert _close(q.view(l_s, E), x[0, s0:rv].double() @ w_q.double(), "bf16")
+        assert _close(k.view(l_x, E), kv[:, :E], "bf16") and _close(v.view(l_x, E), kv[:, E:], "bf16")
+    elif name == "bwd":
+        dx_q, dx = lss.lss_project_bwd(dq, dk, dv, w_q, w_kv, rv)
+        assert _close(dx_q[0], dq[0].reshape(l_s, E).double() @ w_q.double().T, "f32")
+        assert _close(dx[0, :rv], rounded[0] @ w_kv.double().T, "f32") and not dx[:, rv:].any()
+    else:
+        assert _close(lss.lss_project_bwd_weight(x, dq, dk, dv, s0, rv)[1], x[0, :rv].double().T @ rounded[0], "f32")
