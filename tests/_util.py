@@ -89,7 +89,7 @@ def bwd_plan(B, l_x, H, d, s0, l_s, causal, drop=False, elem_bytes=2, over_out=F
 
 
 # Tiles of the products (GemmTile of csrc/lss_gemm_plan.h)
-TILES = ("256x256", "128x128", "128x128 by two", "128x128 of eight", "64x64", "64x64 by four", "32x64", "32x32")
+TILES = ("256x256", "128x128", "128x128 by two", "128x128 of eight", "64x64", "64x64 in groups", "32x64", "32x32")
 
 
 def _linear_plan(op, rows, K, N):

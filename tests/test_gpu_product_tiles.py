@@ -9,28 +9,28 @@ from paper_2311_02382_amd import lss
 from _util import TOL, linear_form, linear_plan, project_form, project_plan
 
 LINEAR = {  # tile: rows, K, N  (contraction over K)
-    "fwd": {"32x32": (45, 1152, 384), "32x64": (58, 512, 4480), "64x64": (70, 512, 5504), "64x64 by four": (67, 768, 6016),
+    "fwd": {"32x32": (45, 1152, 384), "32x64": (58, 512, 4480), "64x64": (70, 512, 5504), "64x64 in groups": (67, 768, 6016),
             "128x128 of eight": (1925, 640, 1920), "128x128": (658, 512, 5760), "256x256": (2224, 512, 5504)},
     # (contraction over N)
-    "bwd_input": {"32x32": (45, 384, 1152), "32x64": (58, 4224, 512), "64x64": (66, 5760, 512), "64x64 by four": (70, 5504, 768),
+    "bwd_input": {"32x32": (45, 384, 1152), "32x64": (58, 4224, 512), "64x64": (66, 5760, 512), "64x64 in groups": (70, 5504, 768),
                   "128x128 of eight": (1925, 1920, 640), "128x128": (772, 4736, 512), "256x256": (2698, 4480, 512)},
 }
 LINEAR["fwd"]["128x128 of eight, whole rows"], LINEAR["bwd_input"]["128x128 of eight, whole rows"] = (2048, 512, 2048), (2048, 2048, 512)
 WEIGHT = {  # (tile, rows in chunks): rows, K, N  (contraction over the rows)
     ("32x32", False): (450, 128, 256), ("32x32", True): (2567, 128, 128), ("32x64", False): (450, 384, 384), ("32x64", True): (6161, 128, 128),
-    ("64x64", False): (515, 640, 1664), ("64x64", True): (2571, 128, 1152), ("64x64 by four", False): (517, 384, 1408),
-    ("64x64 by four", True): (3077, 384, 384), ("128x128 by two", False): (533, 384, 5504), ("128x128 by two", True): (6277, 128, 2176),
+    ("64x64", False): (515, 640, 1664), ("64x64", True): (2571, 128, 1152), ("64x64 in groups", False): (517, 384, 1408),
+    ("64x64 in groups", True): (3077, 384, 384), ("128x128 by two", False): (533, 384, 5504), ("128x128 by two", True): (6277, 128, 2176),
     ("128x128", False): (517, 4736, 896), ("128x128", True): (3411, 384, 3712), ("256x256", False): (515, 1664, 5248), ("256x256", True): (2507, 4736, 896),
 }
 PROJECT = {  # B, l_x, H, l_s, rows_valid
-    "qkv": {"32x32": (1, 125, 6, 49, 115), "32x64": (1, 135, 4, 75, 81), "64x64": (2, 342, 4, 323, 338), "64x64 by four": (1, 228, 12, 187, 195),
+    "qkv": {"32x32": (1, 125, 6, 49, 115), "32x64": (1, 135, 4, 75, 81), "64x64": (2, 342, 4, 323, 338), "64x64 in groups": (1, 228, 12, 187, 195),
             "128x128 of eight": (2, 1429, 4, 1244, 1322), "128x128": (3, 2001, 4, 1368, 1422), "256x256": (3, 7527, 4, 1421, 5412)},
-    "bwd": {"32x32": (1, 135, 4, 75, 81), "32x64": (2, 142, 4, 108, 132), "64x64": (3, 376, 4, 329, 373), "64x64 by four": (2, 765, 4, 299, 747),
+    "bwd": {"32x32": (1, 135, 4, 75, 81), "32x64": (2, 142, 4, 108, 132), "64x64": (3, 376, 4, 329, 373), "64x64 in groups": (2, 765, 4, 299, 747),
             "128x128 by two": (3, 1569, 4, 1305, 1552), "128x128": (3, 2341, 6, 1415, 2279), "256x256": (3, 7967, 6, 1476, 7384)},
 }
 PARTIALS = {  # (tile of dW_kv, rows in chunks): B, l_x, H, l_s, rows_valid
     ("32x32", False): (1, 206, 4, 100, 204), ("64x64", False): (1, 135, 4, 75, 81), ("64x64", True): (3, 535, 4, 286, 531),
-    ("64x64 by four", False): (2, 267, 4, 148, 261), ("64x64 by four", True): (2, 519, 4, 429, 514), ("128x128 by two", False): (2, 269, 12, 163, 266),
+    ("64x64 in groups", False): (2, 267, 4, 148, 261), ("64x64 in groups", True): (2, 519, 4, 429, 514), ("128x128 by two", False): (2, 269, 12, 163, 266),
     ("128x128 by two", True): (3, 971, 8, 873, 971), ("128x128", False): (2, 135, 12, 43, 76), ("128x128", True): (2, 1047, 12, 413, 1040),
     ("256x256", True): (3, 1448, 14, 335, 1426),
 }
@@ -189,10 +189,10 @@ def test_projections_of_the_shortest_contractions_of_the_loop():
     assert _close(dx[0, :rv], rounded[0] @ w_kv.double().T, "f32") and not dx[:, rv:].any()
 
 
-LONG = {"64x64 by four": (1, 1709, 6, 1700), "32x32": (1, 1130, 2, 1127)}      # B, l_x, H, rows_valid: float chunks of more than 1536 and 1024 rows
+LONG = {"64x64 in groups": (1, 1709, 6, 1700), "32x32": (1, 1130, 2, 1127)}      # B, l_x, H, rows_valid: float chunks of more than 1536 and 1024 rows
 
 
-LONG_MAPS = {"64x64 by four": (1, 1110, 16, 284, 344), "32x32": (1, 300, 16, 60, 120)}       # B, l_x, H, l_s, rows_valid: float contractions of 2048
+LONG_MAPS = {"64x64 in groups": (1, 1110, 16, 284, 344), "32x32": (1, 300, 16, 60, 120)}       # B, l_x, H, l_s, rows_valid: float contractions of 2048
 
 
 def test_long_float_contractions_take_their_tiles():
@@ -229,14 +229,14 @@ def test_input_gradient_of_long_float_contractions(tile):
 # Maps of float partials in the small tiles, whose groups and slots are not those of bf16 operands: (tile, groups, slots, H): B, l_x, l_s, rows_valid.  32 x 32 ones on
 # either side of where more groups share a contraction, 832.
 FLOAT_MAPS = {("32x64", 4, 2, 16): (1, 209, 40, 200), ("32x64", 4, 2, 32): (1, 79, 33, 70), ("32x32", 4, 4, 6): (1, 49, 33, 40), ("32x32", 8, 2, 8): (1, 49, 33, 40),
-              ("64x64 by four", 4, 2, 32): (1, 209, 40, 200)}
+              ("64x64 in groups", 4, 2, 32): (1, 209, 40, 200)}
 
 
 def test_float_maps_take_their_groups_and_slots():
     """(needs no GPU)"""
     for (tile, groups, slots, H), (B, l_x, l_s, rv) in FLOAT_MAPS.items():
         assert (project_plan(1, B, l_x, H, 64, l_s, rv), project_form(1, B, l_x, H, 64, l_s, rv)) == (tile, (groups, slots)), (tile, H)
-    bf16 = {"32x32": (4, 4), "32x64": (4, 3), "64x64": (1, 4), "64x64 by four": (2, 4), "128x128 of eight": (1, 4), "128x128": (1, 2), "256x256": (1, 3)}
+    bf16 = {"32x32": (4, 4), "32x64": (4, 3), "64x64": (1, 4), "64x64 in groups": (2, 4), "128x128 of eight": (1, 4), "128x128": (1, 2), "256x256": (1, 3)}
     for op, name in enumerate(LINEAR):
         for tile, size in LINEAR[name].items():
             assert linear_form(op, *size) == bf16[tile.split(",")[0]], (name, tile)
@@ -255,7 +255,7 @@ def test_input_gradient_of_float_maps(tile, groups, slots, H):
 
 
 # dW_kv by chunks of rows on either side of where more groups of wavefronts share a float contraction: (tile, rows_valid): H, groups, slots
-FLOAT_CHUNKS = {("64x64 by four", 832): (6, 2, 4), ("64x64 by four", 833): (6, 4, 2), ("32x32", 832): (2, 4, 4), ("32x32", 833): (2, 8, 2)}
+FLOAT_CHUNKS = {("64x64 in groups", 832): (6, 2, 4), ("64x64 in groups", 833): (6, 4, 2), ("32x32", 832): (2, 4, 4), ("32x32", 833): (2, 8, 2)}
 
 
 def test_float_chunks_take_their_groups_and_slots():
@@ -263,7 +263,7 @@ def test_float_chunks_take_their_groups_and_slots():
     for (tile, rv), (H, groups, slots) in FLOAT_CHUNKS.items():
         assert project_plan(2, 1, rv + 7, H, 64, 90, rv)[2:4] == (tile, 1) and project_form(2, 1, rv + 7, H, 64, 90, rv) == (groups, slots), (tile, rv)
     # measured shorter with four groups, 15.2 us instead of 15.8
-    assert project_plan(2, 1, 1352, 6, 64, 90, 1352)[2:4] == ("64x64 by four", 1) and project_form(2, 1, 1352, 6, 64, 90, 1352) == (4, 2)
+    assert project_plan(2, 1, 1352, 6, 64, 90, 1352)[2:4] == ("64x64 in groups", 1) and project_form(2, 1, 1352, 6, 64, 90, 1352) == (4, 2)
 
 
 @pytest.mark.gpu

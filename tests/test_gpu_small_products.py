@@ -66,7 +66,7 @@ def test_projections_in_small_tiles(B, l_x, H, s0, l_s):
 
 @pytest.mark.parametrize("skip_tail", [False, True])
 @pytest.mark.parametrize("tile,B,l_x,H,l_s,rows_valid", [
-    ("32x32", 1, 340, 2, 22, 24), ("32x32", 3, 700, 2, 32, 32), ("32x64", 1, 1280, 2, 89, 931), ("64x64 by four", 1, 612, 14, 14, 292),
+    ("32x32", 1, 340, 2, 22, 24), ("32x32", 3, 700, 2, 32, 32), ("32x64", 1, 1280, 2, 89, 931), ("64x64 in groups", 1, 612, 14, 14, 292),
     ("64x64", 2, 2276, 2, 98, 1946), ("128x128 by two", 1, 2303, 16, 88, 1988), ("128x128", 2, 2449, 16, 117, 2124), ("256x256", 1, 17000, 8, 200, 16500),
 ])
 def test_rows_without_data_are_cleared(tile, B, l_x, H, l_s, rows_valid, skip_tail):
