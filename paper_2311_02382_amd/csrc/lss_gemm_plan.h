@@ -16,12 +16,14 @@ enum GemmTile { TILE_L, TILE_M, TILE_M2, TILE_M8, TILE_S, TILE_S4, TILE_T4, TILE
 struct GemmTileCost { int tm, tn, groups, per_cu; double fixed, per_tile[2]; };
 // The figures are fitted to linear_fwd and linear_bwd_input at 230 .. 98304 rows and
 // 512 .. 8192 columns either way (20 launches in a graph each), with the loop of 32 x 32 x 16 instructions that there was; those of M8, T4 and T8 came
-// later, fitted to linear_fwd, bwd_input and bwd_weight at 58 .. 2048 rows and 256 .. 7680 columns.  With the present loop, behind a launch that writes
-// their operands, 5747 drawn linear maps in every tile: the choice costs 0.5 and 0.8 % over the best one on average (7.2 and 9.5 % without the last
-// three), 0.8 % over 3744 weight gradients, 1.9 % in project_bwd, 2.4 % in the weight gradients of its float partials.  Large tiles move the fewest bytes per flop
-// but a launch of few of them leaves compute units idle (2048 x 2048 -> 512: 16 workgroups of 256 x 256, 46 us;
-// 256 of 64 x 64, 12 us with the former loop), and where even 64 x 64 tiles leave one wavefront per SIMD the chain of contraction
-// tiles is what takes the time, which groups of wavefronts share (S4: two, four when the figures were fitted).
+// later, fitted to linear_fwd, bwd_input and bwd_weight at 58 .. 2048 rows and 256 .. 7680 columns.  L has been 10 % faster since, S4, T4 and T8 with other groups and slots
+// 10 to 20 %, and times beside the rules below that name these tiles are of the kernels before that; GeLU behind a product is in no figure.  What that costs,
+// 300 drawn feed-forward units and 240 projections, each product in every tile in a graph, behind a kernel that writes its operand, over the best tile: linear_fwd 1.7 % on average
+// (at worst 28, long contractions of 4000 to 8000 rows in 128 x 128 tiles: 7697 x 5120 -> 1280 118.7 us, in 256 x 256 ones 92.4), bwd_input 2.4 (36, likewise), with GeLU 0.9
+// and 1.0, project_qkv 0.8, bwd_weight 0.7, project_bwd 1.5, its float weight gradient 2.5.  Large tiles move the fewest bytes per flop
+// but a launch of few of them leaves compute units idle (2048 x 2048 -> 512: 16 workgroups of 256 x 256, 44 us;
+// 256 of 64 x 64, 14), and where even 64 x 64 tiles leave one wavefront per SIMD the chain of contraction
+// tiles is what takes the time, which groups of wavefronts share.
 constexpr GemmTileCost kGemmTiles[TILE_COUNT] = {
     {256, 256, 1, 1, 6.5, {1.40, 1.70}}, {128, 128, 1, 2, 2.8, {0.62, 1.00}}, {128, 128, 2, 1, 3.0, {0.50, 0.58}}, {128, 128, 1, 1, 2.5, {0.51, 0.585}},
     {64, 64, 1, 2, 2.5, {0.30, 0.40}}, {64, 64, 2, 1, 3.3, {0.165, 0.22}}, {32, 64, 4, 1, 3.0, {0.117, 0.165}}, {32, 32, 4, 1, 3.2, {0.069, 0.107}}};
@@ -129,10 +131,10 @@ inline int gemm_zero_tiles(int rows, int rows_ok, bool skip_tail, int tm, int tn
     return left > 0 ? (int)((left + gemm_zero_rows(tm, tn) - 1) / gemm_zero_rows(tm, tn)) : 0;
 }
 
-// Whether a launch may take tiles `t`.  32-wide ones only where one round of workgroups takes them all (of 4000 drawn linear maps that need more none is
-// faster in them, which take 1.4 times as long at two rounds: the weights come once more from the last-level cache, which the estimate does not know;
-// 644 x 6144 -> 1536, 504 workgroups, 49.1 us, in 64 x 64 tiles 41.1; counted as the launch's estimate counts them, per XCD unless A is float:
-// project_bwd's 252 for 282 x 2304 floats -> 1152 and 152 x 1152 -> 1152 16.2 us, in 64 x 64 tiles 18.4), and never with results past the caches,
+// Whether a launch may take tiles `t`.  32-wide ones only where one round of workgroups takes them all (with the kernels of two slots none of 4000 drawn linear maps that
+// need more was faster in them: the weights come once more from the last-level cache, which the estimate does not know; with the present ones
+// 644 x 6144 -> 1536, 504 workgroups, takes 40.4 us, 40.1 in 64 x 64 tiles, 581 x 6656 -> 1664 36.6 and 42.5; counted as the launch's estimate counts them, per XCD unless A is float:
+// project_bwd's 252 for 282 x 2304 floats -> 1152 and 152 x 1152 -> 1152 13.8 us, in 64 x 64 tiles 16.3), and never with results past the caches,
 // without which their kernel is built
 inline bool gemm_takes(GemmTile t, const GemmWork *work, int n, bool a_any, bool streams)
 {

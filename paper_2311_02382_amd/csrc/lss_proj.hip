@@ -10,12 +10,13 @@
 // matrix instruction and the activations its B operand.  Each wavefront owns a WM x WN part.  The
 // contraction runs in tiles of 64 through a ring of STAGES LDS slots that are filled global -> LDS
 // directly, one barrier per tile.  The finished tile goes through LDS once more so that it is written to
-// memory as whole rows.  The tile is chosen per launch (pick_gemm_tile): 2048 x 512 -> 2048 takes 20.4 us in
-// 256 x 256 tiles and 14.0 as chosen, 2048 x 2048 -> 512 46.6 and 13.7 (one after the other, an event after each).
+// memory as whole rows.  The tile is chosen per launch (pick_gemm_tile): 2048 x 512 -> 2048 takes 17.8 us in
+// 256 x 256 tiles and 9.8 as chosen, 2048 x 2048 -> 512 44.1 and 14.2 (in a graph, behind a kernel that writes their operand).
 // Matrix instructions of 16 x 16 x 32, not 32 x 32 x 16: loops on Gaussian operands (lss_microbench, section 7) reach 1700 TFLOP/s
 // with the former and 1630 with the latter in registers, 1500 and 1445 with an LDS read per 65,536 flop.  16384 x 4096 -> 1024:
-// 128 -> 116 us (1185 TFLOP/s), 16384 x 1024 -> 4096: 146 -> 136, the contraction of 98304 x 2048 floats 581 -> 532; weight gradients of
-// 16384 rows 148 -> 138.  Launches of 10 to 25 us gain 1 % and weight gradients among them lose up to 4 %.
+// 128 -> 116 us, 16384 x 1024 -> 4096: 146 -> 136, the contraction of 98304 x 2048 floats 581 -> 532; weight gradients of
+// 16384 rows 148 -> 138, all of these with 256 x 256 tiles as eight wavefronts held them (gemm_wide_loop has what they take now).  Launches of 10 to 25 us gain
+// 1 % and weight gradients among them lose up to 4 %.
 //   W_TR   weights stored [k][n] (forward: W as given).  Their fragments come from the LDS tile
 //          by transposing reads; otherwise the weights are stored [n][k] (backward: W as given
 //          IS W'^T) and are read plainly.
@@ -243,8 +244,9 @@ __device__ __forceinline__ void gemm_loop(f32x4 (&acc)[S::MB][S::NB], int T, int
 // The matrix instructions are assembly, with accumulators in the accumulation half of the registers: left to itself the compiler rotates the accumulators through
 // the register file, 132 copies per 128 matrix instructions.  An accumulator comes up again 64 instructions later; the wait states before other instructions may read
 // one stand at the end.
-// 16384 x 4096 -> 1024 102 -> 94 us, its input gradient 110 -> 95 (1444 TFLOP/s), 8192 x 8192 -> 8192 777 -> 710 (1548 TFLOP/s), against eight wavefronts
-// of 128 x 64 whose loads started all at once behind one barrier per tile, two slots for either operand.
+// Behind a copy that writes the operand, against eight wavefronts of 128 x 64 whose loads started all at once behind one barrier per tile, two slots for either
+// operand: 16384 x 4096 -> 1024 104 -> 95 us, 16384 x 1024 -> 4096 125 -> 111, their input gradients 104 -> 94 and 120 -> 106, 8192 x 8192 -> 8192 797 -> 720
+// (1530 TFLOP/s), its gradients 790 -> 709 and 849 -> 773; projections of 4 x 24576 rows 435 -> 370.
 enum WideReg { REG_NONE, REG_A, REG_W };
 struct WideFrags { Frag<bf16_t> a[GemmWide::MB], w[GemmWide::NB]; };
 template <WideReg REG, int A_NI, int W_NI, int CHUNKS, typename IssueA, typename IssueW, typename LoadA, typename LoadW, typename Publish, typename Fetch,
@@ -533,7 +535,7 @@ __device__ __forceinline__ void proj_gemm_body(const ProjArgs &args)
         }
     };
     // U of a chunk, read ahead of the results' way through LDS.  (Behind it, chunk by chunk, a wavefront waited 1.3 us for each: input
-    // gradient with GeLU' of 2048 x 512 -> 2048 11.4 -> 11.1 us, its operands in the caches.)
+    // gradient with GeLU' of 6400 x 896 -> 3584 in 128 x 128 tiles 62.4 -> 56.6 us, 12000 x 1280 -> 5120 in 256 x 256 ones 179 -> 173, 2048 x 512 -> 2048 13.6 -> 13.0.)
     auto fetch_u = [&](int m, int n) __attribute__((always_inline)) {
         return *reinterpret_cast<const bf16x8 *>(gelu_u + (int64_t)min(m, rows_here - 1) * ldc + min(n, n0 + cols_here - 8));
     };
@@ -904,8 +906,8 @@ using ShapeS = GemmShape<64, 64, 32, 32, 4>;
 // 70.5), 500 x 1024 75.4 -> 68.4 in 32 x 64 ones (two groups with five 69.8), 232 x 1024 58.3 -> 53.3 in 32 x 32 ones (two groups with eight 56.0).
 using ShapeS4 = GemmShape<64, 64, 32, 32, 4, 2>;        // two groups of four wavefronts
 // Where 64 x 64 tiles leave most compute units without one, what a launch waits for is a workgroup's own operand bytes, of which a compute unit
-// gets 40 to 60 per cycle: smaller tiles spread them, although there are more of them.  58 x 4096 -> 1024: S4 14.7 us, T4 11.2, T8 8.6;
-// 256 x 2048 -> 2048 9.7, 8.0, 13.2; dW of 512 x 512 from 1024 rows 7.6 and 5.6 in either (all three with the groups and slots there were before).
+// gets 40 to 60 per cycle: smaller tiles spread them, although there are more of them.  58 x 4096 -> 1024: S4 16.0 us, T4 11.2, T8 9.4;
+// 256 x 2048 -> 2048 10.8, 8.4, 12.8; dW of 512 x 512 from 1024 rows 6.1, 5.2, 4.9.
 using ShapeT4 = GemmShape<32, 64, 32, 32, 3, 4>;        // two wavefronts, four such groups
 using ShapeT8 = GemmShape<32, 32, 32, 32, 4, 4>;        // one wavefront, four such groups
 // ... as gemm_form() says for float operands.  project_bwd in 32 x 64 tiles with two slots and with three: 145 rows and contractions of 3584 15.7 and 16.1 us,
